@@ -715,256 +715,6 @@ __global__ void __launch_bounds__(256) k_cell_grads(
 }
 
 // ------------------------------------------------------------------------------------------
-// Component 2 of the per-block cell gradients: every query of cluster i in a later block that retrieved
-// cluster j but not block a adds  g_k += dl q~,  g_v += p dO,  g_c += dl (1 - q~.kbar) - p dO.vbar  to the
-// cell (a, i, j) that k_cell_grads wrote.  One block of 256 threads per (head, query cluster i): it takes the
-// cluster's queries (bucketed order, blocks >= 1) a chunk at a time, stages their Q and dO rows, LSE and delta
-// in LDS once, lists the (query, slot) entries by chain j with a counting sort over all Ck chains, and gives
-// each non-empty chain to a wave.  About one chain in ten has entries, and those that do have many.  For a
-// chain, the 8-lane group g takes key block a = g, so that the loads of all its blocks are one round trip; a
-// lane holds D/8 elements of a row (d = 32 x + 4 l8 + t).  The counting sort places entries in arrival order;
-// the wave that owns a chain then orders them by query, so every sum has a fixed order.  One owner per cell
-// (chain j -> wave (j / 64) % 4, block a -> group): no atomics on floats.
-// ------------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ void __launch_bounds__(256) k_chain_grads(
-    const T* __restrict__ Q, const T* __restrict__ dO, const float* __restrict__ qc, const float* __restrict__ s_mu,
-    const float* __restrict__ s_k, const T* __restrict__ s_v, const int32_t* __restrict__ perm_q,
-    const int32_t* __restrict__ off_q, const float* __restrict__ LSE, const float* __restrict__ delta,
-    const int32_t* __restrict__ slotinfo, float* __restrict__ G_c, T* __restrict__ G_k, T* __restrict__ G_v, int h0,
-    int N, int nb, int Bs, int Cq, int Ck, int r, float scale) {
-  constexpr int NV = D / 32;
-  constexpr int POOL = 1024;                                   // entries per chunk
-  constexpr int CHB = 32768 / (2 * D * (int)sizeof(T));        // queries whose rows fit 32 KB
-  constexpr int CHMAX = CHB < 128 ? CHB : 128;                 // at most two entries of a chain per lane
-  using F4 = Frag<T, 4>;
-  __shared__ int2 pool[POOL];                                  // x = query of the chunk, y = its block << 16 | retrieved blocks
-  __shared__ __attribute__((aligned(16))) T qS[CHMAX][D];
-  __shared__ __attribute__((aligned(16))) T gS[CHMAX][D];
-  __shared__ float2 ldS[CHMAX];                                // (LSE, delta)
-  __shared__ int nS[CHMAX];
-  __shared__ int bins[kMaxCk + 1];
-  __shared__ int wsum[4];
-  __shared__ int cum[18];                                      // cum[b] = queries of cluster i in blocks 1 .. b-1
-  const int hl = blockIdx.y, hq = h0 + hl, i = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, s8 = lane / 8, l8 = lane % 8;
-  const int NBm = nb - 1;
-  const int32_t* oq = off_q + (size_t)hq * ((size_t)nb * Cq + 1);
-  const int CH = POOL / r < CHMAX ? POOL / r : CHMAX;          // queries per chunk
-  if (tid == 0) {
-    int run = 0;
-    cum[0] = 0;
-    cum[1] = 0;
-    for (int b = 1; b < nb; ++b) {
-      run += oq[b * Cq + i + 1] - oq[b * Cq + i];
-      cum[b + 1] = run;
-    }
-  }
-  __syncthreads();
-  const int Tq = cum[nb];
-  float qcv[NV][4];
-#pragma unroll
-  for (int x = 0; x < NV; ++x) {
-    float4 c4 = *reinterpret_cast<const float4*>(qc + ((size_t)hq * Cq + i) * D + 32 * x + 4 * l8);
-    qcv[x][0] = c4.x; qcv[x][1] = c4.y; qcv[x][2] = c4.z; qcv[x][3] = c4.w;
-  }
-  for (int c0 = 0; c0 < Tq; c0 += CH) {
-    const int nq = Tq - c0 < CH ? Tq - c0 : CH;
-    __syncthreads();  // the previous chunk is consumed
-    for (int t = tid; t <= Ck; t += 256) bins[t] = 0;
-    // this thread's query: position, block, slots
-    int mybq = 0;
-    int info[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) info[t] = -1;
-    const int32_t* si = slotinfo;
-    if (tid < nq) {
-      const int idx = c0 + tid;
-      int b = 1;
-      while (idx >= cum[b + 1]) ++b;
-      const int pq = oq[b * Cq + i] + idx - cum[b];
-      const int n = perm_q[(size_t)hq * N + pq];
-      mybq = b;
-      si = slotinfo + ((size_t)hq * N + pq) * r;
-#pragma unroll
-      for (int t = 0; t < 8; ++t)
-        if (t < r) info[t] = si[t];
-      nS[tid] = n;
-      ldS[tid] = make_float2(LSE[(size_t)hq * N + n], delta[(size_t)hq * N + n]);
-    }
-    __syncthreads();
-    if (tid < nq) {
-      for (int t = 0; t < r; ++t) {
-        const int x = t < 8 ? info[t] : si[t];
-        if (x >= 0) atomicAdd(&bins[x & 0xffff], 1);
-      }
-    }
-    {
-      constexpr int CPR = D * (int)sizeof(T) / 16;
-      for (int idx = tid; idx < nq * CPR; idx += 256) {
-        const int e = idx / CPR, cc = idx % CPR;
-        const size_t qn = (size_t)hq * N + nS[e];
-        reinterpret_cast<uint4*>(&qS[e][0])[cc] = reinterpret_cast<const uint4*>(Q + qn * D)[cc];
-        reinterpret_cast<uint4*>(&gS[e][0])[cc] = reinterpret_cast<const uint4*>(dO + qn * D)[cc];
-      }
-    }
-    __syncthreads();
-    // exclusive scan of the chain counts: bins[j] becomes the cursor of chain j
-    {
-      const int per = (Ck + 255) / 256, base = tid * per;
-      int loc = 0;
-      for (int k = 0; k < per; ++k) loc += base + k < Ck ? bins[base + k] : 0;
-      int incl = loc;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += v;
-      }
-      if (lane == 63) wsum[wave] = incl;
-      __syncthreads();
-      int run = incl - loc;
-      for (int w_ = 0; w_ < wave; ++w_) run += wsum[w_];
-      for (int k = 0; k < per; ++k) {
-        if (base + k < Ck) {
-          const int c = bins[base + k];
-          bins[base + k] = run;
-          run += c;
-        }
-      }
-    }
-    __syncthreads();
-    if (tid < nq) {
-      for (int t = 0; t < r; ++t) {
-        const int x = t < 8 ? info[t] : si[t];
-        if (x >= 0) pool[atomicAdd(&bins[x & 0xffff], 1)] = make_int2(tid, (int)(((uint32_t)mybq << 16) | ((uint32_t)x >> 16)));
-      }
-    }
-    __syncthreads();
-    // chain j now is pool[bins[j-1] .. bins[j])
-    for (int jb = 64 * wave; jb < Ck; jb += 256) {
-      const int jmine = jb + lane;
-      const int e1m = jmine < Ck ? bins[jmine] : 0;
-      const int e0m = jmine < Ck ? (jmine > 0 ? bins[jmine - 1] : 0) : 0;
-      unsigned long long todo = __ballot(e1m > e0m);
-      while (todo) {
-        const int src = __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        const int j = jb + src;
-        const int e0 = __builtin_amdgcn_readlane(e0m, src), e1 = __builtin_amdgcn_readlane(e1m, src);
-        const int ne = e1 - e0;
-        for (int a0 = 0; a0 < NBm; a0 += 8) {
-          const int a = a0 + s8;
-          const bool act = a < NBm;
-          const size_t cell = (((size_t)hl * NBm + (act ? a : 0)) * Cq + i) * Ck + j;
-          const float mu = s_mu[cell];  // an empty cell has mu = -inf and zero rows: p = 0, nothing is added
-          float4 kv[NV];
-          float vv[NV][4];
-          typename F4::raw ogk[NV], ogv[NV];  // the row written by k_cell_grads
-          const float ogc = G_c[cell];
-#pragma unroll
-          for (int x = 0; x < NV; ++x) {
-            kv[x] = *reinterpret_cast<const float4*>(s_k + cell * D + 32 * x + 4 * l8);
-            ld4(s_v, cell * D + 32 * x + 4 * l8, vv[x]);
-            ogk[x] = F4::ld(G_k, cell * D + 32 * x + 4 * l8);
-            ogv[x] = F4::ld(G_v, cell * D + 32 * x + 4 * l8);
-          }
-          if (a0 == 0 && ne > 1) {
-            // order the chain's entries by query (each lane ranks up to two of them against all)
-            int2 mine[2];
-            int rank[2] = {0, 0};
-#pragma unroll
-            for (int u = 0; u < 2; ++u) mine[u] = e0 + lane + 64 * u < e1 ? pool[e0 + lane + 64 * u] : make_int2(0x7fffffff, 0);
-            for (int e = e0; e < e1; ++e) {
-              const int k = pool[e].x;
-              rank[0] += k < mine[0].x;
-              rank[1] += k < mine[1].x;
-            }
-            wave_lds_fence();
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-              if (e0 + lane + 64 * u < e1) pool[e0 + rank[u]] = mine[u];
-            wave_lds_fence();
-          }
-          float gk[NV][4], gv[NV][4], gc = 0.f;
-#pragma unroll
-          for (int x = 0; x < NV; ++x)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) { gk[x][t] = 0.f; gv[x][t] = 0.f; }
-          bool any = false;
-          // two entries per step: their LDS reads and 8-lane reductions are independent and overlap
-          for (int e = e0; e < e1; e += 2) {
-            int2 en[2];
-            bool use[2];
-#pragma unroll
-            for (int z = 0; z < 2; ++z) {
-              en[z] = e + z < e1 ? pool[e + z] : make_int2(0, 0);  // block 0: precedes no key block
-              use[z] = act && (en[z].y >> 16) > a && !((en[z].y >> a) & 1);
-            }
-            if (!use[0] && !use[1]) continue;
-            any = true;
-            float qv[2][NV][4], dv[2][NV][4];
-            float2 ld2[2];
-            float part[2] = {0.f, 0.f}, dpp[2] = {0.f, 0.f};
-#pragma unroll
-            for (int z = 0; z < 2; ++z) {
-#pragma unroll
-              for (int x = 0; x < NV; ++x) {
-                ld4(&qS[en[z].x][0], 32 * x + 4 * l8, qv[z][x]);
-                ld4(&gS[en[z].x][0], 32 * x + 4 * l8, dv[z][x]);
-              }
-              ld2[z] = ldS[en[z].x];
-            }
-#pragma unroll
-            for (int z = 0; z < 2; ++z)
-#pragma unroll
-              for (int x = 0; x < NV; ++x) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) qv[z][x][t] = scale * (qv[z][x][t] - qcv[x][t]);
-                part[z] = fmaf(qv[z][x][0], kv[x].x, part[z]); part[z] = fmaf(qv[z][x][1], kv[x].y, part[z]);
-                part[z] = fmaf(qv[z][x][2], kv[x].z, part[z]); part[z] = fmaf(qv[z][x][3], kv[x].w, part[z]);
-                dpp[z] = fmaf(dv[z][x][0], vv[x][0], dpp[z]); dpp[z] = fmaf(dv[z][x][1], vv[x][1], dpp[z]);
-                dpp[z] = fmaf(dv[z][x][2], vv[x][2], dpp[z]); dpp[z] = fmaf(dv[z][x][3], vv[x][3], dpp[z]);
-              }
-#pragma unroll
-            for (int z = 0; z < 2; ++z) {
-              part[z] = group_sum<8>(part[z]);
-              dpp[z] = group_sum<8>(dpp[z]);
-            }
-#pragma unroll
-            for (int z = 0; z < 2; ++z) {  // entry e first, then e + 1: the order of the sums stays that of the list
-              const float p = use[z] ? __expf(part[z] + mu - ld2[z].x) : 0.f;
-              const float dlg = p * (dpp[z] - ld2[z].y);
-#pragma unroll
-              for (int x = 0; x < NV; ++x)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                  gk[x][t] = fmaf(dlg, qv[z][x][t], gk[x][t]);
-                  gv[x][t] = fmaf(p, dv[z][x][t], gv[x][t]);
-                }
-              gc += dlg * (1.f - part[z]) - p * dpp[z];
-            }
-          }
-          if (any) {
-            if (l8 == 0) G_c[cell] = ogc + gc;
-#pragma unroll
-            for (int x = 0; x < NV; ++x) {
-              float ok4[4], ov4[4];
-#pragma unroll
-              for (int t = 0; t < 4; ++t) {
-                ok4[t] = F4::get(ogk[x], t) + gk[x][t];
-                ov4[t] = F4::get(ogv[x], t) + gv[x][t];
-              }
-              st4(G_k, cell * D + 32 * x + 4 * l8, ok4);
-              st4(G_v, cell * D + 32 * x + 4 * l8, ov4);
-            }
-          }
-        }
-      }
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------
 // summary gradients -> keys and values: one wave per (kv head, key block b', key cluster j); loops
 // over the query heads of the group and over tiles of 32 query clusters.
 //   W[i,m] = exp(L[i,m] - mu[i]),  T[i,m] = G_c[i] + G_k[i].k_m + G_v[i].v_m
@@ -1275,10 +1025,10 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
                      d.scale); }
   { MuseProf prof_("k_cell_grads", st); hipLaunchKernelGGL((k_cell_grads<T, D>), dim3(W, d.Cq, hn), dim3(256), 0, st, w.s_mu, w.A_mu, w.g_A_c,
                      (const T*)w.g_A_k, (const T*)w.g_A_v, w.g_s_c, (T*)w.g_s_k, (T*)w.g_s_v, d.nb, d.Cq, d.Ck); }
-  if (d.r > 0)
-    { MuseProf prof_("k_chain_grads", st); hipLaunchKernelGGL((k_chain_grads<T, D>), dim3(d.Cq, hn), dim3(256), 0, st, Q, dO, qc, w.s_mu, w.s_k,
-                       (const T*)w.s_v, w.perm_q, w.off_q, LSE, w.delta, w.slotinfo, w.g_s_c, (T*)w.g_s_k, (T*)w.g_s_v, h0, d.N,
-                       d.nb, d.Bs, d.Cq, d.Ck, d.r, d.scale); }
+  if (d.r > 0) {
+    const int rc2 = muse_launch_chain_grads<T>(d, Q, dO, qc, LSE, w, h0, hn, st);
+    if (rc2) return rc2;
+  }
   const int G_ = d.Hq / d.Hkv;
   if (sizeof(T) == 2) {
     int rc2 = muse_launch_cells_to_keys_mx(d, w.Ks, w.Vs, qc, w.qcT, w.L, w.s_mu, w.g_s_c, w.g_s_k, w.g_s_v, w.off_k, w.dKs, w.dVs,

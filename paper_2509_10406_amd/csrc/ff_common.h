@@ -375,6 +375,11 @@ template <typename T>
 int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, const int32_t* aq, FFWorkspace& w, int h0, int hn,
                             hipStream_t st);
 
+// chain_grads.hip: component 2 of the per-block cell gradients of the query heads [h0, h0+hn)
+template <typename T>
+int muse_launch_chain_grads(const MuseDims& d, const T* Q, const T* dO, const float* qc, const float* LSE, FFWorkspace& w,
+                            int h0, int hn, hipStream_t st);
+
 // attn_mfma.hip
 int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const void* Ks, const void* Vs,
                          const float* LSE, const float* delta, const int32_t* off_k, const int32_t* pair_off,
