@@ -1113,7 +1113,7 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
     for (int h0 = 0; h0 < HQ; h0 += w.hc) {
       int hn = HQ - h0 < w.hc ? HQ - h0 : w.hc;
       if (!reuse && (rc = muse_ff_summaries<T>(d, qc, w, h0, hn, st))) return rc;
-      if (!reuse && (rc = muse_ff_block_summaries<T>(d, selc, aq, w, h0, hn, st))) return rc;
+      if (!reuse && (rc = muse_ff_block_summaries<T>(d, selc, w, h0, hn, st))) return rc;
       if (split) {  // everything the dQ side reads is now queued on the first stream
         MUSE_HIP_CHECK(hipEventRecord(ax.mid, st));
         MUSE_HIP_CHECK(hipStreamWaitEvent(sb, ax.mid, 0));

@@ -264,7 +264,7 @@ struct FFWorkspace {
   int32_t* slotinfo;   // [HQ][N][r] by bucketed query position: cluster | retrieved-block mask << 16
   uint32_t* pairmask;  // [HQ][nb-1][W][N], fp32 inputs only
   int32_t* pair_off;             // inverse index of the retrieval: (kv head, key block, key cluster) -> hits
-  int32_t* pair_cnt;             // hits per pair (later: runs per pair), [HK][pairs + 1]
+  int32_t* pair_cnt;             // hits per pair, [HK][pairs + 1]
   int32_t* run_off;              // [HK][pairs + 1]: first work item of every pair, [pairs] = their number
   int4* run_map;                 // [HK][run_cap]: (pair, first hit, end) of a work item
   int32_t* c3_off;               // [HK][pairs + 1]: first (pair, hit slice) item of every pair, [pairs] = their number
@@ -372,8 +372,7 @@ int muse_ff_prepare(const MuseDims& d, const T* K, const T* V, const int32_t* aq
 template <typename T>
 int muse_ff_summaries(const MuseDims& d, const float* qc, FFWorkspace& w, int h0, int hn, hipStream_t st);
 template <typename T>
-int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, const int32_t* aq, FFWorkspace& w, int h0, int hn,
-                            hipStream_t st);
+int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace& w, int h0, int hn, hipStream_t st);
 
 // chain_grads.hip: component 2 of the per-block cell gradients of the query heads [h0, h0+hn)
 template <typename T>
