@@ -83,25 +83,45 @@ __global__ void __launch_bounds__(64 * kHitWaves) k_hit_lists(const int32_t* __r
   }
 }
 
+// The two passes over the segment counters: 64 pairs (lanes) per workgroup, its 16 waves share the segments.  (A thread
+// per pair walked all segments, up to 2048 of them, one after the other: 0.38 + 0.22 ms at 4 heads of 29k tokens, D = 128,
+// one KV head; 0.03 ms each now.)
+constexpr int kSegWaves = 16;
 // pair_cnt[hk][p] = hits of pair p over all (head of the group, slice) segments
-__global__ void __launch_bounds__(256) k_pair_totals(const int32_t* __restrict__ seg_cnt, int32_t* __restrict__ pair_cnt,
-                                                      int npair, int SEGT) {
-  const int hk = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= npair) return;
-  const int32_t* c = seg_cnt + (size_t)hk * SEGT * npair + p;
+__global__ void __launch_bounds__(64 * kSegWaves) k_pair_totals(const int32_t* __restrict__ seg_cnt, int32_t* __restrict__ pair_cnt,
+                                                                 int npair, int SEGT) {
+  __shared__ int part[kSegWaves][64];
+  const int hk = blockIdx.y, lane = threadIdx.x % 64, wave = threadIdx.x / 64, p = blockIdx.x * 64 + lane;
+  const int per = (SEGT + kSegWaves - 1) / kSegWaves, g0 = wave * per, g1 = g0 + per < SEGT ? g0 + per : SEGT;
+  const int32_t* c = seg_cnt + (size_t)hk * SEGT * npair + (p < npair ? p : npair - 1);
   int tot = 0;
-  for (int gs = 0; gs < SEGT; ++gs) tot += c[(size_t)gs * npair];
-  pair_cnt[(size_t)hk * (npair + 1) + p] = tot;
+#pragma unroll 8
+  for (int gs = g0; gs < g1; ++gs) tot += c[(size_t)gs * npair];
+  part[wave][lane] = tot;
+  __syncthreads();
+  if (wave == 0 && p < npair) {
+    for (int w = 1; w < kSegWaves; ++w) tot += part[w][lane];
+    pair_cnt[(size_t)hk * (npair + 1) + p] = tot;
+  }
 }
 
 // seg_off[hk][gs][p] = pair_off[hk][p] + hits of pair p in the segments before gs
-__global__ void __launch_bounds__(256) k_seg_offsets(const int32_t* __restrict__ seg_cnt, const int32_t* __restrict__ pair_off,
-                                                      int32_t* __restrict__ seg_off, int npair, int SEGT) {
-  const int hk = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(64 * kSegWaves) k_seg_offsets(const int32_t* __restrict__ seg_cnt, const int32_t* __restrict__ pair_off,
+                                                                 int32_t* __restrict__ seg_off, int npair, int SEGT) {
+  __shared__ int part[kSegWaves][64];
+  const int hk = blockIdx.y, lane = threadIdx.x % 64, wave = threadIdx.x / 64, p = blockIdx.x * 64 + lane;
+  const int per = (SEGT + kSegWaves - 1) / kSegWaves, g0 = wave * per, g1 = g0 + per < SEGT ? g0 + per : SEGT;
+  const size_t base = (size_t)hk * SEGT * npair + (p < npair ? p : npair - 1);
+  int tot = 0;
+#pragma unroll 8
+  for (int gs = g0; gs < g1; ++gs) tot += seg_cnt[base + (size_t)gs * npair];
+  part[wave][lane] = tot;
+  __syncthreads();
   if (p >= npair) return;
-  const size_t base = (size_t)hk * SEGT * npair + p;
   int run = pair_off[(size_t)hk * (npair + 1) + p];
-  for (int gs = 0; gs < SEGT; ++gs) {
+  for (int w = 0; w < wave; ++w) run += part[w][lane];
+#pragma unroll 8
+  for (int gs = g0; gs < g1; ++gs) {
     seg_off[base + (size_t)gs * npair] = run;
     run += seg_cnt[base + (size_t)gs * npair];
   }
@@ -109,72 +129,60 @@ __global__ void __launch_bounds__(256) k_seg_offsets(const int32_t* __restrict__
 
 // Work items of the per-pair retrieval kernels: a pair's hit tiles (32 hits each) are cut into runs of kRunTiles, so
 // a heavy pair becomes many equal items and a light one a single item (no empty slices, no tails).
-//   run_cnt[hk][p] = runs of pair p;  run_map[hk][run_off[hk][p] + u] = (p, first hit of run u, end of the run)
-__global__ void __launch_bounds__(256) k_run_counts(const int32_t* __restrict__ pair_off, int32_t* __restrict__ run_cnt, int npair) {
+//   run_map[hk][run_off[hk][p] + u] = (p, first hit of run u, end of the run)
+// The items of the key/value gradient kernel are (pair, hit slice), c3_slices of them per pair that has hits.
+__host__ __device__ inline int pair_runs(int hits) { return ((hits + 31) / 32 + kRunTiles - 1) / kRunTiles; }
+__host__ __device__ inline int pair_slices(int hits) { return hits > 0 ? c3_slices(hits) : 0; }
+__global__ void __launch_bounds__(256) k_pair_items(const int32_t* __restrict__ pair_off, const int32_t* __restrict__ run_off,
+                                                     const int32_t* __restrict__ c3_off, int4* __restrict__ run_map,
+                                                     int2* __restrict__ c3_map, int npair, size_t run_cap) {
   const int hk = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
   if (p >= npair) return;
-  const int32_t* po = pair_off + (size_t)hk * (npair + 1);
-  const int tiles = (po[p + 1] - po[p] + 31) / 32;
-  run_cnt[(size_t)hk * (npair + 1) + p] = (tiles + kRunTiles - 1) / kRunTiles;
-}
-__global__ void __launch_bounds__(256) k_run_fill(const int32_t* __restrict__ pair_off, const int32_t* __restrict__ run_off,
-                                                   int4* __restrict__ run_map, int npair, size_t run_cap) {
-  const int hk = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= npair) return;
-  const int32_t* po = pair_off + (size_t)hk * (npair + 1);
-  const int32_t* ro = run_off + (size_t)hk * (npair + 1);
-  const int lo = po[p], hi = po[p + 1];
-  int4* out = run_map + (size_t)hk * run_cap + ro[p];
+  const size_t at = (size_t)hk * (npair + 1) + p;
+  const int lo = pair_off[at], hi = pair_off[at + 1];
+  int4* run = run_map + (size_t)hk * run_cap + run_off[at];
   for (int u = 0, h = lo; h < hi; ++u, h += 32 * kRunTiles)
-    out[u] = make_int4(p, h, h + 32 * kRunTiles < hi ? h + 32 * kRunTiles : hi, 0);
+    run[u] = make_int4(p, h, h + 32 * kRunTiles < hi ? h + 32 * kRunTiles : hi, 0);
+  int2* sl = c3_map + (size_t)hk * run_cap + c3_off[at];
+  for (int u = 0; u < pair_slices(hi - lo); ++u) sl[u] = make_int2(p, u);
 }
 
-// The same for the key/value gradient kernel: its items are (pair, hit slice), c3_slices of them per pair that has hits.
-__global__ void __launch_bounds__(256) k_c3_counts(const int32_t* __restrict__ pair_off, int32_t* __restrict__ cnt, int npair) {
-  const int hk = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= npair) return;
-  const int32_t* po = pair_off + (size_t)hk * (npair + 1);
-  const int h = po[p + 1] - po[p];
-  cnt[(size_t)hk * (npair + 1) + p] = h > 0 ? c3_slices(h) : 0;
-}
-__global__ void __launch_bounds__(256) k_c3_fill(const int32_t* __restrict__ pair_off, const int32_t* __restrict__ c3_off,
-                                                  int2* __restrict__ c3_map, int npair, size_t run_cap) {
-  const int hk = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= npair) return;
-  const int32_t* po = pair_off + (size_t)hk * (npair + 1);
-  const int h = po[p + 1] - po[p];
-  const int S = h > 0 ? c3_slices(h) : 0;
-  int2* out = c3_map + (size_t)hk * run_cap + c3_off[(size_t)hk * (npair + 1) + p];
-  for (int u = 0; u < S; ++u) out[u] = make_int2(p, u);
-}
-
-// exclusive prefix of n counts per kv head, off[n] = total
-__global__ void __launch_bounds__(1024) k_pair_scan(const int32_t* __restrict__ cnt, int32_t* __restrict__ off, int n) {
-  __shared__ int wsum[16];
+// exclusive prefixes, per kv head, of the pairs' hits, runs and slices (entry n: the totals)
+__global__ void __launch_bounds__(1024) k_pair_scan(const int32_t* __restrict__ cnt, int32_t* __restrict__ pair_off,
+                                                     int32_t* __restrict__ run_off, int32_t* __restrict__ c3_off, int n) {
+  __shared__ int wsum[3][16];
   const int hk = blockIdx.x, lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-  const int32_t* c = cnt + (size_t)hk * (n + 1);
-  int32_t* o = off + (size_t)hk * (n + 1);
+  const size_t base = (size_t)hk * (n + 1);
   const int per = (n + 1023) / 1024;
-  int mine = 0;
+  int mine[3] = {0, 0, 0};
   for (int u = 0; u < per; ++u) {
-    int i = threadIdx.x * per + u;
-    if (i < n) mine += c[i];
+    const int i = threadIdx.x * per + u;
+    const int c = i < n ? cnt[base + i] : 0;
+    mine[0] += c; mine[1] += pair_runs(c); mine[2] += pair_slices(c);
   }
-  int incl = mine;
-  for (int d = 1; d < 64; d <<= 1) {
-    int v = __shfl_up(incl, d, 64);
-    if (lane >= d) incl += v;
+  int run[3];
+#pragma unroll
+  for (int z = 0; z < 3; ++z) {
+    int incl = mine[z];
+    for (int d = 1; d < 64; d <<= 1) {
+      const int v = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += v;
+    }
+    if (lane == 63) wsum[z][wave] = incl;
+    run[z] = incl - mine[z];
   }
-  if (lane == 63) wsum[wave] = incl;
   __syncthreads();
-  int base = 0;
-  for (int w = 0; w < wave; ++w) base += wsum[w];
-  int run = base + incl - mine;
+#pragma unroll
+  for (int z = 0; z < 3; ++z)
+    for (int w = 0; w < wave; ++w) run[z] += wsum[z][w];
   for (int u = 0; u < per; ++u) {
-    int i = threadIdx.x * per + u;
-    if (i < n) { o[i] = run; run += c[i]; }
+    const int i = threadIdx.x * per + u;
+    if (i >= n) break;
+    const int c = cnt[base + i];
+    pair_off[base + i] = run[0]; run_off[base + i] = run[1]; c3_off[base + i] = run[2];
+    run[0] += c; run[1] += pair_runs(c); run[2] += pair_slices(c);
   }
-  if (threadIdx.x == 1023) o[n] = run;
+  if (threadIdx.x == 1023) { pair_off[base + n] = run[0]; run_off[base + n] = run[1]; c3_off[base + n] = run[2]; }
 }
 
 // far-field state of every query  <-  state (+) partial states of its retrieved pairs.
@@ -249,19 +257,13 @@ int muse_ff_build_inverse_index(const MuseDims& d, const int32_t* selc, const in
     MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_hit_lists<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
     attr_set = true;
   }
-  const dim3 g(SEG, HQ), gp((npair + 255) / 256, HK);
+  const dim3 g(SEG, HQ), gs((npair + 63) / 64, HK);
   { MuseProf prof_("k_hit_lists", st); hipLaunchKernelGGL(k_hit_lists<false>, g, dim3(64 * kHitWaves), lds, st, selc, selb, w.seg_cnt, w.seg_off, w.hits, w.hit_cap, N, d.Bs, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, npair, SEG, cps); }
-  { MuseProf prof_("k_pair_totals", st); hipLaunchKernelGGL(k_pair_totals, gp, dim3(256), 0, st, w.seg_cnt, w.pair_cnt, npair, SEGT); }
-  { MuseProf prof_("k_pair_scan", st); hipLaunchKernelGGL(k_pair_scan, dim3(HK), dim3(1024), 0, st, w.pair_cnt, w.pair_off, npair); }
-  { MuseProf prof_("k_seg_offsets", st); hipLaunchKernelGGL(k_seg_offsets, gp, dim3(256), 0, st, w.seg_cnt, w.pair_off, w.seg_off, npair, SEGT); }
+  { MuseProf prof_("k_pair_totals", st); hipLaunchKernelGGL(k_pair_totals, gs, dim3(64 * kSegWaves), 0, st, w.seg_cnt, w.pair_cnt, npair, SEGT); }
+  { MuseProf prof_("k_pair_scan", st); hipLaunchKernelGGL(k_pair_scan, dim3(HK), dim3(1024), 0, st, w.pair_cnt, w.pair_off, w.run_off, w.c3_off, npair); }
+  { MuseProf prof_("k_seg_offsets", st); hipLaunchKernelGGL(k_seg_offsets, gs, dim3(64 * kSegWaves), 0, st, w.seg_cnt, w.pair_off, w.seg_off, npair, SEGT); }
   { MuseProf prof_("k_hit_lists", st); hipLaunchKernelGGL(k_hit_lists<true>, g, dim3(64 * kHitWaves), lds, st, selc, selb, w.seg_cnt, w.seg_off, w.hits, w.hit_cap, N, d.Bs, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, npair, SEG, cps); }
-  // the pair kernels' work items (pair_cnt is free again: it holds the runs per pair now)
-  { MuseProf prof_("k_run_counts", st); hipLaunchKernelGGL(k_run_counts, gp, dim3(256), 0, st, w.pair_off, w.pair_cnt, npair); }
-  { MuseProf prof_("k_pair_scan", st); hipLaunchKernelGGL(k_pair_scan, dim3(HK), dim3(1024), 0, st, w.pair_cnt, w.run_off, npair); }
-  { MuseProf prof_("k_run_fill", st); hipLaunchKernelGGL(k_run_fill, gp, dim3(256), 0, st, w.pair_off, w.run_off, w.run_map, npair, w.run_cap); }
-  { MuseProf prof_("k_c3_counts", st); hipLaunchKernelGGL(k_c3_counts, gp, dim3(256), 0, st, w.pair_off, w.pair_cnt, npair); }
-  { MuseProf prof_("k_pair_scan", st); hipLaunchKernelGGL(k_pair_scan, dim3(HK), dim3(1024), 0, st, w.pair_cnt, w.c3_off, npair); }
-  { MuseProf prof_("k_c3_fill", st); hipLaunchKernelGGL(k_c3_fill, gp, dim3(256), 0, st, w.pair_off, w.c3_off, w.c3_map, npair, w.run_cap); }
+  { MuseProf prof_("k_pair_items", st); hipLaunchKernelGGL(k_pair_items, dim3((npair + 255) / 256, HK), dim3(256), 0, st, w.pair_off, w.run_off, w.c3_off, w.run_map, w.c3_map, npair, w.run_cap); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }
