@@ -1085,10 +1085,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
   }
 }
 
-// adds the partial rows of the hit slices 1 .. S-1 of every pair to the rows slice 0 owns, in slice order: one wave per
-// (key cluster, key block, kv head), 16 lanes per key row
+// adds the partial rows of the hit slices 1 .. S-1 of every pair to the rows slice 0 owns, in slice order: one workgroup
+// per pair, 16 lanes per key row, a row's slices requested together (one wave with dependent loads took 0.56 ms at 16
+// heads of 64k tokens with 128 x 128 clusters, now 0.40: the rows themselves)
 template <int D>
-__global__ void __launch_bounds__(64) k_c3_reduce(const int32_t* __restrict__ off_k, const int32_t* __restrict__ pair_off,
+__global__ void __launch_bounds__(256) k_c3_reduce(const int32_t* __restrict__ off_k, const int32_t* __restrict__ pair_off,
                                                    const int32_t* __restrict__ c3_off, const int2* __restrict__ c3_map,
                                                    const float* __restrict__ part, float* __restrict__ dKs,
                                                    float* __restrict__ dVs, size_t run_cap, int N, int nb, int Ck, int HK) {
@@ -1098,20 +1099,22 @@ __global__ void __launch_bounds__(64) k_c3_reduce(const int32_t* __restrict__ of
   const int2 item = c3_map[(size_t)hk * run_cap + blockIdx.x];
   if (item.y != 1) return;
   const int32_t* po = pair_off + (size_t)hk * ((size_t)NBm * Ck + 1) + item.x;
-  const int S = c3_slices(po[1] - po[0]);
+  const int S = c3_slices(po[1] - po[0]);  // every slice has at least kC3TilesPerSlice - 1 hit tiles
   const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
   const int klo = ok[item.x], khi = ok[item.x + 1];
-  const int lane = threadIdx.x, sub = lane / 16, l16 = lane % 16;
-  for (int m = klo + sub; m < khi; m += 4)
-    for (int d = 4 * l16; d < 2 * D; d += 64) {  // the row pair [dK | dV] as 2 D floats
-      float* dst = (d < D ? dKs : dVs - D) + ((size_t)hk * N + m) * D + d;
-      float4 a = *reinterpret_cast<float4*>(dst);
-      for (int s = 1; s < S; ++s) {
-        // a slice that got no hit tile wrote nothing
-        if (po[0] + 32 * s >= po[1]) break;
-        const float4 x = *reinterpret_cast<const float4*>(part + ((((size_t)(s - 1) * HK + hk) * N + m) * 2) * D + d);
-        a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w;
-      }
+  const int sub = threadIdx.x / 16, l16 = threadIdx.x % 16;
+  for (int m = klo + sub; m < khi; m += 16)
+#pragma unroll
+    for (int d0 = 0; d0 < 2 * D; d0 += 64) {  // the row pair [dK | dV] as 2 D floats
+      const int d = d0 + 4 * l16;
+      float* dst = (d0 < D ? dKs : dVs - D) + ((size_t)hk * N + m) * D + d;
+      float4 a = *reinterpret_cast<float4*>(dst), x[kC3Slices - 1];
+#pragma unroll
+      for (int s = 1; s < kC3Slices; ++s)
+        x[s - 1] = *reinterpret_cast<const float4*>(part + ((((size_t)((s < S ? s : 1) - 1) * HK + hk) * N + m) * 2) * D + d);
+#pragma unroll
+      for (int s = 1; s < kC3Slices; ++s)
+        if (s < S) { a.x += x[s - 1].x; a.y += x[s - 1].y; a.z += x[s - 1].z; a.w += x[s - 1].w; }
       *reinterpret_cast<float4*>(dst) = a;
     }
 }
@@ -1814,24 +1817,30 @@ int muse_launch_ret_bwd_dq_pairs(const MuseDims& d, const void* Q, const void* d
   return MUSE_OK;
 }
 
-int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const void* Ks, const void* Vs,
-                         const float* LSE, const float* delta, const int32_t* off_k, const int32_t* pair_off,
-                         const int32_t* c3_off, const int2* c3_map, size_t run_cap, const uint2* hits, size_t hit_cap,
-                         float* dKs, float* dVs, float* part, hipStream_t st) {
+int muse_launch_c3_reduce(const MuseDims& d, FFWorkspace& w, hipStream_t st) {
   const int HK = d.B * d.Hkv;
-  dim3 g((unsigned)run_cap, HK), gr((unsigned)run_cap, HK);
-  float sl = d.scale * 1.4426950408889634f;
-  if (d.D == 64) {
-    { MuseProf prof_("k_c3_pairs", st); hipLaunchKernelGGL(k_c3_pairs<64>, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, (const bf16_t*)Ks,
-                       (const bf16_t*)Vs, LSE, delta, off_k, pair_off, c3_off, c3_map, hits, dKs, dVs, part, run_cap, hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, HK, d.scale, sl); }
-    { MuseProf prof_("k_c3_reduce", st); hipLaunchKernelGGL(k_c3_reduce<64>, gr, dim3(64), 0, st, off_k, pair_off, c3_off, c3_map, part, dKs, dVs, run_cap, d.N, d.nb, d.Ck, HK); }
-  } else {
-    { MuseProf prof_("k_c3_pairs", st); hipLaunchKernelGGL(k_c3_pairs<128>, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, (const bf16_t*)Ks,
-                       (const bf16_t*)Vs, LSE, delta, off_k, pair_off, c3_off, c3_map, hits, dKs, dVs, part, run_cap, hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, HK, d.scale, sl); }
-    { MuseProf prof_("k_c3_reduce", st); hipLaunchKernelGGL(k_c3_reduce<128>, gr, dim3(64), 0, st, off_k, pair_off, c3_off, c3_map, part, dKs, dVs, run_cap, d.N, d.nb, d.Ck, HK); }
-  }
+  const dim3 g((unsigned)w.run_cap, HK);
+  MuseProf prof_("k_c3_reduce", st);
+  if (d.D == 64) hipLaunchKernelGGL(k_c3_reduce<64>, g, dim3(256), 0, st, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.c3_part, w.dKs, w.dVs, w.run_cap, d.N, d.nb, d.Ck, HK);
+  else hipLaunchKernelGGL(k_c3_reduce<128>, g, dim3(256), 0, st, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.c3_part, w.dKs, w.dVs, w.run_cap, d.N, d.nb, d.Ck, HK);
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
+}
+
+int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const float* LSE, FFWorkspace& w, hipStream_t st) {
+  const int HK = d.B * d.Hkv;
+  const dim3 g((unsigned)w.run_cap, HK);
+  const float sl = d.scale * 1.4426950408889634f;
+  auto go = [&](auto* kernel) {
+    MuseProf prof_("k_c3_pairs", st);
+    hipLaunchKernelGGL(kernel, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, (const bf16_t*)w.Ks, (const bf16_t*)w.Vs, LSE,
+                       w.delta, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.hits, w.dKs, w.dVs, w.c3_part, w.run_cap, w.hit_cap, d.N,
+                       d.nb, d.Ck, d.Hq, d.Hkv, HK, d.scale, sl);
+  };
+  if (d.D == 64) go(k_c3_pairs<64>);
+  else go(k_c3_pairs<128>);
+  MUSE_LAUNCH_CHECK();
+  return muse_launch_c3_reduce(d, w, st);
 }
 
 int muse_launch_attn_fwd_mfma(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V,

@@ -1387,7 +1387,6 @@ int muse_ff_carve(const MuseDims& d, bool bwd, void* ws, size_t ws_bytes, FFWork
   w->ff_ml = w->ff_acc + HQ * N * D;
   {
     size_t R2 = (size_t)(d.r > 0 ? d.r : 1) * d.k2e;
-    w->pairmask = (uint32_t*)take(ff_pairmask_bytes(d));
     w->pair_off = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
     w->pair_cnt = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
     w->run_off = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
@@ -1413,7 +1412,7 @@ int muse_ff_carve(const MuseDims& d, bool bwd, void* ws, size_t ws_bytes, FFWork
     w->dQff = (float*)take(HQ * N * D * 4);
     w->qcT = take(HQ * D * (size_t)((d.Cq + 31) / 32 * 32) * 2);
     w->c3_part = nullptr;
-    if (es == 2 && d.r > 0 && d.nb > 1) w->c3_part = (float*)take((size_t)(kC3Slices - 1) * HK * N * 2 * D * 4);
+    if (d.r > 0 && d.nb > 1) w->c3_part = (float*)take((size_t)(kC3Slices - 1) * HK * N * 2 * D * 4);
     if (d.grad_dtype != MUSE_DTYPE_FP32) {
       w->dQacc = (float*)take(HQ * N * D * 4);
       w->dKacc = (float*)take(HK * N * D * 4);
@@ -1602,7 +1601,7 @@ int run_fwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const f
   }
   if (d.nb > 1 && d.r > 0 && sizeof(T) == 2) {
     // exact retrieval (Sec. 3.3): inverse index pair -> queries, one dense MFMA block per retrieved pair
-    if ((rc = muse_ff_build_inverse_index(d, selc, selb, w, true, st))) return rc;
+    if ((rc = muse_ff_build_inverse_index(d, selc, selb, w, st))) return rc;
     if ((rc = muse_launch_ret_fwd_pairs(d, Q, w.Ks, w.Vs, w.off_k, w.run_off, w.run_map, w.run_cap, w.hits, w.hit_cap, w.ret_part, st))) return rc;
     if ((rc = muse_launch_merge_ret(d, selb, w.ret_part, w.ff_acc, w.ff_ml, st))) return rc;
   }

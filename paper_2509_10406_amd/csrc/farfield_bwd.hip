@@ -809,161 +809,6 @@ __global__ void __launch_bounds__(64) k_cells_to_keys(const T* __restrict__ Ks, 
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// retrieval (component 3) -> keys and values: one wave per (kv head, key block b', tile of 32 key
-// clusters) owns those keys.  Phase 1 scans the queries of later blocks (all heads of the group),
-// collecting (query, cluster) hits into LDS; phase 2 accumulates per cluster in registers and adds
-// the result to the bucketed gradient rows.  When the list fills, phase 2 runs and scanning resumes.
-// ------------------------------------------------------------------------------------------
-constexpr int kHitCap = 2048;
-
-// stable counting sort of the hits by their 5-bit cluster id (single wave): sorted[], start[33]
-__device__ __forceinline__ void c3_sort_hits(const uint32_t* hits, int nh, uint32_t* sorted, int* start, int* cursor) {
-  const int lane = threadIdx.x;
-  if (lane < 33) start[lane] = 0;
-  __syncthreads();
-  for (int i = lane; i < nh; i += 64) atomicAdd(&start[(hits[i] & 31u) + 1], 1);
-  __syncthreads();
-  if (lane == 0)
-    for (int k = 0; k < 32; ++k) start[k + 1] += start[k];
-  __syncthreads();
-  if (lane < 32) cursor[lane] = start[lane];
-  __syncthreads();
-  for (int i0 = 0; i0 < nh; i0 += 64) {
-    const int i = i0 + lane;
-    const bool act = i < nh;
-    const uint32_t h = act ? hits[i] : 0u;
-    const int key = h & 31u;
-    unsigned long long m = __ballot(act);
-#pragma unroll
-    for (int bit = 0; bit < 5; ++bit) {
-      unsigned long long bb = __ballot((key >> bit) & 1);
-      m &= ((key >> bit) & 1) ? bb : ~bb;
-    }
-    const int rank = __popcll(m & ((1ull << lane) - 1ull)), cnt = __popcll(m);
-    if (act) {
-      const int base = cursor[key];
-      sorted[base + rank] = h;
-      if (rank == cnt - 1) cursor[key] = base + cnt;
-    }
-  }
-  __syncthreads();
-}
-
-template <typename T, int D>
-__device__ __forceinline__ void c3_flush(const uint32_t* hits, const int* start, const T* __restrict__ Q,
-                                         const T* __restrict__ dO, const T* __restrict__ Ks, const T* __restrict__ Vs,
-                                         const float* __restrict__ LSE, const float* __restrict__ delta,
-                                         const int32_t* __restrict__ ok, float* __restrict__ dKs,
-                                         float* __restrict__ dVs, int hk, int hqbase, int N, int Ck, int bp, int jt,
-                                         float scale) {
-  constexpr int CH = D / 8, KSL = 64 / CH;  // lanes per key, keys per step
-  const int lane = threadIdx.x, slot = lane / CH, chunk = lane % CH;
-  for (int jl = 0; jl < 32; ++jl) {
-    const int j = jt * 32 + jl;
-    if (j >= Ck) break;
-    const int klo = ok[bp * Ck + j], khi = ok[bp * Ck + j + 1];
-    for (int kb = klo; kb < khi; kb += KSL) {
-      const int pk = kb + slot;
-      const bool kvalid = pk < khi;
-      const size_t krow = ((size_t)hk * N + (kvalid ? pk : klo)) * D + 8 * chunk;
-      float k8[8], v8[8], ak[8], av[8];
-      ld4(Ks, krow, k8); ld4(Ks, krow + 4, k8 + 4);
-      ld4(Vs, krow, v8); ld4(Vs, krow + 4, v8 + 4);
-#pragma unroll
-      for (int x = 0; x < 8; ++x) { ak[x] = 0.f; av[x] = 0.f; }
-      for (int hI = start[jl]; hI < start[jl + 1]; ++hI) {
-        const uint32_t hit = hits[hI];
-        const int g = (hit >> 5) & 7, n = hit >> 8;
-        const size_t qn = ((size_t)hqbase + g) * N + n;
-        float q8[8], g8[8];
-        ld4(Q, qn * D + 8 * chunk, q8); ld4(Q, qn * D + 8 * chunk + 4, q8 + 4);
-        ld4(dO, qn * D + 8 * chunk, g8); ld4(dO, qn * D + 8 * chunk + 4, g8 + 4);
-        float part = 0.f, dpp = 0.f;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          q8[x] *= scale;
-          part = fmaf(q8[x], k8[x], part);
-          dpp = fmaf(g8[x], v8[x], dpp);
-        }
-        part = group_sum<CH>(part);
-        dpp = group_sum<CH>(dpp);
-        const float p = kvalid ? __expf(part - LSE[qn]) : 0.f;
-        const float dlg = p * (dpp - delta[qn]);
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          ak[x] = fmaf(dlg, q8[x], ak[x]);
-          av[x] = fmaf(p, g8[x], av[x]);
-        }
-      }
-      if (kvalid) {
-        float* ok_ = dKs + krow;
-        float* ov_ = dVs + krow;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) { ok_[x] += ak[x]; ov_[x] += av[x]; }
-      }
-    }
-  }
-}
-
-template <typename T, int D>
-__global__ void __launch_bounds__(64) k_c3_keys(const T* __restrict__ Q, const T* __restrict__ dO,
-                                                 const T* __restrict__ Ks, const T* __restrict__ Vs,
-                                                 const float* __restrict__ LSE, const float* __restrict__ delta,
-                                                 const uint32_t* __restrict__ pmask, const int32_t* __restrict__ off_k,
-                                                 float* __restrict__ dKs, float* __restrict__ dVs, int N, int Bs, int nb,
-                                                 int Ck, int Hq, int Hkv, float scale) {
-  __shared__ uint32_t hits[kHitCap];
-  __shared__ uint32_t sorted[kHitCap];
-  __shared__ int start[33], cursor[32];
-  const int hk = blockIdx.z, bp = blockIdx.y, jt = blockIdx.x;
-  const int G_ = Hq / Hkv;
-  const int hqbase = (hk / Hkv) * Hq + (hk % Hkv) * G_;
-  const int lane = threadIdx.x;
-  const int W = (Ck + 31) / 32;
-  const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
-  // nothing to do when the tile has no keys in this block
-  {
-    int jhi = min(jt * 32 + 32, Ck);
-    if (ok[bp * Ck + jt * 32] == ok[bp * Ck + jhi]) return;
-  }
-  int nh = 0;
-  for (int g = 0; g < G_; ++g) {
-    const size_t hq = (size_t)hqbase + g;
-    for (int n0 = (bp + 1) * Bs; n0 < N; n0 += 64) {
-      const int n = n0 + lane;
-      uint32_t keep = n < N ? pmask[((hq * (nb - 1) + bp) * W + jt) * N + n] : 0u;
-      // append (n, g, jl) for every kept bit, in lane order
-      int cnt = __popc(keep);
-      unsigned long long any = __ballot(cnt > 0);
-      if (!any) continue;
-      int incl = cnt;
-      for (int o = 1; o < 64; o <<= 1) {
-        int v = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += v;
-      }
-      const int total = __shfl(incl, 63, 64);
-      if (nh + total > kHitCap) {
-        __syncthreads();
-        c3_sort_hits(hits, nh, sorted, start, cursor);
-        c3_flush<T, D>(sorted, start, Q, dO, Ks, Vs, LSE, delta, ok, dKs, dVs, hk, hqbase, N, Ck, bp, jt, scale);
-        __syncthreads();
-        nh = 0;
-      }
-      int at = nh + incl - cnt;
-      while (keep) {
-        const int jl = __ffs((int)keep) - 1;
-        keep &= keep - 1;
-        hits[at++] = ((uint32_t)n << 8) | ((uint32_t)g << 5) | (uint32_t)jl;
-      }
-      nh += total;
-    }
-  }
-  __syncthreads();
-  c3_sort_hits(hits, nh, sorted, start, cursor);
-  c3_flush<T, D>(sorted, start, Q, dO, Ks, Vs, LSE, delta, ok, dKs, dVs, hk, hqbase, N, Ck, bp, jt, scale);
-}
-
 // rows back to sequence order, added to what the block-diagonal kernels left: dst[perm[p]] += src[p]
 __global__ void __launch_bounds__(256) k_scatter_rows(const float* __restrict__ src, const int32_t* __restrict__ perm,
                                                        float* __restrict__ dst, int N, int D) {
@@ -1086,12 +931,11 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
     MUSE_LAUNCH_CHECK();
     if (d.r > 0) {
       // retrieval (component 3): inverse index (kept from the forward when the state is reused), then per pair
+      // (the forward of fp32 inputs does without it)
       if (!reuse || sizeof(T) == 4)
-        if ((rc = muse_ff_build_inverse_index(d, selc, selb, w, sizeof(T) == 2, st))) return rc;
-      if (sizeof(T) == 2) {
-        if ((rc = muse_launch_c3_pairs(d, Q, dO, w.Ks, w.Vs, LSE, w.delta, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.run_cap, w.hits,
-                                       w.hit_cap, w.dKs, w.dVs, w.c3_part, st)))
-          return rc;
+        if ((rc = muse_ff_build_inverse_index(d, selc, selb, w, st))) return rc;
+      if constexpr (sizeof(T) == 2) {
+        if ((rc = muse_launch_c3_pairs(d, Q, dO, LSE, w, st))) return rc;
         if (split) {
           MUSE_HIP_CHECK(hipEventRecord(ax.mid, st));
           MUSE_HIP_CHECK(hipStreamWaitEvent(sb, ax.mid, 0));
@@ -1100,14 +944,7 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
                                                w.hit_cap, w.ret_part, split ? sb : st)))
           return rc;
       } else {
-        dim3 g((d.Ck + 31) / 32, d.nb - 1, HK);
-        if (D == 64)
-          { MuseProf prof_("k_c3_keys", st); hipLaunchKernelGGL((k_c3_keys<T, 64>), g, dim3(64), 0, st, Q, dO, (const T*)w.Ks, (const T*)w.Vs, LSE, w.delta,
-                             w.pairmask, w.off_k, w.dKs, w.dVs, N, d.Bs, d.nb, d.Ck, d.Hq, d.Hkv, d.scale); }
-        else
-          { MuseProf prof_("k_c3_keys", st); hipLaunchKernelGGL((k_c3_keys<T, 128>), g, dim3(64), 0, st, Q, dO, (const T*)w.Ks, (const T*)w.Vs, LSE, w.delta,
-                             w.pairmask, w.off_k, w.dKs, w.dVs, N, d.Bs, d.nb, d.Ck, d.Hq, d.Hkv, d.scale); }
-        MUSE_LAUNCH_CHECK();
+        if ((rc = muse_launch_c3_pairs_f32(d, Q, dO, LSE, w, st))) return rc;
       }
     }
     for (int h0 = 0; h0 < HQ; h0 += w.hc) {

@@ -262,7 +262,6 @@ struct FFWorkspace {
   float* delta;
   uint32_t* selmask;   // [HQ][W][N] by bucketed query position
   int32_t* slotinfo;   // [HQ][N][r] by bucketed query position: cluster | retrieved-block mask << 16
-  uint32_t* pairmask;  // [HQ][nb-1][W][N], fp32 inputs only
   int32_t* pair_off;             // inverse index of the retrieval: (kv head, key block, key cluster) -> hits
   int32_t* pair_cnt;             // hits per pair, [HK][pairs + 1]
   int32_t* run_off;              // [HK][pairs + 1]: first work item of every pair, [pairs] = their number
@@ -277,7 +276,7 @@ struct FFWorkspace {
   float* knorm;                  // [HK]: largest Euclidean norm of a key row of the kv head (bf16 inputs); then [HK][64] partial maxima
   int32_t* ff_flag;              // [HQ][nb-1][ff_tile_grid_x]: tiles the one-plane forward kernel leaves to the two-plane one
   float *dKs, *dVs;            // fp32 gradients in bucketed key order
-  float* c3_part;              // bf16 inputs, r > 0: [kC3Slices - 1][HK][N][2][D] partial dK | dV rows of the later hit slices of a pair
+  float* c3_part;              // r > 0: [kC3Slices - 1][HK][N][2][D] partial dK | dV rows of the later hit slices of a pair
   float *dQacc, *dKacc, *dVacc;  // fp32 gradients in sequence order (alias the outputs when they are fp32)
   float* dQff;                   // far-field part of dQ, added to dQacc once the block-diagonal backward has finished
   void* qcT;                     // bf16 [hc][D][Cq padded to 32]: scaled query centroids of a head chunk, transposed
@@ -309,20 +308,16 @@ static inline int ff_hit_segments(const MuseDims& d) {
   seg = seg > chunks ? chunks : seg;
   return seg < 1 ? 1 : seg;
 }
-// bytes of the bit matrix (fp32 inputs) and of the segment counters (bf16 inputs) of the inverse index
-static inline size_t ff_pairmask_bytes(const MuseDims& d) {
-  size_t HQ = (size_t)d.B * d.Hq, W = (d.Ck + 31) / 32, NBm = d.nb > 1 ? d.nb - 1 : 1;
-  return d.dtype == MUSE_DTYPE_BF16 ? 0 : HQ * d.N * W * 4 * NBm;
-}
 // most work items (runs of kRunTiles hit tiles inside one pair) a kv head can have
 static inline size_t ff_run_cap(const MuseDims& d) {
   size_t NBm = d.nb > 1 ? d.nb - 1 : 1, R2 = (size_t)(d.r > 0 ? d.r : 1) * d.k2e;
   size_t npair = NBm * d.Ck, hits = (size_t)(d.Hq / d.Hkv) * d.N * R2;
   return (hits / 32 + npair) / kRunTiles + npair + 1;
 }
+// bytes of the segment counters of the inverse index
 static inline size_t ff_segcnt_bytes(const MuseDims& d) {
   size_t HK = (size_t)d.B * d.Hkv, NBm = d.nb > 1 ? d.nb - 1 : 1;
-  return d.dtype == MUSE_DTYPE_BF16 ? HK * (d.Hq / d.Hkv) * ff_hit_segments(d) * NBm * d.Ck * 4 : 0;
+  return HK * (d.Hq / d.Hkv) * ff_hit_segments(d) * NBm * d.Ck * 4;
 }
 
 // bytes of the all-heads part / of one query head of the chunked part
@@ -339,7 +334,7 @@ static inline size_t ff_fixed_bytes(const MuseDims& d, bool bwd) {
              ff_al(HQ * ((size_t)d.nb * d.Cq + 1) * 4) + ff_al(HQ * d.nb * ((size_t)d.Cq + 1) * 4) +
              2 * ff_al(HK * N * D * es) + ff_al(HQ * N * (D + 2) * 4);
   // inverse index of the retrieval and its per-(query, slot) partial results
-  b += ff_al(ff_pairmask_bytes(d)) + 4 * ff_al(HK * ((size_t)d.nb * d.Ck + 1) * 4) + 2 * ff_al(ff_segcnt_bytes(d)) +
+  b += 4 * ff_al(HK * ((size_t)d.nb * d.Ck + 1) * 4) + 2 * ff_al(ff_segcnt_bytes(d)) +
        ff_al(HK * ff_run_cap(d) * 16) + ff_al(HK * ff_run_cap(d) * 8) +
        ff_al(HQ * N * R2 * 8) +
        ff_al(HQ * N * R2 * (D + 4) * 4);
@@ -348,7 +343,7 @@ static inline size_t ff_fixed_bytes(const MuseDims& d, bool bwd) {
     b += ff_al(HQ * N * 4) + ff_al(HQ * N * W * 4) + ff_al(HQ * N * (size_t)(d.r > 0 ? d.r : 1) * 4) + 2 * ff_al(HK * N * D * 4) +
          ff_al(HQ * N * D * 4) + ff_al(HQ * D * (size_t)((d.Cq + 31) / 32 * 32) * 2);
     if (d.grad_dtype != MUSE_DTYPE_FP32) b += ff_al(HQ * N * D * 4) + 2 * ff_al(HK * N * D * 4);
-    if (es == 2 && d.r > 0 && d.nb > 1) b += ff_al((size_t)(kC3Slices - 1) * HK * N * 2 * D * 4);
+    if (d.r > 0 && d.nb > 1) b += ff_al((size_t)(kC3Slices - 1) * HK * N * 2 * D * 4);
   }
   if (d.dipole) b += ff_al(HK * NBm * d.Ck * D * D * 4);
   return b;
@@ -380,10 +375,12 @@ int muse_launch_chain_grads(const MuseDims& d, const T* Q, const T* dO, const fl
                             int h0, int hn, hipStream_t st);
 
 // attn_mfma.hip
-int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const void* Ks, const void* Vs,
-                         const float* LSE, const float* delta, const int32_t* off_k, const int32_t* pair_off,
-                         const int32_t* c3_off, const int2* c3_map, size_t run_cap, const uint2* hits, size_t hit_cap,
-                         float* dKs, float* dVs, float* part, hipStream_t st);
+int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const float* LSE, FFWorkspace& w, hipStream_t st);
+// adds the partial rows of the later hit slices of every pair to dKs, dVs
+int muse_launch_c3_reduce(const MuseDims& d, FFWorkspace& w, hipStream_t st);
+// retrieval_fp32.hip
+int muse_launch_c3_pairs_f32(const MuseDims& d, const float* Q, const float* dO, const float* LSE, FFWorkspace& w, hipStream_t st);
+// attn_mfma.hip
 int muse_launch_ret_fwd_pairs(const MuseDims& d, const void* Q, const void* Ks, const void* Vs, const int32_t* off_k,
                               const int32_t* run_off, const int4* run_map, size_t run_cap, const uint2* hits,
                               size_t hit_cap, float* part, hipStream_t st);
@@ -404,8 +401,7 @@ int muse_dipole_covariances(const MuseDims& d, FFWorkspace& w, hipStream_t st);
 template <typename T>
 int muse_dipole_apply(const MuseDims& d, const T* Q, const float* qc, const int32_t* aq, FFWorkspace& w, int h0, int hn,
                       hipStream_t st);
-// retrieval.hip: pair bitmask + ordered hit lists from the exported selections; merge of the forward partials
-int muse_ff_build_inverse_index(const MuseDims& d, const int32_t* selc, const int32_t* selb, FFWorkspace& w,
-                                bool with_hits, hipStream_t st);
+// retrieval.hip: ordered hit lists and work items from the exported selections; merge of the forward partials
+int muse_ff_build_inverse_index(const MuseDims& d, const int32_t* selc, const int32_t* selb, FFWorkspace& w, hipStream_t st);
 int muse_launch_merge_ret(const MuseDims& d, const int32_t* selb, const float* part, float* ff_acc, float* ff_ml,
                           hipStream_t st);

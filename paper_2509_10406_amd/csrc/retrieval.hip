@@ -1,30 +1,12 @@
 // Exact retrieval (Sec. 3.3): the inverse index "retrieved (key cluster, key block) pair -> queries" and
 // the merge of the per-pair forward partial states into the far-field state of every query.
 //
-//   pairmask[hq][b'][j/32][n]  bit j%32 set iff query n of head hq retrieved the pair (j, b')
 //   hits[hk][pair_off[hk][b'*Ck + j] ...]  the queries of all heads of the KV group that retrieved the
 //                                           pair, ascending (head, position): x = n | g << 22, y = slot*k2e + u
-// Ordered lists (ballot ranks, no atomics on the order) keep every later sum reproducible.  The bit matrix is
-// built for fp32 inputs only (their key/value gradient kernel walks it); bf16 inputs build the lists directly.
+// Ordered lists (ballot ranks, no atomics on the order) keep every later sum reproducible.
 #include "ff_common.h"
 
 namespace {
-
-__global__ void __launch_bounds__(256) k_pairmask(const int32_t* __restrict__ selc, const int32_t* __restrict__ selb,
-                                                   uint32_t* __restrict__ pmask, int HQ, int N, int r, int k2e, int NBm,
-                                                   int W) {
-  size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (size_t)HQ * N * r) return;
-  const int slot = (int)(t % r);
-  const size_t q = t / r;
-  const size_t hq = q / N, n = q % N;
-  const int j = selc[q * r + slot];
-  if (j < 0) return;
-  for (int u = 0; u < k2e; ++u) {
-    const int bp = selb[(q * r + slot) * k2e + u];
-    if (bp >= 0) atomicOr(&pmask[((hq * NBm + bp) * W + (j >> 5)) * N + n], 1u << (j & 31));
-  }
-}
 
 // The hit lists are built by a counting sort whose order is fixed by construction.  The queries with a far field
 // (positions Bs .. N-1) of every query head are cut into SEG slices of whole 64-query chunks; one workgroup owns a
@@ -236,17 +218,8 @@ __global__ void __launch_bounds__(256) k_merge_ret(const int32_t* __restrict__ s
 
 }  // namespace
 
-int muse_ff_build_inverse_index(const MuseDims& d, const int32_t* selc, const int32_t* selb, FFWorkspace& w,
-                                bool with_hits, hipStream_t st) {
-  const int HQ = d.B * d.Hq, HK = d.B * d.Hkv, N = d.N, NBm = d.nb - 1, W = (d.Ck + 31) / 32;
-  const size_t nq = (size_t)HQ * N;
-  int rc;
-  if (!with_hits) {
-    if ((rc = muse_launch_fill_i32((int32_t*)w.pairmask, nq * NBm * W, 0, st))) return rc;
-    { MuseProf prof_("k_pairmask", st); hipLaunchKernelGGL(k_pairmask, dim3((unsigned)((nq * d.r + 255) / 256)), dim3(256), 0, st, selc, selb, w.pairmask, HQ, N, d.r, d.k2e, NBm, W); }
-    MUSE_LAUNCH_CHECK();
-    return MUSE_OK;
-  }
+int muse_ff_build_inverse_index(const MuseDims& d, const int32_t* selc, const int32_t* selb, FFWorkspace& w, hipStream_t st) {
+  const int HQ = d.B * d.Hq, HK = d.B * d.Hkv, N = d.N, NBm = d.nb - 1;
   const int SEG = ff_hit_segments(d), SEGT = (d.Hq / d.Hkv) * SEG, npair = NBm * d.Ck;
   const int chunks = (N - d.Bs + 63) / 64, cps = (chunks + SEG - 1) / SEG;
   const size_t lds = (size_t)npair * sizeof(int);
