@@ -18,71 +18,104 @@ namespace {
 // ------------------------------------------------------------------------------------------
 // centroid gather / preparation
 // ------------------------------------------------------------------------------------------
+// A centroid in the scoring type, chat, and nhc2 = -0.5 * ||chat||^2 (fp32 of the rounded values), by one wave: lane l
+// has the dims l and l + 64.  Every path that prepares centroids sums in this order.
 template <typename T>
-__global__ void k_init_centroids(const T* __restrict__ X, const int32_t* __restrict__ init_idx,
-                                 float* __restrict__ cent, int N, int D, int C) {
-  int h = blockIdx.y, j = blockIdx.x;
-  int row = init_idx[(size_t)h * C + j];
-  for (int d = threadIdx.x; d < D; d += blockDim.x)
-    cent[((size_t)h * C + j) * D + d] = Elem<T>::ld(X, ((size_t)h * N + row) * D + d);
+__device__ __forceinline__ void prep_row(const float (&c)[2], T* __restrict__ chat, float* __restrict__ nhc2, int D, int lane) {
+  float s = 0.f;
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int d = lane + 64 * x;
+    if (d >= D) break;
+    Elem<T>::st(chat, d, c[x]);
+    float cr = c[x];
+    if constexpr (sizeof(T) == 2) cr = bf16_bits_to_f32(f32_to_bf16_bits(c[x]));
+    s = fmaf(cr, cr, s);
+  }
+  asm volatile("" : "+v"(s));  // the last product is rounded before it is added: the same bits whatever kernel this is inlined into
+  s = wave_sum(s);
+  if (lane == 0) *nhc2 = -0.5f * s;
 }
 
-// chat [H,C,D]: centroid in the scoring type; nhc2 [H,C] = -0.5 * ||chat||^2 (fp32 of the rounded values)
+// initial centroids (rows init_idx of X, or what `cent` holds) with their chat [H,C,D] and nhc2 [H,C]; a wave per centroid
 template <typename T>
-__global__ void k_prep_centroids(const float* __restrict__ cent, T* __restrict__ chat,
-                                 float* __restrict__ nhc2, int D, int total) {
-  int row = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
-  int lane = threadIdx.x % 64;
+__global__ void __launch_bounds__(256) k_init_centroids(const T* __restrict__ X, const int32_t* __restrict__ init_idx,
+                                                         float* __restrict__ cent, T* __restrict__ chat,
+                                                         float* __restrict__ nhc2, int N, int D, int C, int total) {
+  const int row = blockIdx.x * 4 + threadIdx.x / 64, lane = threadIdx.x % 64;
   if (row >= total) return;
-  float s = 0.f;
-  for (int d = lane; d < D; d += 64) {
-    float c = cent[(size_t)row * D + d];
-    Elem<T>::st(chat, (size_t)row * D + d, c);
-    float cr = Elem<T>::ld(chat, (size_t)row * D + d);
-    s += cr * cr;
+  const T* src = init_idx ? X + ((size_t)(row / C) * N + init_idx[row]) * D : nullptr;
+  float c[2] = {0.f, 0.f};
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int d = lane + 64 * x;
+    if (d >= D) break;
+    c[x] = src ? Elem<T>::ld(src, d) : cent[(size_t)row * D + d];
+    if (src) cent[(size_t)row * D + d] = c[x];
   }
-  s = wave_sum(s);
-  if (lane == 0) nhc2[row] = -0.5f * s;
+  prep_row(c, chat + (size_t)row * D, nhc2 + row, D, lane);
 }
 
 // ------------------------------------------------------------------------------------------
-// assignment, fp32 inputs: one thread per point, centroid tiles in LDS
+// assignment, fp32 inputs: a lane per point, the centroids broadcast from LDS 16 bytes at a time.  The four waves of a
+// workgroup take the same 64 points and every fourth group of 4 centroids, whose four sums are independent chains; the
+// sum of a score runs over the dims in order.  Bound by the FMAs (one broadcast read per four of them).  With a thread
+// per point and 4-byte reads it was bound by LDS and by too few waves: 45 -> 16 us at 4 heads of 8k
+// points, 32 and 128 centroids.
 // ------------------------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(256) k_assign_f32(const float* __restrict__ X,
                                                      const float* __restrict__ chat,
                                                      const float* __restrict__ nhc2,
                                                      int32_t* __restrict__ assign, int N, int C) {
-  constexpr int CT = 32;
-  __shared__ float cs[CT][D + 1];
+  constexpr int CT = 64;
+  __shared__ __attribute__((aligned(16))) float cs[CT][D];
   __shared__ float c2s[CT];
-  int h = blockIdx.y;
-  int n = blockIdx.x * 256 + threadIdx.x;
+  __shared__ float bv[4][64];
+  __shared__ int bi[4][64];
+  const int h = blockIdx.y, wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int n = blockIdx.x * 64 + lane;
   float x[D];
-  if (n < N) {
+  {
+    const float* row = X + ((size_t)h * N + (n < N ? n : N - 1)) * D;
 #pragma unroll
-    for (int d = 0; d < D; ++d) x[d] = X[((size_t)h * N + n) * D + d];
+    for (int d = 0; d < D; d += 4) ld4(row, d, &x[d]);
   }
   float best = MUSE_NEG_INF;
-  int bj = 0;
+  int bj = 0x7fffffff;
   for (int j0 = 0; j0 < C; j0 += CT) {
     __syncthreads();
-    for (int t = threadIdx.x; t < CT * D; t += 256) {
-      int jj = t / D, d = t % D;
-      cs[jj][d] = (j0 + jj < C) ? chat[((size_t)h * C + j0 + jj) * D + d] : 0.f;
+    for (int t = threadIdx.x; t < CT * (D / 4); t += 256) {
+      const int jj = t / (D / 4), d4 = t % (D / 4);
+      reinterpret_cast<float4*>(&cs[jj][0])[d4] = (j0 + jj < C) ? reinterpret_cast<const float4*>(chat + ((size_t)h * C + j0 + jj) * D)[d4] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     if ((int)threadIdx.x < CT) c2s[threadIdx.x] = (j0 + (int)threadIdx.x < C) ? nhc2[(size_t)h * C + j0 + threadIdx.x] : MUSE_NEG_INF;
     __syncthreads();
-    if (n < N) {
-      for (int jj = 0; jj < CT && j0 + jj < C; ++jj) {
-        float acc = c2s[jj];
+    for (int jj = 4 * wave; jj < CT && j0 + jj < C; jj += 16) {
+      float acc[4];
 #pragma unroll
-        for (int d = 0; d < D; ++d) acc = fmaf(x[d], cs[jj][d], acc);
-        if (acc > best) { best = acc; bj = j0 + jj; }
-      }
+      for (int u = 0; u < 4; ++u) acc[u] = c2s[jj + u];
+#pragma unroll
+      for (int d = 0; d < D; d += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float4 c = *reinterpret_cast<const float4*>(&cs[jj + u][d]);
+          acc[u] = fmaf(x[d], c.x, acc[u]); acc[u] = fmaf(x[d + 1], c.y, acc[u]);
+          acc[u] = fmaf(x[d + 2], c.z, acc[u]); acc[u] = fmaf(x[d + 3], c.w, acc[u]);
+        }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (acc[u] > best) { best = acc[u]; bj = j0 + jj + u; }
     }
   }
-  if (n < N) assign[(size_t)h * N + n] = bj;
+  bv[wave][lane] = best;
+  bi[wave][lane] = bj;
+  __syncthreads();
+  if (wave > 0 || n >= N) return;
+#pragma unroll
+  for (int w = 1; w < 4; ++w)
+    if (bv[w][lane] > best || (bv[w][lane] == best && bi[w][lane] < bj)) { best = bv[w][lane]; bj = bi[w][lane]; }
+  assign[(size_t)h * N + n] = bj < C ? bj : 0;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -405,31 +438,36 @@ __global__ void __launch_bounds__(1024) k_bucket(const int32_t* __restrict__ ass
 }
 
 // ------------------------------------------------------------------------------------------
-// centroid update: one wave per (head, cluster); RL lanes cover one row with 16-byte loads, the
-// 64/RL row slots run over the members in order, slots are combined in a fixed tree.
+// centroid update, with the new centroid's chat and nhc2.  The members of a cluster are summed in a fixed order: row slot
+// s of S takes the spatial blocks s, s + S, ... and adds its members in order of position; the slots are combined in a
+// fixed tree.  S = 64 / (lanes of a row at 16 bytes each), so the order does not depend on which of the two forms runs:
+//   WIDE = false  one wave per cluster, 16 bytes per lane, the slots side by side in the wave (clusters of few rows);
+//   WIDE = true   a wave per slot, a lane per D / 64 dims: twice as many rows in flight and S times as many waves, for
+//                 clusters whose slots walk long chains of rows.  The line between them is in the launch.
 // ------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) k_update(const T* __restrict__ X, const int32_t* __restrict__ perm,
-                                                 const int32_t* __restrict__ off, float* __restrict__ cent,
-                                                 int N, int D, int C, int nb, int total) {
-  constexpr int EPL = 16 / Elem<T>::kBytes;  // elements per lane
-  int wid = blockIdx.x * 4 + threadIdx.x / 64;
+template <typename T, int D, bool WIDE>
+__global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) : 256) k_update(
+    const T* __restrict__ X, const int32_t* __restrict__ perm, const int32_t* __restrict__ off, float* __restrict__ cent,
+    T* __restrict__ chat, float* __restrict__ nhc2, int N, int C, int nb, int total) {
+  constexpr int S = 64 / (D * (int)sizeof(T) / 16);  // row slots
+  constexpr int EPL = WIDE ? D / 64 : 16 / (int)sizeof(T), RL = D / EPL;  // elements per lane, lanes per row
+  constexpr int MPI = WIDE ? 32 : 16;                // rows in flight per slot
+  __shared__ float sum[WIDE ? S : 4][D];
+  __shared__ int cnt[S];
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  const int wid = WIDE ? blockIdx.x : blockIdx.x * 4 + wave;
   if (wid >= total) return;
-  const int lane = threadIdx.x % 64;
   const int h = wid / C, j = wid % C;
-  const int RL = D / EPL, slots = 64 / RL;
-  const int slot = lane / RL, chunk = lane % RL;
-  const T* Xh = X + (size_t)h * N * D;
+  const int slot = WIDE ? wave : lane / RL, chunk = lane % RL;
+  const T* Xh = X + (size_t)h * N * D + chunk * EPL;
   const int32_t* ph = perm + (size_t)h * N;
   const int32_t* oh = off + (size_t)h * ((size_t)nb * C + 1);
   float acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  // a row slot takes every slots-th spatial block and walks its members MPI at a time; the positions of the
-  // next MPI are requested together with the rows of these (one round trip per MPI members)
-  constexpr int MPI = 16;
+  // MPI members per round trip; the positions of the next MPI are requested together with the rows of these
   int count = 0;
-  for (int b = slot; b < nb; b += slots) {
+  for (int b = slot; b < nb; b += S) {
     const int lo = oh[b * C + j], hi = oh[b * C + j + 1];
     count += hi - lo;
     if (lo >= hi) continue;
@@ -443,40 +481,66 @@ __global__ void __launch_bounds__(256) k_update(const T* __restrict__ X, const i
         row[u] = rown[u];
         rown[u] = ph[p + MPI + u < hi ? p + MPI + u : hi - 1];
       }
-      if constexpr (EPL == 8) {
-        uint4 v[MPI];
+      struct __attribute__((aligned(EPL * sizeof(T)))) Row { T e[EPL]; } v[MPI];
 #pragma unroll
-        for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const uint4*>(Xh + (size_t)row[u] * D + chunk * 8);
+      for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const Row*>(Xh + (size_t)row[u] * D);
 #pragma unroll
-        for (int u = 0; u < MPI; ++u) {
-          if (p + u >= hi) continue;
-          const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+      for (int u = 0; u < MPI; ++u) {
+        if (p + u >= hi) continue;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            acc[2 * e] += __uint_as_float(w[e] << 16);
-            acc[2 * e + 1] += __uint_as_float(w[e] & 0xffff0000u);
-          }
-        }
-      } else {
-        float4 v[MPI];
-#pragma unroll
-        for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const float4*>(Xh + (size_t)row[u] * D + chunk * 4);
-#pragma unroll
-        for (int u = 0; u < MPI; ++u) {
-          if (p + u >= hi) continue;
-          acc[0] += v[u].x; acc[1] += v[u].y; acc[2] += v[u].z; acc[3] += v[u].w;
+        for (int e = 0; e < EPL; ++e) {
+          if constexpr (sizeof(T) == 2) acc[e] += bf16_bits_to_f32(v[u].e[e]);
+          else acc[e] += v[u].e[e];
         }
       }
     }
   }
-  for (int o = RL; o < 64; o <<= 1) count += __shfl_xor(count, o, 64);
-  for (int o = RL; o < 64; o <<= 1)
+  const size_t at = (size_t)h * C + j;
+  float* mine = sum[wave];
+  if constexpr (WIDE) {
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
-  if (slot == 0 && count > 0) {
-    float inv = (float)count;
+    for (int e = 0; e < EPL; ++e) mine[chunk * EPL + e] = acc[e];
+    if (lane == 0) cnt[slot] = count;
+    __syncthreads();
+    if (wave > 0) return;
+    count = 0;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) cent[((size_t)h * C + j) * D + chunk * EPL + e] = acc[e] / inv;
+    for (int s = 0; s < S; ++s) count += cnt[s];
+    if (count == 0) return;  // an empty cluster keeps its centroid
+    const float inv = (float)count;
+    float c[2] = {0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < D / 64; ++x) {
+      float t[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) t[s] = sum[s][lane + 64 * x];
+#pragma unroll
+      for (int o = 1; o < S; o *= 2)
+#pragma unroll
+        for (int s = 0; s + o < S; s += 2 * o) t[s] += t[s + o];
+      c[x] = t[0] / inv;
+      cent[at * D + lane + 64 * x] = c[x];
+    }
+    prep_row(c, chat + at * D, nhc2 + at, D, lane);
+  } else {
+    for (int o = RL; o < 64; o <<= 1) count += __shfl_xor(count, o, 64);
+    for (int o = RL; o < 64; o <<= 1)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+    if (count == 0) return;
+    const float inv = (float)count;
+    if (slot == 0) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) mine[chunk * EPL + e] = acc[e] / inv;
+    }
+    wave_lds_fence();
+    float c[2] = {0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < D / 64; ++x) {
+      c[x] = mine[lane + 64 * x];
+      cent[at * D + lane + 64 * x] = c[x];
+    }
+    prep_row(c, chat + at * D, nhc2 + at, D, lane);
   }
 }
 
@@ -937,6 +1001,15 @@ __global__ void __launch_bounds__(256) k_balance(const T* __restrict__ X, const 
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Which form of k_update: the wide one while the device has room for its S times as many waves and a slot walks more
+// than a few rows (us per launch, wide / narrow: 8.8 / 13.7 at one fp32 head of 2k rows, 16 to 32 rows per slot; 13 / 18
+// at 12 bf16 heads of 6k, 10 to 32 rows), and always for long chains (28 / 59 at 6 heads of 20k with 43 and 125
+// clusters, 53 / 60 at 32 heads of 32k, D = 128, 128 rows); many short chains fill the device by themselves (103 / 42 at
+// 16 heads of 64k with 256 and 1024 clusters, 58 / 54 with 128).
+static bool wide_update(int rows_per_slot, long long waves) {
+  return (rows_per_slot >= 12 && waves <= 8192) || rows_per_slot >= 96;
+}
+
 template <typename T>
 int cluster_impl(const MuseDims& d, const T* X, int H, int C, const int32_t* init_idx, float* cent,
                  int32_t* assign, int32_t* trace, float* counts, void* ws, hipStream_t st) {
@@ -986,16 +1059,12 @@ int cluster_impl(const MuseDims& d, const T* X, int H, int C, const int32_t* ini
     if (!assign) return MUSE_OK;
   }
   const int T_ = d.streaming ? 0 : d.T;
-  if (init_idx && !d.streaming) {
-    { MuseProf prof_("k_init_centroids", st); hipLaunchKernelGGL(k_init_centroids<T>, dim3(C, heads), dim3(64), 0, st, X, init_idx, cent, N, D, C); }
-    MUSE_LAUNCH_CHECK();
-  }
+  const int rows = heads * C;
+  { MuseProf prof_("k_init_centroids", st); hipLaunchKernelGGL(k_init_centroids<T>, dim3((rows + 3) / 4), dim3(256), 0, st, X, d.streaming ? nullptr : init_idx, cent, chat, nhc2, N, D, C, rows); }
+  MUSE_LAUNCH_CHECK();
   for (int it = 0; it <= T_; ++it) {
-    int rows = heads * C;
-    { MuseProf prof_("k_prep_centroids", st); hipLaunchKernelGGL(k_prep_centroids<T>, dim3((rows + 3) / 4), dim3(256), 0, st, cent, chat, nhc2, D, rows); }
-    MUSE_LAUNCH_CHECK();
     if constexpr (sizeof(T) == 4) {
-      dim3 g((N + 255) / 256, heads);
+      dim3 g((N + 63) / 64, heads);
       if (D == 64) { MuseProf prof_("k_assign_f32", st); hipLaunchKernelGGL(k_assign_f32<64>, g, dim3(256), 0, st, (const float*)X, (const float*)chat, nhc2, assign, N, C); }
       else { MuseProf prof_("k_assign_f32", st); hipLaunchKernelGGL(k_assign_f32<128>, g, dim3(256), 0, st, (const float*)X, (const float*)chat, nhc2, assign, N, C); }
     } else {
@@ -1039,7 +1108,15 @@ int cluster_impl(const MuseDims& d, const T* X, int H, int C, const int32_t* ini
     if (it == T_) break;
     int rc = muse_launch_bucket(assign, heads, N, d.Bs, C, perm, off, st);
     if (rc) return rc;
-    { MuseProf prof_("k_update", st); hipLaunchKernelGGL(k_update<T>, dim3((rows + 3) / 4), dim3(256), 0, st, X, perm, off, cent, N, D, C, d.nb, rows); }
+    {
+      MuseProf prof_("k_update", st);
+      constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);
+      const int S = D == 64 ? S64 : S128;
+      const bool wide = wide_update(N / C / S, (long long)rows * S);
+      auto go = [&](auto* kernel, int grid, int block) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, st, X, perm, off, cent, chat, nhc2, N, C, d.nb, rows); };
+      if (D == 64) wide ? go(k_update<T, 64, true>, rows, 64 * S64) : go(k_update<T, 64, false>, (rows + 3) / 4, 256);
+      else wide ? go(k_update<T, 128, true>, rows, 64 * S128) : go(k_update<T, 128, false>, (rows + 3) / 4, 256);
+    }
     MUSE_LAUNCH_CHECK();
   }
   return MUSE_OK;
