@@ -1403,198 +1403,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 }
 
 // ------------------------------------------------------------------------------------------
-// Gradients of the accumulated cells (component 1) for bf16 inputs: the (b, i) group's queries against
-// a tile of 32 key clusters is a dense attention-backward block with the accumulated summaries in the
-// role of keys and values.  One block per group: its queries (QT tiles of 32 at a time, nearly always
-// all of them) are staged in LDS once, and every wave walks its share of the cluster tiles with the
-// next tile's summaries already in flight.
-//   g_A_k = sum dl q~,  g_A_v = sum p dO,  g_A_c = sum [dl (1 - q~.kbar) - p dO.vbar]
-// Operands are rounded to bf16 for the matrix cores (gradients only; no selection depends on them).
-// A group with more than 32 QT queries takes further passes that add to the rows of the first.
-// ------------------------------------------------------------------------------------------
-template <int D, int QT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, 2))) k_ff_bwd_cells_mx(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ dO, const float* __restrict__ qc,
-    const float* __restrict__ A_mu, const bf16_t* __restrict__ A_kb, const bf16_t* __restrict__ A_v,
-    const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q, const float* __restrict__ LSE,
-    const float* __restrict__ delta, const uint32_t* __restrict__ selmask, float* __restrict__ g_A_c,
-    bf16_t* __restrict__ g_A_k, bf16_t* __restrict__ g_A_v, int h0, int N, int nb, int Cq, int Ck, float scale) {
-  constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, QR = 32 * QT;
-  __shared__ __attribute__((aligned(16))) bf16_t qs[QR][D + 8];
-  __shared__ __attribute__((aligned(16))) bf16_t gs[QR][D + 8];
-  __shared__ __attribute__((aligned(16))) bf16_t qt_[D][QR + TPAD];
-  __shared__ __attribute__((aligned(16))) bf16_t gt_[D][QR + TPAD];
-  __shared__ __attribute__((aligned(16))) float ls[QR];
-  __shared__ __attribute__((aligned(16))) float ds[QR];
-  __shared__ uint32_t mws[4][QR];
-  __shared__ __attribute__((aligned(16))) bf16_t tw[4][32][D + 8];
-  const int hl = blockIdx.z, hq = h0 + hl;
-  const int NBm = nb - 1, W = (Ck + 31) / 32;
-  const int b = blockIdx.y / Cq + 1, i = blockIdx.y % Cq;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
-  const int32_t* oq = off_q + (size_t)hq * ((size_t)nb * Cq + 1);
-  const int qlo = oq[b * Cq + i], qhi = oq[b * Cq + i + 1];
-  const size_t acell = (((size_t)hl * NBm + (b - 1)) * Cq + i) * Ck;
-  const float* qci = qc + ((size_t)hq * Cq + i) * D;
-  struct CT {  // one tile of 32 accumulated summaries as this lane's operand fragments
-    bf16x8_t kf[KS], vf[KS];
-    float amu;  // raw: any arithmetic on a prefetched value would wait for the whole prefetch at once
-    uint32_t mw[QT];  // word of the selection mask of staged query 32 qt + col for this cluster tile
-  };
-  auto load_ct = [&](int jt, int q0, int qhi, CT& c) {
-    const int jc = jt * 32 + col;
-    const int jcc = jc < Ck ? jc : Ck - 1;
-#pragma unroll
-    for (int x = 0; x < KS; ++x) {
-      c.kf[x] = *reinterpret_cast<const bf16x8_t*>(A_kb + (acell + jcc) * D + 16 * x + 8 * half);
-      c.vf[x] = *reinterpret_cast<const bf16x8_t*>(A_v + (acell + jcc) * D + 16 * x + 8 * half);
-    }
-    c.amu = A_mu[acell + jcc];
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-      const int pq = q0 + 32 * qt + col;
-      c.mw[qt] = selmask[((size_t)hq * W + jt) * N + (pq < qhi ? pq : q0)];
-    }
-  };
-  for (int q0 = qlo; q0 < qhi || q0 == qlo; q0 += QR) {  // an empty group still writes its (zero) cells
-    const bool first = q0 == qlo;
-    __syncthreads();
-    for (int c = threadIdx.x; c < (q0 < qhi ? QR * CPR : 0); c += 256) {
-      const int row = c % QR, cc = c / QR;  // lanes along the rows: conflict-free transposed stores
-      const int pos = q0 + row < qhi ? q0 + row : q0;
-      const size_t qn = (size_t)hq * N + perm_q[(size_t)hq * N + pos];
-      uint4 qv = *reinterpret_cast<const uint4*>(Q + qn * D + cc * 8);
-      uint4 gvv = *reinterpret_cast<const uint4*>(dO + qn * D + cc * 8);
-      const bf16_t* pq = reinterpret_cast<const bf16_t*>(&qv);
-      const bf16_t* pg = reinterpret_cast<const bf16_t*>(&gvv);
-      float4 c0 = *reinterpret_cast<const float4*>(qci + cc * 8), c1 = *reinterpret_cast<const float4*>(qci + cc * 8 + 4);
-      const float cv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-      bf16_t qtl[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) qtl[e] = f32_to_bf16_bits(scale * (bf16_bits_to_f32(pq[e]) - cv[e]));
-      *reinterpret_cast<uint4*>(&qs[row][cc * 8]) = *reinterpret_cast<const uint4*>(qtl);
-      *reinterpret_cast<uint4*>(&gs[row][cc * 8]) = gvv;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) { qt_[cc * 8 + e][row] = qtl[e]; gt_[cc * 8 + e][row] = pg[e]; }
-    }
-    if (threadIdx.x < QR && q0 < qhi) {
-      const int row = threadIdx.x;
-      const bool ok = q0 + row < qhi;
-      const size_t qn = (size_t)hq * N + perm_q[(size_t)hq * N + (ok ? q0 + row : q0)];
-      ls[row] = ok ? LSE[qn] * 1.4426950408889634f : __builtin_huge_valf();  // +inf -> p = 0 for padding rows
-      ds[row] = delta[qn];
-    }
-    __syncthreads();
-    const int ntl = (qhi - q0 + 31) / 32 < QT ? (qhi - q0 + 31) / 32 : QT;  // staged query tiles (0 for an empty group)
-    CT cur, nxt;
-    if (wave < W) load_ct(wave, q0 < qhi ? q0 : 0, qhi, cur);
-    for (int jt = wave; jt < W; jt += 4) {
-      // always issued (the last tile again at the end): with the same number of loads in flight on every path
-      // the wait for this tile's operands can leave the next tile's loads outstanding
-      load_ct(jt + 4 < W ? jt + 4 : jt, q0 < qhi ? q0 : 0, qhi, nxt);
-      // this wave's words of the selection mask: one per staged query, for cluster tile jt
-      if (half == 0) {
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) mws[wave][32 * qt + col] = cur.mw[qt];
-      }
-      wave_lds_fence();
-      const int jc = jt * 32 + col;
-      const bool jvalid = jc < Ck;
-      const float amu2 = jvalid ? cur.amu * 1.4426950408889634f : MUSE_NEG_INF;
-      f32x16_t gk[DT], gv[DT];
-#pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) { gk[t][e] = 0.f; gv[t][e] = 0.f; }
-      float csum = 0.f;
-      for (int qt = 0; qt < ntl; ++qt) {
-        f32x16_t s, dp;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-#pragma unroll
-        for (int x = 0; x < KS; ++x) {
-          bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(&qs[32 * qt + col][16 * x + 8 * half]);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, cur.kf[x], s, 0, 0, 0);
-          bf16x8_t ag = *reinterpret_cast<const bf16x8_t*>(&gs[32 * qt + col][16 * x + 8 * half]);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag, cur.vf[x], dp, 0, 0, 0);
-        }
-        f32x16_t pr;
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          float4 l4 = *reinterpret_cast<const float4*>(&ls[32 * qt + 8 * gq + 4 * half]);
-          float4 d4 = *reinterpret_cast<const float4*>(&ds[32 * qt + 8 * gq + 4 * half]);
-          const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int e = 4 * gq + u, row = 32 * qt + 8 * gq + 4 * half + u;
-            float p = fast_exp2(fmaf(s[e], 1.4426950408889634f, amu2 - lv[u]));
-            p = ((mws[wave][row] >> col) & 1u) ? 0.f : p;
-            const float dlg = p * (dp[e] - dv4[u]);
-            csum += p > 0.f ? dlg * (1.f - s[e]) - p * dp[e] : 0.f;
-            pr[e] = p;
-            s[e] = dlg;
-          }
-        }
-#pragma unroll
-        for (int G = 0; G < 2; ++G) {
-          bf16x8_t pf = pack8(pr, 2 * G, 2 * G + 1);
-          bf16x8_t df = pack8(s, 2 * G, 2 * G + 1);
-#pragma unroll
-          for (int t = 0; t < DT; ++t) {
-            bf16x8_t ag = ld_tr8(&gt_[32 * t + col][0], 32 * qt + 16 * G, half);
-            gv[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag, pf, gv[t], 0, 0, 0);
-            bf16x8_t aq = ld_tr8(&qt_[32 * t + col][0], 32 * qt + 16 * G, half);
-            gk[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, df, gk[t], 0, 0, 0);
-          }
-        }
-      }
-      wave_lds_fence();  // mws is rewritten for the next cluster tile
-      csum += __shfl_xor(csum, 32, 64);
-      // rows go out through a per-wave LDS tile: a store instruction then writes 64 / (D/8) whole rows of
-      // consecutive clusters (contiguous memory) instead of 32 fragments of 8 bytes
-#pragma unroll
-      for (int arr = 0; arr < 2; ++arr) {
-        wave_lds_fence();
-#pragma unroll
-        for (int t = 0; t < DT; ++t)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x16_t& a = arr == 0 ? gk[t] : gv[t];
-            *reinterpret_cast<uint2*>(&tw[wave][col][32 * t + 8 * g + 4 * half]) =
-                make_uint2(pack_bf16x2(a[4 * g], a[4 * g + 1]), pack_bf16x2(a[4 * g + 2], a[4 * g + 3]));
-          }
-        wave_lds_fence();
-        bf16_t* dst = arr == 0 ? g_A_k : g_A_v;
-#pragma unroll
-        for (int it = 0; it < 32 * CPR / 64; ++it) {
-          const int row = it * (64 / CPR) + lane / CPR, cc = lane % CPR;
-          if (jt * 32 + row < Ck) {
-            uint4 v = *reinterpret_cast<const uint4*>(&tw[wave][row][cc * 8]);
-            uint4* o = reinterpret_cast<uint4*>(dst + (acell + jt * 32 + row) * D + cc * 8);
-            if (!first) {  // further pass of a large group: add to what the earlier passes wrote
-              const uint4 old = *o;
-              const uint32_t* pn = reinterpret_cast<const uint32_t*>(&v);
-              const uint32_t* po = reinterpret_cast<const uint32_t*>(&old);
-              uint32_t rr[4];
-#pragma unroll
-              for (int u = 0; u < 4; ++u)
-                rr[u] = pack_bf16x2(__uint_as_float(pn[u] << 16) + __uint_as_float(po[u] << 16),
-                                    __uint_as_float(pn[u] & 0xffff0000u) + __uint_as_float(po[u] & 0xffff0000u));
-              v = make_uint4(rr[0], rr[1], rr[2], rr[3]);
-            }
-            typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-            const u4_t vs = {v.x, v.y, v.z, v.w};
-            __builtin_nontemporal_store(vs, reinterpret_cast<u4_t*>(o));  // written once, read by the next kernel much later
-          }
-        }
-      }
-      if (jvalid && half == 0) g_A_c[acell + jc] = first ? csum : g_A_c[acell + jc] + csum;
-      cur = nxt;
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------
 // Summary gradients -> keys and values for bf16 inputs: one wave per (kv head, key block b', key
 // cluster j); the keys of the segment are the MFMA columns, 32 query clusters at a time the rows.
 //   W[i,m] = exp(L[i,m] - mu[i]),  T[i,m] = G_c[i] + G_k[i].k_m + G_v[i].v_m
@@ -1772,19 +1580,6 @@ int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* 
     { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<64>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcT, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, dKs, dVs, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
   else
     { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<128>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcT, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, dKs, dVs, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
-  MUSE_LAUNCH_CHECK();
-  return MUSE_OK;
-}
-
-int muse_launch_ff_bwd_cells_mx(const MuseDims& d, const void* Q, const void* dO, const float* qc, const float* A_mu,
-                                const void* A_kb, const void* A_v, const int32_t* perm_q, const int32_t* off_q,
-                                const float* LSE, const float* delta, const uint32_t* selmask, float* g_A_c,
-                                void* g_A_k, void* g_A_v, int h0, int hn, hipStream_t st) {
-  dim3 g(1, (d.nb - 1) * d.Cq, hn);
-  if (d.D == 64)
-    { MuseProf prof_("k_ff_bwd_cells_mx", st); hipLaunchKernelGGL((k_ff_bwd_cells_mx<64, 3>), g, dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, qc, A_mu, (const bf16_t*)A_kb, (const bf16_t*)A_v, perm_q, off_q, LSE, delta, selmask, g_A_c, (bf16_t*)g_A_k, (bf16_t*)g_A_v, h0, d.N, d.nb, d.Cq, d.Ck, d.scale); }
-  else
-    { MuseProf prof_("k_ff_bwd_cells_mx", st); hipLaunchKernelGGL((k_ff_bwd_cells_mx<128, 1>), g, dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, qc, A_mu, (const bf16_t*)A_kb, (const bf16_t*)A_v, perm_q, off_q, LSE, delta, selmask, g_A_c, (bf16_t*)g_A_k, (bf16_t*)g_A_v, h0, d.N, d.nb, d.Cq, d.Ck, d.scale); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

@@ -23,16 +23,9 @@
 // at 12 heads of 6k tokens with 23 x 71 clusters, 3.86 -> 0.76 ms at 16 heads of 64k tokens with 128 x 128 clusters,
 // 2.8 -> 2.3 ms there with 256 x 1024, 8.2 -> 6.1 ms at D = 128 (32 heads of 32k, 128 x 512, r = 16).
 #include "ff_common.h"
+#include "lds_tile.h"
 
 namespace {
-
-typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-
-// four k-slots of a transposed operand straight from a row-major LDS tile: the 16 lanes of a group name rows
-// r0 .. r0+3 (lane s: row r0 + s / 4, columns c0 + 4 (s % 4) ..) and each receives its own column c0 + s of the four
-__device__ __forceinline__ s16x4_t lds_tr4(const bf16_t* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)p);
-}
 
 __device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
   hi = (__bf16)x;

@@ -861,8 +861,7 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
   }
   st = sk_;
   if (sizeof(T) == 2) {
-    int rc2 = muse_launch_ff_bwd_cells_mx(d, Q, dO, qc, w.A_mu, w.A_kb, w.A_v, w.perm_q, w.off_q, LSE, w.delta, w.selmask,
-                                          w.g_A_c, w.g_A_k, w.g_A_v, h0, hn, st);
+    const int rc2 = muse_launch_ff_bwd_cells_mx(d, Q, dO, qc, LSE, w, h0, hn, st);
     if (rc2) return rc2;
   } else
   { MuseProf prof_("k_ff_bwd_cells", st); hipLaunchKernelGGL((k_ff_bwd_cells<T, D>), dim3(W, NBm * d.Cq, hn), dim3(64), 0, st, Q, dO, qc, w.A_mu, w.A_k, (const float*)w.A_v,

@@ -369,6 +369,9 @@ int muse_ff_summaries(const MuseDims& d, const float* qc, FFWorkspace& w, int h0
 template <typename T>
 int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace& w, int h0, int hn, hipStream_t st);
 
+// cell_grads.hip: gradients of the accumulated cells (component 1), bf16 inputs, of the query heads [h0, h0+hn)
+int muse_launch_ff_bwd_cells_mx(const MuseDims& d, const void* Q, const void* dO, const float* qc, const float* LSE,
+                                FFWorkspace& w, int h0, int hn, hipStream_t st);
 // chain_grads.hip: component 2 of the per-block cell gradients of the query heads [h0, h0+hn)
 template <typename T>
 int muse_launch_chain_grads(const MuseDims& d, const T* Q, const T* dO, const float* qc, const float* LSE, FFWorkspace& w,
@@ -388,10 +391,6 @@ int muse_launch_ret_bwd_dq_pairs(const MuseDims& d, const void* Q, const void* d
                                  const float* LSE, const float* delta, const int32_t* off_k, const int32_t* run_off,
                                  const int4* run_map, size_t run_cap, const uint2* hits, size_t hit_cap, float* dqpart,
                                  hipStream_t st);
-int muse_launch_ff_bwd_cells_mx(const MuseDims& d, const void* Q, const void* dO, const float* qc, const float* A_mu,
-                                const void* A_kb, const void* A_v, const int32_t* perm_q, const int32_t* off_q,
-                                const float* LSE, const float* delta, const uint32_t* selmask, float* g_A_c,
-                                void* g_A_k, void* g_A_v, int h0, int hn, hipStream_t st);
 int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* Vs, const float* qc, void* qcT,
                                  const float* L, const float* s_mu, const float* G_c, const void* G_k, const void* G_v,
                                  const int32_t* off_k, float* dKs, float* dVs, int h0, int hn, hipStream_t st);
