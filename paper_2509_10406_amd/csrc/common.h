@@ -224,7 +224,7 @@ int muse_launch_cluster(const MuseDims& d, const void* X, int H, int C, const in
 int muse_launch_bucket(const int32_t* assign, int heads, int N, int Bs, int C, int32_t* perm,
                        int32_t* off, hipStream_t st);
 
-// attn_simple.hip / attn_mfma.hip: causal attention restricted to keys m with
+// attn_fp32.hip / attn_mfma.hip: causal attention restricted to keys m with
 // floor(n/Bs)*Bs <= m <= n  (Bs = N gives exact attention).  ff (may be NULL): per query
 // (max, sum, acc[D]) fp32 partial softmax state in natural-log units merged into the result.
 int muse_launch_attn_fwd(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V,
