@@ -911,215 +911,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 }
 
 // ------------------------------------------------------------------------------------------
-// Retrieval backward (Sec. 3.3 "Exact retrieval", gradient w.r.t. keys and values): one wave per
-// retrieved (key cluster, key block) pair.  `hits` lists the queries that retrieved the pair (the
-// inverse index: pair -> queries); they are gathered 32 at a time into LDS and the pair is treated as a
-// dense attention-backward block on the matrix cores, the keys of the pair being the MFMA columns.
-//   hit = n | g << 22  (query position, query head inside the KV group)
-// A pair with many hits (at the operating ratio of Sec. 3.3 a pair has some 500, with a heavy tail) is shared by
-// up to kC3Slices waves: slice s of S takes the hit tiles s, s + S, ...; slice 0 adds to the bucketed-order gradient
-// rows of the pair's keys, the others write partial rows, which k_c3_reduce adds in slice order (fixed order, no
-// atomics).  S depends on the pair's hit count only.
-// ------------------------------------------------------------------------------------------
-
-template <int D>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, D == 64 ? 2 : 1))) k_c3_pairs(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ dO,
-                                                  const bf16_t* __restrict__ Ks, const bf16_t* __restrict__ Vs,
-                                                  const float* __restrict__ LSE, const float* __restrict__ delta,
-                                                  const int32_t* __restrict__ off_k, const int32_t* __restrict__ pair_off,
-                                                  const int32_t* __restrict__ c3_off, const int2* __restrict__ c3_map,
-                                                  const uint2* __restrict__ hits, float* __restrict__ dKs,
-                                                  float* __restrict__ dVs, float* __restrict__ part, size_t run_cap,
-                                                  size_t hit_cap, int N, int nb, int Ck, int Hq, int Hkv, int HK,
-                                                  float scale, float scale_log2e) {
-  constexpr int KS = D / 16, DT = D / 32;
-  __shared__ __attribute__((aligned(16))) bf16_t qt_[D][32 + TPAD];
-  __shared__ __attribute__((aligned(16))) bf16_t gt_[D][32 + TPAD];
-  __shared__ __attribute__((aligned(16))) float lse_s[32];
-  __shared__ __attribute__((aligned(16))) float dl_s[32];
-  // one wave per work item (pair, hit slice): only the slices a pair has are launched
-  const int hk = blockIdx.y, NBm = nb - 1;
-  if ((int)blockIdx.x >= c3_off[(size_t)hk * ((size_t)NBm * Ck + 1) + (size_t)NBm * Ck]) return;  // past the last item
-  const int2 item = c3_map[(size_t)hk * run_cap + blockIdx.x];  // (pair, slice)
-  const int sl = item.y;
-  const int G_ = Hq / Hkv;
-  const size_t hqbase = (size_t)(hk / Hkv) * Hq + (size_t)(hk % Hkv) * G_;
-  const int lane = threadIdx.x, col = lane % 32, half = lane / 32;
-  const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
-  const int klo = ok[item.x], khi = ok[item.x + 1];  // pair = b' Ck + j indexes the segment table directly
-  const int32_t* po = pair_off + (size_t)hk * ((size_t)NBm * Ck + 1) + item.x;
-  const int hlo = po[0], hhi = po[1];
-  if (klo == khi || hlo == hhi) return;
-  const int S = c3_slices(hhi - hlo);
-  if (sl >= S) return;
-  const int step = 32 * S, hfirst = hlo + 32 * sl;  // this slice's hit tiles start at hfirst, hfirst + step, ...
-  if (hfirst >= hhi) return;
-  const uint2* hh = hits + (size_t)hk * hit_cap;
-  for (int k0 = klo; k0 < khi; k0 += 32) {
-    const int mk = k0 + col;
-    const bool kvalid = mk < khi;
-    const size_t krow = ((size_t)hk * N + (kvalid ? mk : klo)) * D;
-    bf16x8_t kf[KS], vf[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      kf[s] = *reinterpret_cast<const bf16x8_t*>(Ks + krow + 16 * s + 8 * half);
-      vf[s] = *reinterpret_cast<const bf16x8_t*>(Vs + krow + 16 * s + 8 * half);
-    }
-    f32x16_t dk[DT], dv[DT];
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { dk[t][e] = 0.f; dv[t][e] = 0.f; }
-    // A tile of 32 hits: the hit of row `col` (one coalesced load of the list), that query's q and dO rows as
-    // this lane's half of every 16 dims (the A operands of the score contractions as they are, and the source
-    // of the transposed LDS tiles), its LSE and delta.  The next tile is gathered while this one is used; a
-    // tile index past the end repeats the last hit, the values stay raw until they are used.
-    constexpr int NIT = KS;
-    struct HT {
-      uint4 q[NIT], g[NIT];
-      float lse, dl;
-    };
-    auto gather = [&](HT& t, int h0) {
-      const int hi = h0 + col < hhi ? h0 + col : hhi - 1;
-      const uint32_t hit = hh[hi].x;
-      const size_t qn = (hqbase + (hit >> 22)) * N + (hit & 0x3fffffu);
-#pragma unroll
-      for (int it = 0; it < NIT; ++it) {
-        t.q[it] = *reinterpret_cast<const uint4*>(Q + qn * D + 16 * it + 8 * half);
-        t.g[it] = *reinterpret_cast<const uint4*>(dO + qn * D + 16 * it + 8 * half);
-      }
-      t.lse = LSE[qn];
-      t.dl = delta[qn];
-    };
-    auto use = [&](const HT& t, int h0) {
-      wave_lds_fence();
-#pragma unroll
-      for (int it = 0; it < NIT; ++it) {  // lanes run along the rows: conflict-free transposed stores
-        const uint32_t wq[4] = {t.q[it].x, t.q[it].y, t.q[it].z, t.q[it].w};
-        const uint32_t wg[4] = {t.g[it].x, t.g[it].y, t.g[it].z, t.g[it].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          qt_[16 * it + 8 * half + 2 * e][col] = (bf16_t)(wq[e] & 0xffffu);
-          qt_[16 * it + 8 * half + 2 * e + 1][col] = (bf16_t)(wq[e] >> 16);
-          gt_[16 * it + 8 * half + 2 * e][col] = (bf16_t)(wg[e] & 0xffffu);
-          gt_[16 * it + 8 * half + 2 * e + 1][col] = (bf16_t)(wg[e] >> 16);
-        }
-      }
-      if (half == 0) {
-        lse_s[col] = h0 + col < hhi ? t.lse * 1.4426950408889634f : __builtin_huge_valf();  // +inf -> p = 0
-        dl_s[col] = t.dl;
-      }
-      wave_lds_fence();
-      f32x16_t s, dp;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-#pragma unroll
-      for (int x = 0; x < KS; ++x) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, t.q[x]), kf[x], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, t.g[x]), vf[x], dp, 0, 0, 0);
-      }
-      f32x16_t pr;
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        float4 l4 = *reinterpret_cast<const float4*>(&lse_s[8 * gq + 4 * half]);
-        float4 d4 = *reinterpret_cast<const float4*>(&dl_s[8 * gq + 4 * half]);
-        float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int e = 4 * gq + u;
-          float p = fast_exp2(fmaf(s[e], scale_log2e, -lv[u]));
-          p = kvalid ? p : 0.f;
-          pr[e] = p;
-          s[e] = p * (dp[e] - dv4[u]);
-        }
-      }
-#pragma unroll
-      for (int G = 0; G < 2; ++G) {
-        bf16x8_t pf = pack8(pr, 2 * G, 2 * G + 1);
-        bf16x8_t df = pack8(s, 2 * G, 2 * G + 1);
-#pragma unroll
-        for (int t = 0; t < DT; ++t) {
-          bf16x8_t ag = ld_tr8(&gt_[32 * t + col][0], 16 * G, half);
-          dv[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag, pf, dv[t], 0, 0, 0);
-          bf16x8_t aq = ld_tr8(&qt_[32 * t + col][0], 16 * G, half);
-          dk[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, df, dk[t], 0, 0, 0);
-        }
-      }
-    };
-    if constexpr (D == 64) {
-      HT ta, tb;
-      gather(ta, hfirst);
-      for (int h0 = hfirst; h0 < hhi; h0 += 2 * step) {
-        gather(tb, h0 + step);
-        use(ta, h0);
-        if (h0 + step < hhi) {
-          gather(ta, h0 + 2 * step);
-          use(tb, h0 + step);
-        }
-      }
-    } else {  // two buffers do not fit the registers at D = 128
-      for (int h0 = hfirst; h0 < hhi; h0 += step) {
-        HT ta;
-        gather(ta, h0);
-        use(ta, h0);
-      }
-    }
-    if (kvalid) {
-      // slice 0 owns the gradient rows; a later slice leaves its share in its own partial rows [dK | dV]
-      float* pk = sl == 0 ? dKs + ((size_t)hk * N + mk) * D : part + ((((size_t)(sl - 1) * HK + hk) * N + mk) * 2) * D;
-      float* pv = sl == 0 ? dVs + ((size_t)hk * N + mk) * D : pk + D;
-#pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int o = 32 * t + 8 * g + 4 * half;
-          float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
-          if (sl == 0) { a = *reinterpret_cast<float4*>(pk + o); c = *reinterpret_cast<float4*>(pv + o); }
-          a.x += scale * dk[t][4 * g + 0]; a.y += scale * dk[t][4 * g + 1];
-          a.z += scale * dk[t][4 * g + 2]; a.w += scale * dk[t][4 * g + 3];
-          c.x += dv[t][4 * g + 0]; c.y += dv[t][4 * g + 1]; c.z += dv[t][4 * g + 2]; c.w += dv[t][4 * g + 3];
-          *reinterpret_cast<float4*>(pk + o) = a;
-          *reinterpret_cast<float4*>(pv + o) = c;
-        }
-    }
-  }
-}
-
-// adds the partial rows of the hit slices 1 .. S-1 of every pair to the rows slice 0 owns, in slice order: one workgroup
-// per pair, 16 lanes per key row, a row's slices requested together (one wave with dependent loads took 0.56 ms at 16
-// heads of 64k tokens with 128 x 128 clusters, now 0.40: the rows themselves)
-template <int D>
-__global__ void __launch_bounds__(256) k_c3_reduce(const int32_t* __restrict__ off_k, const int32_t* __restrict__ pair_off,
-                                                   const int32_t* __restrict__ c3_off, const int2* __restrict__ c3_map,
-                                                   const float* __restrict__ part, float* __restrict__ dKs,
-                                                   float* __restrict__ dVs, size_t run_cap, int N, int nb, int Ck, int HK) {
-  // walks the same item list as k_c3_pairs: the item (pair, slice 1) exists exactly for the pairs with partial rows
-  const int hk = blockIdx.y, NBm = nb - 1;
-  if ((int)blockIdx.x >= c3_off[(size_t)hk * ((size_t)NBm * Ck + 1) + (size_t)NBm * Ck]) return;
-  const int2 item = c3_map[(size_t)hk * run_cap + blockIdx.x];
-  if (item.y != 1) return;
-  const int32_t* po = pair_off + (size_t)hk * ((size_t)NBm * Ck + 1) + item.x;
-  const int S = c3_slices(po[1] - po[0]);  // every slice has at least kC3TilesPerSlice - 1 hit tiles
-  const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
-  const int klo = ok[item.x], khi = ok[item.x + 1];
-  const int sub = threadIdx.x / 16, l16 = threadIdx.x % 16;
-  for (int m = klo + sub; m < khi; m += 16)
-#pragma unroll
-    for (int d0 = 0; d0 < 2 * D; d0 += 64) {  // the row pair [dK | dV] as 2 D floats
-      const int d = d0 + 4 * l16;
-      float* dst = (d0 < D ? dKs : dVs - D) + ((size_t)hk * N + m) * D + d;
-      float4 a = *reinterpret_cast<float4*>(dst), x[kC3Slices - 1];
-#pragma unroll
-      for (int s = 1; s < kC3Slices; ++s)
-        x[s - 1] = *reinterpret_cast<const float4*>(part + ((((size_t)((s < S ? s : 1) - 1) * HK + hk) * N + m) * 2) * D + d);
-#pragma unroll
-      for (int s = 1; s < kC3Slices; ++s)
-        if (s < S) { a.x += x[s - 1].x; a.y += x[s - 1].y; a.z += x[s - 1].z; a.w += x[s - 1].w; }
-      *reinterpret_cast<float4*>(dst) = a;
-    }
-}
-
-// ------------------------------------------------------------------------------------------
 // Retrieval forward (Sec. 3.3 "Exact retrieval"): one wave per work item, a run of up to kRunTiles hit tiles of one
 // retrieved pair (a heavy pair is many items, a light one a single item); the queries that retrieved the pair are
 // the MFMA columns (32 at a time, rows read straight from Q), its keys the rows.
@@ -1610,32 +1401,6 @@ int muse_launch_ret_bwd_dq_pairs(const MuseDims& d, const void* Q, const void* d
     { MuseProf prof_("k_ret_bwd_dq_pairs", st); hipLaunchKernelGGL(k_ret_bwd_dq_pairs<128>, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, (const bf16_t*)Ks, (const bf16_t*)Vs, LSE, delta, off_k, run_off, run_map, hits, dqpart, run_cap, hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, d.r * d.k2e, d.scale, sl); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
-}
-
-int muse_launch_c3_reduce(const MuseDims& d, FFWorkspace& w, hipStream_t st) {
-  const int HK = d.B * d.Hkv;
-  const dim3 g((unsigned)w.run_cap, HK);
-  MuseProf prof_("k_c3_reduce", st);
-  if (d.D == 64) hipLaunchKernelGGL(k_c3_reduce<64>, g, dim3(256), 0, st, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.c3_part, w.dKs, w.dVs, w.run_cap, d.N, d.nb, d.Ck, HK);
-  else hipLaunchKernelGGL(k_c3_reduce<128>, g, dim3(256), 0, st, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.c3_part, w.dKs, w.dVs, w.run_cap, d.N, d.nb, d.Ck, HK);
-  MUSE_LAUNCH_CHECK();
-  return MUSE_OK;
-}
-
-int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const float* LSE, FFWorkspace& w, hipStream_t st) {
-  const int HK = d.B * d.Hkv;
-  const dim3 g((unsigned)w.run_cap, HK);
-  const float sl = d.scale * 1.4426950408889634f;
-  auto go = [&](auto* kernel) {
-    MuseProf prof_("k_c3_pairs", st);
-    hipLaunchKernelGGL(kernel, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, (const bf16_t*)w.Ks, (const bf16_t*)w.Vs, LSE,
-                       w.delta, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.hits, w.dKs, w.dVs, w.c3_part, w.run_cap, w.hit_cap, d.N,
-                       d.nb, d.Ck, d.Hq, d.Hkv, HK, d.scale, sl);
-  };
-  if (d.D == 64) go(k_c3_pairs<64>);
-  else go(k_c3_pairs<128>);
-  MUSE_LAUNCH_CHECK();
-  return muse_launch_c3_reduce(d, w, st);
 }
 
 int muse_launch_attn_fwd_mfma(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V,

@@ -245,12 +245,19 @@ constexpr int kMaxCk = 2304;  // key clusters a kernel can index in LDS
 static_assert(kMaxCk >= MUSE_MAX_CLUSTERS, "the host accepts more clusters than the kernels index");
 constexpr int kRunTiles = 4;  // hit tiles (of 32) per work item of the retrieval forward / dq pair kernels
 constexpr int kC3Slices = 8;  // most waves that share the hits of one retrieved pair in the key/value gradients
-constexpr int kC3TilesPerSlice = 4;  // a pair gets one slice per so many tiles of 32 hits
-// hit slices of a pair in the key/value gradient kernel of the retrieval (depends on its hit count only)
-__host__ __device__ inline int c3_slices(int nhits) {
+// hit slices of a pair in the key/value gradient kernels of the retrieval: one per `tps` tiles of 32 hits
+__host__ __device__ inline int c3_slices(int nhits, int tps) {
   const int nt = (nhits + 31) / 32;
-  const int s = nt / kC3TilesPerSlice;
+  const int s = nt / tps;
   return s < 1 ? 1 : (s > kC3Slices ? kC3Slices : s);
+}
+// Tiles per slice.  A further slice costs a partial row of dK and dV per key, written and read again (as many bytes as the
+// gathered rows of four tiles), so where the problem fills the device with long slices (4096 of them), they are long: at
+// 16 heads of 64k tokens with 128 x 128 clusters 16 tiles against 4 take 1.22 + 0.16 ms (kernel + reduction) against
+// 1.55 + 0.39, at 12 heads of 6k 4 tiles are what keeps the device busy.
+static inline int ff_c3_tiles(const MuseDims& d) {
+  const size_t tiles = (size_t)d.B * d.Hq * d.N * (d.r > 0 ? d.r : 1) * d.k2e / 32 / 4096;
+  return tiles < 4 ? 4 : tiles > 16 ? 16 : (int)tiles;
 }
 
 struct FFWorkspace {
@@ -377,7 +384,7 @@ template <typename T>
 int muse_launch_chain_grads(const MuseDims& d, const T* Q, const T* dO, const float* qc, const float* LSE, FFWorkspace& w,
                             int h0, int hn, hipStream_t st);
 
-// attn_mfma.hip
+// retrieval_kv.hip
 int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const float* LSE, FFWorkspace& w, hipStream_t st);
 // adds the partial rows of the later hit slices of every pair to dKs, dVs
 int muse_launch_c3_reduce(const MuseDims& d, FFWorkspace& w, hipStream_t st);

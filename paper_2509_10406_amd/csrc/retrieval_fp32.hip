@@ -16,7 +16,7 @@ __global__ void __launch_bounds__(64) k_c3_pairs_f32(
     const float* __restrict__ LSE, const float* __restrict__ delta, const int32_t* __restrict__ off_k,
     const int32_t* __restrict__ pair_off, const int32_t* __restrict__ c3_off, const int2* __restrict__ c3_map,
     const uint2* __restrict__ hits, float* __restrict__ dKs, float* __restrict__ dVs, float* __restrict__ part,
-    size_t run_cap, size_t hit_cap, int N, int nb, int Ck, int Hq, int Hkv, int HK, float scale) {
+    size_t run_cap, size_t hit_cap, int N, int nb, int Ck, int Hq, int Hkv, int HK, int tps, float scale) {
   constexpr int MT = D / 16;
   __shared__ __attribute__((aligned(16))) float qrow[16][D + 4];
   __shared__ __attribute__((aligned(16))) float grow[16][D + 4];
@@ -32,7 +32,7 @@ __global__ void __launch_bounds__(64) k_c3_pairs_f32(
   const int32_t* po = pair_off + (size_t)hk * ((size_t)NBm * Ck + 1) + item.x;
   const int hlo = po[0], hhi = po[1];
   if (klo == khi) return;
-  const int step = 32 * c3_slices(hhi - hlo);  // the slice's tiles of 32 hits, two tiles of 16 here
+  const int step = 32 * c3_slices(hhi - hlo, tps);  // the slice's tiles of 32 hits, two tiles of 16 here
   const uint2* hh = hits + (size_t)hk * hit_cap;
   for (int k0 = klo; k0 < khi; k0 += 16) {
     const bool kvalid = k0 + c16 < khi;
@@ -127,7 +127,7 @@ int muse_launch_c3_pairs_f32(const MuseDims& d, const float* Q, const float* dO,
   auto go = [&](auto* kernel) {
     MuseProf prof_("k_c3_pairs_f32", st);
     hipLaunchKernelGGL(kernel, g, dim3(64), 0, st, Q, dO, (const float*)w.Ks, (const float*)w.Vs, LSE, w.delta, w.off_k, w.pair_off,
-                       w.c3_off, w.c3_map, w.hits, w.dKs, w.dVs, w.c3_part, w.run_cap, w.hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, HK, d.scale);
+                       w.c3_off, w.c3_map, w.hits, w.dKs, w.dVs, w.c3_part, w.run_cap, w.hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, HK, ff_c3_tiles(d), d.scale);
   };
   if (d.D == 64) go(k_c3_pairs_f32<64>);
   else go(k_c3_pairs_f32<128>);
