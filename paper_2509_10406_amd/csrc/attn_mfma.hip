@@ -911,289 +911,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 }
 
 // ------------------------------------------------------------------------------------------
-// Retrieval forward (Sec. 3.3 "Exact retrieval"): one wave per work item, a run of up to kRunTiles hit tiles of one
-// retrieved pair (a heavy pair is many items, a light one a single item); the queries that retrieved the pair are
-// the MFMA columns (32 at a time, rows read straight from Q), its keys the rows.
-// A pair rarely has more than 32 keys: its key fragments and transposed value tile are then loaded once
-// and reused by every hit tile; the hit list of the next tile is fetched while this one is computed.
-// Writes, per (query, slot), the partial softmax state over the keys of the pair:
-//   part[(qn*R2 + su)][0..D) = sum_m exp(l_m - max) v_m,  [D] = max (natural log units),  [D+1] = sum.
-// ------------------------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, 4))) k_ret_fwd_pairs(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Ks,
-                                                       const bf16_t* __restrict__ Vs, const int32_t* __restrict__ off_k,
-                                                       const int32_t* __restrict__ run_off, const int4* __restrict__ run_map,
-                                                       const uint2* __restrict__ hits, float* __restrict__ part,
-                                                       size_t run_cap, size_t hit_cap, int N, int nb, int Ck,
-                                                       int Hq, int Hkv, int R2, float scale_log2e) {
-  constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, NIT = 32 * CPR / 64;
-  __shared__ __attribute__((aligned(16))) bf16_t vt[D][32 + TPAD];
-  const int hk = blockIdx.y, NBm = nb - 1;
-  if ((int)blockIdx.x >= run_off[(size_t)hk * ((size_t)NBm * Ck + 1) + (size_t)NBm * Ck]) return;  // past the last work item
-  const int4 item = run_map[(size_t)hk * run_cap + blockIdx.x];  // (pair, first hit, end)
-  const int G_ = Hq / Hkv;
-  const size_t hqbase = (size_t)(hk / Hkv) * Hq + (size_t)(hk % Hkv) * G_;
-  const int lane = threadIdx.x, col = lane % 32, half = lane / 32;
-  const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
-  const int klo = ok[item.x], khi = ok[item.x + 1];  // pair = b' Ck + j indexes the segment table directly
-  const int hlo = item.y, hhi = item.z;
-  if (klo == khi) return;
-  const uint2* hh = hits + (size_t)hk * hit_cap;
-  const bool single = khi - klo <= 32;
-  bf16x8_t kf[KS];
-  auto stage = [&](int k0) {  // key fragments of row `col` and the transposed value tile of keys k0 .. k0+31
-    uint4 v[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int c = lane + 64 * it, row = c % 32, cc = c / 32;  // lanes along the rows: conflict-free transposed stores
-      const int kr = k0 + row < khi ? k0 + row : khi - 1;
-      v[it] = *reinterpret_cast<const uint4*>(Vs + ((size_t)hk * N + kr) * D + cc * 8);
-    }
-    const int kr = k0 + col < khi ? k0 + col : khi - 1;
-#pragma unroll
-    for (int x = 0; x < KS; ++x)
-      kf[x] = *reinterpret_cast<const bf16x8_t*>(Ks + ((size_t)hk * N + kr) * D + 16 * x + 8 * half);
-    wave_lds_fence();
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int c = lane + 64 * it, row = c % 32, cc = c / 32;  // lanes along the rows: conflict-free transposed stores
-      const bf16_t* pv = reinterpret_cast<const bf16_t*>(&v[it]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vt[cc * 8 + e][row] = pv[e];
-    }
-    wave_lds_fence();
-  };
-  // the hits of all the item's tiles are requested at once, and the query rows of tile t + 1 while tile t is
-  // computed: one memory round trip per item after the first tile, not two per tile
-  uint2 hitv[kRunTiles];
-#pragma unroll
-  for (int t = 0; t < kRunTiles; ++t) {
-    const int h = hlo + 32 * t + col;
-    hitv[t] = hh[h < hhi ? h : hhi - 1];
-  }
-  if (single) stage(klo);
-  auto qrow = [&](const uint2 h) { return (hqbase + (h.x >> 22)) * N + (h.x & 0x3fffffu); };
-  bf16x8_t qnext[KS];
-  {
-    const size_t q0 = qrow(hitv[0]);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) qnext[s] = *reinterpret_cast<const bf16x8_t*>(Q + q0 * D + 16 * s + 8 * half);
-  }
-#pragma unroll
-  for (int ti = 0; ti < kRunTiles; ++ti) {
-    const int h0 = hlo + 32 * ti;
-    if (h0 >= hhi) break;
-    const bool hvalid = h0 + col < hhi;
-    const uint2 hcur = hitv[ti];
-    const size_t qn = qrow(hcur);
-    bf16x8_t qf[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) qf[s] = qnext[s];
-    if (ti + 1 < kRunTiles && h0 + 32 < hhi) {
-      const size_t q1 = qrow(hitv[ti + 1 < kRunTiles ? ti + 1 : ti]);
-#pragma unroll
-      for (int s = 0; s < KS; ++s) qnext[s] = *reinterpret_cast<const bf16x8_t*>(Q + q1 * D + 16 * s + 8 * half);
-    }
-    f32x16_t o[DT];
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) o[t][e] = 0.f;
-    float m = MUSE_NEG_INF, l = 0.f;
-    for (int k0 = klo; k0 < khi; k0 += 32) {
-      if (!single) stage(k0);
-      f32x16_t s;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) s[e] = 0.f;
-#pragma unroll
-      for (int x = 0; x < KS; ++x) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[x], qf[x], s, 0, 0, 0);
-      float tmax = MUSE_NEG_INF;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int kg = k0 + 8 * (e / 4) + 4 * half + (e % 4);
-        if (kg >= khi) s[e] = MUSE_NEG_INF;
-        tmax = fmaxf(tmax, s[e]);
-      }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-      const float mn = fmaxf(m, tmax * scale_log2e);
-      const float alpha = fast_exp2(m - mn);  // every tile holds at least one key, so mn is finite
-      float psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float p = fast_exp2(fmaf(s[e], scale_log2e, -mn));
-        s[e] = p;
-        psum += p;
-      }
-      l = l * alpha + psum;
-      m = mn;
-#pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) o[t][e] *= alpha;
-#pragma unroll
-      for (int G = 0; G < 2; ++G) {
-        bf16x8_t pf = pack8(s, 2 * G, 2 * G + 1);
-#pragma unroll
-        for (int t = 0; t < DT; ++t) {
-          bf16x8_t a = ld_tr8(&vt[32 * t + col][0], 16 * G, half);
-          o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf, o[t], 0, 0, 0);
-        }
-      }
-    }
-    l += __shfl_xor(l, 32, 64);
-    if (hvalid) {
-      float* pr = part + (qn * R2 + hcur.y) * (size_t)(D + 4);
-#pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<float4*>(pr + 32 * t + 8 * g + 4 * half) =
-              make_float4(o[t][4 * g], o[t][4 * g + 1], o[t][4 * g + 2], o[t][4 * g + 3]);
-      if (half == 0) { pr[D] = m * 0.6931471805599453f; pr[D + 1] = l; }
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------
-// Retrieval backward, gradient w.r.t. the queries: same tiling as the forward pair kernel;
-// dqpart[(qn*R2 + su)][0..D) = scale * sum_m dl_m k_m over the keys of the pair.
-// ------------------------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, 3))) k_ret_bwd_dq_pairs(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ dO,
-                                                          const bf16_t* __restrict__ Ks, const bf16_t* __restrict__ Vs,
-                                                          const float* __restrict__ LSE, const float* __restrict__ delta,
-                                                          const int32_t* __restrict__ off_k,
-                                                          const int32_t* __restrict__ run_off,
-                                                          const int4* __restrict__ run_map,
-                                                          const uint2* __restrict__ hits, float* __restrict__ dqpart,
-                                                          size_t run_cap, size_t hit_cap, int N, int nb, int Ck, int Hq,
-                                                          int Hkv, int R2, float scale, float scale_log2e) {
-  constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, NIT = 32 * CPR / 64;
-  __shared__ __attribute__((aligned(16))) bf16_t kt_[D][32 + TPAD];
-  const int hk = blockIdx.y, NBm = nb - 1;
-  if ((int)blockIdx.x >= run_off[(size_t)hk * ((size_t)NBm * Ck + 1) + (size_t)NBm * Ck]) return;  // past the last work item
-  const int4 item = run_map[(size_t)hk * run_cap + blockIdx.x];  // (pair, first hit, end)
-  const int G_ = Hq / Hkv;
-  const size_t hqbase = (size_t)(hk / Hkv) * Hq + (size_t)(hk % Hkv) * G_;
-  const int lane = threadIdx.x, col = lane % 32, half = lane / 32;
-  const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
-  const int klo = ok[item.x], khi = ok[item.x + 1];  // pair = b' Ck + j indexes the segment table directly
-  const int hlo = item.y, hhi = item.z;
-  if (klo == khi) return;
-  const uint2* hh = hits + (size_t)hk * hit_cap;
-  const bool single = khi - klo <= 32;
-  bf16x8_t kf[KS], vf[KS];
-  auto stage = [&](int k0) {  // key / value fragments of row `col` and the transposed key tile of keys k0 .. k0+31
-    uint4 v[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int c = lane + 64 * it, row = c % 32, cc = c / 32;  // lanes along the rows: conflict-free transposed stores
-      const int kr = k0 + row < khi ? k0 + row : khi - 1;
-      v[it] = *reinterpret_cast<const uint4*>(Ks + ((size_t)hk * N + kr) * D + cc * 8);
-    }
-    const int kr = k0 + col < khi ? k0 + col : khi - 1;
-#pragma unroll
-    for (int x = 0; x < KS; ++x) {
-      kf[x] = *reinterpret_cast<const bf16x8_t*>(Ks + ((size_t)hk * N + kr) * D + 16 * x + 8 * half);
-      vf[x] = *reinterpret_cast<const bf16x8_t*>(Vs + ((size_t)hk * N + kr) * D + 16 * x + 8 * half);
-    }
-    wave_lds_fence();
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int c = lane + 64 * it, row = c % 32, cc = c / 32;  // lanes along the rows: conflict-free transposed stores
-      const bf16_t* pv = reinterpret_cast<const bf16_t*>(&v[it]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) kt_[cc * 8 + e][row] = pv[e];
-    }
-    wave_lds_fence();
-  };
-  // the hits of all the item's tiles are requested at once, and the rows of tile t + 1 while tile t is computed
-  uint2 hitv[kRunTiles];
-#pragma unroll
-  for (int t = 0; t < kRunTiles; ++t) {
-    const int h = hlo + 32 * t + col;
-    hitv[t] = hh[h < hhi ? h : hhi - 1];
-  }
-  if (single) stage(klo);
-  auto qrow = [&](const uint2 h) { return (hqbase + (h.x >> 22)) * N + (h.x & 0x3fffffu); };
-  bf16x8_t qnext[KS], gnext[KS];
-  float lnext, dnext;
-  {
-    const size_t q0 = qrow(hitv[0]);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      qnext[s] = *reinterpret_cast<const bf16x8_t*>(Q + q0 * D + 16 * s + 8 * half);
-      gnext[s] = *reinterpret_cast<const bf16x8_t*>(dO + q0 * D + 16 * s + 8 * half);
-    }
-    lnext = LSE[q0];
-    dnext = delta[q0];
-  }
-#pragma unroll
-  for (int ti = 0; ti < kRunTiles; ++ti) {
-    const int h0 = hlo + 32 * ti;
-    if (h0 >= hhi) break;
-    const bool hvalid = h0 + col < hhi;
-    const uint2 hcur = hitv[ti];
-    const size_t qn = qrow(hcur);
-    bf16x8_t qf[KS], gf[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) { qf[s] = qnext[s]; gf[s] = gnext[s]; }
-    const float lse2 = lnext * 1.4426950408889634f, dl = dnext;
-    if (ti + 1 < kRunTiles && h0 + 32 < hhi) {
-      const size_t q1 = qrow(hitv[ti + 1 < kRunTiles ? ti + 1 : ti]);
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        qnext[s] = *reinterpret_cast<const bf16x8_t*>(Q + q1 * D + 16 * s + 8 * half);
-        gnext[s] = *reinterpret_cast<const bf16x8_t*>(dO + q1 * D + 16 * s + 8 * half);
-      }
-      lnext = LSE[q1];
-      dnext = delta[q1];
-    }
-    f32x16_t dq[DT];
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) dq[t][e] = 0.f;
-    for (int k0 = klo; k0 < khi; k0 += 32) {
-      if (!single) stage(k0);
-      f32x16_t s, dp;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-#pragma unroll
-      for (int x = 0; x < KS; ++x) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[x], qf[x], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[x], gf[x], dp, 0, 0, 0);
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int kg = k0 + 8 * (e / 4) + 4 * half + (e % 4);
-        float p = fast_exp2(fmaf(s[e], scale_log2e, -lse2));
-        p = kg < khi ? p : 0.f;
-        s[e] = p * (dp[e] - dl);
-      }
-#pragma unroll
-      for (int G = 0; G < 2; ++G) {
-        bf16x8_t df = pack8(s, 2 * G, 2 * G + 1);
-#pragma unroll
-        for (int t = 0; t < DT; ++t) {
-          bf16x8_t a = ld_tr8(&kt_[32 * t + col][0], 16 * G, half);
-          dq[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, df, dq[t], 0, 0, 0);
-        }
-      }
-    }
-    if (hvalid) {
-      float* pr = dqpart + (qn * R2 + hcur.y) * (size_t)D;
-#pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<float4*>(pr + 32 * t + 8 * g + 4 * half) =
-              make_float4(scale * dq[t][4 * g], scale * dq[t][4 * g + 1], scale * dq[t][4 * g + 2], scale * dq[t][4 * g + 3]);
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------
 // Summary gradients -> keys and values for bf16 inputs: one wave per (kv head, key block b', key
 // cluster j); the keys of the segment are the MFMA columns, 32 query clusters at a time the rows.
 //   W[i,m] = exp(L[i,m] - mu[i]),  T[i,m] = G_c[i] + G_k[i].k_m + G_v[i].v_m
@@ -1371,34 +1088,6 @@ int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* 
     { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<64>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcT, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, dKs, dVs, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
   else
     { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<128>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcT, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, dKs, dVs, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
-  MUSE_LAUNCH_CHECK();
-  return MUSE_OK;
-}
-
-int muse_launch_ret_fwd_pairs(const MuseDims& d, const void* Q, const void* Ks, const void* Vs, const int32_t* off_k,
-                              const int32_t* run_off, const int4* run_map, size_t run_cap, const uint2* hits,
-                              size_t hit_cap, float* part, hipStream_t st) {
-  // one wave per work item (a run of hit tiles inside one pair); the grid covers the most there can be
-  dim3 g((unsigned)run_cap, d.B * d.Hkv);
-  float sl = d.scale * 1.4426950408889634f;
-  if (d.D == 64)
-    { MuseProf prof_("k_ret_fwd_pairs", st); hipLaunchKernelGGL(k_ret_fwd_pairs<64>, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)Ks, (const bf16_t*)Vs, off_k, run_off, run_map, hits, part, run_cap, hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, d.r * d.k2e, sl); }
-  else
-    { MuseProf prof_("k_ret_fwd_pairs", st); hipLaunchKernelGGL(k_ret_fwd_pairs<128>, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)Ks, (const bf16_t*)Vs, off_k, run_off, run_map, hits, part, run_cap, hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, d.r * d.k2e, sl); }
-  MUSE_LAUNCH_CHECK();
-  return MUSE_OK;
-}
-
-int muse_launch_ret_bwd_dq_pairs(const MuseDims& d, const void* Q, const void* dO, const void* Ks, const void* Vs,
-                                 const float* LSE, const float* delta, const int32_t* off_k, const int32_t* run_off,
-                                 const int4* run_map, size_t run_cap, const uint2* hits, size_t hit_cap, float* dqpart,
-                                 hipStream_t st) {
-  dim3 g((unsigned)run_cap, d.B * d.Hkv);
-  float sl = d.scale * 1.4426950408889634f;
-  if (d.D == 64)
-    { MuseProf prof_("k_ret_bwd_dq_pairs", st); hipLaunchKernelGGL(k_ret_bwd_dq_pairs<64>, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, (const bf16_t*)Ks, (const bf16_t*)Vs, LSE, delta, off_k, run_off, run_map, hits, dqpart, run_cap, hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, d.r * d.k2e, d.scale, sl); }
-  else
-    { MuseProf prof_("k_ret_bwd_dq_pairs", st); hipLaunchKernelGGL(k_ret_bwd_dq_pairs<128>, g, dim3(64), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, (const bf16_t*)Ks, (const bf16_t*)Vs, LSE, delta, off_k, run_off, run_map, hits, dqpart, run_cap, hit_cap, d.N, d.nb, d.Ck, d.Hq, d.Hkv, d.r * d.k2e, d.scale, sl); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

@@ -279,7 +279,7 @@ struct FFWorkspace {
   int32_t *seg_cnt, *seg_off;    // its construction: counts / list starts [HK][head of the group x query slice][pair]
   uint2* hits;                   // x = n | g << 22 (query position, head inside the KV group), y = slot*k2e + u
   size_t hit_cap;                // hits per kv head
-  float* ret_part;               // per (query, slot, u): forward partial state [acc D | max | sum | pad2], or dq partial [D]
+  float* ret_part;               // per (query, slot, u): forward partial rows [D], then (max, sum) [2] of all rows; or dq partial rows [D]
   float* knorm;                  // [HK]: largest Euclidean norm of a key row of the kv head (bf16 inputs); then [HK][64] partial maxima
   int32_t* ff_flag;              // [HQ][nb-1][ff_tile_grid_x]: tiles the one-plane forward kernel leaves to the two-plane one
   float *dKs, *dVs;            // fp32 gradients in bucketed key order
@@ -390,7 +390,7 @@ int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const
 int muse_launch_c3_reduce(const MuseDims& d, FFWorkspace& w, hipStream_t st);
 // retrieval_fp32.hip
 int muse_launch_c3_pairs_f32(const MuseDims& d, const float* Q, const float* dO, const float* LSE, FFWorkspace& w, hipStream_t st);
-// attn_mfma.hip
+// retrieval_q.hip
 int muse_launch_ret_fwd_pairs(const MuseDims& d, const void* Q, const void* Ks, const void* Vs, const int32_t* off_k,
                               const int32_t* run_off, const int4* run_map, size_t run_cap, const uint2* hits,
                               size_t hit_cap, float* part, hipStream_t st);
@@ -398,6 +398,7 @@ int muse_launch_ret_bwd_dq_pairs(const MuseDims& d, const void* Q, const void* d
                                  const float* LSE, const float* delta, const int32_t* off_k, const int32_t* run_off,
                                  const int4* run_map, size_t run_cap, const uint2* hits, size_t hit_cap, float* dqpart,
                                  hipStream_t st);
+// attn_mfma.hip
 int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* Vs, const float* qc, void* qcT,
                                  const float* L, const float* s_mu, const float* G_c, const void* G_k, const void* G_v,
                                  const int32_t* off_k, float* dKs, float* dVs, int h0, int hn, hipStream_t st);

@@ -168,9 +168,9 @@ __global__ void __launch_bounds__(1024) k_pair_scan(const int32_t* __restrict__ 
 }
 
 // far-field state of every query  <-  state (+) partial states of its retrieved pairs.
-// D/4 lanes per query, each owning 4 dims; part rows are [acc D | max | sum | pad2].
+// D/4 lanes per query, each owning 4 dims; part rows are [D], and (max, sum) of all rows follow them.
 __global__ void __launch_bounds__(256) k_merge_ret(const int32_t* __restrict__ selb, const float* __restrict__ part,
-                                                    float* __restrict__ ff_acc, float* __restrict__ ff_ml, size_t nq,
+                                                    const float* __restrict__ part_ml, float* __restrict__ ff_acc, float* __restrict__ ff_ml, size_t nq,
                                                     int N, int Bs, int D, int R2) {
   const int LPQ = D / 4;
   size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -196,9 +196,9 @@ __global__ void __launch_bounds__(256) k_merge_ret(const int32_t* __restrict__ s
 #pragma unroll
     for (int su = 0; su < 8; ++su) {
       const bool ok = su < R2 && selb[q * R2 + (su < R2 ? su : 0)] >= 0;
-      const float* pr = part + (q * R2 + (su < R2 ? su : 0)) * (size_t)(D + 4);
-      ml[su] = ok ? *reinterpret_cast<const float2*>(pr + D) : make_float2(0.f, 0.f);
-      pa[su] = ok ? *reinterpret_cast<const float4*>(pr + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      const size_t at = q * R2 + (su < R2 ? su : 0);
+      ml[su] = ok ? *reinterpret_cast<const float2*>(part_ml + 2 * at) : make_float2(0.f, 0.f);
+      pa[su] = ok ? *reinterpret_cast<const float4*>(part + at * D + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
     for (int su = 0; su < 8; ++su)
@@ -206,10 +206,10 @@ __global__ void __launch_bounds__(256) k_merge_ret(const int32_t* __restrict__ s
   } else {
     for (int su = 0; su < R2; ++su) {
       if (selb[q * R2 + su] < 0) continue;
-      const float* pr = part + (q * R2 + su) * (size_t)(D + 4);
-      const float pm = pr[D], pl = pr[D + 1];
+      const size_t at = q * R2 + su;
+      const float pm = part_ml[2 * at], pl = part_ml[2 * at + 1];
       if (!(pl > 0.f)) continue;
-      fold(pm, pl, *reinterpret_cast<const float4*>(pr + 4 * c));
+      fold(pm, pl, *reinterpret_cast<const float4*>(part + at * D + 4 * c));
     }
   }
   *reinterpret_cast<float4*>(ff_acc + q * D + 4 * c) = a;
@@ -245,7 +245,7 @@ int muse_launch_merge_ret(const MuseDims& d, const int32_t* selb, const float* p
                           hipStream_t st) {
   const size_t nq = (size_t)d.B * d.Hq * d.N;
   const size_t threads = nq * (d.D / 4);
-  { MuseProf prof_("k_merge_ret", st); hipLaunchKernelGGL(k_merge_ret, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, selb, part, ff_acc, ff_ml, nq, d.N, d.Bs, d.D, d.r * d.k2e); }
+  { MuseProf prof_("k_merge_ret", st); hipLaunchKernelGGL(k_merge_ret, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, selb, part, part + nq * d.r * d.k2e * d.D, ff_acc, ff_ml, nq, d.N, d.Bs, d.D, d.r * d.k2e); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

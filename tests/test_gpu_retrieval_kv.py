@@ -1,4 +1,5 @@
-"""GPU parity of the bf16 backward where the retrieval's key/value gradients (retrieval_kv.hip) change form: pairs of up to
+"""GPU parity of the bf16 retrieval where its kernels change form.  Query side (retrieval_q.hip): 64 keys staged at a time,
+so pairs of up to 64 keys and of several stages.  Key/value gradients (retrieval_kv.hip): pairs of up to
 32 keys (the waves share the hits), 33 to 64 (a wave per key tile) and more (several key groups), several hit slices, one
 hit, and grouped queries.  D = 128 with several key groups is bf16_d128_pairs40 of the parity suite (more keys per pair
 than its 40 put the query gradient, another kernel's, at its bound of 2e-2).  Tolerance: the parity suite's."""
