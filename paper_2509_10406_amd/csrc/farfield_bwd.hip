@@ -410,11 +410,14 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
   bwv = __builtin_amdgcn_readfirstlane(bwv);
   auto run = [&](auto bw_c) {
   constexpr int bw = decltype(bw_c)::value;
+  int next = si[0];  // a slot is read a step ahead of its rows: one round trip per slot
   for (int t = 0; t < r; ++t) {
-    const int info = si[t];
+    const int info = next;
+    next = si[t + 1 < r ? t + 1 : t];
     if (info < 0) continue;
     const int j = info & 0xffff;
     const unsigned selbits = (unsigned)info >> 16;
+    if (NBC == 1 && ((selbits + 1u) & ((1u << b) - 1u)) == 0u) continue;  // every preceding block is retrieved
 #pragma unroll
     for (int c0 = 0; c0 < 8 * NBC; c0 += 8) {
       if (c0 >= bw) break;
@@ -424,7 +427,10 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (c0 + u >= bw) break;
-        const int bp = c0 + u < b ? c0 + u : b - 1;
+        int bp = c0 + u < b ? c0 + u : b - 1;
+        // a retrieved block's rows are not used: the neighbour's, requested anyway, instead of rows of their own (the rows
+        // come from the L2, whose rate is what bounds this kernel)
+        if ((selbits >> bp) & 1u) bp = bp > 0 ? bp - 1 : b > 1 ? 1 : 0;
         const size_t cell = (((size_t)hl * NBm + bp) * Cq + i) * Ck + j;
         mu[u] = s_mu[cell];
 #pragma unroll
@@ -486,23 +492,25 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
 #pragma unroll
     for (int t = 0; t < 4; ++t) dq[x][t] *= scale;
   // retrieval part, computed per retrieved pair (already scaled); a slot's pair u exists iff its block bit is set
-  if (k2e == 1 && r <= 8) {
-    // the usual shape: the partial rows of all slots are requested together and added in slot order
-    int inf[8];
+  if (k2e == 1) {
+    // the usual shape: the partial rows of eight slots are requested together and added in slot order
+    for (int t0 = 0; t0 < r; t0 += 8) {
+      int inf[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) inf[t] = t < r ? si[t] : -1;
-    float4 v[8][NG];
+      for (int t = 0; t < 8; ++t) inf[t] = t0 + t < r ? si[t0 + t] : -1;
+      float4 v[8][NG];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const bool ok = inf[t] >= 0 && ((unsigned)inf[t] >> 16) != 0u;
+      for (int t = 0; t < 8; ++t) {
+        const bool ok = inf[t] >= 0 && ((unsigned)inf[t] >> 16) != 0u;
 #pragma unroll
-      for (int x = 0; x < NG; ++x)
-        v[t][x] = ok ? *reinterpret_cast<const float4*>(dqpart + (qn * r + t) * D + 64 * x + 4 * l16) : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int x = 0; x < NG; ++x)
+          v[t][x] = ok ? *reinterpret_cast<const float4*>(dqpart + (qn * r + t0 + t) * D + 64 * x + 4 * l16) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int x = 0; x < NG; ++x) { dq[x][0] += v[t][x].x; dq[x][1] += v[t][x].y; dq[x][2] += v[t][x].z; dq[x][3] += v[t][x].w; }
     }
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-#pragma unroll
-      for (int x = 0; x < NG; ++x) { dq[x][0] += v[t][x].x; dq[x][1] += v[t][x].y; dq[x][2] += v[t][x].z; dq[x][3] += v[t][x].w; }
   } else {
     for (int t = 0; t < r; ++t) {
       const int info = si[t];

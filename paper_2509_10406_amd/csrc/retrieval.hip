@@ -189,28 +189,20 @@ __global__ void __launch_bounds__(256) k_merge_ret(const int32_t* __restrict__ s
     a.z = a.z * ca + pa.z * cb; a.w = a.w * ca + pa.w * cb;
     m = mn;
   };
-  if (R2 <= 8) {
-    // the usual shape: all the query's partial states are requested together and folded in slot order
+  for (int s0 = 0; s0 < R2; s0 += 8) {
+    // eight of the query's partial states are requested together and folded in slot order
     float2 ml[8];
     float4 pa[8];
 #pragma unroll
     for (int su = 0; su < 8; ++su) {
-      const bool ok = su < R2 && selb[q * R2 + (su < R2 ? su : 0)] >= 0;
-      const size_t at = q * R2 + (su < R2 ? su : 0);
+      const size_t at = q * R2 + (s0 + su < R2 ? s0 + su : 0);
+      const bool ok = s0 + su < R2 && selb[at] >= 0;
       ml[su] = ok ? *reinterpret_cast<const float2*>(part_ml + 2 * at) : make_float2(0.f, 0.f);
       pa[su] = ok ? *reinterpret_cast<const float4*>(part + at * D + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
     for (int su = 0; su < 8; ++su)
       if (ml[su].y > 0.f) fold(ml[su].x, ml[su].y, pa[su]);
-  } else {
-    for (int su = 0; su < R2; ++su) {
-      if (selb[q * R2 + su] < 0) continue;
-      const size_t at = q * R2 + su;
-      const float pm = part_ml[2 * at], pl = part_ml[2 * at + 1];
-      if (!(pl > 0.f)) continue;
-      fold(pm, pl, *reinterpret_cast<const float4*>(part + at * D + 4 * c));
-    }
   }
   *reinterpret_cast<float4*>(ff_acc + q * D + 4 * c) = a;
   if (c == 0) { ff_ml[q * 2] = m; ff_ml[q * 2 + 1] = l; }
