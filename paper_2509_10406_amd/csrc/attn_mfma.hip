@@ -13,6 +13,7 @@
 //     half h over 16 keys are keys {4h..4h+3} and {8+4h..8+4h+3}: a permutation applied to both
 //     operands, which a contraction does not see.
 #include "ff_common.h"
+#include "lds_tile.h"
 
 namespace {
 
@@ -594,125 +595,147 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     }
 }
 
-template <int D>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, D == 64 ? 2 : 1))) k_flash_bwd_dkv(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
-                                                        const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
-                                                        const float* __restrict__ LSE, const float* __restrict__ delta,
-                                                        float* __restrict__ dK, float* __restrict__ dV, int N, int Bs,
-                                                        int Hq, int Hkv, int nbatch, float scale, float scale_log2e) {
-  constexpr int KS = D / 16, DT = D / 32;
-  constexpr int BQ = D == 64 ? 64 : 32;  // queries staged per step (LDS budget)
-  __shared__ __attribute__((aligned(16))) bf16_t qs[BQ][D + 8];
-  __shared__ __attribute__((aligned(16))) bf16_t gs[BQ][D + 8];
-  __shared__ __attribute__((aligned(16))) bf16_t qt_[D][BQ + TPAD16];
-  __shared__ __attribute__((aligned(16))) bf16_t gt_[D][BQ + TPAD16];
-  __shared__ __attribute__((aligned(16))) float lse_s[BQ];
-  __shared__ __attribute__((aligned(16))) float dl_s[BQ];
+// dK/dV for D = 128.  One wave with dK and dV of its 32 keys needs 128 accumulator registers beside 64 of keys and values:
+// one wave per SIMD, and nothing runs while it waits.  So two waves share 32 keys: wave w computes P = exp2(c (Q K^T - LSE))
+// and dV += P^T dO, wave w + 4 (on the same SIMD) dP = dO V^T and, a step behind, dS = P dP and dK += dS^T Q; P passes
+// between them through LDS in fp32, one barrier per step of 32 queries.  A step's rows are staged once, row-major for both
+// operand forms (lds_tile.h): Q in three buffers (next, current, the one dK still reads), dO in two.  The accumulators of S
+// and dP start at -LSE / scale and -delta.  The query heads of the group follow one another in one sequence of steps.
+// Matrix pipe 0.45 busy, LDS 0.4, vector 0.4: the three share the time between barriers.  One wave per 32 keys and SIMD with
+// 32 queries staged per two barriers took 1.75 ms at 32 heads of 8k tokens (8 KV heads, exact attention), this 1.39;
+// 3.57 -> 2.82 ms at 32k tokens in blocks of 4096.  One wave per SIMD with the next scores issued between the vector
+// instructions of the current ones took 1.51, this kernel with each role pipelined over two steps 2.09 (spills).
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) k_flash_bwd_dkv128(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
+    const float* __restrict__ LSE, const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV, int N,
+    int Bs, int Hq, int Hkv, int nbatch, float scale, float scale_log2e) {
+  constexpr int D = 128, KS = D / 16, DT = D / 32, BQ = 32, kTile = BQ * D;
+  __shared__ __attribute__((aligned(16))) bf16_t qs[3][kTile];
+  __shared__ __attribute__((aligned(16))) bf16_t gs[2][kTile];
+  __shared__ __attribute__((aligned(16))) float4 px[2][4][4][64];  // P of a step: [wave pair][4 rows][lane]
+  __shared__ __attribute__((aligned(16))) float seeds[2][2][BQ];   // -LSE / scale, -delta
   const FlashTile ft = flash_tile(N, Bs, Hkv, nbatch);
   if (!ft.ok) return;
   const int hk = ft.h, b = ft.b, G_ = Hq / Hkv;
   const size_t kh = ((size_t)b * Hkv + hk) * N;
   const int k0 = (ft.blk * ft.tpg + ft.t) * 128;  // the first key tiles of a block see the most queries
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
-  const int mk = k0 + 32 * wave + col;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, col = lane % 32, half = lane / 32;
+  const int kw = w % 4;
+  const bool second = w >= 4;  // dP and dK
+  const int mk = k0 + 32 * kw + col;
   const int mkc = mk < N ? mk : N - 1;
-  const int myend = min((mkc / Bs + 1) * Bs, N);
+  const int nlen = min((mkc / Bs + 1) * Bs, N) - mk;  // the key's queries are mk .. mk + nlen - 1
   const int qend = min((min(k0 + 127, N - 1) / Bs + 1) * Bs, N);
+  const int nq = (qend - k0 + BQ - 1) / BQ, nt = G_ * nq;  // steps per query head, steps of the group
+  // a tile of 128 keys inside one block with every row in range: only the diagonal needs a mask
+  const bool aligned = (Bs % 128) == 0 && k0 + 128 <= N;
+  const float seed = -1.4426950408889634f / scale_log2e;
 
-  bf16x8_t kf[KS], vf[KS];
+  bf16x8_t kv[KS];
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    kf[s] = *reinterpret_cast<const bf16x8_t*>(K + (kh + mkc) * D + 16 * s + 8 * half);
-    vf[s] = *reinterpret_cast<const bf16x8_t*>(V + (kh + mkc) * D + 16 * s + 8 * half);
-  }
-  f32x16_t dk[DT], dv[DT];
+  for (int x = 0; x < KS; ++x) kv[x] = *reinterpret_cast<const bf16x8_t*>((second ? V : K) + (kh + mkc) * D + 16 * x + 8 * half);
+  f32x16_t acc[DT];
 #pragma unroll
-  for (int t = 0; t < DT; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) { dk[t][e] = 0.f; dv[t][e] = 0.f; }
+  for (int t = 0; t < DT; ++t) acc[t] = zero16();
 
-  for (int g = 0; g < G_; ++g) {
-    const size_t qh = ((size_t)b * Hq + (size_t)hk * G_ + g) * N;
-    TileRegs qreg, greg;
-    float lreg = 0.f, dreg = 0.f;
-    auto fetch = [&](int q0) {
-      fetch_pairs<D, BQ>(Q + qh * D, q0, N, qreg);
-      fetch_pairs<D, BQ>(dO + qh * D, q0, N, greg);
-      if (threadIdx.x < BQ) {
-        int n = q0 + threadIdx.x;
-        n = n < N ? n : N - 1;
-        lreg = LSE[qh + n];
-        dreg = delta[qh + n];
-      }
-    };
-    if (k0 < qend) fetch(k0);
-    for (int q0 = k0; q0 < qend; q0 += BQ) {
-      __syncthreads();
-      commit_pairs<D, BQ, true>(qreg, qs, qt_);
-      commit_pairs<D, BQ, true>(greg, gs, gt_);
-      if (threadIdx.x < BQ) {
-        lse_s[threadIdx.x] = lreg * 1.4426950408889634f;
-        dl_s[threadIdx.x] = dreg;
-      }
-      __syncthreads();
-      if (q0 + BQ < qend) fetch(q0 + BQ);  // in flight while this tile is consumed
-      if (q0 + BQ - 1 < k0 + 32 * wave) continue;  // every query of the tile precedes this wave's keys
-#pragma unroll
-      for (int qt = 0; qt < BQ / 32; ++qt) {
-        f32x16_t s, dp;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-#pragma unroll
-        for (int x = 0; x < KS; ++x) {
-          bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(&qs[32 * qt + col][16 * x + 8 * half]);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[x], s, 0, 0, 0);
-          bf16x8_t ag = *reinterpret_cast<const bf16x8_t*>(&gs[32 * qt + col][16 * x + 8 * half]);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag, vf[x], dp, 0, 0, 0);
-        }
-        f32x16_t pr;
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          float4 l4 = *reinterpret_cast<const float4*>(&lse_s[32 * qt + 8 * gq + 4 * half]);
-          float4 d4 = *reinterpret_cast<const float4*>(&dl_s[32 * qt + 8 * gq + 4 * half]);
-          float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            int e = 4 * gq + u;
-            float p = fast_exp2(fmaf(s[e], scale_log2e, -lv[u]));
-            {
-              int n = q0 + 32 * qt + 8 * gq + 4 * half + u;
-              p = (n < mk || n >= myend) ? 0.f : p;
-            }
-            pr[e] = p;
-            s[e] = p * (dp[e] - dv4[u]);
-          }
-        }
-#pragma unroll
-        for (int G = 0; G < 2; ++G) {
-          bf16x8_t pf = pack8(pr, 2 * G, 2 * G + 1);
-          bf16x8_t df = pack8(s, 2 * G, 2 * G + 1);
-#pragma unroll
-          for (int t = 0; t < DT; ++t) {
-            bf16x8_t ag = ld_tr16(gt_, 32 * t + col, 32 * qt + 16 * G, half);
-            dv[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag, pf, dv[t], 0, 0, 0);
-            bf16x8_t aq = ld_tr16(qt_, 32 * t + col, 32 * qt + 16 * G, half);
-            dk[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, df, dk[t], 0, 0, 0);
-          }
-        }
-      }
+  uint4 qr, gr;  // this thread's chunk of row tid / 16 of a coming step
+  float lr = 0.f;
+  const int sr = tid / 16, sc = tid % 16;
+  const size_t qh0 = ((size_t)b * Hq + (size_t)hk * G_) * N;
+  const bf16_t *qp = Q + qh0 * D + 8 * sc, *gp = dO + qh0 * D + 8 * sc;
+  const float* lp = ((tid / BQ) % 2 ? delta : LSE) + qh0;
+  int fq = k0;  // first query of the next step to fetch
+  auto fetch = [&]() {
+    const int row = min(fq + sr, N - 1);
+    qr = *reinterpret_cast<const uint4*>(qp + (size_t)row * D);
+    gr = *reinterpret_cast<const uint4*>(gp + (size_t)row * D);
+    lr = lp[min(fq + tid % BQ, N - 1)];
+    fq += BQ;
+    if (fq >= qend) {  // on to the next query head
+      fq = k0;
+      qp += (size_t)N * D;
+      gp += (size_t)N * D;
+      lp += N;
     }
+  };
+  auto commit = [&](int bq, int bg) {
+    const int at = tile_at<D>(sr, sc);
+    *reinterpret_cast<uint4*>(qs[bq] + at) = qr;
+    *reinterpret_cast<uint4*>(gs[bg] + at) = gr;
+    if (tid < 2 * BQ) seeds[bg][tid / BQ][tid % BQ] = lr * (tid < BQ ? seed : -1.f);
+  };
+  // 32 staged rows times the wave's keys or values
+  auto scores = [&](const bf16_t* rows, const float* sd) {
+    f32x16_t s;
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      const float4 x = *reinterpret_cast<const float4*>(sd + 8 * gq + 4 * half);
+      s[4 * gq + 0] = x.x; s[4 * gq + 1] = x.y; s[4 * gq + 2] = x.z; s[4 * gq + 3] = x.w;
+    }
+#pragma unroll
+    for (int x = 0; x < KS; ++x) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_row<D>(rows, col, 2 * x + half), kv[x], s, 0, 0, 0);
+    return s;
+  };
+  const int rr = 4 * half + (lane % 16) / 4, cc = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+  auto grads = [&](const bf16_t* rows, const f32x16_t& p) {  // acc += rows^T p
+#pragma unroll
+    for (int G = 0; G < 2; ++G) {
+      const bf16x8_t pf = pack8(p, 2 * G, 2 * G + 1);
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            tr_join(tile_tr4<D>(rows, 16 * G + rr, 32 * t + cc), tile_tr4<D>(rows, 16 * G + rr + 8, 32 * t + cc)), pf, acc[t], 0, 0, 0);
+    }
+  };
+  f32x16_t dp = zero16();
+  auto finish = [&](int bq, int bp) {  // dS of a step from its P and dP, into dK
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      const float4 p = px[bp][kw][gq][lane];
+      dp[4 * gq] *= p.x; dp[4 * gq + 1] *= p.y; dp[4 * gq + 2] *= p.z; dp[4 * gq + 3] *= p.w;
+    }
+    grads(qs[bq], dp);
+  };
+  fetch();
+  commit(0, 0);
+  __syncthreads();
+  if (nt > 1) fetch();
+  int bq = 0, q0 = k0;
+  for (int T = 0; T < nt; ++T) {
+    const int bn = bq == 2 ? 0 : bq + 1, bl = bq == 0 ? 2 : bq - 1, bg = T & 1;
+    if (T + 1 < nt) commit(bn, bg ^ 1);  // buffers last read before the previous barrier
+    if (T + 2 < nt) fetch();
+    if (!second) {
+      f32x16_t s = scores(qs[bq], seeds[bg][0]);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[e] = fast_exp2(s[e] * scale_log2e);
+      if (!aligned || q0 < k0 + 32 * kw + 32) {
+        const int nm = q0 + 4 * half - mk;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = (unsigned)(nm + 8 * (e / 4) + e % 4) < (unsigned)nlen ? s[e] : 0.f;
+      }
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) px[bg][kw][gq][lane] = make_float4(s[4 * gq], s[4 * gq + 1], s[4 * gq + 2], s[4 * gq + 3]);
+      grads(gs[bg], s);
+    } else {
+      if (T > 0) finish(bl, bg ^ 1);
+      dp = scores(gs[bg], seeds[bg][1]);
+    }
+    __syncthreads();
+    bq = bn;
+    q0 = q0 + BQ < qend ? q0 + BQ : k0;
   }
+  if (second) finish(bq == 0 ? 2 : bq - 1, (nt - 1) & 1);
   if (mk >= N) return;
+  float* out = (second ? dK : dV) + (kh + mk) * D;
+  const float mul = second ? scale : 1.f;
 #pragma unroll
   for (int t = 0; t < DT; ++t)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < 4; ++g)
       // every key row belongs to exactly one tile (the query heads of the group are summed in registers)
-      size_t o = (kh + mk) * D + 32 * t + 8 * g + 4 * half;
-      *reinterpret_cast<float4*>(dK + o) =
-          make_float4(scale * dk[t][4 * g + 0], scale * dk[t][4 * g + 1], scale * dk[t][4 * g + 2], scale * dk[t][4 * g + 3]);
-      *reinterpret_cast<float4*>(dV + o) = make_float4(dv[t][4 * g + 0], dv[t][4 * g + 1], dv[t][4 * g + 2], dv[t][4 * g + 3]);
-    }
+      *reinterpret_cast<float4*>(out + 32 * t + 8 * g + 4 * half) =
+          make_float4(mul * acc[t][4 * g + 0], mul * acc[t][4 * g + 1], mul * acc[t][4 * g + 2], mul * acc[t][4 * g + 3]);
 }
 
 // dK/dV of the block diagonal for D = 64, arranged in phases so that a wave never waits for LDS right before a
@@ -1118,7 +1141,7 @@ int muse_launch_attn_bwd_mfma(const MuseDims& d, int Bs, const void* Q, const vo
     { MuseProf prof_("k_flash_bwd_dkv", st); hipLaunchKernelGGL(k_flash_bwd_dkv_p<64>, gk, dim3(256), 0, st, q, k, v, g, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl); }
   } else {
     { MuseProf prof_("k_flash_bwd_dq", st); hipLaunchKernelGGL(k_flash_bwd_dq<128>, gq, dim3(256), 0, st, q, k, v, g, LSE, delta, dQacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl); }
-    { MuseProf prof_("k_flash_bwd_dkv", st); hipLaunchKernelGGL(k_flash_bwd_dkv<128>, gk, dim3(256), 0, st, q, k, v, g, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl); }
+    { MuseProf prof_("k_flash_bwd_dkv", st); hipLaunchKernelGGL(k_flash_bwd_dkv128, gk, dim3(512), 0, st, q, k, v, g, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl); }
   }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
