@@ -11,6 +11,7 @@
 // the remainder (>= 19 significant bits, exact products, fp32 accumulation) on the 16-bit matrix cores, and the
 // block selection scores stay fp32.
 #include "ff_common.h"
+#include "lds_tile.h"
 
 #include <type_traits>
 
@@ -879,8 +880,12 @@ __global__ void __launch_bounds__(64) k_key_norm_max(const float* __restrict__ p
 // entries; a tile where one overflows (many near-equal scores) is flagged and left to the two-plane kernel, which
 // runs as a second launch over the flagged tiles only.
 // ------------------------------------------------------------------------------------------
+// Two waves per SIMD at both head dims: at D = 128 one wave with all its registers (360) and 23 KB of lists and values took
+// 6.85 ms at 32 heads of 32k with 128 x 512 clusters (15 GB of summaries), two waves with 37 registers spilled 6.32; 1.18
+// and 0.96 ms with 64 x 64 clusters.  (With the next tile's key planes requested behind the values the spills are in the
+// loop, 7.4 ms; at D = 64, where that fits, it makes no difference.)
 template <int D, int RCAP>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, 2))) k_farfield_fwd_b(
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) k_farfield_fwd_b(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ A_kb, const uint16_t* __restrict__ A_km,
     const float* __restrict__ A_c, const bf16_t* __restrict__ A_v, const float* __restrict__ knorm,
     const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q, const int32_t* __restrict__ tile_off,
@@ -888,9 +893,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
     int h0, int N, int nb, int Cq, int Ck, int r, int Hq, int Hkv, float scale) {
   constexpr int DT = D / 32, KS = D / 16, CPR = D / 8, NIT = 32 * CPR / 64;
   constexpr int CAP = RCAP + 8;
-  __shared__ __attribute__((aligned(16))) bf16_t vt[D][32 + 4];
+  __shared__ __attribute__((aligned(16))) bf16_t vt[32 * D];
   __shared__ float cs[64][CAP];   // scores of a lane's candidates
-  __shared__ int ci[64][CAP];     // their clusters
+  __shared__ uint16_t ci[64][CAP];  // their clusters (MUSE_MAX_CLUSTERS fits)
   __shared__ int sel_s[32][RCAP];
   const int hl = blockIdx.z, hq = h0 + hl;
   const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);
@@ -917,7 +922,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 
   // the query itself as the bf16 operand (dims 16 ks + 8 half .. + 7), and its norm
   bf16x8_t qb[KS];
-  f16x8_t qh[KS];
   float q2 = 0.f;
   {
     const bf16_t* qrow = Q + ((size_t)hq * N + n) * D;
@@ -925,10 +929,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
     for (int ks = 0; ks < KS; ++ks) {
       qb[ks] = *reinterpret_cast<const bf16x8_t*>(qrow + 16 * ks + 8 * half);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        qh[ks][e] = (_Float16)(float)qb[ks][e];
-        q2 = fmaf((float)qb[ks][e], (float)qb[ks][e], q2);
-      }
+      for (int e = 0; e < 8; ++e) q2 = fmaf((float)qb[ks][e], (float)qb[ks][e], q2);
     }
     q2 += __shfl_xor(q2, 32, 64);
   }
@@ -1007,13 +1008,13 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
     load_ktile_h<D>(pt.kt, A_c + acell, A_kb + acell * D, A_km + acell * D, j0, Ck, col, half);
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-      const int c = lane + 64 * it, row = c % 32, cc = c / 32;
+      const int c = lane + 64 * it, row = c / CPR, cc = c % CPR;
       const int jr = j0 + row < Ck ? j0 + row : Ck - 1;
       pt.vch[it] = *reinterpret_cast<const uint4*>(Av + (size_t)jr * D + cc * 8);
     }
   };
   auto process = [&](const PTile& pt, int j0) {
-    f32x16_t acc = score_ktile_h<D>(pt.kt, j0, Ck, qb, qh, scale, half);
+    f32x16_t acc = score_ktile_h<D>(pt.kt, j0, Ck, qb, scale, half);
     float tmax = MUSE_NEG_INF;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -1049,10 +1050,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
     wave_lds_fence();
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-      const int c = lane + 64 * it, row = c % 32, cc = c / 32;
-      const bf16_t* pv = reinterpret_cast<const bf16_t*>(&pt.vch[it]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vt[cc * 8 + e][row] = pv[e];
+      const int c = lane + 64 * it, row = c / CPR, cc = c % CPR;
+      *reinterpret_cast<uint4*>(vt + tile_at<D>(row, cc)) = pt.vch[it];
     }
     wave_lds_fence();
 #pragma unroll
@@ -1060,7 +1059,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
       const bf16x8_t pf = pack8(acc, 2 * G, 2 * G + 1);
 #pragma unroll
       for (int x = 0; x < DT; ++x)
-        o[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_tr8(&vt[32 * x + col][0], 16 * G, half), pf, o[x], 0, 0, 0);
+        o[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_cols<D>(vt, 16 * G, x, lane), pf, o[x], 0, 0, 0);
     }
   };
   for (int jt = 0; jt < ntile; ++jt) {
@@ -1076,9 +1075,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
   for (int k = lane; k < 32 * RCAP; k += 64) (&sel_s[0][0])[k] = -1;
   __syncthreads();
   // ---- rank the query's candidates by (exact score desc, index asc); the r first are the selection ----
-  // (the ranks go where the transposed value tile was: pass 2 is over)
+  // (the ranks go where the value tile was: pass 2 is over)
   static_assert(sizeof(vt) >= 64 * CAP && 2 * CAP < 256, "the rank table (a byte per candidate) does not fit the value tile");
-  unsigned char (*rk)[CAP] = reinterpret_cast<unsigned char (*)[CAP]>(&vt[0][0]);
+  unsigned char (*rk)[CAP] = reinterpret_cast<unsigned char (*)[CAP]>(vt);
   const int nother = __shfl_xor(ncand, 32, 64);
   {
     for (int k = 0; k < ncand; ++k) {

@@ -160,6 +160,33 @@ __device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, i
   }
   return acc;
 }
+// The same with the fp16 query made from the bf16 one where it is used.  At D = 128 the conversion is kept inside the
+// caller's loop (the empty asm): hoisted, the 32 registers of the copy cost the kernel its second wave per SIMD.
+template <int D>
+__device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, int Ck, const bf16x8_t (&qb)[D / 16],
+                                                  float scale, int half) {
+  f32x16_t acc = zero16();
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kt.h[ks]), qb[ks], acc, 0, 0, 0);
+    uint4 raw = __builtin_bit_cast(uint4, qb[ks]);
+    if constexpr (D == 128) {
+      asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bf16x8_t q = __builtin_bit_cast(bf16x8_t, raw);
+    f16x8_t qh;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) qh[e] = (_Float16)(float)q[e];
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, kt.m[ks]), qh, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int jr = j0 + 8 * (e / 4) + 4 * half + (e % 4);
+    acc[e] = jr < Ck ? fmaf(scale, acc[e], kt.mu[e]) : MUSE_NEG_INF;
+  }
+  return acc;
+}
 
 // The bf16 plane alone: an approximate score, off by at most scale * 2^-8 * |q| . |k-bar| (the plane is k-bar rounded
 // to nearest), for the passes that only need to know which clusters can be among the r best.

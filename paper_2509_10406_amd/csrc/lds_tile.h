@@ -33,3 +33,9 @@ template <int D>
 __device__ __forceinline__ s16x4_t tile_tr4(const bf16_t* tile, int row, int col) {
   return lds_tr4(tile + tile_at<D>(row, col >> 3) + (col & 4));
 }
+// transposed operand of a 32x32x16 instruction: columns 32 t .. of the 16 rows from r0, k-slots in accumulator order
+template <int D>
+__device__ __forceinline__ bf16x8_t tile_cols(const bf16_t* tile, int r0, int t, int lane) {
+  const int row = r0 + 4 * (lane / 32) + (lane % 16) / 4, col = 32 * t + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+  return tr_join(tile_tr4<D>(tile, row, col), tile_tr4<D>(tile, row + 8, col));
+}

@@ -46,13 +46,6 @@ __device__ __forceinline__ void stage_keys(const bf16_t* __restrict__ Ks, const 
     }
 }
 
-// transposed operand: 32 columns (dims 32 t ..) of the 16 rows from r0, k-slots in accumulator order
-template <int D>
-__device__ __forceinline__ bf16x8_t tile_cols(const bf16_t* tile, int r0, int t, int lane) {
-  const int row = r0 + 4 * (lane / 32) + (lane % 16) / 4, col = 32 * t + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
-  return tr_join(tile_tr4<D>(tile, row, col), tile_tr4<D>(tile, row + 8, col));
-}
-
 // The wave's 32 result rows (accumulator columns) to dst + idx * D, idx the lane's own row number: through 4 KB of LDS
 // per 32 dims, so that a store instruction writes whole 128-byte lines of 8 rows and not 32 bytes of 32.
 template <int D>
