@@ -385,10 +385,12 @@ template <typename T, int D>
 void launch(const MuseDims& d, const T* Q, const T* dO, const float* qc, const float* LSE, FFWorkspace& w, int h0, int hn,
             hipStream_t st) {
   // S: the chains of a 32-cluster word are spread over S workgroups until the grid can fill the device (a workgroup
-  // stages its cluster's queries, so more than that only repeats the staging)
+  // stages its cluster's queries, so more than that only repeats the staging).  S decides which chains share a wave and how
+  // many waves share a chain, and with that the order of the sums: it is taken from all heads of the call, not from the
+  // heads of this chunk, so that the bits do not depend on the size of the workspace.
   const int W = (d.Ck + 31) / 32, cq8 = (d.Cq + 7) / 8 * 8;
   int S = 1;
-  while (S < 16 && (long long)W * S * d.Cq * hn < 2048) S *= 2;
+  while (S < 16 && (long long)W * S * d.Cq * d.B * d.Hq < 2048) S *= 2;
   const uint32_t pattern = S == 1 ? 0xffffffffu : S == 2 ? 0x55555555u : S == 4 ? 0x11111111u : S == 8 ? 0x01010101u : 0x00010001u;
   MuseProf prof_("k_chain_grads", st);
   auto go = [&](auto* kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)(cq8 * W * S), hn), dim3(256), 0, st, Q, dO, qc, w.s_mu, w.s_k,
