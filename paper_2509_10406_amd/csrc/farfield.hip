@@ -1377,22 +1377,27 @@ int muse_ff_carve(const MuseDims& d, bool bwd, void* ws, size_t ws_bytes, FFWork
   w->tile_off = (int32_t*)take(HQ * d.nb * ((size_t)d.Cq + 1) * 4);
   w->Ks = take(HK * N * D * es);
   w->Vs = take(HK * N * D * es);
-  w->ff_acc = (float*)take(HQ * N * (D + 2) * 4);
+  w->ff_acc = (float*)take(ff_acc_bytes(d, bwd));
   w->ff_ml = w->ff_acc + HQ * N * D;
+  w->run_cap = ff_run_cap(d);
+  w->run_map = nullptr; w->ret_part = nullptr;
   {
     size_t R2 = (size_t)(d.r > 0 ? d.r : 1) * d.k2e;
-    w->pair_off = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
-    w->pair_cnt = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
-    w->run_off = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
-    w->run_cap = ff_run_cap(d);
-    w->run_map = (int4*)take(HK * w->run_cap * 16);
-    w->c3_off = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
-    w->c3_map = (int2*)take(HK * w->run_cap * 8);
-    w->seg_cnt = (int32_t*)take(ff_segcnt_bytes(d));
-    w->seg_off = (int32_t*)take(ff_segcnt_bytes(d));
-    w->hit_cap = (size_t)(d.Hq / d.Hkv) * N * R2;
-    w->hits = (uint2*)take(HQ * N * R2 * 8);
-    w->ret_part = (float*)take(HQ * N * R2 * (D + 4) * 4);
+    if (ff_has_index(d, bwd)) {
+      w->pair_off = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
+      w->pair_cnt = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
+      w->run_off = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
+      w->c3_off = (int32_t*)take(HK * ((size_t)d.nb * d.Ck + 1) * 4);
+      w->c3_map = (int2*)take(HK * w->run_cap * 8);
+      w->seg_cnt = (int32_t*)take(ff_segcnt_bytes(d));
+      w->seg_off = (int32_t*)take(ff_segcnt_bytes(d));
+      w->hit_cap = (size_t)(d.Hq / d.Hkv) * N * R2;
+      w->hits = (uint2*)take(HQ * N * R2 * 8);
+    }
+    if (es == 2) {
+      w->run_map = (int4*)take(HK * w->run_cap * 16);
+      w->ret_part = (float*)take(ff_ret_part_bytes(d));
+    }
   }
   w->knorm = (float*)take(HK * 65 * 4);  // [HK] and the partial maxima [HK][64] behind them
   w->ff_flag = (int32_t*)take(ff_flag_bytes(d));
@@ -1405,8 +1410,8 @@ int muse_ff_carve(const MuseDims& d, bool bwd, void* ws, size_t ws_bytes, FFWork
     w->dVs = (float*)take(HK * N * D * 4);
     w->dQff = (float*)take(HQ * N * D * 4);
     w->qcT = take(HQ * D * (size_t)((d.Cq + 31) / 32 * 32) * 2);
-    w->c3_part = nullptr;
-    if (d.r > 0 && d.nb > 1) w->c3_part = (float*)take((size_t)(kC3Slices - 1) * HK * N * 2 * D * 4);
+    w->c3_part = w->ff_acc;  // fp32 inputs
+    if (es == 2 && d.r > 0 && d.nb > 1) w->c3_part = (float*)take((kC3Slices - 1) * ff_c3_slice_bytes(d));
     if (d.grad_dtype != MUSE_DTYPE_FP32) {
       w->dQacc = (float*)take(HQ * N * D * 4);
       w->dKacc = (float*)take(HK * N * D * 4);

@@ -272,19 +272,32 @@ constexpr int kMaxCk = 2304;  // key clusters a kernel can index in LDS
 static_assert(kMaxCk >= MUSE_MAX_CLUSTERS, "the host accepts more clusters than the kernels index");
 constexpr int kRunTiles = 4;  // hit tiles (of 32) per work item of the retrieval forward / dq pair kernels
 constexpr int kC3Slices = 8;  // most waves that share the hits of one retrieved pair in the key/value gradients
-// hit slices of a pair in the key/value gradient kernels of the retrieval: one per `tps` tiles of 32 hits
-__host__ __device__ inline int c3_slices(int nhits, int tps) {
+// hit slices of a pair in the key/value gradient kernels of the retrieval: one per `tiles` tiles of 32 hits, `most` at most
+struct C3Cut {
+  int tiles, most;
+};
+__host__ __device__ inline int c3_slices(int nhits, C3Cut cut) {
   const int nt = (nhits + 31) / 32;
-  const int s = nt / tps;
-  return s < 1 ? 1 : (s > kC3Slices ? kC3Slices : s);
+  const int s = nt / cut.tiles;
+  return s < 1 ? 1 : (s > cut.most ? cut.most : s);
 }
+// bytes of the far-field state of all queries, of the retrieval's partial rows per (query, slot), and of the partial
+// dK | dV rows of one hit slice
+static inline size_t ff_state_bytes(const MuseDims& d) { return (size_t)d.B * d.Hq * d.N * (d.D + 2) * 4; }
+static inline size_t ff_ret_part_bytes(const MuseDims& d) {
+  return (size_t)d.B * d.Hq * d.N * (d.r > 0 ? d.r : 1) * d.k2e * (d.D + 4) * 4;
+}
+static inline size_t ff_c3_slice_bytes(const MuseDims& d) { return (size_t)d.B * d.Hkv * d.N * 2 * d.D * 4; }
 // Tiles per slice.  A further slice costs a partial row of dK and dV per key, written and read again (as many bytes as the
 // gathered rows of four tiles), so where the problem fills the device with long slices (4096 of them), they are long: at
 // 16 heads of 64k tokens with 128 x 128 clusters 16 tiles against 4 take 1.22 + 0.16 ms (kernel + reduction) against
 // 1.55 + 0.39, at 12 heads of 6k 4 tiles are what keeps the device busy.
-static inline int ff_c3_tiles(const MuseDims& d) {
+// fp32 inputs have no partial rows per (query, slot): the slices take the room that bf16 inputs need for them and that of the
+// forward's far-field state, which the backward does not read, and no more.
+static inline C3Cut ff_c3_cut(const MuseDims& d) {
   const size_t tiles = (size_t)d.B * d.Hq * d.N * (d.r > 0 ? d.r : 1) * d.k2e / 32 / 4096;
-  return tiles < 4 ? 4 : tiles > 16 ? 16 : (int)tiles;
+  const size_t later = d.dtype == MUSE_DTYPE_BF16 ? kC3Slices - 1 : (ff_state_bytes(d) + ff_ret_part_bytes(d)) / ff_c3_slice_bytes(d);
+  return {tiles < 4 ? 4 : tiles > 16 ? 16 : (int)tiles, later < kC3Slices - 1 ? 1 + (int)later : kC3Slices};
 }
 
 struct FFWorkspace {
@@ -299,18 +312,18 @@ struct FFWorkspace {
   int32_t* pair_off;             // inverse index of the retrieval: (kv head, key block, key cluster) -> hits
   int32_t* pair_cnt;             // hits per pair, [HK][pairs + 1]
   int32_t* run_off;              // [HK][pairs + 1]: first work item of every pair, [pairs] = their number
-  int4* run_map;                 // [HK][run_cap]: (pair, first hit, end) of a work item
+  int4* run_map;                 // [HK][run_cap]: (pair, first hit, end) of a work item; bf16 inputs
   int32_t* c3_off;               // [HK][pairs + 1]: first (pair, hit slice) item of every pair, [pairs] = their number
   int2* c3_map;                  // [HK][run_cap]: (pair, slice) items of the key/value gradient kernel
   size_t run_cap;                // work items per kv head the map can hold
   int32_t *seg_cnt, *seg_off;    // its construction: counts / list starts [HK][head of the group x query slice][pair]
   uint2* hits;                   // x = n | g << 22 (query position, head inside the KV group), y = slot*k2e + u
   size_t hit_cap;                // hits per kv head
-  float* ret_part;               // per (query, slot, u): forward partial rows [D], then (max, sum) [2] of all rows; or dq partial rows [D]
+  float* ret_part;               // bf16 inputs, per (query, slot, u): forward partial rows [D], then (max, sum) [2] of all rows; or dq partial rows [D]
   float* knorm;                  // [HK]: largest Euclidean norm of a key row of the kv head (bf16 inputs); then [HK][64] partial maxima
   int32_t* ff_flag;              // [HQ][nb-1][ff_tile_grid_x]: tiles the one-plane forward kernel leaves to the two-plane one
   float *dKs, *dVs;            // fp32 gradients in bucketed key order
-  float* c3_part;              // r > 0: [kC3Slices - 1][HK][N][2][D] partial dK | dV rows of the later hit slices of a pair
+  float* c3_part;              // r > 0: [slices - 1][HK][N][2][D] partial dK | dV rows of the later hit slices of a pair (fp32: over ff_acc)
   float *dQacc, *dKacc, *dVacc;  // fp32 gradients in sequence order (alias the outputs when they are fp32)
   float* dQff;                   // far-field part of dQ, added to dQacc once the block-diagonal backward has finished
   void* qcT;                     // bf16 [hc][D][Cq padded to 32]: scaled query centroids of a head chunk, transposed
@@ -348,6 +361,13 @@ static inline size_t ff_run_cap(const MuseDims& d) {
   size_t npair = NBm * d.Ck, hits = (size_t)(d.Hq / d.Hkv) * d.N * R2;
   return (hits / 32 + npair) / kRunTiles + npair + 1;
 }
+// the forward of fp32 inputs reads the retrieved keys per query, without the inverse index
+static inline bool ff_has_index(const MuseDims& d, bool bwd) { return bwd || d.dtype == MUSE_DTYPE_BF16; }
+// bytes of the far-field state and, for fp32 inputs, of the slices' partial rows in the same place
+static inline size_t ff_acc_bytes(const MuseDims& d, bool bwd) {
+  const size_t a = ff_state_bytes(d), c3 = (ff_c3_cut(d).most - 1) * ff_c3_slice_bytes(d);
+  return bwd && d.dtype == MUSE_DTYPE_FP32 && d.r > 0 && d.nb > 1 && c3 > a ? c3 : a;
+}
 // bytes of the segment counters of the inverse index
 static inline size_t ff_segcnt_bytes(const MuseDims& d) {
   size_t HK = (size_t)d.B * d.Hkv, NBm = d.nb > 1 ? d.nb - 1 : 1;
@@ -366,18 +386,18 @@ static inline size_t ff_fixed_bytes(const MuseDims& d, bool bwd) {
   size_t W = (d.Ck + 31) / 32, NBm = d.nb > 1 ? d.nb - 1 : 1, R2 = (size_t)(d.r > 0 ? d.r : 1) * d.k2e;
   size_t b = ff_al(HK * N * 4) + ff_al(HK * ((size_t)d.nb * d.Ck + 1) * 4) + ff_al(HQ * N * 4) +
              ff_al(HQ * ((size_t)d.nb * d.Cq + 1) * 4) + ff_al(HQ * d.nb * ((size_t)d.Cq + 1) * 4) +
-             2 * ff_al(HK * N * D * es) + ff_al(HQ * N * (D + 2) * 4);
-  // inverse index of the retrieval and its per-(query, slot) partial results
-  b += 4 * ff_al(HK * ((size_t)d.nb * d.Ck + 1) * 4) + 2 * ff_al(ff_segcnt_bytes(d)) +
-       ff_al(HK * ff_run_cap(d) * 16) + ff_al(HK * ff_run_cap(d) * 8) +
-       ff_al(HQ * N * R2 * 8) +
-       ff_al(HQ * N * R2 * (D + 4) * 4);
+             2 * ff_al(HK * N * D * es) + ff_al(ff_acc_bytes(d, bwd));
+  // inverse index of the retrieval and, for bf16 inputs, its per-(query, slot) partial results
+  if (ff_has_index(d, bwd))
+    b += 4 * ff_al(HK * ((size_t)d.nb * d.Ck + 1) * 4) + 2 * ff_al(ff_segcnt_bytes(d)) +
+         ff_al(HK * ff_run_cap(d) * 8) + ff_al(HQ * N * R2 * 8);
+  if (es == 2) b += ff_al(HK * ff_run_cap(d) * 16) + ff_al(ff_ret_part_bytes(d));
   b += ff_al(HK * 65 * 4) + ff_al(ff_flag_bytes(d));
   if (bwd) {
     b += ff_al(HQ * N * 4) + ff_al(HQ * N * W * 4) + ff_al(HQ * N * (size_t)(d.r > 0 ? d.r : 1) * 4) + 2 * ff_al(HK * N * D * 4) +
          ff_al(HQ * N * D * 4) + ff_al(HQ * D * (size_t)((d.Cq + 31) / 32 * 32) * 2);
     if (d.grad_dtype != MUSE_DTYPE_FP32) b += ff_al(HQ * N * D * 4) + 2 * ff_al(HK * N * D * 4);
-    if (d.r > 0 && d.nb > 1) b += ff_al((size_t)(kC3Slices - 1) * HK * N * 2 * D * 4);
+    if (es == 2 && d.r > 0 && d.nb > 1) b += ff_al((kC3Slices - 1) * ff_c3_slice_bytes(d));
   }
   if (d.dipole) b += ff_al(HK * NBm * d.Ck * D * D * 4);
   return b;

@@ -114,24 +114,26 @@ __global__ void __launch_bounds__(64 * kSegWaves) k_seg_offsets(const int32_t* _
 //   run_map[hk][run_off[hk][p] + u] = (p, first hit of run u, end of the run)
 // The items of the key/value gradient kernel are (pair, hit slice), c3_slices of them per pair that has hits.
 __host__ __device__ inline int pair_runs(int hits) { return ((hits + 31) / 32 + kRunTiles - 1) / kRunTiles; }
-__host__ __device__ inline int pair_slices(int hits, int tps) { return hits > 0 ? c3_slices(hits, tps) : 0; }
+__host__ __device__ inline int pair_slices(int hits, C3Cut cut) { return hits > 0 ? c3_slices(hits, cut) : 0; }
 __global__ void __launch_bounds__(256) k_pair_items(const int32_t* __restrict__ pair_off, const int32_t* __restrict__ run_off,
                                                      const int32_t* __restrict__ c3_off, int4* __restrict__ run_map,
-                                                     int2* __restrict__ c3_map, int npair, size_t run_cap, int tps) {
+                                                     int2* __restrict__ c3_map, int npair, size_t run_cap, C3Cut cut) {
   const int hk = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
   if (p >= npair) return;
   const size_t at = (size_t)hk * (npair + 1) + p;
   const int lo = pair_off[at], hi = pair_off[at + 1];
-  int4* run = run_map + (size_t)hk * run_cap + run_off[at];
-  for (int u = 0, h = lo; h < hi; ++u, h += 32 * kRunTiles)
-    run[u] = make_int4(p, h, h + 32 * kRunTiles < hi ? h + 32 * kRunTiles : hi, 0);
+  if (run_map) {
+    int4* run = run_map + (size_t)hk * run_cap + run_off[at];
+    for (int u = 0, h = lo; h < hi; ++u, h += 32 * kRunTiles)
+      run[u] = make_int4(p, h, h + 32 * kRunTiles < hi ? h + 32 * kRunTiles : hi, 0);
+  }
   int2* sl = c3_map + (size_t)hk * run_cap + c3_off[at];
-  for (int u = 0; u < pair_slices(hi - lo, tps); ++u) sl[u] = make_int2(p, u);
+  for (int u = 0; u < pair_slices(hi - lo, cut); ++u) sl[u] = make_int2(p, u);
 }
 
 // exclusive prefixes, per kv head, of the pairs' hits, runs and slices (entry n: the totals)
 __global__ void __launch_bounds__(1024) k_pair_scan(const int32_t* __restrict__ cnt, int32_t* __restrict__ pair_off,
-                                                     int32_t* __restrict__ run_off, int32_t* __restrict__ c3_off, int n, int tps) {
+                                                     int32_t* __restrict__ run_off, int32_t* __restrict__ c3_off, int n, C3Cut cut) {
   __shared__ int wsum[3][16];
   const int hk = blockIdx.x, lane = threadIdx.x % 64, wave = threadIdx.x / 64;
   const size_t base = (size_t)hk * (n + 1);
@@ -140,7 +142,7 @@ __global__ void __launch_bounds__(1024) k_pair_scan(const int32_t* __restrict__ 
   for (int u = 0; u < per; ++u) {
     const int i = threadIdx.x * per + u;
     const int c = i < n ? cnt[base + i] : 0;
-    mine[0] += c; mine[1] += pair_runs(c); mine[2] += pair_slices(c, tps);
+    mine[0] += c; mine[1] += pair_runs(c); mine[2] += pair_slices(c, cut);
   }
   int run[3];
 #pragma unroll
@@ -162,7 +164,7 @@ __global__ void __launch_bounds__(1024) k_pair_scan(const int32_t* __restrict__ 
     if (i >= n) break;
     const int c = cnt[base + i];
     pair_off[base + i] = run[0]; run_off[base + i] = run[1]; c3_off[base + i] = run[2];
-    run[0] += c; run[1] += pair_runs(c); run[2] += pair_slices(c, tps);
+    run[0] += c; run[1] += pair_runs(c); run[2] += pair_slices(c, cut);
   }
   if (threadIdx.x == 1023) { pair_off[base + n] = run[0]; run_off[base + n] = run[1]; c3_off[base + n] = run[2]; }
 }
@@ -225,10 +227,10 @@ int muse_ff_build_inverse_index(const MuseDims& d, const int32_t* selc, const in
   const dim3 g(SEG, HQ), gs((npair + 63) / 64, HK);
   { MuseProf prof_("k_hit_lists", st); hipLaunchKernelGGL(k_hit_lists<false>, g, dim3(64 * kHitWaves), lds, st, selc, selb, w.seg_cnt, w.seg_off, w.hits, w.hit_cap, N, d.Bs, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, npair, SEG, cps); }
   { MuseProf prof_("k_pair_totals", st); hipLaunchKernelGGL(k_pair_totals, gs, dim3(64 * kSegWaves), 0, st, w.seg_cnt, w.pair_cnt, npair, SEGT); }
-  { MuseProf prof_("k_pair_scan", st); hipLaunchKernelGGL(k_pair_scan, dim3(HK), dim3(1024), 0, st, w.pair_cnt, w.pair_off, w.run_off, w.c3_off, npair, ff_c3_tiles(d)); }
+  { MuseProf prof_("k_pair_scan", st); hipLaunchKernelGGL(k_pair_scan, dim3(HK), dim3(1024), 0, st, w.pair_cnt, w.pair_off, w.run_off, w.c3_off, npair, ff_c3_cut(d)); }
   { MuseProf prof_("k_seg_offsets", st); hipLaunchKernelGGL(k_seg_offsets, gs, dim3(64 * kSegWaves), 0, st, w.seg_cnt, w.pair_off, w.seg_off, npair, SEGT); }
   { MuseProf prof_("k_hit_lists", st); hipLaunchKernelGGL(k_hit_lists<true>, g, dim3(64 * kHitWaves), lds, st, selc, selb, w.seg_cnt, w.seg_off, w.hits, w.hit_cap, N, d.Bs, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, npair, SEG, cps); }
-  { MuseProf prof_("k_pair_items", st); hipLaunchKernelGGL(k_pair_items, dim3((npair + 255) / 256, HK), dim3(256), 0, st, w.pair_off, w.run_off, w.c3_off, w.run_map, w.c3_map, npair, w.run_cap, ff_c3_tiles(d)); }
+  { MuseProf prof_("k_pair_items", st); hipLaunchKernelGGL(k_pair_items, dim3((npair + 255) / 256, HK), dim3(256), 0, st, w.pair_off, w.run_off, w.c3_off, w.run_map, w.c3_map, npair, w.run_cap, ff_c3_cut(d)); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

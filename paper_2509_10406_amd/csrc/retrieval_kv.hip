@@ -28,7 +28,7 @@ __global__ void __launch_bounds__(128, 2) k_c3_pairs(
     const float* __restrict__ LSE, const float* __restrict__ delta, const int32_t* __restrict__ off_k,
     const int32_t* __restrict__ pair_off, const int32_t* __restrict__ c3_off, const int2* __restrict__ c3_map,
     const uint2* __restrict__ hits, float* __restrict__ dKs, float* __restrict__ dVs, float* __restrict__ part, size_t run_cap,
-    size_t hit_cap, int N, int nb, int Ck, int Hq, int Hkv, int HK, int tps, float scale, float scale_log2e) {
+    size_t hit_cap, int N, int nb, int Ck, int Hq, int Hkv, int HK, C3Cut cut, float scale, float scale_log2e) {
   constexpr int KS = D / 16, CPR = D / 8;
   constexpr bool kSplitD = D == 128;              // the waves share one key tile and split the head dim of the results
   constexpr int DT = 2;                           // 32-dim tiles of dK and dV per wave
@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(128, 2) k_c3_pairs(
   const int kbeg = klo + KG * (int)blockIdx.z;
   if (kbeg >= khi) return;
   const int32_t* po = pair_off + (size_t)hk * ((size_t)NBm * Ck + 1) + item.x;
-  const int plo = po[0], phi = po[1], nt = (phi - plo + 31) / 32, S = c3_slices(phi - plo, tps);
+  const int plo = po[0], phi = po[1], nt = (phi - plo + 31) / 32, S = c3_slices(phi - plo, cut);
   const int hlo = plo + 32 * (nt * sl / S), hhi = min(phi, plo + 32 * (nt * (sl + 1) / S));  // this slice's hits, never empty
   const uint2* hh = hits + (size_t)hk * hit_cap;
   const int row0 = tid / CPR, chunk = tid % CPR;
@@ -200,14 +200,14 @@ template <int D>
 __global__ void __launch_bounds__(256) k_c3_reduce(const int32_t* __restrict__ off_k, const int32_t* __restrict__ pair_off,
                                                    const int32_t* __restrict__ c3_off, const int2* __restrict__ c3_map,
                                                    const float* __restrict__ part, float* __restrict__ dKs,
-                                                   float* __restrict__ dVs, size_t run_cap, int N, int nb, int Ck, int HK, int tps) {
+                                                   float* __restrict__ dVs, size_t run_cap, int N, int nb, int Ck, int HK, C3Cut cut) {
   // walks the same item list as k_c3_pairs: the item (pair, slice 1) exists exactly for the pairs with partial rows
   const int hk = blockIdx.y, NBm = nb - 1;
   if ((int)blockIdx.x >= c3_off[(size_t)hk * ((size_t)NBm * Ck + 1) + (size_t)NBm * Ck]) return;
   const int2 item = c3_map[(size_t)hk * run_cap + blockIdx.x];
   if (item.y != 1) return;
   const int32_t* po = pair_off + (size_t)hk * ((size_t)NBm * Ck + 1) + item.x;
-  const int S = c3_slices(po[1] - po[0], tps);  // every slice has hits
+  const int S = c3_slices(po[1] - po[0], cut);  // every slice has hits
   const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
   const int klo = ok[item.x], khi = ok[item.x + 1];
   const int sub = threadIdx.x / 16, l16 = threadIdx.x % 16;
@@ -233,8 +233,8 @@ int muse_launch_c3_reduce(const MuseDims& d, FFWorkspace& w, hipStream_t st) {
   const int HK = d.B * d.Hkv;
   const dim3 g((unsigned)w.run_cap, HK);
   MuseProf prof_("k_c3_reduce", st);
-  if (d.D == 64) hipLaunchKernelGGL(k_c3_reduce<64>, g, dim3(256), 0, st, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.c3_part, w.dKs, w.dVs, w.run_cap, d.N, d.nb, d.Ck, HK, ff_c3_tiles(d));
-  else hipLaunchKernelGGL(k_c3_reduce<128>, g, dim3(256), 0, st, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.c3_part, w.dKs, w.dVs, w.run_cap, d.N, d.nb, d.Ck, HK, ff_c3_tiles(d));
+  if (d.D == 64) hipLaunchKernelGGL(k_c3_reduce<64>, g, dim3(256), 0, st, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.c3_part, w.dKs, w.dVs, w.run_cap, d.N, d.nb, d.Ck, HK, ff_c3_cut(d));
+  else hipLaunchKernelGGL(k_c3_reduce<128>, g, dim3(256), 0, st, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.c3_part, w.dKs, w.dVs, w.run_cap, d.N, d.nb, d.Ck, HK, ff_c3_cut(d));
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }
@@ -249,7 +249,7 @@ int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const
     MuseProf prof_("k_c3_pairs", st);
     hipLaunchKernelGGL(kernel, g, dim3(128), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, (const bf16_t*)w.Ks, (const bf16_t*)w.Vs, LSE,
                        w.delta, w.off_k, w.pair_off, w.c3_off, w.c3_map, w.hits, w.dKs, w.dVs, w.c3_part, w.run_cap, w.hit_cap, d.N,
-                       d.nb, d.Ck, d.Hq, d.Hkv, HK, ff_c3_tiles(d), d.scale, sl);
+                       d.nb, d.Ck, d.Hq, d.Hkv, HK, ff_c3_cut(d), d.scale, sl);
   };
   if (d.D == 64) go(k_c3_pairs<64>);
   else go(k_c3_pairs<128>);
