@@ -40,3 +40,18 @@ def test_exact(N, Hq, Hkv):
     assert (O.cpu().double() - want).abs().max() <= BF16_ABS
     for name, a, b in zip(("dQ", "dK", "dV"), got, (q.grad, k.grad, v.grad)):
         assert (a.cpu().double() - b).abs().max() <= bf16_grad_bound(float(b.abs().max())), name
+
+
+def test_infinities_stay_out_of_later_keys():
+    """A row of dO that is not finite reaches no key of a later tile of 32, which none of the row's 32 queries attends."""
+    g = torch.Generator().manual_seed(1)
+    p = mb.Params(B=1, Hq=2, Hkv=1, N=300, D=128, Cq=1, Ck=1, r=0, k2=1, block=0, kmeans_iters=0, dtype=mb.BF16, grad_dtype=mb.FP32)
+    Q, K, V, dO = (torch.randn(1, H, 300, 128, generator=g).bfloat16().cuda() for H in (2, 1, 1, 2))
+    O, LSE = mb.exact_attn_fwd(p, Q, K, V)
+    for n in (3, 40, 200):
+        without, gi = dO.clone(), dO.clone()
+        without[0, 1, n], gi[0, 1, n] = 0.0, math.inf
+        want, got = (mb.exact_attn_bwd(p, Q, K, V, O, LSE, x)[1:] for x in (without, gi))
+        first = n // 32 * 32 + 32
+        for a, b in zip(got, want):
+            assert torch.equal(a[:, :, first:], b[:, :, first:]) and not a[:, :, : n + 1].isfinite().any()
