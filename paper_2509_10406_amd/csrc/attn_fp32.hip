@@ -95,9 +95,11 @@ __device__ __forceinline__ f32x4_t dot_tile(const float* rows, const float (&y)[
 }
 
 // acc += p^T . rows over 16 staged rows.  `masked`: some of the (row, column) pairs are not attended and have p = 0; a
-// row that holds an infinity or NaN must not reach their columns through 0 * inf, so it is added pair by pair then.
-template <int D>
-__device__ __forceinline__ void add_tile(f32x4_t (&acc)[D / 16], const float* rows, const f32x4_t p, int c, int h, bool masked) {
+// row that holds an infinity or NaN must not reach their columns through 0 * inf, so it is added pair by pair then.  There
+// `attends(row)` says which rows the lane's column has (an attended weight that underflowed counts: 0 * inf).
+template <int D, typename F>
+__device__ __forceinline__ void add_tile(f32x4_t (&acc)[D / 16], const float* rows, const f32x4_t p, int c, int h, bool masked,
+                                         F attends) {
   constexpr int LD = F32Attn<D>::kLd;
   float4 a[4][D / 64];
 #pragma unroll
@@ -115,7 +117,7 @@ __device__ __forceinline__ void add_tile(f32x4_t (&acc)[D / 16], const float* ro
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const float pk = __shfl(p[t], 16 * k4 + c, 64);
-          if (pk == 0.f) continue;
+          if (!attends(4 * k4 + t)) continue;
           const float* row = rows + (4 * k4 + t) * LD + 16 * h;
 #pragma unroll
           for (int e = 0; e < D / 4; ++e)
@@ -223,7 +225,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd_f32(const float* __restrict
           s[j][t] = __expf(s[j][t] - ref);
           l += s[j][t];
         }
-        add_tile<D>(acc, vs + 16 * j * LD, s[j], c, h, kj + 15 > qa || kj < beg_z);
+        add_tile<D>(acc, vs + 16 * j * LD, s[j], c, h, kj + 15 > qa || kj < beg_z, [&](int r) { return kj + r >= beg && kj + r <= n; });
       }
     }
   }
@@ -309,7 +311,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_f32(const float* __restr
         ds[t] = __expf(s[t] - lse) * (ds[t] - dl);
         if (masked && (!live || key > n || key < beg)) ds[t] = 0.f;
       }
-      add_tile<D>(acc, ks + 16 * j * LD, ds, c, h, masked);
+      add_tile<D>(acc, ks + 16 * j * LD, ds, c, h, masked, [&](int r) { return kj + r >= beg && kj + r <= n; });
     }
   }
   if (live) store_col<D>(acc, dQ + (qh + n) * D, h, scale);
@@ -391,8 +393,9 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_f32(const float* __rest
           ds[t] = p[t] * (ds[t] - da[t]);
           if (masked && (!live || n < m || n >= end)) p[t] = ds[t] = 0.f;
         }
-        add_tile<D>(av, gs + 16 * j * LD, p, c, h, masked);
-        add_tile<D>(ak, qs + 16 * j * LD, ds, c, h, masked);
+        const auto attends = [&](int r) { return qj + r >= m && qj + r < end; };
+        add_tile<D>(av, gs + 16 * j * LD, p, c, h, masked, attends);
+        add_tile<D>(ak, qs + 16 * j * LD, ds, c, h, masked, attends);
       }
     }
   }

@@ -50,3 +50,32 @@ def test_later_infinities_stay_out():
     assert torch.allclose(O[:, :, :70], O0[:, :, :70], rtol=1e-6, atol=1e-6) and not O[:, :, 70:].isfinite().any()
     dQ, dK, dV = mb.exact_attn_bwd(p, Q, K, V, O0, LSE, dO)
     assert dQ[:, :, :70].isfinite().all()
+
+
+def test_attended_infinity_with_a_vanishing_weight():
+    """A query whose weight of a value row that is not finite underflows to zero still attends it: 0 * inf, on every tile."""
+    p, (Q, K, V, _) = inputs(40, 64, 1, 1)
+    Q[..., 0], K[..., 0] = 40.0, 1.0
+    K[0, 0, 5, 0], V[0, 0, 5] = -40.0, math.inf      # a score of -200 against some 5
+    O, _ = mb.exact_attn_fwd(p, Q, K, V)
+    assert O[:, :, :5].isfinite().all() and not O[:, :, 5:].isfinite().any()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("what", ["dO", "Q"])
+def test_earlier_infinities_stay_out_of_later_keys(what, D):
+    """A query row that is not finite reaches dK and dV of the keys up to its position; those of the later keys are what they
+    are without that row."""
+    p, (Q, K, V, dO) = inputs(200, D, 4, 2)
+    O, LSE = mb.exact_attn_fwd(p, Q, K, V)
+    for n in (0, 37, 130):                            # in the second query head of the first group
+        without, Qi, gi = dO.clone(), Q.clone(), dO.clone()
+        without[0, 1, n] = 0.0
+        (gi if what == "dO" else Qi)[0, 1, n] = math.inf
+        _, dK0, dV0 = mb.exact_attn_bwd(p, Q, K, V, O, LSE, without)
+        _, dK, dV = mb.exact_attn_bwd(p, Qi, K, V, O, LSE, gi)
+        assert dK.isfinite()[:, 1].all() and dK.isfinite()[:, :, n + 1:].all() and dV.isfinite()[:, :, n + 1:].all()
+        for a, b in ((dK, dK0), (dV, dV0)):
+            err = (a - b).abs()[:, :, n + 1:].max() / b.abs().max()
+            assert err <= FP32_REL, float(err)
+        assert not dK[:, 0, : n + 1].isfinite().all()
