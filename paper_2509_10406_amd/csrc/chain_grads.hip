@@ -17,6 +17,9 @@
 // of the matrix instructions; one chain beyond that), whose summaries and first queries' rows are one round trip to
 // memory.  With fewer such groups than waves, the waves share a group's tiles and add up through LDS.
 //
+// A query with an infinity or NaN in its rows (its LSE or delta is not finite then) is kept out of the lists: in a tile it
+// would reach the cells that it does not use, those of later blocks among them, as 0 * inf.  k_chain_odd adds its share.
+//
 // Bound by the scattered rows of the chains' cells (s_k, s_v read, G_k, G_v read and written, 640 to 1280 bytes per cell)
 // and their latency where chains have few queries, by the gathered query rows where they have many.  A workgroup per
 // (head, query cluster) on the vector units, as this was before, left small problems to a few workgroups: 1.64 -> 0.09 ms
@@ -26,6 +29,8 @@
 #include "lds_tile.h"
 
 namespace {
+
+__device__ __forceinline__ bool both_finite(float a, float b) { return fabsf(a) < __builtin_huge_valf() && fabsf(b) < __builtin_huge_valf(); }
 
 __device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
   hi = (__bf16)x;
@@ -113,8 +118,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof
       }
     }
     int n2[2];
+    float2 ld2[2];
 #pragma unroll
     for (int z = 0; z < 2; ++z) n2[z] = w2[z] ? perm_q[(size_t)hq * N + p2[z]] : 0;
+#pragma unroll
+    for (int z = 0; z < 2; ++z) ld2[z] = make_float2(LSE[(size_t)hq * N + n2[z]], delta[(size_t)hq * N + n2[z]]);
+#pragma unroll
+    for (int z = 0; z < 2; ++z) w2[z] = both_finite(ld2[z].x, ld2[z].y) ? w2[z] : 0u;
     {
       int k = 0;
       for (uint32_t rest = word; rest; rest &= rest - 1, ++k) {
@@ -127,7 +137,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof
     for (int z = 0; z < 2; ++z)
       if (w2[z]) {
         nS[tid + 256 * z] = (uint32_t)n2[z] | ((uint32_t)b2[z] << 22);
-        ldS[tid + 256 * z] = make_float2(LSE[(size_t)hq * N + n2[z]], delta[(size_t)hq * N + n2[z]]);
+        ldS[tid + 256 * z] = ld2[z];
       }
     __syncthreads();
     if (wave == 0) {
@@ -381,6 +391,98 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof
   }
 }
 
+// The queries that k_chain_grads keeps out, one by one: a workgroup per (head, query cluster) looks through the cluster's LSE
+// and delta, and its waves share the chains of a query that is not finite (a chain has one wave: a cell one owner).  A kernel
+// of its own, because the registers for it cost k_chain_grads 11 % (16 heads of 64k tokens, 256 x 1024 clusters); where every
+// query is finite it takes 50 us there and 8 us at 12 heads of 6k with 23 x 71 clusters.
+constexpr int kOddWaves = 16;
+template <typename T, int D>
+__global__ void __launch_bounds__(64 * kOddWaves) k_chain_odd(
+    const T* __restrict__ Q, const T* __restrict__ dO, const float* __restrict__ qc, const float* __restrict__ s_mu,
+    const float* __restrict__ s_k, const T* __restrict__ s_v, const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q,
+    const float* __restrict__ LSE, const float* __restrict__ delta, const int32_t* __restrict__ slotinfo, float* __restrict__ G_c,
+    T* __restrict__ G_k, T* __restrict__ G_v, int h0, int N, int nb, int Cq, int Ck, int r, float scale) {
+  constexpr int Z = 4;  // queries per thread and round
+  __shared__ unsigned long long odd[Z][kOddWaves];
+  __shared__ int cum[65], seg[64];  // as in k_chain_grads
+  const int i = blockIdx.x, hl = blockIdx.y, hq = h0 + hl, NBm = nb - 1;
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  const float* qci = qc + ((size_t)hq * Cq + i) * D;
+  if (wave == 0) {
+    const int32_t* oq = off_q + (size_t)hq * ((size_t)nb * Cq + 1) + i;
+    const bool far = lane >= 1 && lane < nb;
+    const int lo = far ? oq[lane * Cq] : 0;
+    int incl = far ? oq[lane * Cq + 1] - lo : 0;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    cum[lane + 1] = incl;
+    seg[lane] = lo;
+  }
+  __syncthreads();
+  const int Tq = cum[nb];
+  auto block_of = [&](int idx) {
+    int b = 1;
+    while (idx >= cum[b + 1]) ++b;
+    return b;
+  };
+  for (int c0 = 0; c0 < Tq; c0 += 64 * kOddWaves * Z) {
+    bool bad[Z];
+#pragma unroll
+    for (int z = 0; z < Z; ++z) {
+      const int idx = c0 + 64 * kOddWaves * z + threadIdx.x;
+      bad[z] = false;
+      if (idx < Tq) {
+        const int b = block_of(idx);
+        const size_t qn = (size_t)hq * N + perm_q[(size_t)hq * N + seg[b] + idx - cum[b]];
+        bad[z] = !both_finite(LSE[qn], delta[qn]);
+      }
+    }
+    if (!__syncthreads_or(bad[0] || bad[1] || bad[2] || bad[3])) continue;
+#pragma unroll
+    for (int z = 0; z < Z; ++z) {
+      const unsigned long long m = __ballot(bad[z]);
+      if (lane == 0) odd[z][wave] = m;
+    }
+    __syncthreads();
+    for (int w = 0; w < kOddWaves * Z; ++w)
+      for (unsigned long long rest = odd[w / kOddWaves][w % kOddWaves]; rest; rest &= rest - 1) {
+        const int idx = c0 + 64 * w + __ffsll((long long)rest) - 1, b = block_of(idx);
+        const size_t pos = (size_t)hq * N + seg[b] + idx - cum[b], qn = (size_t)hq * N + perm_q[pos];
+        for (int t = 0; t < r; ++t) {
+          const int x = slotinfo[pos * r + t], j = x & 0xffff;
+          if (x < 0 || j % kOddWaves != wave) continue;
+          for (int a = 0; a < b; ++a) {
+            if (((uint32_t)x >> (16 + a)) & 1u) continue;
+            const size_t cell = (((size_t)hl * NBm + a) * Cq + i) * Ck + j;
+            float q[D / 64], g[D / 64], sv = 0.f, dp = 0.f;
+#pragma unroll
+            for (int y = 0; y < D / 64; ++y) {
+              const int d = lane + 64 * y;
+              q[y] = scale * (Elem<T>::ld(Q, qn * D + d) - qci[d]);
+              g[y] = Elem<T>::ld(dO, qn * D + d);
+              sv = fmaf(q[y], s_k[cell * D + d], sv);
+              dp = fmaf(g[y], Elem<T>::ld(s_v, cell * D + d), dp);
+            }
+            sv = wave_sum(sv);
+            dp = wave_sum(dp);
+            const float p = __expf(sv + s_mu[cell] - LSE[qn]), dl = p * (dp - delta[qn]);
+#pragma unroll
+            for (int y = 0; y < D / 64; ++y) {
+              const size_t at = cell * D + lane + 64 * y;
+              Elem<T>::st(G_k, at, Elem<T>::ld(G_k, at) + dl * q[y]);
+              Elem<T>::st(G_v, at, Elem<T>::ld(G_v, at) + p * g[y]);
+            }
+            if (lane == 0) G_c[cell] += dl * (1.f - sv) - p * dp;
+          }
+        }
+      }
+    __syncthreads();
+  }
+}
+
 template <typename T, int D>
 void launch(const MuseDims& d, const T* Q, const T* dO, const float* qc, const float* LSE, FFWorkspace& w, int h0, int hn,
             hipStream_t st) {
@@ -392,12 +494,14 @@ void launch(const MuseDims& d, const T* Q, const T* dO, const float* qc, const f
   int S = 1;
   while (S < 16 && (long long)W * S * d.Cq * d.B * d.Hq < 2048) S *= 2;
   const uint32_t pattern = S == 1 ? 0xffffffffu : S == 2 ? 0x55555555u : S == 4 ? 0x11111111u : S == 8 ? 0x01010101u : 0x00010001u;
-  MuseProf prof_("k_chain_grads", st);
-  auto go = [&](auto* kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)(cq8 * W * S), hn), dim3(256), 0, st, Q, dO, qc, w.s_mu, w.s_k,
+  auto go = [&](auto* kernel) { MuseProf prof_("k_chain_grads", st); hipLaunchKernelGGL(kernel, dim3((unsigned)(cq8 * W * S), hn), dim3(256), 0, st, Q, dO, qc, w.s_mu, w.s_k,
                      (const T*)w.s_v, w.perm_q, w.off_q, LSE, w.delta, w.selmask, w.slotinfo, w.chainmask, w.g_s_c,
                      (T*)w.g_s_k, (T*)w.g_s_v, h0, d.N, d.nb, d.Cq, d.Ck, d.r, S, pattern, d.scale); };
   if (d.nb <= 9) go(k_chain_grads<T, D, 2>);
   else go(k_chain_grads<T, D, 1>);
+  MuseProf prof_("k_chain_odd", st);
+  hipLaunchKernelGGL((k_chain_odd<T, D>), dim3(d.Cq, hn), dim3(64 * kOddWaves), 0, st, Q, dO, qc, w.s_mu, w.s_k, (const T*)w.s_v, w.perm_q,
+                     w.off_q, LSE, w.delta, w.slotinfo, w.g_s_c, (T*)w.g_s_k, (T*)w.g_s_v, h0, d.N, d.nb, d.Cq, d.Ck, d.r, d.scale);
 }
 
 }  // namespace
