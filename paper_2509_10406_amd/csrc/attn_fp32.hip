@@ -13,8 +13,8 @@
 //     accumulators, which leaves the lane with the dims 64g + 16h .. + 15 of its column: whole float4 results.
 // Rows are padded by four floats: both reads then spread over all banks.
 // Measured, 4 heads of 8k tokens, D = 64, blocks of 1024 (vector kernels with four lanes per query before): forward
-// 407 -> 60 us, dQ 494 -> 79 us, dK/dV 536 -> 100 us (about a third of the instruction rate; one wave per SIMD there).
-#include "common.h"
+// 407 -> 63 us, dQ 494 -> 79 us, dK/dV 536 -> 105 us (about a third of the instruction rate; one wave per SIMD there).
+#include "fp32_sum.h"
 
 namespace {
 
@@ -82,16 +82,17 @@ __device__ __forceinline__ void load_col(const float* __restrict__ X, int row, b
 // 16 staged rows (from `rows`) times the column operand
 template <int D>
 __device__ __forceinline__ f32x4_t dot_tile(const float* rows, const float (&y)[D / 4], int c, int h) {
-  f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+  FoldSum s;
 #pragma unroll
   for (int u = 0; u < D / 16; ++u) {
     const float4 a = *reinterpret_cast<const float4*>(rows + c * F32Attn<D>::kLd + 16 * u + 4 * h);
-    s = mfma16(a.x, y[4 * u], s);
-    s = mfma16(a.y, y[4 * u + 1], s);
-    s = mfma16(a.z, y[4 * u + 2], s);
-    s = mfma16(a.w, y[4 * u + 3], s);
+    s.add(0, a.x, y[4 * u]);
+    s.add(1, a.y, y[4 * u + 1]);
+    s.add(2, a.z, y[4 * u + 2]);
+    s.add(3, a.w, y[4 * u + 3]);
+    s.fold(u);
   }
-  return s;
+  return s.total;
 }
 
 // acc += p^T . rows over 16 staged rows.  `masked`: some of the (row, column) pairs are not attended and have p = 0; a

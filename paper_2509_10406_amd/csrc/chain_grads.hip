@@ -26,6 +26,7 @@
 // at 12 heads of 6k tokens with 23 x 71 clusters, 3.86 -> 0.76 ms at 16 heads of 64k tokens with 128 x 128 clusters,
 // 2.8 -> 2.3 ms there with 256 x 1024, 8.2 -> 6.1 ms at D = 128 (32 heads of 32k, 128 x 512, r = 16).
 #include "ff_common.h"
+#include "fp32_sum.h"
 #include "lds_tile.h"
 
 namespace {
@@ -266,6 +267,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof
               *reinterpret_cast<uint4*>(&grow[c16][32 * x + 8 * g]) = gr[x];
             }
           } else {
+            FoldSum ss, dps;
 #pragma unroll
             for (int x = 0; x < MT; ++x) {
               const float4 c4 = *reinterpret_cast<const float4*>(qci + 16 * x + 4 * g);
@@ -276,12 +278,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof
               const float g4[4] = {gvv.x, gvv.y, gvv.z, gvv.w}, v4[4] = {vrawf[x].x, vrawf[x].y, vrawf[x].z, vrawf[x].w};
 #pragma unroll
               for (int t = 0; t < 4; ++t) {
-                s = __builtin_amdgcn_mfma_f32_16x16x4f32(q4[t], k4[t], s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_16x16x4f32(g4[t], v4[t], dp, 0, 0, 0);
+                ss.add(t, q4[t], k4[t]);
+                dps.add(t, g4[t], v4[t]);
               }
+              ss.fold(x);
+              dps.fold(x);
               *reinterpret_cast<float4*>(&qrow[c16][16 * x + 4 * g]) = qv;
               *reinterpret_cast<float4*>(&grow[c16][16 * x + 4 * g]) = gvv;
             }
+            s = ss.total;
+            dp = dps.total;
           }
           if (lane < ET) { tsc[wave][lane] = sc_next; tum[wave][lane] = um_next; }
           wave_lds_fence();

@@ -6,17 +6,19 @@
 //
 // Bound by the matrix instructions of the heavy pairs (64 of 32 cycles per tile at D = 64), which therefore go to several
 // CUs; partial rows are what a CU more costs in memory, and ff_c3_cut says how many there is room for.  At 4 heads of 8k
-// tokens with 128 key clusters and r = 4, 61 us and 10 for the reduction (three slices at most); one wave per slice and up to
+// tokens with 128 key clusters and r = 4, 65 us and 10 for the reduction (three slices at most); one wave per slice and up to
 // eight slices 71 + 10, a workgroup of eight waves per pair and no slices 112, a wave per (key block, 32 key clusters) that
-// walked a bit matrix of the selections 5100.
+// walked a bit matrix of the selections 5100.  D = 128 (there 156 us) keeps one wave per SIMD: with two, 73 registers spilled
+// take 228.
 #include "ff_common.h"
+#include "fp32_sum.h"
 
 namespace {
 
 constexpr int W = 4;  // waves per workgroup, one per SIMD
 
 template <int D>
-__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 4))) k_c3_pairs_f32(
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, 4))) k_c3_pairs_f32(
     const float* __restrict__ Q, const float* __restrict__ dO, const float* __restrict__ Ks, const float* __restrict__ Vs,
     const float* __restrict__ LSE, const float* __restrict__ delta, const int32_t* __restrict__ off_k,
     const int32_t* __restrict__ pair_off, const int32_t* __restrict__ c3_off, const int2* __restrict__ c3_map,
@@ -72,7 +74,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
     };
     if (wave < nw) gather(hfirst);
     for (int h0 = hfirst; h0 < hhi; h0 += step) {
-      f32x4_t s = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+      FoldSum ss, dps;
       wave_lds_fence();  // the previous tile's rows are read
 #pragma unroll
       for (int u = 0; u < MT; ++u) {
@@ -81,12 +83,15 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
         const float kv[4] = {kf[u].x, kf[u].y, kf[u].z, kf[u].w}, vv[4] = {vf[u].x, vf[u].y, vf[u].z, vf[u].w};
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          s = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[t], kv[t], s, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_16x16x4f32(gv[t], vv[t], dp, 0, 0, 0);
+          ss.add(t, qv[t], kv[t]);
+          dps.add(t, gv[t], vv[t]);
         }
+        ss.fold(u);
+        dps.fold(u);
         *reinterpret_cast<float4*>(&qrow[c16][16 * u + 4 * g]) = q4;
         *reinterpret_cast<float4*>(&grow[c16][16 * u + 4 * g]) = gn_[u];
       }
+      const f32x4_t s = ss.total, dp = dps.total;
       if (lane < 16) tsc[lane] = scn;
       wave_lds_fence();
       if (h0 + step < hhi) gather(h0 + step);
