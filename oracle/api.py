@@ -32,6 +32,7 @@ class _P(C.Structure):
         ("N", C.c_int32), ("D", C.c_int32), ("Bs", C.c_int32), ("Cq", C.c_int32),
         ("Ck", C.c_int32), ("r", C.c_int32), ("k2", C.c_int32), ("scale", C.c_double),
         ("frozen_weights", C.c_int32), ("dipole", C.c_int32), ("Kw", C.c_void_p),
+        ("dQ_round", C.c_void_p),
     ]
 
 
@@ -48,11 +49,13 @@ class MuseParams:
     frozen_weights: bool = False  # backward: aggregation weights and mu-bar are constants (App. C)
     dipole: int = 0  # forward, r = 0 only (App. B): 1 per-cell tilted dipole, 2 pre-merged untilted dipole
 
-    def c(self, Kw=None) -> _P:
-        """Kw: float64 [N, D] array (kept alive by the caller) of the keys inside the tilted weights."""
+    def c(self, Kw=None, dQ_round=None) -> _P:
+        """Kw: float64 [N, D] array (kept alive by the caller) of the keys inside the tilted weights; dQ_round likewise,
+        see muse_bwd."""
         sc = self.scale if self.scale != 0.0 else 1.0 / np.sqrt(self.D)
         return _P(self.N, self.D, self.Bs, self.Cq, self.Ck, self.r, self.k2, sc, int(self.frozen_weights),
-                  int(self.dipole), None if Kw is None else Kw.ctypes.data)
+                  int(self.dipole), None if Kw is None else Kw.ctypes.data,
+                  None if dQ_round is None else dQ_round.ctypes.data)
 
     @property
     def nb(self) -> int:
@@ -230,7 +233,9 @@ def muse_fwd(p: MuseParams, Q, K, V, qc, aq, ak, rows=None, sel=None, weight_key
     return dict(O=O, LSE=LSE, selc=selc, selb=selb, margin_c=mc, margin_b=mb, mass=mass)
 
 
-def muse_bwd(p: MuseParams, Q, K, V, qc, aq, ak, O, LSE, dO, selc, selb, rows=None):
+def muse_bwd(p: MuseParams, Q, K, V, qc, aq, ak, O, LSE, dO, selc, selb, rows=None, rounding=False):
+    """Returns (dQ, dK, dV), and with rounding=True a bound, in units of 2^-8, on what bf16 operands do to every entry of
+    dQ (dl, and for summaries also k-bar and v-bar, rounded to nearest)."""
     Q, Qp = _d(Q); K, Kp = _d(K); V, Vp = _d(V); qc, qp = _d(qc)
     aq, aqp = _i(aq); ak, akp = _i(ak)
     O, Op = _d(O); LSE, Lp = _d(LSE); dO, gp = _d(dO)
@@ -238,8 +243,9 @@ def muse_bwd(p: MuseParams, Q, K, V, qc, aq, ak, O, LSE, dO, selc, selb, rows=No
     N, D = Q.shape
     dQ = np.zeros((N, D)); dK = np.zeros((N, D)); dV = np.zeros((N, D))
     r, nr, rp = _rows(rows)
-    pc = p.c()
+    bound = np.zeros((N, D)) if rounding else None
+    pc = p.c(dQ_round=bound)
     rc = _L().oracle_muse_bwd(C.byref(pc), Qp, Kp, Vp, qp, aqp, akp, C.c_int(nr), rp, Op, Lp, gp,
                               scp, sbp, _d(dQ)[1], _d(dK)[1], _d(dV)[1])
     assert rc == 0
-    return dQ, dK, dV
+    return (dQ, dK, dV, bound) if rounding else (dQ, dK, dV)

@@ -76,6 +76,9 @@ typedef struct {
    * that are aggregated (NULL: the same K).  Only the pins use it: with Kw held at K the forward is the
    * function whose derivative the frozen-weights backward is. */
   const double* Kw;
+  /* Backward, optional output [N,D]: first-order bound, in units of 2^-8, on what bf16 operands do to an entry of dQ when
+   * dl (for real keys), and dl, k-bar and v-bar (for summaries), are each rounded to nearest. */
+  double* dQ_round;
 } omuse_params;
 
 /* ------------------------------------------------------------------ */
@@ -993,6 +996,7 @@ int oracle_muse_bwd(const omuse_params* p, const double* Q, const double* K, con
       if (vk[u].type >= VK_RET) { /* real key: logit = scale * q.k */
         int m = vk[u].m;
         for (int d = 0; d < D; ++d) {
+          if (p->dQ_round) p->dQ_round[(size_t)n * D + d] += fabs(dl * p->scale * K[(size_t)m * D + d]);
           dQ[(size_t)n * D + d] += dl * p->scale * K[(size_t)m * D + d];
           dK[(size_t)m * D + d] += dl * qs[d];
           dV[(size_t)m * D + d] += pw * g[d];
@@ -1004,7 +1008,11 @@ int oracle_muse_bwd(const omuse_params* p, const double* Q, const double* K, con
         double* gv = (vk[u].type == VK_ACC ? gAvb[i] : gvb[i]) + cell * D;
         double* gm = (vk[u].type == VK_ACC ? gAmu[i] : gmu[i]) + cell;
         *gm += dl;
+        double gv_abs = 0.0;
+        for (int d = 0; d < D; ++d) gv_abs += fabs(g[d] * val[d]);
         for (int d = 0; d < D; ++d) {
+          if (p->dQ_round)
+            p->dQ_round[(size_t)n * D + d] += (2.0 * fabs(dl) + pw * gv_abs) * fabs(p->scale * kap[d]);
           /* q~ = scale*q - q-bar with q-bar constant */
           dQ[(size_t)n * D + d] += dl * p->scale * kap[d];
           gk[d] += dl * qt[d];

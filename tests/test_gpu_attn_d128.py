@@ -1,6 +1,6 @@
 """Attention of bf16 inputs at D = 128 where its key/value-gradient kernel has edges: fewer rows than a step of 32 queries or
 a tile of 128 keys, steps past the last query, grouped queries, blocks that are no multiple of the tile.  Tolerance: the
-parity suite's."""
+parity suite's; where dQ would miss it, the oracle's bound on the rounding of its bf16 operands."""
 import math
 
 import pytest
@@ -18,11 +18,9 @@ CASES = {"d128_block96": ("cfg5", dict(N=768, Hq=4, Hkv=2, Cq=5, Ck=19, r=3, k2=
 @pytest.mark.parametrize("name", list(CASES))
 def test_ragged_blocks(name, monkeypatch):
     monkeypatch.setitem(base.CASES, name, CASES[name])
-    # the query gradient is other kernels' and is not compared here: its bf16 P and dS (2^-9 of terms of up to some 4, summed)
-    # put one entry of these inputs at 2.03e-2, above the suite's 2e-2, with or without the kernel that is tested
-    close = base.assert_close
-    monkeypatch.setattr(base, "assert_close", lambda got, want, p, what, **kw: "dQ" in what or close(got, want, p, what, **kw))
-    base.run_case(name, with_bwd=True)
+    # own_outputs: against gradients at the exact O one entry of dQ is at 2.03e-2 (the suite's bound is 2e-2), 0.7e-2 of it
+    # because delta = dO.O is taken with the O that the forward rounded to bf16
+    base.run_case(name, with_bwd=True, own_outputs=True)
 
 
 @pytest.mark.parametrize("N,Hq,Hkv", [(2, 1, 1), (31, 2, 1), (33, 1, 1), (129, 4, 2), (300, 3, 3)])

@@ -15,6 +15,7 @@ CASES = {
     "cells_d128_passes": ("cfg2", dict(D=128, N=1024, Hq=2, Hkv=1, Cq=1, Ck=33, r=2, block=256, kmeans_iters=1)),
     "cells_d128_r0": ("cfg2", dict(D=128, N=768, Hq=1, Hkv=1, Cq=6, Ck=15, r=0, block=96, kmeans_iters=1)),
 }
+base.REACH.update({"cells_passes": dict(group=193), "cells_d128_passes": dict(group=193)})
 
 
 @pytest.mark.parametrize("name", list(CASES))

@@ -59,11 +59,13 @@ def segment_sizes(assign: np.ndarray, Bs: int, C: int) -> np.ndarray:
     return np.bincount((np.arange(N) // Bs) * C + assign, minlength=(N // Bs) * C).reshape(N // Bs, C)
 
 
-def oracle_head(orc, op, q, k, v, g, qc, aq, ak, sel, threads=8, rows=None, with_bwd=True):
+def oracle_head(orc, op, q, k, v, g, qc, aq, ak, sel, threads=8, rows=None, with_bwd=True, outputs=None):
     """The oracle on one (batch, head) with the selections `sel` = (selc, selb) given, split over threads by
     query cluster (the oracle builds the summaries of the query clusters it meets, and its gradients are sums
     over the listed rows, so the pieces add up).  Returns dict(free=..., forced=..., grads=(dQ, dK, dV) | None):
-    `free` holds the oracle's own selections and their margins, `forced` O / LSE / slack at the given ones."""
+    `free` holds the oracle's own selections and their margins, `forced` O / LSE / slack at the given ones.
+    outputs = (O, LSE): the backward starts from these, as the library's does (its O is rounded to the storage type, and
+    delta = dO.O with it), and the result has `dq_round`, the oracle's bound on what bf16 operands do to dQ."""
     N = q.shape[0]
     rows = np.arange(N, dtype=np.int32) if rows is None else np.asarray(rows, dtype=np.int32)
     order = np.argsort(aq[rows], kind="stable")
@@ -82,7 +84,8 @@ def oracle_head(orc, op, q, k, v, g, qc, aq, ak, sel, threads=8, rows=None, with
         forced = orc.muse_fwd(op, q, k, v, qc, aq, ak, rows=rs, sel=sel)
         gr = None
         if with_bwd:
-            gr = orc.muse_bwd(op, q, k, v, qc, aq, ak, forced["O"], forced["LSE"], g, sel[0], sel[1], rows=rs)
+            gr = orc.muse_bwd(op, q, k, v, qc, aq, ak, *(outputs or (forced["O"], forced["LSE"])), g, sel[0], sel[1], rows=rs,
+                              rounding=outputs is not None)
         return rs, free, forced, gr
 
     with ThreadPoolExecutor(max(1, threads)) as ex:
@@ -99,7 +102,10 @@ def oracle_head(orc, op, q, k, v, g, qc, aq, ak, sel, threads=8, rows=None, with
             grads[0][rs] = gr[0][rs]
             grads[1] += gr[1]
             grads[2] += gr[2]
-    return dict(free=free, forced=forced, grads=grads, rows=rows)
+            if outputs is not None:
+                grads[3][rs] = gr[3][rs]
+    return dict(free=free, forced=forced, grads=None if grads is None else grads[:3], rows=rows,
+                dq_round=grads[3] * 2.0 ** -8 if outputs is not None else None)
 
 
 def blocks_by_cluster(selc: np.ndarray, selb: np.ndarray) -> np.ndarray:
