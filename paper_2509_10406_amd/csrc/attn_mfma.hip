@@ -90,24 +90,18 @@ __device__ __forceinline__ void fetch_tile(const bf16_t* __restrict__ src, int r
   if constexpr (NCH > 2) r.c = fetch_chunk<D, ROWS>(src, r0, N, 2);
   if constexpr (NCH > 3) r.d = fetch_chunk<D, ROWS>(src, r0, N, 3);
 }
-template <int D, int ROWS, bool ROWM, bool TRANS>
-__device__ __forceinline__ void commit_chunk(const uint4 v, int it, bf16_t (*rm)[D + 8], bf16_t (*tr)[ROWS + TPAD]) {
-  const int c = threadIdx.x + 256 * it, row = c % ROWS, cc = c / ROWS;
-  if (ROWM) *reinterpret_cast<uint4*>(&rm[row][cc * 8]) = v;
-  if (TRANS) {
-    tr[cc * 8 + 0][row] = (bf16_t)(v.x & 0xffffu); tr[cc * 8 + 1][row] = (bf16_t)(v.x >> 16);
-    tr[cc * 8 + 2][row] = (bf16_t)(v.y & 0xffffu); tr[cc * 8 + 3][row] = (bf16_t)(v.y >> 16);
-    tr[cc * 8 + 4][row] = (bf16_t)(v.z & 0xffffu); tr[cc * 8 + 5][row] = (bf16_t)(v.z >> 16);
-    tr[cc * 8 + 6][row] = (bf16_t)(v.w & 0xffffu); tr[cc * 8 + 7][row] = (bf16_t)(v.w >> 16);
-  }
+template <int D, int ROWS>
+__device__ __forceinline__ void commit_chunk(const uint4 v, int it, bf16_t (*rm)[D + 8]) {
+  const int c = threadIdx.x + 256 * it;
+  *reinterpret_cast<uint4*>(&rm[c % ROWS][c / ROWS * 8]) = v;
 }
-template <int D, int ROWS, bool ROWM, bool TRANS>
-__device__ __forceinline__ void commit_tile(const TileRegs& r, bf16_t (*rm)[D + 8], bf16_t (*tr)[ROWS + TPAD]) {
+template <int D, int ROWS>
+__device__ __forceinline__ void commit_tile(const TileRegs& r, bf16_t (*rm)[D + 8]) {
   constexpr int NCH = ROWS * (D / 8) / 256;
-  commit_chunk<D, ROWS, ROWM, TRANS>(r.a, 0, rm, tr);
-  if constexpr (NCH > 1) commit_chunk<D, ROWS, ROWM, TRANS>(r.b, 1, rm, tr);
-  if constexpr (NCH > 2) commit_chunk<D, ROWS, ROWM, TRANS>(r.c, 2, rm, tr);
-  if constexpr (NCH > 3) commit_chunk<D, ROWS, ROWM, TRANS>(r.d, 3, rm, tr);
+  commit_chunk<D, ROWS>(r.a, 0, rm);
+  if constexpr (NCH > 1) commit_chunk<D, ROWS>(r.b, 1, rm);
+  if constexpr (NCH > 2) commit_chunk<D, ROWS>(r.c, 2, rm);
+  if constexpr (NCH > 3) commit_chunk<D, ROWS>(r.d, 3, rm);
 }
 
 // Transposed tile in operand order.  The second contraction of the backward kernels takes, for lane half h and the
@@ -225,7 +219,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
   fetch_pairs<D, BN>(V + kh * D, kbeg, N, vreg);
   for (int k0 = kbeg; k0 < kend; k0 += BN) {
     __syncthreads();
-    commit_tile<D, BN, true, false>(kreg, ks, nullptr);
+    commit_tile<D, BN>(kreg, ks);
     commit_pairs<D, BN, true, false>(vreg, nullptr, vt);
     __syncthreads();
     if (k0 + BN < kend) {  // in flight while this tile is consumed
@@ -379,7 +373,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
   fetch_pairs<D, BN>(V + kh * D, kbeg, N, vreg);
   for (int k0 = kbeg; k0 < kend; k0 += BN) {
     __syncthreads();
-    commit_tile<D, BN, true, false>(kreg, ks, nullptr);
+    commit_tile<D, BN>(kreg, ks);
     commit_pairs<D, BN, true, false>(vreg, nullptr, vt);
     __syncthreads();
     if (k0 + BN < kend) {  // in flight while this tile is consumed

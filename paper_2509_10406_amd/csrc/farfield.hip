@@ -628,7 +628,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
     else load_ktile<D>(kt, Amu, A_k + acell * D, j0, Ck, col, half);
   };
   auto score_kt = [&](const KT& kt, int j0) {
-    if constexpr (kH) return score_ktile_h<D>(kt, j0, Ck, qb, qh, scale, half);
+    if constexpr (kH) return score_ktile_h<D>(kt, j0, Ck, qb, [&](int ks) { return qh[ks]; }, scale, half);
     else return score_ktile<D>(kt, j0, Ck, qt, half);
   };
 

@@ -141,17 +141,15 @@ __device__ __forceinline__ void load_ktile_h(KTileH<D>& kt, const float* __restr
   }
 }
 
-// qb / qh: the lane's query (column) dims 16 ks + 8 half .. + 7 as bf16 and as fp16
-template <int D>
-__device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, int Ck, const bf16x8_t (&qb)[D / 16],
-                                                  const f16x8_t (&qh)[D / 16], float scale, int half) {
-  f32x16_t acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+// qb: the lane's query (column) dims 16 ks + 8 half .. + 7 as bf16; qh(ks): the same as fp16
+template <int D, typename F>
+__device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, int Ck, const bf16x8_t (&qb)[D / 16], F qh,
+                                                  float scale, int half) {
+  f32x16_t acc = zero16();
 #pragma unroll
   for (int ks = 0; ks < D / 16; ++ks) {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kt.h[ks]), qb[ks], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, kt.m[ks]), qh[ks], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, kt.m[ks]), qh(ks), acc, 0, 0, 0);
   }
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
@@ -165,10 +163,7 @@ __device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, i
 template <int D>
 __device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, int Ck, const bf16x8_t (&qb)[D / 16],
                                                   float scale, int half) {
-  f32x16_t acc = zero16();
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kt.h[ks]), qb[ks], acc, 0, 0, 0);
+  return score_ktile_h<D>(kt, j0, Ck, qb, [&](int ks) {
     uint4 raw = __builtin_bit_cast(uint4, qb[ks]);
     if constexpr (D == 128) {
       asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
@@ -178,14 +173,8 @@ __device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, i
     f16x8_t qh;
 #pragma unroll
     for (int e = 0; e < 8; ++e) qh[e] = (_Float16)(float)q[e];
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, kt.m[ks]), qh, acc, 0, 0, 0);
-  }
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int jr = j0 + 8 * (e / 4) + 4 * half + (e % 4);
-    acc[e] = jr < Ck ? fmaf(scale, acc[e], kt.mu[e]) : MUSE_NEG_INF;
-  }
-  return acc;
+    return qh;
+  }, scale, half);
 }
 
 // The bf16 plane alone: an approximate score, off by at most scale * 2^-8 * |q| . |k-bar| (the plane is k-bar rounded
@@ -257,17 +246,6 @@ __device__ __forceinline__ bf16x8_t ld_tr8(const bf16_t* row, int r0, int half) 
   return *reinterpret_cast<bf16x8_t*>(&v);
 }
 
-__device__ __forceinline__ __bf16 bits_to_bf16(bf16_t b) { return __builtin_bit_cast(__bf16, b); }
-
-__device__ __forceinline__ bf16x8_t cvt8(const float* __restrict__ p) {
-  float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-  bf16x8_t r;
-  r[0] = (__bf16)a.x; r[1] = (__bf16)a.y; r[2] = (__bf16)a.z; r[3] = (__bf16)a.w;
-  r[4] = (__bf16)b.x; r[5] = (__bf16)b.y; r[6] = (__bf16)b.z; r[7] = (__bf16)b.w;
-  return r;
-}
-
-
 constexpr int kMaxCk = 2304;  // key clusters a kernel can index in LDS
 static_assert(kMaxCk >= MUSE_MAX_CLUSTERS, "the host accepts more clusters than the kernels index");
 constexpr int kRunTiles = 4;  // hit tiles (of 32) per work item of the retrieval forward / dq pair kernels
@@ -288,8 +266,9 @@ static inline size_t ff_ret_part_bytes(const MuseDims& d) {
   return (size_t)d.B * d.Hq * d.N * (d.r > 0 ? d.r : 1) * d.k2e * (d.D + 4) * 4;
 }
 static inline size_t ff_c3_slice_bytes(const MuseDims& d) { return (size_t)d.B * d.Hkv * d.N * 2 * d.D * 4; }
-// Tiles per slice.  A further slice costs a partial row of dK and dV per key, written and read again (as many bytes as the
-// gathered rows of four tiles), so where the problem fills the device with long slices (4096 of them), they are long: at
+// Tiles per slice.  A further slice costs a partial row of dK and dV per key of the pair, written and read again (16 D bytes;
+// the gathered rows of a tile of bf16 hits are 128 D: one tile's worth at 8 keys, eight at 64), so where the problem fills the
+// device with long slices (4096 of them), they are long: at
 // 16 heads of 64k tokens with 128 x 128 clusters 16 tiles against 4 take 1.22 + 0.16 ms (kernel + reduction) against
 // 1.55 + 0.39, at 12 heads of 6k 4 tiles are what keeps the device busy.
 // fp32 inputs have no partial rows per (query, slot): the slices take the room that bf16 inputs need for them and that of the

@@ -241,7 +241,11 @@ int muse_launch_c3_reduce(const MuseDims& d, FFWorkspace& w, hipStream_t st) {
 
 int muse_launch_c3_pairs(const MuseDims& d, const void* Q, const void* dO, const float* LSE, FFWorkspace& w, hipStream_t st) {
   const int HK = d.B * d.Hkv;
-  // a pair has N / (nb Ck) keys on average and a few times that at most
+  // A pair has N / (nb Ck) keys on average and a few times that at most: 1, 2 or 4 workgroups share its groups of keys, each
+  // of which gathers the hits anew.  Kernel us with 1 / 2 / 4, by keys of the average pair: 16 heads of 64k tokens, r = 8,
+  //   8: 722 797 894   16: 759 802 854   32: 949 963 1023   64: 1234 1221 1250   128: 1713 1641 1632;
+  // 8 heads of 16k   8: 75 77 88   16: 103 93 94   32: 112 103 113   64: 149 132 132   128: 240 181 168;
+  // 32 heads of 32k, D = 128   8: 962 1024 1025   16: 1341 1256 1258   32: 1785 1543 1651   64: 2820 2509 2340.
   const int keys = d.N / (d.nb * d.Ck), z = keys <= 16 ? 1 : keys <= 32 ? 2 : 4;
   const dim3 g((unsigned)w.run_cap, HK, z);
   const float sl = d.scale * 1.4426950408889634f;
