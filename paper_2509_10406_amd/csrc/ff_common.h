@@ -263,7 +263,7 @@ __host__ __device__ inline int c3_slices(int nhits, C3Cut cut) {
 // dK | dV rows of one hit slice
 static inline size_t ff_state_bytes(const MuseDims& d) { return (size_t)d.B * d.Hq * d.N * (d.D + 2) * 4; }
 static inline size_t ff_ret_part_bytes(const MuseDims& d) {
-  return (size_t)d.B * d.Hq * d.N * (d.r > 0 ? d.r : 1) * d.k2e * (d.D + 4) * 4;
+  return (size_t)d.B * d.Hq * d.N * (d.r > 0 ? d.r : 1) * d.k2e * (d.D + 2) * 4;
 }
 static inline size_t ff_c3_slice_bytes(const MuseDims& d) { return (size_t)d.B * d.Hkv * d.N * 2 * d.D * 4; }
 // Tiles per slice.  A further slice costs a partial row of dK and dV per key of the pair, written and read again (16 D bytes;
