@@ -215,10 +215,21 @@ struct MuseProf {
 // ---- stage launchers (one per translation unit) ------------------------------------------
 // kmeans.hip
 size_t muse_cluster_ws_bytes(const MuseDims& d);
-// d.streaming: the centroids come from the streaming pass (trace [heads,N], counts [heads,C]: optional outputs
-// of that pass; assign may then be NULL to stop after it)
-int muse_launch_cluster(const MuseDims& d, const void* X, int H, int C, const int32_t* init_idx,
-                        float* cent, int32_t* assign, int32_t* trace, float* counts, void* ws, hipStream_t st);
+// one clustering problem (queries or keys: H heads per batch entry, C clusters) with its own workspace and stream
+struct MuseClusterSide {
+  const void* X;
+  int H, C;
+  const int32_t* init_idx;
+  float* cent;
+  int32_t* assign;
+  int32_t* trace;
+  float* counts;
+  void* ws;
+  hipStream_t st;
+};
+// n = 1 or 2 problems; of two the launches take turns.  d.streaming: the centroids come from the streaming pass (trace
+// [heads,N], counts [heads,C]: optional outputs of that pass; assign may then be NULL, for all, to stop after it)
+int muse_launch_cluster(const MuseDims& d, const MuseClusterSide* sides, int n);
 // Stable bucketing of the N positions of every head by (spatial block, cluster):
 // perm [heads, N] position lists, off [heads, nb*C + 1] segment offsets.
 int muse_launch_bucket(const int32_t* assign, int heads, int N, int Bs, int C, int32_t* perm,

@@ -1010,15 +1010,36 @@ static bool wide_update(int rows_per_slot, long long waves) {
   return (rows_per_slot >= 12 && waves <= 8192) || rows_per_slot >= 96;
 }
 
+// One of the two clustering problems of a call on its way: the launches of an iteration are issued by themselves, so that
+// two problems on two streams can take turns.
 template <typename T>
-int cluster_impl(const MuseDims& d, const T* X, int H, int C, const int32_t* init_idx, float* cent,
-                 int32_t* assign, int32_t* trace, float* counts, void* ws, hipStream_t st) {
-  const int N = d.N, D = d.D, heads = d.B * H;
-  char* w = (char*)ws;
-  T* chat = (T*)w;                w += align256((size_t)heads * C * D * sizeof(T));
-  float* nhc2 = (float*)w;        w += align256((size_t)heads * C * sizeof(float));
-  int32_t* perm = (int32_t*)w;    w += align256((size_t)heads * N * sizeof(int32_t));
-  int32_t* off = (int32_t*)w;   w += align256((size_t)heads * ((size_t)d.nb * C + 1) * sizeof(int32_t));
+struct ClusterRun {
+  const MuseDims& d;
+  const T* X;
+  int C, heads, T_;
+  float* cent;
+  int32_t* assign;
+  hipStream_t st;
+  T* chat;
+  float* nhc2;
+  int32_t *perm, *off;
+  char* w;
+
+  ClusterRun(const MuseDims& d_, const MuseClusterSide& s)
+      : d(d_), X((const T*)s.X), C(s.C), heads(d_.B * s.H), T_(d_.streaming ? 0 : d_.T), cent(s.cent), assign(s.assign), st(s.st), w((char*)s.ws) {
+    chat = (T*)w;          w += align256((size_t)heads * C * d.D * sizeof(T));
+    nhc2 = (float*)w;      w += align256((size_t)heads * C * sizeof(float));
+    perm = (int32_t*)w;    w += align256((size_t)heads * d.N * sizeof(int32_t));
+    off = (int32_t*)w;     w += align256((size_t)heads * ((size_t)d.nb * C + 1) * sizeof(int32_t));
+  }
+  int begin(const int32_t* init_idx, int32_t* trace, float* counts);
+  int iteration(int it);
+};
+
+// the streaming pass, if asked for, and the centroids that the first assignment reads
+template <typename T>
+int ClusterRun<T>::begin(const int32_t* init_idx, int32_t* trace, float* counts) {
+  const int N = d.N, D = d.D;
   if (d.streaming) {
     // App. C "Centroid Computation": the streaming pass gives the centroids, one final assignment follows
     const size_t CS = (size_t)(C + 31) / 32 * 32;
@@ -1058,67 +1079,84 @@ int cluster_impl(const MuseDims& d, const T* X, int H, int C, const int32_t* ini
     MUSE_LAUNCH_CHECK();
     if (!assign) return MUSE_OK;
   }
-  const int T_ = d.streaming ? 0 : d.T;
   const int rows = heads * C;
   { MuseProf prof_("k_init_centroids", st); hipLaunchKernelGGL(k_init_centroids<T>, dim3((rows + 3) / 4), dim3(256), 0, st, X, d.streaming ? nullptr : init_idx, cent, chat, nhc2, N, D, C, rows); }
   MUSE_LAUNCH_CHECK();
-  for (int it = 0; it <= T_; ++it) {
-    if constexpr (sizeof(T) == 4) {
-      dim3 g((N + 63) / 64, heads);
-      if (D == 64) { MuseProf prof_("k_assign_f32", st); hipLaunchKernelGGL(k_assign_f32<64>, g, dim3(256), 0, st, (const float*)X, (const float*)chat, nhc2, assign, N, C); }
-      else { MuseProf prof_("k_assign_f32", st); hipLaunchKernelGGL(k_assign_f32<128>, g, dim3(256), 0, st, (const float*)X, (const float*)chat, nhc2, assign, N, C); }
-    } else {
-      // all centroids resident in LDS when they fit (rows padded to a multiple of 64 for the tile pairs)
-      const int Cpad = (C + 63) / 64 * 64;
-      const size_t res_bytes = (size_t)Cpad * (D + 8) * 2 + (size_t)Cpad * 4;
-      if (res_bytes <= 160 * 1024) {
-        static bool attr_set = false;
-        if (!attr_set) {
-          MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<64>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-          MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<128>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-          attr_set = true;
-        }
-        const int bp = (D == 64 ? 64 : 32) * kResWaves;  // points per batch
-        const int nbatch = (N + bp - 1) / bp;
-        int gx = (256 + heads - 1) / heads;  // about one workgroup per CU over all heads
-        gx = gx > nbatch ? nbatch : gx;
-        dim3 g(gx, heads);
-        if (D == 64) { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL(k_assign_res<64>, g, dim3(64 * kResWaves), res_bytes, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C, Cpad); }
-        else { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL(k_assign_res<128>, g, dim3(64 * kResWaves), res_bytes, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C, Cpad); }
-      } else {
-        constexpr int PT = 2;
-        dim3 g((N + 4 * 32 * PT - 1) / (4 * 32 * PT), heads);
-        if (D == 64) { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL((k_assign_bf16<64, PT>), g, dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C); }
-        else { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL((k_assign_bf16<128, PT>), g, dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C); }
+  return MUSE_OK;
+}
+
+// assignment `it`, and the centroid update behind it unless it is the last one
+template <typename T>
+int ClusterRun<T>::iteration(int it) {
+  const int N = d.N, D = d.D, rows = heads * C;
+  if constexpr (sizeof(T) == 4) {
+    dim3 g((N + 63) / 64, heads);
+    if (D == 64) { MuseProf prof_("k_assign_f32", st); hipLaunchKernelGGL(k_assign_f32<64>, g, dim3(256), 0, st, (const float*)X, (const float*)chat, nhc2, assign, N, C); }
+    else { MuseProf prof_("k_assign_f32", st); hipLaunchKernelGGL(k_assign_f32<128>, g, dim3(256), 0, st, (const float*)X, (const float*)chat, nhc2, assign, N, C); }
+  } else {
+    // all centroids resident in LDS when they fit (rows padded to a multiple of 64 for the tile pairs)
+    const int Cpad = (C + 63) / 64 * 64;
+    const size_t res_bytes = (size_t)Cpad * (D + 8) * 2 + (size_t)Cpad * 4;
+    if (res_bytes <= 160 * 1024) {
+      static bool attr_set = false;
+      if (!attr_set) {
+        MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<64>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<128>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        attr_set = true;
       }
+      const int bp = (D == 64 ? 64 : 32) * kResWaves;  // points per batch
+      const int nbatch = (N + bp - 1) / bp;
+      int gx = (256 + heads - 1) / heads;  // about one workgroup per CU over all heads
+      gx = gx > nbatch ? nbatch : gx;
+      dim3 g(gx, heads);
+      if (D == 64) { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL(k_assign_res<64>, g, dim3(64 * kResWaves), res_bytes, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C, Cpad); }
+      else { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL(k_assign_res<128>, g, dim3(64 * kResWaves), res_bytes, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C, Cpad); }
+    } else {
+      constexpr int PT = 2;
+      dim3 g((N + 4 * 32 * PT - 1) / (4 * 32 * PT), heads);
+      if (D == 64) { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL((k_assign_bf16<64, PT>), g, dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C); }
+      else { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL((k_assign_bf16<128, PT>), g, dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C); }
     }
-    MUSE_LAUNCH_CHECK();
-    if (it == T_ && d.balanced) {
-      // App. C "Balanced Assignment": the nearest-centroid assignment bucketed by (block, cluster), then the rows
-      // beyond the cap of their segment are placed again
-      const int cap = (int)((4LL * d.Bs) / C);
-      if (cap < 1 || (long long)cap * C < d.Bs) return MUSE_ERR_UNSUPPORTED;
-      int rc = muse_launch_bucket(assign, heads, N, d.Bs, C, perm, off, st);
-      if (rc) return rc;
-      const size_t lds = (size_t)C * 4 + (size_t)((d.Bs + 31) / 32) * 4 + (size_t)d.Bs * 2 + 16;
-      if (D == 64) { MuseProf prof_("k_balance", st); hipLaunchKernelGGL((k_balance<T, 64>), dim3(d.nb, heads), dim3(256), lds, st, X, chat, nhc2, perm, off, assign, N, d.Bs, C, cap); }
-      else { MuseProf prof_("k_balance", st); hipLaunchKernelGGL((k_balance<T, 128>), dim3(d.nb, heads), dim3(256), lds, st, X, chat, nhc2, perm, off, assign, N, d.Bs, C, cap); }
-      MUSE_LAUNCH_CHECK();
-    }
-    if (it == T_) break;
+  }
+  MUSE_LAUNCH_CHECK();
+  if (it == T_ && d.balanced) {
+    // App. C "Balanced Assignment": the nearest-centroid assignment bucketed by (block, cluster), then the rows
+    // beyond the cap of their segment are placed again
+    const int cap = (int)((4LL * d.Bs) / C);
+    if (cap < 1 || (long long)cap * C < d.Bs) return MUSE_ERR_UNSUPPORTED;
     int rc = muse_launch_bucket(assign, heads, N, d.Bs, C, perm, off, st);
     if (rc) return rc;
-    {
-      MuseProf prof_("k_update", st);
-      constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);
-      const int S = D == 64 ? S64 : S128;
-      const bool wide = wide_update(N / C / S, (long long)rows * S);
-      auto go = [&](auto* kernel, int grid, int block) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, st, X, perm, off, cent, chat, nhc2, N, C, d.nb, rows); };
-      if (D == 64) wide ? go(k_update<T, 64, true>, rows, 64 * S64) : go(k_update<T, 64, false>, (rows + 3) / 4, 256);
-      else wide ? go(k_update<T, 128, true>, rows, 64 * S128) : go(k_update<T, 128, false>, (rows + 3) / 4, 256);
-    }
+    const size_t lds = (size_t)C * 4 + (size_t)((d.Bs + 31) / 32) * 4 + (size_t)d.Bs * 2 + 16;
+    if (D == 64) { MuseProf prof_("k_balance", st); hipLaunchKernelGGL((k_balance<T, 64>), dim3(d.nb, heads), dim3(256), lds, st, X, chat, nhc2, perm, off, assign, N, d.Bs, C, cap); }
+    else { MuseProf prof_("k_balance", st); hipLaunchKernelGGL((k_balance<T, 128>), dim3(d.nb, heads), dim3(256), lds, st, X, chat, nhc2, perm, off, assign, N, d.Bs, C, cap); }
     MUSE_LAUNCH_CHECK();
   }
+  if (it == T_) return MUSE_OK;
+  int rc = muse_launch_bucket(assign, heads, N, d.Bs, C, perm, off, st);
+  if (rc) return rc;
+  {
+    MuseProf prof_("k_update", st);
+    constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);
+    const int S = D == 64 ? S64 : S128;
+    const bool wide = wide_update(N / C / S, (long long)rows * S);
+    auto go = [&](auto* kernel, int grid, int block) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, st, X, perm, off, cent, chat, nhc2, N, C, d.nb, rows); };
+    if (D == 64) wide ? go(k_update<T, 64, true>, rows, 64 * S64) : go(k_update<T, 64, false>, (rows + 3) / 4, 256);
+    else wide ? go(k_update<T, 128, true>, rows, 64 * S128) : go(k_update<T, 128, false>, (rows + 3) / 4, 256);
+  }
+  MUSE_LAUNCH_CHECK();
+  return MUSE_OK;
+}
+
+template <typename T>
+int cluster_impl(const MuseDims& d, const MuseClusterSide* sides, int n) {
+  ClusterRun<T> a(d, sides[0]), b(d, sides[n - 1]);
+  ClusterRun<T>* run[2] = {&a, &b};
+  for (int i = 0; i < n; ++i)
+    if (int rc = run[i]->begin(sides[i].init_idx, sides[i].trace, sides[i].counts)) return rc;
+  if (!a.assign) return MUSE_OK;  // the streaming pass alone
+  for (int it = 0; it <= a.T_; ++it)
+    for (int i = 0; i < n; ++i)
+      if (int rc = run[i]->iteration(it)) return rc;
   return MUSE_OK;
 }
 
@@ -1149,8 +1187,6 @@ int muse_launch_bucket(const int32_t* assign, int heads, int N, int Bs, int C, i
   return MUSE_OK;
 }
 
-int muse_launch_cluster(const MuseDims& d, const void* X, int H, int C, const int32_t* init_idx,
-                        float* cent, int32_t* assign, int32_t* trace, float* counts, void* ws, hipStream_t st) {
-  if (d.dtype == MUSE_DTYPE_FP32) return cluster_impl<float>(d, (const float*)X, H, C, init_idx, cent, assign, trace, counts, ws, st);
-  return cluster_impl<bf16_t>(d, (const bf16_t*)X, H, C, init_idx, cent, assign, trace, counts, ws, st);
+int muse_launch_cluster(const MuseDims& d, const MuseClusterSide* sides, int n) {
+  return d.dtype == MUSE_DTYPE_FP32 ? cluster_impl<float>(d, sides, n) : cluster_impl<bf16_t>(d, sides, n);
 }

@@ -221,7 +221,10 @@ int muse_cluster(const muse_params* p, const void* Q, const void* K, const int32
   hipStream_t st = (hipStream_t)stream;
   if ((rc = stamp_clear(ws, st))) return rc;
   char* w0 = (char*)ws + kTagBytes;
-  // the two problems are independent: the keys go to the second stream (own half of the workspace)
+  // The two problems are independent chains of small launches: the keys go to the second stream (own half of the
+  // workspace), the launches of the two are issued in turns, and only the end of the keys' chain is waited for.  With the
+  // wait queued before the queries' launches the chains ran one after the other (the layer with one fp32 head of 2k
+  // tokens: 651 -> 423 us; 8 heads of 16k: 2.47 -> 2.23 ms; the streaming pass of 16 heads of 32k: 10.6 -> 8.4 ms).
   MuseAux& ax = muse_aux_stream();
   const bool two = Q && K && ax.state == 1 && !muse_profiling();
   hipStream_t sk = two ? ax.s : st;
@@ -229,13 +232,14 @@ int muse_cluster(const muse_params* p, const void* Q, const void* K, const int32
     MUSE_HIP_CHECK(hipEventRecord(ax.fork, st));
     MUSE_HIP_CHECK(hipStreamWaitEvent(sk, ax.fork, 0));
   }
-  int rck = MUSE_OK, rcq = MUSE_OK;
-  if (K) rck = muse_launch_cluster(d, K, d.Hkv, d.Ck, k_init_idx, k_centroids, k_assign, nullptr, nullptr, w0 + muse_cluster_ws_bytes(d), sk);
+  MuseClusterSide sides[2];
+  int n = 0;
+  if (K) sides[n++] = {K, d.Hkv, d.Ck, k_init_idx, k_centroids, k_assign, nullptr, nullptr, w0 + muse_cluster_ws_bytes(d), sk};
+  if (Q) sides[n++] = {Q, d.Hq, d.Cq, q_init_idx, q_centroids, q_assign, nullptr, nullptr, w0, st};
+  rc = muse_launch_cluster(d, sides, n);
   // whatever happened, the caller's stream waits for what the second stream was given
   if (two && (hipEventRecord(ax.join, sk) != hipSuccess || hipStreamWaitEvent(st, ax.join, 0) != hipSuccess)) return MUSE_ERR_HIP;
-  if (rck) return rck;
-  if (Q) rcq = muse_launch_cluster(d, Q, d.Hq, d.Cq, q_init_idx, q_centroids, q_assign, nullptr, nullptr, w0, st);
-  return rcq;
+  return rc;
 }
 
 int muse_kmeans_stream(const muse_params* p, int side, const void* X, const int32_t* init_idx, float* centroids,
@@ -247,8 +251,9 @@ int muse_kmeans_stream(const muse_params* p, int side, const void* X, const int3
   if (ws_bytes < kTagBytes + muse_cluster_ws_bytes(d)) return MUSE_ERR_WORKSPACE_TOO_SMALL;
   d.streaming = true;
   if ((rc = stamp_clear(ws, (hipStream_t)stream))) return rc;
-  return muse_launch_cluster(d, X, side ? d.Hkv : d.Hq, side ? d.Ck : d.Cq, init_idx, centroids, nullptr, stream_assign,
-                             counts, (char*)ws + kTagBytes, (hipStream_t)stream);
+  const MuseClusterSide one = {X, side ? d.Hkv : d.Hq, side ? d.Ck : d.Cq, init_idx, centroids, nullptr, stream_assign,
+                               counts, (char*)ws + kTagBytes, (hipStream_t)stream};
+  return muse_launch_cluster(d, &one, 1);
 }
 
 int muse_fwd(const muse_params* p, const void* Q, const void* K, const void* V, const float* q_centroids,
