@@ -443,15 +443,71 @@ __global__ void __launch_bounds__(1024) k_bucket(const int32_t* __restrict__ ass
 // fixed tree.  S = 64 / (lanes of a row at 16 bytes each), so the order does not depend on which of the two forms runs:
 //   WIDE = false  one wave per cluster, 16 bytes per lane, the slots side by side in the wave (clusters of few rows);
 //   WIDE = true   a wave per slot, a lane per D / 64 dims: twice as many rows in flight and S times as many waves, for
-//                 clusters whose slots walk long chains of rows.  The line between them is in the launch.
+//                 clusters whose slots walk long chains of rows.  64 positions come with one load and go to scalar
+//                 registers: with a broadcast load per position these were half of the kernel's loads (ten iterations
+//                 at 8 bf16 heads of 32k rows, D = 128, 64 clusters: 788 -> 528 us).  The line between them is in the launch.
 // ------------------------------------------------------------------------------------------
+// acc += the rows at the n <= 64 positions that the lanes hold (lane u the u-th), in order, 32 rows in flight.  A position
+// goes to a scalar register, so that a row costs one load with a scalar base; Xl is the head's rows at this lane's dims.
+template <typename T, int D>
+__device__ __forceinline__ void add_rows_of(float (&acc)[D / 64], const T* __restrict__ Xl, int pos, int n) {
+  constexpr int EPL = D / 64, MPI = 32;
+  n = __builtin_amdgcn_readfirstlane(n);
+  for (int q = 0; q < n; q += MPI) {
+    struct __attribute__((aligned(EPL * sizeof(T)))) Row { T e[EPL]; } v[MPI];
+#pragma unroll
+    for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const Row*>(Xl + (size_t)__builtin_amdgcn_readlane(pos, min(q + u, n - 1)) * D);
+#pragma unroll
+    for (int u = 0; u < MPI; ++u) {
+      if (q + u >= n) continue;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        if constexpr (sizeof(T) == 2) acc[e] += bf16_bits_to_f32(v[u].e[e]);
+        else acc[e] += v[u].e[e];
+      }
+    }
+  }
+}
+
+// the end of the forms with a wave per slot: the slots' sums (lane l has the dims D / 64 l ..) and counts meet in LDS in the
+// fixed tree, wave 0 writes the centroid
+template <typename T, int D, int S>
+__device__ __forceinline__ void combine_slots(const float (&acc)[D / 64], int count, float (*sum)[D], int* cnt,
+                                              float* __restrict__ cent, T* __restrict__ chat, float* __restrict__ nhc2) {
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+#pragma unroll
+  for (int e = 0; e < D / 64; ++e) sum[wave][lane * (D / 64) + e] = acc[e];
+  if (lane == 0) cnt[wave] = count;
+  __syncthreads();
+  if (wave > 0) return;
+  count = 0;
+#pragma unroll
+  for (int s = 0; s < S; ++s) count += cnt[s];
+  if (count == 0) return;  // an empty cluster keeps its centroid
+  const float inv = (float)count;
+  float c[2] = {0.f, 0.f};
+#pragma unroll
+  for (int x = 0; x < D / 64; ++x) {
+    float t[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) t[s] = sum[s][lane + 64 * x];
+#pragma unroll
+    for (int o = 1; o < S; o *= 2)
+#pragma unroll
+      for (int s = 0; s + o < S; s += 2 * o) t[s] += t[s + o];
+    c[x] = t[0] / inv;
+    cent[lane + 64 * x] = c[x];
+  }
+  prep_row(c, chat, nhc2, D, lane);
+}
+
 template <typename T, int D, bool WIDE>
 __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) : 256) k_update(
     const T* __restrict__ X, const int32_t* __restrict__ perm, const int32_t* __restrict__ off, float* __restrict__ cent,
     T* __restrict__ chat, float* __restrict__ nhc2, int N, int C, int nb, int total) {
   constexpr int S = 64 / (D * (int)sizeof(T) / 16);  // row slots
   constexpr int EPL = WIDE ? D / 64 : 16 / (int)sizeof(T), RL = D / EPL;  // elements per lane, lanes per row
-  constexpr int MPI = WIDE ? 32 : 16;                // rows in flight per slot
+  constexpr int MPI = 16;                            // rows in flight per slot of the narrow form
   __shared__ float sum[WIDE ? S : 4][D];
   __shared__ int cnt[S];
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
@@ -465,32 +521,47 @@ __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) :
   float acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  // MPI members per round trip; the positions of the next MPI are requested together with the rows of these
   int count = 0;
-  for (int b = slot; b < nb; b += S) {
-    const int lo = oh[b * C + j], hi = oh[b * C + j + 1];
-    count += hi - lo;
-    if (lo >= hi) continue;
-    int rown[MPI];
-#pragma unroll
-    for (int u = 0; u < MPI; ++u) rown[u] = ph[lo + u < hi ? lo + u : hi - 1];
-    for (int p = lo; p < hi; p += MPI) {
-      int row[MPI];
-#pragma unroll
-      for (int u = 0; u < MPI; ++u) {
-        row[u] = rown[u];
-        rown[u] = ph[p + MPI + u < hi ? p + MPI + u : hi - 1];
+  if constexpr (WIDE) {
+    // 64 positions in one load, the next 64 requested before these rows
+    for (int b = slot; b < nb; b += S) {
+      const int lo = oh[b * C + j], hi = oh[b * C + j + 1];
+      count += hi - lo;
+      if (lo >= hi) continue;
+      int next = ph[min(lo + lane, hi - 1)];
+      for (int p = lo; p < hi; p += 64) {
+        const int pos = next;
+        next = ph[min(p + 64 + lane, hi - 1)];
+        add_rows_of<T, D>(acc, Xh, pos, min(hi - p, 64));
       }
-      struct __attribute__((aligned(EPL * sizeof(T)))) Row { T e[EPL]; } v[MPI];
+    }
+  } else {
+    // MPI members per round trip; the positions of the next MPI are requested together with the rows of these
+    for (int b = slot; b < nb; b += S) {
+      const int lo = oh[b * C + j], hi = oh[b * C + j + 1];
+      count += hi - lo;
+      if (lo >= hi) continue;
+      int rown[MPI];
 #pragma unroll
-      for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const Row*>(Xh + (size_t)row[u] * D);
+      for (int u = 0; u < MPI; ++u) rown[u] = ph[lo + u < hi ? lo + u : hi - 1];
+      for (int p = lo; p < hi; p += MPI) {
+        int row[MPI];
 #pragma unroll
-      for (int u = 0; u < MPI; ++u) {
-        if (p + u >= hi) continue;
+        for (int u = 0; u < MPI; ++u) {
+          row[u] = rown[u];
+          rown[u] = ph[p + MPI + u < hi ? p + MPI + u : hi - 1];
+        }
+        struct __attribute__((aligned(EPL * sizeof(T)))) Row { T e[EPL]; } v[MPI];
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-          if constexpr (sizeof(T) == 2) acc[e] += bf16_bits_to_f32(v[u].e[e]);
-          else acc[e] += v[u].e[e];
+        for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const Row*>(Xh + (size_t)row[u] * D);
+#pragma unroll
+        for (int u = 0; u < MPI; ++u) {
+          if (p + u >= hi) continue;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) {
+            if constexpr (sizeof(T) == 2) acc[e] += bf16_bits_to_f32(v[u].e[e]);
+            else acc[e] += v[u].e[e];
+          }
         }
       }
     }
@@ -498,30 +569,7 @@ __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) :
   const size_t at = (size_t)h * C + j;
   float* mine = sum[wave];
   if constexpr (WIDE) {
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) mine[chunk * EPL + e] = acc[e];
-    if (lane == 0) cnt[slot] = count;
-    __syncthreads();
-    if (wave > 0) return;
-    count = 0;
-#pragma unroll
-    for (int s = 0; s < S; ++s) count += cnt[s];
-    if (count == 0) return;  // an empty cluster keeps its centroid
-    const float inv = (float)count;
-    float c[2] = {0.f, 0.f};
-#pragma unroll
-    for (int x = 0; x < D / 64; ++x) {
-      float t[S];
-#pragma unroll
-      for (int s = 0; s < S; ++s) t[s] = sum[s][lane + 64 * x];
-#pragma unroll
-      for (int o = 1; o < S; o *= 2)
-#pragma unroll
-        for (int s = 0; s + o < S; s += 2 * o) t[s] += t[s + o];
-      c[x] = t[0] / inv;
-      cent[at * D + lane + 64 * x] = c[x];
-    }
-    prep_row(c, chat + at * D, nhc2 + at, D, lane);
+    combine_slots<T, D, S>(acc, count, sum, cnt, cent + at * D, chat + at * D, nhc2 + at);
   } else {
     for (int o = RL; o < 64; o <<= 1) count += __shfl_xor(count, o, 64);
     for (int o = RL; o < 64; o <<= 1)
@@ -542,6 +590,54 @@ __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) :
     }
     prep_row(c, chat + at * D, nhc2 + at, D, lane);
   }
+}
+
+// The same update straight from the assignments, without the bucketing launch before it: the wave of a slot finds the
+// members of its cluster in the slot's blocks by ballots, kScan positions at a time, into a list in LDS, and adds their
+// rows as the wide form does (same order, same bits).  Every workgroup reads its head's assignments, 4 N C bytes per head
+// from L2, so it is for small problems (scan_update); what it saves is a launch in a chain of dependent ones.
+constexpr int kScan = 1024;
+constexpr long long kScanMost = 4 << 20;
+template <typename T, int D>
+__global__ void __launch_bounds__(64 * (64 / (D * (int)sizeof(T) / 16))) k_update_scan(
+    const T* __restrict__ X, const int32_t* __restrict__ assign, float* __restrict__ cent, T* __restrict__ chat,
+    float* __restrict__ nhc2, int N, int Bs, int C) {
+  constexpr int S = 64 / (D * (int)sizeof(T) / 16), EPL = D / 64;
+  __shared__ float sum[S][D];
+  __shared__ int cnt[S];
+  __shared__ uint16_t list[S][kScan];
+  const int lane = threadIdx.x % 64, slot = threadIdx.x / 64, j = blockIdx.x, h = blockIdx.y;
+  const int32_t* ah = assign + (size_t)h * N;
+  const T* Xh = X + (size_t)h * N * D + lane * EPL;
+  float acc[EPL];
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+  int count = 0;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  for (int b = slot * Bs; b < N; b += S * Bs)
+    for (int p0 = b; p0 < b + Bs; p0 += kScan) {
+      const int hi = min(p0 + kScan, b + Bs);
+      int a[kScan / 64];
+#pragma unroll
+      for (int u = 0; u < kScan / 64; ++u) {
+        const int p = p0 + 64 * u + lane;
+        a[u] = ah[p < hi ? p : hi - 1];
+      }
+      int n = 0;
+#pragma unroll
+      for (int u = 0; u < kScan / 64; ++u) {
+        const bool mine = a[u] == j && p0 + 64 * u + lane < hi;
+        const unsigned long long m = __ballot(mine);
+        if (mine) list[slot][n + __popcll(m & below)] = (uint16_t)(64 * u + lane);
+        n += __popcll(m);
+      }
+      wave_lds_fence();
+      count += n;
+      for (int q = 0; q < n; q += 64) add_rows_of<T, D>(acc, Xh, p0 + list[slot][min(q + lane, n - 1)], min(n - q, 64));
+      wave_lds_fence();  // the list is rewritten
+    }
+  const size_t at = (size_t)h * C + j;
+  combine_slots<T, D, S>(acc, count, sum, cnt, cent + at * D, chat + at * D, nhc2 + at);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1002,13 +1098,18 @@ __global__ void __launch_bounds__(256) k_balance(const T* __restrict__ X, const 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Which form of k_update: the wide one while the device has room for its S times as many waves and a slot walks more
-// than a few rows (us per launch, wide / narrow: 8.8 / 13.7 at one fp32 head of 2k rows, 16 to 32 rows per slot; 13 / 18
-// at 12 bf16 heads of 6k, 10 to 32 rows), and always for long chains (28 / 59 at 6 heads of 20k with 43 and 125
-// clusters, 53 / 60 at 32 heads of 32k, D = 128, 128 rows); many short chains fill the device by themselves (103 / 42 at
-// 16 heads of 64k with 256 and 1024 clusters, 58 / 54 with 128).
+// than a few rows, and always for long chains; many short chains fill the device by themselves.  us for ten iterations,
+// wide / narrow: 241 / 371 at 4 fp32 heads of 8k rows with 32 clusters (64 rows per slot), 946 / 1008 at 16 heads of 64k
+// with 128 (64 rows), 1202 / 1186 with 256 (32 rows), 2773 / 2178 with 1024 (8 rows), 280 / 215 at 16 heads of 4k with 128
+// (4 rows), 1289 / 1435 at 32 heads of 32k, D = 128, with 128 (64 rows).
 static bool wide_update(int rows_per_slot, long long waves) {
-  return (rows_per_slot >= 12 && waves <= 8192) || rows_per_slot >= 96;
+  return (rows_per_slot >= 12 && waves <= 8192) || rows_per_slot >= 64;
 }
+
+// The update without the bucketing launch (k_update_scan), while what its workgroups read of the assignments stays small.
+// us for ten iterations, with / without it: 135 / 173 at one fp32 head of 2k rows with 16 clusters, 154 / 202 at 6 bf16
+// heads of 6k with 23, 204 / 206 at 16 heads of 4k with 64 (4 M words read), 292 / 213 with 128 (8 M).
+static bool scan_update(int heads, int N, int C) { return (long long)heads * C * N <= kScanMost; }
 
 // One of the two clustering problems of a call on its way: the launches of an iteration are issued by themselves, so that
 // two problems on two streams can take turns.
@@ -1132,11 +1233,19 @@ int ClusterRun<T>::iteration(int it) {
     MUSE_LAUNCH_CHECK();
   }
   if (it == T_) return MUSE_OK;
+  constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);  // row slots
+  if (scan_update(heads, N, C)) {
+    MuseProf prof_("k_update", st);
+    auto go = [&](auto* kernel, int block) { hipLaunchKernelGGL(kernel, dim3(C, heads), dim3(block), 0, st, X, assign, cent, chat, nhc2, N, d.Bs, C); };
+    if (D == 64) go(k_update_scan<T, 64>, 64 * S64);
+    else go(k_update_scan<T, 128>, 64 * S128);
+    MUSE_LAUNCH_CHECK();
+    return MUSE_OK;
+  }
   int rc = muse_launch_bucket(assign, heads, N, d.Bs, C, perm, off, st);
   if (rc) return rc;
   {
     MuseProf prof_("k_update", st);
-    constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);
     const int S = D == 64 ? S64 : S128;
     const bool wide = wide_update(N / C / S, (long long)rows * S);
     auto go = [&](auto* kernel, int grid, int block) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, st, X, perm, off, cent, chat, nhc2, N, C, d.nb, rows); };
