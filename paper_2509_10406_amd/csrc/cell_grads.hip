@@ -1,115 +1,190 @@
-// Gradients of the accumulated cells (component 1) for bf16 inputs: the queries of a (block b, query cluster i) group
-// against the accumulated summaries they saw are a dense attention-backward block with the summaries in the role of
-// keys and values:
+// Gradients of the cells (component 1) for bf16 inputs: the queries of a (block, query cluster i) group against the
+// accumulated summaries they saw are a dense attention-backward block with the summaries in the role of keys and values:
 //   g_A_k = sum dl q~,  g_A_v = sum p dO,  g_A_c = sum [dl (1 - q~.kbar) - p dO.vbar]
-// Operands are rounded to bf16 for the matrix cores (gradients only; no selection depends on them).
+// and an accumulated cell is a sum over the per-block cells before it, so what a per-block cell receives is the reverse
+// accumulation over the key blocks a = nb-2 .. 0 (all factors <= 1):
+//   R[a] = g_A[a] + exp(Amu[a] - Amu[a+1]) R[a+1],   G[a] = exp(mu[a] - Amu[a]) R[a]   (written out)
+// Operands are rounded to bf16 for the matrix cores (gradients only; no selection depends on them); R stays in fp32.
 //
-// One workgroup per group: its queries (up to 96 at a time, nearly always all of them) are staged in LDS once, row-major;
-// a wave walks the units of 16 key clusters (v_mfma_f32_16x16x32_bf16, the clusters being the columns) with the next
-// unit's summaries in flight.  The rows serve S and dP as they lie and G_k, G_v through transposed reads.  A group with
-// more than 96 queries takes further passes that add to the rows of the first.
+// A wave owns one unit of 16 key clusters of one query cluster (v_mfma_f32_16x16x32_bf16, the clusters being the columns)
+// and walks the key blocks downwards: the accumulators of the matrix instructions ARE R, decayed by a factor per lane
+// between two blocks.  The waves of a workgroup take neighbouring units and share the staged queries of the group (kRows
+// at a time, row-major: the rows serve S and dP as they lie and G_k, G_v through transposed reads).  Two stages and the
+// next block's summaries in flight, so a block costs one barrier.
 //
-// Bound by streaming the summaries in and the gradients out.  Units of 16 clusters halve a wave's accumulators against
-// 32: at D = 128 that is two waves per SIMD and 96 staged queries in place of one wave and 32, whose second passes read
-// and wrote everything again (10.2 -> 2.9 ms at 32 heads of 32k tokens, 128 x 512 clusters); at D = 64 three waves per
-// SIMD in place of two (3.43 -> 3.24 ms at 16 heads of 64k, 256 x 1024; 0.63 -> 0.45 ms with 128 x 128).
+// Bound by streaming the summaries in and the gradients out, 15.4 GB at 16 heads of 64k tokens with 256 x 1024 clusters: 3.13
+// ms, 4.9 TB/s, the copy rate.  With the reverse accumulation as a launch of its own the gradients of the accumulated cells
+// took a round trip through HBM in 16 bits: 3.25 + 3.37 ms there, 2.88 + 3.36 (now 2.89) at 32 heads of 32k, D = 128, 128 x 512,
+// 0.44 + 0.17 (now 0.30) at 16 heads of 64k with 128 x 128.
 #include "ff_common.h"
 #include "lds_tile.h"
 
 namespace {
 
-constexpr int kQR = 96;  // queries staged at a time
+// Three waves per SIMD at D = 64, two at D = 128 (registers).  Units per workgroup: ms at 16 heads of 64k tokens, D = 64,
+// 256 x 1024 clusters with 2 / 4 / 8 waves 3.87 / 3.13 / 4.48 (a third workgroup of 8 does not fit); at 32 heads of 32k, D = 128,
+// 128 x 512 clusters 5.46 / 3.46 / 2.89.  Stages of 64 queries in place of 32: 4.32 and 3.62.
+template <int D>
+struct CellCfg {
+  static constexpr int kWaves = D == 64 ? 4 : 8;  // units of a workgroup
+  static constexpr int kRows = 32;                // queries staged at a time
+  static constexpr int kOcc = D == 64 ? 3 : 2;    // waves per SIMD
+};
 
 template <int D>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, D == 64 ? 3 : 2))) k_ff_bwd_cells_mx(
+__global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu_waves_per_eu(CellCfg<D>::kOcc, CellCfg<D>::kOcc))) k_ff_bwd_cells_mx(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ dO, const float* __restrict__ qc,
-    const float* __restrict__ A_mu, const bf16_t* __restrict__ A_kb, const bf16_t* __restrict__ A_v,
-    const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q, const float* __restrict__ LSE,
-    const float* __restrict__ delta, const uint32_t* __restrict__ selmask, float* __restrict__ g_A_c,
-    bf16_t* __restrict__ g_A_k, bf16_t* __restrict__ g_A_v, int h0, int N, int nb, int Cq, int Ck, float scale) {
-  constexpr int KX = D / 32, MT = D / 16, CPR = D / 8;
-  __shared__ __attribute__((aligned(16))) bf16_t qs[kQR * D];
-  __shared__ __attribute__((aligned(16))) bf16_t gs[kQR * D];
-  __shared__ __attribute__((aligned(16))) float ls[kQR];
-  __shared__ __attribute__((aligned(16))) float ds[kQR];
-  __shared__ __attribute__((aligned(16))) uint32_t mws[4][kQR];
-  __shared__ __attribute__((aligned(16))) bf16_t tw[4][16][D + 8];
+    const float* __restrict__ s_mu, const float* __restrict__ A_mu, const bf16_t* __restrict__ A_kb,
+    const bf16_t* __restrict__ A_v, const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q,
+    const float* __restrict__ LSE, const float* __restrict__ delta, const uint32_t* __restrict__ selmask,
+    float* __restrict__ G_c, bf16_t* __restrict__ G_k, bf16_t* __restrict__ G_v, int h0, int N, int nb, int Cq, int Ck,
+    float scale) {
+  constexpr int KX = D / 32, MT = D / 16, CPR = D / 8, NW = CellCfg<D>::kWaves, RP = CellCfg<D>::kRows, NT = 64 * NW;
+  constexpr int NU = RP * CPR / NT;  // 16-byte chunks of a tensor per thread and stage
+  __shared__ __attribute__((aligned(16))) bf16_t qs[2][RP * D];
+  __shared__ __attribute__((aligned(16))) bf16_t gs[2][RP * D];
+  __shared__ __attribute__((aligned(16))) float ls[2][RP];
+  __shared__ __attribute__((aligned(16))) float ds[2][RP];
+  __shared__ __attribute__((aligned(16))) uint32_t mws[NW][RP];
+  __shared__ __attribute__((aligned(16))) bf16_t tw[NW][16][D + 8];
+  __shared__ __attribute__((aligned(16))) float cs[D];
+  __shared__ int2 grp[16];  // [a]: positions of the group that sees the accumulation up to key block a
   const int hl = blockIdx.z, hq = h0 + hl;
-  const int NBm = nb - 1, W = (Ck + 31) / 32, nunit = (Ck + 15) / 16;
-  const int b = blockIdx.y / Cq + 1, i = blockIdx.y % Cq;
+  const int NBm = nb - 1, W = (Ck + 31) / 32, nunit = (Ck + 15) / 16, ng = (nunit + NW - 1) / NW;
+  // the workgroups of one query cluster run on one XCD (x % 8), one after the other: they stage the same queries
+  const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
+  const int i = idx / ng * 8 + xcd;
+  if (i >= Cq) return;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, c16 = lane % 16, g = lane / 16;
+  const int unit = idx % ng * NW + wave;
+  const bool live = unit < nunit;  // the last workgroup's waves may have nothing but the staging to do
+  const int jc = unit * 16 + c16, jcl = min(jc, Ck - 1), bit = 16 * (unit & 1) + c16;
+  const bool jvalid = jc < Ck;
   const int32_t* oq = off_q + (size_t)hq * ((size_t)nb * Cq + 1);
-  const int qlo = oq[b * Cq + i], qhi = oq[b * Cq + i + 1];
-  const size_t acell = (((size_t)hl * NBm + (b - 1)) * Cq + i) * Ck;
-  const float* qci = qc + ((size_t)hq * Cq + i) * D;
-  struct CT {  // one unit of 16 accumulated summaries as this lane's operands (cluster c16, dims 32 x + 8 g ..)
+  const int32_t* pq = perm_q + (size_t)hq * N;
+  const bf16_t *Qh = Q + (size_t)hq * N * D, *Gh = dO + (size_t)hq * N * D;
+  const float *Lh = LSE + (size_t)hq * N, *Dh = delta + (size_t)hq * N;
+  const uint32_t* sm = selmask + ((size_t)hq * W + min(unit / 2, W - 1)) * N;
+  if (threadIdx.x < NBm) grp[threadIdx.x] = make_int2(oq[(threadIdx.x + 1) * Cq + i], oq[(threadIdx.x + 1) * Cq + i + 1]);
+  if (threadIdx.x < D) cs[threadIdx.x] = qc[((size_t)hq * Cq + i) * D + threadIdx.x];
+  __syncthreads();
+
+  struct CT {  // the unit's accumulated summaries as this lane's operands (cluster c16, dims 32 x + 8 g ..)
     bf16x8_t kf[KX], vf[KX];
-    float amu;       // raw: any arithmetic on a prefetched value would wait for the whole prefetch at once
-    uint32_t mw[2];  // selection-mask words of the staged queries lane and 64 + lane
+    float amu, mu;  // raw: any arithmetic on a prefetched value would wait for the whole prefetch at once
   };
-  auto load_ct = [&](int unit, int q0, CT& c) {
-    const int jc = unit * 16 + c16 < Ck ? unit * 16 + c16 : Ck - 1;
+  auto cell_at = [&](int a) { return (((size_t)hl * NBm + a) * Cq + i) * Ck; };
+  auto load_ct = [&](int a, CT& c) {
+    const size_t cell = cell_at(a);
+    const bf16_t *kb = A_kb + cell * D, *vb = A_v + cell * D;  // uniform; the lane's offset takes 32 bits
+    const uint32_t o = (uint32_t)(jcl * D + 8 * g);
 #pragma unroll
     for (int x = 0; x < KX; ++x) {
-      c.kf[x] = *reinterpret_cast<const bf16x8_t*>(A_kb + (acell + jc) * D + 32 * x + 8 * g);
-      c.vf[x] = *reinterpret_cast<const bf16x8_t*>(A_v + (acell + jc) * D + 32 * x + 8 * g);
+      c.kf[x] = *reinterpret_cast<const bf16x8_t*>(kb + (o + 32 * x));
+      c.vf[x] = *reinterpret_cast<const bf16x8_t*>(vb + (o + 32 * x));
     }
-    c.amu = A_mu[acell + jc];
-#pragma unroll
-    for (int z = 0; z < 2; ++z) {
-      const int pq = q0 + 64 * z + lane;
-      c.mw[z] = selmask[((size_t)hq * W + unit / 2) * N + (pq < qhi ? pq : q0)];
-    }
+    c.amu = (A_mu + cell)[(uint32_t)jcl];
+    c.mu = (s_mu + cell)[(uint32_t)jcl];
   };
-  for (int q0 = qlo; q0 < qhi || q0 == qlo; q0 += kQR) {  // an empty group still writes its (zero) cells
-    const bool first = q0 == qlo;
-    const int ntl = q0 < qhi ? min((qhi - q0 + 31) / 32, kQR / 32) : 0;  // staged tiles of 32 queries
-    __syncthreads();
+  // The stages in order: (a, q0), the queries q0 .. of the group of key block a; an empty group is one stage of no rows.
+  struct Cur { int a, q0, hi; };
+  auto advance = [&](Cur c) {  // past the end: the last stage again
+    c.q0 += RP;
+    if (c.q0 >= c.hi && c.a > 0) {
+      const int2 gr = grp[--c.a];
+      c.q0 = __builtin_amdgcn_readfirstlane(gr.x);
+      c.hi = __builtin_amdgcn_readfirstlane(gr.y);
+    }
+    return c;
+  };
+  // a row past the group's end repeats its first one (weight 0); an empty group's are never used
+  auto pos_of = [&](const Cur& c, int row) { return min(c.q0 + row < c.hi ? c.q0 + row : c.q0, N - 1); };
+  int pos[NU];               // sequence positions of this thread's rows, one stage ahead of the rows
+  uint4 rq[NU], rg[NU];      // its chunks of a stage on their way
+  float rl[NU], rd[NU];
+  uint32_t rm;
+  auto load_pos = [&](const Cur& c) {
 #pragma unroll
-    for (int u = 0; u < kQR * CPR / 256; ++u) {
-      const int c = threadIdx.x + 256 * u, row = c / CPR, cc = c % CPR;
-      if (row < 32 * ntl) {
-        const int pos = q0 + row < qhi ? q0 + row : q0;
-        const size_t qn = (size_t)hq * N + perm_q[(size_t)hq * N + pos];
-        const uint4 qv = *reinterpret_cast<const uint4*>(Q + qn * D + cc * 8);
-        const uint4 gvv = *reinterpret_cast<const uint4*>(dO + qn * D + cc * 8);
-        const float4 c0 = *reinterpret_cast<const float4*>(qci + cc * 8), c1 = *reinterpret_cast<const float4*>(qci + cc * 8 + 4);
-        auto two = [&](uint32_t w, float a, float b2) {
-          return pack_bf16x2(scale * (__uint_as_float(w << 16) - a), scale * (__uint_as_float(w & 0xffff0000u) - b2));
-        };
-        *reinterpret_cast<uint4*>(qs + tile_at<D>(row, cc)) = make_uint4(two(qv.x, c0.x, c0.y), two(qv.y, c0.z, c0.w), two(qv.z, c1.x, c1.y), two(qv.w, c1.z, c1.w));
-        *reinterpret_cast<uint4*>(gs + tile_at<D>(row, cc)) = gvv;
+    for (int u = 0; u < NU; ++u) pos[u] = pq[pos_of(c, ((int)threadIdx.x + NT * u) / CPR)];
+  };
+  auto load_rows = [&](const Cur& c) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const uint32_t o = (uint32_t)(pos[u] * D + ((int)threadIdx.x + NT * u) % CPR * 8);
+      rq[u] = *reinterpret_cast<const uint4*>(Qh + o);
+      rg[u] = *reinterpret_cast<const uint4*>(Gh + o);
+      rl[u] = Lh[(uint32_t)pos[u]];
+      rd[u] = Dh[(uint32_t)pos[u]];
+    }
+    rm = sm[pos_of(c, lane % RP)];
+  };
+  auto commit = [&](const Cur& c, int buf) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int t = tid + NT * u, row = t / CPR, cc = t % CPR;
+      const float4 c0 = *reinterpret_cast<const float4*>(cs + cc * 8), c1 = *reinterpret_cast<const float4*>(cs + cc * 8 + 4);
+      auto two = [&](uint32_t w, float x, float y) {
+        return pack_bf16x2(scale * (__uint_as_float(w << 16) - x), scale * (__uint_as_float(w & 0xffff0000u) - y));
+      };
+      *reinterpret_cast<uint4*>(qs[buf] + tile_at<D>(row, cc)) =
+          make_uint4(two(rq[u].x, c0.x, c0.y), two(rq[u].y, c0.z, c0.w), two(rq[u].z, c1.x, c1.y), two(rq[u].w, c1.z, c1.w));
+      *reinterpret_cast<uint4*>(gs[buf] + tile_at<D>(row, cc)) = rg[u];
+      if (cc == 0) {
+        ls[buf][row] = c.q0 + row < c.hi ? rl[u] * 1.4426950408889634f : __builtin_huge_valf();  // +inf -> p = 0 for padding rows
+        ds[buf][row] = rd[u];
       }
     }
-    if (threadIdx.x < 32 * ntl) {
-      const int row = threadIdx.x;
-      const bool ok = q0 + row < qhi;
-      const size_t qn = (size_t)hq * N + perm_q[(size_t)hq * N + (ok ? q0 + row : q0)];
-      ls[row] = ok ? LSE[qn] * 1.4426950408889634f : __builtin_huge_valf();  // +inf -> p = 0 for padding rows
-      ds[row] = delta[qn];
-    }
-    __syncthreads();
-    CT cur, nxt;
-    const int qm = q0 < qhi ? q0 : 0;
-    if (wave < nunit) load_ct(wave, qm, cur);
-    for (int unit = wave; unit < nunit; unit += 4) {
-      // always issued (the last unit again at the end): with the same number of loads in flight on every path the wait
-      // for this unit's operands can leave the next unit's loads outstanding
-      load_ct(unit + 4 < nunit ? unit + 4 : unit, qm, nxt);
-      wave_lds_fence();
-      mws[wave][lane] = cur.mw[0];
-      if (lane < kQR - 64) mws[wave][64 + lane] = cur.mw[1];
-      wave_lds_fence();
-      const int jc = unit * 16 + c16, bit = 16 * (unit & 1) + c16;
-      const bool jvalid = jc < Ck;
-      const float amu2 = jvalid ? cur.amu * 1.4426950408889634f : MUSE_NEG_INF;
-      f32x4_t gk[MT], gv[MT];
+    if (lane < RP) mws[wave][lane] = rm;
+  };
+
+  f32x4_t gk[MT], gv[MT];
 #pragma unroll
-      for (int m = 0; m < MT; ++m)
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) { gk[m][t] = 0.f; gv[m][t] = 0.f; }
-      float csum = 0.f;
-      for (int qt = 0; qt < ntl; ++qt) {
+    for (int t = 0; t < 4; ++t) { gk[m][t] = 0.f; gv[m][t] = 0.f; }
+  float rc = 0.f, an = 0.f;
+  CT cur, nxt;
+  Cur here, ahead;  // the stage whose rows are committed next, and the one behind it
+  {
+    const int2 gr = grp[NBm - 1];
+    here = {NBm - 1, __builtin_amdgcn_readfirstlane(gr.x), __builtin_amdgcn_readfirstlane(gr.y)};
+  }
+  load_pos(here);
+  load_ct(NBm - 1, nxt);
+  load_rows(here);
+  ahead = advance(here);
+  load_pos(ahead);
+  int buf = 0;
+  for (int a = NBm - 1; a >= 0; --a) {
+    float csum = 0.f, amu2 = 0.f;
+    for (bool first = true;; first = false) {
+      commit(here, buf);
+      __syncthreads();
+      const int nrow = here.hi - here.q0, ntl = min((nrow + 31) / 32, RP / 32);
+      const bool last = nrow <= RP;
+      here = ahead;
+      load_rows(here);
+      ahead = advance(here);
+      load_pos(ahead);
+      if (first) {
+        cur = nxt;
+        load_ct(a > 0 ? a - 1 : 0, nxt);
+        const float f = (a < NBm - 1 && cur.amu > MUSE_NEG_INF) ? __expf(cur.amu - an) : 0.f;
+        an = cur.amu;
+        amu2 = jvalid ? cur.amu * 1.4426950408889634f : MUSE_NEG_INF;
+        rc *= f;
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) { gk[m][t] *= f; gv[m][t] *= f; }
+      }
+      // LDS offsets are made from the lane number here, not kept in registers over the whole walk
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      const int c16 = ln % 16, g = ln / 16;
+      for (int qt = 0; live && qt < ntl; ++qt) {
         bf16x8_t pf, df;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -117,10 +192,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
           f32x4_t s = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int x = 0; x < KX; ++x) {
-            s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_row<D>(qs, r0 + c16, 4 * x + g), cur.kf[x], s, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_row<D>(gs, r0 + c16, 4 * x + g), cur.vf[x], dp, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_row<D>(qs[buf], r0 + c16, 4 * x + g), cur.kf[x], s, 0, 0, 0);
+            dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_row<D>(gs[buf], r0 + c16, 4 * x + g), cur.vf[x], dp, 0, 0, 0);
           }
-          const float4 l4 = *reinterpret_cast<const float4*>(&ls[r0 + 4 * g]), d4 = *reinterpret_cast<const float4*>(&ds[r0 + 4 * g]);
+          const float4 l4 = *reinterpret_cast<const float4*>(&ls[buf][r0 + 4 * g]), d4 = *reinterpret_cast<const float4*>(&ds[buf][r0 + 4 * g]);
           const uint4 w4 = *reinterpret_cast<const uint4*>(&mws[wave][r0 + 4 * g]);
           const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
           const uint32_t mv[4] = {w4.x, w4.y, w4.z, w4.w};
@@ -138,49 +213,45 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
         const int rr = 32 * qt + 4 * g + c16 / 4, cc = 4 * (c16 % 4);
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
-          const bf16x8_t ag = tr_join(tile_tr4<D>(gs, rr, 16 * m + cc), tile_tr4<D>(gs, rr + 16, 16 * m + cc));
+          const bf16x8_t ag = tr_join(tile_tr4<D>(gs[buf], rr, 16 * m + cc), tile_tr4<D>(gs[buf], rr + 16, 16 * m + cc));
           gv[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag, pf, gv[m], 0, 0, 0);
-          const bf16x8_t aq = tr_join(tile_tr4<D>(qs, rr, 16 * m + cc), tile_tr4<D>(qs, rr + 16, 16 * m + cc));
+          const bf16x8_t aq = tr_join(tile_tr4<D>(qs[buf], rr, 16 * m + cc), tile_tr4<D>(qs[buf], rr + 16, 16 * m + cc));
           gk[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, df, gk[m], 0, 0, 0);
         }
       }
-      csum += __shfl_xor(csum, 16, 64);
-      csum += __shfl_xor(csum, 32, 64);
-      // rows go out through a per-wave LDS tile: a store instruction then writes 64 / (D/8) whole rows of consecutive
-      // clusters (contiguous memory)
+      buf ^= 1;
+      if (last) break;
+      wave_lds_fence();  // the next stage rewrites this wave's mask words
+    }
+    csum += __shfl_xor(csum, 16, 64);
+    csum += __shfl_xor(csum, 32, 64);
+    rc += csum;
+    if (!live) continue;
+    const float wgt = cur.mu > MUSE_NEG_INF ? __expf(cur.mu - cur.amu) : 0.f;
+    const size_t cell = cell_at(a);
+    // rows go out through a per-wave LDS tile: a store instruction then writes 64 / (D/8) whole rows of consecutive
+    // clusters (contiguous memory)
 #pragma unroll
-      for (int arr = 0; arr < 2; ++arr) {
-        wave_lds_fence();
+    for (int arr = 0; arr < 2; ++arr) {
+      wave_lds_fence();
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-          const f32x4_t& a = arr == 0 ? gk[m] : gv[m];
-          *reinterpret_cast<uint2*>(&tw[wave][c16][16 * m + 4 * g]) = make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
-        }
-        wave_lds_fence();
-        bf16_t* dst = arr == 0 ? g_A_k : g_A_v;
+      for (int m = 0; m < MT; ++m) {
+        const f32x4_t& r = arr == 0 ? gk[m] : gv[m];
+        *reinterpret_cast<uint2*>(&tw[wave][c16][16 * m + 4 * g]) = make_uint2(pack_bf16x2(wgt * r[0], wgt * r[1]), pack_bf16x2(wgt * r[2], wgt * r[3]));
+      }
+      wave_lds_fence();
+      bf16_t* dst = arr == 0 ? G_k : G_v;
 #pragma unroll
-        for (int it = 0; it < 16 * CPR / 64; ++it) {
-          const int row = it * (64 / CPR) + lane / CPR, cc = lane % CPR;
-          if (unit * 16 + row < Ck) {
-            uint4 v = *reinterpret_cast<const uint4*>(&tw[wave][row][cc * 8]);
-            uint4* o = reinterpret_cast<uint4*>(dst + (acell + unit * 16 + row) * D + cc * 8);
-            if (!first) {  // further pass of a large group: add to what the earlier passes wrote
-              const uint4 old = *o;
-              auto add2 = [](uint32_t x, uint32_t y) {
-                return pack_bf16x2(__uint_as_float(x << 16) + __uint_as_float(y << 16),
-                                   __uint_as_float(x & 0xffff0000u) + __uint_as_float(y & 0xffff0000u));
-              };
-              v = make_uint4(add2(v.x, old.x), add2(v.y, old.y), add2(v.z, old.z), add2(v.w, old.w));
-            }
-            typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-            const u4_t vs = {v.x, v.y, v.z, v.w};
-            __builtin_nontemporal_store(vs, reinterpret_cast<u4_t*>(o));  // written once, read by the next kernel much later
-          }
+      for (int it = 0; it < 16 * CPR / 64; ++it) {
+        const int row = it * (64 / CPR) + lane / CPR, cc = lane % CPR;
+        if (unit * 16 + row < Ck) {
+          typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
+          const u4_t v = *reinterpret_cast<const u4_t*>(&tw[wave][row][cc * 8]);
+          __builtin_nontemporal_store(v, reinterpret_cast<u4_t*>(dst + (cell + unit * 16 + row) * D + cc * 8));  // written once, read by later kernels
         }
       }
-      if (jvalid && g == 0) g_A_c[acell + jc] = first ? csum : g_A_c[acell + jc] + csum;
-      cur = nxt;
     }
+    if (jvalid && g == 0) G_c[cell + jc] = wgt * rc;
   }
 }
 
@@ -188,15 +259,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 
 int muse_launch_ff_bwd_cells_mx(const MuseDims& d, const void* Q, const void* dO, const float* qc, const float* LSE,
                                 FFWorkspace& w, int h0, int hn, hipStream_t st) {
-  const dim3 g(1, (d.nb - 1) * d.Cq, hn);
-  auto go = [&](auto* kernel) {
+  auto go = [&](auto* kernel, int waves) {
     MuseProf prof_("k_ff_bwd_cells_mx", st);
-    hipLaunchKernelGGL(kernel, g, dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, qc, w.A_mu, (const bf16_t*)w.A_kb,
-                       (const bf16_t*)w.A_v, w.perm_q, w.off_q, LSE, w.delta, w.selmask, w.g_A_c, (bf16_t*)w.g_A_k,
-                       (bf16_t*)w.g_A_v, h0, d.N, d.nb, d.Cq, d.Ck, d.scale);
+    const int ng = ((d.Ck + 15) / 16 + waves - 1) / waves;
+    hipLaunchKernelGGL(kernel, dim3((d.Cq + 7) / 8 * 8 * ng, 1, hn), dim3(64 * waves), 0, st, (const bf16_t*)Q, (const bf16_t*)dO,
+                       qc, w.s_mu, w.A_mu, (const bf16_t*)w.A_kb, (const bf16_t*)w.A_v, w.perm_q, w.off_q, LSE, w.delta,
+                       w.selmask, w.g_s_c, (bf16_t*)w.g_s_k, (bf16_t*)w.g_s_v, h0, d.N, d.nb, d.Cq, d.Ck, d.scale);
   };
-  if (d.D == 64) go(k_ff_bwd_cells_mx<64>);
-  else go(k_ff_bwd_cells_mx<128>);
+  if (d.D == 64) go(k_ff_bwd_cells_mx<64>, CellCfg<64>::kWaves);
+  else go(k_ff_bwd_cells_mx<128>, CellCfg<128>::kWaves);
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

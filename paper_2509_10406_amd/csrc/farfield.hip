@@ -1441,11 +1441,14 @@ int muse_ff_carve(const MuseDims& d, bool bwd, void* ws, size_t ws_bytes, FFWork
   }
   if (bwd) {
     w->g_s_c = (float*)take(hc * cells * 4);
-    w->g_A_c = (float*)take(hc * cells * 4);
     w->g_s_k = take(hc * cells * D * es);
     w->g_s_v = take(hc * cells * D * es);
-    w->g_A_k = take(hc * cells * D * es);
-    w->g_A_v = take(hc * cells * D * es);
+    w->g_A_c = nullptr; w->g_A_k = nullptr; w->g_A_v = nullptr;
+    if (es == 4) {
+      w->g_A_c = (float*)take(hc * cells * 4);
+      w->g_A_k = (float*)take(hc * cells * D * 4);
+      w->g_A_v = (float*)take(hc * cells * D * 4);
+    }
   }
   if (d.dipole) w->dip_cbar = (float*)take(hc * (size_t)(d.nb > 1 ? d.nb - 1 : 1) * d.Cq * D * D * 4);
   w->hc = (int)hc;

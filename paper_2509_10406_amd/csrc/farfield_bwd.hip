@@ -647,20 +647,20 @@ __global__ void __launch_bounds__(64) k_ff_bwd_cells(
 }
 
 // ------------------------------------------------------------------------------------------
-// Gradients of the per-block cells from those of the accumulated cells: one block of 256 threads per (query
+// Gradients of the per-block cells from those of the accumulated cells, fp32 inputs (bf16: cell_grads.hip): one block of 256 threads per (query
 // cluster i, tile of 32 key clusters); wave w owns the 8 chains (i, j, all blocks), j = 32 jt + 8 w + c.  A
 // wave is 8 groups of 8 lanes; a lane holds D/8 elements of a row (d = 32 x + 4 l8 + t); group c owns chain c.
 // Reverse accumulation over the key blocks a = nb-2 .. 0, in registers:
 //      R[a] = gA[a] + exp(Amu[a] - Amu[a+1]) R[a+1],   G[a] = exp(mu[a] - Amu[a]) R[a]   (written out)
 // All factors are <= 1.  One owner per cell.  Component 2 is added afterwards by k_chain_grads.
 // ------------------------------------------------------------------------------------------
-template <typename T, int D>
+template <int D>
 __global__ void __launch_bounds__(256) k_cell_grads(
     const float* __restrict__ s_mu, const float* __restrict__ A_mu, const float* __restrict__ g_A_c,
-    const T* __restrict__ g_A_k, const T* __restrict__ g_A_v, float* __restrict__ G_c, T* __restrict__ G_k,
-    T* __restrict__ G_v, int nb, int Cq, int Ck) {
+    const float* __restrict__ g_A_k, const float* __restrict__ g_A_v, float* __restrict__ G_c, float* __restrict__ G_k,
+    float* __restrict__ G_v, int nb, int Cq, int Ck) {
   constexpr int NV = D / 32;
-  using F4 = Frag<T, 4>;
+  using F4 = Frag<float, 4>;
   const int hl = blockIdx.z;
   const int i = blockIdx.y, jt = blockIdx.x;
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, s8 = lane / 8, l8 = lane % 8;
@@ -868,15 +868,16 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
                          w.perm_q, aq, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.scale); }
   }
   st = sk_;
-  if (sizeof(T) == 2) {
+  if constexpr (sizeof(T) == 2) {
     const int rc2 = muse_launch_ff_bwd_cells_mx(d, Q, dO, qc, LSE, w, h0, hn, st);
     if (rc2) return rc2;
-  } else
-  { MuseProf prof_("k_ff_bwd_cells", st); hipLaunchKernelGGL((k_ff_bwd_cells<T, D>), dim3(W, NBm * d.Cq, hn), dim3(64), 0, st, Q, dO, qc, w.A_mu, w.A_k, (const float*)w.A_v,
-                     w.perm_q, w.off_q, LSE, w.delta, w.selmask, w.g_A_c, (float*)w.g_A_k, (float*)w.g_A_v, h0, d.N, d.nb, d.Cq, d.Ck,
-                     d.scale); }
-  { MuseProf prof_("k_cell_grads", st); hipLaunchKernelGGL((k_cell_grads<T, D>), dim3(W, d.Cq, hn), dim3(256), 0, st, w.s_mu, w.A_mu, w.g_A_c,
-                     (const T*)w.g_A_k, (const T*)w.g_A_v, w.g_s_c, (T*)w.g_s_k, (T*)w.g_s_v, d.nb, d.Cq, d.Ck); }
+  } else {
+    { MuseProf prof_("k_ff_bwd_cells", st); hipLaunchKernelGGL((k_ff_bwd_cells<T, D>), dim3(W, NBm * d.Cq, hn), dim3(64), 0, st, Q, dO, qc, w.A_mu, w.A_k, (const float*)w.A_v,
+                       w.perm_q, w.off_q, LSE, w.delta, w.selmask, w.g_A_c, w.g_A_k, w.g_A_v, h0, d.N, d.nb, d.Cq, d.Ck,
+                       d.scale); }
+    { MuseProf prof_("k_cell_grads", st); hipLaunchKernelGGL((k_cell_grads<D>), dim3(W, d.Cq, hn), dim3(256), 0, st, w.s_mu, w.A_mu, w.g_A_c,
+                       w.g_A_k, w.g_A_v, w.g_s_c, (float*)w.g_s_k, (float*)w.g_s_v, d.nb, d.Cq, d.Ck); }
+  }
   if (d.r > 0) {
     const int rc2 = muse_launch_chain_grads<T>(d, Q, dO, qc, LSE, w, h0, hn, st);
     if (rc2) return rc2;

@@ -310,14 +310,15 @@ struct FFWorkspace {
   float* L;
   uint32_t* chainmask;  // [hc][Cq][ceil(Ck/32)]: key clusters retrieved by some query of the query cluster
   uint32_t* chainmaskT;  // [hc][Ck][ceil(Cq/32)]: the same bits, key-cluster-major
-  // Value summaries and every cell gradient are stored in the input type.  The accumulated k-bar decides
+  // Value summaries and cell gradients are stored in the input type.  The accumulated k-bar decides
   // selections: fp32 inputs keep it in fp32 (A_k); bf16 inputs keep a bf16 plane A_kb (also the operand of the
   // gradient contractions), an fp16 plane A_km of the remainder and the scalar A_c = mu-bar - scale * qc_i . k-bar
   // per cell.
   float *s_mu, *s_k, *A_mu, *A_k, *A_c;
   void *s_v, *A_v, *A_kb, *A_km;
-  float *g_s_c, *g_A_c;
-  void *g_s_k, *g_s_v, *g_A_k, *g_A_v;
+  float* g_s_c;
+  void *g_s_k, *g_s_v;
+  float *g_A_c, *g_A_k, *g_A_v;  // gradients of the accumulated cells; fp32 inputs (bf16: never leave the kernel)
   // dipole correction (MUSE_FLAG_DIPOLE): untilted covariances [HK][nb-1][Ck][D][D] (all heads) and the merged
   // matrices [hc][nb-1][Cq][D][D] of a head chunk
   float *dip_cov, *dip_cbar;
@@ -387,7 +388,7 @@ static inline size_t ff_head_bytes(const MuseDims& d, bool bwd) {
   size_t es = d.dtype == MUSE_DTYPE_BF16 ? 2 : 4;
   size_t b = ff_al((size_t)d.Cq * d.N * 4) + ff_al((size_t)d.Cq * ((d.Ck + 31) / 32) * 4) + ff_al((size_t)d.Ck * ((d.Cq + 31) / 32) * 4) + 2 * ff_al(cells * 4) + ff_al(cells * D * 4) + 2 * ff_al(cells * D * es);
   b += es == 2 ? 2 * ff_al(cells * D * 2) + ff_al(cells * 4) : ff_al(cells * D * 4);
-  if (bwd) b += 2 * ff_al(cells * 4) + 4 * ff_al(cells * D * es);
+  if (bwd) b += (es == 2 ? 1 : 2) * (ff_al(cells * 4) + 2 * ff_al(cells * D * es));
   if (d.dipole) b += ff_al((size_t)(d.nb > 1 ? d.nb - 1 : 1) * d.Cq * D * D * 4);
   return b;
 }
@@ -402,7 +403,7 @@ int muse_ff_summaries(const MuseDims& d, const float* qc, FFWorkspace& w, int h0
 template <typename T>
 int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace& w, int h0, int hn, hipStream_t st);
 
-// cell_grads.hip: gradients of the accumulated cells (component 1), bf16 inputs, of the query heads [h0, h0+hn)
+// cell_grads.hip: component 1 of the per-block cell gradients, bf16 inputs, of the query heads [h0, h0+hn)
 int muse_launch_ff_bwd_cells_mx(const MuseDims& d, const void* Q, const void* dO, const float* qc, const float* LSE,
                                 FFWorkspace& w, int h0, int hn, hipStream_t st);
 // chain_grads.hip: component 2 of the per-block cell gradients of the query heads [h0, h0+hn)
