@@ -22,6 +22,9 @@ namespace {
 // group, so that every later read is coalesced):
 //   slotinfo[hq][p][t] = j | (bitmask of the retrieved key blocks) << 16 for slot t, -1 when the slot is empty
 //   selmask[hq][j/32][p]: bit j%32 set when query p retrieved key cluster j
+// R >= r: a query's slots are held in registers, so that all its loads are requested together (a loop over the slots beyond
+// eight took 1.02 ms at 32 heads of 32k with r = 16, this @T@).
+template <int R>
 __global__ void __launch_bounds__(256) k_selinfo(const int32_t* __restrict__ selc, const int32_t* __restrict__ selb,
                                                   const int32_t* __restrict__ perm_q, uint32_t* __restrict__ mask,
                                                   int32_t* __restrict__ slotinfo, int N, int r, int k2e, int W) {
@@ -30,51 +33,27 @@ __global__ void __launch_bounds__(256) k_selinfo(const int32_t* __restrict__ sel
   if (p >= N) return;
   const size_t q = hq * N + perm_q[hq * N + p];
   int32_t* si = slotinfo + (hq * N + p) * r;
-  int info[8];
+  int jj[R];
+  uint32_t bm[R];
 #pragma unroll
-  for (int t = 0; t < 8; ++t) info[t] = -1;
-  if (r <= 8 && k2e == 1) {
-    // the usual shape: the query's selections are requested together
-    int jj[8], bb[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      jj[t] = t < r ? selc[q * r + t] : -1;
-      bb[t] = t < r ? selb[q * r + t] : -1;
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      info[t] = jj[t] >= 0 ? (int)((uint32_t)jj[t] | ((bb[t] >= 0 ? 1u << bb[t] : 0u) << 16)) : -1;
-      if (t < r) si[t] = info[t];
-    }
-  } else {
-    for (int t = 0; t < r; ++t) {
-      const int j = selc[q * r + t];
-      int v = -1;
-      if (j >= 0) {
-        uint32_t bm = 0;
-        for (int u = 0; u < k2e; ++u) {
-          const int bb = selb[(q * r + t) * k2e + u];
-          bm |= bb >= 0 ? 1u << bb : 0u;
-        }
-        v = (int)((uint32_t)j | (bm << 16));
-      }
-      si[t] = v;
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (k == t) info[k] = v;
-    }
+  for (int t = 0; t < R; ++t) {
+    jj[t] = t < r ? selc[q * r + t] : -1;
+    bm[t] = 0;
   }
+  for (int u = 0; u < k2e; ++u) {
+    int bb[R];
+#pragma unroll
+    for (int t = 0; t < R; ++t) bb[t] = t < r ? selb[(q * r + t) * k2e + u] : -1;
+#pragma unroll
+    for (int t = 0; t < R; ++t) bm[t] |= bb[t] >= 0 ? 1u << bb[t] : 0u;
+  }
+#pragma unroll
+  for (int t = 0; t < R; ++t)
+    if (t < r) si[t] = jj[t] >= 0 ? (int)((uint32_t)jj[t] | (bm[t] << 16)) : -1;
   for (int w = 0; w < W; ++w) {
     uint32_t m = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int j = info[k] & 0xffff;
-      if (info[k] >= 0 && (j >> 5) == w) m |= 1u << (j & 31);
-    }
-    for (int t = 8; t < r; ++t) {
-      const int v = si[t], j = v & 0xffff;
-      if (v >= 0 && (j >> 5) == w) m |= 1u << (j & 31);
-    }
+    for (int t = 0; t < R; ++t) m |= (jj[t] >> 5) == w ? 1u << (jj[t] & 31) : 0u;
     mask[(hq * W + w) * N + p] = m;
   }
 }
@@ -932,7 +911,11 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
   if (d.nb > 1) {
     const int W = (d.Ck + 31) / 32;
     if (d.r > 0) {
-      { MuseProf prof_("k_selinfo", st); hipLaunchKernelGGL(k_selinfo, dim3((N + 255) / 256, HQ), dim3(256), 0, st, selc, selb, w.perm_q, w.selmask, w.slotinfo, N, d.r, d.k2e, W); }
+      { MuseProf prof_("k_selinfo", st); 
+        auto go = [&](auto* kernel) { hipLaunchKernelGGL(kernel, dim3((N + 255) / 256, HQ), dim3(256), 0, st, selc, selb, w.perm_q, w.selmask, w.slotinfo, N, d.r, d.k2e, W); };
+        if (d.r <= 8) go(k_selinfo<8>);
+        else if (d.r <= 16) go(k_selinfo<16>);
+        else go(k_selinfo<32>); }
     } else {
       if ((rc = muse_launch_fill_i32((int32_t*)w.selmask, nq * W, 0, st))) return rc;
     }
