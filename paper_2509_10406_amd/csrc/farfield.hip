@@ -384,9 +384,11 @@ __global__ void __launch_bounds__(64) k_chainmask_t(const uint32_t* __restrict__
   if (lane < 32 && j < Ck) maskT[((size_t)hl * Ck + j) * WT + itile] = mine;
 }
 
-// One wave per (query cluster i, tile of 32 key clusters).  A chain's blocks go to the wave's eight 8-lane
+// kChainSplit waves per (query cluster i, tile of 32 key clusters), each with every eighth chain (one wave for all 32 was a
+// chain of round trips: 59 us at one head of 2k rows, 16 x 32 clusters, against 16).  A chain's blocks go to the wave's eight 8-lane
 // groups (block b to group b % 8), each lane holding D/8 adjacent head dims.  With mu-bar known, the normalised
 // weight of key p in cell (b, i, j) is exp(L[i][p] - mu-bar), so a row is one pass over the cell's keys.
+constexpr int kChainSplit = 8;
 template <typename T, int D>
 __global__ void __launch_bounds__(64) k_block_summaries(const T* __restrict__ Ks, const T* __restrict__ Vs,
                                                          const float* __restrict__ L, const int32_t* __restrict__ off_k,
@@ -395,10 +397,10 @@ __global__ void __launch_bounds__(64) k_block_summaries(const T* __restrict__ Ks
                                                          T* __restrict__ s_v, int h0, int N, int nb, int Cq, int Ck,
                                                          int Hq, int Hkv) {
   constexpr int DL = D / 8, NV = DL / 4, KB = 4;
-  const int jt = blockIdx.x, i = blockIdx.y, hl = blockIdx.z, hq = h0 + hl;
+  const int jt = blockIdx.x / kChainSplit, i = blockIdx.y, hl = blockIdx.z, hq = h0 + hl;
   const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);
   const int g = threadIdx.x >> 3, l8 = threadIdx.x & 7, NBm = nb - 1, W = (Ck + 31) / 32;
-  uint32_t word = chainmask[((size_t)hl * Cq + i) * W + jt];
+  uint32_t word = chainmask[((size_t)hl * Cq + i) * W + jt] & (0x01010101u << (blockIdx.x % kChainSplit));
   const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
   const float* Li = L + ((size_t)hl * Cq + i) * N;
   const T* Kh = Ks + (size_t)hk * N * D + DL * l8;
@@ -1289,19 +1291,32 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
       for (int bp = 0; bp < b; ++bp) {
         if (!((selbits >> bp) & 1u)) continue;
         const int klo = ok[bp * Ck + j], khi = ok[bp * Ck + j + 1];
-        for (int p_ = klo; p_ < khi; ++p_) {
-          const size_t krow = ((size_t)hk * N + p_) * D;
-          float pa = 0.f, v[NG][4];
+        for (int p0 = klo; p0 < khi; p0 += kKeys) {
+          float k4[kKeys][NG][4], v[kKeys][NG][4], lg[kKeys], pa[kKeys];
 #pragma unroll
-          for (int x = 0; x < NG; ++x) {
-            float k4[4];
-            ld4(Ks, krow + 64 * x + 4 * l16, k4);
-            ld4(Vs, krow + 64 * x + 4 * l16, v[x]);
-            pa = fmaf(qt[x][0], k4[0], pa); pa = fmaf(qt[x][1], k4[1], pa);
-            pa = fmaf(qt[x][2], k4[2], pa); pa = fmaf(qt[x][3], k4[3], pa);
+          for (int u = 0; u < kKeys; ++u) {
+            const int p = min(p0 + u, khi - 1);
+            const size_t krow = ((size_t)hk * N + p) * D;
+            lg[u] = L[((size_t)hl * Cq + i) * N + p];
+#pragma unroll
+            for (int x = 0; x < NG; ++x) {
+              ld4(Ks, krow + 64 * x + 4 * l16, k4[u][x]);
+              ld4(Vs, krow + 64 * x + 4 * l16, v[u][x]);
+            }
           }
-          pa = group_sum<16>(pa);
-          add(pa + L[((size_t)hl * Cq + i) * N + p_], v);  // q.k = q~.k + q-bar.k
+#pragma unroll
+          for (int u = 0; u < kKeys; ++u) {
+            pa[u] = 0.f;
+#pragma unroll
+            for (int x = 0; x < NG; ++x) {
+              pa[u] = fmaf(qt[x][0], k4[u][x][0], pa[u]); pa[u] = fmaf(qt[x][1], k4[u][x][1], pa[u]);
+              pa[u] = fmaf(qt[x][2], k4[u][x][2], pa[u]); pa[u] = fmaf(qt[x][3], k4[u][x][3], pa[u]);
+            }
+            pa[u] = group_sum<16>(pa[u]);
+          }
+#pragma unroll
+          for (int u = 0; u < kKeys; ++u)
+            if (p0 + u < khi) add(pa[u] + lg[u], v[u]);  // q.k = q~.k + q-bar.k
         }
       }
     }
@@ -1513,7 +1528,7 @@ int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace&
   if ((rc = muse_launch_fill_i32((int32_t*)w.chainmask, (size_t)hn * d.Cq * W, 0, st))) return rc;
   dim3 gm((unsigned)((d.nb - 1) * d.Cq), hn);
   { MuseProf prof_("k_chainmask", st); hipLaunchKernelGGL(k_chainmask, gm, dim3(256), 0, st, selc, w.perm_q, w.off_q, w.chainmask, h0, d.N, d.nb, d.r, d.Cq, W); }
-  dim3 gs(W, d.Cq, hn);
+  dim3 gs(kChainSplit * W, d.Cq, hn);
   if (sizeof(T) == 2) {  // bf16 inputs: key-cluster-major on fp32 MFMA
     const int WT = (d.Cq + 31) / 32;
     { MuseProf prof_("k_chainmask_t", st); hipLaunchKernelGGL(k_chainmask_t, dim3(W, WT, hn), dim3(64), 0, st, w.chainmask, w.chainmaskT, d.Cq, d.Ck, W, WT); }

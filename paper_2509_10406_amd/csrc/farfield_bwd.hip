@@ -23,7 +23,7 @@ namespace {
 //   slotinfo[hq][p][t] = j | (bitmask of the retrieved key blocks) << 16 for slot t, -1 when the slot is empty
 //   selmask[hq][j/32][p]: bit j%32 set when query p retrieved key cluster j
 // R >= r: a query's slots are held in registers, so that all its loads are requested together (a loop over the slots beyond
-// eight took 1.02 ms at 32 heads of 32k with r = 16, this @T@).
+// eight took 1.02 ms at 32 heads of 32k with r = 16, this 0.21).
 template <int R>
 __global__ void __launch_bounds__(256) k_selinfo(const int32_t* __restrict__ selc, const int32_t* __restrict__ selb,
                                                   const int32_t* __restrict__ perm_q, uint32_t* __restrict__ mask,
@@ -59,22 +59,17 @@ __global__ void __launch_bounds__(256) k_selinfo(const int32_t* __restrict__ sel
 }
 
 // ------------------------------------------------------------------------------------------
-// dQ of the far field, one wave per query tile (same tiling as the forward kernel)
+// dQ of component 1, one wave per query tile (same tiling as the forward kernel)
 // ------------------------------------------------------------------------------------------
 template <typename T, int D>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, 2))) k_ff_bwd_dq(
-    const T* __restrict__ Q, const T* __restrict__ dO, const float* __restrict__ qc, const T* __restrict__ Ks,
-    const T* __restrict__ Vs, const float* __restrict__ L, const float* __restrict__ s_mu,
-    const float* __restrict__ s_k, const T* __restrict__ s_v, const float* __restrict__ A_mu,
+    const T* __restrict__ Q, const T* __restrict__ dO, const float* __restrict__ qc, const float* __restrict__ A_mu,
     const float* __restrict__ A_k, const T* __restrict__ A_v, const bf16_t* __restrict__ A_kb,
-    const int32_t* __restrict__ perm_q,
-    const int32_t* __restrict__ off_q, const int32_t* __restrict__ off_k, const int32_t* __restrict__ tile_off,
+    const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q, const int32_t* __restrict__ tile_off,
     const float* __restrict__ LSE, const float* __restrict__ delta, const uint32_t* __restrict__ selmask,
-    const int32_t* __restrict__ selc, const int32_t* __restrict__ selb, const float* __restrict__ dqpart,
-    float* __restrict__ dQ, int h0, int N, int nb, int Cq, int Ck, int r, int k2e, int Hq, int Hkv, float scale) {
+    float* __restrict__ dQ, int h0, int N, int nb, int Cq, int Ck, float scale) {
   constexpr int U = D / 8, DT = D / 32;
   const int hl = blockIdx.z, hq = h0 + hl;
-  const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);
   const int b = blockIdx.y + 1, NBm = nb - 1;
   const int lane = threadIdx.x, col = lane % 32, half = lane / 32;
   const int W = (Ck + 31) / 32;
@@ -92,7 +87,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
   }
   const int i = lo_, tt = tile - to[lo_];
   const int32_t* oq = off_q + (size_t)hq * ((size_t)nb * Cq + 1);
-  const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
   const int qlo = oq[b * Cq + i], qhi = oq[b * Cq + i + 1];
   int pos = qlo + 32 * tt + col;
   const bool valid = pos < qhi;
@@ -258,71 +252,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
         for (int x = 0; x < DT; ++x) dq[x] = mfma32(krow[32 * x], s[4 * g + t], dq[x]);
       }
   }
-  // components 2 and 3 (fp32 inputs; bf16 inputs take them in the per-query and per-pair kernels)
-  for (int t = 0; t < (sizeof(T) == 4 ? r : 0); ++t) {
-    const int j = selc[qn * r + t];
-    if (j < 0) continue;
-    unsigned selbits = 0;
-    for (int u = 0; u < k2e; ++u) {
-      int bb = selb[(qn * r + t) * k2e + u];
-      if (bb >= 0) selbits |= 1u << bb;
-    }
-    for (int bp = 0; bp < b; ++bp) {
-      const size_t cell = (((size_t)hl * NBm + bp) * Cq + i) * Ck + j;
-      const float mu = s_mu[cell];
-      if (!(mu > MUSE_NEG_INF)) continue;
-      if (!((selbits >> bp) & 1u)) {
-        const float* kr = s_k + cell * D + 4 * half;
-        float part = 0.f, dpp = 0.f;
-        float4 k4[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          k4[u] = *reinterpret_cast<const float4*>(kr + 8 * u);
-          float v4[4];
-          ld4(s_v, cell * D + 4 * half + 8 * u, v4);
-          part = fmaf(qt[u][0], k4[u].x, part); part = fmaf(qt[u][1], k4[u].y, part);
-          part = fmaf(qt[u][2], k4[u].z, part); part = fmaf(qt[u][3], k4[u].w, part);
-          dpp = fmaf(gt[u][0], v4[0], dpp); dpp = fmaf(gt[u][1], v4[1], dpp);
-          dpp = fmaf(gt[u][2], v4[2], dpp); dpp = fmaf(gt[u][3], v4[3], dpp);
-        }
-        part += __shfl_xor(part, 32, 64);
-        dpp += __shfl_xor(dpp, 32, 64);
-        float p = __expf(part + mu - lse);
-        float dlg = p * (dpp - dl);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          dq[u / 4][4 * (u % 4) + 0] += dlg * k4[u].x; dq[u / 4][4 * (u % 4) + 1] += dlg * k4[u].y;
-          dq[u / 4][4 * (u % 4) + 2] += dlg * k4[u].z; dq[u / 4][4 * (u % 4) + 3] += dlg * k4[u].w;
-        }
-      } else if (sizeof(T) == 4) {
-        const int klo = ok[bp * Ck + j], khi = ok[bp * Ck + j + 1];
-        for (int p_ = klo; p_ < khi; ++p_) {
-          const size_t krow = ((size_t)hk * N + p_) * D + 4 * half;
-          float part = 0.f, dpp = 0.f;
-          float k4[U][4];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            float v4[4];
-            ld4(Ks, krow + 8 * u, k4[u]);
-            ld4(Vs, krow + 8 * u, v4);
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-              part = fmaf(qt[u][x], k4[u][x], part);
-              dpp = fmaf(gt[u][x], v4[x], dpp);
-            }
-          }
-          part += __shfl_xor(part, 32, 64);
-          dpp += __shfl_xor(dpp, 32, 64);
-          float p = __expf(part + L[((size_t)hl * Cq + i) * N + p_] - lse);
-          float dlg = p * (dpp - dl);
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) dq[u / 4][4 * (u % 4) + x] += dlg * k4[u][x];
-        }
-      }
-    }
-  }
   if (!valid) return;
   float res[U][4];
 #pragma unroll
@@ -336,19 +265,23 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 }
 
 // ------------------------------------------------------------------------------------------
-// dQ of component 2 for bf16 inputs, per query (16 lanes, dims 64 x + 4 l16 + t, bucketed order, as in the
-// forward): for every retrieved cluster, the summaries of the preceding blocks that were NOT retrieved
-// contribute  dl k-bar  with  dl = p (dO.v-bar - delta),  p = exp(q~.k-bar + mu-bar - LSE).  The retrieval's
-// per-pair dq partials are added here too, and the sum is added to the row the tile kernel wrote.
+// dQ of component 2, per query (16 lanes, dims 64 x + 4 l16 + t, bucketed order, as in the forward): for every
+// retrieved cluster, the summaries of the preceding blocks that were NOT retrieved contribute  dl k-bar  with
+// dl = p (dO.v-bar - delta),  p = exp(q~.k-bar + mu-bar - LSE).  The retrieval's share is added here too: bf16 inputs
+// have per-pair dq partials, fp32 inputs walk the retrieved keys, kKeys of them requested together.  The sum is added to
+// the row the tile kernel wrote.  (fp32 inputs had both in the tile kernel, a lane pair per query and a key per round trip:
+// 384 us at 4 heads of 8k, r = 4, against 44 + 170 for the two kernels now.)
 // ------------------------------------------------------------------------------------------
-template <int D, int NBC>
+template <typename T, int D, int NBC>
 __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ dO, const float* __restrict__ qc,
-    const float* __restrict__ s_mu, const float* __restrict__ s_k, const bf16_t* __restrict__ s_v,
+    const T* __restrict__ Q, const T* __restrict__ dO, const float* __restrict__ qc, const T* __restrict__ Ks,
+    const T* __restrict__ Vs, const float* __restrict__ L, const int32_t* __restrict__ off_k,
+    const float* __restrict__ s_mu, const float* __restrict__ s_k, const T* __restrict__ s_v,
     const int32_t* __restrict__ perm_q, const int32_t* __restrict__ aq, const float* __restrict__ LSE,
     const float* __restrict__ delta, const int32_t* __restrict__ slotinfo, const float* __restrict__ dqpart,
-    float* __restrict__ dQ, int h0, int N, int nb, int Bs, int Cq, int Ck, int r, int k2e, float scale) {
+    float* __restrict__ dQ, int h0, int N, int nb, int Bs, int Cq, int Ck, int r, int k2e, int Hq, int Hkv, float scale) {
   constexpr int NG = D / 64;
+  constexpr bool kF32 = sizeof(T) == 4;
   const int hl = blockIdx.y, hq = h0 + hl;
   const int l16 = threadIdx.x % 16;
   // Workgroups go to the 8 XCDs round-robin by their linear id (the grid's x extent is a multiple of 256): an XCD
@@ -376,6 +309,10 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
     for (int t = 0; t < 4; ++t) dq[x][t] = 0.f;
   }
   const int32_t* si = slotinfo + ((size_t)hq * N + pos) * r;
+  const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);  // fp32 inputs: the retrieved keys
+  const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
+  const T *Kh = Ks + (size_t)hk * N * D + 4 * l16, *Vh = Vs + (size_t)hk * N * D + 4 * l16;
+  const float* Li = L + ((size_t)hl * Cq + i) * N;
   // the row this kernel adds to is requested now and used at the end
   float4 oldq[NG];
 #pragma unroll
@@ -396,6 +333,47 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
     if (info < 0) continue;
     const int j = info & 0xffff;
     const unsigned selbits = (unsigned)info >> 16;
+    if constexpr (kF32) {  // component 3: the keys of the retrieved (cluster, block) pairs, with the full query
+      for (int bp = 0; bp < b; ++bp) {
+        if (!((selbits >> bp) & 1u)) continue;
+        const int klo = ok[bp * Ck + j], khi = ok[bp * Ck + j + 1];
+        for (int p0 = klo; p0 < khi; p0 += kKeys) {
+          float k4[kKeys][NG][4], v4[kKeys][NG][4], lg[kKeys], part[kKeys], dpp[kKeys];
+#pragma unroll
+          for (int u = 0; u < kKeys; ++u) {
+            const int p = min(p0 + u, khi - 1);
+            lg[u] = Li[p];
+#pragma unroll
+            for (int x = 0; x < NG; ++x) {
+              ld4(Kh, (size_t)p * D + 64 * x, k4[u][x]);
+              ld4(Vh, (size_t)p * D + 64 * x, v4[u][x]);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < kKeys; ++u) {
+            part[u] = dpp[u] = 0.f;
+#pragma unroll
+            for (int x = 0; x < NG; ++x)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                part[u] = fmaf(qt[x][e], k4[u][x][e], part[u]);
+                dpp[u] = fmaf(gt[x][e], v4[u][x][e], dpp[u]);
+              }
+            part[u] = group_sum<16>(part[u]);
+            dpp[u] = group_sum<16>(dpp[u]);
+          }
+#pragma unroll
+          for (int u = 0; u < kKeys; ++u) {
+            if (p0 + u >= khi) continue;
+            const float dlg = __expf(part[u] + lg[u] - lse) * (dpp[u] - dl);  // q.k = q~.k + q-bar.k
+#pragma unroll
+            for (int x = 0; x < NG; ++x)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) dq[x][e] = fmaf(dlg, k4[u][x][e], dq[x][e]);
+          }
+        }
+      }
+    }
     if (NBC == 1 && ((selbits + 1u) & ((1u << b) - 1u)) == 0u) continue;  // every preceding block is retrieved
 #pragma unroll
     for (int c0 = 0; c0 < 8 * NBC; c0 += 8) {
@@ -441,6 +419,7 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
       for (int u = 0; u < 8; ++u) {
         if (c0 + u >= bw) break;
         const bool use = c0 + u < b && mu[u] > MUSE_NEG_INF && !((selbits >> (c0 + u)) & 1u);
+        if (kF32 && !use) continue;
         const float p = use ? __expf(part[u] + mu[u] - lse) : 0.f;
         const float dlg = p * (dpp[u] - dl);
 #pragma unroll
@@ -471,7 +450,8 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
 #pragma unroll
     for (int t = 0; t < 4; ++t) dq[x][t] *= scale;
   // retrieval part, computed per retrieved pair (already scaled); a slot's pair u exists iff its block bit is set
-  if (k2e == 1) {
+  if (kF32) {
+  } else if (k2e == 1) {
     // the usual shape: the partial rows of eight slots are requested together and added in slot order
     for (int t0 = 0; t0 < r; t0 += 8) {
       int inf[8];
@@ -834,17 +814,17 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
   const int W = (d.Ck + 31) / 32;
   dim3 gt((d.Bs / 32 + d.Cq + 1 + 7) / 8 * 8, NBm, hn);
   hipStream_t st = sq_;
-  { MuseProf prof_("k_ff_bwd_dq", st); hipLaunchKernelGGL((k_ff_bwd_dq<T, D>), gt, dim3(64), 0, st, Q, dO, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.s_mu,
-                     w.s_k, (const T*)w.s_v, w.A_mu, w.A_k, (const T*)w.A_v, (const bf16_t*)w.A_kb, w.perm_q, w.off_q, w.off_k, w.tile_off, LSE, w.delta,
-                     w.selmask, selc, selb, w.ret_part, w.dQff, h0, d.N, d.nb, d.Cq, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, d.scale); }
-  if (sizeof(T) == 2 && d.r > 0) {
+  { MuseProf prof_("k_ff_bwd_dq", st); hipLaunchKernelGGL((k_ff_bwd_dq<T, D>), gt, dim3(64), 0, st, Q, dO, qc, w.A_mu, w.A_k, (const T*)w.A_v, (const bf16_t*)w.A_kb,
+                     w.perm_q, w.off_q, w.tile_off, LSE, w.delta, w.selmask, w.dQff, h0, d.N, d.nb, d.Cq, d.Ck, d.scale); }
+  if (d.r > 0) {
     dim3 g2(((d.N - d.Bs + 15) / 16 + 255) / 256 * 256, hn);  // a multiple of 256 (see the kernel)
-    if (d.nb <= 9)
-      { MuseProf prof_("k_comp2_bwd_dq", st); hipLaunchKernelGGL((k_comp2_bwd_dq<D, 1>), g2, dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, qc, w.s_mu, w.s_k, (const bf16_t*)w.s_v,
-                         w.perm_q, aq, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.scale); }
-    else
-      { MuseProf prof_("k_comp2_bwd_dq", st); hipLaunchKernelGGL((k_comp2_bwd_dq<D, 2>), g2, dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)dO, qc, w.s_mu, w.s_k, (const bf16_t*)w.s_v,
-                         w.perm_q, aq, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.scale); }
+    auto go = [&](auto* kernel) {
+      MuseProf prof_("k_comp2_bwd_dq", st);
+      hipLaunchKernelGGL(kernel, g2, dim3(256), 0, st, Q, dO, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.s_mu, w.s_k, (const T*)w.s_v,
+                         w.perm_q, aq, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, d.scale);
+    };
+    if (d.nb <= 9) go(k_comp2_bwd_dq<T, D, 1>);
+    else go(k_comp2_bwd_dq<T, D, 2>);
   }
   st = sk_;
   if constexpr (sizeof(T) == 2) {

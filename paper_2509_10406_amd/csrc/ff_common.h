@@ -248,6 +248,7 @@ __device__ __forceinline__ bf16x8_t ld_tr8(const bf16_t* row, int r0, int half) 
 
 constexpr int kMaxCk = 2304;  // key clusters a kernel can index in LDS
 static_assert(kMaxCk >= MUSE_MAX_CLUSTERS, "the host accepts more clusters than the kernels index");
+constexpr int kKeys = 4;      // retrieved keys that the per-query kernels of fp32 inputs request together
 constexpr int kRunTiles = 4;  // hit tiles (of 32) per work item of the retrieval forward / dq pair kernels
 constexpr int kC3Slices = 8;  // most waves that share the hits of one retrieved pair in the key/value gradients
 // hit slices of a pair in the key/value gradient kernels of the retrieval: one per `tiles` tiles of 32 hits, `most` at most
