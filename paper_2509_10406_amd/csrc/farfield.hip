@@ -1424,7 +1424,7 @@ int muse_ff_carve(const MuseDims& d, bool bwd, void* ws, size_t ws_bytes, FFWork
     w->dKs = (float*)take(HK * N * D * 4);
     w->dVs = (float*)take(HK * N * D * 4);
     w->dQff = (float*)take(HQ * N * D * 4);
-    w->qcT = take(HQ * D * (size_t)((d.Cq + 31) / 32 * 32) * 2);
+    w->qcb = take(HQ * D * (size_t)((d.Cq + 31) / 32 * 32) * 2);
     w->c3_part = w->ff_acc;  // fp32 inputs
     if (es == 2 && d.r > 0 && d.nb > 1) w->c3_part = (float*)take((kC3Slices - 1) * ff_c3_slice_bytes(d));
     if (d.grad_dtype != MUSE_DTYPE_FP32) {

@@ -306,7 +306,7 @@ struct FFWorkspace {
   float* c3_part;              // r > 0: [slices - 1][HK][N][2][D] partial dK | dV rows of the later hit slices of a pair (fp32: over ff_acc)
   float *dQacc, *dKacc, *dVacc;  // fp32 gradients in sequence order (alias the outputs when they are fp32)
   float* dQff;                   // far-field part of dQ, added to dQacc once the block-diagonal backward has finished
-  void* qcT;                     // bf16 [hc][D][Cq padded to 32]: scaled query centroids of a head chunk, transposed
+  void* qcb;                     // bf16 [hc][Cq padded to 32][D]: scaled query centroids of a head chunk
   // per chunk of `hc` query heads
   float* L;
   uint32_t* chainmask;  // [hc][Cq][ceil(Ck/32)]: key clusters retrieved by some query of the query cluster
@@ -427,7 +427,7 @@ int muse_launch_ret_bwd_dq_pairs(const MuseDims& d, const void* Q, const void* d
                                  const int4* run_map, size_t run_cap, const uint2* hits, size_t hit_cap, float* dqpart,
                                  hipStream_t st);
 // attn_mfma.hip
-int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* Vs, const float* qc, void* qcT,
+int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* Vs, const float* qc, void* qcb,
                                  const float* L, const float* s_mu, const float* G_c, const void* G_k, const void* G_v,
                                  const int32_t* off_k, float* dKs, float* dVs, int h0, int hn, hipStream_t st);
 // dipole.hip: dipole correction of the monopole-only mode (App. B), forward
