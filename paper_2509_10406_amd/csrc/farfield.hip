@@ -451,7 +451,12 @@ __global__ void __launch_bounds__(64) k_block_summaries(const T* __restrict__ Ks
 //   E^T[key, i] = exp(L[i, key] - mu-bar[b, i, j]),   s_k^T[d, i] = sum_key K^T[d, key] E^T[key, i]
 // A cell's keys are read once for all its chains instead of once per chain, and the sums leave through an LDS
 // transpose as whole rows.
-template <typename T, int D>
+// Bound by round trips: a chunk of 8 keys, then the rows out.  A cell of one chunk keeps its rows in registers over the passes and
+// has the next pass's logits requested before its rows go out; PIPE: longer cells have their chunks in two buffers, at D =
+// 64 for sixteen keys and more on average.  us before / now: 873 / 795 at 16 heads of 64k with 256 x 1024 clusters (8 keys; with PIPE 831),
+// 4561 / 4305 at 32 heads (4778), 786 / 666 with 128 x 128 (64 keys; without 737), 2762 / 2514 at 32 heads of 32k, D = 128, 8 keys
+// (without 2767), 794 / 697 with 64.
+template <typename T, int D, bool PIPE>
 __global__ void __launch_bounds__(256) k_block_summaries_mx(const T* __restrict__ Ks, const T* __restrict__ Vs,
                                                             const float* __restrict__ L, const int32_t* __restrict__ off_k,
                                                             const uint32_t* __restrict__ maskT,
@@ -486,63 +491,119 @@ __global__ void __launch_bounds__(256) k_block_summaries_mx(const T* __restrict_
   const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
   const int lo = ok[b * Ck + j], hi = ok[b * Ck + j + 1];
   const int lrow = lane / 16;
-  for (int it = 0; it * 32 < nflag; ++it) {
-    const int nrow = nflag - 32 * it < 32 ? nflag - 32 * it : 32;
-    const int il = list[32 * it + (col < nrow ? col : nrow - 1)];
-    const size_t cell = (((size_t)hl * NBm + b) * Cq + il) * Ck + j;
-    const float mu = s_mu[cell];
+  // the chains of pass `it`: this lane's query cluster, its mu-bar and its logits of keys c0 + 4 half + t
+  auto chain_of = [&](int it) { return (int)list[min(32 * it + col, nflag - 1)]; };
+  auto load_logits = [&](int il, int c0, float (&lg)[4]) {
     const float* Li = L + ((size_t)hl * Cq + il) * N;
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) {
-      const int d0 = 64 * ds;
-      // accumulator tile x, row m holds head dim d0 + 2 m + x: one paired load feeds both tiles
-      const T* Kh = Ks + (size_t)hk * N * D + d0 + 2 * col;
-      const T* Vh = Vs + (size_t)hk * N * D + d0 + 2 * col;
-      f32x16_t ak[2], av[2];
-      ak[0] = zero16(); ak[1] = zero16(); av[0] = zero16(); av[1] = zero16();
-      for (int c0 = lo; c0 < hi; c0 += 8) {
-        float lg[4];
-        typename Pair<T>::raw kk[4], vv[4];
+    for (int t = 0; t < 4; ++t) lg[t] = Li[min(c0 + 4 * half + t, hi - 1)];
+  };
+  auto load_mu = [&](int il) { return s_mu[(((size_t)hl * NBm + b) * Cq + il) * Ck + j]; };
+  // accumulator tile x, row m holds head dim 64 ds + 2 m + x: one paired load feeds both tiles
+  const T* Kh = Ks + (size_t)hk * N * D + 2 * col;
+  const T* Vh = Vs + (size_t)hk * N * D + 2 * col;
+  using raw = typename Pair<T>::raw;
+  auto load_rows = [&](int c0, int ds, raw (&kk)[4], raw (&vv)[4]) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int p = c0 + 4 * half + t;
-          const int pc = p < hi ? p : hi - 1;
-          lg[t] = Li[pc];
-          kk[t] = Pair<T>::ld(Kh, (size_t)pc * D);
-          vv[t] = Pair<T>::ld(Vh, (size_t)pc * D);
-        }
+    for (int t = 0; t < 4; ++t) {
+      const int pc = min(c0 + 4 * half + t, hi - 1);
+      kk[t] = Pair<T>::ld(Kh, (size_t)pc * D + 64 * ds);
+      vv[t] = Pair<T>::ld(Vh, (size_t)pc * D + 64 * ds);
+    }
+  };
+  f32x16_t ak[2], av[2];
+  auto clear = [&]() { ak[0] = zero16(); ak[1] = zero16(); av[0] = zero16(); av[1] = zero16(); };
+  auto add = [&](int c0, float mu, const float (&lg)[4], const raw (&kk)[4], const raw (&vv)[4]) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const float e = c0 + 4 * half + t < hi ? __expf(lg[t] - mu) : 0.f;
-          ak[0] = mfma32(Pair<T>::lo(kk[t]), e, ak[0]);
-          ak[1] = mfma32(Pair<T>::hi(kk[t]), e, ak[1]);
-          av[0] = mfma32(Pair<T>::lo(vv[t]), e, av[0]);
-          av[1] = mfma32(Pair<T>::hi(vv[t]), e, av[1]);
-        }
+    for (int t = 0; t < 4; ++t) {
+      const float e = c0 + 4 * half + t < hi ? __expf(lg[t] - mu) : 0.f;
+      ak[0] = mfma32(Pair<T>::lo(kk[t]), e, ak[0]);
+      ak[1] = mfma32(Pair<T>::hi(kk[t]), e, ak[1]);
+      av[0] = mfma32(Pair<T>::lo(vv[t]), e, av[0]);
+      av[1] = mfma32(Pair<T>::hi(vv[t]), e, av[1]);
+    }
+  };
+  // rows out through the LDS transpose: 16 lanes write one row's 64 dims (an empty cell gives zero rows)
+  auto emit = [&](const f32x16_t(&a)[2], bool values, int it, int ds) {
+    const int nrow = min(nflag - 32 * it, 32);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        *reinterpret_cast<float2*>(&tr[col][2 * (8 * g + 4 * half + t)]) = make_float2(a[0][4 * g + t], a[1][4 * g + t]);
+    wave_lds_fence();
+#pragma unroll
+    for (int ps = 0; ps < 8; ++ps) {
+      const int row = 4 * ps + lrow;
+      if (row < nrow) {
+        const float4 v = *reinterpret_cast<const float4*>(&tr[row][4 * (lane % 16)]);
+        const size_t o = ((((size_t)hl * NBm + b) * Cq + list[32 * it + row]) * Ck + j) * D + 64 * ds + 4 * (lane % 16);
+        const float v4[4] = {v.x, v.y, v.z, v.w};
+        if (values) st4_stream(s_v, o, v4);
+        else st4_stream(s_k, o, v4);
       }
-      // rows out through the LDS transpose: 16 lanes write one row's 64 dims (an empty cell gives zero rows)
-      auto emit = [&](const f32x16_t(&a)[2], bool values) {
+    }
+    wave_lds_fence();
+  };
+  const int npass = (nflag + 31) / 32;
+  if (lo < hi && hi - lo <= 8) {
+    // one chunk: its rows stay in registers over the passes, the next pass's logits are requested before this one's rows go
+    // out
+    raw kk[DS][4], vv[DS][4];
+    float lg[4], lgn[4], mu, mun;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+    for (int ds = 0; ds < DS; ++ds) load_rows(lo, ds, kk[ds], vv[ds]);
+    const int i0 = chain_of(0);
+    mun = load_mu(i0);
+    load_logits(i0, lo, lgn);
+    for (int it = 0; it < npass; ++it) {
+      mu = mun;
 #pragma unroll
-          for (int t = 0; t < 4; ++t)
-            *reinterpret_cast<float2*>(&tr[col][2 * (8 * g + 4 * half + t)]) = make_float2(a[0][4 * g + t], a[1][4 * g + t]);
-        wave_lds_fence();
+      for (int t = 0; t < 4; ++t) lg[t] = lgn[t];
+      const int in = chain_of(it + 1 < npass ? it + 1 : it);
+      mun = load_mu(in);
+      load_logits(in, lo, lgn);
 #pragma unroll
-        for (int ps = 0; ps < 8; ++ps) {
-          const int row = 4 * ps + lrow;
-          if (row < nrow) {
-            const float4 v = *reinterpret_cast<const float4*>(&tr[row][4 * (lane % 16)]);
-            const size_t o = ((((size_t)hl * NBm + b) * Cq + list[32 * it + row]) * Ck + j) * D + d0 + 4 * (lane % 16);
-            const float v4[4] = {v.x, v.y, v.z, v.w};
-            if (values) st4_stream(s_v, o, v4);
-            else st4_stream(s_k, o, v4);
+      for (int ds = 0; ds < DS; ++ds) {
+        clear();
+        add(lo, mu, lg, kk[ds], vv[ds]);
+        emit(ak, false, it, ds);
+        emit(av, true, it, ds);
+      }
+    }
+    return;
+  }
+  for (int it = 0; it < npass; ++it) {
+    const int il = chain_of(it);
+    const float mu = load_mu(il);
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) {
+      clear();
+      if (lo < hi) {
+        raw k0[4], v0[4], k1[4], v1[4];
+        float l0[4], l1[4];
+        if constexpr (PIPE) {
+          // the next 8 keys are requested before these are used (past the end: the last key again)
+          load_logits(il, lo, l0);
+          load_rows(lo, ds, k0, v0);
+          for (int c0 = lo; c0 < hi; c0 += 16) {
+            load_logits(il, c0 + 8, l1);
+            load_rows(c0 + 8, ds, k1, v1);
+            add(c0, mu, l0, k0, v0);
+            load_logits(il, c0 + 16, l0);
+            load_rows(c0 + 16, ds, k0, v0);
+            if (c0 + 8 < hi) add(c0 + 8, mu, l1, k1, v1);
+          }
+        } else {
+          for (int c0 = lo; c0 < hi; c0 += 8) {
+            load_logits(il, c0, l0);
+            load_rows(c0, ds, k0, v0);
+            add(c0, mu, l0, k0, v0);
           }
         }
-        wave_lds_fence();
-      };
-      emit(ak, false);
-      emit(av, true);
+      }
+      emit(ak, false, it, ds);
+      emit(av, true, it, ds);
     }
   }
 }
@@ -1533,12 +1594,14 @@ int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace&
     const int WT = (d.Cq + 31) / 32;
     { MuseProf prof_("k_chainmask_t", st); hipLaunchKernelGGL(k_chainmask_t, dim3(W, WT, hn), dim3(64), 0, st, w.chainmask, w.chainmaskT, d.Cq, d.Ck, W, WT); }
     dim3 gj((d.Ck + 7) / 8 * 8, (d.nb - 1 + 3) / 4, hn);
-    if (d.D == 64)
-      { MuseProf prof_("k_block_summaries", st); hipLaunchKernelGGL((k_block_summaries_mx<T, 64>), gj, dim3(256), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k,
-                         w.chainmaskT, w.s_mu, w.s_k, (T*)w.s_v, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv); }
-    else
-      { MuseProf prof_("k_block_summaries", st); hipLaunchKernelGGL((k_block_summaries_mx<T, 128>), gj, dim3(256), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k,
-                         w.chainmaskT, w.s_mu, w.s_k, (T*)w.s_v, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv); }
+    auto go = [&](auto* kernel) {
+      MuseProf prof_("k_block_summaries", st);
+      hipLaunchKernelGGL(kernel, gj, dim3(256), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.chainmaskT, w.s_mu, w.s_k, (T*)w.s_v, h0,
+                         d.N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv);
+    };
+    const bool pipe = d.D == 128 || d.Bs / d.Ck >= 16;
+    if (d.D == 64) pipe ? go(k_block_summaries_mx<T, 64, true>) : go(k_block_summaries_mx<T, 64, false>);
+    else pipe ? go(k_block_summaries_mx<T, 128, true>) : go(k_block_summaries_mx<T, 128, false>);
   } else if (d.D == 64)
     { MuseProf prof_("k_block_summaries", st); hipLaunchKernelGGL((k_block_summaries<T, 64>), gs, dim3(64), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k,
                        w.chainmask, w.s_mu, w.s_k, (T*)w.s_v, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv); }
