@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "ff_common.h"
+#include "lds_tile.h"
 
 namespace {
 
@@ -94,8 +95,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
   const int n = perm_q[(size_t)hq * N + pos];
   const size_t qn = (size_t)hq * N + n;
 
-  float qt[U][4], gt[U][4];
-  {
+  float qt[U][4], gt[U][4];  // fp32 inputs
+  if constexpr (sizeof(T) == 4) {
     const float* qci = qc + ((size_t)hq * Cq + i) * D;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -120,9 +121,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 #pragma unroll
   for (int t = 0; t < DT; ++t) dq[t] = zero16();
   // component 1
-  if (sizeof(T) == 2) {
+  if constexpr (sizeof(T) == 2) {
     // bf16 inputs: operands rounded to bf16 for the matrix cores (gradients only)
-    constexpr int KS = D / 16;
+    constexpr int KS = D / 16, CPR = D / 8, NIT = 32 * CPR / 64;
+    __shared__ __attribute__((aligned(16))) bf16_t kt[32 * D];
+    __shared__ __attribute__((aligned(16))) bf16_t vt[32 * D];
+    __shared__ __attribute__((aligned(16))) float mus[32];
     bf16x8_t qb[KS], gb[KS];
     // the bf16 operand order (8 consecutive dims per lane half) differs from the fp32 row pattern of qt/gt
     {
@@ -139,69 +143,50 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
         }
       }
     }
-    // a tile's operands: this lane's k-bar and v-bar rows (cluster j0 + col, its half of every 16 dims), the
-    // mu-bar of the 16 clusters whose scores land in this lane, and the retrieved-cluster mask of its query.
-    // Two buffers: the next tile's loads are in flight while this one is used; loads are unconditional (a tile
-    // index past the end repeats the last tile) and the values stay raw until they are used.
+    // A tile: the k-bar and v-bar rows of 32 clusters, whole rows per load instruction (a lane that reads its own operand
+    // touches 32 rows with every instruction), their mu-bar (lane col) and the retrieved-cluster mask of the lane's query.
+    // Two buffers in registers: the next tile's loads are in flight while this one is used; loads are unconditional (a
+    // tile index past the end repeats the last tile) and the values stay raw until they are used.  Through LDS, row-major,
+    // the rows serve S and dP as they lie and the dq contraction through transposed reads.
     struct BT {
-      uint4 k[KS], v[KS];
-      float mu[16];
+      bf16x8_t k[NIT], v[NIT];
+      float mu;
       uint32_t mw;
     };
     auto load_bt = [&](BT& t, int jt) {
       jt = jt < ntile ? jt : ntile - 1;
       const int j0 = jt * 32;
-      int c = j0 + col;
-      c = c < Ck ? c : Ck - 1;
 #pragma unroll
-      for (int x = 0; x < KS; ++x) {
-        t.k[x] = *reinterpret_cast<const uint4*>(Akh + (size_t)c * D + 16 * x + 8 * half);
-        t.v[x] = *reinterpret_cast<const uint4*>(Avh + (size_t)c * D + 16 * x + 8 * half);
+      for (int it = 0; it < NIT; ++it) {
+        const uint32_t o = (uint32_t)(min(j0 + it * (64 / CPR) + lane / CPR, Ck - 1) * D + lane % CPR * 8);
+        t.k[it] = *reinterpret_cast<const bf16x8_t*>(Akh + o);
+        t.v[it] = *reinterpret_cast<const bf16x8_t*>(Avh + o);
       }
-      if ((Ck & 3) == 0) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          int base = j0 + 8 * g + 4 * half;
-          base = base < Ck ? base : Ck - 4;
-          const float4 m4 = *reinterpret_cast<const float4*>(Amu + base);
-          t.mu[4 * g] = m4.x; t.mu[4 * g + 1] = m4.y; t.mu[4 * g + 2] = m4.z; t.mu[4 * g + 3] = m4.w;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int jr = j0 + 8 * (e / 4) + 4 * half + (e % 4);
-          t.mu[e] = Amu[jr < Ck ? jr : Ck - 1];
-        }
-      }
+      t.mu = Amu[min(j0 + col, Ck - 1)];
       t.mw = selmask[((size_t)hq * W + jt) * N + pos];
     };
-    // k-bar tile transposed ([dim][cluster]) for the dq contraction; lanes run along the clusters: 2-byte stores
-    // into consecutive banks
-    __shared__ __attribute__((aligned(16))) bf16_t kt[D][32 + 4];
     auto process = [&](const BT& t, int jt) {
       const int j0 = jt * 32;
-      f32x16_t s, dp;
+      wave_lds_fence();
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        s[e] = t.mu[e];
-        dp[e] = 0.f;
+      for (int it = 0; it < NIT; ++it) {
+        const int at = tile_at<D>(it * (64 / CPR) + lane / CPR, lane % CPR);
+        *reinterpret_cast<bf16x8_t*>(kt + at) = t.k[it];
+        *reinterpret_cast<bf16x8_t*>(vt + at) = t.v[it];
+      }
+      if (half == 0) mus[col] = t.mu;
+      wave_lds_fence();
+      f32x16_t s, dp = zero16();
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 m4 = *reinterpret_cast<const float4*>(&mus[8 * g + 4 * half]);
+        s[4 * g] = m4.x; s[4 * g + 1] = m4.y; s[4 * g + 2] = m4.z; s[4 * g + 3] = m4.w;
       }
 #pragma unroll
       for (int x = 0; x < KS; ++x) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, t.k[x]), qb[x], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, t.v[x]), gb[x], dp, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_row<D>(kt, col, 2 * x + half), qb[x], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_row<D>(vt, col, 2 * x + half), gb[x], dp, 0, 0, 0);
       }
-      wave_lds_fence();
-#pragma unroll
-      for (int x = 0; x < KS; ++x) {
-        const uint32_t w4[4] = {t.k[x].x, t.k[x].y, t.k[x].z, t.k[x].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          kt[16 * x + 8 * half + 2 * e][col] = (bf16_t)(w4[e] & 0xffffu);
-          kt[16 * x + 8 * half + 2 * e + 1][col] = (bf16_t)(w4[e] >> 16);
-        }
-      }
-      wave_lds_fence();
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int row = 8 * (e / 4) + 4 * half + (e % 4);
@@ -214,7 +199,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
         const bf16x8_t df = pack8(s, 2 * G, 2 * G + 1);
 #pragma unroll
         for (int x = 0; x < DT; ++x)
-          dq[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_tr8(&kt[32 * x + col][0], 16 * G, half), df, dq[x], 0, 0, 0);
+          dq[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_cols<D>(kt, 16 * G, x, lane), df, dq[x], 0, 0, 0);
       }
     };
     BT ta, tb;
