@@ -63,7 +63,8 @@ def kernel_models(w, p):
         cell_in = cells * (D * 2 + D * es + 4)
         rows_qg = 2 * Nff * D * es
         m["k_ff_bwd_dq"] = ("hbm", PEAK["hbm"], (cell_in + rows_qg + Nff * D * 4) * H, "byte")
-        m["k_ff_bwd_cells_mx"] = ("hbm", PEAK["hbm"], (cell_in + rows_qg + cell_g) * H, "byte")
+        # the gradients of the per-block cells leave it: mu-bar of both copies in
+        m["k_ff_bwd_cells_mx"] = ("hbm", PEAK["hbm"], (cell_in + cells * 4 + rows_qg + cell_g) * H, "byte")
         # per-block cell gradients and mu-bar in, tilt logits in, key/value rows in, fp32 gradient rows read-modify-write
         m["k_cells_to_keys_mx"] = ("hbm", PEAK["hbm"], (cell_g + cells * 4 + Cq * Nff * 4 + 2 * Nff * D * es) * H
                                    + 2 * 2 * Nff * D * 4 * Hk, "byte")
@@ -77,8 +78,10 @@ def kernel_models(w, p):
     # writes the accumulated summaries (the per-block ones follow, for retrieved chains only, in
     # k_block_summaries); reads the tilt logits and K, V once per tile of 32 query clusters
     m["k_summaries"] = ("hbm", PEAK["hbm"], (cell_kv + Cq * Nff * 4 + 2 * Nff * D * es) * H, "byte")
-    # reads the gradients of the accumulated cells and mu of both copies, writes the gradients of the per-block cells
-    m["k_cell_grads"] = ("hbm", PEAK["hbm"], (2 * cell_g + 2 * cells * 4) * H, "byte")
+    if es == 4:
+        # reads the gradients of the accumulated cells and mu of both copies, writes the gradients of the per-block cells
+        # (bf16 inputs: inside k_ff_bwd_cells_mx)
+        m["k_cell_grads"] = ("hbm", PEAK["hbm"], (2 * cell_g + 2 * cells * 4) * H, "byte")
     m["k_tilt_logits"] = ("hbm", PEAK["hbm"], (Cq * N * 4 + N * D * es) * H, "byte")
     return m
 

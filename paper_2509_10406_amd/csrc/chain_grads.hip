@@ -1,7 +1,7 @@
 // Component 2 of the per-block cell gradients (backward of the monopole attention over the non-retrieved blocks of the
 // retrieved clusters): every query of cluster i in a later block that retrieved cluster j but not block a adds
 //   g_k += dl q~,  g_v += p dO,  g_c += dl (1 - q~.kbar) - p dO.vbar
-// to the cell (a, i, j) that k_cell_grads wrote.
+// to the row of cell (a, i, j) that component 1 wrote (k_ff_bwd_cells_mx; fp32 inputs: k_cell_grads).
 //
 // For a chain (i, j) that is an attention-backward block of the chain's queries e against its key blocks a, and it
 // runs on the matrix cores: S[e, a] and dP[e, a] from the gathered rows as they are loaded, then
@@ -366,7 +366,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof
         if (part_w == 0)
           for (int o = 1; o < wpc; ++o) { gc += red[wave + o][0][lane]; dsum += red[wave + o][1][lane]; }
       }
-      // added to the rows of k_cell_grads; a chain's list ascends in the block, so its last query's block bounds the
+      // added to the rows of component 1; a chain's list ascends in the block, so its last query's block bounds the
       // key blocks that received anything
       const int clo = ch == 0 ? elo : emid, chi = ch == 0 ? emid : ehi;
       const int amax = chi > clo ? (int)(nS[list[chi - 1] >> 16] >> 22) : 0;

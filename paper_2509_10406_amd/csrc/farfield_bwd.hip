@@ -591,8 +591,8 @@ __global__ void __launch_bounds__(64) k_ff_bwd_cells(
 }
 
 // ------------------------------------------------------------------------------------------
-// Gradients of the per-block cells from those of the accumulated cells, fp32 inputs (bf16: cell_grads.hip): one block of 256 threads per (query
-// cluster i, tile of 32 key clusters); wave w owns the 8 chains (i, j, all blocks), j = 32 jt + 8 w + c.  A
+// Gradients of the per-block cells from those of the accumulated cells, fp32 inputs (bf16: cell_grads.hip): one block of
+// 256 threads per (query cluster i, tile of 32 key clusters); wave w owns the 8 chains (i, j, all blocks), j = 32 jt + 8 w + c.  A
 // wave is 8 groups of 8 lanes; a lane holds D/8 elements of a row (d = 32 x + 4 l8 + t); group c owns chain c.
 // Reverse accumulation over the key blocks a = nb-2 .. 0, in registers:
 //      R[a] = gA[a] + exp(Amu[a] - Amu[a+1]) R[a+1],   G[a] = exp(mu[a] - Amu[a]) R[a]   (written out)
