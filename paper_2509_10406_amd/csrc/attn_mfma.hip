@@ -1,11 +1,11 @@
 // bf16 causal attention on MFMA (Sec. 3, Eq. 1-2; Sec. 3.3 "Local attention"): keys restricted to
-// the query's own spatial block of size Bs (Bs = N gives exact attention).  Forward plus the two
-// backward kernels (dQ per query tile, dK/dV per key tile; no atomics).
+// the query's own spatial block of size Bs (Bs = N gives exact attention).  The two backward
+// kernels (dQ per query tile, dK/dV per key tile; no atomics); the forward is in attn_fwd.hip.
 //
 // Tiling for 64-wide waves and v_mfma_f32_32x32x16_bf16:
-//   - a wave owns 32 queries (fwd, dQ) or 32 keys (dK/dV) as the N-columns of the MFMA, so every
+//   - a wave owns 32 queries (dQ) or 32 keys (dK/dV) as the N-columns of the MFMA, so every
 //     per-row softmax quantity lives in one lane (two lanes: the two halves hold different K-rows);
-//   - scores are produced transposed (S^T = K Q^T in fwd/dQ, S = Q K^T in dK/dV) so that their
+//   - scores are produced transposed (S^T = K Q^T in dQ, S = Q K^T in dK/dV) so that their
 //     accumulator layout IS the B-operand layout of the following contraction: probabilities go
 //     from registers straight back into the matrix cores, never through LDS;
 //   - accumulator element e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32; an operand
@@ -21,41 +21,12 @@ namespace {
 constexpr int BN = 64;  // rows staged in LDS per step
 
 // Staging of a tile through registers, so that the global loads of the next tile are in flight while the current one is
-// consumed: fetch_tile into registers, commit_tile from registers into LDS.  The registers are named members,
+// consumed: fetch_rows into registers, commit_rows from registers into LDS.  The registers are named members,
 // not an array: an array that is passed around and read through pointer casts ends up in memory (the compiler
 // parks it in LDS), and the wait for its loads then comes right after they are issued.
 struct TileRegs {
   uint4 a, b, c, d;
 };
-template <int D, int ROWS>
-__device__ __forceinline__ uint4 fetch_chunk(const bf16_t* __restrict__ src, int r0, int N, int it) {
-  const int c = threadIdx.x + 256 * it;
-  int gr = r0 + c % ROWS;
-  gr = gr < N ? gr : N - 1;
-  return *reinterpret_cast<const uint4*>(src + (size_t)gr * D + (c / ROWS) * 8);
-}
-template <int D, int ROWS>
-__device__ __forceinline__ void fetch_tile(const bf16_t* __restrict__ src, int r0, int N, TileRegs& r) {
-  constexpr int NCH = ROWS * (D / 8) / 256;
-  static_assert(NCH >= 1 && NCH <= 4, "tile does not fit four chunks per thread");
-  r.a = fetch_chunk<D, ROWS>(src, r0, N, 0);
-  if constexpr (NCH > 1) r.b = fetch_chunk<D, ROWS>(src, r0, N, 1);
-  if constexpr (NCH > 2) r.c = fetch_chunk<D, ROWS>(src, r0, N, 2);
-  if constexpr (NCH > 3) r.d = fetch_chunk<D, ROWS>(src, r0, N, 3);
-}
-template <int D, int ROWS>
-__device__ __forceinline__ void commit_chunk(const uint4 v, int it, bf16_t (*rm)[D + 8]) {
-  const int c = threadIdx.x + 256 * it;
-  *reinterpret_cast<uint4*>(&rm[c % ROWS][c / ROWS * 8]) = v;
-}
-template <int D, int ROWS>
-__device__ __forceinline__ void commit_tile(const TileRegs& r, bf16_t (*rm)[D + 8]) {
-  constexpr int NCH = ROWS * (D / 8) / 256;
-  commit_chunk<D, ROWS>(r.a, 0, rm);
-  if constexpr (NCH > 1) commit_chunk<D, ROWS>(r.b, 1, rm);
-  if constexpr (NCH > 2) commit_chunk<D, ROWS>(r.c, 2, rm);
-  if constexpr (NCH > 3) commit_chunk<D, ROWS>(r.d, 3, rm);
-}
 
 // Transposed tile in operand order.  The second contraction of the backward kernels takes, for lane half h and the
 // 16 rows r0 .. r0+15 of the staged tile, the rows r0 + {4h .. 4h+3} and r0 + {8+4h .. 8+4h+3} as its 8 k-slots.
@@ -66,13 +37,11 @@ constexpr int TPAD16 = 8;
 __device__ __forceinline__ int tr_pos(int row) { return (row & ~12) | ((row & 4) << 1) | ((row & 8) >> 1); }
 // rows 2r and 2r+1 (chunk cc of each) into the row-major tile, and their 8 columns into the transposed tile as
 // 4-byte stores of two neighbouring rows (they stay neighbours in operand order)
-template <int D, int ROWS, bool ROWM = true>
+template <int D, int ROWS>
 __device__ __forceinline__ void commit_pair(const uint4 a, const uint4 b, int r, int cc, bf16_t (*rm)[D + 8],
                                             bf16_t (*tr)[ROWS + TPAD16]) {
-  if constexpr (ROWM) {
-    *reinterpret_cast<uint4*>(&rm[2 * r][cc * 8]) = a;
-    *reinterpret_cast<uint4*>(&rm[2 * r + 1][cc * 8]) = b;
-  }
+  *reinterpret_cast<uint4*>(&rm[2 * r][cc * 8]) = a;
+  *reinterpret_cast<uint4*>(&rm[2 * r + 1][cc * 8]) = b;
   const uint32_t wa[4] = {a.x, a.y, a.z, a.w}, wb[4] = {b.x, b.y, b.z, b.w};
   const int pos = tr_pos(2 * r);
 #pragma unroll
@@ -96,46 +65,44 @@ __device__ __forceinline__ void pair_unit(int c, int& pr, int& pc) {
   pr = c % (ROWS / 2);
   pc = c / (ROWS / 2);
 }
-// a whole tile in row pairs, unit c = thread + 256 i, chunk c / (ROWS / 2) for c = thread + 256 i.  Values, not
-// references into the register struct, go through the helpers (see TileRegs).
-template <int D, int ROWS>
-__device__ __forceinline__ uint4 fetch_pair_row(const bf16_t* __restrict__ src, int r0, int N, int i, int which) {
-  int pr, pc;
-  pair_unit<D, ROWS>(threadIdx.x + 256 * i, pr, pc);
-  int row = r0 + 2 * pr + which;
-  row = row < N ? row : N - 1;
-  return *reinterpret_cast<const uint4*>(src + (size_t)row * D + 8 * pc);
+
+// A tile as it lies: chunk c = thread + 256 i is chunk c % (D / 8) of row c / (D / 8), so a load instruction takes whole rows,
+// and the tile in LDS (lds_tile.h) serves rows and transposed operands alike.
+template <int D>
+__device__ __forceinline__ uint4 fetch_row_chunk(const bf16_t* __restrict__ src, int r0, int N, int i) {
+  const int c = threadIdx.x + 256 * i;
+  return *reinterpret_cast<const uint4*>(src + (size_t)min(r0 + c / (D / 8), N - 1) * D + c % (D / 8) * 8);
 }
-template <int D, int ROWS>
-__device__ __forceinline__ void fetch_pairs(const bf16_t* __restrict__ src, int r0, int N, TileRegs& r) {
-  constexpr int NP = ROWS / 2 * (D / 8) / 256;
-  static_assert(NP == 1 || NP == 2, "one or two row pairs per thread");
-  r.a = fetch_pair_row<D, ROWS>(src, r0, N, 0, 0);
-  r.b = fetch_pair_row<D, ROWS>(src, r0, N, 0, 1);
-  if constexpr (NP > 1) {
-    r.c = fetch_pair_row<D, ROWS>(src, r0, N, 1, 0);
-    r.d = fetch_pair_row<D, ROWS>(src, r0, N, 1, 1);
+template <int D>
+__device__ __forceinline__ void fetch_rows(const bf16_t* __restrict__ src, int r0, int N, TileRegs& r) {
+  static_assert(BN * (D / 8) / 256 == (D == 64 ? 2 : 4), "chunks per thread");
+  r.a = fetch_row_chunk<D>(src, r0, N, 0);
+  r.b = fetch_row_chunk<D>(src, r0, N, 1);
+  if constexpr (D == 128) {
+    r.c = fetch_row_chunk<D>(src, r0, N, 2);
+    r.d = fetch_row_chunk<D>(src, r0, N, 3);
   }
 }
-template <int D, int ROWS, bool TRANS, bool ROWM>
-__device__ __forceinline__ void commit_pair_i(const uint4 lo, const uint4 hi, int i, bf16_t (*rm)[D + 8],
-                                              bf16_t (*tr)[ROWS + TPAD16]) {
-  int pr, pc;
-  pair_unit<D, ROWS>(threadIdx.x + 256 * i, pr, pc);
-  if constexpr (TRANS) {
-    commit_pair<D, ROWS, ROWM>(lo, hi, pr, pc, rm, tr);
-  } else {
-    *reinterpret_cast<uint4*>(&rm[2 * pr][pc * 8]) = lo;
-    *reinterpret_cast<uint4*>(&rm[2 * pr + 1][pc * 8]) = hi;
-  }
+template <int D>
+__device__ __forceinline__ void commit_row_chunk(const uint4 v, int i, bf16_t* tile) {
+  const int c = threadIdx.x + 256 * i;
+  *reinterpret_cast<uint4*>(tile + tile_at<D>(c / (D / 8), c % (D / 8))) = v;
 }
-template <int D, int ROWS, bool TRANS, bool ROWM = true>
-__device__ __forceinline__ void commit_pairs(const TileRegs& r, bf16_t (*rm)[D + 8], bf16_t (*tr)[ROWS + TPAD16]) {
-  constexpr int NP = ROWS / 2 * (D / 8) / 256;
-  commit_pair_i<D, ROWS, TRANS, ROWM>(r.a, r.b, 0, rm, tr);
-  if constexpr (NP > 1) commit_pair_i<D, ROWS, TRANS, ROWM>(r.c, r.d, 1, rm, tr);
+template <int D>
+__device__ __forceinline__ void commit_rows(const TileRegs& r, bf16_t* tile) {
+  commit_row_chunk<D>(r.a, 0, tile);
+  commit_row_chunk<D>(r.b, 1, tile);
+  if constexpr (D == 128) {
+    commit_row_chunk<D>(r.c, 2, tile);
+    commit_row_chunk<D>(r.d, 3, tile);
+  }
 }
 
+// dQ.  The matrix pipe is half busy (0.49 to 0.53 at D = 64); what it waits for is the vector work between S and dQ and the
+// LDS reads in front of it, which three (D = 128: two) waves per SIMD cover in part.  Keys lie in LDS once, row-major, for
+// both contractions; with a transposed copy (4-byte stores in row pairs, half of the LDS-active cycles in bank conflicts) and
+// two barriers per step it took, us before -> after, 989 -> 927 for exact attention of 32 heads of 8k, D = 128, 482 -> 460 at
+// 8 heads of 16k, 1821 -> 1779 at 16 heads of 64k in blocks of 8192, 3560 -> 3376 at 32; same bits.
 template <int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, D == 64 ? 3 : 2))) k_flash_bwd_dq(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                        const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
@@ -143,9 +110,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
                                                        float* __restrict__ dQ, int N, int Bs, int Hq, int Hkv,
                                                        int nbatch, float scale, float scale_log2e) {
   constexpr int KS = D / 16, DT = D / 32;
-  __shared__ __attribute__((aligned(16))) bf16_t ks[BN][D + 8];
-  __shared__ __attribute__((aligned(16))) bf16_t vs[BN][D + 8];
-  __shared__ __attribute__((aligned(16))) bf16_t kt_[D][BN + TPAD16];
+  __shared__ __attribute__((aligned(256))) bf16_t ks[2][BN * D];
+  __shared__ __attribute__((aligned(256))) bf16_t vs[2][BN * D];
   const FlashTile ft = flash_tile(N, Bs, Hq, nbatch);
   if (!ft.ok) return;
   const int hq = ft.h, b = ft.b, hk = hq / (Hq / Hkv);
@@ -171,30 +137,37 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     for (int e = 0; e < 16; ++e) dq[t][e] = 0.f;
 
   const int kbeg = (q0 / Bs) * Bs, kend = min(q0 + 128, N);
+  const bf16_t *Kh = K + kh * D, *Vh = V + kh * D;
+  // two tiles in LDS, a third on its way in registers: a step has one barrier, the next tile is written in its middle
   TileRegs kreg, vreg;
-  fetch_pairs<D, BN>(K + kh * D, kbeg, N, kreg);
-  fetch_pairs<D, BN>(V + kh * D, kbeg, N, vreg);
-  for (int k0 = kbeg; k0 < kend; k0 += BN) {
+  fetch_rows<D>(Kh, kbeg, N, kreg);
+  fetch_rows<D>(Vh, kbeg, N, vreg);
+  commit_rows<D>(kreg, ks[0]);
+  commit_rows<D>(vreg, vs[0]);
+  fetch_rows<D>(Kh, kbeg + BN, N, kreg);
+  fetch_rows<D>(Vh, kbeg + BN, N, vreg);
+  int buf = 0;
+  for (int k0 = kbeg; k0 < kend; k0 += BN, buf ^= 1) {
     __syncthreads();
-    commit_pairs<D, BN, true>(kreg, ks, kt_);
-    commit_pairs<D, BN, false>(vreg, vs, nullptr);
-    __syncthreads();
-    if (k0 + BN < kend) {  // in flight while this tile is consumed
-      fetch_pairs<D, BN>(K + kh * D, k0 + BN, N, kreg);
-      fetch_pairs<D, BN>(V + kh * D, k0 + BN, N, vreg);
-    }
-    if (k0 > q0 + 32 * wave + 31) continue;
+    const bool live = k0 <= q0 + 32 * wave + 31;  // wave-uniform
     const bool edge = unaligned || k0 + BN - 1 > q0 + 32 * wave || k0 + BN > N;
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
+      if (kt == 1) {  // past the end: some row of the sequence that nobody reads
+        commit_rows<D>(kreg, ks[buf ^ 1]);
+        commit_rows<D>(vreg, vs[buf ^ 1]);
+        fetch_rows<D>(Kh, k0 + 2 * BN, N, kreg);
+        fetch_rows<D>(Vh, k0 + 2 * BN, N, vreg);
+      }
+      if (!live) continue;
       f32x16_t s, dp;
 #pragma unroll
       for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
 #pragma unroll
       for (int x = 0; x < KS; ++x) {
-        bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(&ks[32 * kt + col][16 * x + 8 * half]);
+        bf16x8_t a = tile_row<D>(ks[buf], 32 * kt + col, 2 * x + half);
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[x], s, 0, 0, 0);
-        bf16x8_t av = *reinterpret_cast<const bf16x8_t*>(&vs[32 * kt + col][16 * x + 8 * half]);
+        bf16x8_t av = tile_row<D>(vs[buf], 32 * kt + col, 2 * x + half);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, gf[x], dp, 0, 0, 0);
       }
       if (edge) {  // wave-uniform: only tiles on the diagonal or at the sequence end hold masked entries
@@ -214,7 +187,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
         bf16x8_t df = pack8(s, 2 * G, 2 * G + 1);
 #pragma unroll
         for (int t = 0; t < DT; ++t) {
-          bf16x8_t a = ld_tr16(kt_, 32 * t + col, 32 * kt + 16 * G, half);
+          bf16x8_t a = tile_cols<D>(ks[buf], 32 * kt + 16 * G, t, lane);
           dq[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, df, dq[t], 0, 0, 0);
         }
       }
