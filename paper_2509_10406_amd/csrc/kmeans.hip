@@ -350,7 +350,9 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
       const int oj = __shfl_xor(bj, 32, 64);
       if (ov > bv || (ov == bv && oj < bj)) { bv = ov; bj = oj; }
       const int n = batch * BP + (wave * PT + t) * 32 + col;
-      if (half == 0 && n < N) assign[(size_t)h * N + n] = bj;
+      // A row with a NaN or an infinity in it can score NaN everywhere, which fmaxf passes over: the tile number of its -inf
+      // is one past the centroids.  It goes to the last cluster, where the bucketing would put the number.
+      if (half == 0 && n < N) assign[(size_t)h * N + n] = min(bj, C - 1);
     }
   }
 }

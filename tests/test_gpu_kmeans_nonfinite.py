@@ -1,0 +1,36 @@
+"""Rows of Q or K with a NaN or an infinity in them (an overflow one wants to find): they get a cluster number that exists, and
+the same one whichever form of the centroid update runs."""
+import math
+
+import pytest
+import torch
+
+from paper_2509_10406_amd import binding as mb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bad", [math.nan, math.inf, -math.inf])
+@pytest.mark.parametrize("D,C", [(64, 70), (128, 70), (64, 520)])
+def test_lloyd(D, C, bad):
+    N = 1024
+    g = torch.Generator().manual_seed(D + C)
+    X = torch.randn(1, 1, N, D, generator=g)
+    X[0, 0, 5], X[0, 0, 700, 3] = bad, bad
+    at = torch.randperm(N - 6, generator=g)[:C] + 6
+    at[at == 700] = 6
+    got = []
+    # one head: the update that reads the assignments (4 Mi words of them at most); many: the one behind the bucketing
+    for H in (1, 96):
+        assert (H * N * C <= 4 << 20) == (H == 1)
+        p = mb.Params(B=1, Hq=H, Hkv=H, N=N, D=D, Cq=C, Ck=C, kmeans_iters=3)
+        x, init = X.expand(1, H, N, D).bfloat16().cuda().contiguous(), at.int().expand(1, H, C).cuda().contiguous()
+        cent, assign = mb.muse_cluster(p, x, None, init, None)[:2]
+        assert int(assign.min()) >= 0 and int(assign.max()) < C
+        a = assign.cpu()
+        if C < 480:  # no score at all (past 480 an infinite one can be kept): both rows are the last cluster's, nobody else's
+            assert (a[..., [5, 700]] == C - 1).all()
+            assert (cent.isfinite().all(-1).sum(-1) == C - 1).all() and cent[:, :, : C - 1].isfinite().all()
+        assert (a == a[:, :1]).all() and torch.equal(cent.nan_to_num(), cent[:, :1].nan_to_num().expand_as(cent))
+        got.append((cent[:, 0].cpu(), a[:, 0]))
+    assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][0].nan_to_num(), got[1][0].nan_to_num())
