@@ -879,6 +879,7 @@ k_stream_kmeans(const T* __restrict__ X, const int32_t* __restrict__ init_idx, f
           a = oj;
         }
       }
+      a = min(a, C - 1);  // a row that scores NaN everywhere (a NaN, or a value beyond binary16) has no number yet
     }
     const bool live = v0 + lane < N;
     if (wave == 0 && live && trace) trace[(size_t)h * N + v0 + lane] = a;

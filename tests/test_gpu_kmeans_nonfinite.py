@@ -1,5 +1,6 @@
 """Rows of Q or K with a NaN or an infinity in them (an overflow one wants to find): they get a cluster number that exists, and
 the same one whichever form of the centroid update runs."""
+import dataclasses
 import math
 
 import pytest
@@ -34,3 +35,23 @@ def test_lloyd(D, C, bad):
         assert (a == a[:, :1]).all() and torch.equal(cent.nan_to_num(), cent[:, :1].nan_to_num().expand_as(cent))
         got.append((cent[:, 0].cpu(), a[:, 0]))
     assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][0].nan_to_num(), got[1][0].nan_to_num())
+
+
+@pytest.mark.parametrize("dtype", [mb.FP32, mb.BF16])
+@pytest.mark.parametrize("bad", [math.nan, math.inf, 1e30])  # the pass runs in binary16
+@pytest.mark.parametrize("D,C", [(64, 3), (128, 70), (64, 1030)])  # few: the state in LDS
+def test_streaming(D, C, bad, dtype):
+    N = 2080
+    g = torch.Generator().manual_seed(D + C)
+    X = torch.randn(1, 2, N, D, generator=g)
+    X[0, 0, 1500], X[0, 0, 2000, 3] = bad, bad
+    at = torch.stack([torch.randperm(1400, generator=g)[:C] for _ in range(2)]).int()[None].cuda()
+    p = mb.Params(B=1, Hq=2, Hkv=2, N=N, D=D, Cq=C, Ck=C, dtype=dtype)
+    x = X.to(p.torch_dtype).cuda()
+    cent, assign, counts = mb.muse_kmeans_stream(p, 0, x, at)
+    assert int(assign.min()) >= 0 and int(assign.max()) < C and counts.isfinite().all()
+    assert cent[0, 1].isfinite().all()  # the other head
+    if C > 3:  # two rows spoil two centroids at most
+        assert int((~cent[0, 0].isfinite().all(-1)).sum()) in (1, 2)
+    final = mb.muse_cluster(dataclasses.replace(p, flags=mb.FLAG_STREAMING_KMEANS), x, None, at, None)[1]
+    assert int(final.min()) >= 0 and int(final.max()) < C
