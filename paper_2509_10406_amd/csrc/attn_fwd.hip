@@ -43,6 +43,11 @@ __device__ __forceinline__ float sum8(const bf16x8_t& v, float acc) {
   return acc;
 }
 
+// The tiles are those of one block: the last one has what is left of it, and a wave that is left without a query steps once and
+// brings rows.  With tiles of the whole sequence for blocks that are no multiple of 256, every step masked every score, and a
+// wave whose block starts behind its tile's looked for its maximum in steps without a key of its own (us, 8 blocks, whole
+// sequence / per block: 64 / 36 at 12 heads with blocks of 749, 184 / 83 with 1408, 531 / 303 at 32 heads with 2176; D = 128,
+// 12 heads: 210 / 129 with 1408, 66 / 49 with 640).
 // A workgroup takes a long tile of a group and the short one that mirrors it, so that all are equally long, where half as many
 // still fill the device (ms, folded / not: 1.58 / 1.69 at 16 heads of 64k in blocks of 8192, 0.46 / 0.55 at 32k in blocks of
 // 4096, 1.33 / 1.51 at 32 heads of 32k, D = 128; exact attention at 8 heads of 16k 0.42 / 0.53).
@@ -69,13 +74,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, NCH = BN * CPR / 512, kTile = BN * D, NG = KS / 2, NF = 3;
   __shared__ __attribute__((aligned(256))) bf16_t ks[3][kTile];
   __shared__ __attribute__((aligned(256))) bf16_t vs[3][kTile];
-  const FlashTile ft = flash_tile<TR>(N, Bs, Hq, nbatch);
+  const FlashTile ft = flash_tile_of((Bs + TR - 1) / TR, N / Bs, Hq, nbatch);
   if (!ft.ok) return;
   const int hq = ft.h, b = ft.b, hk = hq / (Hq / Hkv);
   const size_t qh = ((size_t)b * Hq + hq) * N, kh = ((size_t)b * Hkv + hk) * N;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, col = lane % 32, half = lane / 32;
   const bool late = wave >= 4;  // a phase behind
-  const bool unaligned = (Bs % TR) != 0;
+  const int kbeg = ft.blk * Bs, bend = kbeg + Bs;  // the block; its last tile may have fewer than TR rows
   const bf16_t *Kh = K + kh * D, *Vh = V + kh * D;
 
   // LDS addresses of this lane's operands (tile_row, tile_cols of lds_tile.h) in the first buffer: the other operands of a
@@ -89,26 +94,26 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   for (int part = 0; part <= fold; ++part) {
     const int t = part == 0 ? ft.tpg - 1 - ft.t : ft.t;  // long rows first
     if (part == 1 && t == ft.tpg - 1 - ft.t) break;      // the middle tile has no mirror
-    const int q0 = (ft.blk * ft.tpg + t) * TR;
-    const int w0 = q0 + 32 * wave, nq = w0 + col, nqc = min(nq, N - 1), myb = (nqc / Bs) * Bs;
-    const int kbeg = (q0 / Bs) * Bs, kend = min(q0 + TR, N), nt = (kend - kbeg + BN - 1) / BN;
+    const int q0 = kbeg + t * TR;
+    const int w0 = q0 + 32 * wave, nq = w0 + col, nqc = min(nq, bend - 1);
+    const int kend = min(q0 + TR, bend), nt = (kend - kbeg + BN - 1) / BN;
     bf16x8_t qf[KS];
 #pragma unroll
     for (int x = 0; x < KS; ++x) qf[x] = *reinterpret_cast<const bf16x8_t*>(Q + (qh + nqc) * D + 16 * x + 8 * half);
 
     // K(c) and V(c-1) into their buffers, straight from memory to LDS.  No branch: behind one, every LDS read in flight would
-    // be waited for.  Tiles past the end bring some row of the sequence that nobody reads.
+    // be waited for.  Rows past the block's end are its last row again, whose scores are masked or whose tile nobody reads.
     auto bring = [&](int c) {
       using gptr = const __attribute__((address_space(1))) void*;
       using lptr = __attribute__((address_space(3))) void*;
-      const int rk = min(kbeg + c * BN, N - 1), rv = max(min(kbeg + c * BN - BN, N - 1), 0);
+      const int rk = min(kbeg + c * BN, bend - 1), rv = max(min(kbeg + c * BN - BN, bend - 1), kbeg);
       const bf16_t *sk = Kh + (size_t)rk * D, *sv = Vh + (size_t)rv * D;
       bf16_t *dk = ks[c % 3] + wave * 512, *dv = vs[(c + 2) % 3] + wave * 512;
 #pragma unroll
       for (int u = 0; u < NCH; ++u) {
         const int row = srow + BN / NCH * u;
-        __builtin_amdgcn_global_load_lds((gptr)(sk + (uint32_t)(min(row, N - 1 - rk) * D + 8 * schunk)), (lptr)(dk + 4096 * u), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((gptr)(sv + (uint32_t)(min(row, N - 1 - rv) * D + 8 * schunk)), (lptr)(dv + 4096 * u), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gptr)(sk + (uint32_t)(min(row, bend - 1 - rk) * D + 8 * schunk)), (lptr)(dk + 4096 * u), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gptr)(sv + (uint32_t)(min(row, bend - 1 - rv) * D + 8 * schunk)), (lptr)(dv + 4096 * u), 16, 0, 0);
       }
     };
     auto arrived = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
@@ -193,13 +198,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     // the same one.  m = -inf (no key yet) makes every p an infinity or a NaN.
     auto softmax = [&](int i) {
       const int k0 = kbeg + i * BN;
-      if (unaligned || k0 + BN - 1 > w0 || k0 + BN > N) {  // wave-uniform
+      if (k0 + BN - 1 > w0) {  // wave-uniform
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
             const int kg = k0 + 32 * h + 8 * (e / 4) + 4 * half + (e % 4);
-            if (kg > nq || kg < myb) s[h][e] = MUSE_NEG_INF;
+            if (kg > nq) s[h][e] = MUSE_NEG_INF;
           }
       }
       float psum = 0.f;
@@ -234,8 +239,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int u = 0; u < 8; ++u) load(u / 4, u % 4, 0);
     if (late) phase_end();
-    // the wave's own steps end with the tile that its last query is in; after that it only brings rows
-    const int nw = (min(w0 + 31, kend - 1) - kbeg) / BN + 1;
+    // the wave's own steps end with the tile that its last query is in; after that it only brings rows.  A wave that the block
+    // leaves without a query has one step.
+    const int nw = w0 < kend ? (min(w0 + 31, kend - 1) - kbeg) / BN + 1 : 1;
     matrix_phase(std::true_type(), std::false_type(), 0);
     phase_end();
     softmax(0);
@@ -259,7 +265,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     phase_end();
 
     l += __shfl_xor(l, 32, 64);
-    if (nq >= N) continue;
+    if (nq >= bend) continue;
     float mnat = m * 0.6931471805599453f;  // natural-log units
     float cl = 1.f;                        // weight of the local part after the merge
     float cf = 0.f, lf = 0.f;
@@ -303,10 +309,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 int muse_launch_attn_fwd_mfma(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V,
                               const float* ff, void* O, float* LSE, hipStream_t st) {
   const float sl = d.scale * 1.4426950408889634f;
-  const bool al = (Bs % TR) == 0;
-  const int tpg = al ? Bs / TR : (d.N + TR - 1) / TR, groups = d.B * d.Hq * (al ? d.N / Bs : 1);
+  const int tpg = (Bs + TR - 1) / TR, groups = d.B * d.Hq * (d.N / Bs);
   const int fold = fold_tiles(tpg, groups);
-  const dim3 g(8 * (fold ? (tpg + 1) / 2 : tpg), (groups + 7) / 8);
+  const dim3 g = flash_grid_of(fold ? (tpg + 1) / 2 : tpg, groups);
   MuseProf prof_("k_flash_fwd", st);
   auto go = [&](auto* kernel) {
     hipLaunchKernelGGL(kernel, g, dim3(512), 0, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, ff, (bf16_t*)O, LSE, d.N,

@@ -1,12 +1,15 @@
-"""bf16 attention forward where its schedule changes: fewer rows than a tile, partial key steps, blocks that do not line up
-with tiles, workgroups that take a tile and its mirror (an odd number of tiles leaves one without), and scores that make the
-softmax reference move in every step, in none, or by more than fp32's range.  Against fp64 on the same bf16 rows: |O| is at
+"""bf16 attention forward where its schedule changes: fewer rows than a tile, partial key steps, blocks that are no multiple of
+the tile of 256 rows (waves without a query, partial last tiles, blocks smaller than a wave's 32 queries), workgroups that take
+a tile and its mirror (an odd number of tiles leaves one without), and scores that make the softmax reference move in every step,
+in none, or by more than fp32's range.  Against fp64 on the same bf16 rows: |O| is at
 most max |v|, its error at most the rounding of P and O to bf16 (2 x 2^-9 of the largest value of a row's keys) plus the fp32
 scores' share; 2e-2 as in the rest of the suite (values here stay below 4)."""
 import pytest
 import torch
 
+import tests.test_gpu_muse as base
 from paper_2509_10406_amd import binding as mb
+from paper_2509_10406_amd.inputs import generate, small
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +52,36 @@ def test_reference_moves(kind, D):
     else:  # all scores far below zero: p = exp(s) alone would vanish
         Q[..., 0], K[..., 0] = 100.0, -20.0
     check(Q.to(torch.bfloat16), K.to(torch.bfloat16), V.to(torch.bfloat16))
+
+
+BLOCKS = {
+    "fwd_block384_d128": ("cfg2", dict(D=128, N=1152, Hq=2, Hkv=1, Cq=6, Ck=20, r=3, block=384, kmeans_iters=1)),
+    "fwd_block128_d128": ("cfg2", dict(D=128, N=640, Hq=1, Hkv=1, Cq=4, Ck=12, r=2, block=128, kmeans_iters=1)),
+    "fwd_block300": ("cfg2", dict(N=900, Hq=2, Hkv=2, Cq=5, Ck=17, r=2, block=300, kmeans_iters=1)),
+    "fwd_block700": ("cfg2", dict(N=1400, Hq=2, Hkv=1, Cq=7, Ck=33, r=4, block=700, kmeans_iters=1)),
+    "fwd_block20": ("cfg2", dict(N=320, Hq=1, Hkv=1, Cq=2, Ck=6, r=1, block=20, kmeans_iters=1)),
+    "fwd_block1": ("cfg2", dict(D=128, N=16, Hq=1, Hkv=1, Cq=1, Ck=2, r=1, block=1, kmeans_iters=1)),
+}
+
+
+@pytest.mark.parametrize("name", list(BLOCKS))
+def test_blocks(name, monkeypatch):
+    monkeypatch.setitem(base.CASES, name, BLOCKS[name])
+    base.run_case(name, with_bwd=False)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H,N,block", [(64, 2048, 512), (32, 3072, 768), (32, 4400, 1100), (32, 4096, 1024)])
+def test_many_heads_match_each_alone(H, N, block, D):
+    """Few workgroups are dispatched one way, many another: the same bits, far field included."""
+    w = small("cfg2", D=D, N=N, Hq=H, Hkv=H, Cq=4, Ck=16, r=2, block=block, kmeans_iters=1)
+    d = generate(w, need_dO=False)
+    p = mb.params_for(w)
+    Q, K, V = (d[x].to(p.torch_dtype).cuda().contiguous() for x in ("Q", "K", "V"))
+    qc, qa, _, ka = mb.muse_cluster(p, Q, K, d["q_init_idx"].cuda(), d["k_init_idx"].cuda())
+    O, LSE = mb.muse_fwd(p, Q, K, V, qc, qa, ka)[:2]
+    one = mb.params_for(w, Hq=1, Hkv=1)
+    for h in range(0, H, 13):
+        part = [x[:, h:h + 1].contiguous() for x in (Q, K, V, qc, qa, ka)]
+        a, b = mb.muse_fwd(one, *part)[:2]
+        assert torch.equal(a, O[:, h:h + 1]) and torch.equal(b, LSE[:, h:h + 1])
