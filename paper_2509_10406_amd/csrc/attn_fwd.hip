@@ -48,10 +48,21 @@ __device__ __forceinline__ float sum8(const bf16x8_t& v, float acc) {
 // wave whose block starts behind its tile's looked for its maximum in steps without a key of its own (us, 8 blocks, whole
 // sequence / per block: 64 / 36 at 12 heads with blocks of 749, 184 / 83 with 1408, 531 / 303 at 32 heads with 2176; D = 128,
 // 12 heads: 210 / 129 with 1408, 66 / 49 with 640).
-// A workgroup takes a long tile of a group and the short one that mirrors it, so that all are equally long, where half as many
-// still fill the device (ms, folded / not: 1.58 / 1.69 at 16 heads of 64k in blocks of 8192, 0.46 / 0.55 at 32k in blocks of
-// 4096, 1.33 / 1.51 at 32 heads of 32k, D = 128; exact attention at 8 heads of 16k 0.42 / 0.53).
-static int fold_tiles(int tpg, int groups) { return tpg > 1 && (long long)((tpg + 1) / 2) * groups >= 256; }
+// The order of the tiles.  A CU holds one workgroup, a tile of a block is as long as its number, and workgroups are dispatched in
+// order, so a short tile handed out late and a long one handed out last both leave CUs idle.  Two ways to spread them:
+//   fold    a workgroup takes a long tile and the one that mirrors it; all are equally long.  For even numbers of tiles whose
+//           halves come out even on 256 CUs.
+//   chunk   else: long tiles first, over as many groups of an XCD as have 8 MB of keys and values (twice its L2; with 4 and
+//           16 MB or all groups the same at blocks up to 1k, at 32 heads of 32k with D = 128 1312, 1283 and 1407 against 1274).
+// us, group by group / folded / in chunks, groups being heads x blocks: 64 groups of 3 tiles 24 / 34 / 25, 160 of 3 45 / 66 / 40, 96 of
+// 4 52 / 41 / 39, 160 of 4 78 / 78 / 61, 96 of 5 57 / 65 / 47, 320 of 7 273 / 277 / 262, 160 of 8 196 / 178 / 165; where folding
+// comes out even: 128 of 4 54 / 44 / 46, 64 of 8 85 / 61 / 63, 8 of 64 (exact attention over 16k) 295 / 285 / 294, 128 of 32 1550 /
+// 1429 / 1436.
+static int fold_tiles(int tpg, int groups) { return tpg % 2 == 0 && (long long)(tpg / 2) * groups % 256 == 0; }
+static int chunk_groups(int Bs, int D, int groups) {
+  const int fit = (8 << 20) / (4 * D) / Bs, all = (groups + 7) / 8;
+  return fit < 1 ? 1 : fit < all ? fit : all;
+}
 
 // The end of a phase.  No release or acquire: what the waves exchange are rows that arrive in LDS by themselves and are
 // waited for by count, and every LDS read of a phase has fed a matrix instruction before the phase ends.
@@ -70,11 +81,11 @@ __device__ __forceinline__ uint32_t lds_addr(const bf16_t* p) { return (uint32_t
 template <int D>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) k_flash_fwd(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const float* __restrict__ ff,
-    bf16_t* __restrict__ O, float* __restrict__ LSE, int N, int Bs, int Hq, int Hkv, int nbatch, int fold, float scale_log2e) {
+    bf16_t* __restrict__ O, float* __restrict__ LSE, int N, int Bs, int Hq, int Hkv, int nbatch, int fold, int tiles, int chunk, float scale_log2e) {
   constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, NCH = BN * CPR / 512, kTile = BN * D, NG = KS / 2, NF = 3;
   __shared__ __attribute__((aligned(256))) bf16_t ks[3][kTile];
   __shared__ __attribute__((aligned(256))) bf16_t vs[3][kTile];
-  const FlashTile ft = flash_tile_of((Bs + TR - 1) / TR, N / Bs, Hq, nbatch);
+  const FlashTile ft = flash_tile_of((Bs + TR - 1) / TR, N / Bs, Hq, nbatch, tiles, chunk);
   if (!ft.ok) return;
   const int hq = ft.h, b = ft.b, hk = hq / (Hq / Hkv);
   const size_t qh = ((size_t)b * Hq + hq) * N, kh = ((size_t)b * Hkv + hk) * N;
@@ -90,10 +101,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // The chunk of a tile that this thread brings in: LDS takes them in order of the thread, so the swizzle is in the source.
   const int srow = tid / CPR, schunk = (tile_at<D>(srow, tid % CPR) - srow * D) / 8;  // the swizzle is its own inverse
 
-  // fold: the workgroup takes a long tile of the group and the short one that mirrors it
   for (int part = 0; part <= fold; ++part) {
     const int t = part == 0 ? ft.tpg - 1 - ft.t : ft.t;  // long rows first
-    if (part == 1 && t == ft.tpg - 1 - ft.t) break;      // the middle tile has no mirror
     const int q0 = kbeg + t * TR;
     const int w0 = q0 + 32 * wave, nq = w0 + col, nqc = min(nq, bend - 1);
     const int kend = min(q0 + TR, bend), nt = (kend - kbeg + BN - 1) / BN;
@@ -310,12 +319,12 @@ int muse_launch_attn_fwd_mfma(const MuseDims& d, int Bs, const void* Q, const vo
                               const float* ff, void* O, float* LSE, hipStream_t st) {
   const float sl = d.scale * 1.4426950408889634f;
   const int tpg = (Bs + TR - 1) / TR, groups = d.B * d.Hq * (d.N / Bs);
-  const int fold = fold_tiles(tpg, groups);
-  const dim3 g = flash_grid_of(fold ? (tpg + 1) / 2 : tpg, groups);
+  const int fold = fold_tiles(tpg, groups), tiles = fold ? tpg / 2 : tpg, chunk = fold ? 1 : chunk_groups(Bs, d.D, groups);
+  const dim3 g = flash_grid_of(tiles, groups);
   MuseProf prof_("k_flash_fwd", st);
   auto go = [&](auto* kernel) {
     hipLaunchKernelGGL(kernel, g, dim3(512), 0, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, ff, (bf16_t*)O, LSE, d.N,
-                       Bs, d.Hq, d.Hkv, d.B, fold, sl);
+                       Bs, d.Hq, d.Hkv, d.B, fold, tiles, chunk, sl);
   };
   if (d.D == 64) go(k_flash_fwd<64>);
   else go(k_flash_fwd<128>);

@@ -13,12 +13,21 @@ struct FlashTile {
   int t, blk, tpg, h, b;  // number inside the group, block of the group, tiles per group, head, batch
   bool ok;
 };
-__device__ __forceinline__ FlashTile flash_tile_of(int tpg, int nblk, int H, int nbatch) {
+// chunk > 1: the workgroups of an XCD do not take its groups one by one but `chunk` at a time, all first workgroups before all
+// second ones (`tiles` = workgroups per group).
+__device__ __forceinline__ FlashTile flash_tile_of(int tpg, int nblk, int H, int nbatch, int tiles = 1, int chunk = 1) {
   FlashTile r;
   r.tpg = tpg;
-  const int g = (blockIdx.z * gridDim.y + blockIdx.y) * 8 + blockIdx.x % 8;
+  const int groups = nbatch * H * nblk, y = blockIdx.z * gridDim.y + blockIdx.y, xcd = blockIdx.x % 8;
+  int g = 8 * y + xcd;
   r.t = blockIdx.x / 8;
-  r.ok = g < nbatch * H * nblk;
+  if (chunk > 1) {
+    const int seq = y * tiles + r.t, first = seq / (tiles * chunk) * chunk, rem = seq - first * tiles;
+    const int n = max(min(chunk, (groups + 7) / 8 - first), 1);  // the last chunk is narrower
+    r.t = rem / n;
+    g = 8 * (first + rem % n) + xcd;
+  }
+  r.ok = g < groups && r.t < tpg;
   r.blk = g % nblk;
   r.h = (g / nblk) % H;
   r.b = g / nblk / H;

@@ -1,6 +1,6 @@
 """bf16 attention forward where its schedule changes: fewer rows than a tile, partial key steps, blocks that are no multiple of
 the tile of 256 rows (waves without a query, partial last tiles, blocks smaller than a wave's 32 queries), workgroups that take
-a tile and its mirror (an odd number of tiles leaves one without), and scores that make the softmax reference move in every step,
+a tile and its mirror or are numbered across groups, and scores that make the softmax reference move in every step,
 in none, or by more than fp32's range.  Against fp64 on the same bf16 rows: |O| is at
 most max |v|, its error at most the rounding of P and O to bf16 (2 x 2^-9 of the largest value of a row's keys) plus the fp32
 scores' share; 2e-2 as in the rest of the suite (values here stay below 4)."""
@@ -71,9 +71,10 @@ def test_blocks(name, monkeypatch):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("H,N,block", [(64, 2048, 512), (32, 3072, 768), (32, 4400, 1100), (32, 4096, 1024)])
+@pytest.mark.parametrize("H,N,block", [(64, 2048, 512), (32, 3072, 768), (32, 4400, 1100), (32, 4096, 1024), (36, 4096, 2048)])
 def test_many_heads_match_each_alone(H, N, block, D):
-    """Few workgroups are dispatched one way, many another: the same bits, far field included."""
+    """Tiles folded (2 and 4 to a block), numbered across all groups of an XCD and (D = 128, blocks of 2048) across eight and
+    the one that is left: the same bits as head by head, far field included."""
     w = small("cfg2", D=D, N=N, Hq=H, Hkv=H, Cq=4, Ck=16, r=2, block=block, kmeans_iters=1)
     d = generate(w, need_dO=False)
     p = mb.params_for(w)
