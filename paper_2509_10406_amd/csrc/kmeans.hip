@@ -11,6 +11,8 @@
 //   update:        fixed-order sum over a cluster's segments, by one wave or by one per row slot (k_update).
 //   streaming pass (App. C "Centroid Computation") and balanced assignment (App. C "Balanced Assignment"):
 //                  the paper's own clustering, behind flags; see k_stream_kmeans and k_balance.
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
@@ -446,29 +448,36 @@ __global__ void __launch_bounds__(1024) k_bucket(const int32_t* __restrict__ ass
 //   WIDE = false  one wave per cluster, 16 bytes per lane, the slots side by side in the wave (clusters of few rows);
 //   WIDE = true   a wave per slot, a lane per D / 64 dims: twice as many rows in flight and S times as many waves, for
 //                 clusters whose slots walk long chains of rows.  64 positions come with one load and go to scalar
-//                 registers: with a broadcast load per position these were half of the kernel's loads (ten iterations
-//                 at 8 bf16 heads of 32k rows, D = 128, 64 clusters: 788 -> 528 us).  The line between them is in the launch.
+//                 registers: with a broadcast load per position these were half of the kernel's loads (ten iterations of
+//                 queries and keys at 8 bf16 heads of 32k rows, D = 128, 64 clusters: 1142 us, 1012 with scalar positions, 633
+//                 with scalar offsets).  The line between them is in the launch.
 // ------------------------------------------------------------------------------------------
 // acc += the rows at the n <= 64 positions that the lanes hold (lane u the u-th), in order, 32 rows in flight.  A position
-// goes to a scalar register, so that a row costs one load with a scalar base; Xl is the head's rows at this lane's dims.
+// goes to a scalar register, as an offset that is made for all 64 at once: a row is a v_readlane, an addition and a load (Xh is
+// the head's rows, uniform; at most 2^18 rows, so 32 bits hold the offset).  With a 64-bit address and a bound per row a wave
+// that walks long chains ran out of issue slots (fp32, D = 64, one cluster of 256k rows: 2.71 ms, 1.52 now).
 template <typename T, int D>
-__device__ __forceinline__ void add_rows_of(float (&acc)[D / 64], const T* __restrict__ Xl, int pos, int n) {
+__device__ __forceinline__ void add_rows_of(float (&acc)[D / 64], const T* __restrict__ Xh, int pos, int n) {
   constexpr int EPL = D / 64, MPI = 32;
+  struct __attribute__((aligned(EPL * sizeof(T)))) Row { T e[EPL]; };
+  const uint32_t off = (uint32_t)pos * (uint32_t)(D * sizeof(T)), mine = (threadIdx.x % 64) * (uint32_t)sizeof(Row);
   n = __builtin_amdgcn_readfirstlane(n);
-  for (int q = 0; q < n; q += MPI) {
-    struct __attribute__((aligned(EPL * sizeof(T)))) Row { T e[EPL]; } v[MPI];
+  auto batch = [&](auto whole, int q) {
+    Row v[MPI];
 #pragma unroll
-    for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const Row*>(Xl + (size_t)__builtin_amdgcn_readlane(pos, min(q + u, n - 1)) * D);
+    for (int u = 0; u < MPI; ++u)
+      v[u] = *reinterpret_cast<const Row*>(reinterpret_cast<const char*>(Xh) + (__builtin_amdgcn_readlane(off, whole ? q + u : min(q + u, n - 1)) + mine));
 #pragma unroll
     for (int u = 0; u < MPI; ++u) {
-      if (q + u >= n) continue;
+      if (!whole && q + u >= n) continue;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
         if constexpr (sizeof(T) == 2) acc[e] += bf16_bits_to_f32(v[u].e[e]);
         else acc[e] += v[u].e[e];
       }
     }
-  }
+  };
+  for (int q = 0; q < n; q += MPI) q + MPI <= n ? batch(std::true_type(), q) : batch(std::false_type(), q);
 }
 
 // the end of the forms with a wave per slot: the slots' sums (lane l has the dims D / 64 l ..) and counts meet in LDS in the
@@ -517,7 +526,7 @@ __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) :
   if (wid >= total) return;
   const int h = wid / C, j = wid % C;
   const int slot = WIDE ? wave : lane / RL, chunk = lane % RL;
-  const T* Xh = X + (size_t)h * N * D + chunk * EPL;
+  const T* Xh = X + (size_t)h * N * D;
   const int32_t* ph = perm + (size_t)h * N;
   const int32_t* oh = off + (size_t)h * ((size_t)nb * C + 1);
   float acc[EPL];
@@ -539,6 +548,7 @@ __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) :
     }
   } else {
     // MPI members per round trip; the positions of the next MPI are requested together with the rows of these
+    const T* Xl = Xh + chunk * EPL;
     for (int b = slot; b < nb; b += S) {
       const int lo = oh[b * C + j], hi = oh[b * C + j + 1];
       count += hi - lo;
@@ -555,7 +565,7 @@ __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) :
         }
         struct __attribute__((aligned(EPL * sizeof(T)))) Row { T e[EPL]; } v[MPI];
 #pragma unroll
-        for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const Row*>(Xh + (size_t)row[u] * D);
+        for (int u = 0; u < MPI; ++u) v[u] = *reinterpret_cast<const Row*>(Xl + (size_t)row[u] * D);
 #pragma unroll
         for (int u = 0; u < MPI; ++u) {
           if (p + u >= hi) continue;
@@ -610,7 +620,7 @@ __global__ void __launch_bounds__(64 * (64 / (D * (int)sizeof(T) / 16))) k_updat
   __shared__ uint16_t list[S][kScan];
   const int lane = threadIdx.x % 64, slot = threadIdx.x / 64, j = blockIdx.x, h = blockIdx.y;
   const int32_t* ah = assign + (size_t)h * N;
-  const T* Xh = X + (size_t)h * N * D + lane * EPL;
+  const T* Xh = X + (size_t)h * N * D;
   float acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
@@ -1101,18 +1111,27 @@ __global__ void __launch_bounds__(256) k_balance(const T* __restrict__ X, const 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Which form of k_update: the wide one while the device has room for its S times as many waves and a slot walks more
-// than a few rows, and always for long chains; many short chains fill the device by themselves.  us for ten iterations,
-// wide / narrow: 241 / 371 at 4 fp32 heads of 8k rows with 32 clusters (64 rows per slot), 946 / 1008 at 16 heads of 64k
-// with 128 (64 rows), 1202 / 1186 with 256 (32 rows), 2773 / 2178 with 1024 (8 rows), 280 / 215 at 16 heads of 4k with 128
-// (4 rows), 1289 / 1435 at 32 heads of 32k, D = 128, with 128 (64 rows).
+// than a few rows, and always for long chains; many short chains fill the device by themselves.  us of ten iterations of
+// queries and keys, bucketing included, wide / narrow: 1019 / 1530 at 16 heads of 64k rows with 128 clusters (64 rows per slot,
+// 16384 waves), 959 / 1024 with 256 (32 rows; the call 1788 / 1721), 1825 / 1015 with 1024 (8 rows), 532 / 898 at 8 of 32k with 64
+// (64 rows, 4096 waves), 399 / 326 at 16 of 4k with 128 (4 rows), 1266 / 1758 at 32 of 32k, D = 128, with 128 (64 rows).
 static bool wide_update(int rows_per_slot, long long waves) {
   return (rows_per_slot >= 12 && waves <= 8192) || rows_per_slot >= 64;
 }
 
-// The update without the bucketing launch (k_update_scan), while what its workgroups read of the assignments stays small.
-// us for ten iterations, with / without it: 135 / 173 at one fp32 head of 2k rows with 16 clusters, 154 / 202 at 6 bf16
-// heads of 6k with 23, 204 / 206 at 16 heads of 4k with 64 (4 M words read), 292 / 213 with 128 (8 M).
-static bool scan_update(int heads, int N, int C) { return (long long)heads * C * N <= kScanMost; }
+// The update without the bucketing launch (k_update_scan), while its workgroups read little of the assignments in all (4 M
+// words) and each (8192 positions per wave), and the device holds them at once: 8192 waves, 8 workgroups per CU.  us of ten
+// iterations of queries and keys, the whole call, scan / bucketing and update, bf16 at D = 64 unless said:
+//   words      212 / 258 at 8 heads of 8k rows with 64 clusters (4 M), 332 / 336 at 8 of 16k with 64 (8 M), 2434 / 1466 at 16 of
+//              64k with 128 (128 M)
+//   positions  fp32, D = 128 1126 / 1293 and 926 / 868 at 4 and 2 heads of 16k with 64 and 128 (8192), 1144 / 956 at one of 32k with
+//              128 (16384); 436 / 424 at one of 64k with 64 (8192), 2659 / 2388 at one of 256k with 16 (32768)
+//   waves      232 / 288 at 16 heads of 4k with 64 (8192), 302 / 254 at 16 of 2k with 128 (16384), 454 / 287 at 32 of 1k with 128
+//   workgroups fp32, D = 128 1300 / 1312 at 32 heads of 2k with 64 (2048), 1291 / 1062 at 32 of 1k with 128 (4096)
+static bool scan_update(int heads, int N, int C, int S) {
+  const long long groups = (long long)heads * C;
+  return groups * N <= kScanMost && N <= 8192 * S && groups <= 2048 && groups * S <= 8192;
+}
 
 // One of the two clustering problems of a call on its way: the launches of an iteration are issued by themselves, so that
 // two problems on two streams can take turns.
@@ -1237,7 +1256,7 @@ int ClusterRun<T>::iteration(int it) {
   }
   if (it == T_) return MUSE_OK;
   constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);  // row slots
-  if (scan_update(heads, N, C)) {
+  if (scan_update(heads, N, C, D == 64 ? S64 : S128)) {
     MuseProf prof_("k_update", st);
     auto go = [&](auto* kernel, int block) { hipLaunchKernelGGL(kernel, dim3(C, heads), dim3(block), 0, st, X, assign, cent, chat, nhc2, N, d.Bs, C); };
     if (D == 64) go(k_update_scan<T, 64>, 64 * S64);

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from paper_2509_10406_amd import binding as mb
+from tests.test_gpu_kmeans_update import form
 
 pytestmark = pytest.mark.gpu
 
@@ -21,9 +22,9 @@ def test_lloyd(D, C, bad):
     at = torch.randperm(N - 6, generator=g)[:C] + 6
     at[at == 700] = 6
     got = []
-    # one head: the update that reads the assignments (4 Mi words of them at most); many: the one behind the bucketing
+    # one head: the update that reads the assignments; many: the one behind the bucketing
     for H in (1, 96):
-        assert (H * N * C <= 4 << 20) == (H == 1)
+        assert (form(H, N, C, D, "bf16") == "scan") == (H == 1)
         p = mb.Params(B=1, Hq=H, Hkv=H, N=N, D=D, Cq=C, Ck=C, kmeans_iters=3)
         x, init = X.expand(1, H, N, D).bfloat16().cuda().contiguous(), at.int().expand(1, H, C).cuda().contiguous()
         cent, assign = mb.muse_cluster(p, x, None, init, None)[:2]

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from paper_2509_10406_amd import binding as mb
+from tests.test_gpu_kmeans_update import form
 
 pytestmark = pytest.mark.gpu
 
@@ -23,7 +24,7 @@ def test_update_from_assignments(N, nb, C, D, dtype):
         cent[:, :, 3] = 100.0  # nobody's nearest: keeps its centroid
     p = mb.Params(B=1, Hq=2, Hkv=2, N=N, D=D, Cq=C, Ck=C, block=N // nb, dtype=dtype, kmeans_iters=1)
     Xd = X.to(p.torch_dtype).cuda()
-    assert 2 * N * C <= 4 << 20  # stays below the line up to which this form runs
+    assert form(2, N, C, D, "fp32" if dtype == mb.FP32 else "bf16") == "scan"
     import dataclasses
     c0 = cent.cuda()
     a0 = mb.muse_cluster(dataclasses.replace(p, kmeans_iters=0), Xd, None, None, None, q_centroids=c0.clone())[1]
