@@ -24,39 +24,48 @@ namespace {
 // Three waves per SIMD at D = 64, two at D = 128 (registers).  Units per workgroup: ms at 16 heads of 64k tokens, D = 64,
 // 256 x 1024 clusters with 2 / 4 / 8 waves 3.87 / 3.13 / 4.48 (a third workgroup of 8 does not fit); at 32 heads of 32k, D = 128,
 // 128 x 512 clusters 5.46 / 3.46 / 2.89.  Stages of 64 queries in place of 32: 4.32 and 3.62.
-template <int D>
+//
+// APART: few units leave the chip to a chain of nb - 1 blocks, whose stages are round trips of 1 to 2 us.  The waves of a workgroup
+// then share one unit and take a key block each, with their own staged queries; what they have summed up goes from wave to wave
+// through LDS, later blocks first, R = own + f R as above.  The lines between the two are in cells_apart.
+template <int D, bool APART>
 struct CellCfg {
-  static constexpr int kWaves = D == 64 ? 4 : 8;  // units of a workgroup
-  static constexpr int kRows = 32;                // queries staged at a time
-  static constexpr int kOcc = D == 64 ? 3 : 2;    // waves per SIMD
+  static constexpr int kWaves = D == 64 && !APART ? 4 : 8;    // units of a workgroup; APART: key blocks at a time
+  static constexpr int kRows = 32;                            // queries staged at a time
+  static constexpr int kOcc = D == 64 && !APART ? 3 : 2;      // waves per SIMD
 };
 
-template <int D>
-__global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu_waves_per_eu(CellCfg<D>::kOcc, CellCfg<D>::kOcc))) k_ff_bwd_cells_mx(
+template <int D, bool APART>
+__global__ void __launch_bounds__((64 * CellCfg<D, APART>::kWaves)) __attribute__((amdgpu_waves_per_eu(CellCfg<D, APART>::kOcc, CellCfg<D, APART>::kOcc))) k_ff_bwd_cells_mx(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ dO, const float* __restrict__ qc,
     const float* __restrict__ s_mu, const float* __restrict__ A_mu, const bf16_t* __restrict__ A_kb,
     const bf16_t* __restrict__ A_v, const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q,
     const float* __restrict__ LSE, const float* __restrict__ delta, const uint32_t* __restrict__ selmask,
     float* __restrict__ G_c, bf16_t* __restrict__ G_k, bf16_t* __restrict__ G_v, int h0, int N, int nb, int Cq, int Ck,
     float scale) {
-  constexpr int KX = D / 32, MT = D / 16, CPR = D / 8, NW = CellCfg<D>::kWaves, RP = CellCfg<D>::kRows, NT = 64 * NW;
-  constexpr int NU = RP * CPR / NT;  // 16-byte chunks of a tensor per thread and stage
-  __shared__ __attribute__((aligned(16))) bf16_t qs[2][RP * D];
-  __shared__ __attribute__((aligned(16))) bf16_t gs[2][RP * D];
-  __shared__ __attribute__((aligned(16))) float ls[2][RP];
-  __shared__ __attribute__((aligned(16))) float ds[2][RP];
+  using Cfg = CellCfg<D, APART>;
+  constexpr int KX = D / 32, MT = D / 16, CPR = D / 8, NW = Cfg::kWaves, RP = Cfg::kRows, NT = APART ? 64 : 64 * NW;
+  constexpr int NU = RP * CPR / NT;   // 16-byte chunks of a tensor per thread and stage
+  constexpr int NBUF = APART ? NW : 2, STEP = APART ? NW : 1;
+  __shared__ __attribute__((aligned(16))) bf16_t qs[NBUF][RP * D];
+  __shared__ __attribute__((aligned(16))) bf16_t gs[NBUF][RP * D];
+  __shared__ __attribute__((aligned(16))) float ls[NBUF][RP];
+  __shared__ __attribute__((aligned(16))) float ds[NBUF][RP];
   __shared__ __attribute__((aligned(16))) uint32_t mws[NW][RP];
-  __shared__ __attribute__((aligned(16))) bf16_t tw[NW][16][D + 8];
+  __shared__ __attribute__((aligned(16))) bf16_t tws[APART ? 1 : NW][16][D + 8];
+  __shared__ __attribute__((aligned(16))) f32x4_t carry[APART ? 2 * MT : 1][64];  // APART: R of the block handed on, as the lanes hold it
+  __shared__ float2 carry_c[64];                                                 // and its scalar part with Amu
   __shared__ __attribute__((aligned(16))) float cs[D];
   __shared__ int2 grp[16];  // [a]: positions of the group that sees the accumulation up to key block a
   const int hl = blockIdx.z, hq = h0 + hl;
-  const int NBm = nb - 1, W = (Ck + 31) / 32, nunit = (Ck + 15) / 16, ng = (nunit + NW - 1) / NW;
-  // the workgroups of one query cluster run on one XCD (x % 8), one after the other: they stage the same queries
-  const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
-  const int i = idx / ng * 8 + xcd;
+  const int NBm = nb - 1, W = (Ck + 31) / 32, nunit = (Ck + 15) / 16, ng = APART ? nunit : (nunit + NW - 1) / NW;
+  // the workgroups of one query cluster run on one XCD (x % 8), one after the other: they stage the same queries (APART: on all,
+  // there are few)
+  const int xcd = blockIdx.x % 8, idx = APART ? blockIdx.x : blockIdx.x / 8;
+  const int i = APART ? idx / ng : idx / ng * 8 + xcd;
   if (i >= Cq) return;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, c16 = lane % 16, g = lane / 16;
-  const int unit = idx % ng * NW + wave;
+  const int wave = APART ? __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : threadIdx.x / 64, lane = threadIdx.x % 64, c16 = lane % 16, g = lane / 16;
+  const int unit = APART ? idx % ng : idx % ng * NW + wave;
   const bool live = unit < nunit;  // the last workgroup's waves may have nothing but the staging to do
   const int jc = unit * 16 + c16, jcl = min(jc, Ck - 1), bit = 16 * (unit & 1) + c16;
   const bool jvalid = jc < Ck;
@@ -64,6 +73,8 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
   const int32_t* pq = perm_q + (size_t)hq * N;
   const bf16_t *Qh = Q + (size_t)hq * N * D, *Gh = dO + (size_t)hq * N * D;
   const float *Lh = LSE + (size_t)hq * N, *Dh = delta + (size_t)hq * N;
+  const int stid = APART ? lane : (int)threadIdx.x;  // the thread's number among those that stage a group's queries
+  bf16_t(*tw)[D + 8] = APART ? reinterpret_cast<bf16_t(*)[D + 8]>(qs[wave]) : tws[wave];  // the rows on their way out
   const uint32_t* sm = selmask + ((size_t)hq * W + min(unit / 2, W - 1)) * N;
   if (threadIdx.x < NBm) grp[threadIdx.x] = make_int2(oq[(threadIdx.x + 1) * Cq + i], oq[(threadIdx.x + 1) * Cq + i + 1]);
   if (threadIdx.x < D) cs[threadIdx.x] = qc[((size_t)hq * Cq + i) * D + threadIdx.x];
@@ -90,8 +101,9 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
   struct Cur { int a, q0, hi; };
   auto advance = [&](Cur c) {  // past the end: the last stage again
     c.q0 += RP;
-    if (c.q0 >= c.hi && c.a > 0) {
-      const int2 gr = grp[--c.a];
+    if (c.q0 >= c.hi && c.a >= STEP) {
+      c.a -= STEP;
+      const int2 gr = grp[c.a];
       c.q0 = __builtin_amdgcn_readfirstlane(gr.x);
       c.hi = __builtin_amdgcn_readfirstlane(gr.y);
     }
@@ -99,27 +111,34 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
   };
   // a row past the group's end repeats its first one (weight 0); an empty group's are never used
   auto pos_of = [&](const Cur& c, int row) { return min(c.q0 + row < c.hi ? c.q0 + row : c.q0, N - 1); };
-  int pos[NU];               // sequence positions of this thread's rows, one stage ahead of the rows
-  uint4 rq[NU], rg[NU];      // its chunks of a stage on their way
-  float rl[NU], rd[NU];
+  // sequence positions of this thread's rows, one stage ahead of the rows (APART: of row lane, handed out by shuffles)
+  constexpr int NP = APART ? 1 : NU;
+  int pos[NP];
+  typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
+  u4_t rq[NU], rg[NU];  // its chunks of a stage on their way
+  float rl[NP], rd[NP];
   uint32_t rm;
   auto load_pos = [&](const Cur& c) {
 #pragma unroll
-    for (int u = 0; u < NU; ++u) pos[u] = pq[pos_of(c, ((int)threadIdx.x + NT * u) / CPR)];
+    for (int u = 0; u < NP; ++u) pos[u] = pq[pos_of(c, APART ? lane % RP : (stid + NT * u) / CPR)];
   };
   auto load_rows = [&](const Cur& c) {
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const uint32_t o = (uint32_t)(pos[u] * D + ((int)threadIdx.x + NT * u) % CPR * 8);
-      rq[u] = *reinterpret_cast<const uint4*>(Qh + o);
-      rg[u] = *reinterpret_cast<const uint4*>(Gh + o);
+      const int p = APART ? __shfl(pos[0], (stid + NT * u) / CPR, 64) : pos[APART ? 0 : u];
+      const uint32_t o = (uint32_t)(p * D + (stid + NT * u) % CPR * 8);
+      rq[u] = *reinterpret_cast<const u4_t*>(Qh + o);
+      rg[u] = *reinterpret_cast<const u4_t*>(Gh + o);
+    }
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
       rl[u] = Lh[(uint32_t)pos[u]];
       rd[u] = Dh[(uint32_t)pos[u]];
     }
     rm = sm[pos_of(c, lane % RP)];
   };
   auto commit = [&](const Cur& c, int buf) {
-    int tid = threadIdx.x;
+    int tid = stid;
     asm volatile("" : "+v"(tid));
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
@@ -130,11 +149,15 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
       };
       *reinterpret_cast<uint4*>(qs[buf] + tile_at<D>(row, cc)) =
           make_uint4(two(rq[u].x, c0.x, c0.y), two(rq[u].y, c0.z, c0.w), two(rq[u].z, c1.x, c1.y), two(rq[u].w, c1.z, c1.w));
-      *reinterpret_cast<uint4*>(gs[buf] + tile_at<D>(row, cc)) = rg[u];
-      if (cc == 0) {
-        ls[buf][row] = c.q0 + row < c.hi ? rl[u] * 1.4426950408889634f : __builtin_huge_valf();  // +inf -> p = 0 for padding rows
-        ds[buf][row] = rd[u];
+      *reinterpret_cast<u4_t*>(gs[buf] + tile_at<D>(row, cc)) = rg[u];
+      if (!APART && cc == 0) {
+        ls[buf][row] = c.q0 + row < c.hi ? rl[APART ? 0 : u] * 1.4426950408889634f : __builtin_huge_valf();  // +inf -> p = 0 for padding rows
+        ds[buf][row] = rd[APART ? 0 : u];
       }
+    }
+    if (APART && lane < RP) {
+      ls[buf][lane] = c.q0 + lane < c.hi ? rl[0] * 1.4426950408889634f : __builtin_huge_valf();
+      ds[buf][lane] = rd[0];
     }
     if (lane < RP) mws[wave][lane] = rm;
   };
@@ -148,20 +171,25 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
   CT cur, nxt;
   Cur here, ahead;  // the stage whose rows are committed next, and the one behind it
   {
-    const int2 gr = grp[NBm - 1];
-    here = {NBm - 1, __builtin_amdgcn_readfirstlane(gr.x), __builtin_amdgcn_readfirstlane(gr.y)};
+    const int a = max(NBm - 1 - (APART ? wave : 0), 0);
+    const int2 gr = grp[a];
+    here = {a, __builtin_amdgcn_readfirstlane(gr.x), __builtin_amdgcn_readfirstlane(gr.y)};
   }
   load_pos(here);
-  load_ct(NBm - 1, nxt);
+  if constexpr (!APART) load_ct(here.a, nxt);
   load_rows(here);
   ahead = advance(here);
   load_pos(ahead);
-  int buf = 0;
-  for (int a = NBm - 1; a >= 0; --a) {
+  int buf = APART ? wave : 0;
+  for (int top = NBm - 1; top >= 0; top -= STEP) {
+    const int a = APART ? top - wave : top;
+    const bool mine = !APART || a >= 0;
     float csum = 0.f, amu2 = 0.f;
-    for (bool first = true;; first = false) {
+    if (APART && mine) load_ct(a, cur);
+    for (bool first = true; mine; first = false) {
       commit(here, buf);
-      __syncthreads();
+      if constexpr (APART) wave_lds_fence();
+      else __syncthreads();
       const int nrow = here.hi - here.q0, ntl = min((nrow + 31) / 32, RP / 32);
       const bool last = nrow <= RP;
       here = ahead;
@@ -169,16 +197,21 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
       ahead = advance(here);
       load_pos(ahead);
       if (first) {
-        cur = nxt;
-        load_ct(a > 0 ? a - 1 : 0, nxt);
-        const float f = (a < NBm - 1 && cur.amu > MUSE_NEG_INF) ? __expf(cur.amu - an) : 0.f;
+        if constexpr (!APART) {
+          cur = nxt;
+          load_ct(max(a - 1, 0), nxt);
+        }
+        const float f = (!APART && a < NBm - 1 && cur.amu > MUSE_NEG_INF) ? __expf(cur.amu - an) : 0.f;
         an = cur.amu;
         amu2 = jvalid ? cur.amu * 1.4426950408889634f : MUSE_NEG_INF;
-        rc *= f;
+        rc = APART ? 0.f : rc * f;
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
-          for (int t = 0; t < 4; ++t) { gk[m][t] *= f; gv[m][t] *= f; }
+          for (int t = 0; t < 4; ++t) {
+            gk[m][t] = APART ? 0.f : gk[m][t] * f;
+            gv[m][t] = APART ? 0.f : gv[m][t] * f;
+          }
       }
       // LDS offsets are made from the lane number here, not kept in registers over the whole walk
       int ln = lane;
@@ -219,14 +252,41 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
           gk[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, df, gk[m], 0, 0, 0);
         }
       }
-      buf ^= 1;
+      if constexpr (!APART) buf ^= 1;
       if (last) break;
-      wave_lds_fence();  // the next stage rewrites this wave's mask words
+      wave_lds_fence();  // the next stage rewrites this wave's mask words (APART: and its rows)
     }
     csum += __shfl_xor(csum, 16, 64);
     csum += __shfl_xor(csum, 32, 64);
     rc += csum;
-    if (!live) continue;
+    if constexpr (APART) {
+      for (int w = 0; w < min(NW, top + 1); ++w) {
+        if (w == wave) {
+          if (a < NBm - 1) {
+            const float2 in = carry_c[lane];
+            const float f = cur.amu > MUSE_NEG_INF ? __expf(cur.amu - in.y) : 0.f;
+            rc = fmaf(f, in.x, rc);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+              const f32x4_t k4 = carry[m][lane], v4 = carry[MT + m][lane];
+#pragma unroll
+              for (int t = 0; t < 4; ++t) {
+                gk[m][t] = fmaf(f, k4[t], gk[m][t]);
+                gv[m][t] = fmaf(f, v4[t], gv[m][t]);
+              }
+            }
+          }
+          carry_c[lane] = make_float2(rc, cur.amu);
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            carry[m][lane] = gk[m];
+            carry[MT + m][lane] = gv[m];
+          }
+        }
+        __syncthreads();
+      }
+    }
+    if (!live || !mine) continue;
     const float wgt = cur.mu > MUSE_NEG_INF ? __expf(cur.mu - cur.amu) : 0.f;
     const size_t cell = cell_at(a);
     // rows go out through a per-wave LDS tile: a store instruction then writes 64 / (D/8) whole rows of consecutive
@@ -237,7 +297,7 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
         const f32x4_t& r = arr == 0 ? gk[m] : gv[m];
-        *reinterpret_cast<uint2*>(&tw[wave][c16][16 * m + 4 * g]) = make_uint2(pack_bf16x2(wgt * r[0], wgt * r[1]), pack_bf16x2(wgt * r[2], wgt * r[3]));
+        *reinterpret_cast<uint2*>(&tw[c16][16 * m + 4 * g]) = make_uint2(pack_bf16x2(wgt * r[0], wgt * r[1]), pack_bf16x2(wgt * r[2], wgt * r[3]));
       }
       wave_lds_fence();
       bf16_t* dst = arr == 0 ? G_k : G_v;
@@ -245,8 +305,7 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
       for (int it = 0; it < 16 * CPR / 64; ++it) {
         const int row = it * (64 / CPR) + lane / CPR, cc = lane % CPR;
         if (unit * 16 + row < Ck) {
-          typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-          const u4_t v = *reinterpret_cast<const u4_t*>(&tw[wave][row][cc * 8]);
+          const u4_t v = *reinterpret_cast<const u4_t*>(&tw[row][cc * 8]);
           __builtin_nontemporal_store(v, reinterpret_cast<u4_t*>(dst + (cell + unit * 16 + row) * D + cc * 8));  // written once, read by later kernels
         }
       }
@@ -255,19 +314,34 @@ __global__ void __launch_bounds__(64 * CellCfg<D>::kWaves) __attribute__((amdgpu
   }
 }
 
+// Key blocks side by side (APART) for few units, counted once for every round of eight key blocks, and enough key blocks to share out.
+// By the heads of the call, not of a chunk: the bits do not depend on the workspace.  us, one after the other / side by side, 8
+// blocks unless said:
+//   units   D = 64: 227 / 60 at one head of 16k with 4 x 8 clusters (4 units), 278 / 70 at 4 of 8k with 1 x 512 (128), 87 / 43 at one of
+//           32k with 64 x 128 (512), 99 / 66 at 16 of 16k with 32 x 32 (1024), 84 / 103 at 2 of 64k with 128 x 128 (2048), 134 / 210 at
+//           16 of 32k with 64 x 64 (4096); D = 128: 195 / 86, 411 / 125, 165 / 60, 166 / 132, 153 / 182 and 245 / 360
+//   blocks  D = 64: 44 / 70 with 2, 39 / 26 with 3, 82 / 68 with 4; D = 128: 48 / 56 with 3, 129 / 135 with 4; with 12
+//           (two rounds) at 1024 units 74 / 72 and 103 / 133, with 16 at 512 97 / 51 and 139 / 101
+static bool cells_apart(const MuseDims& d, int nunit) {
+  const int rounds = (d.nb - 1 + 7) / 8;
+  return d.nb - 1 >= (d.D == 64 ? 2 : 4) && (long long)d.B * d.Hq * d.Cq * nunit * rounds <= 1024;
+}
+
 }  // namespace
 
 int muse_launch_ff_bwd_cells_mx(const MuseDims& d, const void* Q, const void* dO, const float* qc, const float* LSE,
                                 FFWorkspace& w, int h0, int hn, hipStream_t st) {
+  const int nunit = (d.Ck + 15) / 16;
+  const bool apart = cells_apart(d, nunit);
   auto go = [&](auto* kernel, int waves) {
     MuseProf prof_("k_ff_bwd_cells_mx", st);
-    const int ng = ((d.Ck + 15) / 16 + waves - 1) / waves;
-    hipLaunchKernelGGL(kernel, dim3((d.Cq + 7) / 8 * 8 * ng, 1, hn), dim3(64 * waves), 0, st, (const bf16_t*)Q, (const bf16_t*)dO,
+    const int ng = apart ? nunit : (nunit + waves - 1) / waves;
+    hipLaunchKernelGGL(kernel, dim3((apart ? d.Cq : (d.Cq + 7) / 8 * 8) * ng, 1, hn), dim3(64 * waves), 0, st, (const bf16_t*)Q, (const bf16_t*)dO,
                        qc, w.s_mu, w.A_mu, (const bf16_t*)w.A_kb, (const bf16_t*)w.A_v, w.perm_q, w.off_q, LSE, w.delta,
                        w.selmask, w.g_s_c, (bf16_t*)w.g_s_k, (bf16_t*)w.g_s_v, h0, d.N, d.nb, d.Cq, d.Ck, d.scale);
   };
-  if (d.D == 64) go(k_ff_bwd_cells_mx<64>, CellCfg<64>::kWaves);
-  else go(k_ff_bwd_cells_mx<128>, CellCfg<128>::kWaves);
+  if (d.D == 64) apart ? go(k_ff_bwd_cells_mx<64, true>, CellCfg<64, true>::kWaves) : go(k_ff_bwd_cells_mx<64, false>, CellCfg<64, false>::kWaves);
+  else apart ? go(k_ff_bwd_cells_mx<128, true>, CellCfg<128, true>::kWaves) : go(k_ff_bwd_cells_mx<128, false>, CellCfg<128, false>::kWaves);
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

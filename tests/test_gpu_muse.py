@@ -66,7 +66,7 @@ def as_sets(sel):
 # What a case must reach, asserted inside the run so that a change of generator or sizes cannot silently take
 # it off the code path it is there for: pair_keys = keys of the largest RETRIEVED (cluster, block) pair (the
 # pair kernels tile keys by 32); group = queries of the largest (block, query cluster) group (the tile kernels
-# take 32 per wave, the cell-gradient kernel stages 96 per pass).
+# take 32 per wave, the cell-gradient kernel stages 32 at a time).
 # pair_hits = (query, slot) entries of the most retrieved pair of a KV head (all query heads of the group): the
 # key/value-gradient kernel of the retrieval shares a pair among several waves from 8 tiles of 32 hits on.
 REACH = {
