@@ -9,8 +9,12 @@
 // keys is two phases,
 //   M  S(i) = K(i) Q^T and O += V(i-1) P(i-1)      V  masks, maximum, exponentials and P(i)
 // with a barrier behind each, and waves 4 .. 7 run one phase behind waves 0 .. 3: while one half is in M the other is in V.
-// K(i+1) and V(i) are written to LDS during the V phases before M(i+1), row-major, serving both operand forms (lds_tile.h),
-// two buffers each; the rows after those are on their way to registers.
+// A tile of keys or values lies in LDS once, row-major, and serves both operand forms (lds_tile.h).  The rows go there straight
+// from memory: every wave asks for its share of K(i+2) and V(i+1) in M(i), waits for it in V(i), and the barrier behind that V
+// phase makes the tile complete, at the latest (the late half's) one phase before the early half first reads K(i+2), in V(i+1).
+// Three buffers each: the late half reads K(i) and V(i-1) in its M(i), a phase after the early half's; the barrier behind that
+// phase separates the read from the early half's M(i+1), which asks for K(i+3) and V(i+2) into the same buffers.  With two the
+// rows would arrive while they are still read.
 //
 // What it takes now (cycles per step and wave at exact attention over 16k tokens, D = 64): M 930 to 1180 for 512 of matrix
 // instructions, V 860 to 1120 for some 130 vector instructions of which 32 are exponentials; the two pipes still slow each

@@ -98,8 +98,9 @@ __device__ __forceinline__ void commit_rows(const TileRegs& r, bf16_t* tile) {
   }
 }
 
-// dQ.  The matrix pipe is half busy (0.49 to 0.53 at D = 64); what it waits for is the vector work between S and dQ and the
-// LDS reads in front of it, which three (D = 128: two) waves per SIMD cover in part.  Keys lie in LDS once, row-major, for
+// dQ.  The matrix pipe is 0.53 to 0.57 busy at D = 64 (0.50 at D = 128), the vector pipe 0.68; what the matrix pipe waits for is the
+// vector work between S and dQ and the LDS reads in front of it (no bank conflicts), which three (D = 128: two) waves per SIMD
+// cover in part.  Keys lie in LDS once, row-major, for
 // both contractions; with a transposed copy (4-byte stores in row pairs, half of the LDS-active cycles in bank conflicts) and
 // two barriers per step it took, us before -> after, 989 -> 927 for exact attention of 32 heads of 8k, D = 128, 482 -> 460 at
 // 8 heads of 16k, 1821 -> 1779 at 16 heads of 64k in blocks of 8192, 3560 -> 3376 at 32; same bits.

@@ -12,8 +12,10 @@
 // at a time, row-major: the rows serve S and dP as they lie and G_k, G_v through transposed reads).  Two stages and the
 // next block's summaries in flight, so a block costs one barrier.
 //
-// Bound by streaming the summaries in and the gradients out, 15.4 GB at 16 heads of 64k tokens with 256 x 1024 clusters: 3.13
-// ms, 4.9 TB/s, the copy rate.  With the reverse accumulation as a launch of its own the gradients of the accumulated cells
+// Bound at D = 64 by vector instructions (0.67 of the busy cycles at 16 heads of 64k tokens, 256 x 1024 and 128 x 128 clusters: 32
+// queries per group on average, so a stage is often half empty, and both its halves of 16 rows are always worked through) beside
+// the summaries in and the gradients out, 16.0 GB there: 3.1 to 3.3 ms, the copy rate.  At D = 128 (32 heads of 32k, 128 x 512) by
+// that traffic, 5.4 TB/s, with the vector pipe 0.42 busy.  With the reverse accumulation as a launch of its own the gradients of the accumulated cells
 // took a round trip through HBM in 16 bits: 3.25 + 3.37 ms there, 2.88 + 3.36 (now 2.89) at 32 heads of 32k, D = 128, 128 x 512,
 // 0.44 + 0.17 (now 0.30) at 16 heads of 64k with 128 x 128.
 #include "ff_common.h"

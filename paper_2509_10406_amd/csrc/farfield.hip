@@ -453,7 +453,8 @@ __global__ void __launch_bounds__(64) k_block_summaries(const T* __restrict__ Ks
 // transpose as whole rows.
 // Bound by round trips: a chunk of 8 keys, then the rows out.  A cell of one chunk keeps its rows in registers over the passes and
 // has the next pass's logits requested before its rows go out; PIPE: longer cells have their chunks in two buffers, at D =
-// 64 for sixteen keys and more on average.  us before / now: 873 / 795 at 16 heads of 64k with 256 x 1024 clusters (8 keys; with PIPE 831),
+// 64 for sixteen keys and more on average (one chunk at a time / PIPE at 16 heads of 64k: 554 / 568 with 8 keys, 566 / 570 with 12, 599 /
+// 597 with 16, 602 / 566 with 32, 691 / 615 with 64; D = 128 1259 / 1011 with 8).  us before / now: 873 / 795 at 16 heads of 64k with 256 x 1024 clusters (8 keys; with PIPE 831),
 // 4561 / 4305 at 32 heads (4778), 786 / 666 with 128 x 128 (64 keys; without 737), 2762 / 2514 at 32 heads of 32k, D = 128, 8 keys
 // (without 2767), 794 / 697 with 64.
 template <typename T, int D, bool PIPE>

@@ -792,7 +792,7 @@ __global__ void __launch_bounds__(256) k_add_rows(const float* __restrict__ src,
 
 template <typename T, int D>
 int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, const int32_t* aq, const float* LSE,
-                  const int32_t* selc, const int32_t* selb, FFWorkspace& w, int h0, int hn, hipStream_t sq_, hipStream_t sk_) {
+                  FFWorkspace& w, int h0, int hn, hipStream_t sq_, hipStream_t sk_) {
   // the far-field part of dQ goes to stream sq_, the cell gradients and what they give to keys and values to
   // stream sk_: the two share inputs only
   const int NBm = d.nb - 1;
@@ -911,8 +911,8 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
         MUSE_HIP_CHECK(hipEventRecord(ax.mid, st));
         MUSE_HIP_CHECK(hipStreamWaitEvent(sb, ax.mid, 0));
       }
-      if (D == 64) rc = run_bwd_chunk<T, 64>(d, Q, dO, qc, aq, LSE, selc, selb, w, h0, hn, split ? sb : st, st);
-      else rc = run_bwd_chunk<T, 128>(d, Q, dO, qc, aq, LSE, selc, selb, w, h0, hn, split ? sb : st, st);
+      if (D == 64) rc = run_bwd_chunk<T, 64>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st);
+      else rc = run_bwd_chunk<T, 128>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st);
       if (rc) return rc;
     }
   }
