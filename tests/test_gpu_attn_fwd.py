@@ -54,6 +54,14 @@ def test_reference_moves(kind, D):
     check(Q.to(torch.bfloat16), K.to(torch.bfloat16), V.to(torch.bfloat16))
 
 
+def test_more_heads_than_a_grid_dimension_has_rows():
+    g = torch.Generator(device="cuda").manual_seed(1)
+    B = 66000  # 528000 heads, eight to a row of the grid
+    Q, K, V = (torch.randn(B, 8, 1, 64, generator=g, device="cuda").bfloat16() for _ in range(3))
+    O = mb.exact_attn_fwd(mb.Params(B=B, Hq=8, Hkv=8, N=1, D=64), Q, K, V)[0]
+    assert torch.equal(O, V)  # one key: its weight is 1
+
+
 BLOCKS = {
     "fwd_block384_d128": ("cfg2", dict(D=128, N=1152, Hq=2, Hkv=1, Cq=6, Ck=20, r=3, block=384, kmeans_iters=1)),
     "fwd_block128_d128": ("cfg2", dict(D=128, N=640, Hq=1, Hkv=1, Cq=4, Ck=12, r=2, block=128, kmeans_iters=1)),
