@@ -1,0 +1,56 @@
+"""dQ, dK and dV of bf16 attention in tiles of 256 rows, where those tiles end: a block of one tile and a row more, last tiles with
+one row, with one wave, with an odd half of a wave's 64, blocks of whole tiles, grouped query heads (their steps follow one another),
+and enough heads that dQ takes these tiles too.  Against fp64 on the same bf16 rows (a head of each kind), at the parity suite's
+bound for gradients."""
+import math
+
+import pytest
+import torch
+
+from paper_2509_10406_amd import binding as mb
+from tests.util import bf16_grad_bound
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,Hq,Hkv", [(257, 1, 1), (320, 4, 1), (353, 3, 3), (512, 2, 1), (1024, 48, 24), (1025, 32, 32), (1095, 33, 11),
+                                      (1250, 30, 30), (1311, 28, 7)])
+def test_tiles(N, Hq, Hkv, D):
+    g = torch.Generator().manual_seed(N + D)
+    p = mb.Params(B=1, Hq=Hq, Hkv=Hkv, N=N, D=D)
+    Q, K, V, dO = (torch.randn(1, H, N, D, generator=g).bfloat16().cuda() for H in (Hq, Hkv, Hkv, Hq))
+    O, LSE = mb.exact_attn_fwd(p, Q, K, V)
+    got = mb.exact_attn_bwd(p, Q, K, V, O, LSE, dO)
+    G = Hq // Hkv
+    for hk in sorted({0, Hkv - 1}):
+        k, v = K[0, hk].cpu().double(), V[0, hk].cpu().double()
+        wk, wv = torch.zeros_like(k), torch.zeros_like(v)
+        for h in range(hk * G, hk * G + G):
+            q, d = Q[0, h].cpu().double(), dO[0, h].cpu().double()
+            P = (q @ k.T / math.sqrt(D)).masked_fill(torch.ones(N, N, dtype=torch.bool).triu(1), -math.inf).softmax(-1)
+            dP = d @ v.T
+            dS = P * (dP - (P * dP).sum(-1, keepdim=True)) / math.sqrt(D)
+            wq = dS @ k
+            wk += dS.T @ q
+            wv += P.T @ d
+            assert (got[0][0, h].cpu().double() - wq).abs().max() <= bf16_grad_bound(float(wq.abs().max()))
+        for x, w in ((got[1], wk), (got[2], wv)):
+            assert (x[0, hk].cpu().double() - w).abs().max() <= bf16_grad_bound(float(w.abs().max()))
+
+
+def test_a_row_that_is_not_finite_stays_with_its_successors():
+    # a query row, and with it the keys it attends: its block's up to its own position, and no later ones
+    g = torch.Generator().manual_seed(5)
+    H, N, D = 32, 1100, 64
+    p = mb.Params(B=1, Hq=H, Hkv=H, N=N, D=D)
+    Q, K, V, dO = (torch.randn(1, H, N, D, generator=g).bfloat16().cuda() for _ in range(4))
+    O, LSE = mb.exact_attn_fwd(p, Q, K, V)
+    want = mb.exact_attn_bwd(p, Q, K, V, O, LSE, dO)
+    n = 700
+    dO[:, :, n, 3] = float("inf")
+    dQ, dK, dV = mb.exact_attn_bwd(p, Q, K, V, O, LSE, dO)
+    others = torch.arange(N, device="cuda") != n
+    assert torch.equal(dQ[:, :, others], want[0][:, :, others])
+    far = torch.arange(N, device="cuda") >= (n // 64 + 1) * 64  # the matrix instructions meet a masked pair inside 64 rows
+    assert torch.equal(dK[:, :, far], want[1][:, :, far]) and torch.equal(dV[:, :, far], want[2][:, :, far])
