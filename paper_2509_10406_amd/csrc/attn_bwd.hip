@@ -16,9 +16,12 @@
 // compiler is told to let the other matrix instructions write there: left to itself it puts all results into accumulation
 // registers and moves every score out again, 200 moves in 64 matrix instructions).
 // Measured, us, 128 rows per workgroup and 32 per wave -> this: dK/dV 640 -> 465 at 8 heads of 16k, 200 -> 135 at 32 heads of 4k,
-// 82 -> 52 at 128 heads of 1k; dQ 440 -> 370, 150 -> 104, 51 -> 41; dQ at D = 128 791 -> 641 at 32 heads of 8k, 241 -> 175 of 4k.  Cycles
+// 82 -> 52 at 128 heads of 1k; dQ 440 -> 370, 150 -> 104, 51 -> 41; dQ at D = 128 791 -> 641 at 32 heads of 8k, 241 -> 175 of 4k; dK/dV
+// at D = 128 (before: 32 keys and one matrix phase per wave) 1210 -> 1012, 339 -> 287, 149 -> 120 at 128 heads of 1k.  Cycles
 // per step (of 2048 in matrix instructions) 3050 for dK/dV, of 1536 2420 for dQ (D = 128: of 3072 4380); the clock falls to 1.75
 // GHz meanwhile (2.2 on zeros): what is left is the chip's power.
+#include <type_traits>
+
 #include "ff_common.h"
 #include "flash_tile.h"
 #include "lds_tile.h"
@@ -27,6 +30,7 @@ namespace {
 
 constexpr int TR = 256;  // rows of a workgroup's tile: keys (dK / dV) or queries (dQ)
 constexpr int BN = 64;   // rows staged per step
+constexpr int TR128 = 128;  // keys of a workgroup's tile of dK / dV at D = 128
 
 using lds_frag = __attribute__((address_space(3))) const bf16x8_t*;
 using lds_f4 = __attribute__((address_space(3))) const f32x4_t*;
@@ -298,6 +302,296 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   }
 }
 
+// dK and dV at D = 128.  Accumulators of dK and dV and both operands of 64 keys are too many registers for one wave, so two waves
+// share 64 keys: one computes P = exp2(c (Q K^T - LSE)) and dV += P^T dO, the other, a step of 32 queries behind, dP = dO V^T,
+// dS = P dP and dK += dS^T Q; P passes between them through LDS in fp32, one barrier per step.  Within a wave the same
+// three things overlap as above, a step being the parts A and B of one tile.
+// At step T: P and dV of tile T, dP and dK of tile T - 1; rows of tile T + 1 are read, T + 2 is on its way, T + 3 is asked for
+// (behind the barrier that ends the reads of T - 2): five buffers.  Seeds come in chunks of 256 rows, four buffers: a chunk is
+// written at the first step of the chunk two before it, when nobody reads the one before that any more.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) k_flash_bwd_dkv128_wide(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
+    const float* __restrict__ LSE, const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV, int N,
+    int Bs, int Hq, int Hkv, int nbatch, int chunk, float scale, float scale_log2e) {
+  constexpr int D = 128, KS = D / 16, DT = D / 32, BQ = 32, NB = 5, NS = 4, SC = 256, kTile = BQ * D, kB = kTile * 2, NM = 16, LAG = 6;
+  __shared__ __attribute__((aligned(256))) bf16_t tiles[2][NB][kTile];       // Q, dO
+  __shared__ __attribute__((aligned(256))) float4 px[2][2][2][4][64];        // P: [step parity][wave pair][unit][4 rows][lane]
+  __shared__ __attribute__((aligned(256))) float seeds[NS][2][SC];           // -LSE / scale, -delta
+  const int tpg = (Bs + TR128 - 1) / TR128;
+  const FlashTile ft = flash_tile_of(tpg, N / Bs, Hkv, nbatch, tpg, chunk);
+  if (!ft.ok) return;
+  const int hk = ft.h, b = ft.b, G_ = Hq / Hkv;
+  const size_t kh = ((size_t)b * Hkv + hk) * N, qh0 = ((size_t)b * Hq + (size_t)hk * G_) * N;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, col = lane % 32, half = lane / 32;
+  const int pair = wave % 2, role = wave / 2;
+  const int k0 = ft.blk * Bs + ft.t * TR128, bend = (ft.blk + 1) * Bs;
+  const int ka = k0 + 64 * pair;  // the pair's keys: ka .. ka + 63
+  const int ns = (bend - k0 + BQ - 1) / BQ, NT = G_ * ns;
+
+  bf16x8_t kv[2][KS];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int x = 0; x < KS; ++x)
+      kv[u][x] = *reinterpret_cast<const bf16x8_t*>((role ? V : K) + (kh + min(ka + 32 * u + col, bend - 1)) * D + 16 * x + 8 * half);
+  f32x16_t acc[2][DT];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int t = 0; t < DT; ++t) acc[u][t] = zero16();
+
+  // staged rows
+  const bf16_t *qp = Q + qh0 * D, *gp = dO + qh0 * D;
+  const int srow = tid / 16, schunk = (tile_at<D>(srow, tid % 16) - srow * D) / 8;
+  const uint32_t lds0 = lds_addr(&tiles[0][0][0]) + wave * 1024;
+  int fq = k0, fh = 0, fb = 0;
+  auto bring_op = [&](int k) {  // the k-th of the four requests of a tile
+    const uint32_t off = (uint32_t)(min(fq + 16 * (k / 2) + srow, bend - 1) * D + 8 * schunk) * 2;
+    rows_to_lds(lds0 + (k % 2 * NB + fb) * kB + k / 2 * 4096, off, k % 2 ? gp : qp);
+  };
+  auto bring_end = [&]() {
+    fb = fb == NB - 1 ? 0 : fb + 1;
+    fq += BQ;
+    const bool over = fq >= bend;
+    const int step = over && ++fh < G_ ? N : 0;  // past the last head: its tiles again, which nobody reads
+    fq = over ? k0 : fq;
+    qp += (size_t)step * D;
+    gp += (size_t)step * D;
+  };
+  auto bring = [&]() {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bring_op(k);
+    bring_end();
+  };
+  // seeds of a chunk, a row per thread
+  const float seed = -1.4426950408889634f / scale_log2e, dead = seed * __builtin_huge_valf();
+  const float *lp = LSE + qh0, *ep = delta + qh0;
+  int sq = k0, sh = 0, sb = 0;
+  float lv, ev;
+  auto seeds_fetch = [&]() {
+    lv = lp[min(sq + tid, bend - 1)];
+    ev = ep[min(sq + tid, bend - 1)];
+  };
+  auto seeds_commit = [&]() {
+    seeds[sb][0][tid] = sq + tid < bend ? lv * seed : dead;
+    seeds[sb][1][tid] = -ev;
+    sb = (sb + 1) % NS;
+    sq += SC;
+    const bool over = sq >= bend;
+    const int step = over && ++sh < G_ ? N : 0;
+    sq = over ? k0 : sq;
+    lp += step;
+    ep += step;
+  };
+
+  const uint32_t rat = lds_addr(&tiles[0][0][tile_at<D>(col, half)]);
+  const uint32_t tat = lds_addr(&tiles[0][0][tile_at<D>(4 * half + (lane % 16) / 4, 2 * ((lane / 16) % 2) + (lane % 4) / 2) + 4 * (lane % 2)]);
+  const uint32_t sat = lds_addr(&seeds[0][0][4 * half]), pat = lds_addr(&px[0][pair][0][0][lane]);
+
+  auto work = [&](auto role_c) {
+    constexpr int R = decltype(role_c)::value;  // 0: P and dV, 1: dP and dK, a step behind
+    uint32_t ra_[KS], ta_[2 * DT], sa_, pa_ = pat;
+    bf16x8_t rows[KS], cols[2][DT];
+    f32x16_t sd, s[2];
+    float pv[2][16];
+    uint32_t pf[2][2][4];
+    auto load_op = [&](int j) {
+      if (j % 2 == 0) {
+        rows[j / 2] = *(lds_frag)(uintptr_t)(ra_[j / 2] + R * NB * kB);
+      } else {
+        const int G = j / 2 / DT, t = j / 2 % DT;
+        const uint32_t o = (1 - R) * NB * kB + G * 16 * D * 2;
+        cols[G][t] = tr_join(__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr)(uintptr_t)(ta_[2 * t] + o)),
+                             __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr)(uintptr_t)(ta_[2 * t + 1] + (o + 8 * D * 2))));
+      }
+    };
+    auto load_seed = [&](int g) {
+      const f32x4_t v = *(lds_f4)(uintptr_t)(sa_ + (R * SC + 8 * g) * 4);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sd[4 * g + u] = v[u];
+    };
+    auto load_p = [&](int u, int g) {
+      const f32x4_t v = *(lds_f4)(uintptr_t)(pa_ + (u * 4 + g) * 1024);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) pv[u][4 * g + x] = v[x];
+    };
+    auto mfma_op = [&](int j, int us, int ug, bool score, bool grad) {
+      const int x = j / 2;
+      if (j % 2 == 0 && score) s[us] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows[x], kv[us][x], x == 0 ? sd : s[us], 0, 0, 0);
+      if (j % 2 == 1 && grad) {
+        const int G = x / DT, t = x % DT;
+        mfma_acc(acc[ug][t], cols[G][t], __builtin_bit_cast(bf16x8_t, make_uint4(pf[ug][G][0], pf[ug][G][1], pf[ug][G][2], pf[ug][G][3])));
+      }
+    };
+    float tm = 0.f;
+    const int nm = 4 * half - col;
+    auto pack = [&](int u, int k) { pf[u][k / 4][k % 4] = pack_bf16x2(s[u][2 * k], s[u][2 * k + 1]); };
+    auto valu_op = [&](int j, int u, bool mask) {
+      if constexpr (R == 0) {
+        const int e = j;
+        if (e == 0) tm = s[u][0] * scale_log2e;
+        float p = fast_exp2(tm);
+        if (e < 15) tm = s[u][e + 1] * scale_log2e;
+        if (mask) p = nm + 8 * (e / 4) + e % 4 >= 0 ? p : 0.f;
+        s[u][e] = p;
+        if (e >= 2 && e % 2 == 0) pack(u, e / 2 - 1);
+        if (e == 15) pack(u, 7);
+        if ((e % 4 == 0 && e > 0) || e == 15) {  // four rows of P for the other wave
+          const int g = e == 15 ? 3 : e / 4 - 1;
+          const f32x4_t v = {s[u][4 * g], s[u][4 * g + 1], s[u][4 * g + 2], s[u][4 * g + 3]};
+          *(__attribute__((address_space(3))) f32x4_t*)(uintptr_t)(pa_ + (u * 4 + g) * 1024) = v;
+        }
+      } else {  // P arrives in the first positions of part A
+        if (j >= 6 && j < 14) {
+          const int e = 2 * (j - 6);
+          s[u][e] *= pv[u][e];
+          s[u][e + 1] *= pv[u][e + 1];
+        }
+        if (j >= 7 && j < 15) pack(u, j - 7);
+      }
+    };
+#define DKV_PART(SECOND, US, UV, SCORE, VAL, MASK, GRAD)                                 \
+  {                                                                                      \
+    _Pragma("unroll") for (int j = 0; j < NM; ++j) {                                     \
+      mfma_op(j, US, 1 - UV, SCORE, GRAD);                                               \
+      __builtin_amdgcn_sched_barrier(0);                                                 \
+      if (VAL) valu_op(j, UV, MASK);                                                     \
+      if (!(SECOND)) {                                                                   \
+        if (R == 1 && j < 4) load_p(0, j);                                               \
+        if (R == 1 && j >= 12) load_p(1, j - 12);                                        \
+        if (j >= 1 && j < 5) load_seed(j - 1);                                           \
+        if (j >= LAG) load_op(j - LAG);                                                  \
+        if (j % 4 == 1) bring_op(j / 4);                                                 \
+      } else if (j < LAG) {                                                              \
+        load_op(NM - LAG + j);                                                           \
+      }                                                                                  \
+      __builtin_amdgcn_sched_barrier(0);                                                 \
+    }                                                                                    \
+  }
+    int T = 0, t0 = 0, cb = 0, nb = 1, ni = 0, nsb = 0;  // step, its tile's number in the head; of tile T - R the buffer and the next one's; of the next tile the number and the seeds
+    auto begin = [&]() {
+      if (t0 % (SC / BQ) == 0 && T < NT) {  // the first step of a chunk: the one two further on is written
+        seeds_commit();
+        seeds_fetch();
+      }
+      ni = ni + 1 == ns ? 0 : ni + 1;
+      nsb = ni % (SC / BQ) == 0 ? (nsb + 1) % NS : nsb;
+    };
+    auto end = [&]() {
+      ++T;
+      t0 = t0 + 1 == ns ? 0 : t0 + 1;
+      cb = nb;
+      nb = nb == NB - 1 ? 0 : nb + 1;
+      asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // all but the tile asked for last
+      group_barrier();
+    };
+    auto from = [&](int br) {
+#pragma unroll
+      for (int x = 0; x < 2 * DT; ++x) ta_[x] = (tat ^ (uint32_t)(x << 5)) + cb * kB;
+#pragma unroll
+      for (int x = 0; x < KS; ++x) ra_[x] = (rat ^ (uint32_t)(x << 5)) + br * kB;
+      sa_ = sat + (uint32_t)(nsb * 2 * SC + ni % (SC / BQ) * BQ) * 4;
+      pa_ = pat + (uint32_t)((T - R) & 1) * (2 * 2 * 4 * 64 * 16);
+    };
+    auto pin = [&](int u) {  // the operands of a part's last elements are made in that part, not behind the next branch
+#pragma unroll
+      for (int G = 0; G < 2; ++G) asm volatile("" ::"v"(pf[u][G][0]), "v"(pf[u][G][1]), "v"(pf[u][G][2]), "v"(pf[u][G][3]));
+    };
+    auto idle = [&]() {
+      begin();
+      bring();
+      end();
+    };
+    if (R == 1) {  // a step behind
+      bring();
+      if (NT > 0) {
+        seeds_commit();
+        seeds_fetch();
+      }
+      ++T;
+      t0 = ns == 1 ? 0 : 1;
+      asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      group_barrier();
+    }
+    for (int g = 0; g < G_; ++g) {
+      int i = 0;
+      for (; i < min(2 * pair, ns); ++i) idle();
+      if (i < ns) {
+        from(cb);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load_seed(q);
+#pragma unroll
+        for (int j = 0; j < NM; j += 2) load_op(j);
+        begin();
+#pragma unroll
+        for (int j = 0; j < NM; j += 2) mfma_op(j, 0, 1, true, false);
+        __builtin_amdgcn_sched_barrier(0);
+        from(nb);
+        DKV_PART(false, 1, 0, false, true, true, false)
+        bring_end();
+        DKV_PART(true, 0, 1, true, false, false, true)
+        end();
+        if (++i < ns) {
+          begin();
+          from(nb);
+          DKV_PART(false, 1, 0, true, true, false, false)
+          bring_end();
+          DKV_PART(true, 0, 1, true, true, true, true)
+          pin(1);
+          end();
+          for (++i; i < ns; ++i) {
+            begin();
+            from(nb);
+            DKV_PART(false, 1, 0, true, true, false, true)
+            bring_end();
+            DKV_PART(true, 0, 1, true, true, false, true)
+            pin(1);
+            end();
+          }
+#pragma unroll
+          for (int j = 1; j < NM; j += 2) mfma_op(j, 0, 1, false, true);
+        }
+        acc_settle();
+      }
+    }
+    if (R == 0) idle();
+#undef DKV_PART
+  };
+  seeds_fetch();
+  seeds_commit();
+  seeds_fetch();
+  seeds_commit();
+  seeds_fetch();
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int x = 0; x < KS; ++x) asm volatile("" ::"a"(kv[u][x]));
+  bring();
+  bring();
+  bring();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  group_barrier();
+  if (role == 0) work(std::integral_constant<int, 0>{});
+  else work(std::integral_constant<int, 1>{});
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing is on its way into LDS that others may own soon
+  acc_settle();
+  float* out = role ? dK : dV;
+  const float mul = role ? scale : 1.f;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int mk = ka + 32 * u + col;
+    if (mk >= bend) continue;
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x16_t& a = acc[u][t];
+        *reinterpret_cast<float4*>(out + (kh + mk) * D + 32 * t + 8 * g + 4 * half) =
+            make_float4(mul * a[4 * g], mul * a[4 * g + 1], mul * a[4 * g + 2], mul * a[4 * g + 3]);
+      }
+  }
+}
+
 // dQ: a wave owns 64 queries, tiles of keys are staged from the diagonal back to the block's first key: the masked tiles come first,
 // in code of their own in front of the loop (behind it, the compiler spilled at D = 128).  Unit a is the later half of the queries:
 // in the first step, keys 32 .. 63 meet a alone, keys 0 .. 31 meet a and, masked, b.  Four buffers: the requests of step i for tile
@@ -510,11 +804,12 @@ static int chunk_groups(int Bs, int D, int groups) {
 //   dQ      blocks of 384 35 / 102 at 1024 groups, 22 / 29 at 256; of 640 138 / 187 at 1024, 44 / 51 at 256; of 1024 85 / 84 at 256
 //           groups, 51 / 41 at 128, 33 / 28 at 64, 24 / 26 at 32 (128 tiles of 256 rows: half of the chip's CUs); of 2048 39 / 42 at
 //           16 groups, 55 / 46 at 32.  D = 128: 81 / 86 (640, 256 groups), 164 / 147 (1024, 256), 37 / 41 (1024, 32), 65 / 67 (2048, 16).
-//   dK/dV   blocks of 256 74 / 81 at 1024 groups, 15 / 16 at 64; of 320 110 / 98 and 18 / 18; of 128 37 / 41 and 12 / 11
+//   dK/dV   blocks of 256 74 / 81 at 1024 groups, 15 / 16 at 64; of 320 110 / 98 and 18 / 18; of 128 37 / 41 and 12 / 11.  D = 128:
+//           blocks of 384 223 / 255 at 1024 groups, 25 / 24 at 64; of 512 107 / 105 at 256, 31 / 29 at 64; of 640 454 / 459 and 45 / 35
 bool muse_attn_dq_wide(const MuseDims& d, int Bs) {
   return Bs >= 4 * TR && (long long)((Bs + TR - 1) / TR) * d.B * d.Hq * (d.N / Bs) > 128;
 }
-bool muse_attn_dkv_wide(const MuseDims& d, int Bs) { return d.D == 64 && Bs > TR; }
+bool muse_attn_dkv_wide(const MuseDims& d, int Bs) { return d.D == 64 ? Bs > TR : Bs >= 2 * TR; }
 
 int muse_launch_attn_dq_wide(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
                              const float* delta, float* dQacc, hipStream_t st) {
@@ -532,10 +827,14 @@ int muse_launch_attn_dq_wide(const MuseDims& d, int Bs, const void* Q, const voi
 
 int muse_launch_attn_dkv_wide(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
                               const float* delta, float* dKacc, float* dVacc, hipStream_t st) {
-  const int tiles = (Bs + TR - 1) / TR, groups = d.B * d.Hkv * (d.N / Bs);
+  const int tr = d.D == 64 ? TR : TR128, tiles = (Bs + tr - 1) / tr, groups = d.B * d.Hkv * (d.N / Bs);
   MuseProf prof_("k_flash_bwd_dkv", st);
-  hipLaunchKernelGGL(k_flash_bwd_dkv_wide, flash_grid_of(tiles, groups), dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V,
-                     (const bf16_t*)dO, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, chunk_groups(Bs, d.D, groups), d.scale, d.scale * 1.4426950408889634f);
+  auto go = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, flash_grid_of(tiles, groups), dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V,
+                       (const bf16_t*)dO, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, chunk_groups(Bs, d.D, groups), d.scale, d.scale * 1.4426950408889634f);
+  };
+  if (d.D == 64) go(k_flash_bwd_dkv_wide);
+  else go(k_flash_bwd_dkv128_wide);
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

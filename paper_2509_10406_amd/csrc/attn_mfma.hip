@@ -1,6 +1,7 @@
 // bf16 causal attention on MFMA (Sec. 3, Eq. 1-2; Sec. 3.3 "Local attention"): keys restricted to
 // the query's own spatial block of size Bs (Bs = N gives exact attention).  The two backward
-// kernels (dQ per query tile, dK/dV per key tile; no atomics); the forward is in attn_fwd.hip.
+// kernels (dQ per query tile, dK/dV per key tile; no atomics) in tiles of 128 rows, for short blocks and few
+// tiles; attn_bwd.hip has the others, and says where the line is.  The forward is in attn_fwd.hip.
 //
 // Tiling for 64-wide waves and v_mfma_f32_32x32x16_bf16:
 //   - a wave owns 32 queries (dQ) or 32 keys (dK/dV) as the N-columns of the MFMA, so every
@@ -205,7 +206,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     }
 }
 
-// dK/dV for D = 128.  One wave with dK and dV of its 32 keys needs 128 accumulator registers beside 64 of keys and values:
+// dK/dV for D = 128 in short blocks.  One wave with dK and dV of its 32 keys needs 128 accumulator registers beside 64 of keys and values:
 // one wave per SIMD, and nothing runs while it waits.  So two waves share 32 keys: wave w computes P = exp2(c (Q K^T - LSE))
 // and dV += P^T dO, wave w + 4 (on the same SIMD) dP = dO V^T and, a step behind, dS = P dP and dK += dS^T Q; P passes
 // between them through LDS in fp32, one barrier per step of 32 queries.  A step's rows are staged once, row-major for both

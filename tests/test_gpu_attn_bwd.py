@@ -1,5 +1,5 @@
 """dQ, dK and dV of bf16 attention in tiles of 256 rows, where those tiles end: a block of one tile and a row more, last tiles with
-one row, with one wave, with an odd half of a wave's 64, blocks of whole tiles, grouped query heads (their steps follow one another),
+one row, with one wave, with an odd half of a wave's 64 (D = 128: tiles of 128 keys, seeds in chunks of 256 rows), blocks of whole tiles, grouped query heads (their steps follow one another),
 and enough heads that dQ takes these tiles too.  Against fp64 on the same bf16 rows (a head of each kind), at the parity suite's
 bound for gradients."""
 import math
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("N,Hq,Hkv", [(257, 1, 1), (320, 4, 1), (353, 3, 3), (512, 2, 1), (1024, 48, 24), (1025, 32, 32), (1095, 33, 11),
+@pytest.mark.parametrize("N,Hq,Hkv", [(257, 1, 1), (320, 4, 1), (353, 3, 3), (512, 2, 1), (513, 4, 1), (545, 6, 3), (769, 8, 2), (1024, 48, 24), (1025, 32, 32), (1095, 33, 11),
                                       (1250, 30, 30), (1311, 28, 7)])
 def test_tiles(N, Hq, Hkv, D):
     g = torch.Generator().manual_seed(N + D)
