@@ -944,12 +944,14 @@ __global__ void __launch_bounds__(64) k_key_norm_max(const float* __restrict__ p
 // entries; a tile where one overflows (many near-equal scores) is flagged and left to the two-plane kernel, which
 // runs as a second launch over the flagged tiles only.
 // ------------------------------------------------------------------------------------------
-// Two waves per SIMD at both head dims: at D = 128 one wave with all its registers (360) and 23 KB of lists and values took
-// 6.85 ms at 32 heads of 32k with 128 x 512 clusters (15 GB of summaries), two waves with 37 registers spilled 6.32; 1.18
-// and 0.96 ms with 64 x 64 clusters.  (With the next tile's key planes requested behind the values the spills are in the
-// loop, 7.4 ms; at D = 64, where that fits, it makes no difference.)
+// Bound by the summaries' way to the CU.  A tile of 32 rows comes with whole rows per load instruction and goes through LDS to
+// become an operand; with every lane loading its own operand (32 bytes of 32 rows per instruction) the loads took 4 times as many
+// cache lines, and at D = 128 37 registers spilled.  us, before / now: 6170 / 4050 at 32 heads of 32k with 128 x 512 clusters, D =
+// 128 (15 GB of summaries); D = 64: 3620 / 3230 at 16 heads of 64k with 256 x 1024, 155 / 131 at 8 heads of 16k with 64 x 256.
+// At D = 64 that is with three waves per SIMD, for which the tiles take turns in one buffer of LDS (r <= 16; with two waves and a
+// buffer more 3600 and 153); at D = 128 the registers allow two.
 template <int D, int RCAP>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) k_farfield_fwd_b(
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 && RCAP < 32 ? 3 : 2, D == 64 && RCAP < 32 ? 3 : 2))) k_farfield_fwd_b(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ A_kb, const uint16_t* __restrict__ A_km,
     const float* __restrict__ A_c, const bf16_t* __restrict__ A_v, const float* __restrict__ knorm,
     const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q, const int32_t* __restrict__ tile_off,
@@ -958,6 +960,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int DT = D / 32, KS = D / 16, CPR = D / 8, NIT = 32 * CPR / 64;
   constexpr int CAP = RCAP + 8;
   __shared__ __attribute__((aligned(16))) bf16_t vt[32 * D];
+  __shared__ __attribute__((aligned(16))) float mus[32];
   __shared__ float cs[64][CAP];   // scores of a lane's candidates
   __shared__ uint16_t ci[64][CAP];  // their clusters (MUSE_MAX_CLUSTERS fits)
   __shared__ int sel_s[32][RCAP];
@@ -1002,9 +1005,33 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const size_t acell = (((size_t)hl * NBm + (b - 1)) * Cq + i) * Ck;
   const bf16_t* Av = A_v + acell * D;
   const int ntile = (Ck + 31) / 32;
-  using KT = KTileB<D>;
-  auto load_kt = [&](KT& kt, int j0) { load_ktile_b<D>(kt, A_c + acell, A_kb + acell * D, j0, Ck, col, half); };
-  auto score_kt = [&](const KT& kt, int j0) { return score_ktile_b<D>(kt, j0, Ck, qb, scale, half); };
+  // 32 rows of a plane: whole rows per load instruction (a lane that loads its own operand touches 32 rows with every one of
+  // them), unconditional (a tile past the end repeats the last cluster); through LDS, row-major, they become operands
+  auto load_rows = [&](bf16x8_t (&x)[NIT], const void* plane, int j0) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const uint32_t o = (uint32_t)(min(j0 + it * (64 / CPR) + lane / CPR, Ck - 1) * D + lane % CPR * 8);
+      x[it] = *reinterpret_cast<const bf16x8_t*>(static_cast<const uint16_t*>(plane) + o);
+    }
+  };
+  auto put_rows = [&](bf16_t* lds, const bf16x8_t (&x)[NIT]) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) *reinterpret_cast<bf16x8_t*>(lds + tile_at<D>(it * (64 / CPR) + lane / CPR, lane % CPR)) = x[it];
+  };
+  // scale * the product so far + the cells' mu-bar
+  auto finish = [&](f32x16_t& acc, int j0) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 m4 = *reinterpret_cast<const float4*>(&mus[8 * g + 4 * half]);
+      const float mu[4] = {m4.x, m4.y, m4.z, m4.w};
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        acc[4 * g + t] = j0 + 8 * g + 4 * half + t < Ck ? fmaf(scale, acc[4 * g + t], mu[t]) : MUSE_NEG_INF;
+    }
+  };
+  const bf16_t* Ah = A_kb + acell * D;
+  const uint16_t* Am = A_km + acell * D;
+  const float* Ac = A_c + acell;
 
   // ---- pass 1: the r largest approximate scores seen by this lane half ----
   float list[RCAP];
@@ -1020,14 +1047,34 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         list[0] = fmaxf(list[0], x);
       }
     };
-    KT ka, kb;
-    load_kt(ka, 0);
+    auto score = [&](const bf16x8_t (&h)[NIT], float mu, int j0) {
+      wave_lds_fence();
+      put_rows(vt, h);
+      if (half == 0) mus[col] = mu;
+      wave_lds_fence();
+      f32x16_t acc = zero16();
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_row<D>(vt, col, 2 * ks + half), qb[ks], acc, 0, 0, 0);
+      finish(acc, j0);
+      return acc;
+    };
+    bf16x8_t ha[NIT], hb[NIT];
+    float ma, mb = 0.f;
+    load_rows(ha, Ah, 0);
+    ma = Ac[min(col, Ck - 1)];
     for (int jt = 0; jt < ntile; jt += 2) {
-      if (jt + 1 < ntile) load_kt(kb, (jt + 1) * 32);
-      insert(score_kt(ka, jt * 32));
       if (jt + 1 < ntile) {
-        if (jt + 2 < ntile) load_kt(ka, (jt + 2) * 32);
-        insert(score_kt(kb, (jt + 1) * 32));
+        load_rows(hb, Ah, (jt + 1) * 32);
+        mb = Ac[min((jt + 1) * 32 + col, Ck - 1)];
+      }
+      insert(score(ha, ma, jt * 32));
+      if (jt + 1 < ntile) {
+        if (jt + 2 < ntile) {
+          load_rows(ha, Ah, (jt + 2) * 32);
+          ma = Ac[min((jt + 2) * 32 + col, Ck - 1)];
+        }
+        insert(score(hb, mb, (jt + 1) * 32));
       }
     }
   }
@@ -1065,20 +1112,41 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   int ncand = 0;
   bool over = false;
   struct PTile {
-    KTileH<D> kt;
-    uint4 vch[NIT];
+    bf16x8_t h[NIT], m[NIT], v[NIT];
+    float mu;
   };
   auto load_ptile = [&](PTile& pt, int j0) {
-    load_ktile_h<D>(pt.kt, A_c + acell, A_kb + acell * D, A_km + acell * D, j0, Ck, col, half);
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int c = lane + 64 * it, row = c / CPR, cc = c % CPR;
-      const int jr = j0 + row < Ck ? j0 + row : Ck - 1;
-      pt.vch[it] = *reinterpret_cast<const uint4*>(Av + (size_t)jr * D + cc * 8);
-    }
+    load_rows(pt.h, Ah, j0);
+    load_rows(pt.m, Am, j0);
+    pt.mu = Ac[min(j0 + col, Ck - 1)];
+    load_rows(pt.v, Av, j0);
   };
   auto process = [&](const PTile& pt, int j0) {
-    f32x16_t acc = score_ktile_h<D>(pt.kt, j0, Ck, qb, scale, half);
+    f32x16_t acc = zero16();
+    wave_lds_fence();
+    put_rows(vt, pt.h);
+    if (half == 0) mus[col] = pt.mu;
+    wave_lds_fence();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_row<D>(vt, col, 2 * ks + half), qb[ks], acc, 0, 0, 0);
+    wave_lds_fence();
+    put_rows(vt, pt.m);
+    wave_lds_fence();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint4 raw = __builtin_bit_cast(uint4, qb[ks]);
+      if constexpr (D == 128) {  // the conversion stays in the loop: hoisted, the copy's 32 registers spill
+        asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const bf16x8_t q = __builtin_bit_cast(bf16x8_t, raw);
+      f16x8_t qh;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qh[e] = (_Float16)(float)q[e];
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, tile_row<D>(vt, col, 2 * ks + half)), qh, acc, 0, 0, 0);
+    }
+    finish(acc, j0);
     float tmax = MUSE_NEG_INF;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -1112,11 +1180,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[t][e] *= alpha;
     wave_lds_fence();
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int c = lane + 64 * it, row = c / CPR, cc = c % CPR;
-      *reinterpret_cast<uint4*>(vt + tile_at<D>(row, cc)) = pt.vch[it];
-    }
+    put_rows(vt, pt.v);
     wave_lds_fence();
 #pragma unroll
     for (int G = 0; G < 2; ++G) {

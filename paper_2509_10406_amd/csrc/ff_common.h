@@ -158,72 +158,6 @@ __device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, i
   }
   return acc;
 }
-// The same with the fp16 query made from the bf16 one where it is used.  At D = 128 the conversion is kept inside the
-// caller's loop (the empty asm): hoisted, the 32 registers of the copy cost the kernel its second wave per SIMD.
-template <int D>
-__device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, int Ck, const bf16x8_t (&qb)[D / 16],
-                                                  float scale, int half) {
-  return score_ktile_h<D>(kt, j0, Ck, qb, [&](int ks) {
-    uint4 raw = __builtin_bit_cast(uint4, qb[ks]);
-    if constexpr (D == 128) {
-      asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    const bf16x8_t q = __builtin_bit_cast(bf16x8_t, raw);
-    f16x8_t qh;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) qh[e] = (_Float16)(float)q[e];
-    return qh;
-  }, scale, half);
-}
-
-// The bf16 plane alone: an approximate score, off by at most scale * 2^-8 * |q| . |k-bar| (the plane is k-bar rounded
-// to nearest), for the passes that only need to know which clusters can be among the r best.
-template <int D>
-struct KTileB {
-  uint4 h[D / 16];
-  float mu[16];
-};
-template <int D>
-__device__ __forceinline__ void load_ktile_b(KTileB<D>& kt, const float* __restrict__ Amuq,
-                                             const bf16_t* __restrict__ Akb, int j0, int Ck, int col, int half) {
-  int c = j0 + col;
-  c = c < Ck ? c : Ck - 1;
-  const bf16_t* rh = Akb + (size_t)c * D + 8 * half;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) kt.h[ks] = *reinterpret_cast<const uint4*>(rh + 16 * ks);
-  if ((Ck & 3) == 0) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      int base = j0 + 8 * g + 4 * half;
-      base = base < Ck ? base : Ck - 4;
-      const float4 m4 = *reinterpret_cast<const float4*>(Amuq + base);
-      kt.mu[4 * g] = m4.x; kt.mu[4 * g + 1] = m4.y; kt.mu[4 * g + 2] = m4.z; kt.mu[4 * g + 3] = m4.w;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      int jr = j0 + 8 * (e / 4) + 4 * half + (e % 4);
-      kt.mu[e] = Amuq[jr < Ck ? jr : Ck - 1];
-    }
-  }
-}
-template <int D>
-__device__ __forceinline__ f32x16_t score_ktile_b(const KTileB<D>& kt, int j0, int Ck, const bf16x8_t (&qb)[D / 16],
-                                                  float scale, int half) {
-  f32x16_t acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks)
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kt.h[ks]), qb[ks], acc, 0, 0, 0);
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int jr = j0 + 8 * (e / 4) + 4 * half + (e % 4);
-    acc[e] = jr < Ck ? fmaf(scale, acc[e], kt.mu[e]) : MUSE_NEG_INF;
-  }
-  return acc;
-}
 
 // bf16 MFMA (v_mfma_f32_32x32x16_bf16) helpers.  pack8: accumulator rows 4*g0..+3 and 4*g1..+3 of a lane
 // become the 8 k-slots of a B (or A) operand; the matching other operand must use the same row order.
