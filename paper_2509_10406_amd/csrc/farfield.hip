@@ -946,8 +946,8 @@ __global__ void __launch_bounds__(64) k_key_norm_max(const float* __restrict__ p
 // ------------------------------------------------------------------------------------------
 // Bound by the summaries' way to the CU.  A tile of 32 rows comes with whole rows per load instruction and goes through LDS to
 // become an operand; with every lane loading its own operand (32 bytes of 32 rows per instruction) the loads took 4 times as many
-// cache lines, and at D = 128 37 registers spilled.  us, before / now: 6170 / 4050 at 32 heads of 32k with 128 x 512 clusters, D =
-// 128 (15 GB of summaries); D = 64: 3620 / 3230 at 16 heads of 64k with 256 x 1024, 155 / 131 at 8 heads of 16k with 64 x 256.
+// cache lines, and at D = 128 37 registers spilled.  us, before / now: 6170 / 4230 at 32 heads of 32k with 128 x 512 clusters, D =
+// 128 (15 GB of summaries); D = 64: 3620 / 3330 at 16 heads of 64k with 256 x 1024, 155 / 131 at 8 heads of 16k with 64 x 256.
 // At D = 64 that is with three waves per SIMD, for which the tiles take turns in one buffer of LDS (r <= 16; with two waves and a
 // buffer more 3600 and 153); at D = 128 the registers allow two.
 template <int D, int RCAP>
@@ -1127,9 +1127,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
     put_rows(vt, pt.h);
     if (half == 0) mus[col] = pt.mu;
     wave_lds_fence();
+    bf16x8_t hi[KS];  // the planes take turns in the sum: its order decides between clusters of nearly equal scores
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_row<D>(vt, col, 2 * ks + half), qb[ks], acc, 0, 0, 0);
+    for (int ks = 0; ks < KS; ++ks) hi[ks] = tile_row<D>(vt, col, 2 * ks + half);
     wave_lds_fence();
     put_rows(vt, pt.m);
     wave_lds_fence();
@@ -1144,6 +1144,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
       f16x8_t qh;
 #pragma unroll
       for (int e = 0; e < 8; ++e) qh[e] = (_Float16)(float)q[e];
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi[ks], qb[ks], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, tile_row<D>(vt, col, 2 * ks + half)), qh, acc, 0, 0, 0);
     }
     finish(acc, j0);
