@@ -35,21 +35,32 @@ __global__ void __launch_bounds__(256) k_gather_rows(const T* __restrict__ X, co
 }
 
 // ------------------------------------------------------------------------------------------
-// tile schedule: tile_off[hq][b][i] = number of 32-query tiles of clusters < i in block b
+// tile schedule: tile_off[hq][b][i] = number of 32-query tiles of clusters < i in block b >= 1;
+// tile_off[hq][0][i] = number of queries of clusters < i in the blocks >= 1 (far_query).  A wave per (head, block).
 // ------------------------------------------------------------------------------------------
-__global__ void k_tile_schedule(const int32_t* __restrict__ off_q, int32_t* __restrict__ tile_off, int HQ, int nb,
-                                int Cq) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= HQ * nb) return;
-  int hq = t / nb, b = t % nb;
-  const int32_t* o = off_q + (size_t)hq * ((size_t)nb * Cq + 1) + (size_t)b * Cq;
-  int32_t* to = tile_off + (size_t)t * (Cq + 1);
+__global__ void __launch_bounds__(64) k_tile_schedule(const int32_t* __restrict__ off_q, int32_t* __restrict__ tile_off, int nb, int Cq) {
+  const int hq = blockIdx.x / nb, b = blockIdx.x % nb, lane = threadIdx.x;
+  const int32_t* o = off_q + (size_t)hq * ((size_t)nb * Cq + 1);
+  int32_t* to = tile_off + (size_t)blockIdx.x * (Cq + 1);
   int run = 0;
-  for (int i = 0; i < Cq; ++i) {
-    to[i] = run;
-    run += (o[i + 1] - o[i] + 31) / 32;
+  for (int i0 = 0; i0 < Cq; i0 += 64) {
+    const int i = i0 + lane;
+    int v = 0;
+    if (i < Cq) {
+      if (b > 0) v = (o[b * Cq + i + 1] - o[b * Cq + i] + 31) / 32;
+      else
+        for (int x = 1; x < nb; ++x) v += o[x * Cq + i + 1] - o[x * Cq + i];
+    }
+    int incl = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int u = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += u;
+    }
+    if (i < Cq) to[i] = run + incl - v;
+    run += __shfl(incl, 63, 64);
   }
-  to[Cq] = run;
+  if (lane == 0) to[Cq] = run;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1273,32 +1284,33 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 // block), then component 2 = monopole attention over the per-block summaries of the blocks NOT
 // retrieved; fp32 inputs also take component 3 (exact attention over the retrieved pairs) here, bf16
 // inputs take it on the matrix cores in the pair kernels.  The result is merged into the query's
-// far-field state.  16 lanes per query, a lane owns the dims 64 x + 4 l16 + t; queries are visited in
-// bucketed order so that neighbours share the summary rows.
+// far-field state.  16 lanes per query, a lane owns the dims 64 x + 4 l16 + t, and the scalars of one of eight key blocks.
+//
+// Bound by the rows, 10 to 12 TB/s of them from the L2 (a row is read again for every query that retrieved its chain).  What
+// helped is the order of the queries, cluster by cluster instead of block by block: us, before / now, 3810 / 3500 at 32 heads of
+// 32k with D = 128 and 128 x 512 clusters, 3120 / 2880 at 32 heads of 64k with rotary rows, 75 / 53 at 12 heads of 6k with 23 x
+// 71 clusters, 165 / 134 at 4 fp32 heads of 8k; 1150 / 1145 at 16 heads of 64k with 256 x 1024.  Working the scalars of a block
+// out in one lane, with one maximum per cluster instead of one per row, saves a third of the vector instructions but shows only
+// in small calls.
 // ------------------------------------------------------------------------------------------
 template <typename T, int D, int NBC>
 __global__ void __launch_bounds__(256) k_comp2_fwd(
     const T* __restrict__ Q, const float* __restrict__ qc, const T* __restrict__ Ks, const T* __restrict__ Vs,
     const float* __restrict__ L, const float* __restrict__ s_mu, const float* __restrict__ s_k,
-    const T* __restrict__ s_v, const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_k,
-    const int32_t* __restrict__ aq, const int32_t* __restrict__ selc, int32_t* __restrict__ selb,
+    const T* __restrict__ s_v, const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q,
+    const int32_t* __restrict__ tile_off, const int32_t* __restrict__ off_k, const int32_t* __restrict__ selc, int32_t* __restrict__ selb,
     float* __restrict__ ff_acc, float* __restrict__ ff_ml, int h0, int N, int nb, int Bs, int Cq, int Ck, int r,
     int k2e, int Hq, int Hkv, float scale) {
   constexpr int NG = D / 64;
   const int hl = blockIdx.y, hq = h0 + hl;
   const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);
   const int l16 = threadIdx.x % 16;
-  // Workgroups go to the 8 XCDs round-robin by their linear id (the grid's x extent is a multiple of 256): an XCD
-  // takes runs of 32 consecutive workgroups of the bucketed order, so the queries of one cluster, which read the
-  // same summary rows, meet in one L2, while the late blocks (more work per query) still spread over all XCDs.
-  const int sq = blockIdx.x / 8;
-  const int wg = ((sq / 32) * 8 + blockIdx.x % 8) * 32 + sq % 32;
-  const int pos = Bs + wg * 16 + threadIdx.x / 16;  // bucketed order is block-major: block 0 comes first
-  if (pos >= N) return;
-  const int n = perm_q[(size_t)hq * N + pos];
+  const int idx = far_index();
+  if (idx >= N - Bs) return;
+  const FarQuery fq = far_query(tile_off + (size_t)hq * nb * (Cq + 1), off_q + (size_t)hq * ((size_t)nb * Cq + 1), idx, nb, Cq);
+  const int n = perm_q[(size_t)hq * N + fq.pos];
   const size_t qn = (size_t)hq * N + n;
-  const int b = n / Bs, NBm = nb - 1;
-  const int i = aq[qn];
+  const int b = fq.b, i = fq.i, NBm = nb - 1;
   const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
   float qt[NG][4];
 #pragma unroll
@@ -1309,7 +1321,7 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
     qt[x][0] = scale * (q4[0] - c4.x); qt[x][1] = scale * (q4[1] - c4.y);
     qt[x][2] = scale * (q4[2] - c4.z); qt[x][3] = scale * (q4[3] - c4.w);
   }
-  // the four queries of a wave are neighbours in the block-major order: the largest b among them (wave-uniform)
+  // the four queries of a wave are neighbours, mostly of one block: the largest b among them (wave-uniform)
   // bounds the block loops, so a wave of block-1 queries handles one summary row per cluster, not eight
   // (the bound is a template constant of the loop body below: one straight-line body per value, loads batched)
   int bwv = b;
@@ -1321,16 +1333,23 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
   for (int x = 0; x < NG; ++x)
 #pragma unroll
     for (int t = 0; t < 4; ++t) o[x][t] = 0.f;
-  auto add = [&](float lg, const float (&v)[NG][4]) {  // one more (logit, value row) into the running state
+  const int u8 = l16 & 7;  // the key block (of eight) whose scalars this lane has; its share of l is theirs
+  [[maybe_unused]] auto add = [&](float lg, const float (&v)[NG][4]) {  // one more (logit, value row) into the running state
     const float mn = fmaxf(m, lg);
     const float a = __expf(m - mn), p = __expf(lg - mn);
-    l = l * a + p;
+    l = l * a + (u8 == 0 ? p : 0.f);
     m = mn;
 #pragma unroll
     for (int x = 0; x < NG; ++x)
 #pragma unroll
       for (int t = 0; t < 4; ++t) o[x][t] = o[x][t] * a + p * v[x][t];
   };
+  // places in the head's summaries, in units of the lane's share of a row (16 bytes of s_k); 32 bits hold them
+  using F4 = Frag<T, 4>;
+  const uint32_t cells = (uint32_t)Cq * Ck, stride = cells * (D / 4);
+  const float* kbase = s_k + (size_t)hl * NBm * cells * D;
+  const T* vbase = s_v + (size_t)hl * NBm * cells * D;
+  const float* mubase = s_mu + (size_t)hl * NBm * cells;
   int next = selc[qn * r];  // a retrieved cluster is read a step ahead of its rows: one round trip per cluster
   auto run = [&](auto bw_c) {
   constexpr int bw = decltype(bw_c)::value;
@@ -1338,81 +1357,97 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
     const int j = next;
     next = selc[qn * r + (t + 1 < r ? t + 1 : t)];
     if (j < 0) continue;
+    const uint32_t cell0 = (uint32_t)i * Ck + j, at = cell0 * (D / 4) + l16;
     // scores of the preceding blocks, 8 at a time: every load of a chunk is in flight together (with at
     // most 8 preceding blocks the value rows ride along, one round trip per retrieved cluster)
-    float sc2[8 * NBC];
+    float sc[NBC];  // of block 8 c + u8
+    typename F4::raw vr[8][NG];
+    auto load_values = [&](int c0) {
+      uint32_t pl = at + (uint32_t)min(c0, b - 1) * stride;
 #pragma unroll
-    for (int bp = 0; bp < 8 * NBC; ++bp) sc2[bp] = MUSE_NEG_INF;
-    float vr[8][NG][4];
+      for (int u = 0; u < 8; ++u) {
+        if (c0 + u >= bw) break;
+        if (u > 0 && c0 + u < b) pl += stride;
 #pragma unroll
-    for (int c0 = 0; c0 < 8 * NBC; c0 += 8) {
+        for (int x = 0; x < NG; ++x) vr[u][x] = F4::ld(vbase + (size_t)pl * 4, 64 * x);
+      }
+    };
+#pragma unroll
+    for (int c = 0; c < NBC; ++c) {
+      sc[c] = MUSE_NEG_INF;
+      const int c0 = 8 * c;
       if (c0 >= bw) break;
-      float mu[8], part[8];
+      float part[8];
       float4 kr[8][NG];
+      const float mu = mubase[cell0 + (uint32_t)min(c0 + u8, b - 1) * cells];
+      uint32_t pl = at + (uint32_t)min(c0, b - 1) * stride;
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (c0 + u >= bw) break;
-        const int bp = c0 + u < b ? c0 + u : b - 1;
-        const size_t cell = (((size_t)hl * NBm + bp) * Cq + i) * Ck + j;
-        mu[u] = s_mu[cell];
+        if (u > 0 && c0 + u < b) pl += stride;  // past the last preceding block: that one again
+#pragma unroll
+        for (int x = 0; x < NG; ++x) kr[u][x] = *reinterpret_cast<const float4*>(kbase + (size_t)pl * 4 + 64 * x);
+      }
+      if (NBC == 1) load_values(0);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        part[u] = 0.f;
+        if (c0 + u >= bw) continue;
 #pragma unroll
         for (int x = 0; x < NG; ++x) {
-          kr[u][x] = *reinterpret_cast<const float4*>(s_k + cell * D + 64 * x + 4 * l16);
-          if (NBC == 1) ld4(s_v, cell * D + 64 * x + 4 * l16, vr[u][x]);
+          part[u] = fmaf(qt[x][0], kr[u][x].x, part[u]); part[u] = fmaf(qt[x][1], kr[u][x].y, part[u]);
+          part[u] = fmaf(qt[x][2], kr[u][x].z, part[u]); part[u] = fmaf(qt[x][3], kr[u][x].w, part[u]);
         }
       }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        float pa = 0.f;
-#pragma unroll
-        for (int x = 0; x < NG; ++x) {
-          pa = fmaf(qt[x][0], kr[u][x].x, pa); pa = fmaf(qt[x][1], kr[u][x].y, pa);
-          pa = fmaf(qt[x][2], kr[u][x].z, pa); pa = fmaf(qt[x][3], kr[u][x].w, pa);
-        }
-        part[u] = pa;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        part[u] = group_sum<16>(part[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        if (c0 + u < b && mu[u] > MUSE_NEG_INF) sc2[c0 + u] = part[u] + mu[u];
-      }
+      const float sum = sums_to_lanes(part);
+      if (c0 + u8 < b && mu > MUSE_NEG_INF) sc[c] = sum + mu;
     }
     unsigned selbits = 0;
-    for (int u = 0; u < k2e; ++u) {
-      float best = MUSE_NEG_INF;
-      int bi = -1;
+    float cand[NBC];
 #pragma unroll
-      for (int bp = 0; bp < 8 * NBC; ++bp)
-        if (!((selbits >> bp) & 1u) && sc2[bp] > best) { best = sc2[bp]; bi = bp; }
+    for (int c = 0; c < NBC; ++c) cand[c] = sc[c];
+    for (int u = 0; u < k2e; ++u) {
+      float best = cand[0];
+      if (NBC > 1) best = fmaxf(best, cand[NBC - 1]);
+      best = max_of_8(best);
+      unsigned at_best = lanes_of_8(cand[0] == best);
+      if (NBC > 1) at_best |= lanes_of_8(cand[NBC - 1] == best) << 8;
+      const int bi = best > MUSE_NEG_INF ? __ffs((int)at_best) - 1 : -1;
       if (bi >= 0) selbits |= 1u << bi;
+#pragma unroll
+      for (int c = 0; c < NBC; ++c)
+        if (8 * c + u8 == bi) cand[c] = MUSE_NEG_INF;
       if (l16 == 0) selb[(qn * r + t) * k2e + u] = bi;
     }
     // component 2: value summaries of the blocks that are not retrieved
+    float mn = m;
 #pragma unroll
-    for (int c0 = 0; c0 < 8 * NBC; c0 += 8) {
-      if (c0 >= bw) break;
-      if (NBC > 1) {
+    for (int c = 0; c < NBC; ++c) {
+      if (!(sc[c] > MUSE_NEG_INF) || ((selbits >> (8 * c + u8)) & 1u)) sc[c] = MUSE_NEG_INF;
+      mn = fmaxf(mn, sc[c]);
+    }
+    mn = max_of_8(mn);
+    const float ref = mn == MUSE_NEG_INF ? 0.f : mn, alpha = __expf(m - ref);
+    m = mn;
+    l *= alpha;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (c0 + u >= bw) break;
-          const int bp = c0 + u < b ? c0 + u : b - 1;
-          const size_t cell = (((size_t)hl * NBm + bp) * Cq + i) * Ck + j;
+    for (int x = 0; x < NG; ++x)
 #pragma unroll
-          for (int x = 0; x < NG; ++x) ld4(s_v, cell * D + 64 * x + 4 * l16, vr[u][x]);
-        }
-      }
+      for (int e = 0; e < 4; ++e) o[x][e] *= alpha;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        if (!(sc2[c0 + u] > MUSE_NEG_INF) || ((selbits >> (c0 + u)) & 1u)) continue;
-        add(sc2[c0 + u], vr[u]);
-      }
+    for (int c = 0; c < NBC; ++c) {
+      if (8 * c >= bw) break;
+      if (NBC > 1) load_values(8 * c);
+      const float p = __expf(sc[c] - ref);
+      const unsigned used = lanes_of_8(sc[c] > MUSE_NEG_INF);
+      l += p;
+      each_lane<(bw < 8 ? bw : 8)>(p, [&](int u, float pu) {
+        if (!((used >> u) & 1u)) return;
+#pragma unroll
+        for (int x = 0; x < NG; ++x)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[x][e] = fmaf(pu, F4::get(vr[u][x], e), o[x][e]);
+      });
     }
     if (sizeof(T) == 4) {  // component 3: the keys of the retrieved (cluster, block) pairs, with the full query
       for (int bp = 0; bp < b; ++bp) {
@@ -1463,6 +1498,7 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
   } else {
     run(std::integral_constant<int, 8 * NBC>{});
   }
+  l = sum_of_8(l);
   if (!(l > 0.f)) return;
   // merge into the far-field state left by the tile kernel
   float fm = ff_ml[qn * 2], fl = ff_ml[qn * 2 + 1];
@@ -1609,7 +1645,7 @@ int muse_ff_prepare(const MuseDims& d, const T* K, const T* V, const int32_t* aq
   dim3 g((unsigned)(((size_t)N * CPR + 255) / 256), HK);
   { MuseProf prof_("k_gather_rows", st); hipLaunchKernelGGL(k_gather_rows<T>, g, dim3(256), 0, st, K, w.perm_k, (T*)w.Ks, N, D); }
   { MuseProf prof_("k_gather_rows", st); hipLaunchKernelGGL(k_gather_rows<T>, g, dim3(256), 0, st, V, w.perm_k, (T*)w.Vs, N, D); }
-  { MuseProf prof_("k_tile_schedule", st); hipLaunchKernelGGL(k_tile_schedule, dim3((HQ * d.nb + 63) / 64), dim3(64), 0, st, w.off_q, w.tile_off, HQ, d.nb, d.Cq); }
+  { MuseProf prof_("k_tile_schedule", st); hipLaunchKernelGGL(k_tile_schedule, dim3(HQ * d.nb), dim3(64), 0, st, w.off_q, w.tile_off, d.nb, d.Cq); }
   if constexpr (sizeof(T) == 2) {
     MuseProf prof_("k_key_norm_max", st);
     float* part = w.knorm + HK;  // [HK][kNormParts]
@@ -1713,14 +1749,14 @@ void launch_ff_fwd_r(const MuseDims& d, const T* Q, const float* qc, const int32
   else launch_ff_fwd<T, D, 32>(d, Q, qc, w, selc, h0, hn, st);
   if (d.r > 0) {
     (void)muse_ff_block_summaries<T>(d, selc, w, h0, hn, st);
-    dim3 g(((d.N - d.Bs + 15) / 16 + 255) / 256 * 256, hn);  // a multiple of 256 (see the kernel)
+    const dim3 g = far_grid(d, hn);
     if (d.nb <= 9)
       { MuseProf prof_("k_comp2_fwd", st); hipLaunchKernelGGL((k_comp2_fwd<T, D, 1>), g, dim3(256), 0, st, Q, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.s_mu, w.s_k,
-                         (const T*)w.s_v, w.perm_q, w.off_k, aq, selc, selb, w.ff_acc, w.ff_ml, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r,
+                         (const T*)w.s_v, w.perm_q, w.off_q, w.tile_off, w.off_k, selc, selb, w.ff_acc, w.ff_ml, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r,
                          d.k2e, d.Hq, d.Hkv, d.scale); }
     else
       { MuseProf prof_("k_comp2_fwd", st); hipLaunchKernelGGL((k_comp2_fwd<T, D, 2>), g, dim3(256), 0, st, Q, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.s_mu, w.s_k,
-                         (const T*)w.s_v, w.perm_q, w.off_k, aq, selc, selb, w.ff_acc, w.ff_ml, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r,
+                         (const T*)w.s_v, w.perm_q, w.off_q, w.tile_off, w.off_k, selc, selb, w.ff_acc, w.ff_ml, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r,
                          d.k2e, d.Hq, d.Hkv, d.scale); }
   }
 }

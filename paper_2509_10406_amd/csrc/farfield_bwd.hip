@@ -250,36 +250,33 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 }
 
 // ------------------------------------------------------------------------------------------
-// dQ of component 2, per query (16 lanes, dims 64 x + 4 l16 + t, bucketed order, as in the forward): for every
+// dQ of component 2, per query (16 lanes, dims 64 x + 4 l16 + t, cluster by cluster, as in the forward): for every
 // retrieved cluster, the summaries of the preceding blocks that were NOT retrieved contribute  dl k-bar  with
 // dl = p (dO.v-bar - delta),  p = exp(q~.k-bar + mu-bar - LSE).  The retrieval's share is added here too: bf16 inputs
 // have per-pair dq partials, fp32 inputs walk the retrieved keys, kKeys of them requested together.  The sum is added to
-// the row the tile kernel wrote.  (fp32 inputs had both in the tile kernel, a lane pair per query and a key per round trip:
-// 384 us at 4 heads of 8k, r = 4, against 44 + 170 for the two kernels now.)
+// the row the tile kernel wrote.  us, with the queries block by block and every lane summing every block's product / now: 4510
+// / 4060 at 32 heads of 32k with D = 128, 1245 / 1190 at 16 heads of 64k, 1100 / 1045 with 128 x 128 clusters, 109 / 75 at 12 heads of
+// 6k, 172 / 136 at 4 fp32 heads of 8k.  (fp32 inputs had both in the tile kernel, a lane pair per query and a key per round trip:
+// 384 us at 4 heads of 8k, r = 4, against 44 + 136 for the two kernels now.)
 // ------------------------------------------------------------------------------------------
 template <typename T, int D, int NBC>
 __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
     const T* __restrict__ Q, const T* __restrict__ dO, const float* __restrict__ qc, const T* __restrict__ Ks,
     const T* __restrict__ Vs, const float* __restrict__ L, const int32_t* __restrict__ off_k,
     const float* __restrict__ s_mu, const float* __restrict__ s_k, const T* __restrict__ s_v,
-    const int32_t* __restrict__ perm_q, const int32_t* __restrict__ aq, const float* __restrict__ LSE,
-    const float* __restrict__ delta, const int32_t* __restrict__ slotinfo, const float* __restrict__ dqpart,
+    const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q, const int32_t* __restrict__ tile_off,
+    const float* __restrict__ LSE, const float* __restrict__ delta, const int32_t* __restrict__ slotinfo, const float* __restrict__ dqpart,
     float* __restrict__ dQ, int h0, int N, int nb, int Bs, int Cq, int Ck, int r, int k2e, int Hq, int Hkv, float scale) {
   constexpr int NG = D / 64;
   constexpr bool kF32 = sizeof(T) == 4;
   const int hl = blockIdx.y, hq = h0 + hl;
   const int l16 = threadIdx.x % 16;
-  // Workgroups go to the 8 XCDs round-robin by their linear id (the grid's x extent is a multiple of 256): an XCD
-  // takes runs of 32 consecutive workgroups of the bucketed order, so the queries of one cluster, which read the
-  // same summary rows, meet in one L2, while the late blocks (more work per query) still spread over all XCDs.
-  const int sq = blockIdx.x / 8;
-  const int wg = ((sq / 32) * 8 + blockIdx.x % 8) * 32 + sq % 32;
-  const int pos = Bs + wg * 16 + threadIdx.x / 16;  // bucketed order is block-major: block 0 comes first
-  if (pos >= N) return;
-  const int n = perm_q[(size_t)hq * N + pos];
+  const int idx = far_index();
+  if (idx >= N - Bs) return;
+  const FarQuery fq = far_query(tile_off + (size_t)hq * nb * (Cq + 1), off_q + (size_t)hq * ((size_t)nb * Cq + 1), idx, nb, Cq);
+  const int pos = fq.pos, n = perm_q[(size_t)hq * N + pos];
   const size_t qn = (size_t)hq * N + n;
-  const int b = pos / Bs, NBm = nb - 1;
-  const int i = aq[qn];
+  const int b = fq.b, i = fq.i, NBm = nb - 1;
   const float lse = LSE[qn], dl = delta[qn];
   float qt[NG][4], gt[NG][4], dq[NG][4];
 #pragma unroll
@@ -302,13 +299,20 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
   float4 oldq[NG];
 #pragma unroll
   for (int x = 0; x < NG; ++x) oldq[x] = *reinterpret_cast<const float4*>(dQ + qn * D + 64 * x + 4 * l16);
-  // the four queries of a wave are neighbours in the block-major order: the largest b among them (wave-uniform)
+  // the four queries of a wave are neighbours, mostly of one block: the largest b among them (wave-uniform)
   // bounds the block loops
   // (the bound is a template constant of the loop body below: one straight-line body per value, loads batched)
   int bwv = b;
   bwv = max(bwv, __shfl_xor(bwv, 16, 64));
   bwv = max(bwv, __shfl_xor(bwv, 32, 64));
   bwv = __builtin_amdgcn_readfirstlane(bwv);
+  // places in the head's summaries, in units of the lane's share of a row (16 bytes of s_k); 32 bits hold them
+  using F4 = Frag<T, 4>;
+  const int u8 = l16 & 7;  // the key block (of eight) whose scalars this lane has
+  const uint32_t cells = (uint32_t)Cq * Ck, stride = cells * (D / 4);
+  const float* kbase = s_k + (size_t)hl * NBm * cells * D;
+  const T* vbase = s_v + (size_t)hl * NBm * cells * D;
+  const float* mubase = s_mu + (size_t)hl * NBm * cells;
   auto run = [&](auto bw_c) {
   constexpr int bw = decltype(bw_c)::value;
   int next = si[0];  // a slot is read a step ahead of its rows: one round trip per slot
@@ -359,60 +363,53 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
         }
       }
     }
-    if (NBC == 1 && ((selbits + 1u) & ((1u << b) - 1u)) == 0u) continue;  // every preceding block is retrieved
+    const unsigned used = ((1u << b) - 1u) & ~selbits;
+    if (used == 0u) continue;  // every preceding block is retrieved
+    const uint32_t cell0 = (uint32_t)i * Ck + j, at = cell0 * (D / 4) + l16;
 #pragma unroll
     for (int c0 = 0; c0 < 8 * NBC; c0 += 8) {
       if (c0 >= bw) break;
-      float mu[8], part[8], dpp[8];
+      float part[8], dpp[8];
       float4 kr[8][NG];
-      float vr[8][NG][4];
+      typename F4::raw vr[8][NG];
+      const float mu = mubase[cell0 + (uint32_t)min(c0 + u8, b - 1) * cells];
+      // a retrieved block's rows are not used: rows that are requested anyway, instead of its own (the rows
+      // come from the L2, whose rate is half of what bounds this kernel)
+      uint32_t pl = at + (uint32_t)(c0 == 0 ? ((used & 1u) || b == 1 ? 0 : 1) : min(c0, b - 1)) * stride;
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (c0 + u >= bw) break;
-        int bp = c0 + u < b ? c0 + u : b - 1;
-        // a retrieved block's rows are not used: the neighbour's, requested anyway, instead of rows of their own (the rows
-        // come from the L2, whose rate is what bounds this kernel)
-        if ((selbits >> bp) & 1u) bp = bp > 0 ? bp - 1 : b > 1 ? 1 : 0;
-        const size_t cell = (((size_t)hl * NBm + bp) * Cq + i) * Ck + j;
-        mu[u] = s_mu[cell];
+        if (u > 0 && ((used >> (c0 + u)) & 1u)) pl = at + (uint32_t)(c0 + u) * stride;
 #pragma unroll
         for (int x = 0; x < NG; ++x) {
-          kr[u][x] = *reinterpret_cast<const float4*>(s_k + cell * D + 64 * x + 4 * l16);
-          ld4(s_v, cell * D + 64 * x + 4 * l16, vr[u][x]);
+          kr[u][x] = *reinterpret_cast<const float4*>(kbase + (size_t)pl * 4 + 64 * x);
+          vr[u][x] = F4::ld(vbase + (size_t)pl * 4, 64 * x);
         }
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        float pa = 0.f, pd = 0.f;
+        part[u] = dpp[u] = 0.f;
+        if (c0 + u >= bw) continue;
 #pragma unroll
         for (int x = 0; x < NG; ++x) {
-          pa = fmaf(qt[x][0], kr[u][x].x, pa); pa = fmaf(qt[x][1], kr[u][x].y, pa);
-          pa = fmaf(qt[x][2], kr[u][x].z, pa); pa = fmaf(qt[x][3], kr[u][x].w, pa);
-          pd = fmaf(gt[x][0], vr[u][x][0], pd); pd = fmaf(gt[x][1], vr[u][x][1], pd);
-          pd = fmaf(gt[x][2], vr[u][x][2], pd); pd = fmaf(gt[x][3], vr[u][x][3], pd);
+          part[u] = fmaf(qt[x][0], kr[u][x].x, part[u]); part[u] = fmaf(qt[x][1], kr[u][x].y, part[u]);
+          part[u] = fmaf(qt[x][2], kr[u][x].z, part[u]); part[u] = fmaf(qt[x][3], kr[u][x].w, part[u]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dpp[u] = fmaf(gt[x][e], F4::get(vr[u][x], e), dpp[u]);
         }
-        part[u] = pa; dpp[u] = pd;
       }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        part[u] = group_sum<16>(part[u]);
-        dpp[u] = group_sum<16>(dpp[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        const bool use = c0 + u < b && mu[u] > MUSE_NEG_INF && !((selbits >> (c0 + u)) & 1u);
-        if (kF32 && !use) continue;
-        const float p = use ? __expf(part[u] + mu[u] - lse) : 0.f;
-        const float dlg = p * (dpp[u] - dl);
+      const float sum = sums_to_lanes(part), dp = sums_to_lanes(dpp);
+      const bool use = mu > MUSE_NEG_INF && ((used >> (c0 + u8)) & 1u);
+      const float dlg = use ? __expf(sum + mu - lse) * (dp - dl) : 0.f;
+      [[maybe_unused]] const unsigned uses = kF32 ? lanes_of_8(use) : 0u;
+      each_lane<(bw < 8 ? bw : 8)>(dlg, [&](int u, float du) {
+        if (kF32 && !((uses >> u) & 1u)) return;
 #pragma unroll
         for (int x = 0; x < NG; ++x) {
-          dq[x][0] = fmaf(dlg, kr[u][x].x, dq[x][0]); dq[x][1] = fmaf(dlg, kr[u][x].y, dq[x][1]);
-          dq[x][2] = fmaf(dlg, kr[u][x].z, dq[x][2]); dq[x][3] = fmaf(dlg, kr[u][x].w, dq[x][3]);
+          dq[x][0] = fmaf(du, kr[u][x].x, dq[x][0]); dq[x][1] = fmaf(du, kr[u][x].y, dq[x][1]);
+          dq[x][2] = fmaf(du, kr[u][x].z, dq[x][2]); dq[x][3] = fmaf(du, kr[u][x].w, dq[x][3]);
         }
-      }
+      });
     }
   }
   };
@@ -802,11 +799,11 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
   { MuseProf prof_("k_ff_bwd_dq", st); hipLaunchKernelGGL((k_ff_bwd_dq<T, D>), gt, dim3(64), 0, st, Q, dO, qc, w.A_mu, w.A_k, (const T*)w.A_v, (const bf16_t*)w.A_kb,
                      w.perm_q, w.off_q, w.tile_off, LSE, w.delta, w.selmask, w.dQff, h0, d.N, d.nb, d.Cq, d.Ck, d.scale); }
   if (d.r > 0) {
-    dim3 g2(((d.N - d.Bs + 15) / 16 + 255) / 256 * 256, hn);  // a multiple of 256 (see the kernel)
+    const dim3 g2 = far_grid(d, hn);
     auto go = [&](auto* kernel) {
       MuseProf prof_("k_comp2_bwd_dq", st);
       hipLaunchKernelGGL(kernel, g2, dim3(256), 0, st, Q, dO, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.s_mu, w.s_k, (const T*)w.s_v,
-                         w.perm_q, aq, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, d.scale);
+                         w.perm_q, w.off_q, w.tile_off, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, d.scale);
     };
     if (d.nb <= 9) go(k_comp2_bwd_dq<T, D, 1>);
     else go(k_comp2_bwd_dq<T, D, 2>);

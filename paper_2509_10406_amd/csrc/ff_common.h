@@ -10,6 +10,8 @@
 //   "Column pattern": A[m][k] = X[k][m] read as X[k0 + 8g + 4(l/32) + t][m0 + l%32] (coalesced over
 //   lanes), pairing with a B operand taken straight from an accumulator (its rows are 8g+4h+t).
 #pragma once
+#include <utility>
+
 #include "common.h"
 
 __device__ __forceinline__ f32x16_t mfma32(float a, float b, f32x16_t c) {
@@ -180,6 +182,86 @@ __device__ __forceinline__ bf16x8_t ld_tr8(const bf16_t* row, int r0, int half) 
   return *reinterpret_cast<bf16x8_t*>(&v);
 }
 
+// The queries of the kernels that read the retrieved chains' summaries per query (k_comp2_fwd, k_comp2_bwd_dq): 16 lanes per
+// query, in order of (cluster, block, position), every XCD (workgroups go to them round-robin) a contiguous eighth of them: the
+// queries of a cluster, which read the same rows whatever their block, meet in one L2 at one time.
+struct FarQuery {
+  int i, b, pos;  // cluster, block, bucketed position
+};
+__device__ __forceinline__ int far_index() {
+  return (int)((blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8) * 16 + threadIdx.x / 16);
+}
+// first[i] = number of queries of clusters < i in the blocks >= 1, oq the head's segment table; idx < first[Cq].  A 16-lane group
+// calls it with its own idx: 16 entries per round trip.
+__device__ __forceinline__ FarQuery far_query(const int32_t* __restrict__ first, const int32_t* __restrict__ oq, int idx, int nb, int Cq) {
+  const int l16 = threadIdx.x % 16, sh = threadIdx.x % 64 / 16 * 16;
+  auto leading = [&](bool x) { return __popc((unsigned)(__ballot(x) >> sh) & 0xffffu); };
+  FarQuery q;
+  q.i = 0;
+  int base = 0;  // first[i]
+  for (int step = Cq > 256 ? 256 : Cq > 16 ? 16 : 1; step >= 1; step /= 16) {
+    const int at = q.i + l16 * step, v = at < Cq ? first[at] : 0x7fffffff;
+    const int k = leading(v <= idx) - 1;
+    base = __shfl(v, k, 16);
+    q.i += k * step;
+  }
+  const int b = l16 < nb ? l16 : 0;  // lane b: block b
+  const int lo = oq[b * Cq + q.i], cnt = l16 >= 1 && l16 < nb ? oq[b * Cq + q.i + 1] - lo : 0;
+  int incl = cnt;
+#pragma unroll
+  for (int d = 1; d < 16; d <<= 1) {
+    const int v = __shfl_up(incl, d, 16);
+    if (l16 >= d) incl += v;
+  }
+  const int rest = idx - base;
+  q.b = leading(incl <= rest);
+  q.pos = __shfl(lo - (incl - cnt), q.b, 16) + rest;
+  return q;
+}
+
+// What a 16-lane group does with one value per key block, eight of them at a time: the dims' partial sums of all eight meet in
+// the lane of the block (value u in lanes u and u + 8; three exchanges that halve the values and one addition, where a sum for
+// every lane takes four for each value), the scalars of a block are worked out there once, and go back by a broadcast.
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float xor4_of(float v) {  // row_shl:4 into the even quads, row_shr:4 into the odd ones
+  const int x = __builtin_bit_cast(int, v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0x5, false), x, 0x114, 0xf, 0xa, false));
+}
+__device__ __forceinline__ float sums_to_lanes(const float (&v)[8]) {  // added up in the order of group_sum
+  const bool l4 = threadIdx.x & 4, l2 = threadIdx.x & 2, l1 = threadIdx.x & 1;
+  float t[4], w[2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) t[k] = (l1 ? v[2 * k + 1] : v[2 * k]) + dpp_of<0xB1>(l1 ? v[2 * k] : v[2 * k + 1]);  // quad_perm [1,0,3,2]
+#pragma unroll
+  for (int k = 0; k < 2; ++k) w[k] = (l2 ? t[2 * k + 1] : t[2 * k]) + dpp_of<0x4E>(l2 ? t[2 * k] : t[2 * k + 1]);  // quad_perm [2,3,0,1]
+  const float x = (l4 ? w[1] : w[0]) + xor4_of(l4 ? w[0] : w[1]);
+  return x + dpp_of<0x128>(x);  // row_ror:8
+}
+__device__ __forceinline__ float max_of_8(float x) {
+  x = fmaxf(x, dpp_of<0x141>(x));
+  x = fmaxf(x, dpp_of<0xB1>(x));
+  return fmaxf(x, dpp_of<0x4E>(x));
+}
+__device__ __forceinline__ float sum_of_8(float x) {
+  x += dpp_of<0x141>(x);
+  x += dpp_of<0xB1>(x);
+  return x + dpp_of<0x4E>(x);
+}
+// the lanes 0 .. 7 of the group where x holds
+__device__ __forceinline__ unsigned lanes_of_8(bool x) { return (unsigned)(__ballot(x) >> (threadIdx.x % 64 / 16 * 16)) & 0xffu; }
+// f(u, the value of lane u) for u < n; u is a constant
+template <int n, typename F, int... U>
+__device__ __forceinline__ void each_lane_(float x, F f, std::integer_sequence<int, U...>) {
+  (f(U, dpp_of<0x150 + U>(x)), ...);  // row_newbcast
+}
+template <int n, typename F>
+__device__ __forceinline__ void each_lane(float x, F f) {
+  each_lane_<n>(x, f, std::make_integer_sequence<int, n>());
+}
+
 constexpr int kMaxCk = 2304;  // key clusters a kernel can index in LDS
 static_assert(kMaxCk >= MUSE_MAX_CLUSTERS, "the host accepts more clusters than the kernels index");
 constexpr int kKeys = 4;      // retrieved keys that the per-query kernels of fp32 inputs request together
@@ -292,6 +374,8 @@ static inline size_t ff_segcnt_bytes(const MuseDims& d) {
 // bytes of the all-heads part / of one query head of the chunked part
 // x extent of the forward tile kernels' grid: the tiles of a (head, block) pair, rounded up to the 8 XCDs
 static inline size_t ff_tile_grid_x(const MuseDims& d) { return (size_t)(d.Bs / 32 + d.Cq + 1 + 7) / 8 * 8; }
+// the grid of far_index
+static inline dim3 far_grid(const MuseDims& d, int hn) { return dim3((unsigned)(((d.N - d.Bs + 15) / 16 + 7) / 8 * 8), hn); }
 static inline size_t ff_flag_bytes(const MuseDims& d) {
   return (size_t)d.B * d.Hq * (d.nb > 1 ? d.nb - 1 : 1) * ff_tile_grid_x(d) * 4;
 }
