@@ -9,59 +9,123 @@
 namespace {
 
 // The hit lists are built by a counting sort whose order is fixed by construction.  The queries with a far field
-// (positions Bs .. N-1) of every query head are cut into SEG slices of whole 64-query chunks; one workgroup owns a
-// (slice, head), walks its chunks in order and keeps one counter per pair in LDS.  Each of its kHitWaves waves
-// takes the pairs of one residue class (pair % kHitWaves), so a counter has one owner and the waves never wait
-// for each other.  For a chunk and a selection slot, the lanes that name the same pair are found by ballots (one
-// round per distinct pair of the wave's class among the 64 lanes) and ranked by lane, so a list is ascending in
-// (head of the group, position) without any atomic deciding an order.  Pass 1 (FILL = false) leaves the counts per (kv head, head of the group x slice, pair); k_pair_totals,
+// (positions Bs .. N-1) of every query head are cut into SEG slices of whole 64-query chunks, with one counter per pair in LDS.
+// Pass 1 (k_hit_counts) leaves the counts per (kv head, head of the group x slice, pair); k_pair_totals,
 // k_pair_scan and k_seg_offsets turn them into list starts (pair-major, then head of the group, then slice);
-// pass 2 (FILL = true) starts from those and writes the hits, with the slot index the pair has in the query's
-// exported selections.
-constexpr int kHitWaves = 8;
-template <bool FILL>
-__global__ void __launch_bounds__(64 * kHitWaves) k_hit_lists(const int32_t* __restrict__ selc, const int32_t* __restrict__ selb,
-                                                   int32_t* __restrict__ seg_cnt, const int32_t* __restrict__ seg_off,
-                                                   uint2* __restrict__ hits, size_t hit_cap, int N, int Bs, int Ck,
-                                                   int r, int k2e, int Hq, int Hkv, int npair, int SEG, int cps) {
-  extern __shared__ int cur[];  // per pair: hits counted so far (pass 1) / next list position (pass 2)
-  const int s = blockIdx.x, hq = blockIdx.y, lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-  const int G_ = Hq / Hkv, g = (hq % Hq) % G_;
-  const int hk = (hq / Hq) * Hkv + (hq % Hq) / G_;
-  const size_t sbase = ((size_t)hk * G_ * SEG + (size_t)g * SEG + s) * npair;
-  for (int p = threadIdx.x; p < npair; p += 64 * kHitWaves) cur[p] = FILL ? seg_off[sbase + p] : 0;
+// pass 2 (k_hit_lists) starts from those and writes the hits, with the slot index the pair has in the query's
+// exported selections: one wave walks a slice's chunks, and for a selection slot of a chunk the lanes that name the same pair are
+// found by ballots over the bits of its number and ranked by lane, so a list is ascending in (head of the group, chunk, slot,
+// position) without any atomic deciding an order.
+// us of the two passes, with eight waves per slice that shared the pairs and went through the distinct ones of a chunk one by
+// one, in both passes / now: 222 + 327 / 36 + 129 at 16 heads of 64k with 256 x 1024 clusters, 245 + 298 / 29 + 75 with 128 x 128, 440 +
+// 667 / 67 + 201 at 32 heads of 32k with 128 x 512 and r = 16, 17 + 28 / 7 + 12 at 12 heads of 6k.
+constexpr int kHitWaves = 8;   // of the workgroup that counts
+constexpr int kHitSlots = 8;   // selection slots requested together
+
+struct HitSlice {
+  int hq, hk, g, c0, c1;  // query head, its kv head and number in the group; chunks
+  size_t sbase;           // the slice's counters
+};
+__device__ __forceinline__ HitSlice hit_slice(int N, int Bs, int Hq, int Hkv, int npair, int SEG, int cps) {
+  HitSlice x;
+  const int G_ = Hq / Hkv, s = blockIdx.x, chunks = (N - Bs + 63) / 64;
+  x.hq = blockIdx.y;
+  x.g = (x.hq % Hq) % G_;
+  x.hk = (x.hq / Hq) * Hkv + (x.hq % Hq) / G_;
+  x.c0 = s * cps;
+  x.c1 = min((s + 1) * cps, chunks);
+  x.sbase = ((size_t)x.hk * G_ * SEG + (size_t)x.g * SEG + s) * npair;
+  return x;
+}
+// the pairs of slots s0 .. of a chunk's queries (slot s: retrieved cluster s / k2e, its block s % k2e), -1 where there is none
+// (selections are trusted inputs; one outside the table is dropped rather than indexed)
+__device__ __forceinline__ void load_pairs(int (&pair)[kHitSlots], const int32_t* __restrict__ selc, const int32_t* __restrict__ selb,
+                                           size_t qn, bool valid, int s0, int r, int k2e, int Ck, int npair) {
+  const int R2 = r * k2e;
+  int j[kHitSlots], bp[kHitSlots];
+#pragma unroll
+  for (int u = 0; u < kHitSlots; ++u) {
+    const int s = min(s0 + u, R2 - 1);
+    j[u] = selc[qn * r + s / k2e];
+    bp[u] = selb[qn * R2 + s];
+  }
+#pragma unroll
+  for (int u = 0; u < kHitSlots; ++u) {
+    const int p = bp[u] * Ck + j[u];
+    pair[u] = valid && s0 + u < R2 && j[u] >= 0 && j[u] < Ck && bp[u] >= 0 && bp[u] < 16 && p < npair ? p : -1;
+  }
+}
+
+__global__ void __launch_bounds__(64 * kHitWaves) k_hit_counts(const int32_t* __restrict__ selc, const int32_t* __restrict__ selb,
+                                                               int32_t* __restrict__ seg_cnt, int N, int Bs, int Ck, int r, int k2e,
+                                                               int Hq, int Hkv, int npair, int SEG, int cps) {
+  extern __shared__ int cur[];
+  const HitSlice sl = hit_slice(N, Bs, Hq, Hkv, npair, SEG, cps);
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  for (int p = threadIdx.x; p < npair; p += 64 * kHitWaves) cur[p] = 0;
   __syncthreads();
-  const int chunks = (N - Bs + 63) / 64;
-  const int c1 = (s + 1) * cps < chunks ? (s + 1) * cps : chunks;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  for (int c = s * cps; c < c1; ++c) {
+  for (int c = sl.c0 + wave; c < sl.c1; c += kHitWaves) {
     const int n = Bs + 64 * c + lane;
-    const bool valid = n < N;
-    const size_t qn = (size_t)hq * N + (valid ? n : N - 1);
-    for (int t = 0; t < r; ++t) {
-      const int j = valid ? selc[qn * r + t] : -1;
-      for (int u = 0; u < k2e; ++u) {
-        const int bp = j >= 0 ? selb[(qn * r + t) * k2e + u] : -1;
-        // (selections are trusted inputs; one outside the table is dropped rather than indexed)
-        const int pair = (bp >= 0 && j < Ck && bp * Ck + j < npair) ? bp * Ck + j : -1;
-        unsigned long long act = __ballot(pair >= 0 && pair % kHitWaves == wave);
-        while (act) {
-          const int src = __ffsll((long long)act) - 1;
-          const int pv = __builtin_amdgcn_readlane(pair, src);
-          const unsigned long long same = __ballot(pair == pv);
-          const int base = cur[pv];
-          if (FILL && pair == pv)
-            hits[(size_t)hk * hit_cap + base + __popcll(same & below)] =
-                make_uint2((uint32_t)n | ((uint32_t)g << 22), (uint32_t)(t * k2e + u));
-          if (lane == src) cur[pv] = base + __popcll(same);
-          act &= ~same;
-        }
-      }
+    const size_t qn = (size_t)sl.hq * N + min(n, N - 1);
+    for (int s0 = 0; s0 < r * k2e; s0 += kHitSlots) {
+      int pair[kHitSlots];
+      load_pairs(pair, selc, selb, qn, n < N, s0, r, k2e, Ck, npair);
+#pragma unroll
+      for (int u = 0; u < kHitSlots; ++u)
+        if (pair[u] >= 0) atomicAdd(&cur[pair[u]], 1);
     }
   }
-  if (!FILL) {
-    __syncthreads();
-    for (int p = threadIdx.x; p < npair; p += 64 * kHitWaves) seg_cnt[sbase + p] = cur[p];
+  __syncthreads();
+  for (int p = threadIdx.x; p < npair; p += 64 * kHitWaves) seg_cnt[sl.sbase + p] = cur[p];
+}
+
+__global__ void __launch_bounds__(64) k_hit_lists(const int32_t* __restrict__ selc, const int32_t* __restrict__ selb,
+                                                  const int32_t* __restrict__ seg_off, uint2* __restrict__ hits, size_t hit_cap, int N,
+                                                  int Bs, int Ck, int r, int k2e, int Hq, int Hkv, int npair, int SEG, int cps) {
+  extern __shared__ int cur[];  // per pair: next list position
+  const HitSlice sl = hit_slice(N, Bs, Hq, Hkv, npair, SEG, cps);
+  const int lane = threadIdx.x, bits = 32 - __clz(npair - 1 > 0 ? npair - 1 : 1);
+  const unsigned long long below = (1ull << lane) - 1ull;
+  for (int p0 = 0; p0 < npair; p0 += 64 * 8) {
+    int v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = seg_off[sl.sbase + min(p0 + 64 * u + lane, npair - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (p0 + 64 * u + lane < npair) cur[p0 + 64 * u + lane] = v[u];
+  }
+  wave_lds_fence();
+  uint2* out = hits + (size_t)sl.hk * hit_cap;
+  const int R2 = r * k2e, per = (R2 + kHitSlots - 1) / kHitSlots, total = (sl.c1 - sl.c0) * per;
+  int next[kHitSlots];
+  auto load = [&](int x) {  // the x-th group of slots of the slice
+    const int n = Bs + 64 * (sl.c0 + x / per) + lane;
+    load_pairs(next, selc, selb, (size_t)sl.hq * N + min(n, N - 1), n < N, x % per * kHitSlots, r, k2e, Ck, npair);
+  };
+  if (total > 0) load(0);
+  for (int x = 0; x < total; ++x) {
+    int pair[kHitSlots];
+#pragma unroll
+    for (int u = 0; u < kHitSlots; ++u) pair[u] = next[u];
+    if (x + 1 < total) load(x + 1);
+    const int n = Bs + 64 * (sl.c0 + x / per) + lane, s0 = x % per * kHitSlots;
+#pragma unroll
+    for (int u = 0; u < kHitSlots; ++u) {
+      const bool hit = pair[u] >= 0;
+      unsigned long long same = __ballot(hit);
+      if (same == 0ull) continue;
+      for (int bit = 0; bit < bits; ++bit) {
+        const bool one = (pair[u] >> bit) & 1;
+        const unsigned long long ones = __ballot(one);
+        same &= one ? ones : ~ones;
+      }
+      if (hit) {
+        const int base = cur[pair[u]], rank = __popcll(same & below), count = __popcll(same);
+        out[base + rank] = make_uint2((uint32_t)n | ((uint32_t)sl.g << 22), (uint32_t)(s0 + u));
+        if (rank == count - 1) cur[pair[u]] = base + count;
+      }
+      wave_lds_fence();
+    }
   }
 }
 
@@ -220,16 +284,16 @@ int muse_ff_build_inverse_index(const MuseDims& d, const int32_t* selc, const in
   static_assert((size_t)15 * MUSE_MAX_CLUSTERS * sizeof(int) <= 128 * 1024, "the pair counters of the largest accepted shape fit the LDS");
   static bool attr_set = false;
   if (!attr_set) {
-    MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_hit_lists<false>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
-    MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_hit_lists<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
+    MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_hit_counts, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
+    MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_hit_lists, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
     attr_set = true;
   }
   const dim3 g(SEG, HQ), gs((npair + 63) / 64, HK);
-  { MuseProf prof_("k_hit_lists", st); hipLaunchKernelGGL(k_hit_lists<false>, g, dim3(64 * kHitWaves), lds, st, selc, selb, w.seg_cnt, w.seg_off, w.hits, w.hit_cap, N, d.Bs, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, npair, SEG, cps); }
+  { MuseProf prof_("k_hit_counts", st); hipLaunchKernelGGL(k_hit_counts, g, dim3(64 * kHitWaves), lds, st, selc, selb, w.seg_cnt, N, d.Bs, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, npair, SEG, cps); }
   { MuseProf prof_("k_pair_totals", st); hipLaunchKernelGGL(k_pair_totals, gs, dim3(64 * kSegWaves), 0, st, w.seg_cnt, w.pair_cnt, npair, SEGT); }
   { MuseProf prof_("k_pair_scan", st); hipLaunchKernelGGL(k_pair_scan, dim3(HK), dim3(1024), 0, st, w.pair_cnt, w.pair_off, w.run_off, w.c3_off, npair, ff_c3_cut(d)); }
   { MuseProf prof_("k_seg_offsets", st); hipLaunchKernelGGL(k_seg_offsets, gs, dim3(64 * kSegWaves), 0, st, w.seg_cnt, w.pair_off, w.seg_off, npair, SEGT); }
-  { MuseProf prof_("k_hit_lists", st); hipLaunchKernelGGL(k_hit_lists<true>, g, dim3(64 * kHitWaves), lds, st, selc, selb, w.seg_cnt, w.seg_off, w.hits, w.hit_cap, N, d.Bs, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, npair, SEG, cps); }
+  { MuseProf prof_("k_hit_lists", st); hipLaunchKernelGGL(k_hit_lists, g, dim3(64), lds, st, selc, selb, w.seg_off, w.hits, w.hit_cap, N, d.Bs, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, npair, SEG, cps); }
   { MuseProf prof_("k_pair_items", st); hipLaunchKernelGGL(k_pair_items, dim3((npair + 255) / 256, HK), dim3(256), 0, st, w.pair_off, w.run_off, w.c3_off, w.run_map, w.c3_map, npair, w.run_cap, ff_c3_cut(d)); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
