@@ -1,0 +1,42 @@
+"""The small kernels around bf16 and fp32 attention: row sums dO . O and the casts of the gradients, where their wide forms give
+way to the narrow ones (an O or a result that does not start at a 16-byte boundary: the same values) and where their last
+workgroup has rows left over.  The row sums are checked through dQ of one block, against fp64."""
+import math
+
+import pytest
+import torch
+
+from paper_2509_10406_amd import binding as mb
+from tests.util import bf16_grad_bound
+
+pytestmark = pytest.mark.gpu
+
+
+def _offset(x):
+    """The same values one element behind a 16-byte boundary."""
+    y = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)[1:1 + x.numel()].view(x.shape)
+    y.copy_(x)
+    return y
+
+
+@pytest.mark.parametrize("dtype", [mb.BF16, mb.FP32])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,H", [(1, 1), (33, 3), (127, 1), (130, 5)])
+def test_row_sums_and_casts(N, H, D, dtype):
+    g = torch.Generator().manual_seed(N + D)
+    p = mb.Params(B=1, Hq=H, Hkv=H, N=N, D=D, dtype=dtype, grad_dtype=dtype)
+    Q, K, V, dO = (torch.randn(1, H, N, D, generator=g).to(p.torch_dtype).cuda() for _ in range(4))
+    O, LSE = mb.exact_attn_fwd(p, Q, K, V)
+    got = mb.exact_attn_bwd(p, Q, K, V, O, LSE, dO)
+    again = mb.exact_attn_bwd(p, Q, K, V, _offset(O), LSE, dO)
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    if dtype == mb.BF16:
+        out = tuple(_offset(torch.zeros_like(x)) for x in got)
+        mb.exact_attn_bwd(p, Q, K, V, O, LSE, dO, out=out)
+        assert all(torch.equal(a, b) for a, b in zip(got, out))
+    q, k, v, d = (x[0].cpu().double() for x in (Q, K, V, dO))
+    P = (q @ k.transpose(1, 2) / math.sqrt(D)).masked_fill(torch.ones(N, N, dtype=torch.bool).triu(1), -math.inf).softmax(-1)
+    dP = d @ v.transpose(1, 2)
+    want = (P * (dP - (P * dP).sum(-1, keepdim=True))) @ k / math.sqrt(D)
+    bound = bf16_grad_bound(float(want.abs().max())) if dtype == mb.BF16 else 1e-5 * max(1.0, float(want.abs().max()))
+    assert (got[0][0].cpu().double() - want).abs().max() <= bound
