@@ -64,9 +64,10 @@ __device__ __forceinline__ void mfma_acc(f32x16_t& acc, bf16x8_t a, bf16x8_t b) 
 // Queries past the block's end start at -inf: P is zero there.
 // Three buffers: in step i, tile i + 1 has to be complete at the barrier in the middle (A(i + 1) reads its rows in the second half),
 // behind that barrier nobody reads tile i - 1 any more and i + 2 goes there.
+template <typename OT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) k_flash_bwd_dkv_wide(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
-    const float* __restrict__ LSE, const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV, int N,
+    const float* __restrict__ LSE, const float* __restrict__ delta, OT* __restrict__ dK, OT* __restrict__ dV, int N,
     int Bs, int Hq, int Hkv, int nbatch, int chunk, float scale, float scale_log2e) {
   constexpr int D = 64, KS = D / 16, DT = D / 32, NB = 3, kTile = BN * D, kB = kTile * 2, LAG = 8, CPR = D / 8, NCH = BN * CPR / 256;
   __shared__ __attribute__((aligned(256))) bf16_t tiles[2][NB][kTile];  // Q, dO
@@ -296,8 +297,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
       for (int g = 0; g < 4; ++g) {
         const size_t o = (kh + mk) * D + 32 * t + 8 * g + 4 * half;
         const f32x16_t &a = dk[u][t], &c = dv[u][t];
-        *reinterpret_cast<float4*>(dK + o) = make_float4(scale * a[4 * g], scale * a[4 * g + 1], scale * a[4 * g + 2], scale * a[4 * g + 3]);
-        *reinterpret_cast<float4*>(dV + o) = make_float4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
+        const float k4[4] = {scale * a[4 * g], scale * a[4 * g + 1], scale * a[4 * g + 2], scale * a[4 * g + 3]};
+        const float v4[4] = {c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+        st4(dK, o, k4);
+        st4(dV, o, v4);
       }
   }
 }
@@ -309,9 +312,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 // At step T: P and dV of tile T, dP and dK of tile T - 1; rows of tile T + 1 are read, T + 2 is on its way, T + 3 is asked for
 // (behind the barrier that ends the reads of T - 2): five buffers.  Seeds come in chunks of 256 rows, four buffers: a chunk is
 // written at the first step of the chunk two before it, when nobody reads the one before that any more.
+template <typename OT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) k_flash_bwd_dkv128_wide(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
-    const float* __restrict__ LSE, const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV, int N,
+    const float* __restrict__ LSE, const float* __restrict__ delta, OT* __restrict__ dK, OT* __restrict__ dV, int N,
     int Bs, int Hq, int Hkv, int nbatch, int chunk, float scale, float scale_log2e) {
   constexpr int D = 128, KS = D / 16, DT = D / 32, BQ = 32, NB = 5, NS = 4, SC = 256, kTile = BQ * D, kB = kTile * 2, NM = 16, LAG = 6;
   __shared__ __attribute__((aligned(256))) bf16_t tiles[2][NB][kTile];       // Q, dO
@@ -575,7 +579,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   else work(std::integral_constant<int, 1>{});
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing is on its way into LDS that others may own soon
   acc_settle();
-  float* out = role ? dK : dV;
+  OT* out = role ? dK : dV;
   const float mul = role ? scale : 1.f;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -586,8 +590,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const f32x16_t& a = acc[u][t];
-        *reinterpret_cast<float4*>(out + (kh + mk) * D + 32 * t + 8 * g + 4 * half) =
-            make_float4(mul * a[4 * g], mul * a[4 * g + 1], mul * a[4 * g + 2], mul * a[4 * g + 3]);
+        const float r4[4] = {mul * a[4 * g], mul * a[4 * g + 1], mul * a[4 * g + 2], mul * a[4 * g + 3]};
+        st4(out, (kh + mk) * D + 32 * t + 8 * g + 4 * half, r4);
       }
   }
 }
@@ -596,10 +600,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 // in code of their own in front of the loop (behind it, the compiler spilled at D = 128).  Unit a is the later half of the queries:
 // in the first step, keys 32 .. 63 meet a alone, keys 0 .. 31 meet a and, masked, b.  Four buffers: the requests of step i for tile
 // i + 2 are only waited for in the middle of step i + 1.
-template <int D>
+template <int D, typename OT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) k_flash_bwd_dq_wide(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
-    const float* __restrict__ LSE, const float* __restrict__ delta, float* __restrict__ dQ, int N, int Bs, int Hq, int Hkv,
+    const float* __restrict__ LSE, const float* __restrict__ delta, OT* __restrict__ dQ, int N, int Bs, int Hq, int Hkv,
     int nbatch, int chunk, float scale, float scale_log2e) {
   constexpr int KS = D / 16, DT = D / 32, NM = 2 * KS + 2 * DT, LAG = NM / 3, CPR = D / 8, NCH = BN * CPR / 256;
   constexpr int NB = 4, kTile = BN * D, kB = kTile * 2;
@@ -785,8 +789,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const f32x16_t& a = dq[u][t];
-        *reinterpret_cast<float4*>(dQ + (qh + nq) * D + 32 * t + 8 * g + 4 * half) =
-            make_float4(scale * a[4 * g], scale * a[4 * g + 1], scale * a[4 * g + 2], scale * a[4 * g + 3]);
+        const float r4[4] = {scale * a[4 * g], scale * a[4 * g + 1], scale * a[4 * g + 2], scale * a[4 * g + 3]};
+        st4(dQ, (qh + nq) * D + 32 * t + 8 * g + 4 * half, r4);
       }
   }
 }
@@ -811,30 +815,39 @@ bool muse_attn_dq_wide(const MuseDims& d, int Bs) {
 }
 bool muse_attn_dkv_wide(const MuseDims& d, int Bs) { return d.D == 64 ? Bs > TR : Bs >= 2 * TR; }
 
+// the gradients may leave in bf16 (MuseDims::grads16): all of them come from the kernels of this file
+bool muse_attn_bwd_writes16(const MuseDims& d, int Bs) {
+  return d.dtype == MUSE_DTYPE_BF16 && muse_attn_dq_wide(d, Bs) && muse_attn_dkv_wide(d, Bs);
+}
+
 int muse_launch_attn_dq_wide(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
-                             const float* delta, float* dQacc, hipStream_t st) {
+                             const float* delta, void* dQ, hipStream_t st) {
   const int tiles = (Bs + TR - 1) / TR, groups = d.B * d.Hq * (d.N / Bs);
   MuseProf prof_("k_flash_bwd_dq", st);
-  auto go = [&](auto* kernel) {
+  auto go = [&](auto* kernel, auto* out) {
     hipLaunchKernelGGL(kernel, flash_grid_of(tiles, groups), dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V,
-                       (const bf16_t*)dO, LSE, delta, dQacc, d.N, Bs, d.Hq, d.Hkv, d.B, chunk_groups(Bs, d.D, groups), d.scale, d.scale * 1.4426950408889634f);
+                       (const bf16_t*)dO, LSE, delta, out, d.N, Bs, d.Hq, d.Hkv, d.B, chunk_groups(Bs, d.D, groups), d.scale, d.scale * 1.4426950408889634f);
   };
-  if (d.D == 64) go(k_flash_bwd_dq_wide<64>);
-  else go(k_flash_bwd_dq_wide<128>);
+  if (d.grads16) d.D == 64 ? go(k_flash_bwd_dq_wide<64, bf16_t>, (bf16_t*)dQ) : go(k_flash_bwd_dq_wide<128, bf16_t>, (bf16_t*)dQ);
+  else d.D == 64 ? go(k_flash_bwd_dq_wide<64, float>, (float*)dQ) : go(k_flash_bwd_dq_wide<128, float>, (float*)dQ);
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }
 
 int muse_launch_attn_dkv_wide(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
-                              const float* delta, float* dKacc, float* dVacc, hipStream_t st) {
+                              const float* delta, void* dK, void* dV, hipStream_t st) {
   const int tr = d.D == 64 ? TR : TR128, tiles = (Bs + tr - 1) / tr, groups = d.B * d.Hkv * (d.N / Bs);
   MuseProf prof_("k_flash_bwd_dkv", st);
-  auto go = [&](auto* kernel) {
+  auto go = [&](auto* kernel, auto* k, auto* v) {
     hipLaunchKernelGGL(kernel, flash_grid_of(tiles, groups), dim3(256), 0, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V,
-                       (const bf16_t*)dO, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, chunk_groups(Bs, d.D, groups), d.scale, d.scale * 1.4426950408889634f);
+                       (const bf16_t*)dO, LSE, delta, k, v, d.N, Bs, d.Hq, d.Hkv, d.B, chunk_groups(Bs, d.D, groups), d.scale, d.scale * 1.4426950408889634f);
   };
-  if (d.D == 64) go(k_flash_bwd_dkv_wide);
-  else go(k_flash_bwd_dkv128_wide);
+  auto as = [&](auto* k, auto* v) {
+    using OT = std::remove_pointer_t<decltype(k)>;
+    d.D == 64 ? go(k_flash_bwd_dkv_wide<OT>, k, v) : go(k_flash_bwd_dkv128_wide<OT>, k, v);
+  };
+  if (d.grads16) as((bf16_t*)dK, (bf16_t*)dV);
+  else as((float*)dK, (float*)dV);
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

@@ -723,9 +723,9 @@ int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* 
 bool muse_attn_dq_wide(const MuseDims& d, int Bs);
 bool muse_attn_dkv_wide(const MuseDims& d, int Bs);
 int muse_launch_attn_dq_wide(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
-                             const float* delta, float* dQacc, hipStream_t st);
+                             const float* delta, void* dQ, hipStream_t st);
 int muse_launch_attn_dkv_wide(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
-                              const float* delta, float* dKacc, float* dVacc, hipStream_t st);
+                              const float* delta, void* dK, void* dV, hipStream_t st);
 
 int muse_launch_attn_bwd_mfma(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V,
                               const void* dO, const float* LSE, const float* delta, float* dQacc,

@@ -175,6 +175,7 @@ struct MuseDims {
   bool streaming;       // MUSE_FLAG_STREAMING_KMEANS
   bool balanced;        // MUSE_FLAG_BALANCED_ASSIGN
   bool dipole;          // MUSE_FLAG_DIPOLE
+  bool grads16 = false; // attention's backward writes bf16 gradients (muse_attn_bwd_writes16), not fp32 sums
 };
 
 #define MUSE_HIP_CHECK(expr)                      \
@@ -242,6 +243,7 @@ int muse_launch_attn_fwd(const MuseDims& d, int Bs, const void* Q, const void* K
                          const float* ff, void* O, float* LSE, hipStream_t st);
 // delta [B,Hq,N] = dO . O
 int muse_launch_delta(const MuseDims& d, const void* O, const void* dO, float* delta, hipStream_t st);
+bool muse_attn_bwd_writes16(const MuseDims& d, int Bs);
 // dQacc [B,Hq,N,D], dKacc, dVacc [B,Hkv,N,D] fp32: overwritten with the gradients of this attention.
 int muse_launch_attn_bwd(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V,
                          const void* dO, const float* LSE, const float* delta, float* dQacc,

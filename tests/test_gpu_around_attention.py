@@ -19,6 +19,22 @@ def _offset(x):
     return y
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_bf16_gradients_of_long_blocks(D):
+    # written by the attention kernels themselves (odd results: cast from fp32): the fp32 gradients, rounded once
+    g = torch.Generator().manual_seed(D)
+    H, Hkv, N = 34, 17, 1100
+    Q, K, V, dO = (torch.randn(1, h, N, D, generator=g).bfloat16().cuda() for h in (H, Hkv, Hkv, H))
+    p = mb.Params(B=1, Hq=H, Hkv=Hkv, N=N, D=D)
+    p16 = mb.Params(B=1, Hq=H, Hkv=Hkv, N=N, D=D, grad_dtype=mb.BF16)
+    O, LSE = mb.exact_attn_fwd(p, Q, K, V)
+    want = tuple(x.bfloat16() for x in mb.exact_attn_bwd(p, Q, K, V, O, LSE, dO))
+    assert all(torch.equal(a, b) for a, b in zip(mb.exact_attn_bwd(p16, Q, K, V, O, LSE, dO), want))
+    out = tuple(_offset(torch.zeros_like(x)) for x in want)
+    mb.exact_attn_bwd(p16, Q, K, V, O, LSE, dO, out=out)
+    assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
 @pytest.mark.parametrize("dtype", [mb.BF16, mb.FP32])
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("N,H", [(1, 1), (33, 3), (127, 1), (130, 5)])
