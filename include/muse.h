@@ -196,7 +196,10 @@ int muse_bwd(const muse_params* p, const void* Q, const void* K, const void* V,
 
 /* Exact causal softmax attention (Sec. 3, Eq. 1-2) with the same scale, and its gradient: the
  * in-house baseline the MuSe timings are compared with.  Uses N, D, B, Hq, Hkv, dtype, grad_dtype,
- * scale of p; the other fields are ignored. */
+ * scale of p; the other fields are ignored.
+ * Gradients in bf16 may lie on Q, K, V, O, LSE or dO (a gradient then replaces the tensor): they are made in the scratch, which
+ * is demanded for that whether or not a call uses it, and written when nothing is read any more.  fp32 gradients may lie on O
+ * only. */
 int exact_attn_fwd(const muse_params* p, const void* Q, const void* K, const void* V,
                    void* O, float* LSE, void* ws, size_t ws_bytes, void* stream);
 int exact_attn_bwd(const muse_params* p, const void* Q, const void* K, const void* V,

@@ -153,6 +153,19 @@ bool balanced_cap_ok(const MuseDims& d, int C) {
   return cap >= 1 && cap * C >= d.Bs;
 }
 
+// whether a gradient shares memory with what the attention kernels read (not O: its row sums come first) or with another one
+bool grads_overlap(const MuseDims& d, const void* Q, const void* K, const void* V, const float* LSE, const void* dO, const void* dQ,
+                   const void* dK, const void* dV) {
+  const size_t q = (size_t)d.B * d.Hq * d.N, k = (size_t)d.B * d.Hkv * d.N;
+  const size_t es = d.dtype == MUSE_DTYPE_BF16 ? 2 : 4, gs = d.grad_dtype == MUSE_DTYPE_BF16 ? 2 : 4;
+  const struct { const void* p; size_t bytes; } t[] = {{dQ, q * d.D * gs}, {dK, k * d.D * gs}, {dV, k * d.D * gs}, {Q, q * d.D * es},
+                                                       {K, k * d.D * es}, {V, k * d.D * es}, {dO, q * d.D * es}, {LSE, q * 4}};
+  for (int a = 0; a < 3; ++a)
+    for (int b = a + 1; b < 8; ++b)
+      if ((uintptr_t)t[a].p < (uintptr_t)t[b].p + t[b].bytes && (uintptr_t)t[b].p < (uintptr_t)t[a].p + t[a].bytes) return true;
+  return false;
+}
+
 size_t exact_bwd_bytes(const MuseDims& d) {
   size_t q = (size_t)d.B * d.Hq * d.N, k = (size_t)d.B * d.Hkv * d.N;
   size_t b = al(q * 4);  // delta
@@ -323,8 +336,10 @@ int exact_attn_bwd(const muse_params* p, const void* Q, const void* K, const voi
   float* delta = (float*)w; w += al(q * 4);
   float *aq, *ak, *av;
   // The kernels of long blocks write bf16 gradients themselves, 8 bytes at a time; others leave fp32 sums, which are cast.  At
-  // 32 heads of 8k with D = 128 that takes the call from 2362 to 2294 us.
-  d.grads16 = d.grad_dtype == MUSE_DTYPE_BF16 && muse_attn_bwd_writes16(d, d.N) && ((uintptr_t)dQ | (uintptr_t)dK | (uintptr_t)dV) % 8 == 0;
+  // 32 heads of 8k with D = 128 that takes the call from 2362 to 2294 us.  dQ is then written while dK and dV are still to be
+  // made from Q and dO, so gradients that lie on what is read keep the sums in the scratch.
+  d.grads16 = d.grad_dtype == MUSE_DTYPE_BF16 && muse_attn_bwd_writes16(d, d.N) && ((uintptr_t)dQ | (uintptr_t)dK | (uintptr_t)dV) % 8 == 0 &&
+              !grads_overlap(d, Q, K, V, LSE, dO, dQ, dK, dV);
   const bool direct = d.grad_dtype == MUSE_DTYPE_FP32 || d.grads16;
   if (direct) {
     aq = (float*)dQ; ak = (float*)dK; av = (float*)dV;

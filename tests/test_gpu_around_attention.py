@@ -56,3 +56,24 @@ def test_row_sums_and_casts(N, H, D, dtype):
     want = (P * (dP - (P * dP).sum(-1, keepdim=True))) @ k / math.sqrt(D)
     bound = bf16_grad_bound(float(want.abs().max())) if dtype == mb.BF16 else 1e-5 * max(1.0, float(want.abs().max()))
     assert (got[0][0].cpu().double() - want).abs().max() <= bound
+
+
+@pytest.mark.parametrize("D,N", [(64, 1100), (128, 1100), (64, 300)])
+@pytest.mark.parametrize("on", [("dO", None, None), (None, "K", "V"), ("Q", "K", "V"), ("O", "V", "K"), ("dO half", None, None)])
+def test_bf16_gradients_on_the_inputs(on, D, N):
+    # gradients that replace the tensors they are made from: the values of gradients in memory of their own, also in the long
+    # blocks whose kernels write bf16 gradients one after the other
+    g = torch.Generator().manual_seed(D)
+    H = 34
+    t = {n: torch.randn(1, H, N, D, generator=g).bfloat16().cuda() for n in ("Q", "K", "V", "dO")}
+    p = mb.Params(B=1, Hq=H, Hkv=H, N=N, D=D, grad_dtype=mb.BF16)
+    t["O"], LSE = mb.exact_attn_fwd(p, t["Q"], t["K"], t["V"])
+    want = mb.exact_attn_bwd(p, t["Q"], t["K"], t["V"], t["O"], LSE, t["dO"])
+    if on[0] == "dO half":  # dQ begins in the middle of dO
+        both = torch.empty(t["dO"].numel() * 3 // 2, dtype=torch.bfloat16, device="cuda")
+        n = t["dO"].numel()
+        both[:n] = t["dO"].flatten()
+        t["dO"], t["dO half"] = both[:n].view(1, H, N, D), both[n // 2:].view(1, H, N, D)
+    out = tuple(torch.empty_like(w) if x is None else t[x] for x, w in zip(on, want))
+    mb.exact_attn_bwd(p, t["Q"], t["K"], t["V"], t["O"], LSE, t["dO"], out=out)
+    assert all(torch.equal(a, b) for a, b in zip(out, want))
