@@ -815,9 +815,15 @@ bool muse_attn_dq_wide(const MuseDims& d, int Bs) {
 }
 bool muse_attn_dkv_wide(const MuseDims& d, int Bs) { return d.D == 64 ? Bs > TR : Bs >= 2 * TR; }
 
+// Rows go from memory to LDS 16 bytes at a time, from 16-byte boundaries: tensors that begin elsewhere (a view one element into
+// its storage) are read through registers by the kernels of 128 rows, where any address will do.
+bool muse_attn_rows_to_lds(const void* Q, const void* K, const void* V, const void* dO) {
+  return ((uintptr_t)Q | (uintptr_t)K | (uintptr_t)V | (uintptr_t)dO) % 16 == 0;
+}
+
 // the gradients may leave in bf16 (MuseDims::grads16): all of them come from the kernels of this file
-bool muse_attn_bwd_writes16(const MuseDims& d, int Bs) {
-  return d.dtype == MUSE_DTYPE_BF16 && muse_attn_dq_wide(d, Bs) && muse_attn_dkv_wide(d, Bs);
+bool muse_attn_bwd_writes16(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V, const void* dO) {
+  return d.dtype == MUSE_DTYPE_BF16 && muse_attn_dq_wide(d, Bs) && muse_attn_dkv_wide(d, Bs) && muse_attn_rows_to_lds(Q, K, V, dO);
 }
 
 int muse_launch_attn_dq_wide(const MuseDims& d, int Bs, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,

@@ -338,7 +338,7 @@ int exact_attn_bwd(const muse_params* p, const void* Q, const void* K, const voi
   // The kernels of long blocks write bf16 gradients themselves, 8 bytes at a time; others leave fp32 sums, which are cast.  At
   // 32 heads of 8k with D = 128 that takes the call from 2362 to 2294 us.  dQ is then written while dK and dV are still to be
   // made from Q and dO, so gradients that lie on what is read keep the sums in the scratch.
-  d.grads16 = d.grad_dtype == MUSE_DTYPE_BF16 && muse_attn_bwd_writes16(d, d.N) && ((uintptr_t)dQ | (uintptr_t)dK | (uintptr_t)dV) % 8 == 0 &&
+  d.grads16 = d.grad_dtype == MUSE_DTYPE_BF16 && muse_attn_bwd_writes16(d, d.N, Q, K, V, dO) && ((uintptr_t)dQ | (uintptr_t)dK | (uintptr_t)dV) % 8 == 0 &&
               !grads_overlap(d, Q, K, V, LSE, dO, dQ, dK, dV);
   const bool direct = d.grad_dtype == MUSE_DTYPE_FP32 || d.grads16;
   if (direct) {

@@ -54,3 +54,25 @@ def test_a_row_that_is_not_finite_stays_with_its_successors():
     assert torch.equal(dQ[:, :, others], want[0][:, :, others])
     far = torch.arange(N, device="cuda") >= (n // 64 + 1) * 64  # the matrix instructions meet a masked pair inside 64 rows
     assert torch.equal(dK[:, :, far], want[1][:, :, far]) and torch.equal(dV[:, :, far], want[2][:, :, far])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("odd", ["Q", "K", "V", "dO"])
+def test_tensors_off_a_16_byte_boundary(odd, D):
+    # a view one element into its storage: the kernels of 128 rows, with gradients in either type.  dK and dV add up in the same
+    # order there; dQ takes its key tiles the other way round: the same products, N of them, added in fp32 (2^-24 each of what has
+    # been added up, which stays below 16 times the largest entry for rows like these).
+    g = torch.Generator().manual_seed(D)
+    H, N = 32, 1100
+    t = {n: torch.randn(1, H, N, D, generator=g).bfloat16().cuda() for n in ("Q", "K", "V", "dO")}
+    args = lambda: (t["Q"], t["K"], t["V"], O, LSE, t["dO"])
+    p = mb.Params(B=1, Hq=H, Hkv=H, N=N, D=D)
+    p16 = mb.Params(B=1, Hq=H, Hkv=H, N=N, D=D, grad_dtype=mb.BF16)
+    O, LSE = mb.exact_attn_fwd(p, t["Q"], t["K"], t["V"])
+    want = mb.exact_attn_bwd(p, *args())
+    x = torch.empty(t[odd].numel() + 8, dtype=torch.bfloat16, device="cuda")[1:1 + t[odd].numel()].view(t[odd].shape)
+    t[odd] = x.copy_(t[odd])
+    got = mb.exact_attn_bwd(p, *args())
+    assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+    assert (got[0] - want[0]).abs().max() <= 16 * N * 2.0 ** -24 * want[0].abs().max()
+    assert all(torch.equal(a, b.bfloat16()) for a, b in zip(mb.exact_attn_bwd(p16, *args()), got))
