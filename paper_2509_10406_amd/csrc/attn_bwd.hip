@@ -41,7 +41,8 @@ __device__ __forceinline__ uint32_t lds_addr(const T* p) { return (uint32_t)(uin
 __device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 // 16 bytes of every lane from base + off to LDS at at + 16 lane.  Written out, because behind the builtin the compiler lets every
 // LDS read wait for the rows; they are waited for by count (the caller's s_waitcnt vmcnt) in front of a
-// barrier.  m0 holds nothing of the compiler's in these kernels: it has no other use on this architecture than indexed registers and this.
+// barrier.  m0 is reserved and cannot be named as clobbered; nothing else in these kernels uses it (tests/test_attn_bwd_code.py looks
+// through the machine code for that, and for the wait states that mfma_acc needs).
 __device__ __forceinline__ void rows_to_lds(uint32_t at, uint32_t off, const bf16_t* base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
 }
