@@ -73,16 +73,18 @@ __global__ void __launch_bounds__(64) k_tile_schedule(const int32_t* __restrict_
 // are exact and the sums fp32, so L keeps fp32 accuracy; one wave per 32 keys, rows = query clusters.
 // The split of a centroid tile is about as much work as its logits' way to memory, so a wave takes KT tiles of 32 keys and splits
 // once for all of them (KT as the registers allow), and the centroid tiles are spread over more workgroups where the keys
-// do not fill the device.  us, one tile per wave / now: 366 / 272 at 16
+// do not fill the device.  us, one tile per wave and all its centroids / now: 366 / 272 at 16
 // heads of 64k with 256 clusters, 671 / 469 at 32 heads, 202 / 156 at 16 with 128; D = 128, 32 heads of 32k: 305 / 244 with 128, 181 / 148
-// with 64; 9 / 9 at 12 heads of 6k.
+// with 64.  With fewer units (32 keys x 32 clusters) than make 1024 such waves, one for each SIMD, the wave's own chain sets the time,
+// and it keeps one tile; us, KT = 1 / 4 (D = 128: 2): 6.2 / 9.2 with 64 units, 7.0 / 10.5 with 512, 9.4 / 11.2 with 2048, 13.3 / 12.9, 13.4 /
+// 12.6 and 13.4 / 12.4 with 4096, 21.7 / 18.2 with 8192; D = 128: 8.0 / 10.0 with 512, 8.6 / 10.2 with 1024, 12.2 / 11.6 with 2048, 19.3 / 17.1.
 template <int D>
 constexpr int kTiltTiles = D == 64 ? 4 : 2;
-template <int D>
+template <int D, int KT>
 __global__ void __launch_bounds__(256) k_tilt_logits_mx(const bf16_t* __restrict__ Ks, const float* __restrict__ qc,
                                                          float* __restrict__ L, int h0, int N, int Cq, int Hq, int Hkv, int per,
                                                          float scale) {
-  constexpr int KS = D / 16, KT = kTiltTiles<D>;
+  constexpr int KS = D / 16;
   const int hl = blockIdx.y, hq = h0 + hl;
   const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
@@ -133,11 +135,17 @@ __global__ void __launch_bounds__(256) k_tilt_logits_mx(const bf16_t* __restrict
 }
 template <int D>
 void launch_tilt_logits_mx(const MuseDims& d, const bf16_t* Ks, const float* qc, float* L, int h0, int hn, hipStream_t st) {
-  const int keys = 128 * kTiltTiles<D>, x = (d.N + keys - 1) / keys, tiles = (d.Cq + 31) / 32;
-  const long long waves = 4ll * x * hn;
-  const int want = (int)std::min<long long>(tiles, (4096 + waves - 1) / waves), per = (tiles + want - 1) / want;
+  const int tiles = (d.Cq + 31) / 32;
   MuseProf prof_("k_tilt_logits", st);
-  hipLaunchKernelGGL(k_tilt_logits_mx<D>, dim3(x, hn, (tiles + per - 1) / per), dim3(256), 0, st, Ks, qc, L, h0, d.N, d.Cq, d.Hq, d.Hkv, per, d.scale);
+  auto go = [&](auto kt) {
+    constexpr int KT = decltype(kt)::value;
+    const int x = (d.N + 128 * KT - 1) / (128 * KT);
+    const long long waves = 4ll * x * hn;
+    const int want = (int)std::min<long long>(tiles, (4096 + waves - 1) / waves), per = (tiles + want - 1) / want;
+    hipLaunchKernelGGL((k_tilt_logits_mx<D, KT>), dim3(x, hn, (tiles + per - 1) / per), dim3(256), 0, st, Ks, qc, L, h0, d.N, d.Cq, d.Hq, d.Hkv, per, d.scale);
+  };
+  if ((d.N + 31) / 32 * (long long)hn * tiles < 1024 * kTiltTiles<D>) go(std::integral_constant<int, 1>{});
+  else go(std::integral_constant<int, kTiltTiles<D>>{});
 }
 
 template <typename T, int D>

@@ -13,6 +13,9 @@ CASES = {
     "bf16": ("cfg2", dict(N=2048, Hq=8, Hkv=8, Cq=24, Ck=71, r=4, block=256, kmeans_iters=2)),
     "bf16_gqa_k2_2": ("cfg2", dict(N=2048, Hq=8, Hkv=2, Cq=64, Ck=32, r=5, k2=2, block=256, kmeans_iters=2)),
     "bf16_d128_nb12": ("cfg5", dict(N=1536, Hq=4, Hkv=2, Cq=40, Ck=35, r=9, block=128, kmeans_iters=2)),
+    # tilt logits: one tile of keys per wave in a chunk of one head, four (two) in a launch of all heads; sizes that end inside both
+    "bf16_tilt": ("cfg2", dict(N=16392, Hq=8, Hkv=8, Cq=33, Ck=20, r=1, block=2049, kmeans_iters=1)),
+    "bf16_tilt_d128": ("cfg5", dict(N=8200, Hq=8, Hkv=8, Cq=33, Ck=20, r=1, block=1025, kmeans_iters=1)),
     "fp32": ("cfg1", dict(N=1536, Hq=6, Hkv=3, Cq=32, Ck=48, r=3, block=192, kmeans_iters=2)),
 }
 
