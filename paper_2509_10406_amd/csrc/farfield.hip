@@ -38,7 +38,7 @@ __global__ void __launch_bounds__(256) k_gather_rows(const T* __restrict__ X, co
 
 // ------------------------------------------------------------------------------------------
 // tile schedule: tile_off[hq][b][i] = number of 32-query tiles of clusters < i in block b >= 1;
-// tile_off[hq][0][i] = number of queries of clusters < i in the blocks >= 1 (far_query).  A wave per (head, block).
+// (row 0 is not read).  A wave per (head, block).
 // ------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) k_tile_schedule(const int32_t* __restrict__ off_q, int32_t* __restrict__ tile_off, int nb, int Cq) {
   const int hq = blockIdx.x / nb, b = blockIdx.x % nb, lane = threadIdx.x;
@@ -48,11 +48,7 @@ __global__ void __launch_bounds__(64) k_tile_schedule(const int32_t* __restrict_
   for (int i0 = 0; i0 < Cq; i0 += 64) {
     const int i = i0 + lane;
     int v = 0;
-    if (i < Cq) {
-      if (b > 0) v = (o[b * Cq + i + 1] - o[b * Cq + i] + 31) / 32;
-      else
-        for (int x = 1; x < nb; ++x) v += o[x * Cq + i + 1] - o[x * Cq + i];
-    }
+    if (i < Cq) v = (o[b * Cq + i + 1] - o[b * Cq + i] + 31) / 32;
     int incl = v;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -1319,31 +1315,29 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 // inputs take it on the matrix cores in the pair kernels.  The result is merged into the query's
 // far-field state.  16 lanes per query, a lane owns the dims 64 x + 4 l16 + t, and the scalars of one of eight key blocks.
 //
-// Bound by the rows, 10 to 12 TB/s of them from the L2 (a row is read again for every query that retrieved its chain).  What
-// helped is the order of the queries, cluster by cluster instead of block by block: us, before / now, 3810 / 3500 at 32 heads of
-// 32k with D = 128 and 128 x 512 clusters, 3120 / 2880 at 32 heads of 64k with rotary rows, 75 / 53 at 12 heads of 6k with 23 x
-// 71 clusters, 165 / 134 at 4 fp32 heads of 8k; 1150 / 1145 at 16 heads of 64k with 256 x 1024.  Working the scalars of a block
-// out in one lane, with one maximum per cluster instead of one per row, saves a third of the vector instructions but shows only
-// in small calls.
+// Bound by the rows, 10 to 12 TB/s of them from the L2 (a row is read again for every query that retrieved its chain).  Working the
+// scalars of a block out in one lane, with one maximum per cluster instead of one per row (l and the values are added up against
+// it: another order of the same sums than row by row), saves a third of the vector instructions; the order of the queries is at
+// far_position.  us of the three together, before / now: 3285 / 3095 at 32 heads of 32k with D = 128 and 128 x 512 clusters, 2692 / 2670
+// at 32 heads of 64k with rotary rows, 1158 / 1114 at 16 heads of 64k with 256 x 1024, 74 / 50 at 12 heads of 6k with 23 x 71,
+// 193 / 145 at 4 fp32 heads of 8k.
 // ------------------------------------------------------------------------------------------
 template <typename T, int D, int NBC>
 __global__ void __launch_bounds__(256) k_comp2_fwd(
     const T* __restrict__ Q, const float* __restrict__ qc, const T* __restrict__ Ks, const T* __restrict__ Vs,
     const float* __restrict__ L, const float* __restrict__ s_mu, const float* __restrict__ s_k,
-    const T* __restrict__ s_v, const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q,
-    const int32_t* __restrict__ tile_off, const int32_t* __restrict__ off_k, const int32_t* __restrict__ selc, int32_t* __restrict__ selb,
+    const T* __restrict__ s_v, const int32_t* __restrict__ perm_q, const int32_t* __restrict__ aq, const int32_t* __restrict__ off_k, const int32_t* __restrict__ selc, int32_t* __restrict__ selb,
     float* __restrict__ ff_acc, float* __restrict__ ff_ml, int h0, int N, int nb, int Bs, int Cq, int Ck, int r,
     int k2e, int Hq, int Hkv, float scale) {
   constexpr int NG = D / 64;
   const int hl = blockIdx.y, hq = h0 + hl;
   const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);
   const int l16 = threadIdx.x % 16;
-  const int idx = far_index();
-  if (idx >= N - Bs) return;
-  const FarQuery fq = far_query(tile_off + (size_t)hq * nb * (Cq + 1), off_q + (size_t)hq * ((size_t)nb * Cq + 1), idx, nb, Cq);
-  const int n = perm_q[(size_t)hq * N + fq.pos];
+  const int pos = far_position(N);
+  if (pos < Bs) return;
+  const int n = perm_q[(size_t)hq * N + pos];
   const size_t qn = (size_t)hq * N + n;
-  const int b = fq.b, i = fq.i, NBm = nb - 1;
+  const int b = n / Bs, i = aq[qn], NBm = nb - 1;
   const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
   float qt[NG][4];
 #pragma unroll
@@ -1354,7 +1348,7 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
     qt[x][0] = scale * (q4[0] - c4.x); qt[x][1] = scale * (q4[1] - c4.y);
     qt[x][2] = scale * (q4[2] - c4.z); qt[x][3] = scale * (q4[3] - c4.w);
   }
-  // the four queries of a wave are neighbours, mostly of one block: the largest b among them (wave-uniform)
+  // the four queries of a wave are neighbours in the block-major order: the largest b among them (wave-uniform)
   // bounds the block loops, so a wave of block-1 queries handles one summary row per cluster, not eight
   // (the bound is a template constant of the loop body below: one straight-line body per value, loads batched)
   int bwv = b;
@@ -1785,11 +1779,11 @@ void launch_ff_fwd_r(const MuseDims& d, const T* Q, const float* qc, const int32
     const dim3 g = far_grid(d, hn);
     if (d.nb <= 9)
       { MuseProf prof_("k_comp2_fwd", st); hipLaunchKernelGGL((k_comp2_fwd<T, D, 1>), g, dim3(256), 0, st, Q, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.s_mu, w.s_k,
-                         (const T*)w.s_v, w.perm_q, w.off_q, w.tile_off, w.off_k, selc, selb, w.ff_acc, w.ff_ml, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r,
+                         (const T*)w.s_v, w.perm_q, aq, w.off_k, selc, selb, w.ff_acc, w.ff_ml, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r,
                          d.k2e, d.Hq, d.Hkv, d.scale); }
     else
       { MuseProf prof_("k_comp2_fwd", st); hipLaunchKernelGGL((k_comp2_fwd<T, D, 2>), g, dim3(256), 0, st, Q, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.s_mu, w.s_k,
-                         (const T*)w.s_v, w.perm_q, w.off_q, w.tile_off, w.off_k, selc, selb, w.ff_acc, w.ff_ml, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r,
+                         (const T*)w.s_v, w.perm_q, aq, w.off_k, selc, selb, w.ff_acc, w.ff_ml, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r,
                          d.k2e, d.Hq, d.Hkv, d.scale); }
   }
 }

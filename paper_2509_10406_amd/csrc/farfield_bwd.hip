@@ -250,33 +250,32 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 }
 
 // ------------------------------------------------------------------------------------------
-// dQ of component 2, per query (16 lanes, dims 64 x + 4 l16 + t, cluster by cluster, as in the forward): for every
+// dQ of component 2, per query (16 lanes, dims 64 x + 4 l16 + t, in the order of far_position): for every
 // retrieved cluster, the summaries of the preceding blocks that were NOT retrieved contribute  dl k-bar  with
 // dl = p (dO.v-bar - delta),  p = exp(q~.k-bar + mu-bar - LSE).  The retrieval's share is added here too: bf16 inputs
 // have per-pair dq partials, fp32 inputs walk the retrieved keys, kKeys of them requested together.  The sum is added to
-// the row the tile kernel wrote.  us, with the queries block by block and every lane summing every block's product / now: 4510
-// / 4060 at 32 heads of 32k with D = 128, 1245 / 1190 at 16 heads of 64k, 1100 / 1045 with 128 x 128 clusters, 109 / 75 at 12 heads of
-// 6k, 172 / 136 at 4 fp32 heads of 8k.  (fp32 inputs had both in the tile kernel, a lane pair per query and a key per round trip:
-// 384 us at 4 heads of 8k, r = 4, against 44 + 136 for the two kernels now.)
+// the row the tile kernel wrote.  us, every lane summing every block's product and without far_position's order / now: 4166 / 3709
+// at 32 heads of 32k with D = 128, 1240 / 1164 at 16 heads of 64k, 1097 / 983 with 128 x 128 clusters, 110 / 70 at 12 heads of
+// 6k, 196 / 143 at 4 fp32 heads of 8k.  (fp32 inputs had both in the tile kernel, a lane pair per query and a key per round trip:
+// 384 us at 4 heads of 8k, r = 4, against 44 + 143 for the two kernels now.)
 // ------------------------------------------------------------------------------------------
 template <typename T, int D, int NBC>
 __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
     const T* __restrict__ Q, const T* __restrict__ dO, const float* __restrict__ qc, const T* __restrict__ Ks,
     const T* __restrict__ Vs, const float* __restrict__ L, const int32_t* __restrict__ off_k,
     const float* __restrict__ s_mu, const float* __restrict__ s_k, const T* __restrict__ s_v,
-    const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q, const int32_t* __restrict__ tile_off,
+    const int32_t* __restrict__ perm_q, const int32_t* __restrict__ aq,
     const float* __restrict__ LSE, const float* __restrict__ delta, const int32_t* __restrict__ slotinfo, const float* __restrict__ dqpart,
     float* __restrict__ dQ, int h0, int N, int nb, int Bs, int Cq, int Ck, int r, int k2e, int Hq, int Hkv, float scale) {
   constexpr int NG = D / 64;
   constexpr bool kF32 = sizeof(T) == 4;
   const int hl = blockIdx.y, hq = h0 + hl;
   const int l16 = threadIdx.x % 16;
-  const int idx = far_index();
-  if (idx >= N - Bs) return;
-  const FarQuery fq = far_query(tile_off + (size_t)hq * nb * (Cq + 1), off_q + (size_t)hq * ((size_t)nb * Cq + 1), idx, nb, Cq);
-  const int pos = fq.pos, n = perm_q[(size_t)hq * N + pos];
+  const int pos = far_position(N);
+  if (pos < Bs) return;
+  const int n = perm_q[(size_t)hq * N + pos];
   const size_t qn = (size_t)hq * N + n;
-  const int b = fq.b, i = fq.i, NBm = nb - 1;
+  const int b = pos / Bs, i = aq[qn], NBm = nb - 1;
   const float lse = LSE[qn], dl = delta[qn];
   float qt[NG][4], gt[NG][4], dq[NG][4];
 #pragma unroll
@@ -299,7 +298,7 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
   float4 oldq[NG];
 #pragma unroll
   for (int x = 0; x < NG; ++x) oldq[x] = *reinterpret_cast<const float4*>(dQ + qn * D + 64 * x + 4 * l16);
-  // the four queries of a wave are neighbours, mostly of one block: the largest b among them (wave-uniform)
+  // the four queries of a wave are neighbours in the block-major order: the largest b among them (wave-uniform)
   // bounds the block loops
   // (the bound is a template constant of the loop body below: one straight-line body per value, loads batched)
   int bwv = b;
@@ -803,7 +802,7 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
     auto go = [&](auto* kernel) {
       MuseProf prof_("k_comp2_bwd_dq", st);
       hipLaunchKernelGGL(kernel, g2, dim3(256), 0, st, Q, dO, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.s_mu, w.s_k, (const T*)w.s_v,
-                         w.perm_q, w.off_q, w.tile_off, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, d.scale);
+                         w.perm_q, aq, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, d.scale);
     };
     if (d.nb <= 9) go(k_comp2_bwd_dq<T, D, 1>);
     else go(k_comp2_bwd_dq<T, D, 2>);

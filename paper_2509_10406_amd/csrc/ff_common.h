@@ -182,41 +182,21 @@ __device__ __forceinline__ bf16x8_t ld_tr8(const bf16_t* row, int r0, int half) 
   return *reinterpret_cast<bf16x8_t*>(&v);
 }
 
-// The queries of the kernels that read the retrieved chains' summaries per query (k_comp2_fwd, k_comp2_bwd_dq): 16 lanes per
-// query, in order of (cluster, block, position), every XCD (workgroups go to them round-robin) a contiguous eighth of them: the
-// queries of a cluster, which read the same rows whatever their block, meet in one L2 at one time.
-struct FarQuery {
-  int i, b, pos;  // cluster, block, bucketed position
-};
-__device__ __forceinline__ int far_index() {
-  return (int)((blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8) * 16 + threadIdx.x / 16);
-}
-// first[i] = number of queries of clusters < i in the blocks >= 1, oq the head's segment table; idx < first[Cq].  A 16-lane group
-// calls it with its own idx: 16 entries per round trip.
-__device__ __forceinline__ FarQuery far_query(const int32_t* __restrict__ first, const int32_t* __restrict__ oq, int idx, int nb, int Cq) {
-  const int l16 = threadIdx.x % 16, sh = threadIdx.x % 64 / 16 * 16;
-  auto leading = [&](bool x) { return __popc((unsigned)(__ballot(x) >> sh) & 0xffffu); };
-  FarQuery q;
-  q.i = 0;
-  int base = 0;  // first[i]
-  for (int step = Cq > 256 ? 256 : Cq > 16 ? 16 : 1; step >= 1; step /= 16) {
-    const int at = q.i + l16 * step, v = at < Cq ? first[at] : 0x7fffffff;
-    const int k = leading(v <= idx) - 1;
-    base = __shfl(v, k, 16);
-    q.i += k * step;
-  }
-  const int b = l16 < nb ? l16 : 0;  // lane b: block b
-  const int lo = oq[b * Cq + q.i], cnt = l16 >= 1 && l16 < nb ? oq[b * Cq + q.i + 1] - lo : 0;
-  int incl = cnt;
-#pragma unroll
-  for (int d = 1; d < 16; d <<= 1) {
-    const int v = __shfl_up(incl, d, 16);
-    if (l16 >= d) incl += v;
-  }
-  const int rest = idx - base;
-  q.b = leading(incl <= rest);
-  q.pos = __shfl(lo - (incl - cnt), q.b, 16) + rest;
-  return q;
+// The queries of the kernels that read the retrieved chains' summaries per query (k_comp2_fwd, k_comp2_bwd_dq), 16 lanes per query:
+// this group's place in the bucketed order (block by block, cluster by cluster), from the end: the last blocks have the most work
+// per query and go first.  Less than Bs: none.  Workgroups go to the 8 XCDs round-robin; an XCD takes runs of 32 consecutive
+// ones (8 where there are fewer than 1024), so that queries of one cluster and block, which read the same rows, meet in one L2 while
+// every XCD gets some of every block.  Which XCD has the first run changes with the head, or the runs left over at the end would
+// all be the first XCDs'.
+// us of k_comp2_fwd / k_comp2_bwd_dq, runs of 32 from the first block on without that turn / with it and runs of 8 / now: 71 / 95, 50 / 70 and
+// 50 / 70 at 12 heads of 6k; 178 / 176, 159 / 156 and 145 / 143 at 4 fp32 heads of 8k; 86 / 92, 81 / 82 and 76 / 80 at 8 heads of 16k with 64 x
+// 256; 3270 / 3765, 3259 / 3740 and 3095 / 3709 at 32 heads of 32k with D = 128.  Cluster by cluster over all blocks, an eighth of them
+// per XCD, finding a place takes two more round trips: 54 / 75, 155 / 151, 87 / 89, 3121 / 3753; 905 / 1041 against 840 / 983 at 16 heads of
+// 64k with 128 x 128, 286 / 321 against 248 / 296 of 32k with 64 x 64, 583 / 659 against 518 / 616 with four blocks; better only for the
+// forward of 32 heads of 64k with rotary rows and 256 x 1024: 2575 against 2670.
+__device__ __forceinline__ int far_position(int N) {
+  const int run = gridDim.x < 1024 ? 8 : 32, sq = blockIdx.x / 8, xcd = (blockIdx.x + blockIdx.y) % 8;
+  return N - 1 - (((sq / run * 8 + xcd) * run + sq % run) * 16 + (int)threadIdx.x / 16);
 }
 
 // What a 16-lane group does with one value per key block, eight of them at a time: the dims' partial sums of all eight meet in
@@ -374,8 +354,11 @@ static inline size_t ff_segcnt_bytes(const MuseDims& d) {
 // bytes of the all-heads part / of one query head of the chunked part
 // x extent of the forward tile kernels' grid: the tiles of a (head, block) pair, rounded up to the 8 XCDs
 static inline size_t ff_tile_grid_x(const MuseDims& d) { return (size_t)(d.Bs / 32 + d.Cq + 1 + 7) / 8 * 8; }
-// the grid of far_index
-static inline dim3 far_grid(const MuseDims& d, int hn) { return dim3((unsigned)(((d.N - d.Bs + 15) / 16 + 7) / 8 * 8), hn); }
+// the grid of far_position: whole rounds of runs
+static inline dim3 far_grid(const MuseDims& d, int hn) {
+  const int wgs = (d.N - d.Bs + 15) / 16, round = wgs < 1024 ? 64 : 256;
+  return dim3((unsigned)((wgs + round - 1) / round * round), hn);
+}
 static inline size_t ff_flag_bytes(const MuseDims& d) {
   return (size_t)d.B * d.Hq * (d.nb > 1 ? d.nb - 1 : 1) * ff_tile_grid_x(d) * 4;
 }

@@ -1,7 +1,6 @@
-"""GPU parity of the kernels that take the far-field queries in order of their cluster (component 2, forward and dQ) where the
-search for a query's cluster and block changes: one, two and three levels of 16 clusters (with clusters that no query is in), two,
-nine (a second chunk of eight key blocks) and sixteen blocks, ends of the order that fill no workgroup.  Tolerances are those of
-the parity suite."""
+"""GPU parity of the kernels that take the far-field queries one by one (component 2, forward and dQ) at odd counts: clusters that no
+query is in, two, nine (a second chunk of eight key blocks) and sixteen blocks, ends of the order that fill no workgroup and rounds of
+workgroups that are not full.  Tolerances are those of the parity suite."""
 import pytest
 
 import tests.test_gpu_muse as base
