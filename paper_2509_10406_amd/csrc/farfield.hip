@@ -1385,6 +1385,73 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
     next = selc[qn * r + (t + 1 < r ? t + 1 : t)];
     if (j < 0) continue;
     const uint32_t cell0 = (uint32_t)i * Ck + j, at = cell0 * (D / 4) + l16;
+    unsigned selbits = 0;
+    if constexpr (bw <= 2) {
+      // One or two preceding blocks: every lane works their scalars out (the exchanges below are made for eight), and there are
+      // values to add only if there are two.  us, with the exchanges / now (row by row, before them): 126 / 118 (111) at 16 heads
+      // of 32k in two blocks, 301 / 288 (287) of 48k in three; D = 128: 177 / 163 (161), 431 / 407 (416).
+      float mu[bw], sc[bw];
+      float4 kr[bw][NG];
+      typename F4::raw vr[bw][NG];
+      uint32_t pl = at, pc = cell0;
+#pragma unroll
+      for (int u = 0; u < bw; ++u) {
+        if (u > 0 && u < b) { pl += stride; pc += cells; }
+        mu[u] = mubase[pc];
+#pragma unroll
+        for (int x = 0; x < NG; ++x) {
+          kr[u][x] = *reinterpret_cast<const float4*>(kbase + (size_t)pl * 4 + 64 * x);
+          if (bw > 1) vr[u][x] = F4::ld(vbase + (size_t)pl * 4, 64 * x);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < bw; ++u) {
+        float part = 0.f;
+#pragma unroll
+        for (int x = 0; x < NG; ++x) {
+          part = fmaf(qt[x][0], kr[u][x].x, part); part = fmaf(qt[x][1], kr[u][x].y, part);
+          part = fmaf(qt[x][2], kr[u][x].z, part); part = fmaf(qt[x][3], kr[u][x].w, part);
+        }
+        const float sum = group_sum<16>(part) + mu[u];
+        sc[u] = u < b && mu[u] > MUSE_NEG_INF && sum > MUSE_NEG_INF ? sum : MUSE_NEG_INF;
+      }
+      for (int u = 0; u < k2e; ++u) {
+        float best = MUSE_NEG_INF;
+        int bi = -1;
+#pragma unroll
+        for (int bp = 0; bp < bw; ++bp)
+          if (sc[bp] > best && !((selbits >> bp) & 1u)) { best = sc[bp]; bi = bp; }
+        if (bi >= 0) selbits |= 1u << bi;
+        if (l16 == 0) selb[(qn * r + t) * k2e + u] = bi;
+      }
+      if constexpr (bw > 1) {
+        float mn = m;
+#pragma unroll
+        for (int u = 0; u < bw; ++u) {
+          if ((selbits >> u) & 1u) sc[u] = MUSE_NEG_INF;
+          mn = fmaxf(mn, sc[u]);
+        }
+        const float ref = mn == MUSE_NEG_INF ? 0.f : mn, alpha = __expf(m - ref);
+        m = mn;
+        l *= alpha;
+#pragma unroll
+        for (int x = 0; x < NG; ++x)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[x][e] *= alpha;
+        float share = 0.f;
+#pragma unroll
+        for (int u = 0; u < bw; ++u) {
+          const float p = __expf(sc[u] - ref);
+          share = u8 == u ? p : share;
+          if (!(sc[u] > MUSE_NEG_INF)) continue;
+#pragma unroll
+          for (int x = 0; x < NG; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[x][e] = fmaf(p, F4::get(vr[u][x], e), o[x][e]);
+        }
+        l += share;
+      }
+    } else {
     // scores of the preceding blocks, 8 at a time: every load of a chunk is in flight together (with at
     // most 8 preceding blocks the value rows ride along, one round trip per retrieved cluster)
     float sc[NBC];  // of block 8 c + u8
@@ -1429,7 +1496,6 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
       const float sum = sums_to_lanes(part);
       if (c0 + u8 < b && mu > MUSE_NEG_INF) sc[c] = sum + mu;
     }
-    unsigned selbits = 0;
     float cand[NBC];
 #pragma unroll
     for (int c = 0; c < NBC; ++c) cand[c] = sc[c];
@@ -1475,6 +1541,7 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[x][e] = fmaf(pu, F4::get(vr[u][x], e), o[x][e]);
       });
+    }
     }
     if (sizeof(T) == 4) {  // component 3: the keys of the retrieved (cluster, block) pairs, with the full query
       for (int bp = 0; bp < b; ++bp) {
