@@ -1452,96 +1452,96 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
         l += share;
       }
     } else {
-    // scores of the preceding blocks, 8 at a time: every load of a chunk is in flight together (with at
-    // most 8 preceding blocks the value rows ride along, one round trip per retrieved cluster)
-    float sc[NBC];  // of block 8 c + u8
-    typename F4::raw vr[8][NG];
-    auto load_values = [&](int c0) {
-      uint32_t pl = at + (uint32_t)min(c0, b - 1) * stride;
+      // scores of the preceding blocks, 8 at a time: every load of a chunk is in flight together (with at
+      // most 8 preceding blocks the value rows ride along, one round trip per retrieved cluster)
+      float sc[NBC];  // of block 8 c + u8
+      typename F4::raw vr[8][NG];
+      auto load_values = [&](int c0) {
+        uint32_t pl = at + (uint32_t)min(c0, b - 1) * stride;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        if (u > 0 && c0 + u < b) pl += stride;
+        for (int u = 0; u < 8; ++u) {
+          if (c0 + u >= bw) break;
+          if (u > 0 && c0 + u < b) pl += stride;
 #pragma unroll
-        for (int x = 0; x < NG; ++x) vr[u][x] = F4::ld(vbase + (size_t)pl * 4, 64 * x);
-      }
-    };
-#pragma unroll
-    for (int c = 0; c < NBC; ++c) {
-      sc[c] = MUSE_NEG_INF;
-      const int c0 = 8 * c;
-      if (c0 >= bw) break;
-      float part[8];
-      float4 kr[8][NG];
-      const float mu = mubase[cell0 + (uint32_t)min(c0 + u8, b - 1) * cells];
-      uint32_t pl = at + (uint32_t)min(c0, b - 1) * stride;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (c0 + u >= bw) break;
-        if (u > 0 && c0 + u < b) pl += stride;  // past the last preceding block: that one again
-#pragma unroll
-        for (int x = 0; x < NG; ++x) kr[u][x] = *reinterpret_cast<const float4*>(kbase + (size_t)pl * 4 + 64 * x);
-      }
-      if (NBC == 1) load_values(0);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        part[u] = 0.f;
-        if (c0 + u >= bw) continue;
-#pragma unroll
-        for (int x = 0; x < NG; ++x) {
-          part[u] = fmaf(qt[x][0], kr[u][x].x, part[u]); part[u] = fmaf(qt[x][1], kr[u][x].y, part[u]);
-          part[u] = fmaf(qt[x][2], kr[u][x].z, part[u]); part[u] = fmaf(qt[x][3], kr[u][x].w, part[u]);
+          for (int x = 0; x < NG; ++x) vr[u][x] = F4::ld(vbase + (size_t)pl * 4, 64 * x);
         }
+      };
+#pragma unroll
+      for (int c = 0; c < NBC; ++c) {
+        sc[c] = MUSE_NEG_INF;
+        const int c0 = 8 * c;
+        if (c0 >= bw) break;
+        float part[8];
+        float4 kr[8][NG];
+        const float mu = mubase[cell0 + (uint32_t)min(c0 + u8, b - 1) * cells];
+        uint32_t pl = at + (uint32_t)min(c0, b - 1) * stride;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (c0 + u >= bw) break;
+          if (u > 0 && c0 + u < b) pl += stride;  // past the last preceding block: that one again
+#pragma unroll
+          for (int x = 0; x < NG; ++x) kr[u][x] = *reinterpret_cast<const float4*>(kbase + (size_t)pl * 4 + 64 * x);
+        }
+        if (NBC == 1) load_values(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          part[u] = 0.f;
+          if (c0 + u >= bw) continue;
+#pragma unroll
+          for (int x = 0; x < NG; ++x) {
+            part[u] = fmaf(qt[x][0], kr[u][x].x, part[u]); part[u] = fmaf(qt[x][1], kr[u][x].y, part[u]);
+            part[u] = fmaf(qt[x][2], kr[u][x].z, part[u]); part[u] = fmaf(qt[x][3], kr[u][x].w, part[u]);
+          }
+        }
+        const float sum = sums_to_lanes(part);
+        if (c0 + u8 < b && mu > MUSE_NEG_INF) sc[c] = sum + mu;
       }
-      const float sum = sums_to_lanes(part);
-      if (c0 + u8 < b && mu > MUSE_NEG_INF) sc[c] = sum + mu;
-    }
-    float cand[NBC];
+      float cand[NBC];
 #pragma unroll
-    for (int c = 0; c < NBC; ++c) cand[c] = sc[c];
-    for (int u = 0; u < k2e; ++u) {
-      float best = cand[0];
-      if (NBC > 1) best = fmaxf(best, cand[NBC - 1]);
-      best = max_of_8(best);
-      unsigned at_best = lanes_of_8(cand[0] == best);
-      if (NBC > 1) at_best |= lanes_of_8(cand[NBC - 1] == best) << 8;
-      const int bi = best > MUSE_NEG_INF ? __ffs((int)at_best) - 1 : -1;
-      if (bi >= 0) selbits |= 1u << bi;
+      for (int c = 0; c < NBC; ++c) cand[c] = sc[c];
+      for (int u = 0; u < k2e; ++u) {
+        float best = cand[0];
+        if (NBC > 1) best = fmaxf(best, cand[NBC - 1]);
+        best = max_of_8(best);
+        unsigned at_best = lanes_of_8(cand[0] == best);
+        if (NBC > 1) at_best |= lanes_of_8(cand[NBC - 1] == best) << 8;
+        const int bi = best > MUSE_NEG_INF ? __ffs((int)at_best) - 1 : -1;
+        if (bi >= 0) selbits |= 1u << bi;
 #pragma unroll
-      for (int c = 0; c < NBC; ++c)
-        if (8 * c + u8 == bi) cand[c] = MUSE_NEG_INF;
-      if (l16 == 0) selb[(qn * r + t) * k2e + u] = bi;
-    }
-    // component 2: value summaries of the blocks that are not retrieved
-    float mn = m;
+        for (int c = 0; c < NBC; ++c)
+          if (8 * c + u8 == bi) cand[c] = MUSE_NEG_INF;
+        if (l16 == 0) selb[(qn * r + t) * k2e + u] = bi;
+      }
+      // component 2: value summaries of the blocks that are not retrieved
+      float mn = m;
 #pragma unroll
-    for (int c = 0; c < NBC; ++c) {
-      if (!(sc[c] > MUSE_NEG_INF) || ((selbits >> (8 * c + u8)) & 1u)) sc[c] = MUSE_NEG_INF;
-      mn = fmaxf(mn, sc[c]);
-    }
-    mn = max_of_8(mn);
-    const float ref = mn == MUSE_NEG_INF ? 0.f : mn, alpha = __expf(m - ref);
-    m = mn;
-    l *= alpha;
+      for (int c = 0; c < NBC; ++c) {
+        if (!(sc[c] > MUSE_NEG_INF) || ((selbits >> (8 * c + u8)) & 1u)) sc[c] = MUSE_NEG_INF;
+        mn = fmaxf(mn, sc[c]);
+      }
+      mn = max_of_8(mn);
+      const float ref = mn == MUSE_NEG_INF ? 0.f : mn, alpha = __expf(m - ref);
+      m = mn;
+      l *= alpha;
 #pragma unroll
-    for (int x = 0; x < NG; ++x)
+      for (int x = 0; x < NG; ++x)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[x][e] *= alpha;
+        for (int e = 0; e < 4; ++e) o[x][e] *= alpha;
 #pragma unroll
-    for (int c = 0; c < NBC; ++c) {
-      if (8 * c >= bw) break;
-      if (NBC > 1) load_values(8 * c);
-      const float p = __expf(sc[c] - ref);
-      const unsigned used = lanes_of_8(sc[c] > MUSE_NEG_INF);
-      l += p;
-      each_lane<(bw < 8 ? bw : 8)>(p, [&](int u, float pu) {
-        if (!((used >> u) & 1u)) return;
+      for (int c = 0; c < NBC; ++c) {
+        if (8 * c >= bw) break;
+        if (NBC > 1) load_values(8 * c);
+        const float p = __expf(sc[c] - ref);
+        const unsigned used = lanes_of_8(sc[c] > MUSE_NEG_INF);
+        l += p;
+        each_lane<(bw < 8 ? bw : 8)>(p, [&](int u, float pu) {
+          if (!((used >> u) & 1u)) return;
 #pragma unroll
-        for (int x = 0; x < NG; ++x)
+          for (int x = 0; x < NG; ++x)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[x][e] = fmaf(pu, F4::get(vr[u][x], e), o[x][e]);
-      });
-    }
+            for (int e = 0; e < 4; ++e) o[x][e] = fmaf(pu, F4::get(vr[u][x], e), o[x][e]);
+        });
+      }
     }
     if (sizeof(T) == 4) {  // component 3: the keys of the retrieved (cluster, block) pairs, with the full query
       for (int bp = 0; bp < b; ++bp) {
