@@ -35,8 +35,6 @@ constexpr int TR128 = 128;  // keys of a workgroup's tile of dK / dV at D = 128
 using lds_frag = __attribute__((address_space(3))) const bf16x8_t*;
 using lds_f4 = __attribute__((address_space(3))) const f32x4_t*;
 using lds_tr = __attribute__((address_space(3))) s16x4_t*;
-template <typename T>
-__device__ __forceinline__ uint32_t lds_addr(const T* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const T*)p; }
 
 __device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 // 16 bytes of every lane from base + off to LDS at at + 16 lane.  Written out, because behind the builtin the compiler lets every
@@ -797,12 +795,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 }
 
 }  // namespace
-
-// The order of the tiles as in the forward (attn_fwd.hip): long ones first, over as many groups of an XCD as have 8 MB of rows.
-static int chunk_groups(int Bs, int D, int groups) {
-  const int fit = (8 << 20) / (4 * D) / Bs, all = (groups + 7) / 8;
-  return fit < 1 ? 1 : fit < all ? fit : all;
-}
 
 // Where a workgroup's fixed part (operands of 256 rows, the masked steps, 64 KB of results) shows, the kernels of 128 rows with two
 // or three workgroups on a CU are better.  us, 128 rows / 256 rows:

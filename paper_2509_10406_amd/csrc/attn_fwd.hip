@@ -63,10 +63,6 @@ __device__ __forceinline__ float sum8(const bf16x8_t& v, float acc) {
 // comes out even: 128 of 4 54 / 44 / 46, 64 of 8 85 / 61 / 63, 8 of 64 (exact attention over 16k) 295 / 285 / 294, 128 of 32 1550 /
 // 1429 / 1436.
 static int fold_tiles(int tpg, int groups) { return tpg % 2 == 0 && (long long)(tpg / 2) * groups % 256 == 0; }
-static int chunk_groups(int Bs, int D, int groups) {
-  const int fit = (8 << 20) / (4 * D) / Bs, all = (groups + 7) / 8;
-  return fit < 1 ? 1 : fit < all ? fit : all;
-}
 
 // The end of a phase.  No release or acquire: what the waves exchange are rows that arrive in LDS by themselves and are
 // waited for by count, and every LDS read of a phase has fed a matrix instruction before the phase ends.
@@ -80,7 +76,6 @@ __device__ __forceinline__ void phase_end() {
 
 using lds_frag = __attribute__((address_space(3))) const bf16x8_t*;
 using lds_tr = __attribute__((address_space(3))) s16x4_t*;
-__device__ __forceinline__ uint32_t lds_addr(const bf16_t* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16_t*)p; }
 
 template <int D>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) k_flash_fwd(

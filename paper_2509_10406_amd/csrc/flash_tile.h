@@ -37,6 +37,11 @@ static inline dim3 flash_grid_of(int tiles, int groups) {
   const int y = (groups + 7) / 8, most = 65535;
   return dim3(8 * tiles, y < most ? y : most, (y + most - 1) / most);
 }
+// `chunk`: as many groups of an XCD as have 8 MB of keys and values (or queries and their gradients), measured in attn_fwd.hip
+static inline int chunk_groups(int Bs, int D, int groups) {
+  const int fit = (8 << 20) / (4 * D) / Bs, all = (groups + 7) / 8;
+  return fit < 1 ? 1 : fit < all ? fit : all;
+}
 
 // The backward kernels' tiles of 128 rows: of a block, or of the whole sequence when the block size is not a multiple of 128.
 __device__ __forceinline__ FlashTile flash_tile(int N, int Bs, int H, int nbatch) {

@@ -6,6 +6,9 @@
 
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 
+template <typename T>
+__device__ __forceinline__ uint32_t lds_addr(const T* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const T*)p; }
+
 // Four k-slots of a transposed operand straight from a row-major tile: the 16 lanes of a group name rows r0 .. r0+3
 // (lane s: row r0 + s / 4, columns c0 + 4 (s % 4) ..) and each receives its own column c0 + s of the four.
 __device__ __forceinline__ s16x4_t lds_tr4(const bf16_t* p) {
