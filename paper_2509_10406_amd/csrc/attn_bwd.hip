@@ -802,7 +802,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 //           groups, 51 / 41 at 128, 33 / 28 at 64, 24 / 26 at 32 (128 tiles of 256 rows: half of the chip's CUs); of 2048 39 / 42 at
 //           16 groups, 55 / 46 at 32.  D = 128: 81 / 86 (640, 256 groups), 164 / 147 (1024, 256), 37 / 41 (1024, 32), 65 / 67 (2048, 16).
 //   dK/dV   blocks of 256 74 / 81 at 1024 groups, 15 / 16 at 64; of 320 110 / 98 and 18 / 18; of 128 37 / 41 and 12 / 11.  D = 128:
-//           blocks of 384 223 / 255 at 1024 groups, 25 / 24 at 64; of 512 107 / 105 at 256, 31 / 29 at 64; of 640 454 / 459 and 45 / 35
+//           blocks of 384 223 / 255 at 1024 groups, 25 / 24 at 64; of 512 107 / 105 at 256, 31 / 29 at 64; of 640 454 / 459 and 45 / 35.
+//           Few groups need no clause here, although the larger tiles halve the workgroups at D = 64: the longest tile sets the
+//           time, and it has twice the keys but reads each query once for them.  At 1 group and at 16: blocks of 320 17 / 16 and 17 /
+//           16, of 512 19 / 20 and 20 / 20, of 1024 31 / 30 and 31 / 31, of 2048 53 / 51 and 53 / 52, of 4096 98 / 92 and 140 / 98,
+//           of 16k 574 / 386 and 1200 / 948; four query heads per group 56 / 51 and 57 / 52 (512), 2158 / 1412 and 5011 / 3717 (16k).
+//           D = 128: of 512 26 / 25 and 27 / 26, of 2048 77 / 68 and 79 / 69, of 16k 1148 / 975 and 2673 / 2187.
 bool muse_attn_dq_wide(const MuseDims& d, int Bs) {
   return Bs >= 4 * TR && (long long)((Bs + TR - 1) / TR) * d.B * d.Hq * (d.N / Bs) > 128;
 }

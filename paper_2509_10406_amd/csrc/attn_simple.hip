@@ -11,6 +11,8 @@ namespace {
 
 // Bound by the rows: 16 bytes per lane, D sizeof(T) / 16 lanes per row, kDeltaRows rows of a lane requested together.  (A wave per
 // row and a value per lane took 160 us at 16 heads of 64k, 57 at 32 heads of 8k with D = 128; 46 and 20 now, 22 -> 7 at 8 heads of 16k.)
+// A row's sum is added up within the lane first: another order of the fp32 sums than a wave per row had (differences of a last bit,
+// which flip the rounding of a bf16 dS now and then; against 64 bits both are equally far).
 // O may lie anywhere (no other kernel reads it): WIDE is for 16-byte boundaries, the other form loads value by value, same sums.
 constexpr int kDeltaRows = 4;
 template <typename T, int D, bool WIDE>

@@ -988,8 +988,12 @@ __global__ void __launch_bounds__(64) k_key_norm_max(const float* __restrict__ p
 // become an operand; with every lane loading its own operand (32 bytes of 32 rows per instruction) the loads took 4 times as many
 // cache lines, and at D = 128 37 registers spilled.  us, before / now: 6170 / 4230 at 32 heads of 32k with 128 x 512 clusters, D =
 // 128 (15 GB of summaries); D = 64: 3620 / 3330 at 16 heads of 64k with 256 x 1024, 155 / 131 at 8 heads of 16k with 64 x 256.
-// At D = 64 that is with three waves per SIMD, for which the tiles take turns in one buffer of LDS (r <= 16; with two waves and a
-// buffer more 3600 and 153); at D = 128 the registers allow two.
+// At D = 64 that is with three waves per SIMD, for which the tiles take turns in one buffer of LDS (with two waves and a
+// buffer more 3600 and 153); at D = 128 the registers allow two.  The candidates' lists of r = 9 .. 16 leave LDS for ten waves of a
+// CU, not twelve: 824 with three waves per SIMD, 862 with two, 870 before at 16 heads of 32k with 64 x 512 and r = 9, 998 / 1073 / 1082 with
+// r = 16, 131 / 130 / 128 at 8 heads of 8k.  With r > 16 it is six waves, and 3 to 8 % slower than before (1638 -> 1686 with r = 17, 2447 ->
+// 2472 with r = 32), whether the rows go through LDS or not; so are calls with fewer tiles than CUs, which wait for one wave's
+// chain of tiles: 190 -> 216 at one head of 8k with 8 x 2048, 116 -> 128 of 16k with 16 x 1024.
 template <int D, int RCAP>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 && RCAP < 32 ? 3 : 2, D == 64 && RCAP < 32 ? 3 : 2))) k_farfield_fwd_b(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ A_kb, const uint16_t* __restrict__ A_km,

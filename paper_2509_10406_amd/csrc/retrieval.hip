@@ -18,7 +18,9 @@ namespace {
 // position) without any atomic deciding an order.
 // us of the two passes, with eight waves per slice that shared the pairs and went through the distinct ones of a chunk one by
 // one, in both passes / now: 222 + 327 / 36 + 129 at 16 heads of 64k with 256 x 1024 clusters, 245 + 298 / 29 + 75 with 128 x 128, 440 +
-// 667 / 67 + 201 at 32 heads of 32k with 128 x 512 and r = 16, 17 + 28 / 7 + 12 at 12 heads of 6k.
+// 667 / 67 + 201 at 32 heads of 32k with 128 x 512 and r = 16, 17 + 28 / 7 + 12 at 12 heads of 6k.  With the most pairs there can be (15 blocks
+// x 2048 clusters, 120 KB of counters: one wave of the second pass on a CU), the two together: 55 / 51 at one head of 8k, 192 / 189 at one
+// of 64k, 647 / 519 at 16 heads of 16k, 2929 / 1235 there with r = 32 and k2 = 2, 1704 / 846 at 16 heads of 64k.
 constexpr int kHitWaves = 8;   // of the workgroup that counts
 constexpr int kHitSlots = 8;   // selection slots requested together
 
