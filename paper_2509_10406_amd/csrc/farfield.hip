@@ -1322,9 +1322,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 // Bound by the rows, 10 to 12 TB/s of them from the L2 (a row is read again for every query that retrieved its chain).  Working the
 // scalars of a block out in one lane, with one maximum per cluster instead of one per row (l and the values are added up against
 // it: another order of the same sums than row by row), saves a third of the vector instructions; the order of the queries is at
-// far_position.  us of the three together, before / now: 3285 / 3095 at 32 heads of 32k with D = 128 and 128 x 512 clusters, 2692 / 2670
-// at 32 heads of 64k with rotary rows, 1158 / 1114 at 16 heads of 64k with 256 x 1024, 74 / 50 at 12 heads of 6k with 23 x 71,
-// 193 / 145 at 4 fp32 heads of 8k.
+// far_position.  us of the three together, before / now: 3771 / 3450 at 32 heads of 32k with D = 128 and 128 x 512 clusters, 3104 / 2853
+// at 32 heads of 64k with rotary rows, 1136 / 1039 at 16 heads of 64k with 256 x 1024, 73 / 52 at 12 heads of 6k with 23 x 71,
+// 160 / 120 at 4 fp32 heads of 8k.
 // ------------------------------------------------------------------------------------------
 template <typename T, int D, int NBC>
 __global__ void __launch_bounds__(256) k_comp2_fwd(
@@ -1337,8 +1337,8 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
   const int hl = blockIdx.y, hq = h0 + hl;
   const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);
   const int l16 = threadIdx.x % 16;
-  const int pos = far_position(N);
-  if (pos < Bs) return;
+  const int pos = far_position(Bs, nb);
+  if (pos < 0) return;
   const int n = perm_q[(size_t)hq * N + pos];
   const size_t qn = (size_t)hq * N + n;
   const int b = n / Bs, i = aq[qn], NBm = nb - 1;
@@ -1352,13 +1352,10 @@ __global__ void __launch_bounds__(256) k_comp2_fwd(
     qt[x][0] = scale * (q4[0] - c4.x); qt[x][1] = scale * (q4[1] - c4.y);
     qt[x][2] = scale * (q4[2] - c4.z); qt[x][3] = scale * (q4[3] - c4.w);
   }
-  // the four queries of a wave are neighbours in the block-major order: the largest b among them (wave-uniform)
-  // bounds the block loops, so a wave of block-1 queries handles one summary row per cluster, not eight
+  // the four queries of a wave are of one block, which bounds the block loops: a wave of block-1 queries handles one summary
+  // row per cluster, not eight
   // (the bound is a template constant of the loop body below: one straight-line body per value, loads batched)
-  int bwv = b;
-  bwv = max(bwv, __shfl_xor(bwv, 16, 64));
-  bwv = max(bwv, __shfl_xor(bwv, 32, 64));
-  bwv = __builtin_amdgcn_readfirstlane(bwv);
+  const int bwv = __builtin_amdgcn_readfirstlane(b);
   float m = MUSE_NEG_INF, l = 0.f, o[NG][4];
 #pragma unroll
   for (int x = 0; x < NG; ++x)

@@ -254,10 +254,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 // retrieved cluster, the summaries of the preceding blocks that were NOT retrieved contribute  dl k-bar  with
 // dl = p (dO.v-bar - delta),  p = exp(q~.k-bar + mu-bar - LSE).  The retrieval's share is added here too: bf16 inputs
 // have per-pair dq partials, fp32 inputs walk the retrieved keys, kKeys of them requested together.  The sum is added to
-// the row the tile kernel wrote.  us, every lane summing every block's product and without far_position's order / now: 4166 / 3709
-// at 32 heads of 32k with D = 128, 1240 / 1164 at 16 heads of 64k, 1097 / 983 with 128 x 128 clusters, 110 / 70 at 12 heads of
-// 6k, 196 / 143 at 4 fp32 heads of 8k.  (fp32 inputs had both in the tile kernel, a lane pair per query and a key per round trip:
-// 384 us at 4 heads of 8k, r = 4, against 44 + 143 for the two kernels now.)
+// the row the tile kernel wrote.  us, every lane summing every block's product and without far_position's order / now: 4498 / 3996
+// at 32 heads of 32k with D = 128, 1235 / 1121 at 16 heads of 64k, 1103 / 981 with 128 x 128 clusters, 111 / 73 at 12 heads of
+// 6k, 162 / 120 at 4 fp32 heads of 8k.  (fp32 inputs had both in the tile kernel, a lane pair per query and a key per round trip:
+// 384 us at 4 heads of 8k, r = 4, against 44 + 120 for the two kernels now.)
 // ------------------------------------------------------------------------------------------
 template <typename T, int D, int NBC>
 __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
@@ -271,8 +271,8 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
   constexpr bool kF32 = sizeof(T) == 4;
   const int hl = blockIdx.y, hq = h0 + hl;
   const int l16 = threadIdx.x % 16;
-  const int pos = far_position(N);
-  if (pos < Bs) return;
+  const int pos = far_position(Bs, nb);
+  if (pos < 0) return;
   const int n = perm_q[(size_t)hq * N + pos];
   const size_t qn = (size_t)hq * N + n;
   const int b = pos / Bs, i = aq[qn], NBm = nb - 1;
@@ -298,13 +298,9 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
   float4 oldq[NG];
 #pragma unroll
   for (int x = 0; x < NG; ++x) oldq[x] = *reinterpret_cast<const float4*>(dQ + qn * D + 64 * x + 4 * l16);
-  // the four queries of a wave are neighbours in the block-major order: the largest b among them (wave-uniform)
-  // bounds the block loops
+  // the four queries of a wave are of one block, which bounds the block loops
   // (the bound is a template constant of the loop body below: one straight-line body per value, loads batched)
-  int bwv = b;
-  bwv = max(bwv, __shfl_xor(bwv, 16, 64));
-  bwv = max(bwv, __shfl_xor(bwv, 32, 64));
-  bwv = __builtin_amdgcn_readfirstlane(bwv);
+  const int bwv = __builtin_amdgcn_readfirstlane(b);
   // places in the head's summaries, in units of the lane's share of a row (16 bytes of s_k); 32 bits hold them
   using F4 = Frag<T, 4>;
   const int u8 = l16 & 7;  // the key block (of eight) whose scalars this lane has
