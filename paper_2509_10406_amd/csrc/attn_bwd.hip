@@ -18,8 +18,9 @@
 // Measured, us, 128 rows per workgroup and 32 per wave -> this: dK/dV 640 -> 465 at 8 heads of 16k, 200 -> 135 at 32 heads of 4k,
 // 82 -> 52 at 128 heads of 1k; dQ 440 -> 370, 150 -> 104, 51 -> 41; dQ at D = 128 791 -> 641 at 32 heads of 8k, 241 -> 175 of 4k; dK/dV
 // at D = 128 (before: 32 keys and one matrix phase per wave) 1210 -> 1012, 339 -> 287, 149 -> 120 at 128 heads of 1k.  Cycles
-// per step (of 2048 in matrix instructions) 3050 for dK/dV, of 1536 2420 for dQ (D = 128: of 3072 4380); the clock falls to 1.75
-// GHz meanwhile (2.2 on zeros): what is left is the chip's power.
+// per step (of 2048 in matrix instructions) 3050 for dK/dV, of 1536 2420 for dQ (D = 128: of 3072 4380).  The clock is below its 2.4
+// GHz meanwhile: 1.7 to 1.8 in the first passes after a pause (GRBM_GUI_ACTIVE over the time), 2.0 where calls follow one another (2.2
+// for dK/dV at D = 128): the times above are of calls in a row, a single pass takes 10 to 35 % longer.
 #include <type_traits>
 
 #include "ff_common.h"
