@@ -184,24 +184,27 @@ __device__ __forceinline__ bf16x8_t ld_tr8(const bf16_t* row, int r0, int half) 
 
 // The queries of the kernels that read the retrieved chains' summaries per query (k_comp2_fwd, k_comp2_bwd_dq), 16 lanes per query:
 // this group's place in the bucketed order (block by block, cluster by cluster), negative: none.  Workgroups go to the 8 XCDs
-// round-robin.  A block's queries are cut into runs of up to 16 workgroups, eight of them at least where it has the queries; an XCD takes
+// round-robin.  A block's queries are cut into runs of up to 16 workgroups, eight or a multiple of eight of them; an XCD takes
 // a run of the last block, the same one of the block before, and so on, then its next run.  So the queries that it has at one
 // time are of a few clusters, whatever their block, and read the same rows, and the last blocks, whose queries have the most work, go
 // first.  (Clusters lie at about the same share of every block; nothing but speed depends on it.)  Which XCD has the first run
 // changes with the head, or the runs left over at the end would all be the first XCDs'.
 // us of k_comp2_fwd / k_comp2_bwd_dq with other orders: block by block in runs of 32, which leaves the last XCDs idle at every head's end / the same
 // with that turn, from the last block / exactly cluster by cluster, an eighth per XCD, for which a place takes two more round trips / now:
-//   32 heads of 64k, rotary rows, 256 x 1024      3125 / 3108, 3113 / 3085, 2890 / 3024, 2820 / 2952
-//   32 heads of 32k, D = 128, 128 x 512, r = 16   3760 / 4113, 3606 / 4081, 3507 / 4044, 3435 / 3998
-//   16 heads of 64k, 256 x 1024; 128 x 128        1156 / 1164, 1094 / 1149, 1125 / 1187, 1054 / 1122; 907 / 1006, 862 / 996, 921 / 1032, 844 / 971
-//   8 heads of 16k; 12 of 6k; 4 fp32 of 8k        87 / 91, 77 / 80, 88 / 89, 78 / 81; 71 / 97, 50 / 75, 55 / 77, 53 / 75; 149 / 146, 132 / 128, 130 / 127, 121 / 119
-// Runs of 32: 2900 / 3018, 3612 / 4092, 1071 / 1143; of 8: 2843 / 2951, 3509 / 3955, 1084 / 1126.
-static inline __host__ __device__ int far_run(int Bs) { return Bs >= 2048 ? 16 : Bs >= 128 ? Bs / 128 : 1; }
-static inline __host__ __device__ int far_runs(int Bs) { return (Bs + 16 * far_run(Bs) - 1) / (16 * far_run(Bs)); }
+//   32 heads of 64k, rotary rows, 256 x 1024      3125 / 3108, 3113 / 3085, 2890 / 3024, 2779 / 2945
+//   32 heads of 32k, D = 128, 128 x 512, r = 16   3760 / 4113, 3606 / 4081, 3507 / 4044, 3371 / 3973
+//   16 heads of 64k, 256 x 1024; 128 x 128        1156 / 1164, 1094 / 1149, 1125 / 1187, 1040 / 1115; 907 / 1006, 862 / 996, 921 / 1032, 825 / 977
+//   8 heads of 16k; 12 of 6k; 4 fp32 of 8k        87 / 91, 77 / 80, 88 / 89, 75 / 79; 71 / 97, 50 / 75, 55 / 77, 49 / 71; 149 / 146, 132 / 128, 130 / 127, 121 / 118
+// Runs of 32 in the first three: 2900 / 3018, 3612 / 4092, 1071 / 1143; of 8: 2843 / 2951, 3509 / 3955, 1084 / 1126 (of 16 on that box 2820 /
+// 2952, 3435 / 3998, 1054 / 1122).
+static inline __host__ __device__ int far_run(int Bs) {  // workgroups of a run: at most 16, as many runs for every XCD
+  const int wgs = (Bs + 15) / 16, turns = (wgs + 127) / 128;
+  return (wgs + 8 * turns - 1) / (8 * turns);
+}
 __device__ __forceinline__ int far_position(int Bs, int nb) {
   const int run = far_run(Bs), g = blockIdx.x / 8 / run, k = g / (nb - 1) * 8 + (blockIdx.x + blockIdx.y) % 8;
   const int at = (k * run + blockIdx.x / 8 % run) * 16 + threadIdx.x / 16;
-  return k < far_runs(Bs) && at < Bs ? (nb - 1 - g % (nb - 1)) * Bs + at : -1;
+  return at < Bs ? (nb - 1 - g % (nb - 1)) * Bs + at : -1;
 }
 
 // What a 16-lane group does with one value per key block, eight of them at a time: the dims' partial sums of all eight meet in
@@ -360,7 +363,10 @@ static inline size_t ff_segcnt_bytes(const MuseDims& d) {
 // x extent of the forward tile kernels' grid: the tiles of a (head, block) pair, rounded up to the 8 XCDs
 static inline size_t ff_tile_grid_x(const MuseDims& d) { return (size_t)(d.Bs / 32 + d.Cq + 1 + 7) / 8 * 8; }
 // the grid of far_position (nb > 1)
-static inline dim3 far_grid(const MuseDims& d, int hn) { return dim3(8 * ((far_runs(d.Bs) + 7) / 8) * (d.nb - 1) * far_run(d.Bs), hn); }
+static inline dim3 far_grid(const MuseDims& d, int hn) {
+  const int round = 16 * 8 * far_run(d.Bs);  // queries of a block in a run for every XCD
+  return dim3((d.Bs + round - 1) / round * 8 * (d.nb - 1) * far_run(d.Bs), hn);
+}
 static inline size_t ff_flag_bytes(const MuseDims& d) {
   return (size_t)d.B * d.Hq * (d.nb > 1 ? d.nb - 1 : 1) * ff_tile_grid_x(d) * 4;
 }
