@@ -47,13 +47,11 @@ def kernel_models(w, p):
     m["k_flash_bwd_dkv"] = ("mfma", PEAK["mfma_bf16"], 4 * N * Bs * D * H, "flop")       # S, dP, dV, dK
     # k-means assignment: one launch per tensor per pass; report the key launch (larger C)
     m["k_assign_bf16"] = ("mfma", PEAK["mfma_bf16"], 2 * N * Ck * D * Hk, "flop")
-    # forward tile kernel: two passes over k-bar (scores for the selection, then scores again + monopole PV).
-    # bf16 inputs: the scores run on 16-bit MFMA and the kernel streams each (block, query cluster) group's
-    # summaries once per pass: the bf16 plane of k-bar in the first (with r > 0; both planes with r = 0), both planes
-    # and v-bar in the second, the per-cell scalar in both; fp32 inputs: fp32 MFMA decides
+    # forward tile kernel.  bf16 inputs: the scores run on 16-bit MFMA and the kernel streams each (block, query cluster)
+    # group's summaries once: both planes of k-bar, v-bar and the per-cell scalar; fp32 inputs: two passes over k-bar (scores
+    # for the selection, then scores again + monopole PV), and fp32 MFMA decides
     if es == 2:
-        first = D * 2 if r > 0 else 2 * D * 2
-        m["k_farfield_fwd"] = ("hbm", PEAK["hbm"], (cells * (first + 2 * D * 2 + D * es + 2 * 4) + 2 * Nff * D * 4) * H, "byte")
+        m["k_farfield_fwd"] = ("hbm", PEAK["hbm"], (cells * (2 * D * 2 + D * es + 4) + 2 * Nff * D * 4) * H, "byte")
     else:
         m["k_farfield_fwd"] = ("mfma", PEAK["mfma_fp32"], 2 * 2 * Nff * Ck * D * H, "flop")
     if es == 2:
@@ -91,7 +89,7 @@ def algorithmic_bytes(w):
     the tile kernel (cluster scores, top-r and monopole values) reads the accumulated summaries once,
     Cq Ck (nb-1) (2 D 2 + 4) bytes per head; the summary kernel writes the summaries once, Cq Ck nb (2 D 2 + 4)
     bytes per head.  The kernels' own byte models (kernel_models) count what THEY stream: a second plane of the
-    key summaries that keeps the selection reproducible, a second pass over them, fp32 scalars; measured traffic
+    key summaries that keeps the selection reproducible, fp32 scalars; measured traffic
     above these figures is what a better kernel could still save."""
     H, D, Cq, Ck = w.B * w.Hq, w.D, w.Cq, w.Ck
     nb = w.N // w.Bs
@@ -347,8 +345,8 @@ def measured_traffic(kernel, workload):
     try:
         with open(path) as f:
             ks = json.load(f)["kernels"]
-        # the profiler's stage name covers the one-plane kernel and the launch that takes the tiles it left
-        names = {"k_farfield_fwd": ["k_farfield_fwd_b", "k_farfield_fwd"]}.get(kernel, [kernel])
+        # the profiler's stage name covers the kernels of both input types
+        names = {"k_farfield_fwd": ["k_farfield_tiles", "k_farfield_fwd"]}.get(kernel, [kernel])
         ts = [ks[n] for n in names if n in ks]
         return float(sum(t["fetch_bytes"] + t["write_bytes"] for t in ts)) if ts else None
     except (OSError, ValueError, KeyError):

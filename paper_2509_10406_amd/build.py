@@ -7,7 +7,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmuse.so")
-SOURCES = ["muse_api.hip", "kmeans.hip", "attn_simple.hip", "attn_fp32.hip", "attn_fwd.hip", "attn_bwd.hip", "attn_mfma.hip", "farfield.hip", "farfield_bwd.hip", "cell_grads.hip", "chain_grads.hip", "retrieval.hip", "retrieval_fp32.hip", "retrieval_kv.hip", "retrieval_q.hip", "dipole.hip", "probe.hip"]
+SOURCES = ["muse_api.hip", "kmeans.hip", "attn_simple.hip", "attn_fp32.hip", "attn_fwd.hip", "attn_bwd.hip", "attn_mfma.hip", "farfield.hip", "farfield_tiles.hip", "farfield_bwd.hip", "cell_grads.hip", "chain_grads.hip", "retrieval.hip", "retrieval_fp32.hip", "retrieval_kv.hip", "retrieval_q.hip", "dipole.hip", "probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # attn_bwd.hip: matrix instructions write vector registers; what stays in accumulation registers is said there

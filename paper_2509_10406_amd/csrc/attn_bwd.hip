@@ -38,13 +38,6 @@ using lds_f4 = __attribute__((address_space(3))) const f32x4_t*;
 using lds_tr = __attribute__((address_space(3))) s16x4_t*;
 
 __device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-// 16 bytes of every lane from base + off to LDS at at + 16 lane.  Written out, because behind the builtin the compiler lets every
-// LDS read wait for the rows; they are waited for by count (the caller's s_waitcnt vmcnt) in front of a
-// barrier.  m0 is reserved and cannot be named as clobbered; nothing else in these kernels uses it (tests/test_attn_bwd_code.py looks
-// through the machine code for that, and for the wait states that mfma_acc needs).
-__device__ __forceinline__ void rows_to_lds(uint32_t at, uint32_t off, const bf16_t* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
-}
 __device__ __forceinline__ void group_barrier() {
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

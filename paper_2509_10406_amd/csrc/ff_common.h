@@ -101,66 +101,6 @@ __device__ __forceinline__ f32x16_t score_tile(const float* __restrict__ Amu, co
   return score_ktile<D>(kt, j0, Ck, qt, half);
 }
 
-// The same tile for bf16 inputs, where the scores run on the 16-bit matrix cores without losing the precision
-// that decides selections: k-bar is stored as a bf16 plane plus an fp16 plane of the remainder (together 19
-// significant bits or more), the query operand is the bf16 query itself (exact, also as fp16), and the query
-// centroid's share of q~ . k-bar is a per-cell scalar c = scale * qc_i . k-bar, the weighted mean of the tilt
-// logits that the kernel which wrote the planes has at hand:  score = scale * q . (hi + mid) + (mu-bar - c).
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
-template <int D>
-struct KTileH {
-  uint4 h[D / 16], m[D / 16];
-  float mu[16];
-};
-
-template <int D>
-__device__ __forceinline__ void load_ktile_h(KTileH<D>& kt, const float* __restrict__ Amuq,
-                                             const bf16_t* __restrict__ Akb, const uint16_t* __restrict__ Akm, int j0,
-                                             int Ck, int col, int half) {
-  int c = j0 + col;
-  c = c < Ck ? c : Ck - 1;
-  const bf16_t* rh = Akb + (size_t)c * D + 8 * half;
-  const uint16_t* rm = Akm + (size_t)c * D + 8 * half;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
-    kt.h[ks] = *reinterpret_cast<const uint4*>(rh + 16 * ks);
-    kt.m[ks] = *reinterpret_cast<const uint4*>(rm + 16 * ks);
-  }
-  if ((Ck & 3) == 0) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      int base = j0 + 8 * g + 4 * half;
-      base = base < Ck ? base : Ck - 4;
-      const float4 m4 = *reinterpret_cast<const float4*>(Amuq + base);
-      kt.mu[4 * g] = m4.x; kt.mu[4 * g + 1] = m4.y; kt.mu[4 * g + 2] = m4.z; kt.mu[4 * g + 3] = m4.w;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      int jr = j0 + 8 * (e / 4) + 4 * half + (e % 4);
-      kt.mu[e] = Amuq[jr < Ck ? jr : Ck - 1];
-    }
-  }
-}
-
-// qb: the lane's query (column) dims 16 ks + 8 half .. + 7 as bf16; qh(ks): the same as fp16
-template <int D, typename F>
-__device__ __forceinline__ f32x16_t score_ktile_h(const KTileH<D>& kt, int j0, int Ck, const bf16x8_t (&qb)[D / 16], F qh,
-                                                  float scale, int half) {
-  f32x16_t acc = zero16();
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kt.h[ks]), qb[ks], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, kt.m[ks]), qh(ks), acc, 0, 0, 0);
-  }
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int jr = j0 + 8 * (e / 4) + 4 * half + (e % 4);
-    acc[e] = jr < Ck ? fmaf(scale, acc[e], kt.mu[e]) : MUSE_NEG_INF;
-  }
-  return acc;
-}
-
 // bf16 MFMA (v_mfma_f32_32x32x16_bf16) helpers.  pack8: accumulator rows 4*g0..+3 and 4*g1..+3 of a lane
 // become the 8 k-slots of a B (or A) operand; the matching other operand must use the same row order.
 __device__ __forceinline__ bf16x8_t pack8(const f32x16_t& s, int g0, int g1) {
@@ -171,15 +111,6 @@ __device__ __forceinline__ bf16x8_t pack8(const f32x16_t& s, int g0, int g1) {
     r[4 + t] = (__bf16)s[4 * g1 + t];
   }
   return r;
-}
-
-// A operand for the second contraction from a transposed LDS tile `row` ([..][BN+8]): the 8 k-slots
-// of lane half `half` over the 16 rows starting at r0
-__device__ __forceinline__ bf16x8_t ld_tr8(const bf16_t* row, int r0, int half) {
-  uint2 a = *reinterpret_cast<const uint2*>(row + r0 + 4 * half);
-  uint2 b = *reinterpret_cast<const uint2*>(row + r0 + 8 + 4 * half);
-  uint4 v = make_uint4(a.x, a.y, b.x, b.y);
-  return *reinterpret_cast<bf16x8_t*>(&v);
 }
 
 // The queries of the kernels that read the retrieved chains' summaries per query (k_comp2_fwd, k_comp2_bwd_dq), 16 lanes per query:
@@ -304,8 +235,6 @@ struct FFWorkspace {
   uint2* hits;                   // x = n | g << 22 (query position, head inside the KV group), y = slot*k2e + u
   size_t hit_cap;                // hits per kv head
   float* ret_part;               // bf16 inputs, per (query, slot, u): forward partial rows [D], then (max, sum) [2] of all rows; or dq partial rows [D]
-  float* knorm;                  // [HK]: largest Euclidean norm of a key row of the kv head (bf16 inputs); then [HK][64] partial maxima
-  int32_t* ff_flag;              // [HQ][nb-1][ff_tile_grid_x]: tiles the one-plane forward kernel leaves to the two-plane one
   float *dKs, *dVs;            // fp32 gradients in bucketed key order
   float* c3_part;              // r > 0: [slices - 1][HK][N][2][D] partial dK | dV rows of the later hit slices of a pair (fp32: over ff_acc)
   float *dQacc, *dKacc, *dVacc;  // fp32 gradients in sequence order (alias the outputs when they are fp32)
@@ -367,9 +296,6 @@ static inline dim3 far_grid(const MuseDims& d, int hn) {
   const int round = 16 * 8 * far_run(d.Bs);  // queries of a block in a run for every XCD
   return dim3((d.Bs + round - 1) / round * 8 * (d.nb - 1) * far_run(d.Bs), hn);
 }
-static inline size_t ff_flag_bytes(const MuseDims& d) {
-  return (size_t)d.B * d.Hq * (d.nb > 1 ? d.nb - 1 : 1) * ff_tile_grid_x(d) * 4;
-}
 static inline size_t ff_fixed_bytes(const MuseDims& d, bool bwd) {
   size_t HQ = (size_t)d.B * d.Hq, HK = (size_t)d.B * d.Hkv, N = d.N, D = d.D;
   size_t es = d.dtype == MUSE_DTYPE_BF16 ? 2 : 4;
@@ -382,7 +308,6 @@ static inline size_t ff_fixed_bytes(const MuseDims& d, bool bwd) {
     b += 4 * ff_al(HK * ((size_t)d.nb * d.Ck + 1) * 4) + 2 * ff_al(ff_segcnt_bytes(d)) +
          ff_al(HK * ff_run_cap(d) * 8) + ff_al(HQ * N * R2 * 8);
   if (es == 2) b += ff_al(HK * ff_run_cap(d) * 16) + ff_al(ff_ret_part_bytes(d));
-  b += ff_al(HK * 65 * 4) + ff_al(ff_flag_bytes(d));
   if (bwd) {
     b += ff_al(HQ * N * 4) + ff_al(HQ * N * W * 4) + ff_al(HQ * N * (size_t)(d.r > 0 ? d.r : 1) * 4) + 2 * ff_al(HK * N * D * 4) +
          ff_al(HQ * N * D * 4) + ff_al(HQ * D * (size_t)((d.Cq + 31) / 32 * 32) * 2);
@@ -410,6 +335,9 @@ int muse_ff_prepare(const MuseDims& d, const T* K, const T* V, const int32_t* aq
                     hipStream_t st);
 template <typename T>
 int muse_ff_summaries(const MuseDims& d, const float* qc, FFWorkspace& w, int h0, int hn, hipStream_t st);
+// farfield_tiles.hip: the far-field forward's tile kernel of bf16 inputs
+int muse_launch_farfield_tiles(const MuseDims& d, const void* Q, const FFWorkspace& w, int32_t* selc, int h0, int hn,
+                               hipStream_t st);
 template <typename T>
 int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace& w, int h0, int hn, hipStream_t st);
 

@@ -42,3 +42,15 @@ __device__ __forceinline__ bf16x8_t tile_cols(const bf16_t* tile, int r0, int t,
   const int row = r0 + 4 * (lane / 32) + (lane % 16) / 4, col = 32 * t + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
   return tr_join(tile_tr4<D>(tile, row, col), tile_tr4<D>(tile, row + 8, col));
 }
+
+// 16 bytes of every lane from base + off to LDS at at + 16 lane.  Written out, because behind the builtin the compiler lets every
+// LDS read wait for the rows; they are waited for by count (the caller's s_waitcnt vmcnt).  m0 is reserved and cannot be named as
+// clobbered; nothing else in the kernels that use this does (tests/test_attn_bwd_code.py and tests/test_farfield_code.py look
+// through the machine code for that).
+__device__ __forceinline__ void rows_to_lds(uint32_t at, uint32_t off, const bf16_t* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
+}
+// the same with 4 bytes of every lane, to at + 4 lane
+__device__ __forceinline__ void words_to_lds(uint32_t at, uint32_t off, const float* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
+}

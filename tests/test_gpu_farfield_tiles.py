@@ -1,4 +1,4 @@
-"""GPU parity of the far-field forward of bf16 inputs (k_farfield_fwd_b) where its tiles of 32 key clusters end: one cluster, one
+"""GPU parity of the far-field forward of bf16 inputs (k_farfield_tiles) where its tiles of 32 key clusters end: one cluster, one
 less and one more than a tile, three tiles with one cluster in the last, at both head dimensions and at every list length (8, 16
 and 32 candidates).  Tolerances are those of the parity suite."""
 import pytest
