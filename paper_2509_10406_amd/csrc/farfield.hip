@@ -491,14 +491,18 @@ __global__ void __launch_bounds__(64) k_block_summaries(const T* __restrict__ Ks
 //   E^T[key, i] = exp(L[i, key] - mu-bar[b, i, j]),   s_k^T[d, i] = sum_key K^T[d, key] E^T[key, i]
 // A cell's keys are read once for all its chains instead of once per chain, and the sums leave through an LDS
 // transpose as whole rows.
-// Bound by round trips: a chunk of 8 keys, then the rows out.  A cell of one chunk keeps its rows in registers over the passes and
-// has the next pass's logits requested before its rows go out; PIPE: longer cells have their chunks in two buffers, at D =
-// 64 for sixteen keys and more on average (one chunk at a time / PIPE at 16 heads of 64k: 554 / 568 with 8 keys, 566 / 570 with 12, 599 /
-// 597 with 16, 602 / 566 with 32, 691 / 615 with 64; D = 128 1259 / 1011 with 8).  us before / now: 873 / 795 at 16 heads of 64k with 256 x 1024 clusters (8 keys; with PIPE 831),
-// 4561 / 4305 at 32 heads (4778), 786 / 666 with 128 x 128 (64 keys; without 737), 2762 / 2514 at 32 heads of 32k, D = 128, 8 keys
-// (without 2767), 794 / 697 with 64.
-template <typename T, int D, bool PIPE>
-__global__ void __launch_bounds__(256) k_block_summaries_mx(const T* __restrict__ Ks, const T* __restrict__ Vs,
+// Bound by round trips: a chunk of 8 keys, then the rows out.  A cell of up to three chunks (two at D = 128, or where cells are long)
+// keeps its rows in registers over the passes, makes its weights once for keys and values, and has the next pass's logits
+// requested before its rows go out; longer cells have their chunks in two buffers.  LONG: four waves per SIMD, which the LDS allows
+// and which suits cells of 32 keys and more on average (16 at D = 128); else three, with registers for the third chunk.
+// us at 16 heads of 32k rotary rows with 64 x Ck clusters, one chunk held and the others in one or two buffers (before) / three waves / four:
+//   keys per cell    4               8               12              16              32              64
+//   D = 64           551, 503, 478   417, 340, 352   352, 278, 316   339, 258, 297   264, 247, 247   227, 227, 229
+//   D = 128          911, 754, 815   688, 557, 618   582, 528, 557   550, 552, 529   476, 522, 458   435, 484, 411
+// before / now: 809 / 666 at 16 heads of 64k with 256 x 1024 clusters, 4353 / 3700 at 32 with rotary rows, 2508 / 2170 at 32 heads of 32k
+// with D = 128, 128 x 512, 80 / 68 at 8 of 16k.  Plain instead of streaming stores: 840, 4785 and 2665 before.
+template <typename T, int D, bool LONG>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LONG ? 4 : 3, LONG ? 4 : 3))) k_block_summaries_mx(const T* __restrict__ Ks, const T* __restrict__ Vs,
                                                             const float* __restrict__ L, const int32_t* __restrict__ off_k,
                                                             const uint32_t* __restrict__ maskT,
                                                             const float* __restrict__ s_mu, float* __restrict__ s_k,
@@ -533,37 +537,40 @@ __global__ void __launch_bounds__(256) k_block_summaries_mx(const T* __restrict_
   const int lo = ok[b * Ck + j], hi = ok[b * Ck + j + 1];
   const int lrow = lane / 16;
   // the chains of pass `it`: this lane's query cluster, its mu-bar and its logits of keys c0 + 4 half + t
-  auto chain_of = [&](int it) { return (int)list[min(32 * it + col, nflag - 1)]; };
-  auto load_logits = [&](int il, int c0, float (&lg)[4]) {
-    const float* Li = L + ((size_t)hl * Cq + il) * N;
+  // (32-bit offsets from uniform pointers: at most 2048 clusters x 2^18 positions, 2^18 rows of 128)
+  auto chain_of = [&](int it) { return (uint32_t)list[min(32 * it + col, nflag - 1)]; };
+  const float* Lh = L + (size_t)hl * Cq * N;
+  auto load_logits = [&](uint32_t il, int c0, float (&lg)[4]) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) lg[t] = Li[min(c0 + 4 * half + t, hi - 1)];
+    for (int t = 0; t < 4; ++t) lg[t] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Lh) + (il * (uint32_t)N + (uint32_t)min(c0 + 4 * half + t, hi - 1)) * 4u);
   };
-  auto load_mu = [&](int il) { return s_mu[(((size_t)hl * NBm + b) * Cq + il) * Ck + j]; };
+  const float* muh = s_mu + ((size_t)hl * NBm + b) * Cq * Ck + j;
+  auto load_mu = [&](uint32_t il) { return muh[il * (uint32_t)Ck]; };
   // accumulator tile x, row m holds head dim 64 ds + 2 m + x: one paired load feeds both tiles
-  const T* Kh = Ks + (size_t)hk * N * D + 2 * col;
-  const T* Vh = Vs + (size_t)hk * N * D + 2 * col;
+  const T* Kh = Ks + (size_t)hk * N * D;
+  const T* Vh = Vs + (size_t)hk * N * D;
   using raw = typename Pair<T>::raw;
   auto load_rows = [&](int c0, int ds, raw (&kk)[4], raw (&vv)[4]) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int pc = min(c0 + 4 * half + t, hi - 1);
-      kk[t] = Pair<T>::ld(Kh, (size_t)pc * D + 64 * ds);
-      vv[t] = Pair<T>::ld(Vh, (size_t)pc * D + 64 * ds);
+      const uint32_t o = ((uint32_t)min(c0 + 4 * half + t, hi - 1) * D + 64 * ds + 2 * col) * (uint32_t)sizeof(T);
+      kk[t] = *reinterpret_cast<const raw*>(reinterpret_cast<const char*>(Kh) + o);
+      vv[t] = *reinterpret_cast<const raw*>(reinterpret_cast<const char*>(Vh) + o);
     }
   };
-  f32x16_t ak[2], av[2];
-  auto clear = [&]() { ak[0] = zero16(); ak[1] = zero16(); av[0] = zero16(); av[1] = zero16(); };
-  auto add = [&](int c0, float mu, const float (&lg)[4], const raw (&kk)[4], const raw (&vv)[4]) {
+  // a chunk's weights, and its rows added with them
+  auto weigh = [&](int c0, float mu, float (&lg)[4]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) lg[t] = c0 + 4 * half + t < hi ? __expf(lg[t] - mu) : 0.f;
+  };
+  auto add = [&](f32x16_t (&acc)[2], const float (&e)[4], const raw (&x)[4]) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const float e = c0 + 4 * half + t < hi ? __expf(lg[t] - mu) : 0.f;
-      ak[0] = mfma32(Pair<T>::lo(kk[t]), e, ak[0]);
-      ak[1] = mfma32(Pair<T>::hi(kk[t]), e, ak[1]);
-      av[0] = mfma32(Pair<T>::lo(vv[t]), e, av[0]);
-      av[1] = mfma32(Pair<T>::hi(vv[t]), e, av[1]);
+      acc[0] = mfma32(Pair<T>::lo(x[t]), e[t], acc[0]);
+      acc[1] = mfma32(Pair<T>::hi(x[t]), e[t], acc[1]);
     }
   };
+  const size_t cells = (((size_t)hl * NBm + b) * Cq * Ck + j) * D;  // the cell of query cluster 0; at most 2048 x 2048 x 128 elements behind it
   // rows out through the LDS transpose: 16 lanes write one row's 64 dims (an empty cell gives zero rows)
   auto emit = [&](const f32x16_t(&a)[2], bool values, int it, int ds) {
     const int nrow = min(nflag - 32 * it, 32);
@@ -578,69 +585,82 @@ __global__ void __launch_bounds__(256) k_block_summaries_mx(const T* __restrict_
       const int row = 4 * ps + lrow;
       if (row < nrow) {
         const float4 v = *reinterpret_cast<const float4*>(&tr[row][4 * (lane % 16)]);
-        const size_t o = ((((size_t)hl * NBm + b) * Cq + list[32 * it + row]) * Ck + j) * D + 64 * ds + 4 * (lane % 16);
+        const uint32_t o = (uint32_t)list[32 * it + row] * (uint32_t)(Ck * D) + 64 * ds + 4 * (lane % 16);
         const float v4[4] = {v.x, v.y, v.z, v.w};
-        if (values) st4_stream(s_v, o, v4);
-        else st4_stream(s_k, o, v4);
+        if (values) st4_stream(reinterpret_cast<T*>(reinterpret_cast<char*>(s_v + cells) + o * (uint32_t)sizeof(T)), 0, v4);
+        else st4_stream(reinterpret_cast<float*>(reinterpret_cast<char*>(s_k + cells) + o * 4u), 0, v4);
       }
     }
     wave_lds_fence();
   };
   const int npass = (nflag + 31) / 32;
-  if (lo < hi && hi - lo <= 8) {
-    // one chunk: its rows stay in registers over the passes, the next pass's logits are requested before this one's rows go
-    // out
-    raw kk[DS][4], vv[DS][4];
-    float lg[4], lgn[4], mu, mun;
+  // NC chunks: their rows stay in registers over the passes, the next pass's logits are requested before this one's rows go out
+  auto held = [&](auto chunks) {
+    constexpr int NC = decltype(chunks)::value;
+    raw kk[DS][NC][4], vv[DS][NC][4];
+    float lgn[NC][4], mun;
+    auto request = [&](int it) {
+      const uint32_t i = chain_of(it);
+      mun = load_mu(i);
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) load_rows(lo, ds, kk[ds], vv[ds]);
-    const int i0 = chain_of(0);
-    mun = load_mu(i0);
-    load_logits(i0, lo, lgn);
+      for (int c = 0; c < NC; ++c) load_logits(i, lo + 8 * c, lgn[c]);
+    };
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int ds = 0; ds < DS; ++ds) load_rows(lo + 8 * c, ds, kk[ds][c], vv[ds][c]);
+    request(0);
     for (int it = 0; it < npass; ++it) {
-      mu = mun;
+      float e[NC][4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) lg[t] = lgn[t];
-      const int in = chain_of(it + 1 < npass ? it + 1 : it);
-      mun = load_mu(in);
-      load_logits(in, lo, lgn);
+      for (int c = 0; c < NC; ++c) {
 #pragma unroll
-      for (int ds = 0; ds < DS; ++ds) {
-        clear();
-        add(lo, mu, lg, kk[ds], vv[ds]);
-        emit(ak, false, it, ds);
-        emit(av, true, it, ds);
+        for (int t = 0; t < 4; ++t) e[c][t] = lgn[c][t];
+        weigh(lo + 8 * c, mun, e[c]);
       }
+      request(it + 1 < npass ? it + 1 : it);
+#pragma unroll
+      for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          f32x16_t acc[2] = {zero16(), zero16()};
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+            if (c < 2 || lo + 8 * c < hi) add(acc, e[c], x == 0 ? kk[ds][c] : vv[ds][c]);
+          emit(acc, x == 1, it, ds);
+        }
     }
-    return;
+  };
+  if (lo < hi) {
+    if (hi - lo <= 8) return held(std::integral_constant<int, 1>());
+    if (hi - lo <= 16) return held(std::integral_constant<int, 2>());
+    if constexpr (D == 64 && !LONG)
+      if (hi - lo <= 24) return held(std::integral_constant<int, 3>());
   }
   for (int it = 0; it < npass; ++it) {
-    const int il = chain_of(it);
+    const uint32_t il = chain_of(it);
     const float mu = load_mu(il);
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds) {
-      clear();
+      f32x16_t ak[2] = {zero16(), zero16()}, av[2] = {zero16(), zero16()};
       if (lo < hi) {
+        // the next 8 keys are requested before these are used (past the end: the last key again)
         raw k0[4], v0[4], k1[4], v1[4];
         float l0[4], l1[4];
-        if constexpr (PIPE) {
-          // the next 8 keys are requested before these are used (past the end: the last key again)
-          load_logits(il, lo, l0);
-          load_rows(lo, ds, k0, v0);
-          for (int c0 = lo; c0 < hi; c0 += 16) {
-            load_logits(il, c0 + 8, l1);
-            load_rows(c0 + 8, ds, k1, v1);
-            add(c0, mu, l0, k0, v0);
-            load_logits(il, c0 + 16, l0);
-            load_rows(c0 + 16, ds, k0, v0);
-            if (c0 + 8 < hi) add(c0 + 8, mu, l1, k1, v1);
-          }
-        } else {
-          for (int c0 = lo; c0 < hi; c0 += 8) {
-            load_logits(il, c0, l0);
-            load_rows(c0, ds, k0, v0);
-            add(c0, mu, l0, k0, v0);
-          }
+        auto use = [&](int c0, float (&l)[4], const raw (&k)[4], const raw (&v)[4]) {
+          weigh(c0, mu, l);
+          add(ak, l, k);
+          add(av, l, v);
+        };
+        load_logits(il, lo, l0);
+        load_rows(lo, ds, k0, v0);
+        for (int c0 = lo; c0 < hi; c0 += 16) {
+          load_logits(il, c0 + 8, l1);
+          load_rows(c0 + 8, ds, k1, v1);
+          use(c0, l0, k0, v0);
+          load_logits(il, c0 + 16, l0);
+          load_rows(c0 + 16, ds, k0, v0);
+          if (c0 + 8 < hi) use(c0 + 8, l1, k1, v1);
         }
       }
       emit(ak, false, it, ds);
@@ -1341,7 +1361,7 @@ int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace&
   dim3 gm((unsigned)((d.nb - 1) * d.Cq), hn);
   { MuseProf prof_("k_chainmask", st); hipLaunchKernelGGL(k_chainmask, gm, dim3(256), 0, st, selc, w.perm_q, w.off_q, w.chainmask, h0, d.N, d.nb, d.r, d.Cq, W); }
   dim3 gs(kChainSplit * W, d.Cq, hn);
-  if (sizeof(T) == 2) {  // bf16 inputs: key-cluster-major on fp32 MFMA
+  if constexpr (sizeof(T) == 2) {  // bf16 inputs: key-cluster-major on fp32 MFMA
     const int WT = (d.Cq + 31) / 32;
     { MuseProf prof_("k_chainmask_t", st); hipLaunchKernelGGL(k_chainmask_t, dim3(W, WT, hn), dim3(64), 0, st, w.chainmask, w.chainmaskT, d.Cq, d.Ck, W, WT); }
     dim3 gj((d.Ck + 7) / 8 * 8, (d.nb - 1 + 3) / 4, hn);
@@ -1350,9 +1370,9 @@ int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace&
       hipLaunchKernelGGL(kernel, gj, dim3(256), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.chainmaskT, w.s_mu, w.s_k, (T*)w.s_v, h0,
                          d.N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv);
     };
-    const bool pipe = d.D == 128 || d.Bs / d.Ck >= 16;
-    if (d.D == 64) pipe ? go(k_block_summaries_mx<T, 64, true>) : go(k_block_summaries_mx<T, 64, false>);
-    else pipe ? go(k_block_summaries_mx<T, 128, true>) : go(k_block_summaries_mx<T, 128, false>);
+    const bool longer = d.Bs / d.Ck >= (d.D == 64 ? 32 : 16);
+    if (d.D == 64) longer ? go(k_block_summaries_mx<T, 64, true>) : go(k_block_summaries_mx<T, 64, false>);
+    else longer ? go(k_block_summaries_mx<T, 128, true>) : go(k_block_summaries_mx<T, 128, false>);
   } else if (d.D == 64)
     { MuseProf prof_("k_block_summaries", st); hipLaunchKernelGGL((k_block_summaries<T, 64>), gs, dim3(64), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k,
                        w.chainmask, w.s_mu, w.s_k, (T*)w.s_v, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv); }
