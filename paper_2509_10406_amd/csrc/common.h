@@ -231,10 +231,16 @@ struct MuseClusterSide {
 // n = 1 or 2 problems; of two the launches take turns.  d.streaming: the centroids come from the streaming pass (trace
 // [heads,N], counts [heads,C]: optional outputs of that pass; assign may then be NULL, for all, to stop after it)
 int muse_launch_cluster(const MuseDims& d, const MuseClusterSide* sides, int n);
+// the two problems of a call go in the same launches when they are given one stream
+bool muse_cluster_shares_launches(const MuseDims& d);
 // Stable bucketing of the N positions of every head by (spatial block, cluster):
 // perm [heads, N] position lists, off [heads, nb*C + 1] segment offsets.
-int muse_launch_bucket(const int32_t* assign, int heads, int N, int Bs, int C, int32_t* perm,
-                       int32_t* off, hipStream_t st);
+struct MuseBucketSide {
+  const int32_t* assign;
+  int heads, C;
+  int32_t *perm, *off;
+};
+int muse_launch_bucket(const MuseBucketSide* sides, int n, int N, int Bs, hipStream_t st);  // one or two, in one launch
 
 // attn_fp32.hip / attn_mfma.hip: causal attention restricted to keys m with
 // floor(n/Bs)*Bs <= m <= n  (Bs = N gives exact attention).  ff (may be NULL): per query
@@ -249,6 +255,16 @@ int muse_launch_attn_bwd(const MuseDims& d, int Bs, const void* Q, const void* K
                          const void* dO, const float* LSE, const float* delta, float* dQacc,
                          float* dKacc, float* dVacc, hipStream_t st);
 // fp32 accumulators -> gradient tensors of grad dtype, multiplied by `mul`
-int muse_launch_cast(const float* src, void* dst, size_t n, int dst_dtype, float mul, hipStream_t st);
-int muse_launch_fill(float* dst, size_t n, float v, hipStream_t st);
-int muse_launch_fill_i32(int32_t* dst, size_t n, int32_t v, hipStream_t st);
+struct CastRanges {
+  struct { const float* src; void* dst; size_t n; } r[3];
+  int n = 0;
+  void add(const float* src, void* dst, size_t count) { r[n].src = src; r[n].dst = dst; r[n++].n = count; }
+};
+int muse_launch_casts(const CastRanges& c, int dst_dtype, float mul, hipStream_t st);
+// arrays of 32-bit words (0 is a float's zero too)
+struct FillRanges {
+  struct { void* p; size_t n; uint32_t v; } r[4];
+  int n = 0;
+  void add(void* p, size_t count, uint32_t v) { r[n].p = p; r[n].v = v; r[n++].n = count; }
+};
+int muse_launch_fills(const FillRanges& f, hipStream_t st);

@@ -23,8 +23,10 @@ namespace {
 // bucketed copies of K and V: Xs[p] = X[perm[p]]
 // ------------------------------------------------------------------------------------------
 template <typename T>
-__global__ void __launch_bounds__(256) k_gather_rows(const T* __restrict__ X, const int32_t* __restrict__ perm,
-                                                      T* __restrict__ Xs, int N, int D) {
+__global__ void __launch_bounds__(256) k_gather_rows(const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ perm,
+                                                      T* __restrict__ Ks, T* __restrict__ Vs, int N, int D) {
+  const T* X = blockIdx.z ? V : K;
+  T* Xs = blockIdx.z ? Vs : Ks;
   const int CPR = D * (int)sizeof(T) / 16;
   size_t h = blockIdx.y;
   size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -1315,12 +1317,11 @@ int muse_ff_prepare(const MuseDims& d, const T* K, const T* V, const int32_t* aq
                     hipStream_t st) {
   const int HQ = d.B * d.Hq, HK = d.B * d.Hkv, N = d.N, D = d.D;
   int rc;
-  if ((rc = muse_launch_bucket(ak, HK, N, d.Bs, d.Ck, w.perm_k, w.off_k, st))) return rc;
-  if ((rc = muse_launch_bucket(aq, HQ, N, d.Bs, d.Cq, w.perm_q, w.off_q, st))) return rc;
+  const MuseBucketSide sides[2] = {{ak, HK, d.Ck, w.perm_k, w.off_k}, {aq, HQ, d.Cq, w.perm_q, w.off_q}};
+  if ((rc = muse_launch_bucket(sides, 2, N, d.Bs, st))) return rc;
   const int CPR = D * (int)sizeof(T) / 16;
-  dim3 g((unsigned)(((size_t)N * CPR + 255) / 256), HK);
-  { MuseProf prof_("k_gather_rows", st); hipLaunchKernelGGL(k_gather_rows<T>, g, dim3(256), 0, st, K, w.perm_k, (T*)w.Ks, N, D); }
-  { MuseProf prof_("k_gather_rows", st); hipLaunchKernelGGL(k_gather_rows<T>, g, dim3(256), 0, st, V, w.perm_k, (T*)w.Vs, N, D); }
+  dim3 g((unsigned)(((size_t)N * CPR + 255) / 256), HK, 2);
+  { MuseProf prof_("k_gather_rows", st); hipLaunchKernelGGL(k_gather_rows<T>, g, dim3(256), 0, st, K, V, w.perm_k, (T*)w.Ks, (T*)w.Vs, N, D); }
   { MuseProf prof_("k_tile_schedule", st); hipLaunchKernelGGL(k_tile_schedule, dim3(HQ * d.nb), dim3(64), 0, st, w.off_q, w.tile_off, d.nb, d.Cq); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
@@ -1353,11 +1354,15 @@ int muse_ff_summaries(const MuseDims& d, const float* qc, FFWorkspace& w, int h0
 
 // per-block summaries of the retrieved chains of the query heads [h0, h0+hn): needs selc of these heads
 template <typename T>
-int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace& w, int h0, int hn, hipStream_t st) {
+int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace& w, int h0, int hn, bool cleared, hipStream_t st) {
   if (d.nb <= 1 || d.r <= 0) return MUSE_OK;
   const int W = (d.Ck + 31) / 32;
   int rc;
-  if ((rc = muse_launch_fill_i32((int32_t*)w.chainmask, (size_t)hn * d.Cq * W, 0, st))) return rc;
+  if (!cleared) {
+    FillRanges f;
+    f.add(w.chainmask, (size_t)hn * d.Cq * W, 0);
+    if ((rc = muse_launch_fills(f, st))) return rc;
+  }
   dim3 gm((unsigned)((d.nb - 1) * d.Cq), hn);
   { MuseProf prof_("k_chainmask", st); hipLaunchKernelGGL(k_chainmask, gm, dim3(256), 0, st, selc, w.perm_q, w.off_q, w.chainmask, h0, d.N, d.nb, d.r, d.Cq, W); }
   dim3 gs(kChainSplit * W, d.Cq, hn);
@@ -1382,8 +1387,8 @@ int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace&
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }
-template int muse_ff_block_summaries<float>(const MuseDims&, const int32_t*, FFWorkspace&, int, int, hipStream_t);
-template int muse_ff_block_summaries<bf16_t>(const MuseDims&, const int32_t*, FFWorkspace&, int, int, hipStream_t);
+template int muse_ff_block_summaries<float>(const MuseDims&, const int32_t*, FFWorkspace&, int, int, bool, hipStream_t);
+template int muse_ff_block_summaries<bf16_t>(const MuseDims&, const int32_t*, FFWorkspace&, int, int, bool, hipStream_t);
 
 template int muse_ff_prepare<float>(const MuseDims&, const float*, const float*, const int32_t*, const int32_t*, FFWorkspace&, hipStream_t);
 template int muse_ff_prepare<bf16_t>(const MuseDims&, const bf16_t*, const bf16_t*, const int32_t*, const int32_t*, FFWorkspace&, hipStream_t);
@@ -1412,7 +1417,7 @@ int launch_ff_fwd_r(const MuseDims& d, const T* Q, const float* qc, const int32_
     else launch_ff_fwd<D, 32>(d, Q, qc, w, selc, h0, hn, st);
   }
   if (d.r > 0) {
-    if (const int rc = muse_ff_block_summaries<T>(d, selc, w, h0, hn, st)) return rc;
+    if (const int rc = muse_ff_block_summaries<T>(d, selc, w, h0, hn, w.hc >= d.B * d.Hq, st)) return rc;
     const dim3 g = far_grid(d, hn);
     if (d.nb <= 9)
       { MuseProf prof_("k_comp2_fwd", st); hipLaunchKernelGGL((k_comp2_fwd<T, D, 1>), g, dim3(256), 0, st, Q, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.s_mu, w.s_k,
@@ -1434,7 +1439,19 @@ int run_fwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const f
   const int HQ = d.B * d.Hq;
   int rc;
   if ((rc = muse_ff_prepare<T>(d, K, V, aq, ak, w, st))) return rc;
-  if ((rc = muse_launch_fill(w.ff_ml, (size_t)HQ * d.N * 2, 0.f, st))) return rc;
+  // block-0 queries have no far field, and nothing selected (r = 0 selects nothing either); the chain mask is cleared here where
+  // all heads are one chunk
+  {
+    FillRanges f;
+    const size_t nq = (size_t)HQ * d.N;
+    f.add(w.ff_ml, nq * 2, 0);
+    if (d.r > 0) {
+      f.add(selc, nq * d.r, 0xffffffffu);
+      f.add(selb, nq * d.r * d.k2e, 0xffffffffu);
+      if (d.nb > 1 && w.hc >= HQ) f.add(w.chainmask, (size_t)HQ * d.Cq * ((d.Ck + 31) / 32), 0);
+    }
+    if ((rc = muse_launch_fills(f, st))) return rc;
+  }
   if (d.nb > 1) {
     if (d.dipole && (rc = muse_dipole_covariances<T>(d, w, st))) return rc;
     for (int h0 = 0; h0 < HQ; h0 += w.hc) {
@@ -1471,13 +1488,6 @@ int muse_run_fwd(const MuseDims& d, const void* Q, const void* K, const void* V,
   FFWorkspace w;
   if (!muse_ff_carve(d, d.keep_state, ws, ws_bytes, &w, nullptr, nullptr, nullptr)) return MUSE_ERR_WORKSPACE_TOO_SMALL;
   if (d.keep_state && w.hc < d.B * d.Hq) return MUSE_ERR_WORKSPACE_TOO_SMALL;
-  // block-0 queries and r = 0 leave the selection outputs untouched by the tile kernel: pad them
-  if (d.r > 0) {
-    size_t nq = (size_t)d.B * d.Hq * d.N;
-    int rc;
-    if ((rc = muse_launch_fill_i32(selc, nq * d.r, -1, st))) return rc;
-    if ((rc = muse_launch_fill_i32(selb, nq * d.r * d.k2e, -1, st))) return rc;
-  }
   if (d.dtype == MUSE_DTYPE_FP32)
     return run_fwd_typed<float>(d, (const float*)Q, (const float*)K, (const float*)V, qc, aq, ak, O, LSE, selc, selb, w, st);
   return run_fwd_typed<bf16_t>(d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, qc, aq, ak, O, LSE, selc, selb, w, st);

@@ -754,8 +754,10 @@ __global__ void __launch_bounds__(64) k_cells_to_keys(const T* __restrict__ Ks, 
 }
 
 // rows back to sequence order, added to what the block-diagonal kernels left: dst[perm[p]] += src[p]
-__global__ void __launch_bounds__(256) k_scatter_rows(const float* __restrict__ src, const int32_t* __restrict__ perm,
-                                                       float* __restrict__ dst, int N, int D) {
+__global__ void __launch_bounds__(256) k_scatter_rows(const float* __restrict__ dKs, const float* __restrict__ dVs, const int32_t* __restrict__ perm,
+                                                       float* __restrict__ dK, float* __restrict__ dV, int N, int D) {
+  const float* src = blockIdx.z ? dVs : dKs;
+  float* dst = blockIdx.z ? dV : dK;
   const int CPR = D / 4;
   size_t h = blockIdx.y;
   size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -863,8 +865,13 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
   // info and the inverse index, which the first stream builds: event `mid`), beside the cell gradients.
   const bool split = two && w.hc >= HQ;
   if (two && !split) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));
-  if ((rc = muse_launch_fill(w.dKs, nk * D, 0.f, st))) return rc;
-  if ((rc = muse_launch_fill(w.dVs, nk * D, 0.f, st))) return rc;
+  {
+    FillRanges f;
+    f.add(w.dKs, nk * D, 0);
+    f.add(w.dVs, nk * D, 0);
+    if (d.nb > 1 && d.r == 0) f.add(w.selmask, nq * ((d.Ck + 31) / 32), 0);
+    if ((rc = muse_launch_fills(f, st))) return rc;
+  }
   if (d.nb > 1) {
     const int W = (d.Ck + 31) / 32;
     if (d.r > 0) {
@@ -873,8 +880,6 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
         if (d.r <= 8) go(k_selinfo<8>);
         else if (d.r <= 16) go(k_selinfo<16>);
         else go(k_selinfo<32>); }
-    } else {
-      if ((rc = muse_launch_fill_i32((int32_t*)w.selmask, nq * W, 0, st))) return rc;
     }
     MUSE_LAUNCH_CHECK();
     if (d.r > 0) {
@@ -898,7 +903,7 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
     for (int h0 = 0; h0 < HQ; h0 += w.hc) {
       int hn = HQ - h0 < w.hc ? HQ - h0 : w.hc;
       if (!reuse && (rc = muse_ff_summaries<T>(d, qc, w, h0, hn, st))) return rc;
-      if (!reuse && (rc = muse_ff_block_summaries<T>(d, selc, w, h0, hn, st))) return rc;
+      if (!reuse && (rc = muse_ff_block_summaries<T>(d, selc, w, h0, hn, false, st))) return rc;
       if (split) {  // everything the dQ side reads is now queued on the first stream
         MUSE_HIP_CHECK(hipEventRecord(ax.mid, st));
         MUSE_HIP_CHECK(hipStreamWaitEvent(sb, ax.mid, 0));
@@ -912,9 +917,8 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
   if (two) MUSE_HIP_CHECK(hipStreamWaitEvent(st, ax.join, 0));
   guard.armed = false;
   {
-    dim3 g((unsigned)(((size_t)N * (D / 4) + 255) / 256), HK);
-    { MuseProf prof_("k_scatter_rows", st); hipLaunchKernelGGL(k_scatter_rows, g, dim3(256), 0, st, w.dKs, w.perm_k, w.dKacc, N, D); }
-    { MuseProf prof_("k_scatter_rows", st); hipLaunchKernelGGL(k_scatter_rows, g, dim3(256), 0, st, w.dVs, w.perm_k, w.dVacc, N, D); }
+    dim3 g((unsigned)(((size_t)N * (D / 4) + 255) / 256), HK, 2);
+    { MuseProf prof_("k_scatter_rows", st); hipLaunchKernelGGL(k_scatter_rows, g, dim3(256), 0, st, w.dKs, w.dVs, w.perm_k, w.dKacc, w.dVacc, N, D); }
     MUSE_LAUNCH_CHECK();
   }
   if (d.nb > 1) {
@@ -923,9 +927,11 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
     MUSE_LAUNCH_CHECK();
   }
   if (d.grad_dtype != MUSE_DTYPE_FP32) {
-    if ((rc = muse_launch_cast(w.dQacc, dQ, nq * D, d.grad_dtype, 1.f, st))) return rc;
-    if ((rc = muse_launch_cast(w.dKacc, dK, nk * D, d.grad_dtype, 1.f, st))) return rc;
-    if ((rc = muse_launch_cast(w.dVacc, dV, nk * D, d.grad_dtype, 1.f, st))) return rc;
+    CastRanges c;
+    c.add(w.dQacc, dQ, nq * D);
+    c.add(w.dKacc, dK, nk * D);
+    c.add(w.dVacc, dV, nk * D);
+    if ((rc = muse_launch_casts(c, d.grad_dtype, 1.f, st))) return rc;
   }
   return MUSE_OK;
 }

@@ -339,7 +339,7 @@ int muse_ff_summaries(const MuseDims& d, const float* qc, FFWorkspace& w, int h0
 int muse_launch_farfield_tiles(const MuseDims& d, const void* Q, const FFWorkspace& w, int32_t* selc, int h0, int hn,
                                hipStream_t st);
 template <typename T>
-int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace& w, int h0, int hn, hipStream_t st);
+int muse_ff_block_summaries(const MuseDims& d, const int32_t* selc, FFWorkspace& w, int h0, int hn, bool cleared, hipStream_t st);  // cleared: w.chainmask is all zeros
 
 // cell_grads.hip: component 1 of the per-block cell gradients, bf16 inputs, of the query heads [h0, h0+hn)
 int muse_launch_ff_bwd_cells_mx(const MuseDims& d, const void* Q, const void* dO, const float* qc, const float* LSE,

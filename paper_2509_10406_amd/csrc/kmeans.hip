@@ -11,11 +11,35 @@
 //   update:        fixed-order sum over a cluster's segments, by one wave or by one per row slot (k_update).
 //   streaming pass (App. C "Centroid Computation") and balanced assignment (App. C "Balanced Assignment"):
 //                  the paper's own clustering, behind flags; see k_stream_kmeans and k_balance.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
 
 namespace {
+
+// One clustering problem as the kernels of an iteration see it, and one or two of them that share a launch: blockIdx.y counts the heads
+// of the first, then those of the second.
+template <typename T>
+struct KSide {
+  const T* X;
+  const int32_t* init_idx;
+  float* cent;
+  T* chat;
+  float* nhc2;
+  int32_t* assign;
+  int C, heads;
+};
+template <typename T>
+struct KSides {
+  KSide<T> s[2];
+};
+template <typename T>
+__device__ __forceinline__ KSide<T> side_of(const KSides<T>& both, int y, int& h) {
+  const bool second = y >= both.s[0].heads;
+  h = second ? y - both.s[0].heads : y;
+  return second ? both.s[1] : both.s[0];
+}
 
 // ------------------------------------------------------------------------------------------
 // centroid gather / preparation
@@ -41,10 +65,15 @@ __device__ __forceinline__ void prep_row(const float (&c)[2], T* __restrict__ ch
 
 // initial centroids (rows init_idx of X, or what `cent` holds) with their chat [H,C,D] and nhc2 [H,C]; a wave per centroid
 template <typename T>
-__global__ void __launch_bounds__(256) k_init_centroids(const T* __restrict__ X, const int32_t* __restrict__ init_idx,
-                                                         float* __restrict__ cent, T* __restrict__ chat,
-                                                         float* __restrict__ nhc2, int N, int D, int C, int total) {
-  const int row = blockIdx.x * 4 + threadIdx.x / 64, lane = threadIdx.x % 64;
+__global__ void __launch_bounds__(256) k_init_centroids(KSides<T> both, int N, int D) {
+  const int rows0 = both.s[0].heads * both.s[0].C, at = blockIdx.x * 4 + threadIdx.x / 64, lane = threadIdx.x % 64;
+  const bool second = at >= rows0;
+  const KSide<T> side = second ? both.s[1] : both.s[0];
+  const int row = second ? at - rows0 : at, total = side.heads * side.C, C = side.C;
+  const T* X = side.X;
+  const int32_t* init_idx = side.init_idx;
+  float *cent = side.cent, *nhc2 = side.nhc2;
+  T* chat = side.chat;
   if (row >= total) return;
   const T* src = init_idx ? X + ((size_t)(row / C) * N + init_idx[row]) * D : nullptr;
   float c[2] = {0.f, 0.f};
@@ -66,16 +95,18 @@ __global__ void __launch_bounds__(256) k_init_centroids(const T* __restrict__ X,
 // points, 32 and 128 centroids.
 // ------------------------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256) k_assign_f32(const float* __restrict__ X,
-                                                     const float* __restrict__ chat,
-                                                     const float* __restrict__ nhc2,
-                                                     int32_t* __restrict__ assign, int N, int C) {
+__global__ void __launch_bounds__(256) k_assign_f32(KSides<float> both, int N) {
+  int h;
+  const KSide<float> side = side_of(both, blockIdx.y, h);
+  const float *__restrict__ X = side.X, *__restrict__ chat = side.chat, *__restrict__ nhc2 = side.nhc2;
+  int32_t* __restrict__ assign = side.assign;
+  const int C = side.C;
   constexpr int CT = 64;
   __shared__ __attribute__((aligned(16))) float cs[CT][D];
   __shared__ float c2s[CT];
   __shared__ float bv[4][64];
   __shared__ int bi[4][64];
-  const int h = blockIdx.y, wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int n = blockIdx.x * 64 + lane;
   float x[D];
   {
@@ -245,14 +276,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 constexpr float kPadScore = -3.0e38f;  // score of the padding rows past C: finite, so that tagging its low bits keeps it a number
 constexpr int kResWaves = 8;
 template <int D>
-__global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) k_assign_res(
-    const bf16_t* __restrict__ X, const bf16_t* __restrict__ chat, const float* __restrict__ nhc2,
-    int32_t* __restrict__ assign, int N, int C, int Cpad) {
+__global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) k_assign_res(KSides<bf16_t> both, int N) {
+  int h;
+  const KSide<bf16_t> side = side_of(both, blockIdx.y, h);
+  const bf16_t *__restrict__ X = side.X, *__restrict__ chat = side.chat;
+  const float* __restrict__ nhc2 = side.nhc2;
+  int32_t* __restrict__ assign = side.assign;
+  const int C = side.C, Cpad = (C + 63) / 64 * 64;  // rows padded to a multiple of 64 for the tile pairs
   constexpr int KS = D / 16, CPR = D / 8, PT = D == 64 ? 2 : 1, LDW = D + 8;
   extern __shared__ __attribute__((aligned(16))) unsigned char res_lds[];
   bf16_t* cs = reinterpret_cast<bf16_t*>(res_lds);                          // [Cpad][D + 8]
   float* c2s = reinterpret_cast<float*>(res_lds + (size_t)Cpad * LDW * 2);  // [Cpad]
-  const int h = blockIdx.y;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
   const bf16_t* Xh = X + (size_t)h * N * D;
   const bf16_t* Ch = chat + (size_t)h * C * D;
@@ -362,14 +396,20 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
 // ------------------------------------------------------------------------------------------
 // stable bucketing by (block, cluster): grid (nb, heads), 1024 threads = 16 waves
 // ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(1024) k_bucket(const int32_t* __restrict__ assign,
-                                                  int32_t* __restrict__ perm,
-                                                  int32_t* __restrict__ off, int N, int Bs, int C) {
+struct BucketSides {
+  MuseBucketSide s[2];
+};
+__global__ void __launch_bounds__(1024) k_bucket(BucketSides sides, int N, int Bs) {
+  const bool second = (int)blockIdx.y >= sides.s[0].heads;
+  const int C = second ? sides.s[1].C : sides.s[0].C;
+  const int32_t* __restrict__ assign = second ? sides.s[1].assign : sides.s[0].assign;
+  int32_t* __restrict__ perm = second ? sides.s[1].perm : sides.s[0].perm;
+  int32_t* __restrict__ off = second ? sides.s[1].off : sides.s[0].off;
   extern __shared__ uint32_t smem[];
   uint32_t* hist = smem;               // [16][C]
   uint32_t* tot = smem + 16 * C;       // [C]
   __shared__ uint32_t wsum[16];
-  const int b = blockIdx.x, h = blockIdx.y, nb = gridDim.x;
+  const int b = blockIdx.x, h = blockIdx.y - (second ? sides.s[0].heads : 0), nb = gridDim.x;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int32_t* a = assign + (size_t)h * N + (size_t)b * Bs;
   const int sub = (Bs + 15) / 16;
@@ -611,14 +651,20 @@ __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) :
 constexpr int kScan = 1024;
 constexpr long long kScanMost = 4 << 20;
 template <typename T, int D>
-__global__ void __launch_bounds__(64 * (64 / (D * (int)sizeof(T) / 16))) k_update_scan(
-    const T* __restrict__ X, const int32_t* __restrict__ assign, float* __restrict__ cent, T* __restrict__ chat,
-    float* __restrict__ nhc2, int N, int Bs, int C) {
+__global__ void __launch_bounds__(64 * (64 / (D * (int)sizeof(T) / 16))) k_update_scan(KSides<T> both, int N, int Bs) {
+  int h;
+  const KSide<T> side = side_of(both, blockIdx.y, h);
+  const T* __restrict__ X = side.X;
+  const int32_t* __restrict__ assign = side.assign;
+  float *__restrict__ cent = side.cent, *__restrict__ nhc2 = side.nhc2;
+  T* __restrict__ chat = side.chat;
+  const int C = side.C;
+  if ((int)blockIdx.x >= C) return;
   constexpr int S = 64 / (D * (int)sizeof(T) / 16), EPL = D / 64;
   __shared__ float sum[S][D];
   __shared__ int cnt[S];
   __shared__ uint16_t list[S][kScan];
-  const int lane = threadIdx.x % 64, slot = threadIdx.x / 64, j = blockIdx.x, h = blockIdx.y;
+  const int lane = threadIdx.x % 64, slot = threadIdx.x / 64, j = blockIdx.x;
   const int32_t* ah = assign + (size_t)h * N;
   const T* Xh = X + (size_t)h * N * D;
   float acc[EPL];
@@ -1147,6 +1193,7 @@ struct ClusterRun {
   float* nhc2;
   int32_t *perm, *off;
   char* w;
+  KSide<T> side(const int32_t* init_idx) const { return {X, init_idx, cent, chat, nhc2, assign, C, heads}; }
 
   ClusterRun(const MuseDims& d_, const MuseClusterSide& s)
       : d(d_), X((const T*)s.X), C(s.C), heads(d_.B * s.H), T_(d_.streaming ? 0 : d_.T), cent(s.cent), assign(s.assign), st(s.st), w((char*)s.ws) {
@@ -1155,13 +1202,13 @@ struct ClusterRun {
     perm = (int32_t*)w;    w += align256((size_t)heads * d.N * sizeof(int32_t));
     off = (int32_t*)w;     w += align256((size_t)heads * ((size_t)d.nb * C + 1) * sizeof(int32_t));
   }
-  int begin(const int32_t* init_idx, int32_t* trace, float* counts);
+  int stream(const int32_t* init_idx, int32_t* trace, float* counts);
   int iteration(int it);
 };
 
-// the streaming pass, if asked for, and the centroids that the first assignment reads
+// the streaming pass, if asked for
 template <typename T>
-int ClusterRun<T>::begin(const int32_t* init_idx, int32_t* trace, float* counts) {
+int ClusterRun<T>::stream(const int32_t* init_idx, int32_t* trace, float* counts) {
   const int N = d.N, D = d.D;
   if (d.streaming) {
     // App. C "Centroid Computation": the streaming pass gives the centroids, one final assignment follows
@@ -1200,54 +1247,84 @@ int ClusterRun<T>::begin(const int32_t* init_idx, int32_t* trace, float* counts)
     }
 #undef MUSE_STREAM_LAUNCH
     MUSE_LAUNCH_CHECK();
-    if (!assign) return MUSE_OK;
   }
-  const int rows = heads * C;
-  { MuseProf prof_("k_init_centroids", st); hipLaunchKernelGGL(k_init_centroids<T>, dim3((rows + 3) / 4), dim3(256), 0, st, X, d.streaming ? nullptr : init_idx, cent, chat, nhc2, N, D, C, rows); }
-  MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }
+
+// The launches of an iteration, for one problem or for two at once.
+template <typename T>
+struct ClusterLaunch {
+  KSides<T> k;
+  int N, D, Bs, heads;
+  hipStream_t st;
+  ClusterLaunch(const ClusterRun<T>& a, const int32_t* ia, const ClusterRun<T>* b, const int32_t* ib)
+      : k{{a.side(ia), b ? b->side(ib) : a.side(ia)}}, N(a.d.N), D(a.d.D), Bs(a.d.Bs), heads(a.heads + (b ? b->heads : 0)), st(a.st) {
+    if (!b) k.s[1].heads = 0;
+  }
+  int init(int rows) {  // the centroids that the first assignment reads
+    { MuseProf prof_("k_init_centroids", st); hipLaunchKernelGGL(k_init_centroids<T>, dim3((rows + 3) / 4), dim3(256), 0, st, k, N, D); }
+    MUSE_LAUNCH_CHECK();
+    return MUSE_OK;
+  }
+  static size_t resident_bytes(int C, int D) { return (size_t)((C + 63) / 64 * 64) * ((D + 8) * 2 + 4); }  // all centroids in LDS
+  int assign() {
+    const int C = std::max(k.s[0].C, k.s[1].C);
+    if constexpr (sizeof(T) == 4) {
+      dim3 g((N + 63) / 64, heads);
+      MuseProf prof_("k_assign_f32", st);
+      if (D == 64) hipLaunchKernelGGL(k_assign_f32<64>, g, dim3(256), 0, st, k, N);
+      else hipLaunchKernelGGL(k_assign_f32<128>, g, dim3(256), 0, st, k, N);
+    } else {
+      const size_t bytes = resident_bytes(C, D);
+      MuseProf prof_("k_assign_bf16", st);
+      if (bytes <= 160 * 1024) {
+        static bool attr_set = false;
+        if (!attr_set) {
+          MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<64>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+          MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<128>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+          attr_set = true;
+        }
+        const int bp = (D == 64 ? 64 : 32) * kResWaves;  // points per batch
+        const int nbatch = (N + bp - 1) / bp;
+        int gx = (256 + heads - 1) / heads;  // about one workgroup per CU over all heads
+        gx = gx > nbatch ? nbatch : gx;
+        dim3 g(gx, heads);
+        if (D == 64) hipLaunchKernelGGL(k_assign_res<64>, g, dim3(64 * kResWaves), bytes, st, k, N);
+        else hipLaunchKernelGGL(k_assign_res<128>, g, dim3(64 * kResWaves), bytes, st, k, N);
+      } else {  // (one problem)
+        constexpr int PT = 2;
+        dim3 g((N + 4 * 32 * PT - 1) / (4 * 32 * PT), heads);
+        if (D == 64) hipLaunchKernelGGL((k_assign_bf16<64, PT>), g, dim3(256), 0, st, k.s[0].X, k.s[0].chat, k.s[0].nhc2, k.s[0].assign, N, C);
+        else hipLaunchKernelGGL((k_assign_bf16<128, PT>), g, dim3(256), 0, st, k.s[0].X, k.s[0].chat, k.s[0].nhc2, k.s[0].assign, N, C);
+      }
+    }
+    MUSE_LAUNCH_CHECK();
+    return MUSE_OK;
+  }
+  int update_scan() {
+    MuseProf prof_("k_update", st);
+    constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);  // row slots
+    const dim3 g(std::max(k.s[0].C, k.s[1].C), heads);
+    if (D == 64) hipLaunchKernelGGL((k_update_scan<T, 64>), g, dim3(64 * S64), 0, st, k, N, Bs);
+    else hipLaunchKernelGGL((k_update_scan<T, 128>), g, dim3(64 * S128), 0, st, k, N, Bs);
+    MUSE_LAUNCH_CHECK();
+    return MUSE_OK;
+  }
+};
 
 // assignment `it`, and the centroid update behind it unless it is the last one
 template <typename T>
 int ClusterRun<T>::iteration(int it) {
   const int N = d.N, D = d.D, rows = heads * C;
-  if constexpr (sizeof(T) == 4) {
-    dim3 g((N + 63) / 64, heads);
-    if (D == 64) { MuseProf prof_("k_assign_f32", st); hipLaunchKernelGGL(k_assign_f32<64>, g, dim3(256), 0, st, (const float*)X, (const float*)chat, nhc2, assign, N, C); }
-    else { MuseProf prof_("k_assign_f32", st); hipLaunchKernelGGL(k_assign_f32<128>, g, dim3(256), 0, st, (const float*)X, (const float*)chat, nhc2, assign, N, C); }
-  } else {
-    // all centroids resident in LDS when they fit (rows padded to a multiple of 64 for the tile pairs)
-    const int Cpad = (C + 63) / 64 * 64;
-    const size_t res_bytes = (size_t)Cpad * (D + 8) * 2 + (size_t)Cpad * 4;
-    if (res_bytes <= 160 * 1024) {
-      static bool attr_set = false;
-      if (!attr_set) {
-        MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<64>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-        MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<128>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-        attr_set = true;
-      }
-      const int bp = (D == 64 ? 64 : 32) * kResWaves;  // points per batch
-      const int nbatch = (N + bp - 1) / bp;
-      int gx = (256 + heads - 1) / heads;  // about one workgroup per CU over all heads
-      gx = gx > nbatch ? nbatch : gx;
-      dim3 g(gx, heads);
-      if (D == 64) { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL(k_assign_res<64>, g, dim3(64 * kResWaves), res_bytes, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C, Cpad); }
-      else { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL(k_assign_res<128>, g, dim3(64 * kResWaves), res_bytes, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C, Cpad); }
-    } else {
-      constexpr int PT = 2;
-      dim3 g((N + 4 * 32 * PT - 1) / (4 * 32 * PT), heads);
-      if (D == 64) { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL((k_assign_bf16<64, PT>), g, dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C); }
-      else { MuseProf prof_("k_assign_bf16", st); hipLaunchKernelGGL((k_assign_bf16<128, PT>), g, dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)chat, nhc2, assign, N, C); }
-    }
-  }
-  MUSE_LAUNCH_CHECK();
+  ClusterLaunch<T> own(*this, nullptr, nullptr, nullptr);
+  if (int rc = own.assign()) return rc;
   if (it == T_ && d.balanced) {
     // App. C "Balanced Assignment": the nearest-centroid assignment bucketed by (block, cluster), then the rows
     // beyond the cap of their segment are placed again
     const int cap = (int)((4LL * d.Bs) / C);
     if (cap < 1 || (long long)cap * C < d.Bs) return MUSE_ERR_UNSUPPORTED;
-    int rc = muse_launch_bucket(assign, heads, N, d.Bs, C, perm, off, st);
+    const MuseBucketSide one = {assign, heads, C, perm, off};
+    int rc = muse_launch_bucket(&one, 1, N, d.Bs, st);
     if (rc) return rc;
     const size_t lds = (size_t)C * 4 + (size_t)((d.Bs + 31) / 32) * 4 + (size_t)d.Bs * 2 + 16;
     if (D == 64) { MuseProf prof_("k_balance", st); hipLaunchKernelGGL((k_balance<T, 64>), dim3(d.nb, heads), dim3(256), lds, st, X, chat, nhc2, perm, off, assign, N, d.Bs, C, cap); }
@@ -1256,15 +1333,9 @@ int ClusterRun<T>::iteration(int it) {
   }
   if (it == T_) return MUSE_OK;
   constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);  // row slots
-  if (scan_update(heads, N, C, D == 64 ? S64 : S128)) {
-    MuseProf prof_("k_update", st);
-    auto go = [&](auto* kernel, int block) { hipLaunchKernelGGL(kernel, dim3(C, heads), dim3(block), 0, st, X, assign, cent, chat, nhc2, N, d.Bs, C); };
-    if (D == 64) go(k_update_scan<T, 64>, 64 * S64);
-    else go(k_update_scan<T, 128>, 64 * S128);
-    MUSE_LAUNCH_CHECK();
-    return MUSE_OK;
-  }
-  int rc = muse_launch_bucket(assign, heads, N, d.Bs, C, perm, off, st);
+  if (scan_update(heads, N, C, D == 64 ? S64 : S128)) return own.update_scan();
+  const MuseBucketSide one = {assign, heads, C, perm, off};
+  int rc = muse_launch_bucket(&one, 1, N, d.Bs, st);
   if (rc) return rc;
   {
     MuseProf prof_("k_update", st);
@@ -1278,13 +1349,44 @@ int ClusterRun<T>::iteration(int it) {
   return MUSE_OK;
 }
 
+// Queries and keys in the same launches, on one stream: small problems, whose launches (3.4 us of the host each, and two streams to
+// fork and join: 45 us) cost more than their work.  On two streams one side's update runs beside the other's assignment, which
+// tells where an iteration has something to do: the line is drawn at 4 M (row, cluster) pairs of 128-byte rows, the square of
+// that for longer rows.  us of ten iterations, two streams / shared, heads x rows, clusters:
+//   bf16, D = 64    2+2 x 2k, 8 x 16  210 / 143    4+4 x 4k, 16 x 32  212 / 156   4+4 x 8k, 32 x 64  214 / 180
+//                   8+8 x 8k, 32 x 64  220 / 212   16+16 x 4k, 16 x 64  228 / 271   1+1 x 16k, 64 x 256  221 / 236
+//   bf16, D = 128   8+2 x 4k, 16 x 32  227 / 216   8+2 x 8k, 32 x 64  345 / 363
+//   fp32, D = 64    1+1 x 2k, 16 x 32  207 / 152   1+1 x 8k, 32 x 64  218 / 201   4+4 x 4k, 16 x 64  218 / 235   4+4 x 8k, 32 x 128  348 / 394
+//   fp32, D = 128   1+1 x 2k, 8 x 16   329 / 309   4+4 x 4k, 16 x 32  390 / 407
+template <typename T>
+bool shared_launches(const MuseDims& d) {
+  const int S = 64 / (d.D * (int)sizeof(T) / 16);
+  const long long longer = d.D * (long long)sizeof(T) / 128, pairs = (long long)d.B * d.N * (d.Hq * d.Cq + d.Hkv * d.Ck);
+  return !d.streaming && !d.balanced && pairs * longer * longer <= 4 << 20 && scan_update(d.B * d.Hq, d.N, d.Cq, S) &&
+         scan_update(d.B * d.Hkv, d.N, d.Ck, S) && (sizeof(T) == 4 || ClusterLaunch<T>::resident_bytes(std::max(d.Cq, d.Ck), d.D) <= 160 * 1024);
+}
+
 template <typename T>
 int cluster_impl(const MuseDims& d, const MuseClusterSide* sides, int n) {
   ClusterRun<T> a(d, sides[0]), b(d, sides[n - 1]);
   ClusterRun<T>* run[2] = {&a, &b};
-  for (int i = 0; i < n; ++i)
-    if (int rc = run[i]->begin(sides[i].init_idx, sides[i].trace, sides[i].counts)) return rc;
-  if (!a.assign) return MUSE_OK;  // the streaming pass alone
+  if (n == 2 && a.st == b.st && shared_launches<T>(d)) {
+    ClusterLaunch<T> both(a, sides[0].init_idx, &b, sides[1].init_idx);
+    if (int rc = both.init(a.heads * a.C + b.heads * b.C)) return rc;
+    for (int it = 0; it <= a.T_; ++it) {
+      if (int rc = both.assign()) return rc;
+      if (it == a.T_) break;
+      if (int rc = both.update_scan()) return rc;
+    }
+    return MUSE_OK;
+  }
+  for (int i = 0; i < n; ++i) {
+    if (int rc = run[i]->stream(sides[i].init_idx, sides[i].trace, sides[i].counts)) return rc;
+    if (!run[i]->assign) continue;  // the streaming pass alone
+    ClusterLaunch<T> own(*run[i], d.streaming ? nullptr : sides[i].init_idx, nullptr, nullptr);
+    if (int rc = own.init(run[i]->heads * run[i]->C)) return rc;
+  }
+  if (!a.assign) return MUSE_OK;
   for (int it = 0; it <= a.T_; ++it)
     for (int i = 0; i < n; ++i)
       if (int rc = run[i]->iteration(it)) return rc;
@@ -1303,8 +1405,9 @@ size_t muse_cluster_ws_bytes(const MuseDims& d) {
          align256(heads * C * d.D * 4) + align256(heads * CS * 4) + align256(heads * C * d.D * 2) + align256(heads * CS * 4);
 }
 
-int muse_launch_bucket(const int32_t* assign, int heads, int N, int Bs, int C, int32_t* perm,
-                       int32_t* off, hipStream_t st) {
+int muse_launch_bucket(const MuseBucketSide* sides, int n, int N, int Bs, hipStream_t st) {
+  const BucketSides both = {{sides[0], sides[n - 1]}};
+  const int C = std::max(both.s[0].C, both.s[1].C), heads = both.s[0].heads + (n == 2 ? both.s[1].heads : 0);
   static_assert((size_t)17 * MUSE_MAX_CLUSTERS * sizeof(uint32_t) <= 150 * 1024, "histograms of the largest accepted C fit the LDS");
   size_t lds = (size_t)17 * C * sizeof(uint32_t);
   if (C > MUSE_MAX_CLUSTERS) return MUSE_ERR_UNSUPPORTED;  // the entry points have checked this already
@@ -1313,11 +1416,15 @@ int muse_launch_bucket(const int32_t* assign, int heads, int N, int Bs, int C, i
     MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_bucket, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024));
     attr_set = true;
   }
-  { MuseProf prof_("k_bucket", st); hipLaunchKernelGGL(k_bucket, dim3(N / Bs, heads), dim3(1024), lds, st, assign, perm, off, N, Bs, C); }
+  { MuseProf prof_("k_bucket", st); hipLaunchKernelGGL(k_bucket, dim3(N / Bs, heads), dim3(1024), lds, st, both, N, Bs); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }
 
 int muse_launch_cluster(const MuseDims& d, const MuseClusterSide* sides, int n) {
   return d.dtype == MUSE_DTYPE_FP32 ? cluster_impl<float>(d, sides, n) : cluster_impl<bf16_t>(d, sides, n);
+}
+
+bool muse_cluster_shares_launches(const MuseDims& d) {
+  return d.dtype == MUSE_DTYPE_FP32 ? shared_launches<float>(d) : shared_launches<bf16_t>(d);
 }

@@ -239,7 +239,7 @@ int muse_cluster(const muse_params* p, const void* Q, const void* K, const int32
   // wait queued before the queries' launches the chains ran one after the other (the layer with one fp32 head of 2k
   // tokens: 651 -> 423 us; 8 heads of 16k: 2.47 -> 2.23 ms; the streaming pass of 16 heads of 32k: 10.6 -> 8.4 ms).
   MuseAux& ax = muse_aux_stream();
-  const bool two = Q && K && ax.state == 1 && !muse_profiling();
+  const bool two = Q && K && ax.state == 1 && !muse_profiling() && !muse_cluster_shares_launches(d);
   hipStream_t sk = two ? ax.s : st;
   if (two) {
     MUSE_HIP_CHECK(hipEventRecord(ax.fork, st));
@@ -351,9 +351,11 @@ int exact_attn_bwd(const muse_params* p, const void* Q, const void* K, const voi
   if ((rc = muse_launch_delta(d, O, dO, delta, st))) return rc;
   if ((rc = muse_launch_attn_bwd(d, d.N, Q, K, V, dO, LSE, delta, aq, ak, av, st))) return rc;
   if (!direct) {
-    if ((rc = muse_launch_cast(aq, dQ, q * d.D, d.grad_dtype, 1.f, st))) return rc;
-    if ((rc = muse_launch_cast(ak, dK, k * d.D, d.grad_dtype, 1.f, st))) return rc;
-    if ((rc = muse_launch_cast(av, dV, k * d.D, d.grad_dtype, 1.f, st))) return rc;
+    CastRanges c;
+    c.add(aq, dQ, q * d.D);
+    c.add(ak, dK, k * d.D);
+    c.add(av, dV, k * d.D);
+    if ((rc = muse_launch_casts(c, d.grad_dtype, 1.f, st))) return rc;
   }
   return MUSE_OK;
 }
