@@ -576,8 +576,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
                                                           const bf16_t* __restrict__ qcb, const float* __restrict__ L,
                                                           const float* __restrict__ s_mu, const float* __restrict__ G_c,
                                                           const bf16_t* __restrict__ G_k, const bf16_t* __restrict__ G_v,
-                                                          const int32_t* __restrict__ off_k, float* __restrict__ dKs,
-                                                          float* __restrict__ dVs, int h0, int N, int nb, int Cq, int CqP,
+                                                          const int32_t* __restrict__ off_k, const int32_t* __restrict__ perm_k, const float* __restrict__ dKs,
+                                                          const float* __restrict__ dVs, float* __restrict__ dK, float* __restrict__ dV, int h0, int N, int nb, int Cq, int CqP,
                                                           int Ck, int Hq, int Hkv, int frozen) {
   constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, NIT = 32 * CPR / 64;
   __shared__ __attribute__((aligned(16))) bf16_t gks[32 * D];
@@ -685,18 +685,19 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
       }
     }
     if (mvalid) {
-      float* ok_ = dKs + ((size_t)hk * N + pm) * D;
-      float* ov_ = dVs + ((size_t)hk * N + pm) * D;
+      // with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order)
+      const size_t to = ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D, from = ((size_t)hk * N + pm) * D;
 #pragma unroll
       for (int t = 0; t < DT; ++t)
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg) {
           const int d = 32 * t + 8 * gg + 4 * half;
-          float4 a = *reinterpret_cast<float4*>(ok_ + d), c = *reinterpret_cast<float4*>(ov_ + d);
-          a.x += dk[t][4 * gg]; a.y += dk[t][4 * gg + 1]; a.z += dk[t][4 * gg + 2]; a.w += dk[t][4 * gg + 3];
-          c.x += dv[t][4 * gg]; c.y += dv[t][4 * gg + 1]; c.z += dv[t][4 * gg + 2]; c.w += dv[t][4 * gg + 3];
-          *reinterpret_cast<float4*>(ok_ + d) = a;
-          *reinterpret_cast<float4*>(ov_ + d) = c;
+          const float4 a = *reinterpret_cast<const float4*>(dKs + from + d), c = *reinterpret_cast<const float4*>(dVs + from + d);
+          float4 k = *reinterpret_cast<float4*>(dK + to + d), v = *reinterpret_cast<float4*>(dV + to + d);
+          k.x += a.x + dk[t][4 * gg]; k.y += a.y + dk[t][4 * gg + 1]; k.z += a.z + dk[t][4 * gg + 2]; k.w += a.w + dk[t][4 * gg + 3];
+          v.x += c.x + dv[t][4 * gg]; v.y += c.y + dv[t][4 * gg + 1]; v.z += c.z + dv[t][4 * gg + 2]; v.w += c.w + dv[t][4 * gg + 3];
+          *reinterpret_cast<float4*>(dK + to + d) = k;
+          *reinterpret_cast<float4*>(dV + to + d) = v;
         }
     }
   }
@@ -706,15 +707,16 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 
 int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* Vs, const float* qc, void* qcb,
                                  const float* L, const float* s_mu, const float* G_c, const void* G_k, const void* G_v,
-                                 const int32_t* off_k, float* dKs, float* dVs, int h0, int hn, hipStream_t st) {
+                                 const int32_t* off_k, const int32_t* perm_k, const float* dKs, const float* dVs, float* dK, float* dV, int h0, int hn,
+                                 hipStream_t st) {
   const int CqP = (d.Cq + 31) / 32 * 32;
   // qcb holds the scaled centroids of the chunk's heads [h0, h0 + hn)
   { MuseProf prof_("k_qc_rows", st); hipLaunchKernelGGL(k_qc_rows, dim3((d.D * CqP + 255) / 256, hn), dim3(256), 0, st, qc + (size_t)h0 * d.Cq * d.D, (bf16_t*)qcb, d.D, d.Cq, CqP, d.scale); }
   dim3 g((d.Ck + 7) / 8 * 8, d.nb - 1, hn / (d.Hq / d.Hkv));
   if (d.D == 64)
-    { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<64>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcb, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, dKs, dVs, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
+    { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<64>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcb, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, perm_k, dKs, dVs, dK, dV, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
   else
-    { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<128>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcb, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, dKs, dVs, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
+    { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<128>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcb, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, perm_k, dKs, dVs, dK, dV, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

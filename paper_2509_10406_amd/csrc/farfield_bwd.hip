@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
     const float* __restrict__ A_k, const T* __restrict__ A_v, const bf16_t* __restrict__ A_kb,
     const int32_t* __restrict__ perm_q, const int32_t* __restrict__ off_q, const int32_t* __restrict__ tile_off,
     const float* __restrict__ LSE, const float* __restrict__ delta, const uint32_t* __restrict__ selmask,
-    float* __restrict__ dQ, int h0, int N, int nb, int Cq, int Ck, float scale) {
+    float* __restrict__ dQ, bool add, int h0, int N, int nb, int Cq, int Ck, float scale) {
   constexpr int U = D / 8, DT = D / 32;
   const int hl = blockIdx.z, hq = h0 + hl;
   const int b = blockIdx.y + 1, NBm = nb - 1;
@@ -244,6 +244,13 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 #pragma unroll
     for (int x = 0; x < 4; ++x) res[u][x] = scale * dq[u / 4][4 * (u % 4) + x];
   float* out = dQ + qn * D + 4 * half;
+  if (add) {  // to what the block-diagonal kernel left
+    float4 o[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) o[u] = *reinterpret_cast<const float4*>(out + 8 * u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) { res[u][0] += o[u].x; res[u][1] += o[u].y; res[u][2] += o[u].z; res[u][3] += o[u].w; }
+  }
 #pragma unroll
   for (int u = 0; u < U; ++u)
     *reinterpret_cast<float4*>(out + 8 * u) = make_float4(res[u][0], res[u][1], res[u][2], res[u][3]);
@@ -253,8 +260,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 // dQ of component 2, per query (16 lanes, dims 64 x + 4 l16 + t, in the order of far_position): for every
 // retrieved cluster, the summaries of the preceding blocks that were NOT retrieved contribute  dl k-bar  with
 // dl = p (dO.v-bar - delta),  p = exp(q~.k-bar + mu-bar - LSE).  The retrieval's share is added here too: bf16 inputs
-// have per-pair dq partials, fp32 inputs walk the retrieved keys, kKeys of them requested together.  The sum is added to
-// the row the tile kernel wrote.  us, every lane summing every block's product and without far_position's order / now: 4498 / 3996
+// have per-pair dq partials, fp32 inputs walk the retrieved keys, kKeys of them requested together.  The sum of
+// this and the tile kernel's row (dQff) is added to what the block-diagonal kernel left in dQ.  us, every lane summing every block's product and without far_position's order / now: 4498 / 3996
 // at 32 heads of 32k with D = 128, 1235 / 1121 at 16 heads of 64k, 1103 / 981 with 128 x 128 clusters, 111 / 73 at 12 heads of
 // 6k, 162 / 120 at 4 fp32 heads of 8k.  (fp32 inputs had both in the tile kernel, a lane pair per query and a key per round trip:
 // 384 us at 4 heads of 8k, r = 4, against 44 + 120 for the two kernels now.)
@@ -266,7 +273,7 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
     const float* __restrict__ s_mu, const float* __restrict__ s_k, const T* __restrict__ s_v,
     const int32_t* __restrict__ perm_q, const int32_t* __restrict__ aq,
     const float* __restrict__ LSE, const float* __restrict__ delta, const int32_t* __restrict__ slotinfo, const float* __restrict__ dqpart,
-    float* __restrict__ dQ, int h0, int N, int nb, int Bs, int Cq, int Ck, int r, int k2e, int Hq, int Hkv, float scale) {
+    const float* __restrict__ dQff, float* __restrict__ dQ, int h0, int N, int nb, int Bs, int Cq, int Ck, int r, int k2e, int Hq, int Hkv, float scale) {
   constexpr int NG = D / 64;
   constexpr bool kF32 = sizeof(T) == 4;
   const int hl = blockIdx.y, hq = h0 + hl;
@@ -294,10 +301,10 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
   const int32_t* ok = off_k + (size_t)hk * ((size_t)nb * Ck + 1);
   const T *Kh = Ks + (size_t)hk * N * D + 4 * l16, *Vh = Vs + (size_t)hk * N * D + 4 * l16;
   const float* Li = L + ((size_t)hl * Cq + i) * N;
-  // the row this kernel adds to is requested now and used at the end
+  // the tile kernel's row is requested now and used at the end
   float4 oldq[NG];
 #pragma unroll
-  for (int x = 0; x < NG; ++x) oldq[x] = *reinterpret_cast<const float4*>(dQ + qn * D + 64 * x + 4 * l16);
+  for (int x = 0; x < NG; ++x) oldq[x] = *reinterpret_cast<const float4*>(dQff + qn * D + 64 * x + 4 * l16);
   // the four queries of a wave are of one block, which bounds the block loops
   // (the bound is a template constant of the loop body below: one straight-line body per value, loads batched)
   const int bwv = __builtin_amdgcn_readfirstlane(b);
@@ -426,6 +433,9 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
   for (int x = 0; x < NG; ++x)
 #pragma unroll
     for (int t = 0; t < 4; ++t) dq[x][t] *= scale;
+  float4 base[NG];  // what the block-diagonal kernel left
+#pragma unroll
+  for (int x = 0; x < NG; ++x) base[x] = *reinterpret_cast<const float4*>(dQ + qn * D + 64 * x + 4 * l16);
   // retrieval part, computed per retrieved pair (already scaled); a slot's pair u exists iff its block bit is set
   if (kF32) {
   } else if (k2e == 1) {
@@ -465,10 +475,10 @@ __global__ void __launch_bounds__(256) k_comp2_bwd_dq(
   }
 #pragma unroll
   for (int x = 0; x < NG; ++x) {
-    float4* out = reinterpret_cast<float4*>(dQ + qn * D + 64 * x + 4 * l16);
     float4 o = oldq[x];
     o.x += dq[x][0]; o.y += dq[x][1]; o.z += dq[x][2]; o.w += dq[x][3];
-    *out = o;
+    o.x += base[x].x; o.y += base[x].y; o.z += base[x].z; o.w += base[x].w;
+    *reinterpret_cast<float4*>(dQ + qn * D + 64 * x + 4 * l16) = o;
   }
 }
 
@@ -669,8 +679,8 @@ __global__ void __launch_bounds__(64) k_cells_to_keys(const T* __restrict__ Ks, 
                                                        const float* __restrict__ qc, const float* __restrict__ L,
                                                        const float* __restrict__ s_mu, const float* __restrict__ G_c,
                                                        const float* __restrict__ G_k, const float* __restrict__ G_v,
-                                                       const int32_t* __restrict__ off_k, float* __restrict__ dKs,
-                                                       float* __restrict__ dVs, int h0, int N, int nb, int Cq, int Ck,
+                                                       const int32_t* __restrict__ off_k, const int32_t* __restrict__ perm_k, const float* __restrict__ dKs,
+                                                       const float* __restrict__ dVs, float* __restrict__ dK, float* __restrict__ dV, int h0, int N, int nb, int Cq, int Ck,
                                                        int Hq, int Hkv, float scale, int frozen) {
   constexpr int U = D / 8, DT = D / 32;
   const int G_ = Hq / Hkv;
@@ -736,71 +746,45 @@ __global__ void __launch_bounds__(64) k_cells_to_keys(const T* __restrict__ Ks, 
       }
     }
     if (mvalid) {
-      float* ok_ = dKs + ((size_t)hk * N + pm) * D;
-      float* ov_ = dVs + ((size_t)hk * N + pm) * D;
+      // with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order)
+      const size_t to = ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D, from = ((size_t)hk * N + pm) * D;
 #pragma unroll
       for (int x = 0; x < DT; ++x)
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg) {
-          int d = 32 * x + 8 * gg + 4 * half;
-          float4 a = *reinterpret_cast<float4*>(ok_ + d), c = *reinterpret_cast<float4*>(ov_ + d);
-          a.x += dk[x][4 * gg]; a.y += dk[x][4 * gg + 1]; a.z += dk[x][4 * gg + 2]; a.w += dk[x][4 * gg + 3];
-          c.x += dv[x][4 * gg]; c.y += dv[x][4 * gg + 1]; c.z += dv[x][4 * gg + 2]; c.w += dv[x][4 * gg + 3];
-          *reinterpret_cast<float4*>(ok_ + d) = a;
-          *reinterpret_cast<float4*>(ov_ + d) = c;
+          const int d = 32 * x + 8 * gg + 4 * half;
+          const float4 a = *reinterpret_cast<const float4*>(dKs + from + d), c = *reinterpret_cast<const float4*>(dVs + from + d);
+          float4 k = *reinterpret_cast<float4*>(dK + to + d), v = *reinterpret_cast<float4*>(dV + to + d);
+          k.x += a.x + dk[x][4 * gg]; k.y += a.y + dk[x][4 * gg + 1]; k.z += a.z + dk[x][4 * gg + 2]; k.w += a.w + dk[x][4 * gg + 3];
+          v.x += c.x + dv[x][4 * gg]; v.y += c.y + dv[x][4 * gg + 1]; v.z += c.z + dv[x][4 * gg + 2]; v.w += c.w + dv[x][4 * gg + 3];
+          *reinterpret_cast<float4*>(dK + to + d) = k;
+          *reinterpret_cast<float4*>(dV + to + d) = v;
         }
     }
   }
 }
 
-// rows back to sequence order, added to what the block-diagonal kernels left: dst[perm[p]] += src[p]
-__global__ void __launch_bounds__(256) k_scatter_rows(const float* __restrict__ dKs, const float* __restrict__ dVs, const int32_t* __restrict__ perm,
-                                                       float* __restrict__ dK, float* __restrict__ dV, int N, int D) {
-  const float* src = blockIdx.z ? dVs : dKs;
-  float* dst = blockIdx.z ? dV : dK;
-  const int CPR = D / 4;
-  size_t h = blockIdx.y;
-  size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= (size_t)N * CPR) return;
-  int p = (int)(c / CPR), cc = (int)(c % CPR);
-  int to = perm[h * N + p];
-  float4* o = reinterpret_cast<float4*>(dst + (h * N + to) * D) + cc;
-  const float4 a = reinterpret_cast<const float4*>(src + (h * N + p) * D)[cc];
-  float4 v = *o;
-  v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
-  *o = v;
-}
-
-// dst[h][n] += src[h][n] for the rows n >= n0 of every head (the queries that have a far field)
-__global__ void __launch_bounds__(256) k_add_rows(const float* __restrict__ src, float* __restrict__ dst, int N, int n0,
-                                                   int D) {
-  const size_t per = (size_t)(N - n0) * (D / 4);
-  const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= per) return;
-  const size_t o = ((size_t)blockIdx.y * N + n0) * (D / 4) + c;
-  const float4 a = reinterpret_cast<const float4*>(src)[o];
-  float4 v = reinterpret_cast<float4*>(dst)[o];
-  v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
-  reinterpret_cast<float4*>(dst)[o] = v;
-}
-
 template <typename T, int D>
 int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, const int32_t* aq, const float* LSE,
-                  FFWorkspace& w, int h0, int hn, hipStream_t sq_, hipStream_t sk_) {
+                  FFWorkspace& w, int h0, int hn, hipStream_t sq_, hipStream_t sk_, hipStream_t sdiag, hipEvent_t diag) {
   // the far-field part of dQ goes to stream sq_, the cell gradients and what they give to keys and values to
-  // stream sk_: the two share inputs only
+  // stream sk_: the two share inputs only.  Either adds its last kernel's results to what the block-diagonal kernels left, which run on
+  // stream sdiag and have ended at the event diag.
+  auto behind_diagonal = [&](hipStream_t s) { return s == sdiag ? hipSuccess : hipStreamWaitEvent(s, diag, 0); };
   const int NBm = d.nb - 1;
   const int W = (d.Ck + 31) / 32;
   dim3 gt((d.Bs / 32 + d.Cq + 1 + 7) / 8 * 8, NBm, hn);
   hipStream_t st = sq_;
+  if (d.r == 0) MUSE_HIP_CHECK(behind_diagonal(st));
   { MuseProf prof_("k_ff_bwd_dq", st); hipLaunchKernelGGL((k_ff_bwd_dq<T, D>), gt, dim3(64), 0, st, Q, dO, qc, w.A_mu, w.A_k, (const T*)w.A_v, (const bf16_t*)w.A_kb,
-                     w.perm_q, w.off_q, w.tile_off, LSE, w.delta, w.selmask, w.dQff, h0, d.N, d.nb, d.Cq, d.Ck, d.scale); }
+                     w.perm_q, w.off_q, w.tile_off, LSE, w.delta, w.selmask, d.r > 0 ? w.dQff : w.dQacc, d.r == 0, h0, d.N, d.nb, d.Cq, d.Ck, d.scale); }
   if (d.r > 0) {
+    MUSE_HIP_CHECK(behind_diagonal(st));
     const dim3 g2 = far_grid(d, hn);
     auto go = [&](auto* kernel) {
       MuseProf prof_("k_comp2_bwd_dq", st);
       hipLaunchKernelGGL(kernel, g2, dim3(256), 0, st, Q, dO, qc, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.s_mu, w.s_k, (const T*)w.s_v,
-                         w.perm_q, aq, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, d.scale);
+                         w.perm_q, aq, LSE, w.delta, w.slotinfo, w.ret_part, w.dQff, w.dQacc, h0, d.N, d.nb, d.Bs, d.Cq, d.Ck, d.r, d.k2e, d.Hq, d.Hkv, d.scale);
     };
     if (d.nb <= 9) go(k_comp2_bwd_dq<T, D, 1>);
     else go(k_comp2_bwd_dq<T, D, 2>);
@@ -821,13 +805,14 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
     if (rc2) return rc2;
   }
   const int G_ = d.Hq / d.Hkv;
+  MUSE_HIP_CHECK(behind_diagonal(st));
   if (sizeof(T) == 2) {
-    int rc2 = muse_launch_cells_to_keys_mx(d, w.Ks, w.Vs, qc, w.qcb, w.L, w.s_mu, w.g_s_c, w.g_s_k, w.g_s_v, w.off_k, w.dKs, w.dVs,
-                                           h0, hn, st);
+    int rc2 = muse_launch_cells_to_keys_mx(d, w.Ks, w.Vs, qc, w.qcb, w.L, w.s_mu, w.g_s_c, w.g_s_k, w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs,
+                                           w.dKacc, w.dVacc, h0, hn, st);
     if (rc2) return rc2;
   } else
   { MuseProf prof_("k_cells_to_keys", st); hipLaunchKernelGGL((k_cells_to_keys<T, D>), dim3(d.Ck, NBm, hn / G_), dim3(64), 0, st, (const T*)w.Ks, (const T*)w.Vs,
-                     qc, w.L, w.s_mu, w.g_s_c, (const float*)w.g_s_k, (const float*)w.g_s_v, w.off_k, w.dKs, w.dVs, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq,
+                     qc, w.L, w.s_mu, w.g_s_c, (const float*)w.g_s_k, (const float*)w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs, w.dKacc, w.dVacc, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq,
                      d.Hkv, d.scale, d.frozen_weights ? 1 : 0); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
@@ -844,7 +829,7 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
   if (!reuse && (rc = muse_ff_prepare<T>(d, K, V, aq, ak, w, st))) return rc;
   if ((rc = muse_launch_delta(d, O, dO, w.delta, st))) return rc;
   // the block-diagonal backward (matrix-core bound) runs beside the far field (memory bound) on a second
-  // stream; it writes the accumulators and the far-field results are added after the join
+  // stream; it writes the accumulators, to which the far field's last kernels add
   MuseAux& ax = muse_aux_stream();
   const bool two = ax.state == 1 && !muse_profiling();
   hipStream_t sb = two ? ax.s : st;
@@ -864,7 +849,7 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
   // With all heads in one chunk the far-field part of dQ follows on the second stream (it needs the selection
   // info and the inverse index, which the first stream builds: event `mid`), beside the cell gradients.
   const bool split = two && w.hc >= HQ;
-  if (two && !split) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));
+  if (two) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));  // the block-diagonal gradients are there
   {
     FillRanges f;
     f.add(w.dKs, nk * D, 0);
@@ -908,24 +893,14 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
         MUSE_HIP_CHECK(hipEventRecord(ax.mid, st));
         MUSE_HIP_CHECK(hipStreamWaitEvent(sb, ax.mid, 0));
       }
-      if (D == 64) rc = run_bwd_chunk<T, 64>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st);
-      else rc = run_bwd_chunk<T, 128>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st);
+      if (D == 64) rc = run_bwd_chunk<T, 64>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st, sb, ax.join);
+      else rc = run_bwd_chunk<T, 128>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st, sb, ax.join);
       if (rc) return rc;
     }
   }
   if (split) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));
   if (two) MUSE_HIP_CHECK(hipStreamWaitEvent(st, ax.join, 0));
   guard.armed = false;
-  {
-    dim3 g((unsigned)(((size_t)N * (D / 4) + 255) / 256), HK, 2);
-    { MuseProf prof_("k_scatter_rows", st); hipLaunchKernelGGL(k_scatter_rows, g, dim3(256), 0, st, w.dKs, w.dVs, w.perm_k, w.dKacc, w.dVacc, N, D); }
-    MUSE_LAUNCH_CHECK();
-  }
-  if (d.nb > 1) {
-    dim3 g((unsigned)(((size_t)(N - d.Bs) * (D / 4) + 255) / 256), HQ);
-    { MuseProf prof_("k_add_rows", st); hipLaunchKernelGGL(k_add_rows, g, dim3(256), 0, st, w.dQff, w.dQacc, N, d.Bs, D); }
-    MUSE_LAUNCH_CHECK();
-  }
   if (d.grad_dtype != MUSE_DTYPE_FP32) {
     CastRanges c;
     c.add(w.dQacc, dQ, nq * D);

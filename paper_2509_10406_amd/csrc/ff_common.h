@@ -366,7 +366,8 @@ int muse_launch_ret_bwd_dq_pairs(const MuseDims& d, const void* Q, const void* d
 // attn_mfma.hip
 int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* Vs, const float* qc, void* qcb,
                                  const float* L, const float* s_mu, const float* G_c, const void* G_k, const void* G_v,
-                                 const int32_t* off_k, float* dKs, float* dVs, int h0, int hn, hipStream_t st);
+                                 const int32_t* off_k, const int32_t* perm_k, const float* dKs, const float* dVs, float* dK, float* dV, int h0, int hn,
+                                 hipStream_t st);
 // dipole.hip: dipole correction of the monopole-only mode (App. B), forward
 template <typename T>
 int muse_dipole_covariances(const MuseDims& d, FFWorkspace& w, hipStream_t st);
