@@ -186,7 +186,8 @@ __global__ void __launch_bounds__(256) k_tilt_logits(const T* __restrict__ Ks, c
 // A_*[b] is the accumulation of blocks 0..b (what query block b+1 sees), b = 0..nb-2; of the summary of
 // key block b alone only mu-bar (s_mu) is written here.
 // ------------------------------------------------------------------------------------------
-template <typename T, int D>
+// PARTS = 2: keys (with the scalars) and values by two waves, where there are few and a wave's chain over the blocks sets the time.
+template <typename T, int D, int PARTS>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 4))) k_summaries(const T* __restrict__ Ks, const T* __restrict__ Vs,
                                                    const float* __restrict__ L, const int32_t* __restrict__ off_k,
                                                    float* __restrict__ s_mu, float* __restrict__ A_mu,
@@ -203,7 +204,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 4)))
   if (j >= Ck) return;
   const int hl = blockIdx.z, hq = h0 + hl;
   const int hk = (hq / Hq) * Hkv + (hq % Hq) / (Hq / Hkv);
-  const int it = blockIdx.y / DS, d0 = (blockIdx.y % DS) * 64;
+  const int it = blockIdx.y / (DS * PARTS), d0 = (blockIdx.y / PARTS % DS) * 64;
+  const bool keys = PARTS == 1 || blockIdx.y % PARTS == 0, values = PARTS == 1 || !keys;
   const int lane = threadIdx.x, col = lane % 32, half = lane / 32;
   const int i = it * 32 + col;
   const bool iv = i < Cq;
@@ -232,8 +234,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 4)))
         const int p = c0 + 8 * u + 4 * half + t;
         const int pc = p < hi ? p : hi - 1;
         c.lg[u][t] = Li[pc];
-        c.kk[u][t] = Pair<T>::ld(Kh, (size_t)pc * D);
-        c.vv[u][t] = Pair<T>::ld(Vh, (size_t)pc * D);
+        if (PARTS == 1) {
+          c.kk[u][t] = Pair<T>::ld(Kh, (size_t)pc * D);
+          c.vv[u][t] = Pair<T>::ld(Vh, (size_t)pc * D);
+        } else {
+          c.kk[u][t] = c.vv[u][t] = Pair<T>::ld(keys ? Kh : Vh, (size_t)pc * D);
+        }
       }
   };
   // position of the chunk in flight: block nb_, first key nc0, end of its cell nhi (nb_ == NBm: none)
@@ -304,8 +310,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 4)))
           AL = fmaf(e, c0 + 8 * u + 4 * half + t < hi ? cur.lg[u][t] : 0.f, AL);
           Aak[0] = mfma32(Pair<T>::lo(cur.kk[u][t]), e, Aak[0]);
           Aak[1] = mfma32(Pair<T>::hi(cur.kk[u][t]), e, Aak[1]);
-          Aav[0] = mfma32(Pair<T>::lo(cur.vv[u][t]), e, Aav[0]);
-          Aav[1] = mfma32(Pair<T>::hi(cur.vv[u][t]), e, Aav[1]);
+          if (PARTS == 1) {
+            Aav[0] = mfma32(Pair<T>::lo(cur.vv[u][t]), e, Aav[0]);
+            Aav[1] = mfma32(Pair<T>::hi(cur.vv[u][t]), e, Aav[1]);
+          }
         }
     }
     S += __shfl_xor(S, 32, 64);
@@ -314,7 +322,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 4)))
     const size_t cell = (((size_t)hl * NBm + b) * Cq + ic) * Ck + j;
     const bool aempty = ASt == 0.f;
     const float ainv = aempty ? 0.f : 1.f / ASt;
-    if (iv && half == 0 && d0 == 0) {
+    if (iv && half == 0 && d0 == 0 && keys) {
       s_mu[cell] = empty ? MUSE_NEG_INF : mx + __logf(S);
       const float amu = aempty ? MUSE_NEG_INF : Amx + __logf(ASt);
       A_mu[cell] = amu;
@@ -375,9 +383,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 4)))
     // The per-block rows s_k, s_v are read for retrieved (query cluster, key cluster) chains only, about one
     // chain in ten: they are written later, for those chains, by k_block_summaries; mu-bar is dense.
     constexpr bool kH = sizeof(T) == 2;
-    if constexpr (kH) emit_planes(Aak, ainv);
-    else emit(A_k, nullptr, Aak, ainv);
-    emit(kH ? nullptr : reinterpret_cast<float*>(A_v), kH ? reinterpret_cast<bf16_t*>(A_v) : nullptr, Aav, ainv);
+    if (keys) {
+      if constexpr (kH) emit_planes(Aak, ainv);
+      else emit(A_k, nullptr, Aak, ainv);
+    }
+    if (values) emit(kH ? nullptr : reinterpret_cast<float*>(A_v), kH ? reinterpret_cast<bf16_t*>(A_v) : nullptr, PARTS == 1 ? Aav : Aak, ainv);
   }
 }
 
@@ -1332,21 +1342,29 @@ template <typename T>
 int muse_ff_summaries(const MuseDims& d, const float* qc, FFWorkspace& w, int h0, int hn, hipStream_t st) {
   const int N = d.N;
   dim3 gl((N + 255) / 256, hn);
-  dim3 gs((d.Ck + 7) / 8 * 8, ((d.Cq + 31) / 32) * (d.D / 64), hn);
+  // Two waves instead of one where there is one for every SIMD at most.  us, one / two: 73 / 60 at 12 heads of 6k with 23 x 71 (852
+  // waves), 83 / 69 and 90 / 77 at 4 and 8 of 8k with 32 x 64 (256, 512), fp32 53 / 48 at 4 of 8k with 32 x 128 (512), 28 / 25 at one of 2k, D =
+  // 128 110 / 108 at 8 of 8k (1024); 2048 waves 156 / 148 and 83 / 78, D = 128 230 / 285; 8192 waves 222 / 247.
+  const long long waves = (long long)d.Ck * ((d.Cq + 31) / 32) * (d.D / 64) * d.B * d.Hq;
+  const int parts = waves <= 1024 ? 2 : 1;
+  dim3 gs((d.Ck + 7) / 8 * 8, ((d.Cq + 31) / 32) * (d.D / 64) * parts, hn);
+  auto go = [&](auto* kernel) {
+    MuseProf prof_("k_summaries", st);
+    hipLaunchKernelGGL(kernel, gs, dim3(64), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.s_mu, w.A_mu, w.A_k, (T*)w.A_v, (bf16_t*)w.A_kb,
+                       (uint16_t*)w.A_km, w.A_c, h0, N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv);
+  };
   if (d.D == 64) {
     if constexpr (sizeof(T) == 2)
       launch_tilt_logits_mx<64>(d, (const bf16_t*)w.Ks, qc, w.L, h0, hn, st);
     else
       { MuseProf prof_("k_tilt_logits", st); hipLaunchKernelGGL((k_tilt_logits<T, 64>), gl, dim3(256), 0, st, (const T*)w.Ks, qc, w.L, h0, N, d.Cq, d.Hq, d.Hkv, d.scale); }
-    { MuseProf prof_("k_summaries", st); hipLaunchKernelGGL((k_summaries<T, 64>), gs, dim3(64), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.s_mu,
-                       w.A_mu, w.A_k, (T*)w.A_v, (bf16_t*)w.A_kb, (uint16_t*)w.A_km, w.A_c, h0, N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv); }
+    parts == 2 ? go(k_summaries<T, 64, 2>) : go(k_summaries<T, 64, 1>);
   } else {
     if constexpr (sizeof(T) == 2)
       launch_tilt_logits_mx<128>(d, (const bf16_t*)w.Ks, qc, w.L, h0, hn, st);
     else
       { MuseProf prof_("k_tilt_logits", st); hipLaunchKernelGGL((k_tilt_logits<T, 128>), gl, dim3(256), 0, st, (const T*)w.Ks, qc, w.L, h0, N, d.Cq, d.Hq, d.Hkv, d.scale); }
-    { MuseProf prof_("k_summaries", st); hipLaunchKernelGGL((k_summaries<T, 128>), gs, dim3(64), 0, st, (const T*)w.Ks, (const T*)w.Vs, w.L, w.off_k, w.s_mu,
-                       w.A_mu, w.A_k, (T*)w.A_v, (bf16_t*)w.A_kb, (uint16_t*)w.A_km, w.A_c, h0, N, d.nb, d.Cq, d.Ck, d.Hq, d.Hkv); }
+    parts == 2 ? go(k_summaries<T, 128, 2>) : go(k_summaries<T, 128, 1>);
   }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
