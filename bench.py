@@ -63,9 +63,9 @@ def kernel_models(w, p):
         m["k_ff_bwd_dq"] = ("hbm", PEAK["hbm"], (cell_in + rows_qg + Nff * D * 4) * H, "byte")
         # the gradients of the per-block cells leave it: mu-bar of both copies in
         m["k_ff_bwd_cells_mx"] = ("hbm", PEAK["hbm"], (cell_in + cells * 4 + rows_qg + cell_g) * H, "byte")
-        # per-block cell gradients and mu-bar in, tilt logits in, key/value rows in, fp32 gradient rows read-modify-write
+        # per-block cell gradients and mu-bar in, tilt logits in, key/value rows in, two fp32 gradient rows in and one out
         m["k_cells_to_keys_mx"] = ("hbm", PEAK["hbm"], (cell_g + cells * 4 + Cq * Nff * 4 + 2 * Nff * D * es) * H
-                                   + 2 * 2 * Nff * D * 4 * Hk, "byte")
+                                   + 3 * 2 * Nff * D * 4 * Hk, "byte")
     else:
         for name, nmm in (("k_ff_bwd_dq", 3), ("k_ff_bwd_cells", 4)):
             m[name] = ("mfma", PEAK[far], nmm * 2 * Nff * Ck * D * H, "flop")

@@ -199,8 +199,7 @@ def test_forward_with_small_workspace_chunks_heads():
 def test_forward_tiles_with_many_tied_clusters():
     """Every key is the same row and the key clusters are dealt round-robin (teacher-forced), so in every block all
     64 accumulated cells of a query cluster are equal: every cluster scores the same, all of them are candidates
-    for the r best, and the candidate lists of the one-plane tile kernel (r + 8 entries per lane half, 32 clusters
-    per half here) overflow in every tile.  Those tiles are left to the two-plane kernel; the result must be a
+    for the r best, and the order of the cluster numbers alone decides in every tile.  The result must be a
     valid selection (nothing chosen scores below something left out, by the oracle's scores) and O, LSE must be
     the oracle's at that selection (Sec. 3.2, Eq. 7; Sec. 3.3)."""
     w = small("cfg2", N=1024, Hq=2, Hkv=1, Cq=4, Ck=64, r=3, block=128, kmeans_iters=1)
