@@ -870,13 +870,15 @@ int launch(const MuseDims& d, const T* Q, const T* dO, const float* qc, const fl
     looked = head_of;
     const int bits = std::max(5, 32 - __builtin_clz(d.Ck - 1 | 1));
     static_assert(MUSE_MAX_CLUSTERS <= 1 << 11, "bits of a cluster's number");
-    auto sort = [&](auto* kernel) {
-      if (lds > 64 * 1024 && hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (kListWaves + 1) * MUSE_MAX_CLUSTERS * 4) != hipSuccess) return;
+    auto sort = [&](auto* kernel) -> int {
+      if (lds > 64 * 1024) MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (kListWaves + 1) * MUSE_MAX_CLUSTERS * 4));
       MuseProf prof_("k_chain_lists", st);
       hipLaunchKernelGGL(kernel, dim3(d.Cq, hn), dim3(64 * nw), lds, st, w.perm_q, w.off_q, LSE, w.delta, w.slotinfo, chains, lists, head_of, h0, d.N, d.Bs, d.nb,
                          d.Cq, d.Ck, d.r);
+      MUSE_LAUNCH_CHECK();
+      return MUSE_OK;
     };
-    auto sort_v = [&](auto v4) {
+    auto sort_v = [&](auto v4) -> int {
       constexpr bool V = decltype(v4)::value;
       switch (bits) {
         case 5: return sort(k_chain_lists<V, 5>);
@@ -888,7 +890,8 @@ int launch(const MuseDims& d, const T* Q, const T* dO, const float* qc, const fl
         default: return sort(k_chain_lists<V, 11>);
       }
     };
-    d.r % 4 == 0 ? sort_v(std::true_type()) : sort_v(std::false_type());
+    // without the lists the next kernel must not run
+    if (const int rc = d.r % 4 == 0 ? sort_v(std::true_type()) : sort_v(std::false_type())) return rc;
     auto go = [&](auto* kernel) { MuseProf prof_("k_chain_grads", st); hipLaunchKernelGGL(kernel, dim3((unsigned)(cq8 * S), hn), dim3(one ? 64 : 256), 0, st, Q, dO, qc, w.s_mu,
                        w.s_k, (const T*)w.s_v, LSE, w.delta, chains, lists, head_of, w.g_s_c, (T*)w.g_s_k, (T*)w.g_s_v, h0, d.N, d.Bs, d.nb, d.Cq, d.Ck,
                        d.r, S, share, d.scale); };
