@@ -5,10 +5,11 @@
 
 namespace {
 
-// The scores run on the 16-bit matrix cores without losing the precision that decides selections: k-bar is stored as a bf16 plane plus an fp16 plane of the remainder (together 19
-// significant bits or more), the query operand is the bf16 query itself (exact, also as fp16), and the query
-// centroid's share of q~ . k-bar is a per-cell scalar c = scale * qc_i . k-bar, the weighted mean of the tilt
-// logits that the kernel which wrote the planes has at hand:  score = scale * q . (hi + mid) + (mu-bar - c).
+// The scores run on the 16-bit matrix cores without losing the precision that decides selections: k-bar is stored as a bf16 plane
+// plus an fp16 plane of the remainder (together 19 significant bits or more), the query operand is the bf16 query itself (as fp16 it is
+// exact from 2^-17 to 65504; larger entries make infinite scores), and the query centroid's share of q~ . k-bar is a per-cell scalar
+// c = scale * qc_i . k-bar, the weighted mean of the tilt logits that the kernel which wrote the planes has at hand:
+//   score = scale * q . (hi + mid) + (mu-bar - c).
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 
 // top RCAP of two lists sorted from the largest down, into a
@@ -204,7 +205,8 @@ __global__ void __launch_bounds__(64 * kFfWaves) __attribute__((amdgpu_waves_per
         }
       }
     }
-    float thr = __builtin_huge_valf();  // the query's r-th largest score
+    // the query's r-th largest score; not a number: none is taken out (no score compares with it, one that is infinite neither)
+    float thr = __builtin_nanf("");
     if (r > 0) {
       float other[RCAP];
 #pragma unroll
@@ -308,7 +310,7 @@ __global__ void __launch_bounds__(64 * kFfWaves) __attribute__((amdgpu_waves_per
           for (int e = 0; e < 16; ++e)
             if (S[t][e] > ps || (S[t][e] == ps && jt + 8 * (e / 4) + e % 4 <= pj)) S[t][e] = MUSE_NEG_INF;
         }
-        thr = __builtin_huge_valf();
+        thr = __builtin_nanf("");
       }
     }
     if (L::kLate && TPW > 1) bring_v(1);

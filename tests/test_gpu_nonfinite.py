@@ -1,6 +1,7 @@
 """A query row of Q or dO that is not finite (an overflow one wants to find) reaches the gradients of the keys that the query
 attends, directly or through a summary, and nothing behind its own block: the keys of later blocks get what they get without
-that row, and the other queries' dQ is untouched.  Clusters of many queries, so that the chains' tiles mix blocks."""
+that row, and the other queries' dQ is untouched.  Clusters of many queries, so that the chains' tiles mix blocks.  In the forward
+without retrieval, cluster scores that overflow reach that query's output, and no other query's."""
 import math
 
 import pytest
@@ -49,3 +50,24 @@ def test_rows_that_are_not_finite_stay_in_their_past(name, what):
         others[n] = False
         assert got[0][0, 0, others].isfinite().all() and not got[0][0, 0, n].isfinite().all()
         assert not got[1][0, 0, : n + 1].isfinite().all()
+
+
+@pytest.mark.parametrize("D,Ck", [(64, 40), (64, 300), (128, 40), (128, 600)])
+def test_overflowing_scores_reach_the_output(D, Ck):
+    """A finite query row with one entry past the fp16 range has infinite scores, of both signs, against the remainder plane of the
+    key summaries.  With nothing retrieved their softmax is no number, and must not come out as the softmax of the rest; the
+    other rows keep their bits."""
+    N, block, n = 16 * Ck, 2 * Ck, 15 * Ck + 3
+    g = torch.Generator(device="cuda").manual_seed(7)
+    Q, K, V = (torch.randn(1, 1, N, D, generator=g, device="cuda").bfloat16() for _ in range(3))
+    p = mb.Params(B=1, Hq=1, Hkv=1, N=N, D=D, Cq=2, Ck=Ck, r=0, k2=1, block=block, kmeans_iters=0, dtype=mb.BF16, grad_dtype=mb.FP32)
+    qc = torch.randn(1, 1, 2, D, generator=g, device="cuda")
+    aq = torch.randint(0, 2, (1, 1, N), generator=g, device="cuda", dtype=torch.int32)
+    ak = (torch.arange(N, device="cuda", dtype=torch.int32) % Ck).view(1, 1, N)  # two keys a cell: no summary is a bf16 row
+    O, LSE, _, _ = mb.muse_fwd(p, Q, K, V, qc, aq, ak)
+    Qi = Q.clone()
+    Qi[0, 0, n, 3] = 80000.0
+    Oi, Li, _, _ = mb.muse_fwd(p, Qi, K, V, qc, aq, ak)
+    others = torch.arange(N, device="cuda") != n
+    assert O.isfinite().all() and torch.equal(Oi[0, 0, others], O[0, 0, others]) and torch.equal(Li[0, 0, others], LSE[0, 0, others])
+    assert not Li[0, 0, n].isfinite() and not Oi[0, 0, n].isfinite().any()
