@@ -65,7 +65,10 @@ __device__ __forceinline__ void lds_read() {
 //              a cluster that reaches the last of them is selected, and its place is the number of larger ones.  Where two
 //              scores are equal the places are given out one by one, lowest cluster first.
 //   softmax    over the others, against the maximum of all waves, and P V, the first value tiles on their way since the scores
-//              were made; the waves' sums meet in LDS.
+//              were made; the waves' sums meet in LDS.  A weight enters as two bf16 terms (16 bits and more): the largest of
+//              those that stay behind a selection would be what bf16 rounds worst.  The second term is free: the kernel waits for memory
+//              (layer at 16 heads of 64k 28523 us with one term, 28555 with two; at 32 heads of 32k, D = 128 41411 and 41318), and O is
+//              closer to its value in 64 bits (4096 tokens, 16 x 256 clusters, r = 8: 2.07e-3 and 2.01e-3 of the norm).
 // Bound by the summaries' way from memory: 12.7 GB at 16 heads of 64k with 256 x 1024 clusters, 4.9 TB/s; without the selection
 // (insertion and places) it takes 2577 us instead of 2614.  The kernel before this one was a wave per tile that read the bf16
 // plane of k-bar for a bound of the scores and then everything (8 D + 8 bytes), left tiles with many candidates to a second launch, and
@@ -354,8 +357,14 @@ __global__ void __launch_bounds__(64 * kFfWaves) __attribute__((amdgpu_waves_per
     for (int G = 0; G < 2; ++G) {
       const bf16x8_t pf = pack8(S[t], 2 * G, 2 * G + 1);
 #pragma unroll
-      for (int x = 0; x < DT; ++x)
-        o[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_cols<D>(vt, 16 * G, x, lane), pf, o[x], 0, 0, 0);
+      for (int e = 0; e < 8; ++e) S[t][8 * G + e] -= (float)pf[e];  // what the rounding left
+      const bf16x8_t pr = pack8(S[t], 2 * G, 2 * G + 1);
+#pragma unroll
+      for (int x = 0; x < DT; ++x) {
+        const bf16x8_t v = tile_cols<D>(vt, 16 * G, x, lane);
+        o[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf, o[x], 0, 0, 0);
+        o[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pr, o[x], 0, 0, 0);
+      }
     }
     if (t + NB < TPW) {
       lds_read();

@@ -1,7 +1,7 @@
 """GPU parity of the far-field forward of bf16 inputs (k_farfield_tiles) where several waves share a tile of queries: every number
 of tiles per wave at both head dimensions, waves that are left without a tile, lists of 8, 16 and 32 that are all selected, no
 selection at all.  Scores that tie between waves, at the last place and in front of it.  The wide forms of large calls against
-the narrow ones of single heads.  Tolerances are those of the parity suite."""
+the narrow ones of single heads.  Tolerances are those of the parity suite.  And the weights of the softmax against 64 bits."""
 import numpy as np
 import pytest
 import torch
@@ -71,3 +71,31 @@ def test_large_calls_as_single_heads(Ck, r):
         # fp32 sums in another order, then one bf16 rounding: one unit in the last place of the entry, or of the far field's share
         assert ((o[0, 0].float() - O[0, h].float()).abs() <= 2.0**-7 * O[0, h].float().abs() + 1e-4).all()
         torch.testing.assert_close(lse[0, 0], LSE[0, h], rtol=0, atol=1e-5)
+
+
+@pytest.mark.parametrize("D,Ck,r", [(64, 40, 0), (64, 96, 1), (64, 300, 4), (64, 1100, 0), (128, 48, 3), (128, 300, 0), (128, 600, 16)])
+def test_weights_against_64_bits(D, Ck, r):
+    """With one key per cell the second block's queries attend the first block's keys exactly, by way of the summaries, and keys of their own
+    block that weigh e^-64: O is the softmax's sum of the first block's values.  Its error is one rounding to bf16 (2^-9 of the
+    entry) and what the weights' precision makes of sum p |v|: 2^-17 (a bf16 weight and a bf16 remainder) plus fp32 exponentials and
+    scores (2^-18 for scores up to 16), bounded here at twice their sum.  Weights in bf16 alone are 2^-9 off."""
+    g = torch.Generator().manual_seed(11)
+    N, S = 2 * Ck, 1.0
+    Q, K, V = (torch.randn(1, 1, N, D, generator=g) for _ in range(3))
+    Q, K = Q * D**-0.5, K.clone()
+    Q[..., 0], K[0, 0, :Ck, 0], K[0, 0, Ck:, 0] = 4.0, 0.0, -16.0
+    Q, K, V = (x.bfloat16() for x in (Q, K, V))
+    p = mb.Params(B=1, Hq=1, Hkv=1, N=N, D=D, Cq=3, Ck=Ck, r=r, k2=1, block=Ck, kmeans_iters=0, dtype=mb.BF16, grad_dtype=mb.FP32, scale=S)
+    qc = 0.1 * torch.randn(1, 1, 3, D, generator=g)
+    aq = torch.randint(0, 3, (1, 1, N), generator=g, dtype=torch.int32)
+    ak = (torch.randperm(N, generator=g, dtype=torch.int32) % Ck).view(1, 1, N)
+    ak[0, 0, :Ck] = torch.randperm(Ck, generator=g, dtype=torch.int32)
+    O, LSE, _, _ = (x.cpu() for x in mb.muse_fwd(p, *(x.cuda() for x in (Q, K, V, qc, aq, ak))))
+    q, k, v = (x[0, 0].double() for x in (Q, K, V))
+    s = q[Ck:] @ k[:Ck].T
+    w = s.softmax(-1)
+    want = w @ v[:Ck]
+    bound = 2.0**-8 * want.abs() + 2.0**-15 * (w @ v[:Ck].abs())
+    err = (O[0, 0, Ck:].double() - want).abs()
+    assert (err <= bound).all(), (err / bound).max()
+    torch.testing.assert_close(LSE[0, 0, Ck:].double(), s.logsumexp(-1), rtol=0, atol=2e-5)
