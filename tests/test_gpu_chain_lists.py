@@ -25,6 +25,9 @@ CASES = {
     "lists_nb16": ("cfg2", dict(N=2048, Hq=40, Hkv=20, Cq=16, Ck=33, r=6, k2=2, block=128, kmeans_iters=1)),
     # a cluster of 3584 far queries: several rounds of 64 per wave
     "lists_one_cluster": ("cfg2", dict(N=4096, Hq=1, Hkv=1, Cq=1, Ck=40, r=20, block=512, kmeans_iters=1)),
+    # few query clusters: every group of chains has a workgroup of its own, whose waves share it; one and two chains a group
+    "lists_shared_nb16": ("cfg2", dict(N=2048, Hq=2, Hkv=1, Cq=2, Ck=37, r=6, k2=2, block=128, kmeans_iters=1)),
+    "lists_shared_d128": ("cfg2", dict(D=128, N=1536, Hq=1, Hkv=1, Cq=1, Ck=57, r=17, block=512, kmeans_iters=1)),
     "lists_two_blocks": ("cfg2", dict(N=512, Hq=2, Hkv=1, Cq=3, Ck=17, r=4, block=256, kmeans_iters=1)),
 }
 
