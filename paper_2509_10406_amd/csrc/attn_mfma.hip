@@ -737,15 +737,16 @@ int muse_launch_attn_bwd_mfma(const MuseDims& d, int Bs, const void* Q, const vo
   float sl = d.scale * 1.4426950408889634f;
   const bf16_t *q = (const bf16_t*)Q, *k = (const bf16_t*)K, *v = (const bf16_t*)V, *g = (const bf16_t*)dO;
   const bool to_lds = muse_attn_rows_to_lds(Q, K, V, dO);
-  if (to_lds && muse_attn_dq_wide(d, Bs)) {
+  if (!dQacc) {
+  } else if (to_lds && muse_attn_dq_wide(d, Bs)) {
     if (int rc = muse_launch_attn_dq_wide(d, Bs, Q, K, V, dO, LSE, delta, dQacc, st)) return rc;
   } else {
     MuseProf prof_("k_flash_bwd_dq", st);
     if (d.D == 64) hipLaunchKernelGGL(k_flash_bwd_dq<64>, gq, dim3(256), 0, st, q, k, v, g, LSE, delta, dQacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl);
     else hipLaunchKernelGGL(k_flash_bwd_dq<128>, gq, dim3(256), 0, st, q, k, v, g, LSE, delta, dQacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl);
   }
-  if (to_lds && muse_attn_dkv_wide(d, Bs)) return muse_launch_attn_dkv_wide(d, Bs, Q, K, V, dO, LSE, delta, dKacc, dVacc, st);
-  {
+  if (dKacc && to_lds && muse_attn_dkv_wide(d, Bs)) return muse_launch_attn_dkv_wide(d, Bs, Q, K, V, dO, LSE, delta, dKacc, dVacc, st);
+  if (dKacc) {
     MuseProf prof_("k_flash_bwd_dkv", st);
     if (d.D == 64) hipLaunchKernelGGL(k_flash_bwd_dkv_p<64>, gk, dim3(256), 0, st, q, k, v, g, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl);
     else hipLaunchKernelGGL(k_flash_bwd_dkv128, gk, dim3(512), 0, st, q, k, v, g, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl);

@@ -12,6 +12,7 @@
 //   where G = own gradient + sum over later accumulated cells a of exp(mu - Amu[a]) gA[a].
 // Every reduction has one owner (no float atomics): cells by (query cluster, key-cluster tile),
 // keys by (key block, key-cluster tile).
+#include <algorithm>
 #include <type_traits>
 
 #include "ff_common.h"
@@ -769,7 +770,7 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
                   FFWorkspace& w, int h0, int hn, hipStream_t sq_, hipStream_t sk_, hipStream_t sdiag, hipEvent_t diag) {
   // the far-field part of dQ goes to stream sq_, the cell gradients and what they give to keys and values to
   // stream sk_: the two share inputs only.  Either adds its last kernel's results to what the block-diagonal kernels left, which run on
-  // stream sdiag and have ended at the event diag.
+  // stream sdiag and, as far as another stream adds to them, have ended at the event diag.
   auto behind_diagonal = [&](hipStream_t s) { return s == sdiag ? hipSuccess : hipStreamWaitEvent(s, diag, 0); };
   const int NBm = d.nb - 1;
   const int W = (d.Ck + 31) / 32;
@@ -818,6 +819,21 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
   return MUSE_OK;
 }
 
+// Whether the block diagonal takes so much longer than the far field up to k_cells_to_keys*, which waits for it, that dK and dV are made
+// first and that kernel does not wait for dQ as well.  A query's multiply-adds over its block (fp32 ones take several times as long, and dK, dV more
+// where their tiles of 64 keys leave CUs idle) against the key clusters and the selected chains' blocks that it meets.
+// Backward, us, dQ first / dK, dV first (and with far-field gradients added by launches behind both streams):
+//   2 heads of 3.5k, 2 blocks, r = 0, 3 x 9  192 / 169 (171)      4 of 32k, r = 8, 64 x 64            899 / 929 (976)
+//   8 of 32k, 2 blocks, r = 4, 64 x 64      2352 / 2229 (2350)    16 (4) of 64k, r = 4, 128 x 128    6579 / 6828 (6933)
+//   8 (2) of 32k, 4 blocks, r = 4, 64 x 128 1656 / 1523 (1709)    16 of 64k, r = 8, 128 x 128        8652 / 8725 (9068)
+//   fp32, 2 of 5k, 16 blocks, r = 0          309 / 255 (273)      8 (2) of 16k, D = 128, r = 8       1220 / 1259 (1285)
+//   fp32, 8 of 8k, 2 blocks, r = 8          2469 / 2411 (2416)    8 of 16k, r = 0, 64 x 256           520 / 529 (555)
+//   fp32, 8 (1) of 9.5k, D = 128, r = 8     5120 / 4902 (4986)    fp32, 4 of 8k, r = 8, 32 x 128      817 / 824 (818)
+bool diagonal_is_longer(const MuseDims& d) {
+  const double idle = std::max(1.0, 256.0 * 64 / ((double)d.B * d.Hkv * d.N));
+  return d.Bs * (d.dtype == MUSE_DTYPE_BF16 ? 1.0 : 16.0) * (3 + 4 * idle) / 7 >= 32.0 * d.Ck + 320.0 * d.r * (d.nb - 1);
+}
+
 template <typename T>
 int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T* O, const float* LSE, const T* dO,
                   const float* qc, const int32_t* aq, const int32_t* ak, const int32_t* selc, const int32_t* selb,
@@ -845,11 +861,16 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
     MUSE_HIP_CHECK(hipStreamWaitEvent(sb, ax.fork, 0));
     guard.armed = true;
   }
-  if ((rc = muse_launch_attn_bwd(d, d.Bs, Q, K, V, dO, LSE, w.delta, w.dQacc, w.dKacc, w.dVacc, sb))) return rc;
   // With all heads in one chunk the far-field part of dQ follows on the second stream (it needs the selection
-  // info and the inverse index, which the first stream builds: event `mid`), beside the cell gradients.
-  const bool split = two && w.hc >= HQ;
-  if (two) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));  // the block-diagonal gradients are there
+  // info and the inverse index, which the first stream builds: event `mid`), beside the cell gradients.  The first stream then needs only
+  // dK and dV of the block diagonal.
+  const bool split = two && w.hc >= HQ, kv_first = split && diagonal_is_longer(d);
+  if (kv_first) {
+    if ((rc = muse_launch_attn_bwd(d, d.Bs, Q, K, V, dO, LSE, w.delta, nullptr, w.dKacc, w.dVacc, sb))) return rc;
+    MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));
+  }
+  if ((rc = muse_launch_attn_bwd(d, d.Bs, Q, K, V, dO, LSE, w.delta, w.dQacc, kv_first ? nullptr : w.dKacc, kv_first ? nullptr : w.dVacc, sb))) return rc;
+  if (two && !kv_first) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));
   {
     FillRanges f;
     f.add(w.dKs, nk * D, 0);
