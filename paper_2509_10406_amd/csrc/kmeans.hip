@@ -34,6 +34,13 @@ template <typename T>
 struct KSides {
   KSide<T> s[2];
 };
+// A launch of one problem takes it as it is: looking for it costs 0.2 to 0.3 us a launch (a clustering on two streams, before / now: fp32, one head
+// of 3k with 69 x 224, D = 128, 996 / 990 us, 4 of 8k with 32 x 128 339 / 335; bf16, 12 of 6k with 23 x 71 264.5 / 262.3).
+template <typename T>
+__device__ __forceinline__ KSide<T> side_of(const KSide<T>& one, int y, int& h) {
+  h = y;
+  return one;
+}
 template <typename T>
 __device__ __forceinline__ KSide<T> side_of(const KSides<T>& both, int y, int& h) {
   const bool second = y >= both.s[0].heads;
@@ -94,8 +101,8 @@ __global__ void __launch_bounds__(256) k_init_centroids(KSides<T> both, int N, i
 // per point and 4-byte reads it was bound by LDS and by too few waves: 45 -> 16 us at 4 heads of 8k
 // points, 32 and 128 centroids.
 // ------------------------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(256) k_assign_f32(KSides<float> both, int N) {
+template <int D, class Sides>
+__global__ void __launch_bounds__(256) k_assign_f32(Sides both, int N) {
   int h;
   const KSide<float> side = side_of(both, blockIdx.y, h);
   const float *__restrict__ X = side.X, *__restrict__ chat = side.chat, *__restrict__ nhc2 = side.nhc2;
@@ -275,8 +282,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 // ------------------------------------------------------------------------------------------
 constexpr float kPadScore = -3.0e38f;  // score of the padding rows past C: finite, so that tagging its low bits keeps it a number
 constexpr int kResWaves = 8;
-template <int D>
-__global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) k_assign_res(KSides<bf16_t> both, int N) {
+template <int D, class Sides>
+__global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) k_assign_res(Sides both, int N) {
   int h;
   const KSide<bf16_t> side = side_of(both, blockIdx.y, h);
   const bf16_t *__restrict__ X = side.X, *__restrict__ chat = side.chat;
@@ -650,8 +657,8 @@ __global__ void __launch_bounds__(WIDE ? 64 * (64 / (D * (int)sizeof(T) / 16)) :
 // from L2, so it is for small problems (scan_update); what it saves is a launch in a chain of dependent ones.
 constexpr int kScan = 1024;
 constexpr long long kScanMost = 4 << 20;
-template <typename T, int D>
-__global__ void __launch_bounds__(64 * (64 / (D * (int)sizeof(T) / 16))) k_update_scan(KSides<T> both, int N, int Bs) {
+template <typename T, int D, class Sides>
+__global__ void __launch_bounds__(64 * (64 / (D * (int)sizeof(T) / 16))) k_update_scan(Sides both, int N, int Bs) {
   int h;
   const KSide<T> side = side_of(both, blockIdx.y, h);
   const T* __restrict__ X = side.X;
@@ -659,7 +666,7 @@ __global__ void __launch_bounds__(64 * (64 / (D * (int)sizeof(T) / 16))) k_updat
   float *__restrict__ cent = side.cent, *__restrict__ nhc2 = side.nhc2;
   T* __restrict__ chat = side.chat;
   const int C = side.C;
-  if ((int)blockIdx.x >= C) return;
+  if (std::is_same_v<Sides, KSides<T>> && (int)blockIdx.x >= C) return;  // the side with fewer clusters
   constexpr int S = 64 / (D * (int)sizeof(T) / 16), EPL = D / 64;
   __shared__ float sum[S][D];
   __shared__ int cnt[S];
@@ -1252,14 +1259,19 @@ int ClusterRun<T>::stream(const int32_t* init_idx, int32_t* trace, float* counts
 }
 
 // The launches of an iteration, for one problem or for two at once.
-template <typename T>
+template <typename T, bool TWO>
 struct ClusterLaunch {
+  using Sides = std::conditional_t<TWO, KSides<T>, KSide<T>>;
   KSides<T> k;
   int N, D, Bs, heads;
   hipStream_t st;
   ClusterLaunch(const ClusterRun<T>& a, const int32_t* ia, const ClusterRun<T>* b, const int32_t* ib)
       : k{{a.side(ia), b ? b->side(ib) : a.side(ia)}}, N(a.d.N), D(a.d.D), Bs(a.d.Bs), heads(a.heads + (b ? b->heads : 0)), st(a.st) {
     if (!b) k.s[1].heads = 0;
+  }
+  const Sides& sides() const {
+    if constexpr (TWO) return k;
+    else return k.s[0];
   }
   int init(int rows) {  // the centroids that the first assignment reads
     { MuseProf prof_("k_init_centroids", st); hipLaunchKernelGGL(k_init_centroids<T>, dim3((rows + 3) / 4), dim3(256), 0, st, k, N, D); }
@@ -1272,16 +1284,16 @@ struct ClusterLaunch {
     if constexpr (sizeof(T) == 4) {
       dim3 g((N + 63) / 64, heads);
       MuseProf prof_("k_assign_f32", st);
-      if (D == 64) hipLaunchKernelGGL(k_assign_f32<64>, g, dim3(256), 0, st, k, N);
-      else hipLaunchKernelGGL(k_assign_f32<128>, g, dim3(256), 0, st, k, N);
+      if (D == 64) hipLaunchKernelGGL((k_assign_f32<64, Sides>), g, dim3(256), 0, st, sides(), N);
+      else hipLaunchKernelGGL((k_assign_f32<128, Sides>), g, dim3(256), 0, st, sides(), N);
     } else {
       const size_t bytes = resident_bytes(C, D);
       MuseProf prof_("k_assign_bf16", st);
       if (bytes <= 160 * 1024) {
         static bool attr_set = false;
         if (!attr_set) {
-          MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<64>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-          MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<128>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+          MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<64, Sides>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+          MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)k_assign_res<128, Sides>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
           attr_set = true;
         }
         const int bp = (D == 64 ? 64 : 32) * kResWaves;  // points per batch
@@ -1289,8 +1301,8 @@ struct ClusterLaunch {
         int gx = (256 + heads - 1) / heads;  // about one workgroup per CU over all heads
         gx = gx > nbatch ? nbatch : gx;
         dim3 g(gx, heads);
-        if (D == 64) hipLaunchKernelGGL(k_assign_res<64>, g, dim3(64 * kResWaves), bytes, st, k, N);
-        else hipLaunchKernelGGL(k_assign_res<128>, g, dim3(64 * kResWaves), bytes, st, k, N);
+        if (D == 64) hipLaunchKernelGGL((k_assign_res<64, Sides>), g, dim3(64 * kResWaves), bytes, st, sides(), N);
+        else hipLaunchKernelGGL((k_assign_res<128, Sides>), g, dim3(64 * kResWaves), bytes, st, sides(), N);
       } else {  // (one problem)
         constexpr int PT = 2;
         dim3 g((N + 4 * 32 * PT - 1) / (4 * 32 * PT), heads);
@@ -1305,8 +1317,8 @@ struct ClusterLaunch {
     MuseProf prof_("k_update", st);
     constexpr int S64 = 64 / (64 * (int)sizeof(T) / 16), S128 = 64 / (128 * (int)sizeof(T) / 16);  // row slots
     const dim3 g(std::max(k.s[0].C, k.s[1].C), heads);
-    if (D == 64) hipLaunchKernelGGL((k_update_scan<T, 64>), g, dim3(64 * S64), 0, st, k, N, Bs);
-    else hipLaunchKernelGGL((k_update_scan<T, 128>), g, dim3(64 * S128), 0, st, k, N, Bs);
+    if (D == 64) hipLaunchKernelGGL((k_update_scan<T, 64, Sides>), g, dim3(64 * S64), 0, st, sides(), N, Bs);
+    else hipLaunchKernelGGL((k_update_scan<T, 128, Sides>), g, dim3(64 * S128), 0, st, sides(), N, Bs);
     MUSE_LAUNCH_CHECK();
     return MUSE_OK;
   }
@@ -1316,7 +1328,7 @@ struct ClusterLaunch {
 template <typename T>
 int ClusterRun<T>::iteration(int it) {
   const int N = d.N, D = d.D, rows = heads * C;
-  ClusterLaunch<T> own(*this, nullptr, nullptr, nullptr);
+  ClusterLaunch<T, false> own(*this, nullptr, nullptr, nullptr);
   if (int rc = own.assign()) return rc;
   if (it == T_ && d.balanced) {
     // App. C "Balanced Assignment": the nearest-centroid assignment bucketed by (block, cluster), then the rows
@@ -1363,7 +1375,7 @@ bool shared_launches(const MuseDims& d) {
   const int S = 64 / (d.D * (int)sizeof(T) / 16);
   const long long longer = d.D * (long long)sizeof(T) / 128, pairs = (long long)d.B * d.N * (d.Hq * d.Cq + d.Hkv * d.Ck);
   return !d.streaming && !d.balanced && pairs * longer * longer <= 4 << 20 && scan_update(d.B * d.Hq, d.N, d.Cq, S) &&
-         scan_update(d.B * d.Hkv, d.N, d.Ck, S) && (sizeof(T) == 4 || ClusterLaunch<T>::resident_bytes(std::max(d.Cq, d.Ck), d.D) <= 160 * 1024);
+         scan_update(d.B * d.Hkv, d.N, d.Ck, S) && (sizeof(T) == 4 || ClusterLaunch<T, true>::resident_bytes(std::max(d.Cq, d.Ck), d.D) <= 160 * 1024);
 }
 
 template <typename T>
@@ -1371,7 +1383,7 @@ int cluster_impl(const MuseDims& d, const MuseClusterSide* sides, int n) {
   ClusterRun<T> a(d, sides[0]), b(d, sides[n - 1]);
   ClusterRun<T>* run[2] = {&a, &b};
   if (n == 2 && a.st == b.st && shared_launches<T>(d)) {
-    ClusterLaunch<T> both(a, sides[0].init_idx, &b, sides[1].init_idx);
+    ClusterLaunch<T, true> both(a, sides[0].init_idx, &b, sides[1].init_idx);
     if (int rc = both.init(a.heads * a.C + b.heads * b.C)) return rc;
     for (int it = 0; it <= a.T_; ++it) {
       if (int rc = both.assign()) return rc;
@@ -1383,7 +1395,7 @@ int cluster_impl(const MuseDims& d, const MuseClusterSide* sides, int n) {
   for (int i = 0; i < n; ++i) {
     if (int rc = run[i]->stream(sides[i].init_idx, sides[i].trace, sides[i].counts)) return rc;
     if (!run[i]->assign) continue;  // the streaming pass alone
-    ClusterLaunch<T> own(*run[i], d.streaming ? nullptr : sides[i].init_idx, nullptr, nullptr);
+    ClusterLaunch<T, false> own(*run[i], d.streaming ? nullptr : sides[i].init_idx, nullptr, nullptr);
     if (int rc = own.init(run[i]->heads * run[i]->C)) return rc;
   }
   if (!a.assign) return MUSE_OK;
