@@ -132,24 +132,25 @@ int muse_launch_attn_bwd(const MuseDims& d, int Bs, const void* Q, const void* K
 }
 
 int muse_launch_casts(const CastRanges& c, int dst_dtype, float mul, hipStream_t st) {
+  CastRanges wide;
   size_t most = 0;
-  bool whole = dst_dtype == MUSE_DTYPE_BF16;
   for (int r = 0; r < c.n; ++r) {
-    most = std::max(most, c.r[r].n);
-    whole = whole && ((uintptr_t)c.r[r].src & 15) == 0 && ((uintptr_t)c.r[r].dst & 15) == 0 && c.r[r].n % 8 == 0;
-  }
-  if (most == 0) return MUSE_OK;
-  if (whole) {
-    MuseProf prof_("k_cast", st);
-    hipLaunchKernelGGL(k_cast8, dim3((unsigned)std::min<size_t>((most / 8 + 255) / 256, 1 << 20)), dim3(256), 0, st, c, mul);
-  } else {
-    for (int r = 0; r < c.n; ++r) {
-      const size_t n = c.r[r].n, blocks = std::min<size_t>((n + 1023) / 1024, 65535 * 16);
-      if (blocks == 0) continue;
-      MuseProf prof_("k_cast", st);
-      if (dst_dtype == MUSE_DTYPE_BF16) hipLaunchKernelGGL(k_cast<bf16_t>, dim3((unsigned)blocks), dim3(256), 0, st, c.r[r].src, (bf16_t*)c.r[r].dst, n, mul);
-      else hipLaunchKernelGGL(k_cast<float>, dim3((unsigned)blocks), dim3(256), 0, st, c.r[r].src, (float*)c.r[r].dst, n, mul);
+    const float* src = c.r[r].src;
+    void* dst = c.r[r].dst;
+    const size_t n = c.r[r].n, blocks = std::min<size_t>((n + 1023) / 1024, 65535 * 16);
+    if (n == 0) continue;
+    if (dst_dtype == MUSE_DTYPE_BF16 && (((uintptr_t)src | (uintptr_t)dst) & 15) == 0 && n % 8 == 0) {
+      wide.add(src, dst, n);
+      most = std::max(most, n);
+      continue;
     }
+    MuseProf prof_("k_cast", st);
+    if (dst_dtype == MUSE_DTYPE_BF16) hipLaunchKernelGGL(k_cast<bf16_t>, dim3((unsigned)blocks), dim3(256), 0, st, src, (bf16_t*)dst, n, mul);
+    else hipLaunchKernelGGL(k_cast<float>, dim3((unsigned)blocks), dim3(256), 0, st, src, (float*)dst, n, mul);
+  }
+  if (most > 0) {
+    MuseProf prof_("k_cast", st);
+    hipLaunchKernelGGL(k_cast8, dim3((unsigned)std::min<size_t>((most / 8 + 255) / 256, 1 << 20)), dim3(256), 0, st, wide, mul);
   }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;

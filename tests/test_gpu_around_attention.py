@@ -58,6 +58,24 @@ def test_row_sums_and_casts(N, H, D, dtype):
     assert (got[0][0].cpu().double() - want).abs().max() <= bound
 
 
+@pytest.mark.parametrize("odd,launches", [((), 1), ((2,), 2), ((0, 1), 3), ((0, 1, 2), 3)])
+def test_one_gradient_off_the_boundary(odd, launches):
+    # it goes through the narrow kernel alone: the others keep the wide one, in one launch
+    g = torch.Generator().manual_seed(7)
+    p = mb.Params(B=1, Hq=2, Hkv=2, N=130, D=64, grad_dtype=mb.BF16)
+    Q, K, V, dO = (torch.randn(1, 2, 130, 64, generator=g).bfloat16().cuda() for _ in range(4))
+    O, LSE = mb.exact_attn_fwd(p, Q, K, V)
+    want = mb.exact_attn_bwd(p, Q, K, V, O, LSE, dO)
+    out = tuple(_offset(torch.zeros_like(x)) if i in odd else torch.zeros_like(x) for i, x in enumerate(want))
+    mb.muse_profile_enable(True)
+    try:
+        mb.exact_attn_bwd(p, Q, K, V, O, LSE, dO, out=out)
+        assert mb.muse_profile_report()["k_cast"][0] == launches
+    finally:
+        mb.muse_profile_enable(False)
+    assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
 @pytest.mark.parametrize("D,N", [(64, 1100), (128, 1100), (64, 300)])
 @pytest.mark.parametrize("on", [("dO", None, None), (None, "K", "V"), ("Q", "K", "V"), ("O", "V", "K"), ("dO half", None, None)])
 def test_bf16_gradients_on_the_inputs(on, D, N):
