@@ -862,23 +862,16 @@ int launch(const MuseDims& d, const T* Q, const T* dO, const float* qc, const fl
     // (few query clusters with few chains share theirs: us one / shared 143 / 45 at 2 heads of 8k, D = 128, 16 x 16, 115 / 37 at one of 16k, 8 x 16)
     const bool one = share <= 8 && (long long)share * d.Cq * d.B * d.Hq >= 2048;
     const int S = one ? std::min(64, (d.Ck + 1) / 2) : std::max(share, std::min(16, (d.Ck + 7) / 8));
-    // They lie where the backward of bf16 inputs reads nothing: the chains over the forward's state (264 bytes per query or more; r
-    // <= 32 chains of 8 bytes for those of all blocks but the first, an end and a head per cluster), the lists over the
-    // maxima and sums behind the retrieval's rows (8 bytes per query and slot or more).
-    const size_t HQ = (size_t)d.B * d.Hq, slots = (size_t)d.r * d.k2e;
-    uint2* chains = reinterpret_cast<uint2*>(w.ff_acc);
-    int2* head_of = reinterpret_cast<int2*>(chains + HQ * ((size_t)(d.N - d.Bs) * d.r + d.Cq));
-    uint2* lists = reinterpret_cast<uint2*>(w.ret_part + HQ * d.N * slots * d.D);
     // waves: most where there are few clusters, else one for 64 of a cluster's queries or two for 256
     const int nw = (long long)d.Cq * d.B * d.Hq <= 512 ? kListWaves : d.N / d.Cq > 256 ? 8 : 4;
     const size_t lds = (size_t)(nw + 1) * d.Ck * 4;
-    looked = head_of;
+    looked = w.head_of;
     const int bits = std::max(5, 32 - __builtin_clz(d.Ck - 1 | 1));
     static_assert(MUSE_MAX_CLUSTERS <= 1 << 11, "bits of a cluster's number");
     auto sort = [&](auto* kernel) -> int {
       if (lds > 64 * 1024) MUSE_HIP_CHECK(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (kListWaves + 1) * MUSE_MAX_CLUSTERS * 4));
       MuseProf prof_("k_chain_lists", st);
-      hipLaunchKernelGGL(kernel, dim3(d.Cq, hn), dim3(64 * nw), lds, st, w.perm_q, w.off_q, LSE, w.delta, w.slotinfo, chains, lists, head_of, h0, d.N, d.Bs, d.nb,
+      hipLaunchKernelGGL(kernel, dim3(d.Cq, hn), dim3(64 * nw), lds, st, w.perm_q, w.off_q, LSE, w.delta, w.slotinfo, w.chains, w.lists, w.head_of, h0, d.N, d.Bs, d.nb,
                          d.Cq, d.Ck, d.r);
       MUSE_LAUNCH_CHECK();
       return MUSE_OK;
@@ -898,7 +891,7 @@ int launch(const MuseDims& d, const T* Q, const T* dO, const float* qc, const fl
     // without the lists the next kernel must not run
     if (const int rc = d.r % 4 == 0 ? sort_v(std::true_type()) : sort_v(std::false_type())) return rc;
     auto go = [&](auto* kernel) { MuseProf prof_("k_chain_grads", st); hipLaunchKernelGGL(kernel, dim3((unsigned)(cq8 * S), hn), dim3(one ? 64 : 256), 0, st, Q, dO, qc, w.s_mu,
-                       w.s_k, (const T*)w.s_v, LSE, w.delta, chains, lists, head_of, w.g_s_c, (T*)w.g_s_k, (T*)w.g_s_v, h0, d.N, d.Bs, d.nb, d.Cq, d.Ck,
+                       w.s_k, (const T*)w.s_v, LSE, w.delta, w.chains, w.lists, w.head_of, w.g_s_c, (T*)w.g_s_k, (T*)w.g_s_v, h0, d.N, d.Bs, d.nb, d.Cq, d.Ck,
                        d.r, S, share, d.scale); };
     if (d.nb <= 9) one ? go(k_chain_grads<D, 2, 1>) : go(k_chain_grads<D, 2, 4>);
     else one ? go(k_chain_grads<D, 1, 1>) : go(k_chain_grads<D, 1, 4>);

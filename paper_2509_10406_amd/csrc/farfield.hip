@@ -1249,6 +1249,9 @@ int muse_ff_carve(const MuseDims& d, bool bwd, void* ws, size_t ws_bytes, FFWork
   w->ff_ml = w->ff_acc + HQ * N * D;
   w->run_cap = ff_run_cap(d);
   w->run_map = nullptr; w->ret_part = nullptr;
+  w->chains = (uint2*)w->ff_acc;
+  w->head_of = (int2*)(w->chains + ff_chains(d));
+  w->lists = nullptr;
   {
     size_t R2 = (size_t)(d.r > 0 ? d.r : 1) * d.k2e;
     if (ff_has_index(d, bwd)) {
@@ -1265,6 +1268,7 @@ int muse_ff_carve(const MuseDims& d, bool bwd, void* ws, size_t ws_bytes, FFWork
     if (es == 2) {
       w->run_map = (int4*)take(HK * w->run_cap * 16);
       w->ret_part = (float*)take(ff_ret_part_bytes(d));
+      w->lists = (uint2*)((char*)w->ret_part + ff_ret_rows_bytes(d));
     }
   }
   if (bwd) {

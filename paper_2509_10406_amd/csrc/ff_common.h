@@ -198,8 +198,16 @@ __host__ __device__ inline int c3_slices(int nhits, C3Cut cut) {
 // bytes of the far-field state of all queries, of the retrieval's partial rows per (query, slot), and of the partial
 // dK | dV rows of one hit slice
 static inline size_t ff_state_bytes(const MuseDims& d) { return (size_t)d.B * d.Hq * d.N * (d.D + 2) * 4; }
+// The chain gradients' lists (backward, bf16 inputs) lie where that backward reads nothing.  Over the far-field state: the chains, r at most
+// per query behind the first block and an end per query cluster, and a head per query cluster.  Over the maxima and sums behind the
+// retrieval's partial rows: the entries, r per query.
+static inline size_t ff_chains(const MuseDims& d) { return (size_t)d.B * d.Hq * ((size_t)(d.N - d.Bs) * d.r + d.Cq); }
+static inline size_t ff_chain_bytes(const MuseDims& d) { return (ff_chains(d) + (size_t)d.B * d.Hq * d.Cq) * 8; }
+static inline size_t ff_chain_list_bytes(const MuseDims& d) { return (size_t)d.B * d.Hq * d.N * d.r * 8; }
+static inline size_t ff_ret_rows_bytes(const MuseDims& d) { return (size_t)d.B * d.Hq * d.N * (d.r > 0 ? d.r : 1) * d.k2e * d.D * 4; }
 static inline size_t ff_ret_part_bytes(const MuseDims& d) {
-  return (size_t)d.B * d.Hq * d.N * (d.r > 0 ? d.r : 1) * d.k2e * (d.D + 2) * 4;
+  const size_t ml = ff_ret_rows_bytes(d) / d.D * 2;
+  return ff_ret_rows_bytes(d) + (ml > ff_chain_list_bytes(d) ? ml : ff_chain_list_bytes(d));
 }
 static inline size_t ff_c3_slice_bytes(const MuseDims& d) { return (size_t)d.B * d.Hkv * d.N * 2 * d.D * 4; }
 // Tiles per slice.  A further slice costs a partial row of dK and dV per key of the pair, written and read again (16 D bytes;
@@ -235,6 +243,8 @@ struct FFWorkspace {
   uint2* hits;                   // x = n | g << 22 (query position, head inside the KV group), y = slot*k2e + u
   size_t hit_cap;                // hits per kv head
   float* ret_part;               // bf16 inputs, per (query, slot, u): forward partial rows [D], then (max, sum) [2] of all rows; or dq partial rows [D]
+  uint2 *chains, *lists;         // lists of the chain gradients, bf16 inputs: in ff_acc and behind the rows of ret_part
+  int2* head_of;                 // [HQ][Cq]: in ff_acc
   float *dKs, *dVs;            // fp32 gradients in bucketed key order
   float* c3_part;              // r > 0: [slices - 1][HK][N][2][D] partial dK | dV rows of the later hit slices of a pair (fp32: over ff_acc)
   float *dQacc, *dKacc, *dVacc;  // fp32 gradients in sequence order (alias the outputs when they are fp32)
@@ -277,10 +287,11 @@ static inline size_t ff_run_cap(const MuseDims& d) {
 }
 // the forward of fp32 inputs reads the retrieved keys per query, without the inverse index
 static inline bool ff_has_index(const MuseDims& d, bool bwd) { return bwd || d.dtype == MUSE_DTYPE_BF16; }
-// bytes of the far-field state and, for fp32 inputs, of the slices' partial rows in the same place
+// bytes of the far-field state and of what the backward keeps in the same place: the slices' partial rows (fp32 inputs) or the chains
 static inline size_t ff_acc_bytes(const MuseDims& d, bool bwd) {
   const size_t a = ff_state_bytes(d), c3 = (ff_c3_cut(d).most - 1) * ff_c3_slice_bytes(d);
-  return bwd && d.dtype == MUSE_DTYPE_FP32 && d.r > 0 && d.nb > 1 && c3 > a ? c3 : a;
+  const size_t later = d.dtype == MUSE_DTYPE_FP32 ? c3 : ff_chain_bytes(d);
+  return bwd && d.r > 0 && d.nb > 1 && later > a ? later : a;
 }
 // bytes of the segment counters of the inverse index
 static inline size_t ff_segcnt_bytes(const MuseDims& d) {
