@@ -1,7 +1,7 @@
 """GPU parity of the backward of bf16 inputs where the lists behind component 2 of the cell gradients (k_chain_lists, k_chain_grads)
 change their form: one, several and no whole 64 queries per wave, slots loaded four at a time and one by one, numbers of
 clusters of 5 to 11 bits, one-wave workgroups that loop over a cluster's chains, waves that share a chain.  Tolerances are those
-of the parity suite.  And two calls on one kept state, whose first writes the lists over the forward's."""
+of the parity suite.  And several backwards on one kept state, the first of which writes the lists over the forward's."""
 import dataclasses
 
 import pytest
@@ -39,6 +39,26 @@ def test_chain_lists(name, monkeypatch):
 
 
 def test_backward_twice_on_one_state():
+    w = small("cfg2", N=1024, Hq=2, Hkv=1, Cq=8, Ck=32, r=3, block=128, kmeans_iters=1)
+    d = generate(w, need_dO=True)
+    p = dataclasses.replace(mb.params_for(w), flags=mb.FLAG_KEEP_FWD_STATE)
+    qc, aq, ak = (torch.tensor(x).cuda() for x in base.oracle_clustering(w, d, p))
+    Q, K, V, dO = (base.dev(d[x], p) for x in ("Q", "K", "V", "dO"))
+    ws = torch.empty(mb.muse_workspace_bytes(p, mb.WS_BWD)[1], dtype=torch.uint8, device="cuda")
+
+    def backward(p, fwd, ws):
+        O, LSE, selc, selb = fwd
+        return mb.muse_bwd(p, Q, K, V, O, LSE, dO, qc, aq, ak, selc, selb, ws=ws)
+
+    fwd = mb.muse_fwd(p, Q, K, V, qc, aq, ak, ws=ws)
+    grads = [backward(p, fwd, ws) for _ in range(3)]
+    # and without a state
+    grads.append(backward(dataclasses.replace(p, flags=0), fwd, torch.empty_like(ws)))
+    for got in grads[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got, grads[0]))
+
+
+def test_forward_and_backward_again_in_one_workspace():
     w = small("cfg2", N=1024, Hq=2, Hkv=1, Cq=8, Ck=32, r=3, block=128, kmeans_iters=1)
     d = generate(w, need_dO=True)
     p = dataclasses.replace(mb.params_for(w), flags=mb.FLAG_KEEP_FWD_STATE)
