@@ -31,7 +31,7 @@ def regs(text):
 
 class Ins:
     def __init__(self, op, args, asm):
-        self.op, self.asm = op, asm
+        self.op, self.args, self.asm = op, args, asm
         parts = args.split(", ")
         self.first, self.rest = regs(parts[0]), [regs(p) for p in parts[1:]]
         self.all = self.first.union(*self.rest)
