@@ -847,23 +847,26 @@ int launch(const MuseDims& d, const T* Q, const T* dO, const float* qc, const fl
   if constexpr (sizeof(T) == 2) {
     // The waves of a workgroup share a group of chains where a query cluster has no more groups than `share`, with which the grid
     // would just fill the device (it decides the order of the sums: it is taken from all heads of the call, not from the heads of this
-    // chunk, so that the bits do not depend on the size of the workspace), or with which every group of a cluster has a workgroup.
-    // us with half as many at most / with it, where there are few query clusters:
+    // chunk, so that the bits do not depend on the size of the workspace).  A quarter of the key clusters is enough, but where that leaves a
+    // quarter of the device idle, every group may have a workgroup.  us without / with that, where there are few query clusters:
     //   1 head of 64k, 16 x 128       241 / 133     1 of 16k, D = 128, 4 x 256, r = 16   140 / 91     1 of 16k, 8 x 128   36 / 24
     //   1 of 4.6k, D = 128, 3 x 56     90 / 51      2 of 16k, 4 x 64                      90 / 53     1 of 8k, 4 x 256    30 / 22
+    // and 26 / 32 for 4 heads of 8.5k with 15 x 112, which fill it without.
     const int groups = d.nb <= 9 ? (d.Ck + 1) / 2 : d.Ck;
+    const long long clusters = (long long)d.Cq * d.B * d.Hq;
     int share = 1;
-    while (share < groups && (long long)share * d.Cq * d.B * d.Hq < 2048) share *= 2;
+    while (share < (d.Ck + 3) / 4 && share * clusters < 2048) share *= 2;
+    while (share < groups && share * clusters < 1536) share *= 2;
     // With enough query clusters a workgroup is one wave, up to 64 of them per cluster: a place is free again as soon as its wave
     // has ended.  us with 1, 4, 16, 64 such workgroups / 1, 4, 16 of four waves:
     //   16 heads of 64k, 256 x 1024   1841, 1080, 916, 891 / 1132, 1002, 1034       12 of 6k, 23 x 71   365, 133, 85, 86 / 136, 93, 90
     //   16 heads of 64k, 128 x 128    1210, 652, 502, 481 / 673, 606, 651           8 of 16k, 64 x 256  479, 175, 86, 77 / 170, 90, 85
     //   32 of 32k, D = 128, 128 x 512 4136, 3437, 3332, 3339 / 3478, 3529, 3700     1 of 16k, 16 x 1024 1308, 368, 128, 59 / 611, 169, 67, shared 34
     // (few query clusters with few chains share theirs: us one / shared 143 / 45 at 2 heads of 8k, D = 128, 16 x 16, 115 / 37 at one of 16k, 8 x 16)
-    const bool one = share <= 8 && (long long)share * d.Cq * d.B * d.Hq >= 2048;
+    const bool one = share <= 8 && share * clusters >= 1536;
     const int S = one ? std::min(64, (d.Ck + 1) / 2) : std::max(share, std::min(16, (d.Ck + 7) / 8));
     // waves: most where there are few clusters, else one for 64 of a cluster's queries or two for 256
-    const int nw = (long long)d.Cq * d.B * d.Hq <= 512 ? kListWaves : d.N / d.Cq > 256 ? 8 : 4;
+    const int nw = clusters <= 512 ? kListWaves : d.N / d.Cq > 256 ? 8 : 4;
     const size_t lds = (size_t)(nw + 1) * d.Ck * 4;
     looked = w.head_of;
     const int bits = std::max(5, 32 - __builtin_clz(d.Ck - 1 | 1));
