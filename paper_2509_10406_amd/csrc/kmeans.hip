@@ -1361,6 +1361,23 @@ int ClusterRun<T>::iteration(int it) {
   return MUSE_OK;
 }
 
+// us of an assignment and of an update by scan, H heads with C clusters: fits of some 8000 launches (to 2 us for most), for the rule below.
+template <typename T>
+double assign_us(const MuseDims& d, int H, double C) {
+  auto up = [](int a, int b) { return (a + b - 1) / b; };
+  if constexpr (sizeof(T) == 2) {  // batches of rows, by one workgroup per CU
+    const int batches = up(d.N, d.D == 64 ? 512 : 256), gx = std::min(batches, up(256, H)), rounds = up(batches, gx) * up(gx * H, 256);
+    const double tiles = up((int)C, 64);
+    return 2.5 + tiles + (rounds - 1) * (3.5 + 3 * tiles);
+  } else {  // four workgroups of 64 rows per CU
+    return (d.D == 64 ? 2 + 0.09 * C : 6.6 + 0.29 * C) * std::max(1.0, up(d.N, 64) * (double)H / 1024);
+  }
+}
+template <typename T>
+double update_us(const MuseDims& d, int H, int C) {
+  return d.D * (double)sizeof(T) / 128 * (1 + 3e-4 * d.N + 4.2e-3 * d.N / C + 1e-6 * H * C * d.N);
+}
+
 // Queries and keys in the same launches, on one stream: small problems, whose launches (3.4 us of the host each, and two streams to
 // fork and join: 45 us) cost more than their work.  On two streams one side's update runs beside the other's assignment, which
 // tells where an iteration has something to do: the line is drawn at 4 M (row, cluster) pairs of 128-byte rows, the square of
@@ -1370,12 +1387,23 @@ int ClusterRun<T>::iteration(int it) {
 //   bf16, D = 128   8+2 x 4k, 16 x 32  227 / 216   8+2 x 8k, 32 x 64  345 / 363
 //   fp32, D = 64    1+1 x 2k, 16 x 32  207 / 152   1+1 x 8k, 32 x 64  218 / 201   4+4 x 4k, 16 x 64  218 / 235   4+4 x 8k, 32 x 128  348 / 394
 //   fp32, D = 128   1+1 x 2k, 8 x 16   329 / 309   4+4 x 4k, 16 x 32  390 / 407
+// Below it, shared launches take the longer assignment and the longer update one behind the other; where one side has few clusters of many
+// rows (a long update) and the other many (a long assignment), or both together are more than a round of workgroups, two streams are faster:
+//   bf16, D = 64    56+14 x 1.8k, 7 x 32  232 / 334    24+6 x 15k, 9 x 2  537 / 737   20+10 x 5.6k, 5 x 10  235 / 314
+//   fp32, D = 64    3+3 x 3.2k, 2 x 105   269 / 347    1+1 x 7.1k, 99 x 3  282 / 353
+// Of 3670 sizes below the line 120 were more than 5 % slower shared; with the estimate 29 are, and 9 that gain more than that are not shared.
 template <typename T>
 bool shared_launches(const MuseDims& d) {
-  const int S = 64 / (d.D * (int)sizeof(T) / 16);
-  const long long longer = d.D * (long long)sizeof(T) / 128, pairs = (long long)d.B * d.N * (d.Hq * d.Cq + d.Hkv * d.Ck);
-  return !d.streaming && !d.balanced && pairs * longer * longer <= 4 << 20 && scan_update(d.B * d.Hq, d.N, d.Cq, S) &&
-         scan_update(d.B * d.Hkv, d.N, d.Ck, S) && (sizeof(T) == 4 || ClusterLaunch<T, true>::resident_bytes(std::max(d.Cq, d.Ck), d.D) <= 160 * 1024);
+  const int S = 64 / (d.D * (int)sizeof(T) / 16), hq = d.B * d.Hq, hk = d.B * d.Hkv;
+  const long long longer = d.D * (long long)sizeof(T) / 128, pairs = (long long)d.N * ((long long)hq * d.Cq + (long long)hk * d.Ck);
+  if (d.streaming || d.balanced || pairs * longer * longer > 4 << 20 || !scan_update(hq, d.N, d.Cq, S) || !scan_update(hk, d.N, d.Ck, S)) return false;
+  const int most = std::max(d.Cq, d.Ck);
+  if (sizeof(T) == 2 && ClusterLaunch<T, true>::resident_bytes(most, d.D) > 160 * 1024) return false;
+  const double aq = assign_us<T>(d, hq, d.Cq), ak = assign_us<T>(d, hk, d.Ck), uq = update_us<T>(d, hq, d.Cq), uk = update_us<T>(d, hk, d.Ck);
+  const double both = sizeof(T) == 2 ? assign_us<T>(d, hq + hk, most)
+                                     : std::max({aq, ak, assign_us<T>(d, hq + hk, ((double)hq * d.Cq + (double)hk * d.Ck) / (hq + hk))});
+  const double shared = both + std::max(uq, uk) + 8.6, two = std::max(18.0, std::max(aq + uq, ak + uk) + 7);  // with the gaps between launches
+  return (d.T + 0.5) * (shared - two) <= 40;  // the fork and the join
 }
 
 template <typename T>

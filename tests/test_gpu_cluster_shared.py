@@ -26,6 +26,28 @@ def test_shared_launches(dtype, B, Hq, Hkv, N, D, Cq, Ck, iters):
     assert int(qa.min()) >= 0 and int(qa.max()) < Cq and int(ka.min()) >= 0 and int(ka.max()) < Ck
 
 
+@pytest.mark.parametrize("shared,dtype,Hq,Hkv,N,Cq,Ck", [
+    (True, mb.BF16, 2, 2, 2048, 8, 16), (True, mb.FP32, 1, 1, 2048, 16, 32),
+    # more than a round of workgroups together, a long update beside a long assignment: 30 to 44 % slower in shared launches
+    (False, mb.BF16, 56, 14, 1824, 7, 32), (False, mb.BF16, 24, 6, 15064, 9, 2), (False, mb.FP32, 3, 3, 3248, 2, 105),
+    (False, mb.BF16, 16, 16, 4096, 16, 64)])  # too many pairs
+def test_which_problems_share(shared, dtype, Hq, Hkv, N, Cq, Ck):
+    g = torch.Generator(device="cuda").manual_seed(4)
+    p = mb.Params(B=1, Hq=Hq, Hkv=Hkv, N=N, D=64, Cq=Cq, Ck=Ck, r=1, k2=1, kmeans_iters=10, dtype=dtype)
+    Q, K = (torch.randn(1, H, N, 64, generator=g, device="cuda").to(p.torch_dtype) for H in (Hq, Hkv))
+    qi, ki = (torch.rand(1, H, N, generator=g, device="cuda").argsort(-1)[..., :C].to(torch.int32).contiguous() for H, C in ((Hq, Cq), (Hkv, Ck)))
+    mb.muse_profile_enable(True)
+    try:
+        out = mb.muse_cluster(p, Q, K, qi, ki)
+        launches = mb.muse_profile_report()["k_assign_bf16" if dtype == mb.BF16 else "k_assign_f32"][0]
+    finally:
+        mb.muse_profile_enable(False)
+    assert launches == (11 if shared else 22)
+    assert all(torch.equal(a, b) for a, b in zip(out, mb.muse_cluster(p, Q, K, qi, ki)))
+    one = mb.muse_cluster(p, Q, None, qi, None)[:2] + mb.muse_cluster(p, None, K, None, ki)[2:]
+    assert all(torch.equal(a, b) for a, b in zip(out, one))
+
+
 @pytest.mark.parametrize("offset", [0, 1, 2])
 def test_outputs_at_any_word(offset):
     """Selections and bf16 gradients that begin between 16-byte boundaries, and end between them, surrounded by words that stay."""
