@@ -424,11 +424,11 @@ int muse_launch_attn_bwd_f32(const MuseDims& d, int Bs, const float* Q, const fl
   const unsigned tiles = (unsigned)((d.N + 63) / 64) * d.B;
   const dim3 gq(tiles * d.Hq), gk(tiles * d.Hkv);
   if (d.D == 64) {
-    if (dQ) { MuseProf prof_("k_attn_bwd_dq_f32", st); hipLaunchKernelGGL((k_attn_bwd_dq_f32<64>), gq, dim3(256), 0, st, Q, K, V, dO, LSE, delta, dQ, d.N, Bs, d.Hq, d.Hkv, d.scale); }
-    if (dK) { MuseProf prof_("k_attn_bwd_dkv_f32", st); hipLaunchKernelGGL((k_attn_bwd_dkv_f32<64>), gk, dim3(256), 0, st, Q, K, V, dO, LSE, delta, dK, dV, d.N, Bs, d.Hq, d.Hkv, d.scale); }
+    { MuseProf prof_("k_attn_bwd_dq_f32", st); hipLaunchKernelGGL((k_attn_bwd_dq_f32<64>), gq, dim3(256), 0, st, Q, K, V, dO, LSE, delta, dQ, d.N, Bs, d.Hq, d.Hkv, d.scale); }
+    { MuseProf prof_("k_attn_bwd_dkv_f32", st); hipLaunchKernelGGL((k_attn_bwd_dkv_f32<64>), gk, dim3(256), 0, st, Q, K, V, dO, LSE, delta, dK, dV, d.N, Bs, d.Hq, d.Hkv, d.scale); }
   } else {
-    if (dQ) { MuseProf prof_("k_attn_bwd_dq_f32", st); hipLaunchKernelGGL((k_attn_bwd_dq_f32<128>), gq, dim3(256), 0, st, Q, K, V, dO, LSE, delta, dQ, d.N, Bs, d.Hq, d.Hkv, d.scale); }
-    if (dK) { MuseProf prof_("k_attn_bwd_dkv_f32", st); hipLaunchKernelGGL((k_attn_bwd_dkv_f32<128>), gk, dim3(256), 0, st, Q, K, V, dO, LSE, delta, dK, dV, d.N, Bs, d.Hq, d.Hkv, d.scale); }
+    { MuseProf prof_("k_attn_bwd_dq_f32", st); hipLaunchKernelGGL((k_attn_bwd_dq_f32<128>), gq, dim3(256), 0, st, Q, K, V, dO, LSE, delta, dQ, d.N, Bs, d.Hq, d.Hkv, d.scale); }
+    { MuseProf prof_("k_attn_bwd_dkv_f32", st); hipLaunchKernelGGL((k_attn_bwd_dkv_f32<128>), gk, dim3(256), 0, st, Q, K, V, dO, LSE, delta, dK, dV, d.N, Bs, d.Hq, d.Hkv, d.scale); }
   }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;

@@ -560,7 +560,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 // rows per load instruction, and serves the row operands of T and, through transposed reads, the contractions over i.
 // Bound by the gradient rows, D x 2 bytes each at a stride of Ck rows.  Row operands read straight from memory touched 32 rows
 // with every instruction, centroids and rows were transposed with 2-byte stores: 3.10 ms at 16 heads of 64k with 256 x 1024
-// clusters (9.2 GB) against 2.29, 2.77 against 1.86 at 32 heads of 32k, D = 128, 128 x 512 clusters.  Three waves per SIMD at
+// clusters (9.2 GB) against 2.29, 2.77 against 1.86 at 32 heads of 32k, D = 128, 128 x 512 clusters (since the rows are added to the block
+// diagonal's here, which saves passes of their own, 2.36 and 1.95).  Three waves per SIMD at
 // D = 64, and a second tile in flight, spill (4.6 and 3.2 ms).
 // ------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_qc_rows(const float* __restrict__ qc, bf16_t* __restrict__ qcb, int D, int Cq, int CqP,
@@ -576,8 +577,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
                                                           const bf16_t* __restrict__ qcb, const float* __restrict__ L,
                                                           const float* __restrict__ s_mu, const float* __restrict__ G_c,
                                                           const bf16_t* __restrict__ G_k, const bf16_t* __restrict__ G_v,
-                                                          const int32_t* __restrict__ off_k, const int32_t* __restrict__ perm_k, const float* __restrict__ dKs,
-                                                          const float* __restrict__ dVs, float* __restrict__ dK, float* __restrict__ dV, int h0, int N, int nb, int Cq, int CqP,
+                                                          const int32_t* __restrict__ off_k, const int32_t* __restrict__ perm_k, float* __restrict__ dKs,
+                                                          float* __restrict__ dVs, float* __restrict__ dK, float* __restrict__ dV, int h0, int N, int nb, int Cq, int CqP,
                                                           int Ck, int Hq, int Hkv, int frozen) {
   constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, NIT = 32 * CPR / 64;
   __shared__ __attribute__((aligned(16))) bf16_t gks[32 * D];
@@ -685,19 +686,24 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
       }
     }
     if (mvalid) {
-      // with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order)
-      const size_t to = ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D, from = ((size_t)hk * N + pm) * D;
+      // with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order), or to the former alone
+      const size_t from = ((size_t)hk * N + pm) * D, to = dK ? ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D : from;
+      float *ok_ = dK ? dK + to : dKs + from, *ov_ = dK ? dV + to : dVs + from;
 #pragma unroll
       for (int t = 0; t < DT; ++t)
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg) {
           const int d = 32 * t + 8 * gg + 4 * half;
-          const float4 a = *reinterpret_cast<const float4*>(dKs + from + d), c = *reinterpret_cast<const float4*>(dVs + from + d);
-          float4 k = *reinterpret_cast<float4*>(dK + to + d), v = *reinterpret_cast<float4*>(dV + to + d);
+          float4 k = *reinterpret_cast<float4*>(ok_ + d), v_ = *reinterpret_cast<float4*>(ov_ + d);
+          float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
+          if (dK) {
+            a = *reinterpret_cast<const float4*>(dKs + from + d);
+            c = *reinterpret_cast<const float4*>(dVs + from + d);
+          }
           k.x += a.x + dk[t][4 * gg]; k.y += a.y + dk[t][4 * gg + 1]; k.z += a.z + dk[t][4 * gg + 2]; k.w += a.w + dk[t][4 * gg + 3];
-          v.x += c.x + dv[t][4 * gg]; v.y += c.y + dv[t][4 * gg + 1]; v.z += c.z + dv[t][4 * gg + 2]; v.w += c.w + dv[t][4 * gg + 3];
-          *reinterpret_cast<float4*>(dK + to + d) = k;
-          *reinterpret_cast<float4*>(dV + to + d) = v;
+          v_.x += c.x + dv[t][4 * gg]; v_.y += c.y + dv[t][4 * gg + 1]; v_.z += c.z + dv[t][4 * gg + 2]; v_.w += c.w + dv[t][4 * gg + 3];
+          *reinterpret_cast<float4*>(ok_ + d) = k;
+          *reinterpret_cast<float4*>(ov_ + d) = v_;
         }
     }
   }
@@ -707,7 +713,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 
 int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* Vs, const float* qc, void* qcb,
                                  const float* L, const float* s_mu, const float* G_c, const void* G_k, const void* G_v,
-                                 const int32_t* off_k, const int32_t* perm_k, const float* dKs, const float* dVs, float* dK, float* dV, int h0, int hn,
+                                 const int32_t* off_k, const int32_t* perm_k, float* dKs, float* dVs, float* dK, float* dV, int h0, int hn,
                                  hipStream_t st) {
   const int CqP = (d.Cq + 31) / 32 * 32;
   // qcb holds the scaled centroids of the chunk's heads [h0, h0 + hn)
@@ -737,16 +743,15 @@ int muse_launch_attn_bwd_mfma(const MuseDims& d, int Bs, const void* Q, const vo
   float sl = d.scale * 1.4426950408889634f;
   const bf16_t *q = (const bf16_t*)Q, *k = (const bf16_t*)K, *v = (const bf16_t*)V, *g = (const bf16_t*)dO;
   const bool to_lds = muse_attn_rows_to_lds(Q, K, V, dO);
-  if (!dQacc) {
-  } else if (to_lds && muse_attn_dq_wide(d, Bs)) {
+  if (to_lds && muse_attn_dq_wide(d, Bs)) {
     if (int rc = muse_launch_attn_dq_wide(d, Bs, Q, K, V, dO, LSE, delta, dQacc, st)) return rc;
   } else {
     MuseProf prof_("k_flash_bwd_dq", st);
     if (d.D == 64) hipLaunchKernelGGL(k_flash_bwd_dq<64>, gq, dim3(256), 0, st, q, k, v, g, LSE, delta, dQacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl);
     else hipLaunchKernelGGL(k_flash_bwd_dq<128>, gq, dim3(256), 0, st, q, k, v, g, LSE, delta, dQacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl);
   }
-  if (dKacc && to_lds && muse_attn_dkv_wide(d, Bs)) return muse_launch_attn_dkv_wide(d, Bs, Q, K, V, dO, LSE, delta, dKacc, dVacc, st);
-  if (dKacc) {
+  if (to_lds && muse_attn_dkv_wide(d, Bs)) return muse_launch_attn_dkv_wide(d, Bs, Q, K, V, dO, LSE, delta, dKacc, dVacc, st);
+  {
     MuseProf prof_("k_flash_bwd_dkv", st);
     if (d.D == 64) hipLaunchKernelGGL(k_flash_bwd_dkv_p<64>, gk, dim3(256), 0, st, q, k, v, g, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl);
     else hipLaunchKernelGGL(k_flash_bwd_dkv128, gk, dim3(512), 0, st, q, k, v, g, LSE, delta, dKacc, dVacc, d.N, Bs, d.Hq, d.Hkv, d.B, d.scale, sl);

@@ -680,8 +680,8 @@ __global__ void __launch_bounds__(64) k_cells_to_keys(const T* __restrict__ Ks, 
                                                        const float* __restrict__ qc, const float* __restrict__ L,
                                                        const float* __restrict__ s_mu, const float* __restrict__ G_c,
                                                        const float* __restrict__ G_k, const float* __restrict__ G_v,
-                                                       const int32_t* __restrict__ off_k, const int32_t* __restrict__ perm_k, const float* __restrict__ dKs,
-                                                       const float* __restrict__ dVs, float* __restrict__ dK, float* __restrict__ dV, int h0, int N, int nb, int Cq, int Ck,
+                                                       const int32_t* __restrict__ off_k, const int32_t* __restrict__ perm_k, float* __restrict__ dKs,
+                                                       float* __restrict__ dVs, float* __restrict__ dK, float* __restrict__ dV, int h0, int N, int nb, int Cq, int Ck,
                                                        int Hq, int Hkv, float scale, int frozen) {
   constexpr int U = D / 8, DT = D / 32;
   const int G_ = Hq / Hkv;
@@ -747,30 +747,51 @@ __global__ void __launch_bounds__(64) k_cells_to_keys(const T* __restrict__ Ks, 
       }
     }
     if (mvalid) {
-      // with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order)
-      const size_t to = ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D, from = ((size_t)hk * N + pm) * D;
+      // with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order), or to the former alone
+      const size_t from = ((size_t)hk * N + pm) * D, to = dK ? ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D : from;
+      float *ok_ = dK ? dK + to : dKs + from, *ov_ = dK ? dV + to : dVs + from;
 #pragma unroll
       for (int x = 0; x < DT; ++x)
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg) {
           const int d = 32 * x + 8 * gg + 4 * half;
-          const float4 a = *reinterpret_cast<const float4*>(dKs + from + d), c = *reinterpret_cast<const float4*>(dVs + from + d);
-          float4 k = *reinterpret_cast<float4*>(dK + to + d), v = *reinterpret_cast<float4*>(dV + to + d);
+          float4 k = *reinterpret_cast<float4*>(ok_ + d), v_ = *reinterpret_cast<float4*>(ov_ + d);
+          float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
+          if (dK) {
+            a = *reinterpret_cast<const float4*>(dKs + from + d);
+            c = *reinterpret_cast<const float4*>(dVs + from + d);
+          }
           k.x += a.x + dk[x][4 * gg]; k.y += a.y + dk[x][4 * gg + 1]; k.z += a.z + dk[x][4 * gg + 2]; k.w += a.w + dk[x][4 * gg + 3];
-          v.x += c.x + dv[x][4 * gg]; v.y += c.y + dv[x][4 * gg + 1]; v.z += c.z + dv[x][4 * gg + 2]; v.w += c.w + dv[x][4 * gg + 3];
-          *reinterpret_cast<float4*>(dK + to + d) = k;
-          *reinterpret_cast<float4*>(dV + to + d) = v;
+          v_.x += c.x + dv[x][4 * gg]; v_.y += c.y + dv[x][4 * gg + 1]; v_.z += c.z + dv[x][4 * gg + 2]; v_.w += c.w + dv[x][4 * gg + 3];
+          *reinterpret_cast<float4*>(ok_ + d) = k;
+          *reinterpret_cast<float4*>(ov_ + d) = v_;
         }
     }
   }
 }
 
+// Keys' and values' far-field rows (bucketed) of all blocks but the last, which has none, added to the block diagonal's (in the sequence's order)
+__global__ void __launch_bounds__(256) k_scatter_rows(const float* __restrict__ dKs, const float* __restrict__ dVs, const int32_t* __restrict__ perm,
+                                                       float* __restrict__ dK, float* __restrict__ dV, int N, int rows, int D) {
+  const float* src = blockIdx.z ? dVs : dKs;
+  float* dst = blockIdx.z ? dV : dK;
+  const int CPR = D / 4;
+  const size_t h = blockIdx.y, c = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (c >= (size_t)rows * CPR) return;
+  const int p = (int)(c / CPR), cc = (int)(c % CPR);
+  float4* o = reinterpret_cast<float4*>(dst + (h * N + perm[h * N + p]) * D) + cc;
+  const float4 a = reinterpret_cast<const float4*>(src + (h * N + p) * D)[cc];
+  float4 v = *o;
+  v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+  *o = v;
+}
+
 template <typename T, int D>
 int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, const int32_t* aq, const float* LSE,
-                  FFWorkspace& w, int h0, int hn, hipStream_t sq_, hipStream_t sk_, hipStream_t sdiag, hipEvent_t diag) {
+                  FFWorkspace& w, int h0, int hn, hipStream_t sq_, hipStream_t sk_, hipStream_t sdiag, hipEvent_t diag, bool apart) {
   // the far-field part of dQ goes to stream sq_, the cell gradients and what they give to keys and values to
   // stream sk_: the two share inputs only.  Either adds its last kernel's results to what the block-diagonal kernels left, which run on
-  // stream sdiag and, as far as another stream adds to them, have ended at the event diag.
+  // stream sdiag and have ended at the event diag (apart: the keys' and values' stay bucketed, for k_scatter_rows).
   auto behind_diagonal = [&](hipStream_t s) { return s == sdiag ? hipSuccess : hipStreamWaitEvent(s, diag, 0); };
   const int NBm = d.nb - 1;
   const int W = (d.Ck + 31) / 32;
@@ -806,32 +827,31 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
     if (rc2) return rc2;
   }
   const int G_ = d.Hq / d.Hkv;
-  MUSE_HIP_CHECK(behind_diagonal(st));
+  if (!apart) MUSE_HIP_CHECK(behind_diagonal(st));
+  float *dK = apart ? nullptr : w.dKacc, *dV = apart ? nullptr : w.dVacc;
   if (sizeof(T) == 2) {
-    int rc2 = muse_launch_cells_to_keys_mx(d, w.Ks, w.Vs, qc, w.qcb, w.L, w.s_mu, w.g_s_c, w.g_s_k, w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs,
-                                           w.dKacc, w.dVacc, h0, hn, st);
+    int rc2 = muse_launch_cells_to_keys_mx(d, w.Ks, w.Vs, qc, w.qcb, w.L, w.s_mu, w.g_s_c, w.g_s_k, w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs, dK, dV, h0,
+                                           hn, st);
     if (rc2) return rc2;
   } else
   { MuseProf prof_("k_cells_to_keys", st); hipLaunchKernelGGL((k_cells_to_keys<T, D>), dim3(d.Ck, NBm, hn / G_), dim3(64), 0, st, (const T*)w.Ks, (const T*)w.Vs,
-                     qc, w.L, w.s_mu, w.g_s_c, (const float*)w.g_s_k, (const float*)w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs, w.dKacc, w.dVacc, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq,
+                     qc, w.L, w.s_mu, w.g_s_c, (const float*)w.g_s_k, (const float*)w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs, dK, dV, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq,
                      d.Hkv, d.scale, d.frozen_weights ? 1 : 0); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }
 
-// Whether the block diagonal takes so much longer than the far field up to k_cells_to_keys*, which waits for it, that dK and dV are made
-// first and that kernel does not wait for dQ as well.  A query's multiply-adds over its block (fp32 ones take several times as long, and dK, dV more
-// where their tiles of 64 keys leave CUs idle) against the key clusters and the selected chains' blocks that it meets.
-// Backward, us, dQ first / dK, dV first (and with far-field gradients added by launches behind both streams):
-//   2 heads of 3.5k, 2 blocks, r = 0, 3 x 9  192 / 169 (171)      4 of 32k, r = 8, 64 x 64            899 / 929 (976)
-//   8 of 32k, 2 blocks, r = 4, 64 x 64      2352 / 2229 (2350)    16 (4) of 64k, r = 4, 128 x 128    6579 / 6828 (6933)
-//   8 (2) of 32k, 4 blocks, r = 4, 64 x 128 1656 / 1523 (1709)    16 of 64k, r = 8, 128 x 128        8652 / 8725 (9068)
-//   fp32, 2 of 5k, 16 blocks, r = 0          309 / 255 (273)      8 (2) of 16k, D = 128, r = 8       1220 / 1259 (1285)
-//   fp32, 8 of 8k, 2 blocks, r = 8          2469 / 2411 (2416)    8 of 16k, r = 0, 64 x 256           520 / 529 (555)
-//   fp32, 8 (1) of 9.5k, D = 128, r = 8     5120 / 4902 (4986)    fp32, 4 of 8k, r = 8, 32 x 128      817 / 824 (818)
-bool diagonal_is_longer(const MuseDims& d) {
-  const double idle = std::max(1.0, 256.0 * 64 / ((double)d.B * d.Hkv * d.N));
-  return d.Bs * (d.dtype == MUSE_DTYPE_BF16 ? 1.0 : 16.0) * (3 + 4 * idle) / 7 >= 32.0 * d.Ck + 320.0 * d.r * (d.nb - 1);
+// Whether k_cells_to_keys_mx adds to the block diagonal's gradients itself: it waits for them then, and each of its waves reads and writes two
+// more rows a key.  That saves a pass over dK and dV, and pays where its waves fill the device and the rows are many (to 5 % of the backward
+// where there is no retrieval, 1 % else); a few long waves lose what runs beside the block diagonal, up to 40 %.  Backward, us, added here / by
+// k_scatter_rows behind both streams (1169 sizes: here 2 % slower on average, and slower than scattering every tensor by itself in 143):
+//   16 heads of 6.6k, r = 0, 17 x 227          379 / 401        16 of 23k, r = 2, 39 x 81      1546 / 1570     16 of 24k, r = 8, 11 x 169  2261 / 2290
+//   8 of 19k, r = 16, 72 x 330                1831 / 1859       32 (16) of 13k, r = 8, 12 x 239 2521 / 2531
+//   fewer waves: 2 heads of 63k, r = 0, 58 x 15  871 / 695      64 (16) of 7k, r = 0, 244 x 8  2199 / 1943     8 of 26k, r = 1, 32 x 16      943 / 927
+//   fp32: 8 of 30k, D = 128, r = 0, 10 x 788   15790 / 15421    2 of 38k, r = 1, 16 x 238      2500 / 2481     8 of 19k, 222 x 66, r = 1     4797 / 4820
+bool keys_add_here(const MuseDims& d) {
+  const size_t keys = (size_t)d.B * d.Hkv * (d.N - d.Bs);
+  return d.dtype == MUSE_DTYPE_BF16 && (size_t)d.B * d.Hkv * (d.nb - 1) * d.Ck >= 4096 && keys * 2 * d.D * 4 >= 64 << 20;
 }
 
 template <typename T>
@@ -845,7 +865,7 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
   if (!reuse && (rc = muse_ff_prepare<T>(d, K, V, aq, ak, w, st))) return rc;
   if ((rc = muse_launch_delta(d, O, dO, w.delta, st))) return rc;
   // the block-diagonal backward (matrix-core bound) runs beside the far field (memory bound) on a second
-  // stream; it writes the accumulators, to which the far field's last kernels add
+  // stream; it writes the accumulators, to which the far field's last kernels add, or k_scatter_rows behind both
   MuseAux& ax = muse_aux_stream();
   const bool two = ax.state == 1 && !muse_profiling();
   hipStream_t sb = two ? ax.s : st;
@@ -861,16 +881,11 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
     MUSE_HIP_CHECK(hipStreamWaitEvent(sb, ax.fork, 0));
     guard.armed = true;
   }
+  if ((rc = muse_launch_attn_bwd(d, d.Bs, Q, K, V, dO, LSE, w.delta, w.dQacc, w.dKacc, w.dVacc, sb))) return rc;
   // With all heads in one chunk the far-field part of dQ follows on the second stream (it needs the selection
-  // info and the inverse index, which the first stream builds: event `mid`), beside the cell gradients.  The first stream then needs only
-  // dK and dV of the block diagonal.
-  const bool split = two && w.hc >= HQ, kv_first = split && diagonal_is_longer(d);
-  if (kv_first) {
-    if ((rc = muse_launch_attn_bwd(d, d.Bs, Q, K, V, dO, LSE, w.delta, nullptr, w.dKacc, w.dVacc, sb))) return rc;
-    MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));
-  }
-  if ((rc = muse_launch_attn_bwd(d, d.Bs, Q, K, V, dO, LSE, w.delta, w.dQacc, kv_first ? nullptr : w.dKacc, kv_first ? nullptr : w.dVacc, sb))) return rc;
-  if (two && !kv_first) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));
+  // info and the inverse index, which the first stream builds: event `mid`), beside the cell gradients.
+  const bool split = two && w.hc >= HQ, apart = !keys_add_here(d);
+  if (two) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));  // the block-diagonal gradients are there
   {
     FillRanges f;
     f.add(w.dKs, nk * D, 0);
@@ -914,14 +929,21 @@ int run_bwd_typed(const MuseDims& d, const T* Q, const T* K, const T* V, const T
         MUSE_HIP_CHECK(hipEventRecord(ax.mid, st));
         MUSE_HIP_CHECK(hipStreamWaitEvent(sb, ax.mid, 0));
       }
-      if (D == 64) rc = run_bwd_chunk<T, 64>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st, sb, ax.join);
-      else rc = run_bwd_chunk<T, 128>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st, sb, ax.join);
+      if (D == 64) rc = run_bwd_chunk<T, 64>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st, sb, ax.join, apart);
+      else rc = run_bwd_chunk<T, 128>(d, Q, dO, qc, aq, LSE, w, h0, hn, split ? sb : st, st, sb, ax.join, apart);
       if (rc) return rc;
     }
   }
   if (split) MUSE_HIP_CHECK(hipEventRecord(ax.join, sb));
   if (two) MUSE_HIP_CHECK(hipStreamWaitEvent(st, ax.join, 0));
   guard.armed = false;
+  if (apart && d.nb > 1) {
+    MuseProf prof_("k_scatter_rows", st);
+    const int rows = N - d.Bs;
+    hipLaunchKernelGGL(k_scatter_rows, dim3((unsigned)(((size_t)rows * (D / 4) + 255) / 256), HK, 2), dim3(256), 0, st, w.dKs, w.dVs, w.perm_k, w.dKacc,
+                       w.dVacc, N, rows, D);
+    MUSE_LAUNCH_CHECK();
+  }
   if (d.grad_dtype != MUSE_DTYPE_FP32) {
     CastRanges c;
     c.add(w.dQacc, dQ, nq * D);

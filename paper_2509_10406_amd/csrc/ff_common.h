@@ -248,7 +248,7 @@ struct FFWorkspace {
   float *dKs, *dVs;            // fp32 gradients in bucketed key order
   float* c3_part;              // r > 0: [slices - 1][HK][N][2][D] partial dK | dV rows of the later hit slices of a pair (fp32: over ff_acc)
   float *dQacc, *dKacc, *dVacc;  // fp32 gradients in sequence order (alias the outputs when they are fp32)
-  float* dQff;                   // far-field part of dQ, added to dQacc once the block-diagonal backward has finished
+  float* dQff;                   // r > 0: component 1's part of dQ, which k_comp2_bwd_dq adds to dQacc with its own (r = 0: k_ff_bwd_dq adds it, unused)
   void* qcb;                     // bf16 [hc][Cq padded to 32][D]: scaled query centroids of a head chunk
   // per chunk of `hc` query heads
   float* L;
@@ -377,7 +377,7 @@ int muse_launch_ret_bwd_dq_pairs(const MuseDims& d, const void* Q, const void* d
 // attn_mfma.hip
 int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* Vs, const float* qc, void* qcb,
                                  const float* L, const float* s_mu, const float* G_c, const void* G_k, const void* G_v,
-                                 const int32_t* off_k, const int32_t* perm_k, const float* dKs, const float* dVs, float* dK, float* dV, int h0, int hn,
+                                 const int32_t* off_k, const int32_t* perm_k, float* dKs, float* dVs, float* dK, float* dV, int h0, int hn,
                                  hipStream_t st);
 // dipole.hip: dipole correction of the monopole-only mode (App. B), forward
 template <typename T>
