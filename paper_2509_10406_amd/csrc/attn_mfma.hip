@@ -572,7 +572,7 @@ __global__ void __launch_bounds__(256) k_qc_rows(const float* __restrict__ qc, b
   qcb[(size_t)h * D * CqP + t] = f32_to_bf16_bits(t / D < Cq ? scale * qc[(size_t)h * Cq * D + t] : 0.f);
 }
 
-template <int D>
+template <int D, bool HERE>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, D == 64 ? 2 : 1))) k_cells_to_keys_mx(const bf16_t* __restrict__ Ks, const bf16_t* __restrict__ Vs,
                                                           const bf16_t* __restrict__ qcb, const float* __restrict__ L,
                                                           const float* __restrict__ s_mu, const float* __restrict__ G_c,
@@ -686,25 +686,37 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
       }
     }
     if (mvalid) {
-      // with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order), or to the former alone
-      const size_t from = ((size_t)hk * N + pm) * D, to = dK ? ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D : from;
-      float *ok_ = dK ? dK + to : dKs + from, *ov_ = dK ? dV + to : dVs + from;
+      // HERE: with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order); else to the former (the two are bodies
+      // of their own: one for both made the former 5 to 20 % slower)
+      const size_t from = ((size_t)hk * N + pm) * D;
+      if constexpr (HERE) {
+        const size_t to = ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D;
+        const float *fk = dKs, *fv = dVs;
 #pragma unroll
-      for (int t = 0; t < DT; ++t)
+        for (int t = 0; t < DT; ++t)
 #pragma unroll
-        for (int gg = 0; gg < 4; ++gg) {
-          const int d = 32 * t + 8 * gg + 4 * half;
-          float4 k = *reinterpret_cast<float4*>(ok_ + d), v_ = *reinterpret_cast<float4*>(ov_ + d);
-          float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
-          if (dK) {
-            a = *reinterpret_cast<const float4*>(dKs + from + d);
-            c = *reinterpret_cast<const float4*>(dVs + from + d);
+          for (int gg = 0; gg < 4; ++gg) {
+            const int d = 32 * t + 8 * gg + 4 * half;
+            const float4 a = *reinterpret_cast<const float4*>(fk + from + d), c = *reinterpret_cast<const float4*>(fv + from + d);
+            float4 k = *reinterpret_cast<float4*>(dK + to + d), v = *reinterpret_cast<float4*>(dV + to + d);
+            k.x += a.x + dk[t][4 * gg]; k.y += a.y + dk[t][4 * gg + 1]; k.z += a.z + dk[t][4 * gg + 2]; k.w += a.w + dk[t][4 * gg + 3];
+            v.x += c.x + dv[t][4 * gg]; v.y += c.y + dv[t][4 * gg + 1]; v.z += c.z + dv[t][4 * gg + 2]; v.w += c.w + dv[t][4 * gg + 3];
+            *reinterpret_cast<float4*>(dK + to + d) = k;
+            *reinterpret_cast<float4*>(dV + to + d) = v;
           }
-          k.x += a.x + dk[t][4 * gg]; k.y += a.y + dk[t][4 * gg + 1]; k.z += a.z + dk[t][4 * gg + 2]; k.w += a.w + dk[t][4 * gg + 3];
-          v_.x += c.x + dv[t][4 * gg]; v_.y += c.y + dv[t][4 * gg + 1]; v_.z += c.z + dv[t][4 * gg + 2]; v_.w += c.w + dv[t][4 * gg + 3];
-          *reinterpret_cast<float4*>(ok_ + d) = k;
-          *reinterpret_cast<float4*>(ov_ + d) = v_;
-        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < DT; ++t)
+#pragma unroll
+          for (int gg = 0; gg < 4; ++gg) {
+            const int d = 32 * t + 8 * gg + 4 * half;
+            float4 a = *reinterpret_cast<float4*>(dKs + from + d), c = *reinterpret_cast<float4*>(dVs + from + d);
+            a.x += dk[t][4 * gg]; a.y += dk[t][4 * gg + 1]; a.z += dk[t][4 * gg + 2]; a.w += dk[t][4 * gg + 3];
+            c.x += dv[t][4 * gg]; c.y += dv[t][4 * gg + 1]; c.z += dv[t][4 * gg + 2]; c.w += dv[t][4 * gg + 3];
+            *reinterpret_cast<float4*>(dKs + from + d) = a;
+            *reinterpret_cast<float4*>(dVs + from + d) = c;
+          }
+      }
     }
   }
 }
@@ -719,10 +731,13 @@ int muse_launch_cells_to_keys_mx(const MuseDims& d, const void* Ks, const void* 
   // qcb holds the scaled centroids of the chunk's heads [h0, h0 + hn)
   { MuseProf prof_("k_qc_rows", st); hipLaunchKernelGGL(k_qc_rows, dim3((d.D * CqP + 255) / 256, hn), dim3(256), 0, st, qc + (size_t)h0 * d.Cq * d.D, (bf16_t*)qcb, d.D, d.Cq, CqP, d.scale); }
   dim3 g((d.Ck + 7) / 8 * 8, d.nb - 1, hn / (d.Hq / d.Hkv));
-  if (d.D == 64)
-    { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<64>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcb, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, perm_k, dKs, dVs, dK, dV, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
-  else
-    { MuseProf prof_("k_cells_to_keys_mx", st); hipLaunchKernelGGL(k_cells_to_keys_mx<128>, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcb, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v, off_k, perm_k, dKs, dVs, dK, dV, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0); }
+  auto go = [&](auto* kernel) {
+    MuseProf prof_("k_cells_to_keys_mx", st);
+    hipLaunchKernelGGL(kernel, g, dim3(64), 0, st, (const bf16_t*)Ks, (const bf16_t*)Vs, (const bf16_t*)qcb, L, s_mu, G_c, (const bf16_t*)G_k, (const bf16_t*)G_v,
+                       off_k, perm_k, dKs, dVs, dK, dV, h0, d.N, d.nb, d.Cq, CqP, d.Ck, d.Hq, d.Hkv, d.frozen_weights ? 1 : 0);
+  };
+  if (d.D == 64) dK ? go(k_cells_to_keys_mx<64, true>) : go(k_cells_to_keys_mx<64, false>);
+  else dK ? go(k_cells_to_keys_mx<128, true>) : go(k_cells_to_keys_mx<128, false>);
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
 }

@@ -680,8 +680,8 @@ __global__ void __launch_bounds__(64) k_cells_to_keys(const T* __restrict__ Ks, 
                                                        const float* __restrict__ qc, const float* __restrict__ L,
                                                        const float* __restrict__ s_mu, const float* __restrict__ G_c,
                                                        const float* __restrict__ G_k, const float* __restrict__ G_v,
-                                                       const int32_t* __restrict__ off_k, const int32_t* __restrict__ perm_k, float* __restrict__ dKs,
-                                                       float* __restrict__ dVs, float* __restrict__ dK, float* __restrict__ dV, int h0, int N, int nb, int Cq, int Ck,
+                                                       const int32_t* __restrict__ off_k, float* __restrict__ dKs,
+                                                       float* __restrict__ dVs, int h0, int N, int nb, int Cq, int Ck,
                                                        int Hq, int Hkv, float scale, int frozen) {
   constexpr int U = D / 8, DT = D / 32;
   const int G_ = Hq / Hkv;
@@ -747,24 +747,17 @@ __global__ void __launch_bounds__(64) k_cells_to_keys(const T* __restrict__ Ks, 
       }
     }
     if (mvalid) {
-      // with the retrieval's rows (bucketed) to the block diagonal's (in the sequence's order), or to the former alone
-      const size_t from = ((size_t)hk * N + pm) * D, to = dK ? ((size_t)hk * N + perm_k[(size_t)hk * N + pm]) * D : from;
-      float *ok_ = dK ? dK + to : dKs + from, *ov_ = dK ? dV + to : dVs + from;
+      float *ok_ = dKs + ((size_t)hk * N + pm) * D, *ov_ = dVs + ((size_t)hk * N + pm) * D;
 #pragma unroll
       for (int x = 0; x < DT; ++x)
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg) {
           const int d = 32 * x + 8 * gg + 4 * half;
-          float4 k = *reinterpret_cast<float4*>(ok_ + d), v_ = *reinterpret_cast<float4*>(ov_ + d);
-          float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
-          if (dK) {
-            a = *reinterpret_cast<const float4*>(dKs + from + d);
-            c = *reinterpret_cast<const float4*>(dVs + from + d);
-          }
-          k.x += a.x + dk[x][4 * gg]; k.y += a.y + dk[x][4 * gg + 1]; k.z += a.z + dk[x][4 * gg + 2]; k.w += a.w + dk[x][4 * gg + 3];
-          v_.x += c.x + dv[x][4 * gg]; v_.y += c.y + dv[x][4 * gg + 1]; v_.z += c.z + dv[x][4 * gg + 2]; v_.w += c.w + dv[x][4 * gg + 3];
-          *reinterpret_cast<float4*>(ok_ + d) = k;
-          *reinterpret_cast<float4*>(ov_ + d) = v_;
+          float4 a = *reinterpret_cast<float4*>(ok_ + d), c = *reinterpret_cast<float4*>(ov_ + d);
+          a.x += dk[x][4 * gg]; a.y += dk[x][4 * gg + 1]; a.z += dk[x][4 * gg + 2]; a.w += dk[x][4 * gg + 3];
+          c.x += dv[x][4 * gg]; c.y += dv[x][4 * gg + 1]; c.z += dv[x][4 * gg + 2]; c.w += dv[x][4 * gg + 3];
+          *reinterpret_cast<float4*>(ok_ + d) = a;
+          *reinterpret_cast<float4*>(ov_ + d) = c;
         }
     }
   }
@@ -828,14 +821,13 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
   }
   const int G_ = d.Hq / d.Hkv;
   if (!apart) MUSE_HIP_CHECK(behind_diagonal(st));
-  float *dK = apart ? nullptr : w.dKacc, *dV = apart ? nullptr : w.dVacc;
   if (sizeof(T) == 2) {
-    int rc2 = muse_launch_cells_to_keys_mx(d, w.Ks, w.Vs, qc, w.qcb, w.L, w.s_mu, w.g_s_c, w.g_s_k, w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs, dK, dV, h0,
+    int rc2 = muse_launch_cells_to_keys_mx(d, w.Ks, w.Vs, qc, w.qcb, w.L, w.s_mu, w.g_s_c, w.g_s_k, w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs, apart ? nullptr : w.dKacc, apart ? nullptr : w.dVacc, h0,
                                            hn, st);
     if (rc2) return rc2;
   } else
   { MuseProf prof_("k_cells_to_keys", st); hipLaunchKernelGGL((k_cells_to_keys<T, D>), dim3(d.Ck, NBm, hn / G_), dim3(64), 0, st, (const T*)w.Ks, (const T*)w.Vs,
-                     qc, w.L, w.s_mu, w.g_s_c, (const float*)w.g_s_k, (const float*)w.g_s_v, w.off_k, w.perm_k, w.dKs, w.dVs, dK, dV, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq,
+                     qc, w.L, w.s_mu, w.g_s_c, (const float*)w.g_s_k, (const float*)w.g_s_v, w.off_k, w.dKs, w.dVs, h0, d.N, d.nb, d.Cq, d.Ck, d.Hq,
                      d.Hkv, d.scale, d.frozen_weights ? 1 : 0); }
   MUSE_LAUNCH_CHECK();
   return MUSE_OK;
@@ -851,7 +843,7 @@ int run_bwd_chunk(const MuseDims& d, const T* Q, const T* dO, const float* qc, c
 //   fp32: 8 of 30k, D = 128, r = 0, 10 x 788   15790 / 15421    2 of 38k, r = 1, 16 x 238      2500 / 2481     8 of 19k, 222 x 66, r = 1     4797 / 4820
 bool keys_add_here(const MuseDims& d) {
   const size_t keys = (size_t)d.B * d.Hkv * (d.N - d.Bs);
-  return d.dtype == MUSE_DTYPE_BF16 && (size_t)d.B * d.Hkv * (d.nb - 1) * d.Ck >= 4096 && keys * 2 * d.D * 4 >= 64 << 20;
+  return d.dtype == MUSE_DTYPE_BF16 && (size_t)d.B * d.Hkv * (d.nb - 1) * d.Ck >= 4096 && keys * 2 * d.D * 4 >= 48 << 20;
 }
 
 template <typename T>
