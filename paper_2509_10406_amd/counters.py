@@ -30,7 +30,7 @@ per-query and per-chain kernels), from
            SQ_ACTIVE_INST_VALU SQ_INSTS_VMEM_WR
     run B: SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_WAIT_INST_LDS SQ_ACTIVE_INST_ANY SQ_INSTS_VMEM_RD SQ_INSTS_SALU
            SQ_ACTIVE_INST_VMEM SQ_WAVES
-    (--kernel-include-regex 'k_summaries|k_farfield|k_block_summaries|k_comp2|k_chain_grads|k_cells_to_keys_mx|k_ff_bwd|k_hit_|k_merge_ret|k_ret_|k_c3_pairs|k_update')
+    (--kernel-include-regex 'k_summaries|k_farfield|k_block_summaries|k_comp2|k_chain|k_cells_to_keys_mx|k_ff_bwd|k_hit_|k_merge_ret|k_ret_|k_c3_pairs|k_update')
     python -m paper_2509_10406_amd.counters DIR_A/a_counter_collection.csv DIR_B/b_counter_collection.csv \
         --mode vector --out profiles/vector_counters_cfg3.txt
 Columns of that mode (per launch averages):

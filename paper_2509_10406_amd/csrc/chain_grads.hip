@@ -500,7 +500,7 @@ __global__ void __launch_bounds__(64 * kListWaves) k_chain_lists(
   }
 }
 
-// S workgroups of 4 waves per (head, query cluster); a wave takes P chains at a time, and where there are fewer such groups than
+// S workgroups of one wave or four per (head, query cluster); a wave takes P chains at a time, and where there are fewer such groups than
 // waves, the waves of a workgroup share a group.  All rows (s_k, the cells' gradients, the queries') come and go whole, through LDS.
 template <int D, int P, int NW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, D == 64 ? 3 : 2))) k_chain_grads(
@@ -749,7 +749,8 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 // The queries that k_chain_grads keeps out, one by one: a workgroup per (head, query cluster) looks through the cluster's LSE
 // and delta, and its waves share the chains of a query that is not finite (a chain has one wave: a cell one owner).  A kernel
 // of its own, because the registers for it cost k_chain_grads 11 % (16 heads of 64k tokens, 256 x 1024 clusters); where every
-// query is finite it takes 50 us there and 8 us at 12 heads of 6k with 23 x 71 clusters.
+// query is finite, it ends at the flag that the lists were left (bf16 inputs: 10 us there, 5 at 12 heads of 6k with 23 x 71 clusters) or reads LSE
+// and delta (fp32 inputs).
 constexpr int kOddWaves = 16;
 template <typename T, int D>
 __global__ void __launch_bounds__(64 * kOddWaves) k_chain_odd(
@@ -760,7 +761,7 @@ __global__ void __launch_bounds__(64 * kOddWaves) k_chain_odd(
   if (head_of && !(head_of[(size_t)(h0 + blockIdx.y) * Cq + blockIdx.x].x >> 16)) return;  // the lists were made without seeing one
   constexpr int Z = 4;  // queries per thread and round
   __shared__ unsigned long long odd[Z][kOddWaves];
-  __shared__ int cum[65], seg[64];  // as in k_chain_grads
+  __shared__ int cum[65], seg[64];  // as in k_chain_lists
   const int i = blockIdx.x, hl = blockIdx.y, hq = h0 + hl, NBm = nb - 1;
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
   const float* qci = qc + ((size_t)hq * Cq + i) * D;

@@ -66,11 +66,13 @@ __device__ __forceinline__ void lds_read() {
 //              scores are equal the places are given out one by one, lowest cluster first.
 //   softmax    over the others, against the maximum of all waves, and P V, the first value tiles on their way since the scores
 //              were made; the waves' sums meet in LDS.  A weight enters as two bf16 terms (16 bits and more): the largest of
-//              those that stay behind a selection would be what bf16 rounds worst.  The second term is free: the kernel waits for memory
-//              (layer at 16 heads of 64k 28523 us with one term, 28555 with two; at 32 heads of 32k, D = 128 41411 and 41318), and O is
-//              closer to its value in 64 bits (4096 tokens, 16 x 256 clusters, r = 8: 2.07e-3 and 2.01e-3 of the norm).
-// Bound by the summaries' way from memory: 12.7 GB at 16 heads of 64k with 256 x 1024 clusters, 4.9 TB/s; without the selection
-// (insertion and places) it takes 2577 us instead of 2614.  The kernel before this one was a wave per tile that read the bf16
+//              those that stay behind a selection would be what bf16 rounds worst.  The second term costs 3 % of the kernel (2608 -> 2689 us
+//              at 16 heads of 64k, 0.3 % of the layer; 2473 -> 2545 at 32 of 32k, D = 128), and O is closer to its value in 64 bits
+//              (4096 tokens, 16 x 256 clusters, r = 8: 2.07e-3 and 2.01e-3 of the norm).  With few query clusters the
+//              summaries come from the L2 and it is 7 % (16 heads of 46k, 9 x 771: 1027 -> 1096).
+// Bound by the summaries' way from memory: 12.2 GB fetched and written at 16 heads of 64k with 256 x 1024 clusters, 4.5 TB/s; without the
+// selection (insertion and places) it took 2577 us instead of 2614.  With six and eight tiles per wave most forms spill 2 to 7
+// vector registers, the one with six tiles and lists of 32 at D = 64 17.  (The times below are with weights of one term.)  The kernel before this one was a wave per tile that read the bf16
 // plane of k-bar for a bound of the scores and then everything (8 D + 8 bytes), left tiles with many candidates to a second launch, and
 // needed the largest key norm of every head.  us, before (with its second launch) / now: 3270 / 2614 there, 6550 / 4930 at 32
 // heads, 585 / 300 with 128 x 128, 139 / 102 at 8 heads of 16k with 64 x 256, 67 / 38 at 12 of 6k with 23 x 71, 4040 / 2745 at 32 of 32k

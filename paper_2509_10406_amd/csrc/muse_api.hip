@@ -236,8 +236,8 @@ int muse_cluster(const muse_params* p, const void* Q, const void* K, const int32
   char* w0 = (char*)ws + kTagBytes;
   // The two problems are independent chains of small launches: the keys go to the second stream (own half of the
   // workspace), the launches of the two are issued in turns, and only the end of the keys' chain is waited for.  With the
-  // wait queued before the queries' launches the chains ran one after the other (the layer with one fp32 head of 2k
-  // tokens: 651 -> 423 us; 8 heads of 16k: 2.47 -> 2.23 ms; the streaming pass of 16 heads of 32k: 10.6 -> 8.4 ms).
+  // wait queued before the queries' launches the chains ran one after the other (the layer with 8 heads of 16k: 2.47 -> 2.23 ms;
+  // the streaming pass of 16 heads of 32k: 10.6 -> 8.4 ms).
   // Problems small enough to share every launch (muse_cluster_shares_launches) stay on the caller's stream.
   MuseAux& ax = muse_aux_stream();
   const bool two = Q && K && ax.state == 1 && !muse_profiling() && !muse_cluster_shares_launches(d);
